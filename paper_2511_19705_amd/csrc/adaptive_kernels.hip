@@ -16,15 +16,13 @@
 //                      on the fly; chunk partials are written out, not atomically added.
 //   gram_pair16_kernel : the same pair for heads of 128 and 256 on the 16-bit matrix pipe, operands
 //                      split exactly into three bfloat16 parts.
-//   gj_panel_kernel  : sums the chunk partials of S in float64 and inverts it by register-
-//                      resident Gauss-Jordan elimination with partial pivoting; also serves
-//                      cafeq_block_inverse.  C = I - S^-1 R follows as a batched product.
+//   gj_panel_kernel  : (gj_panel.hpp) sums the chunk partials of S in float64 and inverts it by register-
+//                      resident Gauss-Jordan elimination.  C = I - S^-1 R follows as a batched product.
 //   gj_spd256_kernel : the inversion of S for heads of 256 as a block elimination whose products
 //                      run on the 16-bit matrix pipe.
 #include <atomic>
-#include <type_traits>
 
-#include "xform_core.hpp"
+#include "gj_panel.hpp"
 
 namespace cafeq {
 
@@ -442,349 +440,6 @@ __global__ void pqe_finish_kernel(const double* __restrict__ perq, int nq, float
   out[1] = float(den);
 }
 
-// Arguments of the Gauss-Jordan inversion kernel (one workgroup per block).
-struct GjArgs {
-  int mode, K, nz;
-  const float* T;        // matrix to invert when partial == nullptr
-  const float* partial;  // else [nb][nz][2][K][K]: chunk partials whose first matrix is summed and inverted
-  const double* sum64 = nullptr;  // optional with partial: that float64 sum, already formed, [nb][K][K]
-  const float* sum32 = nullptr;   // optional with sum64: the same sum rounded to float32 (gj_spd256_kernel reads this)
-  double* work;          // unused by the register-resident kernel
-  float* out;            // [nb][K][K]
-  float* rho_row; float* rho_col;  // optional squared row / column norms of the inverse
-  int* status; int status_stride, status_offset;
-  const int* need;       // optional [nb][need_n]: blocks whose entries are all 0 are already done (see
-  int need_n = 1;        // rotation_inverse_kernel, rotation_slice_kernel)
-};
-
-// Compile-time loop: f(integral_constant<int, I>) for I in [B, E).
-template <int B, int E>
-struct StaticFor {
-  template <typename F>
-  static __device__ __forceinline__ void run(F& f) {
-    f(std::integral_constant<int, B>{});
-    StaticFor<B + 1, E>::run(f);
-  }
-};
-template <int E>
-struct StaticFor<E, E> {
-  template <typename F>
-  static __device__ __forceinline__ void run(F&) {}
-};
-
-__device__ __forceinline__ uint32_t dpp_u32_max(uint32_t v, uint32_t o) { return v > o ? v : o; }
-// maximum over the wave, returned as a wave-uniform value: DPP inside each row of 16 lanes,
-// then the four row results are read back as scalars
-__device__ __forceinline__ uint32_t wave_allmax_u32(uint32_t v) {
-  v = dpp_u32_max(v, uint32_t(__builtin_amdgcn_update_dpp(0, int(v), 0xB1, 0xF, 0xF, true)));    // quad_perm [1,0,3,2]
-  v = dpp_u32_max(v, uint32_t(__builtin_amdgcn_update_dpp(0, int(v), 0x4E, 0xF, 0xF, true)));    // quad_perm [2,3,0,1]
-  v = dpp_u32_max(v, uint32_t(__builtin_amdgcn_update_dpp(0, int(v), 0x141, 0xF, 0xF, true)));   // row_half_mirror
-  v = dpp_u32_max(v, uint32_t(__builtin_amdgcn_update_dpp(0, int(v), 0x140, 0xF, 0xF, true)));   // row_mirror
-  const uint32_t a = uint32_t(__builtin_amdgcn_readlane(int(v), 0)), b = uint32_t(__builtin_amdgcn_readlane(int(v), 16));
-  const uint32_t c = uint32_t(__builtin_amdgcn_readlane(int(v), 32)), d = uint32_t(__builtin_amdgcn_readlane(int(v), 48));
-  return dpp_u32_max(dpp_u32_max(a, b), dpp_u32_max(c, d));
-}
-// value held by lane `src` (wave-uniform) of a per-lane variable
-__device__ __forceinline__ double read_lane(double x, int src) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(x), src);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(x), src);
-  return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ float read_lane(float x, int src) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), src));
-}
-
-// |x| as an unsigned key that orders like |x|: the leading 32 bits of the number without its sign
-__device__ __forceinline__ uint32_t mag_bits(double x) { return uint32_t(__double2hiint(x)) & 0x7FFFFFFFu; }
-__device__ __forceinline__ uint32_t mag_bits(float x) { return __float_as_uint(x) & 0x7FFFFFFFu; }
-
-__device__ __forceinline__ double fma_s(double a, double b, double c) { return __builtin_fma(a, b, c); }
-__device__ __forceinline__ float fma_s(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-
-// Register-resident in-place Gauss-Jordan inversion with partial pivoting, one workgroup per block.
-// Thread (rt, ct) of an NRT x NCT thread grid keeps the RT x CT elements (rt + i*NRT, ct + j*NCT)
-// in registers (both strides interleaved, so the LDS reads are either broadcasts or run over
-// consecutive addresses).  No physical row swaps: the pivot of column k is the largest entry among
-// the rows not yet used (PIV; for symmetric positive definite input, PIV == false, it is the diagonal
-// entry), and the pivot order is a permutation undone on output.  One elimination
-// step replaces column k by the unit vector e_p and adds multiples of row p / pivot to every row;
-// row p itself goes through the same update with the multiplier (1 - pivot), which loses accuracy
-// only for |pivot| >> 1, so the block is first scaled by a power of two to max |a_ij| in (1/2, 1].
-// The steps of NB = 8 columns (a panel) are taken by the first wave on the K x NB panel alone -- rows
-// in registers (lane l holds rows l, l + 64, ...), pivot search by DPP, pivot row through scalar lane
-// reads, no barriers -- and their combined effect on the other columns, the rank-NB update
-// R += C . X  (C: the panel after its steps minus the unit vectors of the pivot rows, X: the NB pivot
-// rows as they were before the panel), is applied by all threads at once: three barriers per panel.
-// A singular block keeps running (on infinities) and is zeroed at the end.
-//   A = T_b (float32) when partial == nullptr, else the float64 sum over nz chunk partials
-//   of S (first of the two K x K matrices of each partial).  out = A^-1 (zeros if singular).
-template <int K, int RT, int CT, typename S, bool PIV>
-__global__ __launch_bounds__((K / RT) * (K / CT)) void gj_panel_kernel(const GjArgs a) {
-  constexpr int NRT = K / RT, NCT = K / CT, NTHR = NRT * NCT, NWAVE = (NTHR + 63) / 64;
-  constexpr int NB = 8, NPH = NCT / NB, NRW = (K + 63) / 64;
-  static_assert(NCT % NB == 0, "panel width");
-  __shared__ __align__(16) S pan[2][K][NB];
-  __shared__ __align__(16) S xrow[2][NB][K];
-  __shared__ int pk[K], kinv[K];
-  __shared__ int pvt[2][NB];
-  __shared__ int deadflag;
-  __shared__ S wred[16];
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-  if (a.need) {                           // uniform over the workgroup
-    int any = 0;
-    for (int i = 0; i < a.need_n; ++i) any |= a.need[b * a.need_n + i];
-    if (!any) return;
-  }
-  const int rt = tid / NCT, ct = tid % NCT;
-  S reg[RT][CT];
-  if (a.partial == nullptr) {
-    const float* src = a.T + size_t(b) * K * K;
-#pragma unroll
-    for (int i = 0; i < RT; ++i)
-#pragma unroll
-      for (int j = 0; j < CT; ++j) reg[i][j] = S(src[(rt + i * NRT) * K + ct + j * NCT]);
-  } else if (a.sum64) {
-    // one workgroup reading nz partials of its block is a long serial prologue when the blocks are few:
-    // the float64 sum then comes from a kernel that spreads that work over the chip
-    const double* src = a.sum64 + size_t(b) * K * K;
-#pragma unroll
-    for (int i = 0; i < RT; ++i)
-#pragma unroll
-      for (int j = 0; j < CT; ++j) reg[i][j] = S(src[(rt + i * NRT) * K + ct + j * NCT]);
-  } else {
-    const float* src = a.partial + size_t(b) * a.nz * 2 * K * K;
-#pragma unroll
-    for (int i = 0; i < RT; ++i)
-#pragma unroll
-      for (int j = 0; j < CT; ++j) reg[i][j] = 0;
-    for (int z = 0; z < a.nz; ++z) {
-      // float64 accumulation; the float elimination (K = 256) rounds the sum once
-      double t[RT][CT];
-#pragma unroll
-      for (int i = 0; i < RT; ++i)
-#pragma unroll
-        for (int j = 0; j < CT; ++j) t[i][j] = double(src[size_t(z) * 2 * K * K + (rt + i * NRT) * K + ct + j * NCT]);
-#pragma unroll
-      for (int i = 0; i < RT; ++i)
-#pragma unroll
-        for (int j = 0; j < CT; ++j) reg[i][j] = S(double(reg[i][j]) + t[i][j]);
-    }
-  }
-  S anorm = 0;
-#pragma unroll
-  for (int i = 0; i < RT; ++i)
-#pragma unroll
-    for (int j = 0; j < CT; ++j) anorm = fmax(anorm, fabs(reg[i][j]));
-  for (int m = 1; m < 64; m <<= 1) anorm = fmax(anorm, __shfl_xor(anorm, m));
-  if (lane == 0) wred[tid >> 6] = anorm;
-  if (tid == 0) deadflag = 0;
-  __syncthreads();
-  anorm = 0;
-  for (int i = 0; i < NWAVE; ++i) anorm = fmax(anorm, wred[i]);
-  int ex = 0;
-  (void)frexp(double(anorm), &ex);
-  const S scale = S(ldexp(1.0, -ex));    // exact power of two; 1 if the block is all zero
-#pragma unroll
-  for (int i = 0; i < RT; ++i)
-#pragma unroll
-    for (int j = 0; j < CT; ++j) reg[i][j] *= scale;
-  const S tol = anorm * scale * S(a.partial ? 1e-5 : (sizeof(S) == 8 ? 1e-12 : 1e-6));
-  uint32_t usedbits = 0;   // first wave only: bit q = row lane + 64 q has been a pivot
-
-  auto panels = [&](auto jj_c) {
-    constexpr int jj = decltype(jj_c)::value;
-    for (int h = 0; h < NPH; ++h) {
-      const int buf = (jj * NPH + h) & 1;
-      const int q_own = ct - h * NB;
-      const bool owner = q_own >= 0 && q_own < NB;
-      if (owner) {
-#pragma unroll
-        for (int i = 0; i < RT; ++i) pan[buf][rt + i * NRT][q_own] = reg[i][jj];
-      }
-      __syncthreads();
-      if (tid < 64) {
-        S prow[NRW][NB];
-#pragma unroll
-        for (int q = 0; q < NRW; ++q) {
-          const int rr = lane + 64 * q;
-#pragma unroll
-          for (int c = 0; c < NB; ++c) prow[q][c] = rr < K ? pan[buf][rr < K ? rr : 0][c] : S(0);
-        }
-        int pivs[NB];
-        bool dd = false;
-#pragma unroll
-        for (int s = 0; s < NB; ++s) {
-          // pivot = (approximately) largest |entry| of the column among the unused rows: a 32-bit key
-          // (leading bits of the magnitude, low byte 255 - row: ties go to the lowest row) reduced by DPP
-          // (PIV == false, for symmetric positive definite input: the diagonal entry, no search)
-          S colv[NRW];
-          uint32_t key = 0x100u;
-#pragma unroll
-          for (int q = 0; q < NRW; ++q) colv[q] = prow[q][s];
-          int p = jj * NCT + h * NB + s;
-          if (PIV) {
-            key = 0;
-#pragma unroll
-            for (int q = 0; q < NRW; ++q) {
-              const int rr = lane + 64 * q;
-              const uint32_t kk_ = (rr >= K || ((usedbits >> q) & 1u)) ? 0u
-                                                                       : ((mag_bits(colv[q]) & 0xFFFFFF00u) | uint32_t(255 - rr));
-              key = key > kk_ ? key : kk_;
-            }
-            key = wave_allmax_u32(key);
-            p = (255 - int(key & 0xFFu)) & (K - 1);
-          }
-          const int pl = p & 63, pq = p >> 6;
-          S pv = read_lane(colv[0], pl);
-#pragma unroll
-          for (int q = 1; q < NRW; ++q) {
-            const S alt = read_lane(colv[q], pl);
-            pv = pq == q ? alt : pv;
-          }
-          dd = dd || (key >> 8) == 0 || !((PIV ? S(fabs(pv)) : pv) > tol);
-          // reciprocal of the pivot: hardware estimate (2^-22) + Newton steps to full precision
-          S ipiv = S(__builtin_amdgcn_rcpf(float(pv)));
-          ipiv = ipiv * (S(2) - pv * ipiv);
-          if (sizeof(S) == 8) ipiv = ipiv * (S(2) - pv * ipiv);
-          // row p of the panel, with the in-place 1 in the column of this step
-          S rowp[NB];
-#pragma unroll
-          for (int c = 0; c < NB; ++c) {
-            S mine = prow[0][c];
-#pragma unroll
-            for (int q = 1; q < NRW; ++q) mine = pq == q ? prow[q][c] : mine;
-            rowp[c] = c == s ? S(1) : read_lane(mine, pl);
-          }
-#pragma unroll
-          for (int q = 0; q < NRW; ++q) {
-            const bool isp = (lane + 64 * q) == p;
-            const S f = (isp ? S(1) - pv : -colv[q]) * ipiv;
-#pragma unroll
-            for (int c = 0; c < NB; ++c)
-              prow[q][c] = c == s ? (isp ? S(1) : S(0)) + f : fma_s(f, rowp[c], prow[q][c]);
-            usedbits |= uint32_t(isp) << q;
-          }
-          pivs[s] = p;
-        }
-        // hand over C = (panel after its steps) - (unit vectors of the pivot rows), and the pivots
-#pragma unroll
-        for (int q = 0; q < NRW; ++q) {
-          const int rr = lane + 64 * q;
-          if (rr < K) {
-#pragma unroll
-            for (int c = 0; c < NB; ++c) pan[buf][rr][c] = prow[q][c] - (rr == pivs[c] ? S(1) : S(0));
-          }
-        }
-        if (lane == 0) {
-#pragma unroll
-          for (int c = 0; c < NB; ++c) {
-            pvt[buf][c] = pivs[c];
-            pk[jj * NCT + h * NB + c] = pivs[c];
-          }
-          if (dd) deadflag = 1;
-        }
-      }
-      __syncthreads();
-      // the owners of the pivot rows publish them as they were before the panel
-#pragma unroll
-      for (int c = 0; c < NB; ++c) {
-        const int p = pvt[buf][c];
-        const int prt = p % NRT;
-        if constexpr (!PIV && NRT % NCT == 0) {
-          // diagonal pivots p = jj NCT + h NB + c: the register row p / NRT does not depend on h and c
-          constexpr int pi = (jj * NCT) / NRT;
-          if (rt == prt) {
-#pragma unroll
-            for (int j = 0; j < CT; ++j) xrow[buf][c][ct + j * NCT] = reg[pi][j];
-          }
-        } else {
-          // (one flat condition per register row: nesting the row test inside the thread test made the
-          // compiler index the registers dynamically, through scratch memory)
-          const int pi = p / NRT;
-#pragma unroll
-          for (int i = 0; i < RT; ++i)
-            if (rt == prt && i == pi) {
-#pragma unroll
-              for (int j = 0; j < CT; ++j) xrow[buf][c][ct + j * NCT] = reg[i][j];
-            }
-        }
-      }
-      __syncthreads();
-#pragma unroll 2
-      for (int c = 0; c < NB; ++c) {
-        S xv[CT], cr[RT];
-#pragma unroll
-        for (int j = 0; j < CT; ++j) xv[j] = xrow[buf][c][ct + j * NCT];
-#pragma unroll
-        for (int i = 0; i < RT; ++i) cr[i] = pan[buf][rt + i * NRT][c];
-#pragma unroll
-        for (int i = 0; i < RT; ++i)
-#pragma unroll
-          for (int j = 0; j < CT; ++j) reg[i][j] = fma_s(cr[i], xv[j], reg[i][j]);
-      }
-      // a panel column becomes the panel's own result
-      if (owner) {
-        const int pq = pvt[buf][q_own];
-#pragma unroll
-        for (int i = 0; i < RT; ++i) {
-          const int r = rt + i * NRT;
-          reg[i][jj] = pan[buf][r][q_own] + (r == pq ? S(1) : S(0));
-        }
-      }
-    }
-  };
-  StaticFor<0, CT>::run(panels);
-  __syncthreads();
-  const bool dead = deadflag != 0;
-  if (a.status && tid == 0) a.status[size_t(b) * a.status_stride + a.status_offset] = dead ? 1 : 0;
-  float* O = a.out + size_t(b) * K * K;
-  if (dead) {
-#pragma unroll
-    for (int i = 0; i < RT; ++i)
-#pragma unroll
-      for (int j = 0; j < CT; ++j) O[(rt + i * NRT) * K + ct + j * NCT] = 0.f;
-    if (tid < K) {
-      if (a.rho_row) a.rho_row[size_t(b) * K + tid] = 0.f;
-      if (a.rho_col) a.rho_col[size_t(b) * K + tid] = 0.f;
-    }
-    return;
-  }
-  if (tid < K) kinv[pk[tid]] = tid;
-  __syncthreads();
-  // register (r, c) is element (kinv[r], pk[c]) of the inverse of the scaled block
-  int ocol[CT];
-#pragma unroll
-  for (int j = 0; j < CT; ++j) ocol[j] = pk[ct + j * NCT];
-#pragma unroll
-  for (int i = 0; i < RT; ++i) {
-    const int orow = kinv[rt + i * NRT];
-    S rr = 0;
-#pragma unroll
-    for (int j = 0; j < CT; ++j) {
-      reg[i][j] *= scale;
-      O[orow * K + ocol[j]] = float(reg[i][j]);
-      rr += reg[i][j] * reg[i][j];
-    }
-    if (a.rho_row) {
-      for (int m = 1; m < NCT; m <<= 1) rr += __shfl_xor(rr, m);
-      if (ct == 0) a.rho_row[size_t(b) * K + orow] = float(rr);
-    }
-  }
-  if (a.rho_col) {
-    // column norms from the block just written, one thread per column, rows in order (fixed summation order:
-    // the result is reproducible run to run)
-    __syncthreads();
-    if (tid < K) {
-      double c2 = 0;
-      for (int i = 0; i < K; ++i) {
-        const float v = O[i * K + tid];
-        c2 += double(v) * v;
-      }
-      a.rho_col[size_t(b) * K + tid] = float(c2);
-    }
-  }
-}
-
 // The same inversion for a symmetric positive definite block of 256 in float32 (the Gram matrices of the adaptive
 // rounding: diagonal pivots in natural order, so no permutation), as a block elimination in panels of 16 columns
 // with everything but the 16 x 16 pivot block on the 16-bit matrix pipe.  With P the pivot block of panel t (rows
@@ -811,11 +466,7 @@ __global__ __launch_bounds__(512) void gj_spd256_kernel(const GjArgs a) {
   __shared__ int deadflag, ready;        // ready: panels handed over so far
   __shared__ float wred[8];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, ln = lane & 31, h = lane >> 5;
-  if (a.need) {                           // uniform over the workgroup
-    int any = 0;
-    for (int i = 0; i < a.need_n; ++i) any |= a.need[b * a.need_n + i];
-    if (!any) return;
-  }
+  if (a.need && !a.need[b]) return;       // uniform over the workgroup
   const int rbase = 32 * w + 4 * h;       // row of register r: rbase + 8 (r / 4) + r % 4
   floatx16 reg[8];
   if (a.partial == nullptr || a.sum32) {
@@ -1045,29 +696,8 @@ __global__ __launch_bounds__(512) void gj_spd256_kernel(const GjArgs a) {
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int row = rbase + 8 * (r >> 2) + (r & 3);
-    float rr = 0;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const float v = dead ? 0.f : reg[j][r] * scale;
-      O[size_t(row) * K + 32 * j + ln] = v;
-      rr += v * v;
-    }
-    if (a.rho_row) {
-      for (int m = 1; m < 32; m <<= 1) rr += __shfl_xor(rr, m);
-      if (ln == 0) a.rho_row[size_t(b) * K + row] = rr;
-    }
-  }
-  if (a.rho_col) {
-    // column norms from the block just written, one thread per column, rows in order
-    __syncthreads();
-    if (tid < K) {
-      double c2 = 0;
-      for (int i = 0; i < K; ++i) {
-        const float v = O[i * K + tid];
-        c2 += double(v) * v;
-      }
-      a.rho_col[size_t(b) * K + tid] = float(c2);
-    }
+    for (int j = 0; j < 8; ++j) O[size_t(row) * K + 32 * j + ln] = dead ? 0.f : reg[j][r] * scale;
   }
 }
 
@@ -1273,331 +903,19 @@ __global__ __launch_bounds__(256) void eye_minus_kernel(const double* __restrict
 }  // namespace
 
 namespace {
-// Fast path of the blockwise inverse for blocks that are rotations to float32 accuracy -- the paper's
-// initialisation of the transform: the inverse is then the transpose.  One workgroup per block, one wave
-// per 32 x 32 tile: T goes to LDS in both orientations (row stride K + 1 words: rows and columns are both
-// read without bank conflicts), R = I - T T^T is formed on the float32 matrix pipe, and if max |R| is at the
-// level of its own accumulation noise (2e-6) the block is finished here: Tinv = T^T, its squared row /
-// column norms, status 0, need[b] = 0.  Any other block is left to the elimination kernel (need[b] = 1),
-// which skips the finished ones.  (Newton rounds X <- X + X R on this pipe were tried for blocks a little
-// further from a rotation: each round leaves about 3e-6 of relative error, the noise of R; not kept.)
-template <int K>
-__global__ __launch_bounds__((K / 32) * (K / 32) * 64) void rotation_inverse_kernel(
-    const float* __restrict__ T, float* __restrict__ Tinv, float* __restrict__ rho_row, float* __restrict__ rho_col,
-    int* __restrict__ status, int* __restrict__ need) {
-  constexpr int NTL = K / 32, NW = NTL * NTL, NTHR = NW * 64, LD = K + 1;
-  extern __shared__ __align__(16) float nsm[];
-  float* bufT = nsm;                 // T[i][l]
-  float* bufX = nsm + K * LD;        // T^T[l][j]
-  float* red = bufX + K * LD;        // [NW]
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int ln = lane & 31, h = lane >> 5, wi = wave / NTL, wj = wave % NTL;
-  const float* Tb = T + size_t(b) * K * K;
-  for (int e = tid * 4; e < K * K; e += NTHR * 4) {
-    const float4 v = *reinterpret_cast<const float4*>(Tb + e);
-    const int r = e / K, c = e % K;
-    float* d = bufT + r * LD + c;
-    d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
-    bufX[(c + 0) * LD + r] = v.x; bufX[(c + 1) * LD + r] = v.y;
-    bufX[(c + 2) * LD + r] = v.z; bufX[(c + 3) * LD + r] = v.w;
-  }
-  __syncthreads();
-  // cheap necessary condition first: rows of unit length (most blocks that are no rotations leave here)
-  {
-    float dev = 0.f;
-    if (tid < K) {
-      float n2 = 0.f;
-      for (int c = 0; c < K; ++c) { const float x = bufX[c * LD + tid]; n2 = fmaf(x, x, n2); }
-      dev = fabsf(n2 - 1.f);
-      if (!(dev <= 3.0e38f)) dev = INFINITY;
-    }
-    dev = cluster_allmax<64>(dev);
-    if (lane == 0) red[wave] = dev;
-    __syncthreads();
-    float dmax = red[0];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) dmax = fmaxf(dmax, red[w]);
-    __syncthreads();
-    if (!(dmax <= 4e-6f)) {
-      if (tid == 0) need[b] = 1;
-      return;
-    }
-  }
-  floatx16 acc;
-#pragma unroll
-  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-  {
-    const float* pa = bufT + (wi * 32 + ln) * LD + h;   // a(l, i) = T[i][l], l = 2 s + h
-    const float* pb = bufX + h * LD + wj * 32 + ln;      // b(l, j) = T^T[l][j]
-#pragma unroll 8
-    for (int s2 = 0; s2 < K / 2; ++s2) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[2 * s2], pb[2 * s2 * LD], acc, 0, 0, 0);
-  }
-  float m = 0.f;
-  bool bad = false;
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int i = wi * 32 + 8 * (v / 4) + 4 * h + (v % 4), j = wj * 32 + ln;
-    const float ar = fabsf((i == j ? 1.f : 0.f) - acc[v]);
-    bad = bad || !(ar <= 3.0e38f);             // infinity or not a number
-    m = fmaxf(m, ar);
-  }
-  if (bad) m = INFINITY;
-  m = cluster_allmax<64>(m);
-  if (lane == 0) red[wave] = m;
-  __syncthreads();
-  float rmax = red[0];
-#pragma unroll
-  for (int w = 1; w < NW; ++w) rmax = fmaxf(rmax, red[w]);
-  const bool ok = rmax <= 2e-6f;
-  if (tid == 0) need[b] = ok ? 0 : 1;
-  if (!ok) return;
-  float* O = Tinv + size_t(b) * K * K;
-  for (int e = tid; e < K * K; e += NTHR) O[e] = bufX[(e / K) * LD + (e % K)];
-  if (tid < K) {
-    float rr = 0.f, rc = 0.f;
-    for (int c = 0; c < K; ++c) {
-      const float x = bufX[tid * LD + c], d = bufX[c * LD + tid];
-      rr = fmaf(x, x, rr); rc = fmaf(d, d, rc);
-    }
-    if (rho_row) rho_row[size_t(b) * K + tid] = rr;
-    if (rho_col) rho_col[size_t(b) * K + tid] = rc;
-  }
-  if (status && tid == 0) status[b] = 0;
-}
-// The same for blocks of 128 with four workgroups per block, one per slice of 32 rows of T (one workgroup per
-// block keeps sixteen waves on one compute unit's float32 matrix pipe for 10 us; the 112 blocks of the 9B-shaped
-// pair leave more than half of the chip idle).  Every slice loads the whole block (transposed, into LDS), checks
-// its own rows -- unit length, then its 32 x 128 slice of R = I - T T^T, one 32 x 32 tile per wave -- and, if
-// they pass, writes its share of the result: columns 32 s .. of Tinv = T^T, their squared norms, and the squared
-// norms of the rows 32 s .. of Tinv.  need[4 b + s] = 0 / 1; a block with any slice failing is redone as a whole
-// by the elimination kernel, which runs afterwards and overwrites what the passing slices wrote.
-__global__ __launch_bounds__(256) void rotation_slice_kernel(const float* __restrict__ T, float* __restrict__ Tinv,
-                                                             float* __restrict__ rho_row, float* __restrict__ rho_col,
-                                                             int* __restrict__ status, int* __restrict__ need) {
-  constexpr int K = 128, LD = K + 1;
-  extern __shared__ __align__(16) float nsm[];
-  float* bufX = nsm;                 // T^T[l][j]
-  float* red = bufX + K * LD;        // [4]
-  const int b = blockIdx.x >> 2, sl = blockIdx.x & 3;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ln = lane & 31, h = lane >> 5;
-  const float* Tb = T + size_t(b) * K * K;
-  for (int e = tid * 4; e < K * K; e += 256 * 4) {
-    const float4 v = *reinterpret_cast<const float4*>(Tb + e);
-    const int r = e / K, c = e % K;
-    bufX[(c + 0) * LD + r] = v.x; bufX[(c + 1) * LD + r] = v.y;
-    bufX[(c + 2) * LD + r] = v.z; bufX[(c + 3) * LD + r] = v.w;
-  }
-  __syncthreads();
-  // squared lengths of this slice's rows of T (= columns of Tinv) and of its columns (= rows of Tinv): eight
-  // threads per vector, sixteen terms each, combined through LDS in fixed order
-  float* part = red + 4;             // [2][8][32]
-  {
-    const int i = sl * 32 + (tid & 31), q = tid >> 5;
-    float a0 = 0.f, a1 = 0.f;
-#pragma unroll
-    for (int c = 0; c < 16; ++c) {
-      const float x = bufX[(16 * q + c) * LD + i];   // T[i][16 q + c]
-      const float y = bufX[i * LD + 16 * q + c];     // T[16 q + c][i]
-      a0 = fmaf(x, x, a0);
-      a1 = fmaf(y, y, a1);
-    }
-    part[q * 32 + (tid & 31)] = a0;
-    part[256 + q * 32 + (tid & 31)] = a1;
-  }
-  __syncthreads();
-  float n2row = 0.f, n2col = 0.f;
-  // cheap necessary condition first: rows of unit length
-  {
-    float dev = 0.f;
-    if (tid < 32) {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) { n2row += part[q * 32 + tid]; n2col += part[256 + q * 32 + tid]; }
-      dev = fabsf(n2row - 1.f);
-      if (!(dev <= 3.0e38f)) dev = INFINITY;
-    }
-    dev = cluster_allmax<64>(dev);
-    if (lane == 0) red[wave] = dev;
-    __syncthreads();
-    const float dmax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    __syncthreads();
-    if (!(dmax <= 4e-6f)) {
-      if (tid == 0) need[blockIdx.x] = 1;
-      return;
-    }
-  }
-  floatx16 acc;
-#pragma unroll
-  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-  {
-    const float* pa = bufX + h * LD + sl * 32 + ln;      // a(l, i) = T[i][l] = T^T[l][i], l = 2 s + h
-    const float* pb = bufX + h * LD + wave * 32 + ln;    // b(l, j) = T^T[l][j]
-#pragma unroll 8
-    for (int s2 = 0; s2 < K / 2; ++s2) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[2 * s2 * LD], pb[2 * s2 * LD], acc, 0, 0, 0);
-  }
-  float m = 0.f;
-  bool bad = false;
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int i = sl * 32 + 8 * (v / 4) + 4 * h + (v % 4), j = wave * 32 + ln;
-    const float ar = fabsf((i == j ? 1.f : 0.f) - acc[v]);
-    bad = bad || !(ar <= 3.0e38f);
-    m = fmaxf(m, ar);
-  }
-  if (bad) m = INFINITY;
-  m = cluster_allmax<64>(m);
-  if (lane == 0) red[wave] = m;
-  __syncthreads();
-  const float rmax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  const bool ok = rmax <= 2e-6f;
-  if (tid == 0) need[blockIdx.x] = ok ? 0 : 1;
-  if (!ok) return;
-  // Tinv[j][i] = T[i][j] for the slice's i: 32 consecutive floats of every row j
-  float* O = Tinv + size_t(b) * K * K + sl * 32;
-  for (int e = tid; e < K * 32; e += 256) O[(e >> 5) * K + (e & 31)] = bufX[(e >> 5) * LD + sl * 32 + (e & 31)];
-  if (tid < 32) {
-    const int i = sl * 32 + tid;
-    if (rho_col) rho_col[size_t(b) * K + i] = n2row;      // column i of Tinv is row i of T
-    if (rho_row) rho_row[size_t(b) * K + i] = n2col;      // row i of Tinv is column i of T
-  }
-  if (status && tid == 0) status[b] = 0;
-}
-// Warm start for the learning loops, where the transform moves a little per iteration and the previous
-// inverse X_0 is at hand: Newton's iteration  X <- X + X (I - T X), one workgroup per block, one wave per
-// 32 x 32 tile, T and X in LDS; residuals on the float32 matrix pipe, corrections with bfloat16 operands.  The residual R = I - T X is measured every round;
-// at the level of its own accumulation noise (4e-6) X stands, a round that promises max|R^2| <= 4e-6 (by
-// K max|R|^2 or by the squared Frobenius norm) is the last, and a block whose residual is not a safe
-// contraction (Frobenius norm >= 1/2) or is not done in three rounds is left to the elimination kernel
-// (need[b] = 1).  The result carries the noise of R, about 3e-6 relative --
-// below the 16-bit operand parts the loss pass makes of it, but above the elimination's float32 rounding, so
-// the inverse a loop hands back to its caller is always recomputed by the elimination.
-template <int K>
-__global__ __launch_bounds__((K / 32) * (K / 32) * 64) void newton_inverse_kernel(const float* __restrict__ T,
-                                                                                   float* __restrict__ X,
-                                                                                   int* __restrict__ status,
-                                                                                   int* __restrict__ need) {
-  constexpr int NTL = K / 32, NW = NTL * NTL, NTHR = NW * 64, LD = K + 1;
-  extern __shared__ __align__(16) float nsm[];
-  float* bufT = nsm;                 // T[i][l], later R transposed in bfloat16 (rtb)
-  uint16_t* rtb = reinterpret_cast<uint16_t*>(nsm);
-  constexpr int LDB = K + 8;         // bfloat16 elements per row of rtb: 16-byte aligned rows
-  float* bufX = nsm + K * LD;        // X[l][j]
-  float* red = bufX + K * LD;        // [2 NW]: max |R| and sum R^2 of each wave's tile
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int ln = lane & 31, h = lane >> 5, wi = wave / NTL, wj = wave % NTL;
-  const float* Tb = T + size_t(b) * K * K;
-  float* Xb = X + size_t(b) * K * K;
-  auto load = [&](const float* src, float* dst) {
-    for (int e = tid * 4; e < K * K; e += NTHR * 4) {
-      const float4 v = *reinterpret_cast<const float4*>(src + e);
-      float* d = dst + (e / K) * LD + (e % K);
-      d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
-    }
-  };
-  load(Tb, bufT);
-  load(Xb, bufX);
-  __syncthreads();
-  bool ok = false, changed = false;
-#pragma unroll 1
-  for (int it = 0; it < 3; ++it) {
-    floatx16 acc;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-    {
-      const float* pa = bufT + (wi * 32 + ln) * LD + h;   // a(l, i) = T[i][l], l = 2 s + h
-      const float* pb = bufX + h * LD + wj * 32 + ln;      // b(l, j) = X[l][j]
-#pragma unroll 8
-      for (int s2 = 0; s2 < K / 2; ++s2) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[2 * s2], pb[2 * s2 * LD], acc, 0, 0, 0);
-    }
-    float r[16], m = 0.f, q = 0.f;
-    bool bad = false;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int i = wi * 32 + 8 * (v / 4) + 4 * h + (v % 4), j = wj * 32 + ln;
-      r[v] = (i == j ? 1.f : 0.f) - acc[v];
-      const float ar = fabsf(r[v]);
-      bad = bad || !(ar <= 3.0e38f);           // infinity or not a number
-      m = fmaxf(m, ar);
-      q = fmaf(ar, ar, q);
-    }
-    if (bad) m = INFINITY;
-    m = cluster_allmax<64>(m);
-    q = wave_sum(q);
-    if (lane == 0) { red[wave] = m; red[NW + wave] = q; }
-    __syncthreads();                           // also: every wave has finished reading bufT
-    float rmax = red[0], fro2 = red[NW];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) { rmax = fmaxf(rmax, red[w]); fro2 += red[NW + w]; }
-    if (!(fro2 < 0.25f)) break;                // ||R||_2 <= ||R||_F; not a contraction to count on: elimination
-    if (rmax <= 4e-6f) { ok = true; break; }   // the residual is float32 accumulation noise: X stands
-    // The correction X R needs no more than 16-bit operands: what their rounding leaves (2^-8 of the
-    // correction) is part of the next round's residual, and below float32 noise in the last round.
-    // R goes to LDS transposed, in bfloat16, over the rows of the old T.
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int i0 = wi * 32 + 8 * g + 4 * h, j = wj * 32 + ln;
-      uint2 pk;
-      pk.x = pack_bf16(r[4 * g], r[4 * g + 1]);
-      pk.y = pack_bf16(r[4 * g + 2], r[4 * g + 3]);
-      *reinterpret_cast<uint2*>(rtb + j * LDB + i0) = pk;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-    {
-      const float* pa = bufX + (wi * 32 + ln) * LD + 8 * h;          // a(l, i) = X[i][l], l = 16 s + 8 h + e
-      const uint16_t* pb = rtb + (wj * 32 + ln) * LDB + 8 * h;       // b(l, j) = R[l][j] = RT[j][l]
-#pragma unroll 4
-      for (int s2 = 0; s2 < K / 16; ++s2) {
-        const float* x = pa + 16 * s2;
-        const bf16x8 av = as_bf16x8(pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]), pack_bf16(x[4], x[5]), pack_bf16(x[6], x[7]));
-        const bf16x8 bv = as_bf16x8(*reinterpret_cast<const uintx4*>(pb + 16 * s2));
-        acc = CAFEQ_MFMA_BF16(av, bv, acc);
-      }
-    }
-    float xn[16];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int i = wi * 32 + 8 * (v / 4) + 4 * h + (v % 4), j = wj * 32 + ln;
-      xn[v] = bufX[i * LD + j] + acc[v];
-    }
-    __syncthreads();                           // every wave has finished reading bufX and bufT
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int i = wi * 32 + 8 * (v / 4) + 4 * h + (v % 4), j = wj * 32 + ln;
-      bufX[i * LD + j] = xn[v];
-    }
-    changed = true;
-    if (fminf(float(K) * rmax * rmax, fro2) <= 4e-6f) { ok = true; break; }   // max |R^2| is below both
-    load(Tb, bufT);                            // T again for the next round's residual
-    __syncthreads();
-  }
-  __syncthreads();
-  if (tid == 0) need[b] = ok ? 0 : 1;
-  if (!ok) return;
-  if (changed)
-    for (int e = tid; e < K * K; e += NTHR) Xb[e] = bufX[(e / K) * LD + (e % K)];
-  if (status && tid == 0) status[b] = 0;
-}
-}  // namespace
-
-namespace {
 int launch_gj(const GjArgs& a, int nb, hipStream_t st) {
-  // the Gram matrices of the adaptive rounding are symmetric positive definite: no pivot search there
-  const bool piv = a.partial == nullptr;
-#define CAFEQ_GJ(K_, RT_, CT_, S_, THR_)                                                                      \
-  if (piv) hipLaunchKernelGGL((gj_panel_kernel<K_, RT_, CT_, S_, true>), dim3(nb), dim3(THR_), 0, st, a);     \
-  else hipLaunchKernelGGL((gj_panel_kernel<K_, RT_, CT_, S_, false>), dim3(nb), dim3(THR_), 0, st, a)
+  // the Gram matrices of the adaptive rounding are symmetric positive definite: no pivot search there; only the
+  // blockwise inverse of blocks of 256 comes here with general ones (inverse_kernels.hip has the smaller blocks)
   switch (a.K) {
-    case 32: CAFEQ_GJ(32, 4, 4, double, 64); break;
-    case 64: CAFEQ_GJ(64, 4, 8, double, 128); break;
-    case 128: CAFEQ_GJ(128, 4, 8, double, 512); break;
+    case 32: hipLaunchKernelGGL((gj_panel_kernel<32, 4, 4, double, false>), dim3(nb), dim3(64), 0, st, a); break;
+    case 64: hipLaunchKernelGGL((gj_panel_kernel<64, 4, 8, double, false>), dim3(nb), dim3(128), 0, st, a); break;
+    case 128: hipLaunchKernelGGL((gj_panel_kernel<128, 4, 8, double, false>), dim3(nb), dim3(512), 0, st, a); break;
     case 256:
-      if (piv) hipLaunchKernelGGL((gj_panel_kernel<256, 8, 16, float, true>), dim3(nb), dim3(512), 0, st, a);
+      if (a.partial == nullptr) hipLaunchKernelGGL((gj_panel_kernel<256, 8, 16, float, true>), dim3(nb), dim3(512), 0, st, a);
       else hipLaunchKernelGGL(gj_spd256_kernel, dim3(nb), dim3(512), 0, st, a);
       break;
     default: return CAFEQ_ERR_UNSUPPORTED;
   }
-#undef CAFEQ_GJ
   CAFEQ_CHECK_LAUNCH();
   return CAFEQ_OK;
 }
@@ -1690,9 +1008,8 @@ int launch_gram(int axis, const float* X, const int8_t* codes, const float* scal
 int launch_gj_solve(int K, int nb, int nz, const float* partial, double* work, float* Sinv, float* R,
                     float* out, int* status, int status_stride, int status_offset, hipStream_t st) {
   GjArgs a;
-  a.mode = 0; a.K = K; a.nz = nz; a.T = nullptr; a.partial = partial; a.work = work; a.out = Sinv;
-  a.need = nullptr;
-  a.rho_row = a.rho_col = nullptr; a.status = status; a.status_stride = status_stride;
+  a.K = K; a.nz = nz; a.T = nullptr; a.partial = partial; a.out = Sinv;
+  a.status = status; a.status_stride = status_stride;
   a.status_offset = status_offset;
   const size_t mat = size_t(nb) * K * K;
   double *S64 = work, *R64 = work + mat, *res = work + 2 * mat, *X64 = work + 3 * mat;
@@ -1720,41 +1037,6 @@ int launch_gj_solve(int K, int nb, int nz, const float* partial, double* work, f
   hipLaunchKernelGGL(eye_minus_kernel, dim3(unsigned((n + 255) / 256)), dim3(256), 0, st, X64, K, n, out);
   CAFEQ_CHECK_LAUNCH();
   return CAFEQ_OK;
-}
-
-int launch_inverse256(const float* T, int nb, double* work, float* Tinv, float* rho_row, float* rho_col, int* status,
-                      bool warm, hipStream_t st);
-int launch_block_inverse(const float* T, int K, int nb, double* work, float* Tinv, float* rho_row,
-                         float* rho_col, int* status, hipStream_t st) {
-  GjArgs a;
-  a.mode = 0; a.K = K; a.nz = 0; a.T = T; a.partial = nullptr; a.work = work; a.out = Tinv;
-  a.rho_row = rho_row; a.rho_col = rho_col; a.status = status; a.status_stride = 1; a.status_offset = 0;
-  a.need = nullptr;
-  if (K == 64 || K == 128) {
-    // rotations (to float32 accuracy) are inverted by transposition; the elimination then only runs for
-    // the blocks that are none (flags at the start of the work buffer)
-    int* need = reinterpret_cast<int*>(work);
-    const size_t lds = size_t(2 * K * (K + 1) + (K / 32) * (K / 32)) * sizeof(float);
-    if (K == 128) {
-      // four workgroups per block, one per slice of 32 rows (flags need[4 b + slice])
-      const size_t lds4 = size_t(K * (K + 1) + 4 + 512) * sizeof(float);
-      static std::atomic<bool> attr_set{false};
-      if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(rotation_slice_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, int(lds4)) != hipSuccess)
-          return CAFEQ_ERR_LAUNCH;
-        attr_set = true;
-      }
-      hipLaunchKernelGGL(rotation_slice_kernel, dim3(4 * nb), dim3(256), lds4, st, T, Tinv, rho_row, rho_col, status, need);
-      a.need_n = 4;
-    } else {
-      hipLaunchKernelGGL(rotation_inverse_kernel<64>, dim3(nb), dim3(256), lds, st, T, Tinv, rho_row, rho_col, status, need);
-    }
-    CAFEQ_CHECK_LAUNCH();
-    a.need = need;
-  }
-  if (K != 256) return launch_gj(a, nb, st);
-  return launch_inverse256(T, nb, work, Tinv, rho_row, rho_col, status, false, st);
 }
 
 // Blocks of 256.  Newton-Schulz rounds X <- 2 X - X (T X) on the float32 matrix pipe (batched products over the
@@ -1799,9 +1081,9 @@ int launch_inverse256(const float* T, int nb, double* work, float* Tinv, float* 
   hipLaunchKernelGGL(ns_flag_kernel, dim3(nb), dim3(1024), 0, st, Y, K, 1, 3e-4f, 0.f, hop, need, status);
   CAFEQ_CHECK_LAUNCH();
   GjArgs a;
-  a.mode = 0; a.K = K; a.nz = 0; a.T = T; a.partial = nullptr; a.work = work; a.out = Tinv;
-  a.rho_row = a.rho_col = nullptr; a.status = status; a.status_stride = 1; a.status_offset = 0;
-  a.need = need; a.need_n = 1;
+  a.K = K; a.nz = 0; a.T = T; a.partial = nullptr; a.out = Tinv;
+  a.status = status; a.status_stride = 1; a.status_offset = 0;
+  a.need = need;
   if ((rc = launch_gj(a, nb, st))) return rc;
   // one Newton step X <- X + X (I - T X) with float64 residuals
   double *res = work, *X64 = work + mat;
@@ -1815,32 +1097,6 @@ int launch_inverse256(const float* T, int nb, double* work, float* Tinv, float* 
   if (rho_row && (rc = launch_rho(Tinv, K, nb, 1, rho_row, st))) return rc;
   if (rho_col && (rc = launch_rho(Tinv, K, nb, 0, rho_col, st))) return rc;
   return CAFEQ_OK;
-}
-
-// The inverse inside a learning loop: Tinv holds the previous iteration's inverse on entry.
-int launch_block_inverse_warm(const float* T, int K, int nb, double* work, float* Tinv, int* status, hipStream_t st) {
-  if (K == 256) return launch_inverse256(T, nb, work, Tinv, nullptr, nullptr, status, true, st);
-  if (K != 64 && K != 128) return launch_block_inverse(T, K, nb, work, Tinv, nullptr, nullptr, status, st);
-  int* need = reinterpret_cast<int*>(work);
-  const size_t lds = size_t(2 * K * (K + 1) + 2 * (K / 32) * (K / 32)) * sizeof(float);
-  if (K == 128) {
-    static std::atomic<bool> attr_set{false};
-    if (!attr_set) {
-      if (hipFuncSetAttribute(reinterpret_cast<const void*>(newton_inverse_kernel<128>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) != hipSuccess)
-        return CAFEQ_ERR_LAUNCH;
-      attr_set = true;
-    }
-    hipLaunchKernelGGL(newton_inverse_kernel<128>, dim3(nb), dim3(1024), lds, st, T, Tinv, status, need);
-  } else {
-    hipLaunchKernelGGL(newton_inverse_kernel<64>, dim3(nb), dim3(256), lds, st, T, Tinv, status, need);
-  }
-  CAFEQ_CHECK_LAUNCH();
-  GjArgs a;
-  a.mode = 0; a.K = K; a.nz = 0; a.T = T; a.partial = nullptr; a.work = work; a.out = Tinv;
-  a.rho_row = a.rho_col = nullptr; a.status = status; a.status_stride = 1; a.status_offset = 0;
-  a.need = need;
-  return launch_gj(a, nb, st);
 }
 
 }  // namespace cafeq
