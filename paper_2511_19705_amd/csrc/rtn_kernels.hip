@@ -4,16 +4,17 @@
 // described in cafeq.h.  Algorithmic traffic per element: one read (4 B float32 /
 // 2 B bfloat16), one int8 code written, 4/g bytes of scale.
 //
-// Four kernels:
+// The kernels:
 //   rtn_col_fast : groups along the contiguous axis, g = 4 * 2^n <= 256.  One lane owns
-//                  four consecutive elements (one 128-bit load), g/4 adjacent lanes own a
-//                  group; the absmax is an all-reduce over that lane cluster with DPP
+//                  four (float32) or sixteen (bfloat16) consecutive elements, adjacent lanes
+//                  own a group; the absmax is an all-reduce over that lane cluster with DPP
 //                  (inside a 16-lane row) and LDS-crossbar shuffles (across rows).
 //   rtn_row_fast : groups along the strided axis, g = 16 * {1,2,4,8,16}.  A workgroup of
 //                  g/16 waves owns g rows x 256 columns; each wave keeps 16 rows of four
 //                  columns per lane in registers, column maxima are combined through LDS,
 //                  so the tile is read from memory once.
-//   rtn_col_any / rtn_row_any : any group length dividing the line, two passes per group.
+//   rtn_col_long : groups of 2048 and more (whole channels) kept in a workgroup's registers.
+//   rtn_col_vec, rtn_col_any / rtn_row_any : any group length dividing the line, two passes per group.
 // The squared-error output is reduced in two fixed-order stages (per-workgroup partials
 // in the caller's workspace, then one workgroup), so it is reproducible run to run.
 #include "cafeq_common.hpp"
@@ -40,46 +41,209 @@ __device__ __forceinline__ void block_store_partial(float err, double* partial) 
   }
 }
 
-template <typename Tag, int LPG, bool DENSE>
-__global__ __launch_bounds__(kColThreads) void rtn_col_fast(
-    const typename Tag::elem* __restrict__ W, uint32_t nvec, uint32_t cols4, int64_t ld, QGrid grid,
-    uint32_t* __restrict__ codes, float* __restrict__ scales, double* __restrict__ partial) {
-  const uint32_t base = blockIdx.x * (kColThreads * kColUnroll) + threadIdx.x;
-  float4 x[kColUnroll];
-  bool live[kColUnroll];
+// The grid of a call: symmetric (p0 = qmax, p1 = qmin) or the min/max grid of the paper's Eq. (1) (p0 = levels).
+// Min/max, in single precision: r = fl(max - min), inv = min(fl(levels / r), FLT_MAX) (0 for a constant group),
+// q = clamp(rint(fl(fl(z - min) * inv)), 0, levels), s = fl(r / levels), dequantized fl(fl(q * s) + min);
+// levels = 2^b - 1.
+__device__ __forceinline__ float mm_inv(float r, float levels) {
+  return r > 0.f ? fminf(__fdiv_rn(levels, r), FLT_MAX) : 0.f;
+}
+// v = scaled value, clamped to the grid (a NaN to its lower end) and rounded to nearest even: adding 1.5 2^23 leaves
+// the integer in the low mantissa bits, so the sum's low byte is the code and the sum less 1.5 2^23 the code as a float
+constexpr float kRoundMagic = 12582912.f;
+__device__ __forceinline__ float code_bits(float v, float lo, float hi) {
+  return __fadd_rn(__builtin_amdgcn_fmed3f(v, lo, hi), kRoundMagic);
+}
+__device__ __forceinline__ uint32_t pack_code_bits(float m0, float m1, float m2, float m3) {
+  const uint32_t lo = __builtin_amdgcn_perm(__float_as_uint(m1), __float_as_uint(m0), 0x0C0C0400u);
+  const uint32_t hi = __builtin_amdgcn_perm(__float_as_uint(m3), __float_as_uint(m2), 0x04000C0Cu);
+  return lo | hi;
+}
+
+// EPL consecutive elements as loaded
+typedef uint32_t raw4 __attribute__((ext_vector_type(4)));
+template <typename Tag, int EPL>
+struct RawElems;
+template <int EPL>
+struct RawElems<F32Tag, EPL> {
+  raw4 w[EPL / 4];
+  __device__ __forceinline__ void load(const float* p) {
 #pragma unroll
-  for (int j = 0; j < kColUnroll; ++j) {
-    const uint32_t v = base + j * kColThreads;
-    live[j] = v < nvec;
-    x[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (live[j]) {
-      size_t off;
-      if constexpr (DENSE) {
-        off = size_t(v) * 4;
-      } else {
-        const uint32_t r = v / cols4;
-        off = size_t(r) * ld + size_t(v - r * cols4) * 4;
+    for (int q = 0; q < EPL / 4; ++q) w[q] = reinterpret_cast<const raw4*>(p)[q];
+  }
+  __device__ __forceinline__ float get(int e) const { return __uint_as_float(w[e / 4][e % 4]); }
+};
+template <int EPL>
+struct RawElems<BF16Tag, EPL> {
+  uint32_t w[EPL / 2];
+  __device__ __forceinline__ void load(const uint16_t* p) {
+    if constexpr (EPL >= 8) {
+#pragma unroll
+      for (int q = 0; q < EPL / 8; ++q) {
+        const raw4 v = reinterpret_cast<const raw4*>(p)[q];
+        w[4 * q] = v[0]; w[4 * q + 1] = v[1]; w[4 * q + 2] = v[2]; w[4 * q + 3] = v[3];
       }
-      x[j] = load4(W + off);
+    } else {
+      const uint2 v = *reinterpret_cast<const uint2*>(p);
+      w[0] = v.x; w[1] = v.y;
     }
   }
+  __device__ __forceinline__ float get(int e) const {
+    return __uint_as_float(e % 2 ? w[e / 2] & 0xFFFF0000u : w[e / 2] << 16);
+  }
+};
+
+// Groups along the contiguous axis: a lane owns EPL consecutive elements, LPG adjacent lanes a group (g = EPL * LPG, a
+// power of two), U such pieces of a lane are in flight at once.  (Fewer workgroups striding over the matrix leave fewer
+// partials of the squared error but run 8 % slower: 46.5 against 42 us in float32.)
+// float32: four elements per lane (one 128-bit load), bound by HBM: 42 us on three 3584 x 14336 matrices in turn, 6.1 TB/s.
+// bfloat16: half the bytes per element, so with four elements per lane the two divisions, the group reduction (through
+// LDS for 32 lanes) and the packing bound it (39.9 us on 3584 x 14336 with groups of 128, 3.9 TB/s); sixteen elements per
+// lane share them, the reduction stays inside a row of 16 lanes, and a code costs five instructions instead of nine:
+// 27.4 us, 5.6 TB/s.
+template <typename Tag, int EPL, int LPG, int U, bool DENSE, bool MM>
+__global__ __launch_bounds__(kColThreads) void rtn_col_fast(
+    const typename Tag::elem* __restrict__ W, uint32_t nvec, uint32_t colsv, int64_t ld, float p0, float p1,
+    uint32_t* __restrict__ codes, float* __restrict__ scales, float* __restrict__ mins, double* __restrict__ partial) {
   float err = 0.f;
+  const uint32_t base = blockIdx.x * (kColThreads * U) + threadIdx.x;
+  RawElems<Tag, EPL> raw[U];
 #pragma unroll
-  for (int j = 0; j < kColUnroll; ++j) {
+  for (int j = 0; j < U; ++j) {
     const uint32_t v = base + j * kColThreads;
-    float a = fmaxf(fmaxf(fabsf(x[j].x), fabsf(x[j].y)), fmaxf(fabsf(x[j].z), fabsf(x[j].w)));
-    a = cluster_allmax<LPG>(a);   // executed by every lane: clusters never straddle `live`
-    const float inv = grid_inv(a, grid.qmax);
-    const float s = grid_scale(a, grid.qmax);
-    const float q0 = grid_code(x[j].x, inv, grid), q1 = grid_code(x[j].y, inv, grid);
-    const float q2 = grid_code(x[j].z, inv, grid), q3 = grid_code(x[j].w, inv, grid);
-    if (live[j]) {
-      codes[v] = pack4(q0, q1, q2, q3);
-      if ((threadIdx.x % LPG) == 0 && scales) scales[v / LPG] = s;
-      if (partial) {
-        const float e0 = __fmul_rn(q0, s) - x[j].x, e1 = __fmul_rn(q1, s) - x[j].y;
-        const float e2 = __fmul_rn(q2, s) - x[j].z, e3 = __fmul_rn(q3, s) - x[j].w;
-        err += e0 * e0 + e1 * e1 + e2 * e2 + e3 * e3;
+    size_t off;
+    const uint32_t vv = v < nvec ? v : nvec - 1;     // (a group lies wholly inside or outside the matrix)
+    if constexpr (DENSE) {
+      off = size_t(vv) * EPL;
+    } else {
+      const uint32_t r = vv / colsv;
+      off = size_t(r) * ld + size_t(vv - r * colsv) * EPL;
+    }
+    raw[j].load(W + off);
+  }
+#pragma unroll
+  for (int j = 0; j < U; ++j) {
+    const uint32_t v = base + j * kColThreads;
+    const bool live = v < nvec;
+    float inv, s, lo = 0.f;
+    if constexpr (MM) {
+      float hi = raw[j].get(0), nlo = -hi;           // -min, so that one kind of reduction serves both
+#pragma unroll
+      for (int e = 1; e < EPL; ++e) {
+        hi = fmaxf(hi, raw[j].get(e));
+        nlo = fmaxf(nlo, -raw[j].get(e));
+      }
+      hi = cluster_allmax<LPG>(hi);
+      nlo = cluster_allmax<LPG>(nlo);
+      lo = -nlo;
+      const float r = __fsub_rn(hi, lo);
+      inv = mm_inv(r, p0);
+      s = __fdiv_rn(r, p0);
+    } else {
+      float a = fabsf(raw[j].get(0));
+#pragma unroll
+      for (int e = 1; e < EPL; ++e) a = fmaxf(a, fabsf(raw[j].get(e)));
+      a = cluster_allmax<LPG>(a);
+      inv = grid_inv(a, p0);
+      s = grid_scale(a, p0);
+    }
+    uint32_t c[EPL / 4];
+    float e2 = 0.f;
+#pragma unroll
+    for (int e = 0; e < EPL; e += 4) {
+      float m[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float z = raw[j].get(e + i);
+        m[i] = MM ? code_bits(__fmul_rn(__fsub_rn(z, lo), inv), 0.f, p0) : code_bits(__fmul_rn(z, inv), p1, p0);
+        if (partial) {                               // uniform over the launch
+          const float zq = __fmul_rn(__fsub_rn(m[i], kRoundMagic), s);
+          const float d = (MM ? __fadd_rn(zq, lo) : zq) - z;
+          e2 = fmaf(d, d, e2);
+        }
+      }
+      c[e / 4] = pack_code_bits(m[0], m[1], m[2], m[3]);
+    }
+    if (live) {
+      if constexpr (EPL == 16) {
+        const raw4 o = {c[0], c[1], c[2], c[3]};
+        reinterpret_cast<raw4*>(codes)[v] = o;
+      } else {
+        codes[v] = c[0];
+      }
+      if ((threadIdx.x % LPG) == 0) {
+        if (scales) scales[v / LPG] = s;
+        if (MM && mins) mins[v / LPG] = lo;
+      }
+      err += e2;
+    }
+  }
+  if (partial) block_store_partial(err, partial);
+}
+
+// Long groups along the contiguous axis (2048 elements and more: whole channels), one workgroup per group, which keeps the
+// group in registers between the reduction and the rounding: every lane NP pieces of 16 bytes, a workgroup's width apart.
+// One read of the matrix instead of two (rtn_col_vec, one wave per group and one request at a time): whole channels of
+// 3584 x 14336 in bfloat16 63 -> 26 us, in float32 85 -> 44 us.
+template <typename Tag, int NP, bool MM>
+__global__ __launch_bounds__(1024) void rtn_col_long(
+    const typename Tag::elem* __restrict__ W, int64_t gpr, int64_t ngroups, int64_t cols, int64_t ld, int g, float p0, float p1,
+    int8_t* __restrict__ codes, float* __restrict__ scales, float* __restrict__ mins, double* __restrict__ partial) {
+  constexpr int PE = Tag::dtype == CAFEQ_BF16 ? 8 : 4;
+  __shared__ float red[2][2][16];
+  const int nt = blockDim.x, nw = nt / kWave, wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  float err = 0.f;
+  int turn = 0;
+  for (int64_t gi = blockIdx.x; gi < ngroups; gi += gridDim.x, turn ^= 1) {
+    const int64_t r = gi / gpr, c0 = (gi - r * gpr) * g;
+    const typename Tag::elem* src = W + r * ld + c0;
+    int8_t* dst = codes + r * cols + c0;
+    RawElems<Tag, PE> raw[NP];
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const int i = (int(threadIdx.x) + q * nt) * PE;
+      raw[q].load(src + (i < g ? i : g - PE));        // (past the end: the last piece again, which changes no maximum)
+    }
+    float hi = MM ? -FLT_MAX : 0.f, nlo = -FLT_MAX;
+#pragma unroll
+    for (int q = 0; q < NP; ++q)
+#pragma unroll
+      for (int e = 0; e < PE; ++e) {
+        const float z = raw[q].get(e);
+        hi = fmaxf(hi, MM ? z : fabsf(z));
+        if (MM) nlo = fmaxf(nlo, -z);
+      }
+    hi = cluster_allmax<64>(hi);
+    if (MM) nlo = cluster_allmax<64>(nlo);
+    if (lane == 0) { red[turn][0][wave] = hi; red[turn][1][wave] = nlo; }
+    __syncthreads();                                  // (two sets of slots: the next group's do not meet this one's readers)
+    hi = red[turn][0][0]; nlo = red[turn][1][0];
+    for (int w = 1; w < nw; ++w) { hi = fmaxf(hi, red[turn][0][w]); nlo = fmaxf(nlo, red[turn][1][w]); }
+    const float lo = MM ? -nlo : 0.f, range = MM ? __fsub_rn(hi, lo) : hi;
+    const float inv = MM ? mm_inv(range, p0) : grid_inv(hi, p0), s = __fdiv_rn(range, p0);
+    if (threadIdx.x == 0) {
+      if (scales) scales[gi] = s;
+      if (MM && mins) mins[gi] = lo;
+    }
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const int i = (int(threadIdx.x) + q * nt) * PE;
+      if (i < g) {
+#pragma unroll
+        for (int e = 0; e < PE; e += 4) {
+          float m[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const float z = raw[q].get(e + k);
+            m[k] = MM ? code_bits(__fmul_rn(__fsub_rn(z, lo), inv), 0.f, p0) : code_bits(__fmul_rn(z, inv), p1, p0);
+            if (partial) {
+              const float zq = __fmul_rn(__fsub_rn(m[k], kRoundMagic), s);
+              const float d = (MM ? __fadd_rn(zq, lo) : zq) - z;
+              err = fmaf(d, d, err);
+            }
+          }
+          *reinterpret_cast<uint32_t*>(dst + i + e) = pack_code_bits(m[0], m[1], m[2], m[3]);
+        }
       }
     }
   }
@@ -233,63 +397,9 @@ __global__ __launch_bounds__(256) void rtn_row_any(
 }
 
 // ---- the min/max grid of the paper's Eq. (1) ------------------------------------------------
-// Single-precision recipe: r = fl(max - min), inv = min(fl(levels / r), FLT_MAX) (0 for a
-// constant group), q = clamp(rint(fl(fl(z - min) * inv)), 0, levels), s = fl(r / levels),
-// dequantized value fl(fl(q * s) + min); levels = 2^b - 1.
-struct MinMaxGrid { float levels; };
-__device__ __forceinline__ float mm_inv(float r, float levels) {
-  return r > 0.f ? fminf(__fdiv_rn(levels, r), FLT_MAX) : 0.f;
-}
 __device__ __forceinline__ float mm_code(float z, float lo, float inv, float levels) {
   const float q = __builtin_rintf(__fmul_rn(__fsub_rn(z, lo), inv));
   return fminf(fmaxf(q, 0.f), levels);
-}
-
-// groups along the contiguous axis, g = 4 * LPG <= 256 (same lane ownership as rtn_col_fast)
-template <typename Tag, int LPG, bool DENSE>
-__global__ __launch_bounds__(kColThreads) void rtn_col_minmax_fast(
-    const typename Tag::elem* __restrict__ W, uint32_t nvec, uint32_t cols4, int64_t ld, float levels,
-    uint32_t* __restrict__ codes, float* __restrict__ scales, float* __restrict__ mins,
-    double* __restrict__ partial) {
-  const uint32_t base = blockIdx.x * (kColThreads * kColUnroll) + threadIdx.x;
-  float err = 0.f;
-#pragma unroll
-  for (int j = 0; j < kColUnroll; ++j) {
-    const uint32_t v = base + j * kColThreads;
-    const bool live = v < nvec;
-    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (live) {
-      size_t off;
-      if constexpr (DENSE) {
-        off = size_t(v) * 4;
-      } else {
-        const uint32_t r = v / cols4;
-        off = size_t(r) * ld + size_t(v - r * cols4) * 4;
-      }
-      x = load4(W + off);
-    }
-    float hi = fmaxf(fmaxf(x.x, x.y), fmaxf(x.z, x.w));
-    float nlo = fmaxf(fmaxf(-x.x, -x.y), fmaxf(-x.z, -x.w));     // -min, so that one reduction serves both
-    hi = cluster_allmax<LPG>(hi);
-    nlo = cluster_allmax<LPG>(nlo);
-    const float lo = -nlo, r = __fsub_rn(hi, lo);
-    const float inv = mm_inv(r, levels), s = __fdiv_rn(r, levels);
-    const float q0 = mm_code(x.x, lo, inv, levels), q1 = mm_code(x.y, lo, inv, levels);
-    const float q2 = mm_code(x.z, lo, inv, levels), q3 = mm_code(x.w, lo, inv, levels);
-    if (live) {
-      codes[v] = uint32_t(q0) | (uint32_t(q1) << 8) | (uint32_t(q2) << 16) | (uint32_t(q3) << 24);
-      if ((threadIdx.x % LPG) == 0) {
-        if (scales) scales[v / LPG] = s;
-        if (mins) mins[v / LPG] = lo;
-      }
-      if (partial) {
-        const float e0 = __fadd_rn(__fmul_rn(q0, s), lo) - x.x, e1 = __fadd_rn(__fmul_rn(q1, s), lo) - x.y;
-        const float e2 = __fadd_rn(__fmul_rn(q2, s), lo) - x.z, e3 = __fadd_rn(__fmul_rn(q3, s), lo) - x.w;
-        err += e0 * e0 + e1 * e1 + e2 * e2 + e3 * e3;
-      }
-    }
-  }
-  if (partial) block_store_partial(err, partial);
 }
 
 // One wave per group along the contiguous axis, group length a multiple of 4 (whole channels
@@ -410,30 +520,91 @@ __global__ __launch_bounds__(256) void rtn_row_minmax_any(
   if (partial) block_store_partial(err, partial);
 }
 
-__global__ __launch_bounds__(256) void sum_partials_kernel(const double* __restrict__ partial, int n,
+// The partials in fixed order; sixteen waves with four requests each in flight (four waves with one request each took
+// 13.7 us for the 12544 partials of a float32 3584 x 14336 matrix, this takes 5 us).
+__global__ __launch_bounds__(1024) void sum_partials_kernel(const double* __restrict__ partial, int n,
                                                             float* __restrict__ out) {
-  __shared__ double red[256];
-  double t = 0;
-  for (int i = threadIdx.x; i < n; i += 256) t += partial[i];
-  red[threadIdx.x] = t;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
+  __shared__ double red[16];
+  double t[4] = {0, 0, 0, 0};
+  for (int i = threadIdx.x; i < n; i += 4096) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t[u] += i + 1024 * u < n ? partial[i + 1024 * u] : 0.0;
   }
-  if (threadIdx.x == 0) out[0] = float(red[0]);
+  const double w = wave_sum((t[0] + t[1]) + (t[2] + t[3]));
+  if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = w;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double s = 0;
+    for (int i = 0; i < 16; ++i) s += red[i];
+    out[0] = float(s);
+  }
 }
 
-template <typename Tag, int LPG>
-void launch_col_fast(const RtnArgs& a, uint32_t nblk, hipStream_t st) {
+template <typename Tag, int EPL, int LPG, int U, bool MM>
+void launch_col_fast(const RtnArgs& a, float p0, float p1, hipStream_t st, int* nparts) {
   using E = typename Tag::elem;
-  const uint32_t nvec = uint32_t(a.rows * a.cols / 4), cols4 = uint32_t(a.cols / 4);
+  const uint32_t nvec = uint32_t(a.rows * a.cols / EPL), colsv = uint32_t(a.cols / EPL);
+  const uint32_t nblk = (nvec + kColThreads * U - 1) / (kColThreads * U);
+  *nparts = int(nblk);
   if (a.ld == a.cols)
-    hipLaunchKernelGGL((rtn_col_fast<Tag, LPG, true>), dim3(nblk), dim3(kColThreads), 0, st,
-                       (const E*)a.W, nvec, cols4, a.ld, a.grid, (uint32_t*)a.codes, a.scales, a.partial);
+    hipLaunchKernelGGL((rtn_col_fast<Tag, EPL, LPG, U, true, MM>), dim3(nblk), dim3(kColThreads), 0, st, (const E*)a.W, nvec,
+                       colsv, a.ld, p0, p1, (uint32_t*)a.codes, a.scales, a.mins, a.partial);
   else
-    hipLaunchKernelGGL((rtn_col_fast<Tag, LPG, false>), dim3(nblk), dim3(kColThreads), 0, st,
-                       (const E*)a.W, nvec, cols4, a.ld, a.grid, (uint32_t*)a.codes, a.scales, a.partial);
+    hipLaunchKernelGGL((rtn_col_fast<Tag, EPL, LPG, U, false, MM>), dim3(nblk), dim3(kColThreads), 0, st, (const E*)a.W, nvec,
+                       colsv, a.ld, p0, p1, (uint32_t*)a.codes, a.scales, a.mins, a.partial);
+}
+// groups of g = 4 .. 256, a power of two, along the contiguous axis
+template <typename Tag, bool MM>
+void launch_col_groups(const RtnArgs& a, int64_t g, float p0, float p1, hipStream_t st, int* nparts) {
+  // bfloat16 in sixteens (g a multiple of 16: so are the rows' lengths, and every piece is 32-byte aligned inside its row)
+  if constexpr (Tag::dtype == CAFEQ_BF16) {
+    switch (g) {
+      case 16: return launch_col_fast<Tag, 16, 1, 2, MM>(a, p0, p1, st, nparts);
+      case 32: return launch_col_fast<Tag, 16, 2, 2, MM>(a, p0, p1, st, nparts);
+      case 64: return launch_col_fast<Tag, 16, 4, 2, MM>(a, p0, p1, st, nparts);
+      case 128: return launch_col_fast<Tag, 16, 8, 2, MM>(a, p0, p1, st, nparts);
+      case 256: return launch_col_fast<Tag, 16, 16, 2, MM>(a, p0, p1, st, nparts);
+      case 4: return launch_col_fast<Tag, 4, 1, 4, MM>(a, p0, p1, st, nparts);
+      default: return launch_col_fast<Tag, 4, 2, 4, MM>(a, p0, p1, st, nparts);
+    }
+  } else {
+    switch (g) {
+      case 4: return launch_col_fast<Tag, 4, 1, 4, MM>(a, p0, p1, st, nparts);
+      case 8: return launch_col_fast<Tag, 4, 2, 4, MM>(a, p0, p1, st, nparts);
+      case 16: return launch_col_fast<Tag, 4, 4, 4, MM>(a, p0, p1, st, nparts);
+      case 32: return launch_col_fast<Tag, 4, 8, 4, MM>(a, p0, p1, st, nparts);
+      case 64: return launch_col_fast<Tag, 4, 16, 4, MM>(a, p0, p1, st, nparts);
+      case 128: return launch_col_fast<Tag, 4, 32, 4, MM>(a, p0, p1, st, nparts);
+      default: return launch_col_fast<Tag, 4, 64, 4, MM>(a, p0, p1, st, nparts);
+    }
+  }
+}
+
+// groups of 2048 elements and more that are whole numbers of 16-byte pieces at aligned places and fit the registers of a
+// workgroup; false: not such groups
+template <typename Tag, bool MM>
+bool launch_col_long(const RtnArgs& a, int64_t g, float p0, float p1, hipStream_t st, int* nparts) {
+  using E = typename Tag::elem;
+  constexpr int PE = Tag::dtype == CAFEQ_BF16 ? 8 : 4;
+  if (g < 2048 || g % PE || a.ld % PE || a.cols % PE || g > int64_t(1024) * 16 * PE) return false;
+  const int pieces = int(g / PE);
+  // eight pieces per lane, or sixteen where even 1024 lanes need them
+  int nt = 256;
+  while (nt < 1024 && pieces > nt * 8) nt *= 2;
+  const int np = (pieces + nt - 1) / nt;
+  const int64_t gpr = a.cols / g, ngroups = a.rows * gpr;
+  const int nblk = int(std::min<int64_t>(ngroups, 4096));
+  *nparts = nblk;
+#define CAFEQ_LONG(NP)                                                                                                  \
+  hipLaunchKernelGGL((rtn_col_long<Tag, NP, MM>), dim3(nblk), dim3(nt), 0, st, (const E*)a.W, gpr, ngroups, a.cols, a.ld, \
+                     int(g), p0, p1, a.codes, a.scales, a.mins, a.partial)
+  if (np <= 2) CAFEQ_LONG(2);
+  else if (np <= 4) CAFEQ_LONG(4);
+  else if (np <= 6) CAFEQ_LONG(6);
+  else if (np <= 8) CAFEQ_LONG(8);
+  else CAFEQ_LONG(16);
+#undef CAFEQ_LONG
+  return true;
 }
 
 template <typename Tag>
@@ -445,19 +616,8 @@ int launch_rtn_typed(const RtnArgs& a, hipStream_t st, int* nparts) {
   if (a.axis == CAFEQ_AXIS_COL) {
     const bool pow2 = (g & (g - 1)) == 0;
     if (pow2 && g >= 4 && g <= 256 && a.rows * a.cols / 4 < (int64_t(1) << 31)) {
-      const int64_t nvec = a.rows * a.cols / 4;
-      const uint32_t nblk = uint32_t((nvec + kColThreads * kColUnroll - 1) / (kColThreads * kColUnroll));
-      *nparts = int(nblk);
-      switch (g / 4) {
-        case 1: launch_col_fast<Tag, 1>(a, nblk, st); break;
-        case 2: launch_col_fast<Tag, 2>(a, nblk, st); break;
-        case 4: launch_col_fast<Tag, 4>(a, nblk, st); break;
-        case 8: launch_col_fast<Tag, 8>(a, nblk, st); break;
-        case 16: launch_col_fast<Tag, 16>(a, nblk, st); break;
-        case 32: launch_col_fast<Tag, 32>(a, nblk, st); break;
-        default: launch_col_fast<Tag, 64>(a, nblk, st); break;
-      }
-    } else {
+      launch_col_groups<Tag, false>(a, g, a.grid.qmax, a.grid.qmin, st, nparts);
+    } else if (!launch_col_long<Tag, false>(a, g, a.grid.qmax, a.grid.qmin, st, nparts)) {
       const int64_t ngroups = a.rows * (a.cols / g);
       const int nblk = int(std::min<int64_t>((ngroups + 3) / 4, 4096));
       *nparts = nblk;
@@ -499,18 +659,6 @@ int launch_rtn_typed(const RtnArgs& a, hipStream_t st, int* nparts) {
   return CAFEQ_OK;
 }
 
-template <typename Tag, int LPG>
-void launch_col_minmax_fast(const RtnArgs& a, float levels, uint32_t nblk, hipStream_t st) {
-  using E = typename Tag::elem;
-  const uint32_t nvec = uint32_t(a.rows * a.cols / 4), cols4 = uint32_t(a.cols / 4);
-  if (a.ld == a.cols)
-    hipLaunchKernelGGL((rtn_col_minmax_fast<Tag, LPG, true>), dim3(nblk), dim3(kColThreads), 0, st, (const E*)a.W,
-                       nvec, cols4, a.ld, levels, (uint32_t*)a.codes, a.scales, a.mins, a.partial);
-  else
-    hipLaunchKernelGGL((rtn_col_minmax_fast<Tag, LPG, false>), dim3(nblk), dim3(kColThreads), 0, st, (const E*)a.W,
-                       nvec, cols4, a.ld, levels, (uint32_t*)a.codes, a.scales, a.mins, a.partial);
-}
-
 template <typename Tag>
 int launch_minmax_typed(const RtnArgs& a, float levels, hipStream_t st, int* nparts) {
   using E = typename Tag::elem;
@@ -519,19 +667,8 @@ int launch_minmax_typed(const RtnArgs& a, float levels, hipStream_t st, int* npa
   if (a.axis == CAFEQ_AXIS_COL) {
     const bool pow2 = (g & (g - 1)) == 0;
     if (pow2 && g >= 4 && g <= 256 && a.rows * a.cols / 4 < (int64_t(1) << 31)) {
-      const int64_t nvec = a.rows * a.cols / 4;
-      const uint32_t nblk = uint32_t((nvec + kColThreads * kColUnroll - 1) / (kColThreads * kColUnroll));
-      *nparts = int(nblk);
-      switch (g / 4) {
-        case 1: launch_col_minmax_fast<Tag, 1>(a, levels, nblk, st); break;
-        case 2: launch_col_minmax_fast<Tag, 2>(a, levels, nblk, st); break;
-        case 4: launch_col_minmax_fast<Tag, 4>(a, levels, nblk, st); break;
-        case 8: launch_col_minmax_fast<Tag, 8>(a, levels, nblk, st); break;
-        case 16: launch_col_minmax_fast<Tag, 16>(a, levels, nblk, st); break;
-        case 32: launch_col_minmax_fast<Tag, 32>(a, levels, nblk, st); break;
-        default: launch_col_minmax_fast<Tag, 64>(a, levels, nblk, st); break;
-      }
-    } else {
+      launch_col_groups<Tag, true>(a, g, levels, 0.f, st, nparts);
+    } else if (!launch_col_long<Tag, true>(a, g, levels, 0.f, st, nparts)) {
       const int64_t ngroups = a.rows * (a.cols / g);
       const int nblk = int(std::min<int64_t>((ngroups + 3) / 4, 4096));
       *nparts = nblk;
@@ -563,7 +700,7 @@ int launch_rtn_minmax(const RtnArgs& a, int bits, hipStream_t st) {
                                  : launch_minmax_typed<F32Tag>(a, levels, st, &nparts);
   if (rc != CAFEQ_OK) return rc;
   if (a.partial) {
-    hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, st, a.partial, nparts, a.err_sq);
+    hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(1024), 0, st, a.partial, nparts, a.err_sq);
     CAFEQ_CHECK_LAUNCH();
   }
   return CAFEQ_OK;
@@ -582,7 +719,7 @@ int launch_rtn(const RtnArgs& a, hipStream_t st) {
                                  : launch_rtn_typed<F32Tag>(a, st, &nparts);
   if (rc != CAFEQ_OK) return rc;
   if (a.partial) {
-    hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, st, a.partial, nparts, a.err_sq);
+    hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(1024), 0, st, a.partial, nparts, a.err_sq);
     CAFEQ_CHECK_LAUNCH();
   }
   return CAFEQ_OK;
