@@ -1094,8 +1094,11 @@ int launch_inverse256(const float* T, int nb, double* work, float* Tinv, float* 
   hipLaunchKernelGGL((bgemm_f64mfma_kernel<float, double>), dim3(grid), dim3(256), 0, st, Tinv, res, X64, K, 1.0, 0.0);
   hipLaunchKernelGGL(add64_kernel, dim3(unsigned((n + 255) / 256)), dim3(256), 0, st, X64, n, Tinv);
   CAFEQ_CHECK_LAUNCH();
-  if (rho_row && (rc = launch_rho(Tinv, K, nb, 1, rho_row, st))) return rc;
-  if (rho_col && (rc = launch_rho(Tinv, K, nb, 0, rho_col, st))) return rc;
+  RhoRequest rho[2];
+  int nrho = 0;
+  if (rho_row) rho[nrho++] = RhoRequest{Tinv, rho_row, 1};
+  if (rho_col) rho[nrho++] = RhoRequest{Tinv, rho_col, 0};
+  if (nrho && (rc = launch_split_planes_multi(nullptr, 0, K, nb, st, nullptr, 0, rho, nrho))) return rc;
   return CAFEQ_OK;
 }
 

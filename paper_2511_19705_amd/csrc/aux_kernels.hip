@@ -10,62 +10,13 @@ namespace cafeq {
 
 namespace {
 
-// rho[b*K + j]: squared norm of row j (by_row) or column j of P_b, summed in float64.  256 / K threads share a
-// line (K = 256: one each); they take its elements interleaved and meet in LDS, added in thread order.  A workgroup
-// takes nbk consecutive blocks.
-// With rG != null the workgroup also writes the sums of rho over groups of G axis indices (what rho_group_kernel
-// computes, in its arithmetic: lanes interleaved over a group's indices, then a wave sum):
-//   G <= K, G | K, nbk = 1: rG[(b rep + r) (K / G) + q] = sum over indices q G .. q G + G - 1 of block b, for each
-//                           of the rep row-blocks that share the block;
-//   G = nbk K <= 256, rep = 1: rG[workgroup] = sum over its nbk blocks.
-__global__ __launch_bounds__(256) void rho_kernel(const float* __restrict__ P, int K, int by_row,
-                                                   float* __restrict__ rho, float* __restrict__ rG, int G, int rep,
-                                                   int nbk) {
-  __shared__ double part[256];
-  __shared__ float line[256];
-  const int tpl = 256 / K;                       // threads per line: K is 32, 64, 128 or 256
-  // by_row: neighbouring threads share a row (their loads fall into the same cache lines);
-  // by column: neighbouring threads take neighbouring columns (coalesced rows)
-  const int j = by_row ? threadIdx.x / tpl : threadIdx.x % K;
-  const int s = by_row ? threadIdx.x % tpl : threadIdx.x / K;
-  for (int bb = 0; bb < nbk; ++bb) {
-    const size_t b = size_t(blockIdx.x) * nbk + bb;
-    const float* Pb = P + b * K * K;
-    double acc = 0;
-    for (int i = s; i < K; i += tpl) {
-      const float v = by_row ? Pb[j * K + i] : Pb[i * K + j];
-      acc += double(v) * v;
-    }
-    part[s * K + j] = acc;
-    __syncthreads();
-    if (threadIdx.x < K) {
-      double t = part[threadIdx.x];
-      for (int q = 1; q < tpl; ++q) t += part[q * K + threadIdx.x];
-      rho[b * K + threadIdx.x] = float(t);
-      if (rG) line[bb * K + threadIdx.x] = float(t);      // (rG set: nbk K <= 256)
-    }
-    __syncthreads();
-  }
-  if (rG == nullptr) return;                     // uniform
-  const int lane = threadIdx.x % kWave;
-  if (nbk > 1) {
-    if (threadIdx.x < kWave) {
-      float acc = 0.f;
-      for (int e = lane; e < G; e += kWave) acc += line[e];
-      acc = wave_sum(acc);
-      if (lane == 0) rG[blockIdx.x] = acc;
-    }
-    return;
-  }
-  const int ng = K / G;
-  for (int q = threadIdx.x / kWave; q < ng; q += 256 / kWave) {
-    float acc = 0.f;
-    for (int e = lane; e < G; e += kWave) acc += line[q * G + e];
-    acc = wave_sum(acc);
-    if (lane == 0)
-      for (int r = 0; r < rep; ++r) rG[(size_t(blockIdx.x) * rep + r) * ng + q] = acc;
-  }
-}
+// What the loss pass needs of the transform besides the weights, in one launch: operand planes (SplitJob) and the
+// squared norms of the inverse (RhoJob).  Workgroups of 1024 threads, one per (block, job); both kinds read a block's
+// k x k floats once, with every request in flight before the first use, so a workgroup costs one memory latency and not
+// one per 32 x k stage.  Measured against a split launch that walked the stages (and scanned the block once more for its
+// magnitude) after a rho launch of 256 threads per block: 144 blocks of 64
+// 6.9 + 5.7 -> 6.5 us, 72 blocks of 128 10.9 + 8.1 -> 8.2 us, 8 blocks of 32 3.8 + 2.9 -> 3.6 us.
+constexpr int kSplitThreads = 1024;
 
 // Operand planes of the fused core.  Element [out][in] of the k x k operand -- src_b (trans == 0) or
 // src_b^T (trans == 1) -- is split exactly into bfloat16 parts x = hi + mid + lo (+ a residual below
@@ -75,118 +26,238 @@ __global__ __launch_bounds__(256) void rho_kernel(const float* __restrict__ P, i
 // half h -> chunk 2*c2 + h, holding inputs 16*c2 + 8u + 4h + e at position 4u + e), the chunk stored
 // at chunk ^ ((out >> 2) & 3) (LDS bank swizzle).
 struct SplitJob { const float* src; uint16_t* dst; int trans, nplanes; float* fscale; int natural, texp; };   // fscale, texp: see below
-struct SplitJobs { SplitJob job[4]; int njobs, K; float* hdr; int64_t nhdr; };   // hdr: partial headers to reset (may be null)
 // A job with fscale != null writes TWO float16 planes instead: the block is first scaled by the power of
 // two that puts its largest magnitude into [2^texp, 2^(texp+1)) (14: the low parts stay normal numbers; 4: sums of
 // 128 products with operands below 2^4 stay below 2^16 -- the matrix cores take denormal float16 inputs exactly), then
 // x = hi + lo with both parts rounded to nearest; fscale[b] receives the factor that undoes the scale.
-// grid: (nb, njobs): one workgroup per (block, job) walks the K / 32 stages, so that the block's largest
-// magnitude (float16 jobs) is found once.
-constexpr int kSplitThreads = 1024;
+//
+// rho[b*K + j]: squared norm of row j (by_row) or column j of P_b, summed in float64.
+// With rG != null the workgroup also writes the sums of rho over groups of G axis indices (what rho_group_kernel
+// computes, lanes interleaved over a group's indices, then a wave sum):
+//   G <= K, G | K, nbk = 1: rG[(b rep + r) (K / G) + q] = sum over indices q G .. q G + G - 1 of block b, for each
+//                           of the rep row-blocks that share the block;
+//   G = nbk K <= 256, rep = 1: rG[workgroup] = sum over its nbk blocks (consecutive ones).
+struct RhoJob { const float* P; float* rho; float* rG; int by_row, G, rep, nbk; };
+struct SplitJobs {
+  SplitJob job[4]; RhoJob rho[2]; int njobs, nrho, nb;
+  float* hdr; int64_t nhdr;     // partial headers to reset (may be null)
+};
+
+template <int K>
+__device__ __forceinline__ void rho_body(const RhoJob& jb, const int nb, double* part /* [16][K] */, float* line /* [256] */) {
+  constexpr int LPR = K / 4, ROWS = kSplitThreads / LPR, NQ = K / ROWS > 0 ? K / ROWS : 1;   // lanes per row, rows per pass
+  const int tid = threadIdx.x, c = 4 * (tid % LPR), r0 = tid / LPR, lane = tid % kWave, wave = tid / kWave;
+  if (int64_t(blockIdx.x) * jb.nbk >= nb) return;
+  for (int bb = 0; bb < jb.nbk; ++bb) {
+    const size_t b = size_t(blockIdx.x) * jb.nbk + bb;
+    const float* Pb = jb.P + b * K * K;
+    float4 u[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int r = r0 + q * ROWS;
+      u[q] = r < K ? *reinterpret_cast<const float4*>(Pb + r * K + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    if (jb.by_row) {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        double t = double(u[q].x) * u[q].x + double(u[q].y) * u[q].y + double(u[q].z) * u[q].z + double(u[q].w) * u[q].w;
+#pragma unroll
+        for (int o = 1; o < LPR; o *= 2) t += __shfl_xor(t, o);
+        const int r = r0 + q * ROWS;
+        if (c == 0 && r < K) { jb.rho[b * K + r] = float(t); if (jb.rG) line[bb * K + r] = float(t); }   // (rG set: nbk K <= 256)
+      }
+    } else {
+      double t[4] = {0, 0, 0, 0};
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        t[0] += double(u[q].x) * u[q].x; t[1] += double(u[q].y) * u[q].y;
+        t[2] += double(u[q].z) * u[q].z; t[3] += double(u[q].w) * u[q].w;
+      }
+#pragma unroll
+      for (int o = LPR; o < kWave; o *= 2)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] += __shfl_xor(t[e], o);
+      if (lane < LPR)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) part[wave * K + c + e] = t[e];
+      __syncthreads();
+      if (tid < K) {
+        double s = part[tid];
+#pragma unroll
+        for (int w = 1; w < kSplitThreads / kWave; ++w) s += part[w * K + tid];
+        jb.rho[b * K + tid] = float(s);
+        if (jb.rG) line[bb * K + tid] = float(s);
+      }
+    }
+    __syncthreads();
+  }
+  if (jb.rG == nullptr) return;                  // uniform
+  if (jb.nbk > 1) {
+    if (wave == 0) {
+      float acc = 0.f;
+      for (int e = lane; e < jb.G; e += kWave) acc += line[e];
+      acc = wave_sum(acc);
+      if (lane == 0) jb.rG[blockIdx.x] = acc;
+    }
+    return;
+  }
+  const int ng = K / jb.G;
+  for (int q = wave; q < ng; q += kSplitThreads / kWave) {
+    float acc = 0.f;
+    for (int e = lane; e < jb.G; e += kWave) acc += line[q * jb.G + e];
+    acc = wave_sum(acc);
+    if (lane == 0)
+      for (int r = 0; r < jb.rep; ++r) jb.rG[(size_t(blockIdx.x) * jb.rep + r) * ng + q] = acc;
+  }
+}
+
+// grid: (nb, njobs + nrho, z): with z > 1 (few blocks) the K / 32 stages of a block go to a workgroup each.
+template <int K>
 __global__ __launch_bounds__(kSplitThreads) void split_planes_kernel(const SplitJobs js) {
-  // a stage's planes are assembled in LDS in their final order and leave as whole 16-byte vectors
-  __shared__ __align__(16) uint16_t lds[3 * 256 * 32];
-  const int K = js.K, nst = K / 32;
+  // stages' planes are assembled in LDS in their final order and leave as whole 16-byte vectors
+  constexpr int kLdsB = K == 32 ? 33 * 1024 : 64 * 1024;
+  __shared__ __align__(16) unsigned char lds[kLdsB];
+  __shared__ float wmx[kSplitThreads / 64], line[256];
+  constexpr int NST = K / 32, QPS = K * 8, NQ = (K * K / 4 + kSplitThreads - 1) / kSplitThreads;   // stages, quads a stage, a thread
+  const int tid = threadIdx.x;
   // partial headers that no workgroup of the core writes (slots nobody owns) must read as empty
   if (js.hdr) {
     const int64_t nthr = int64_t(gridDim.x) * gridDim.y * gridDim.z * kSplitThreads;
-    for (int64_t i = ((int64_t(blockIdx.z) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * kSplitThreads + threadIdx.x;
+    for (int64_t i = ((int64_t(blockIdx.z) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * kSplitThreads + tid;
          i < js.nhdr; i += nthr)
       js.hdr[i] = (i % kHdrFloats) == kHdrMref ? -INFINITY : 0.f;
+  }
+  if (int(blockIdx.y) >= js.njobs) {
+    if (blockIdx.z == 0) rho_body<K>(js.rho[int(blockIdx.y) - js.njobs], js.nb, reinterpret_cast<double*>(lds), line);
+    return;
   }
   const SplitJob jb = js.job[blockIdx.y];
   const int nplanes = jb.nplanes;
   const float* sb = jb.src + size_t(blockIdx.x) * K * K;
-  const int lk = 31 - __builtin_clz(unsigned(K));
+  const bool whole = gridDim.z == 1;
+  const int stage0 = whole ? 0 : int(blockIdx.z), nquad = whole ? K * K / 4 : QPS;
+  // a quad: four inputs that are adjacent in the plane (e = 0..3 of one (row, step, half, u)): one 128-bit load (or four
+  // coalesced loads of a transposed source) and one 64-bit LDS store per plane
+  float4 x[NQ];
+  float m = 0.f;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int i = tid + q * kSplitThreads, stage = stage0 + i / QPS, qd = i % QPS;
+    x[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (i < nquad) {
+      if (jb.trans) {
+        const float* p = sb + size_t(32 * stage + 4 * (qd / K)) * K + qd % K;
+        x[q] = make_float4(p[0], p[K], p[2 * K], p[3 * K]);
+      } else {
+        x[q] = *reinterpret_cast<const float4*>(sb + size_t(qd >> 3) * K + 32 * stage + 4 * (qd & 7));
+      }
+    }
+  }
   float hsc = 1.f;   // float16 job: the block's scale
   if (jb.fscale) {
-    __shared__ float wmx[kSplitThreads / 64];
-    float m = 0.f;
-    for (int e = threadIdx.x * 4; e < K * K; e += kSplitThreads * 4) {
-      const float4 v = *reinterpret_cast<const float4*>(sb + e);
-      m = fmaxf(fmaxf(m, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w)));
+    if (whole) {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+        m = fmaxf(fmaxf(m, fmaxf(fabsf(x[q].x), fabsf(x[q].y))), fmaxf(fabsf(x[q].z), fabsf(x[q].w)));
+    } else {
+      for (int e = tid * 4; e < K * K; e += kSplitThreads * 4) {
+        const float4 v = *reinterpret_cast<const float4*>(sb + e);
+        m = fmaxf(fmaxf(m, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w)));
+      }
     }
     m = cluster_allmax<64>(m);
-    if ((threadIdx.x & 63) == 0) wmx[threadIdx.x >> 6] = m;
+    if ((tid & 63) == 0) wmx[tid >> 6] = m;
     __syncthreads();
     m = 0.f;
+#pragma unroll
     for (int i = 0; i < kSplitThreads / 64; ++i) m = fmaxf(m, wmx[i]);
     int ex = int(__float_as_uint(m) >> 23);
     ex = ex < 32 ? 32 : (ex > 254 ? 254 : ex);
     hsc = __uint_as_float(uint32_t(254 + jb.texp - ex) << 23);             // 2^(texp - (ex - 127))
-    if (threadIdx.x == 0 && blockIdx.z == 0) jb.fscale[blockIdx.x] = __uint_as_float(uint32_t(ex - jb.texp) << 23);
+    if (tid == 0 && blockIdx.z == 0) jb.fscale[blockIdx.x] = __uint_as_float(uint32_t(ex - jb.texp) << 23);
   }
-  // (grid z: with few blocks the stages of a block are dealt out to several workgroups)
-  for (int stage = blockIdx.z; stage < nst; stage += gridDim.z) {
-    uint16_t* buf = lds;
-    uint16_t* db = jb.dst + (size_t(blockIdx.x) * nst + stage) * nplanes * K * 32;
-    // a thread takes four inputs that are adjacent in the plane (e = 0..3 of one (row, step, half, u)):
-    // one 128-bit load (or four coalesced loads of a transposed source) and one 64-bit LDS store per plane
-    for (int qd = threadIdx.x; qd < K * 8; qd += kSplitThreads) {
-      int out, wq;
-      float x[4];
-      if (jb.trans) {
-        out = qd & (K - 1); wq = qd >> lk;
+  const int spr = kLdsB / (nplanes * K * 64);                              // stages that fit the LDS (K = 256, three planes: one)
+  const int nstw = whole ? NST : 1;
+  for (int s0 = 0; s0 < nstw; s0 += spr) {
+    if (s0 > 0) __syncthreads();                                           // the stages before have left
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = sb[size_t(32 * stage + 4 * wq + e) * K + out];
-      } else {
-        out = qd >> 3; wq = qd & 7;
-        const float4 v = *reinterpret_cast<const float4*>(sb + size_t(out) * K + 32 * stage + 4 * wq);
-        x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
-      }
+    for (int q = 0; q < NQ; ++q) {
+      const int i = tid + q * kSplitThreads, sr = i / QPS - s0, qd = i % QPS;
+      if (i >= nquad || sr < 0 || sr >= spr) continue;
+      const int out = jb.trans ? qd % K : qd >> 3, wq = jb.trans ? qd / K : qd & 7;
       // quad wq holds inputs 4 wq .. 4 wq + 3 of the stage = 16 c2 + 8 u + 4 hh + e; with the natural order the
       // lane half takes eight consecutive inputs, i.e. the two middle bits swap their roles
       const int c2 = wq >> 2, u = jb.natural ? (wq & 1) : (wq >> 1) & 1, hh = jb.natural ? (wq >> 1) & 1 : (wq & 1);
       const int chunk = (2 * c2 + hh) ^ ((out >> 2) & 3);
-      const int at = out * 32 + chunk * 8 + 4 * u;
+      uint16_t* at = reinterpret_cast<uint16_t*>(lds) + sr * nplanes * K * 32 + out * 32 + chunk * 8 + 4 * u;
+      float y[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
       if (jb.fscale) {
         uint32_t hi[4], lo[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float y = x[e] * hsc;
-          const _Float16 a = _Float16(y);
-          const _Float16 b = _Float16(y - float(a));
+          const float z = y[e] * hsc;
+          const _Float16 a = _Float16(z);
+          const _Float16 b = _Float16(z - float(a));
           hi[e] = __builtin_bit_cast(uint16_t, a);
           lo[e] = __builtin_bit_cast(uint16_t, b);
         }
-        *reinterpret_cast<uint2*>(buf + at) = make_uint2(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16));
-        *reinterpret_cast<uint2*>(buf + at + K * 32) = make_uint2(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16));
+        *reinterpret_cast<uint2*>(at) = make_uint2(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16));
+        *reinterpret_cast<uint2*>(at + K * 32) = make_uint2(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16));
         continue;
       }
       for (int pl = 0; pl < nplanes; ++pl) {
         uint32_t part[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          uint32_t bits = __float_as_uint(x[e]);
+          uint32_t bits = __float_as_uint(y[e]);
           bits += 0x7FFFu + ((bits >> 16) & 1u);          // round to nearest even
           part[e] = bits >> 16;
-          x[e] -= __uint_as_float(part[e] << 16);
+          y[e] -= __uint_as_float(part[e] << 16);
         }
-        *reinterpret_cast<uint2*>(buf + at + pl * K * 32) = make_uint2(part[0] | (part[1] << 16), part[2] | (part[3] << 16));
+        *reinterpret_cast<uint2*>(at + pl * K * 32) = make_uint2(part[0] | (part[1] << 16), part[2] | (part[3] << 16));
       }
     }
     __syncthreads();
-    const uint4* s4 = reinterpret_cast<const uint4*>(buf);
-    uint4* d4 = reinterpret_cast<uint4*>(db);
-    for (int e = threadIdx.x; e < nplanes * K * 4; e += kSplitThreads) d4[e] = s4[e];
-    __syncthreads();   // drained before the next stage overwrites it
+    const int ns = nstw - s0 < spr ? nstw - s0 : spr;
+    const uint4* s4 = reinterpret_cast<const uint4*>(lds);
+    uint4* d4 = reinterpret_cast<uint4*>(jb.dst + (size_t(blockIdx.x) * NST + stage0 + s0) * nplanes * K * 32);
+    for (int e = tid; e < ns * nplanes * K * 4; e += kSplitThreads) d4[e] = s4[e];
   }
 }
 
-// rG[gi] = sum of rho over the axis indices of group gi (axis index a -> block (a/K)/rep, a%K).
-// One wave per group.
-__global__ __launch_bounds__(256) void rho_group_kernel(const float* __restrict__ rho, int K, int rep,
-                                                         int G, int64_t ngroups, float* __restrict__ rG) {
-  const int64_t gi = int64_t(blockIdx.x) * (blockDim.x / kWave) + threadIdx.x / kWave;
-  if (gi >= ngroups) return;
-  const int lane = threadIdx.x % kWave;
-  float acc = 0.f;
-  for (int e = lane; e < G; e += kWave) {
-    const int64_t a = gi * G + e;
-    acc += rho[((a / K) / rep) * K + a % K];
+// rG[gi] = sum of rho over the axis indices of group gi (axis index a -> block (a/K)/rep, a%K), wpg waves per group (1
+// or the whole workgroup).  Groups that launch_split_planes_multi's rho jobs do not cover: longer than 256, or across
+// row-blocks that share a block.  A whole channel is one group: with one wave its sum was a chain of up to naxis / 64
+// loads (61 us at 9216; now 4.9 us).
+constexpr int kRhoGroupWaves = 16;
+__global__ __launch_bounds__(kRhoGroupWaves * kWave) void rho_group_kernel(const float* __restrict__ rho, int lk, int rep,
+                                                                          int G, int64_t ngroups, int wpg,
+                                                                          float* __restrict__ rG) {
+  __shared__ double part[kRhoGroupWaves];
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, per = kRhoGroupWaves / wpg;
+  const int64_t gi = int64_t(blockIdx.x) * per + (wpg == 1 ? wave : 0);
+  const int nthr = wpg * kWave, t0 = wpg == 1 ? lane : int(threadIdx.x);
+  double acc = 0;
+  if (gi < ngroups) {
+#pragma unroll 8
+    for (int e = t0; e < G; e += nthr) {
+      const int64_t a = gi * G + e;
+      const unsigned q = unsigned(a >> lk), b = rep == 1 ? q : q / unsigned(rep);
+      acc += rho[(int64_t(b) << lk) + (a & ((1 << lk) - 1))];
+    }
   }
-  acc = wave_sum(acc);
-  if (lane == 0) rG[gi] = acc;
+#pragma unroll
+  for (int o = 1; o < kWave; o *= 2) acc += __shfl_xor(acc, o);
+  if (wpg > 1) {
+    if (lane == 0) part[wave] = acc;
+    __syncthreads();
+    acc = part[0];
+#pragma unroll
+    for (int w = 1; w < kRhoGroupWaves; ++w) acc += part[w];
+    if (threadIdx.x == 0) rG[gi] = float(acc);
+  } else if (lane == 0 && gi < ngroups) {
+    rG[gi] = float(acc);
+  }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -650,18 +721,35 @@ __global__ __launch_bounds__(256) void bgemm32_kernel(const float* __restrict__ 
 
 }  // namespace
 
+// Whether a rho request can also form the group sums of rho_group_kernel for groups of G axis indices.
+bool rho_groups_inline(int K, int nb, int G, int rep) {
+  if (G >= 1 && G <= K) return K % G == 0;
+  return rep == 1 && G <= 256 && G % K == 0 && nb % (G / K) == 0;
+}
 int launch_split_planes_multi(const SplitRequest* req, int n, int K, int nb, hipStream_t st, float* hdr,
-                              int64_t nslot) {
+                              int64_t nslot, const RhoRequest* rho, int nrho) {
+  if (n > 4 || nrho > 2) return CAFEQ_ERR_INVALID_ARG;
   SplitJobs js;
-  js.njobs = n; js.K = K; js.hdr = hdr; js.nhdr = nslot * kHdrFloats;
-  for (int i = 0; i < n && i < 4; ++i) {
+  js.njobs = n; js.nrho = nrho; js.nb = nb; js.hdr = hdr; js.nhdr = nslot * kHdrFloats;
+  for (int i = 0; i < n; ++i) {
     js.job[i].src = req[i].src; js.job[i].dst = req[i].dst;
     js.job[i].trans = req[i].trans; js.job[i].nplanes = req[i].fscale ? 2 : req[i].nplanes;
     js.job[i].fscale = req[i].fscale; js.job[i].natural = req[i].natural; js.job[i].texp = req[i].texp;
   }
+  for (int i = 0; i < nrho; ++i) {
+    if (rho[i].rG && !rho_groups_inline(K, nb, rho[i].G, rho[i].rep)) return CAFEQ_ERR_INVALID_ARG;
+    js.rho[i] = RhoJob{rho[i].P, rho[i].rho, rho[i].rG, rho[i].by_row, rho[i].G, rho[i].rep,
+                       rho[i].rG && rho[i].G > K ? rho[i].G / K : 1};
+  }
   // one workgroup per (block, job) when those fill the chip; else one per (block, job, stage)
-  const int zsplit = nb * n >= 128 ? 1 : K / 32;
-  hipLaunchKernelGGL(split_planes_kernel, dim3(nb, n, zsplit), dim3(kSplitThreads), 0, st, js);
+  const dim3 grid(nb, n + nrho, n == 0 || nb * n >= 128 ? 1 : K / 32);
+  switch (K) {
+    case 32: hipLaunchKernelGGL(split_planes_kernel<32>, grid, dim3(kSplitThreads), 0, st, js); break;
+    case 64: hipLaunchKernelGGL(split_planes_kernel<64>, grid, dim3(kSplitThreads), 0, st, js); break;
+    case 128: hipLaunchKernelGGL(split_planes_kernel<128>, grid, dim3(kSplitThreads), 0, st, js); break;
+    case 256: hipLaunchKernelGGL(split_planes_kernel<256>, grid, dim3(kSplitThreads), 0, st, js); break;
+    default: return CAFEQ_ERR_UNSUPPORTED;
+  }
   CAFEQ_CHECK_LAUNCH();
   return CAFEQ_OK;
 }
@@ -669,21 +757,10 @@ int launch_split_planes(const float* src, int K, int nb, int trans, int nplanes,
   SplitRequest r{src, dst, trans, nplanes};
   return launch_split_planes_multi(&r, 1, K, nb, st);
 }
-// Whether launch_rho can also form the group sums of rho_group_kernel for groups of G axis indices.
-bool rho_groups_inline(int K, int nb, int G, int rep) {
-  if (G >= 1 && G <= K) return K % G == 0;
-  return rep == 1 && G <= 256 && G % K == 0 && nb % (G / K) == 0;
-}
-int launch_rho(const float* P, int K, int nb, int by_row, float* rho, hipStream_t st, float* rG, int G, int rep) {
-  if (rG && !rho_groups_inline(K, nb, G, rep)) return CAFEQ_ERR_INVALID_ARG;
-  const int nbk = rG && G > K ? G / K : 1;
-  hipLaunchKernelGGL(rho_kernel, dim3(nb / nbk), dim3(256), 0, st, P, K, by_row, rho, rG, G, rep, nbk);
-  CAFEQ_CHECK_LAUNCH();
-  return CAFEQ_OK;
-}
 int launch_rho_groups(const float* rho, int K, int rep, int G, int64_t ngroups, float* rG, hipStream_t st) {
-  hipLaunchKernelGGL(rho_group_kernel, dim3(unsigned((ngroups + 3) / 4)), dim3(256), 0, st, rho, K, rep, G,
-                     ngroups, rG);
+  const int wpg = G >= 1024 ? kRhoGroupWaves : 1, per = kRhoGroupWaves / wpg;
+  hipLaunchKernelGGL(rho_group_kernel, dim3(unsigned((ngroups + per - 1) / per)), dim3(kRhoGroupWaves * kWave), 0, st, rho,
+                     31 - __builtin_clz(unsigned(K)), rep, G, ngroups, wpg, rG);
   CAFEQ_CHECK_LAUNCH();
   return CAFEQ_OK;
 }

@@ -1001,13 +1001,6 @@ int cafeq_proxy_loss_fwd_bwd(const cafeq_mat* W, const cafeq_xform* x, const caf
   const float beta = beta_for(cfg, grid);
   const bool f16 = !asym && core_forward_f16(K, gp.Gk, cfg->bits);
 
-  // rho per axis index, its sums per segment-level group (the loss sweep) and per group (the gradient pass)
-  // (groups inside a block, or of a few whole blocks: the same launch)
-  const bool rg_inline = rho_groups_inline(K, nb, gp.Gk, x->rep);
-  if ((rc = launch_rho(x->Tinv, K, nb, col ? 1 : 0, w.rho, st, rg_inline ? w.m.rG : nullptr, gp.Gk, x->rep))) return rc;
-  if (!rg_inline && (rc = launch_rho_groups(w.rho, K, x->rep, gp.Gk, naxis / gp.Gk, w.m.rG, st))) return rc;
-  if (gp.gspan > 1 && (rc = launch_rho_groups(w.rho, K, x->rep, gp.G, naxis / gp.G, w.m.rGreal, st))) return rc;
-
   CoreParams p;
   fill_common(&p, W, pl, x->rep);
   // forward operand [out][in]: T^T (COL) or T (ROW); inverse operand: Tinv^T or Tinv
@@ -1015,7 +1008,13 @@ int cafeq_proxy_loss_fwd_bwd(const cafeq_mat* W, const cafeq_xform* x, const caf
     // (prepared weights: float16 planes for both operands, scaled so that the rounding error fits float16)
     const SplitRequest req[2] = {{x->T, w.m.pfwd, col ? 1 : 0, kFwdPlanes, f16 ? w.m.fs : nullptr, v2 ? 1 : 0, v2 ? 4 : 14},
                                  {x->Tinv, w.m.pinv, col ? 1 : 0, kInvPlanes, v2 ? w.m.fsi : nullptr, 0, 4}};
-    if ((rc = launch_split_planes_multi(req, 2, K, nb, st, w.slot_hdr, pl.nslot))) return rc;
+    // rho per axis index, its sums per segment-level group (the loss sweep) and per group (the gradient pass)
+    // (groups inside a block, or of a few whole blocks: the same launch)
+    const bool rg_inline = rho_groups_inline(K, nb, gp.Gk, x->rep);
+    const RhoRequest rho{x->Tinv, w.rho, col ? 1 : 0, rg_inline ? w.m.rG : nullptr, gp.Gk, x->rep};
+    if ((rc = launch_split_planes_multi(req, 2, K, nb, st, w.slot_hdr, pl.nslot, &rho, 1))) return rc;
+    if (!rg_inline && (rc = launch_rho_groups(w.rho, K, x->rep, gp.Gk, naxis / gp.Gk, w.m.rG, st))) return rc;
+    if (grad && gp.gspan > 1 && (rc = launch_rho_groups(w.rho, K, x->rep, gp.G, naxis / gp.G, w.m.rGreal, st))) return rc;
   }
   p.Afwd = w.m.pfwd; p.Ainv = w.m.pinv; p.fscale = f16 ? w.m.fs : nullptr; p.fscale_inv = v2 ? w.m.fsi : nullptr;
   p.grid = grid; p.do_inverse = 1; p.do_grad = pp.fused ? 1 : 0; p.loss_kind = kLossSur; p.beta = beta;

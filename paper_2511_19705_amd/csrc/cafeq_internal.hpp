@@ -88,12 +88,12 @@ int launch_loss_prepared_pair(int G, const CoreParams& pa, const CoreParams& pb,
 // texp: a float16 job scales the block's largest magnitude into [2^texp, 2^(texp+1)).
 struct SplitRequest { const float* src; uint16_t* dst; int trans, nplanes; float* fscale = nullptr; int natural = 0; int texp = 14; };
 int launch_split_planes(const float* src, int K, int nb, int trans, int nplanes, uint16_t* dst, hipStream_t st);
-// up to four splits in one launch; hdr (may be null): nslot partial headers reset by the same launch
-int launch_split_planes_multi(const SplitRequest* req, int n, int K, int nb, hipStream_t st, float* hdr = nullptr,
-                              int64_t nslot = 0);
+// squared row / column norms of the blocks of P, and (rG != null; rho_groups_inline) their sums over groups of G indices
+struct RhoRequest { const float* P; float* rho; int by_row; float* rG = nullptr; int G = 0, rep = 1; };
 bool rho_groups_inline(int K, int nb, int G, int rep);
-int launch_rho(const float* P, int K, int nb, int by_row, float* rho, hipStream_t st, float* rG = nullptr, int G = 0,
-               int rep = 1);   // rG: also the sums over groups of G indices, where rho_groups_inline (see rho_kernel)
+// up to four splits and two rho requests in one launch; hdr (may be null): nslot partial headers reset by the same launch
+int launch_split_planes_multi(const SplitRequest* req, int n, int K, int nb, hipStream_t st, float* hdr = nullptr,
+                              int64_t nslot = 0, const RhoRequest* rho = nullptr, int nrho = 0);
 int launch_rho_groups(const float* rho, int K, int rep, int G, int64_t ngroups, float* rG, hipStream_t st);
 int launch_reduce_grad(const CoreParams& p, int K, int G, bool fused, int nb, int transpose_out,
                        const double* lse_ms, const float* member_ref, float* out, hipStream_t st);

@@ -429,8 +429,11 @@ int launch_block_inverse(const float* T, int K, int nb, double* work, float* Tin
     case 256: return launch_inverse256(T, nb, work, Tinv, rho_row, rho_col, status, false, st);
   }
   if (rc) return rc;
-  if (rho_row && (rc = launch_rho(Tinv, K, nb, 1, rho_row, st))) return rc;
-  if (rho_col && (rc = launch_rho(Tinv, K, nb, 0, rho_col, st))) return rc;
+  RhoRequest rho[2];
+  int nrho = 0;
+  if (rho_row) rho[nrho++] = RhoRequest{Tinv, rho_row, 1};
+  if (rho_col) rho[nrho++] = RhoRequest{Tinv, rho_col, 0};
+  if (nrho && (rc = launch_split_planes_multi(nullptr, 0, K, nb, st, nullptr, 0, rho, nrho))) return rc;
   return CAFEQ_OK;
 }
 
