@@ -466,7 +466,6 @@ __global__ __launch_bounds__(512) void gj_spd256_kernel(const GjArgs a) {
   __shared__ int deadflag, ready;        // ready: panels handed over so far
   __shared__ float wred[8];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, ln = lane & 31, h = lane >> 5;
-  if (a.need && !a.need[b]) return;       // uniform over the workgroup
   const int rbase = 32 * w + 4 * h;       // row of register r: rbase + 8 (r / 4) + r % 4
   floatx16 reg[8];
   if (a.partial == nullptr || a.sum32) {
@@ -725,9 +724,14 @@ __global__ __launch_bounds__(256) void sum_r_init_c_kernel(const float* __restri
 // of K = 256 requested at the start measured the same.)  Operand layouts: lane l gives A[i = l % 16][k = l / 16] and B[k = l / 16][j = l % 16];
 // its four results are rows l / 16 + 4 r (r = 0..3) of column l % 16.
 typedef double doublex4 __attribute__((ext_vector_type(4)));
-template <typename AT, typename BT>
+// What becomes of the product: kF64Plain C = alpha A B + beta C; kF64Residual C = I - A B; kF64Step F = A + A B and
+// kF64Solve F = I - (C + A B), rounded to float32 once (launches of their own for the identity, the sum and the difference
+// took 5 us each).
+enum { kF64Plain, kF64Residual, kF64Step, kF64Solve };
+template <typename AT, typename BT, int EPI = kF64Plain>
 __global__ __launch_bounds__(256) void bgemm_f64mfma_kernel(const AT* __restrict__ A, const BT* __restrict__ B,
-                                                             double* __restrict__ C, int K, double alpha, double beta) {
+                                                             double* __restrict__ C, int K, double alpha, double beta,
+                                                             float* __restrict__ F) {
   constexpr int LC = 64;
   __shared__ double sa[32][LC + 2];   // [i][l]   (row strides chosen so that the operand reads of 32 lanes cover
   __shared__ double sb[LC][80];       // [l][j]    all banks once)
@@ -786,35 +790,49 @@ __global__ __launch_bounds__(256) void bgemm_f64mfma_kernel(const AT* __restrict
   for (int t = 0; t < 2; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      double* dst = Cb + (i0 + 16 * ti + lk + 4 * r) * K + j0 + 16 * (tj0 + t) + li;
-      *dst = alpha * acc[t][r] + (beta != 0.0 ? beta * *dst : 0.0);
+      const int i = i0 + 16 * ti + lk + 4 * r, j = j0 + 16 * (tj0 + t) + li, at = i * K + j;
+      if constexpr (EPI == kF64Plain) {
+        Cb[at] = alpha * acc[t][r] + (beta != 0.0 ? beta * Cb[at] : 0.0);
+      } else if constexpr (EPI == kF64Residual) {
+        Cb[at] = (i == j ? 1.0 : 0.0) - acc[t][r];
+      } else if constexpr (EPI == kF64Step) {
+        F[size_t(b) * K * K + at] = float(double(Ab[at]) + acc[t][r]);
+      } else {
+        F[size_t(b) * K * K + at] = float((i == j ? 1.0 : 0.0) - (acc[t][r] + Cb[at]));
+      }
     }
 }
 
 // S64, R64 and a second copy of R64 (the residual's starting value) from the chunk partials; optionally S64
 // rounded to float32.
+// (eight partials of both matrices in flight per thread, one element each: with one at a time and eight elements a thread
+// the 34 MB of the 9B-shaped (V, O) pair took 20 us, now 8)
 __global__ __launch_bounds__(256) void sum_partials64_kernel(const float* __restrict__ partial, int nz, int K,
                                                               double* __restrict__ S64, double* __restrict__ R64,
                                                               double* __restrict__ res, float* __restrict__ S32) {
-  const int b = blockIdx.x;
-  for (int e = blockIdx.y * 256 + threadIdx.x; e < K * K; e += gridDim.y * 256) {
-    const float* p = partial + size_t(b) * nz * 2 * K * K + e;
-    double s = 0, r = 0;
-    for (int z = 0; z < nz; ++z) {
-      s += double(p[size_t(z) * 2 * K * K]);
-      r += double(p[size_t(z) * 2 * K * K + size_t(K) * K]);
-    }
-    S64[size_t(b) * K * K + e] = s;
-    if (S32) S32[size_t(b) * K * K + e] = float(s);
-    R64[size_t(b) * K * K + e] = r;
-    res[size_t(b) * K * K + e] = r;
+  const int b = blockIdx.x, e = blockIdx.y * 256 + threadIdx.x;   // (gridDim.y * 256 = K * K)
+  const size_t kk = size_t(K) * K;
+  const float* p = partial + size_t(b) * nz * 2 * kk + e;
+  double s = 0, r = 0;
+  int z = 0;
+  for (; z + 8 <= nz; z += 8) {
+    float u[8], v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) { u[q] = p[(z + q) * 2 * kk]; v[q] = p[((z + q) * 2 + 1) * kk]; }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) { s += double(u[q]); r += double(v[q]); }
   }
+  for (; z < nz; ++z) { s += double(p[z * 2 * kk]); r += double(p[(z * 2 + 1) * kk]); }
+  S64[b * kk + e] = s;
+  if (S32) S32[b * kk + e] = float(s);
+  R64[b * kk + e] = r;
+  res[b * kk + e] = r;
 }
 // ---- blocks of 256 near a (scaled) rotation: Newton-Schulz rounds on the matrix cores before any elimination.
 // X0 = T^T / alpha with alpha = ||T_b||_F^2 / K is the exact inverse of a rotation scaled by any factor and a
 // good start near one.  grid (nb, K / 32): workgroup (b, s) writes rows 32 s .. of X0 (columns of T).
-__global__ __launch_bounds__(1024) void ns_init_kernel(const float* __restrict__ T, float* __restrict__ X0,
-                                                       float* __restrict__ X0copy, int K) {
+__global__ __launch_bounds__(1024) void ns_init_kernel(const float* __restrict__ T, float* __restrict__ X0, int K) {
   __shared__ float tile[256 * 33];
   __shared__ double red[16];
   const int b = blockIdx.x, s0 = blockIdx.y * 32, tid = threadIdx.x;
@@ -836,68 +854,188 @@ __global__ __launch_bounds__(1024) void ns_init_kernel(const float* __restrict__
   for (int w = 0; w < 16; ++w) f2 += red[w];
   const float inv_alpha = f2 > 0 ? float(double(K) / f2) : 0.f;
   float* Xb = X0 + size_t(b) * K * K;
-  float* Xc = X0copy + size_t(b) * K * K;      // (where the rounds' result lands: a block that needs none keeps X0)
   for (int e = tid; e < K * 32; e += 1024) {
     const int ii = e / K, j = e % K;
-    const float x = tile[j * 33 + ii] * inv_alpha;
-    Xb[size_t(s0 + ii) * K + j] = x;
-    Xc[size_t(s0 + ii) * K + j] = x;
+    Xb[size_t(s0 + ii) * K + j] = tile[j * 33 + ii] * inv_alpha;
   }
 }
-// F = ||I - Y_b||_F per block, Y = T X.  mode 0 (after the first product): skip[b] = 1 when !(F <= thresh) -- such a
-// block is hopeless for the rounds --, 2 when F <= done_thresh already (a rotation: the start is the inverse), else 0;
-// the rounds leave blocks with skip != 0 alone.  mode 1 (after the last product): need[b] = skip[b] == 1 ||
-// !(F <= thresh): the elimination takes those, the others are done (status 0).  Comparisons written so that a NaN
-// fails them.  grid: nb.
-__global__ __launch_bounds__(1024) void ns_flag_kernel(const float* __restrict__ Y, int K, int mode, float thresh,
-                                                       float done_thresh, int* __restrict__ skip,
-                                                       int* __restrict__ need, int* __restrict__ status) {
-  __shared__ double red[16];
-  const int b = blockIdx.x, tid = threadIdx.x;
-  if (mode == 1 && skip[b] == 1) {
-    if (tid == 0) need[b] = 1;
-    return;
-  }
-  const float* Yb = Y + size_t(b) * K * K;
-  double acc = 0;
-  for (int e = tid * 4; e < K * K; e += 1024 * 4) {
-    const float4 v = *reinterpret_cast<const float4*>(Yb + e);
-    const int r = e / K, c = e % K;
-    const double d0 = double(v.x) - (r == c ? 1.0 : 0.0), d1 = double(v.y) - (r == c + 1 ? 1.0 : 0.0);
-    const double d2 = double(v.z) - (r == c + 2 ? 1.0 : 0.0), d3 = double(v.w) - (r == c + 3 ? 1.0 : 0.0);
-    acc += d0 * d0 + d1 * d1 + d2 * d2 + d3 * d3;
-  }
-  for (int m = 1; m < 64; m <<= 1) acc += __shfl_xor(acc, m);
-  if ((tid & 63) == 0) red[tid >> 6] = acc;
-  __syncthreads();
-  if (tid == 0) {
-    double f2 = 0;
-  for (int w = 0; w < 16; ++w) f2 += red[w];
-    const bool ok = f2 <= double(thresh) * double(thresh);
-    if (mode == 0) {
-      skip[b] = !ok ? 1 : (f2 <= double(done_thresh) * double(done_thresh) ? 2 : 0);
-    } else {
-      need[b] = ok ? 0 : 1;
-      if (ok && status) status[b] = 0;
+// One Newton round X' = X + X R, R = I - T X, of blocks of 256 in one launch: columns j of X' need columns j of R and all
+// of X, columns j of R those of X and all of T, so a workgroup owns sixteen columns and streams T and X as matrix
+// operands with no exchange between workgroups.  Eight waves, 32 rows each: a wave holds 16 rows of T (64 floats a lane)
+// per tile, scales each row by a power of two and splits it into two float16 parts; the slice of X sits in LDS the
+// same way (scaled per column), three part products (22 significant bits: R carries an error of about 1e-7 an entry).  The
+// correction X R, second order in what its rounding loses, takes one part each.  What bounds it is the latency of 512 KB
+// of operands per workgroup, and splitting them: 21 us for 8 blocks, 3-5 us when it copies.  (As two batched products on
+// the float32 matrix pipe, with launches that measured the residual, a warm start took 12 launches and 107 us, now 5 and
+// 70 us; 8 Adam steps on the 9B-shaped (V, O) pair 3700 -> 3050 us with the cold start's elimination avoided.)
+//   cur[b][16]: the slices' shares of ||R||_F^2.  prev: those of the round before (null: none).  A block whose last measured
+//   residual was below 1e-3 (its correction left less than 1e-6 and the parts' 3e-5) or is beyond any contraction to
+//   count on (||R||_F >= 3, a NaN) is copied, with its residual.  An entry that leaves float16's range makes R infinite.
+constexpr int kNsSlices = 16;
+constexpr float kNsAccept2 = 2.25e-4f;   // ||R||_F^2 before the last correction: 1.5e-2 leaves 2.3e-4 and the parts' 3e-5
+__global__ __launch_bounds__(512) void ns256_round_kernel(const float* __restrict__ T, const float* __restrict__ X,
+                                                          float* __restrict__ Xout, int nb, const float* __restrict__ prev,
+                                                          float* __restrict__ cur) {
+  constexpr int K = 256, SL = K / kNsSlices, LD = K + 8;
+  typedef float floatx4 __attribute__((ext_vector_type(4)));
+  __shared__ __align__(16) uint16_t xh[SL * LD], xl[SL * LD], rh[SL * LD];   // X^T in two parts, R^T in one: [column][row]
+  __shared__ float cmax[8][SL], red[8];
+  const int b = int(blockIdx.x) % nb, sl = int(blockIdx.x) / nb, j0 = sl * SL;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ln = lane & 15, lg = lane >> 4;
+  const float* Tb = T + size_t(b) * K * K;
+  const float* Xb = X + size_t(b) * K * K;
+  float* Ob = Xout + size_t(b) * K * K;
+  // this thread's eight elements of the slice
+  const int l = tid >> 1, c = (tid & 1) * 8;
+  const float4 s0 = *reinterpret_cast<const float4*>(Xb + l * K + j0 + c), s1 = *reinterpret_cast<const float4*>(Xb + l * K + j0 + c + 4);
+  if (prev) {
+    float fp = 0.f;
+    for (int q = 0; q < kNsSlices; ++q) fp += prev[b * kNsSlices + q];
+    if (!(fp < 9.f) || fp <= 1e-6f) {            // uniform over the block
+      *reinterpret_cast<float4*>(Ob + l * K + j0 + c) = s0;
+      *reinterpret_cast<float4*>(Ob + l * K + j0 + c + 4) = s1;
+      if (tid == 0) cur[b * kNsSlices + sl] = sl == 0 ? fp : 0.f;
+      return;
     }
   }
-}
-__global__ __launch_bounds__(256) void eye64_kernel(double* __restrict__ X, int K, int64_t n) {
-  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (i >= n) return;
-  const int e = int(i % (int64_t(K) * K));
-  X[i] = (e / K == e % K) ? 1.0 : 0.0;
-}
-__global__ __launch_bounds__(256) void add64_kernel(const double* __restrict__ D, int64_t n, float* __restrict__ X) {
-  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (i < n) X[i] = float(double(X[i]) + D[i]);
-}
-__global__ __launch_bounds__(256) void eye_minus_kernel(const double* __restrict__ X, int K, int64_t n,
-                                                         float* __restrict__ C) {
-  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (i >= n) return;
-  const int e = int(i % (int64_t(K) * K));
-  C[i] = float(((e / K == e % K) ? 1.0 : 0.0) - X[i]);
+  // 16 rows of a matrix as A operands: lane (row ln, quarter lg) takes eight consecutive floats of every 32
+  auto load_rows = [&](const float* M, int i, float4 (&u)[16]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const float* p = M + (i + ln) * K + 32 * s + 8 * lg;
+      u[2 * s] = *reinterpret_cast<const float4*>(p);
+      u[2 * s + 1] = *reinterpret_cast<const float4*>(p + 4);
+    }
+  };
+  // the power of two that puts a row's largest magnitude into [2^6, 2^7), and its inverse
+  auto pow2_scale = [&](float m, float* inv) __attribute__((always_inline)) {
+    int ex = int(__float_as_uint(m) >> 23);
+    ex = ex < 40 ? 40 : (ex > 220 ? 220 : ex);
+    *inv = __uint_as_float(uint32_t(ex - 6) << 23);
+    return __uint_as_float(uint32_t(254 + 6 - ex) << 23);
+  };
+  auto row_scale = [&](const float4 (&u)[16], float* inv) __attribute__((always_inline)) {
+    float m = 0.f;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) m = fmaxf(fmaxf(m, fmaxf(fabsf(u[q].x), fabsf(u[q].y))), fmaxf(fabsf(u[q].z), fabsf(u[q].w)));
+    m = fmaxf(m, __shfl_xor(m, 16));
+    m = fmaxf(m, __shfl_xor(m, 32));
+    return pow2_scale(m, inv);
+  };
+  const int i0 = 32 * wave;
+  float4 t0[16], t1[16];
+  load_rows(Tb, i0, t0);
+  load_rows(Tb, i0 + 16, t1);
+  __builtin_amdgcn_sched_barrier(0);
+  float xs[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+  {
+    float m[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      m[e] = fabsf(xs[e]);
+#pragma unroll
+      for (int o = 2; o < 64; o *= 2) m[e] = fmaxf(m[e], __shfl_xor(m[e], o));
+    }
+    if (lane < 2)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) cmax[wave][c + e] = m[e];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    float m = cmax[0][c + e];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) m = fmaxf(m, cmax[w][c + e]);
+    float inv;
+    const float y = xs[e] * pow2_scale(m, &inv);
+    const _Float16 hi = _Float16(y), lo = _Float16(y - float(hi));
+    xh[(c + e) * LD + l] = __builtin_bit_cast(uint16_t, hi);
+    xl[(c + e) * LD + l] = __builtin_bit_cast(uint16_t, lo);
+  }
+  float inv_c;                                   // this lane's column
+  {
+    float m = cmax[0][ln];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) m = fmaxf(m, cmax[w][ln]);
+    (void)pow2_scale(m, &inv_c);
+  }
+  __syncthreads();
+  float f2 = 0.f;
+  auto residual = [&](const float4 (&u)[16], int i) __attribute__((always_inline)) {
+    float inv_r;
+    const float sc = row_scale(u, &inv_r);
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f}, low = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const float y[8] = {u[2 * s].x * sc, u[2 * s].y * sc, u[2 * s].z * sc, u[2 * s].w * sc,
+                          u[2 * s + 1].x * sc, u[2 * s + 1].y * sc, u[2 * s + 1].z * sc, u[2 * s + 1].w * sc};
+      halfx8 ah, al;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        ah[e] = _Float16(y[e]);
+        al[e] = _Float16(y[e] - float(ah[e]));
+      }
+      const halfx8 bh = as_halfx8(*reinterpret_cast<const uintx4*>(xh + ln * LD + 32 * s + 8 * lg));
+      const halfx8 bl = as_halfx8(*reinterpret_cast<const uintx4*>(xl + ln * LD + 32 * s + 8 * lg));
+      low = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, bh, low, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bh, acc, 0, 0, 0);
+      low = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bl, low, 0, 0, 0);
+    }
+    // element r: row i + 4 lg + r, column j0 + ln
+    float rv[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float back = __shfl(inv_r, 4 * lg + r) * inv_c;
+      rv[r] = (i + 4 * lg + r == j0 + ln ? 1.f : 0.f) - (acc[r] + low[r]) * back;
+      f2 = fmaf(rv[r], rv[r], f2);
+    }
+    uint32_t p[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) p[r] = __builtin_bit_cast(uint16_t, _Float16(rv[r] * 0x1p14f));
+    *reinterpret_cast<uint2*>(rh + ln * LD + i + 4 * lg) = make_uint2(p[0] | (p[1] << 16), p[2] | (p[3] << 16));
+  };
+  // (the rows of X for the correction are requested as soon as the rows of T have left their registers)
+  residual(t0, i0);
+  __builtin_amdgcn_sched_barrier(0);
+  load_rows(Xb, i0, t0);
+  __builtin_amdgcn_sched_barrier(0);
+  residual(t1, i0 + 16);
+  __builtin_amdgcn_sched_barrier(0);
+  load_rows(Xb, i0 + 16, t1);
+  float old[8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) old[r] = Xb[(i0 + 16 * (r / 4) + 4 * lg + r % 4) * K + j0 + ln];
+  __builtin_amdgcn_sched_barrier(0);
+  f2 = wave_sum(f2);
+  if (lane == 0) red[wave] = f2;
+  __syncthreads();
+  if (tid == 0) {
+    float t = red[0];
+    for (int w = 1; w < 8; ++w) t += red[w];
+    cur[b * kNsSlices + sl] = t;
+  }
+  auto correct = [&](const float4 (&u)[16], int i, const float* o) __attribute__((always_inline)) {
+    float inv_r;
+    const float sc = row_scale(u, &inv_r);
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const float y[8] = {u[2 * s].x * sc, u[2 * s].y * sc, u[2 * s].z * sc, u[2 * s].w * sc,
+                          u[2 * s + 1].x * sc, u[2 * s + 1].y * sc, u[2 * s + 1].z * sc, u[2 * s + 1].w * sc};
+      halfx8 ah;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) ah[e] = _Float16(y[e]);
+      const halfx8 bh = as_halfx8(*reinterpret_cast<const uintx4*>(rh + ln * LD + 32 * s + 8 * lg));
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bh, acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float back = __shfl(inv_r, 4 * lg + r) * 0x1p-14f;
+      Ob[(i + 4 * lg + r) * K + j0 + ln] = fmaf(acc[r], back, o[r]);
+    }
+  };
+  correct(t0, i0, old);
+  correct(t1, i0 + 16, old + 4);
 }
 
 }  // namespace
@@ -1017,7 +1155,7 @@ int launch_gj_solve(int K, int nb, int nz, const float* partial, double* work, f
     // few blocks (always so for K = 256 shapes): the sums over the chunk partials are formed by the whole chip
     // (K == 256 does not use the float32 scratch R otherwise: it holds the rounded sum the elimination reads)
     float* S32 = K == 256 ? R : nullptr;
-    hipLaunchKernelGGL(sum_partials64_kernel, dim3(nb, 32), dim3(256), 0, st, partial, nz, K, S64, R64, res, S32);
+    hipLaunchKernelGGL(sum_partials64_kernel, dim3(nb, K * K / 256), dim3(256), 0, st, partial, nz, K, S64, R64, res, S32);
     CAFEQ_CHECK_LAUNCH();
     a.sum64 = S64;
     a.sum32 = S32;
@@ -1030,69 +1168,54 @@ int launch_gj_solve(int K, int nb, int nz, const float* partial, double* work, f
     return launch_bgemm(false, false, Sinv, R, out, K, nb, -1.f, 1.f, st);
   }
   const unsigned grid = unsigned(nb) * (K / 32) * (K / 64);
-  hipLaunchKernelGGL((bgemm_f64mfma_kernel<float, double>), dim3(grid), dim3(256), 0, st, Sinv, R64, X64, K, 1.0, 0.0);
-  hipLaunchKernelGGL((bgemm_f64mfma_kernel<double, double>), dim3(grid), dim3(256), 0, st, S64, X64, res, K, -1.0, 1.0);
-  hipLaunchKernelGGL((bgemm_f64mfma_kernel<float, double>), dim3(grid), dim3(256), 0, st, Sinv, res, X64, K, 1.0, 1.0);
-  const int64_t n = int64_t(mat);
-  hipLaunchKernelGGL(eye_minus_kernel, dim3(unsigned((n + 255) / 256)), dim3(256), 0, st, X64, K, n, out);
+  hipLaunchKernelGGL((bgemm_f64mfma_kernel<float, double>), dim3(grid), dim3(256), 0, st, Sinv, R64, X64, K, 1.0, 0.0,
+                     static_cast<float*>(nullptr));
+  hipLaunchKernelGGL((bgemm_f64mfma_kernel<double, double>), dim3(grid), dim3(256), 0, st, S64, X64, res, K, -1.0, 1.0,
+                     static_cast<float*>(nullptr));
+  hipLaunchKernelGGL((bgemm_f64mfma_kernel<float, double, kF64Solve>), dim3(grid), dim3(256), 0, st, Sinv, res, X64, K, 1.0,
+                     1.0, out);
   CAFEQ_CHECK_LAUNCH();
   return CAFEQ_OK;
 }
 
-// Blocks of 256.  Newton-Schulz rounds X <- 2 X - X (T X) on the float32 matrix pipe (batched products over the
-// whole chip) from X0 = T^T / alpha (cold) or from the inverse already in Tinv (warm: inside a learning loop),
-// accepted per block when ||I - T X||_F <= 3e-4 afterwards -- an a-posteriori bound, so a start that was not
-// good enough only costs the rounds; blocks that are hopeless after the first product (||I - T X0||_F > 1.2) skip
-// them, and so do blocks whose start already meets the bound (rotations).  Every other block is eliminated in float32 (one compute unit each, 283 us).  Either way one Newton step
-// with float64 residuals follows and brings the result to float32 rounding accuracy (it squares the residual).
-// work: 2 nb K K doubles; the rounds' two float32 matrices and the flags share it with the refinement's buffers.
+// Blocks of 256.  Newton rounds (ns256_round_kernel) from X0 = T^T / alpha (cold: up to five) or from the inverse already
+// in Tinv (warm: inside a learning loop, two), accepted per block when the residual measured before the last correction
+// is at most 1.5e-2: a round squares it, so what enters the last step is below 3e-4 -- an a-posteriori bound, so a start
+// that was not good enough only costs the rounds; a block that meets it early is copied through the rest.  Every other
+// block is eliminated in float32 (one compute unit each, 283 us).  Either way one Newton step with float64 residuals
+// follows and brings the result to float32 rounding accuracy (it squares the residual).
+// Five rounds: they reach blocks with ||I - T X0||_2 up to about 0.7 (three left 0.05-perturbed rotations next to the
+// elimination, whose 283 us one block of a call is enough to pay).
+// work: 2 nb K K doubles: the float64 residual (before it the rounds' residual norms), then two float32 matrices.
 int launch_inverse256(const float* T, int nb, double* work, float* Tinv, float* rho_row, float* rho_col, int* status,
                       bool warm, hipStream_t st) {
-  constexpr int K = 256;
+  constexpr int K = 256, kCold = 5, kWarm = 2;
   int rc;
   const size_t mat = size_t(nb) * K * K;
-  float* Xs = reinterpret_cast<float*>(work);
-  float* Y = Xs + mat;
-  int* hop = reinterpret_cast<int*>(reinterpret_cast<unsigned char*>(work) + 2 * mat * sizeof(double) -
-                                    ((size_t(2 * nb) * sizeof(int) + 255) / 256) * 256);
-  int* need = hop + nb;
-  auto product_tx = [&](const float* X) { return launch_bgemm(false, false, T, X, Y, K, nb, 1.f, 0.f, st); };
-  auto round = [&](const float* X, float* Xn) {   // Xn = 2 X - X Y
-    return launch_bgemm(false, false, X, Y, Xn, K, nb, -1.f, 2.f, st, nullptr, X, hop);
-  };
-  if (!warm) {
-    hipLaunchKernelGGL(ns_init_kernel, dim3(nb, K / 32), dim3(1024), 0, st, T, Xs, Tinv, K);
-    CAFEQ_CHECK_LAUNCH();
-    if ((rc = product_tx(Xs))) return rc;
-    hipLaunchKernelGGL(ns_flag_kernel, dim3(nb), dim3(1024), 0, st, Y, K, 0, 1.2f, 3e-4f, hop, need, status);
-    if ((rc = round(Xs, Tinv))) return rc;
-    if ((rc = product_tx(Tinv))) return rc;
-    if ((rc = round(Tinv, Xs))) return rc;
-    if ((rc = product_tx(Xs))) return rc;
-    if ((rc = round(Xs, Tinv))) return rc;
-  } else {
-    if ((rc = product_tx(Tinv))) return rc;
-    hipLaunchKernelGGL(ns_flag_kernel, dim3(nb), dim3(1024), 0, st, Y, K, 0, 1.2f, 3e-4f, hop, need, status);
-    if ((rc = round(Tinv, Xs))) return rc;
-    if ((rc = product_tx(Xs))) return rc;
-    if ((rc = round(Xs, Tinv))) return rc;
+  double* res = work;
+  float* buf[2] = {reinterpret_cast<float*>(work + mat), reinterpret_cast<float*>(work + mat) + mat};
+  float* norms = reinterpret_cast<float*>(work);             // [round][nb][kNsSlices]
+  if (!warm) hipLaunchKernelGGL(ns_init_kernel, dim3(nb, K / 32), dim3(1024), 0, st, T, buf[0], K);
+  const int rounds = warm ? kWarm : kCold;
+  const float* X = warm ? Tinv : buf[0];
+  for (int r = 0; r < rounds; ++r) {
+    float* Xn = X == buf[0] ? buf[1] : buf[0];
+    hipLaunchKernelGGL(ns256_round_kernel, dim3(unsigned(nb) * kNsSlices), dim3(512), 0, st, T, X, Xn, nb,
+                       r ? norms + size_t(r - 1) * nb * kNsSlices : nullptr, norms + size_t(r) * nb * kNsSlices);
+    X = Xn;
   }
-  if ((rc = product_tx(Tinv))) return rc;
-  hipLaunchKernelGGL(ns_flag_kernel, dim3(nb), dim3(1024), 0, st, Y, K, 1, 3e-4f, 0.f, hop, need, status);
   CAFEQ_CHECK_LAUNCH();
   GjArgs a;
-  a.K = K; a.nz = 0; a.T = T; a.partial = nullptr; a.out = Tinv;
+  a.K = K; a.nz = 0; a.T = T; a.partial = nullptr; a.out = const_cast<float*>(X);
   a.status = status; a.status_stride = 1; a.status_offset = 0;
-  a.need = need;
+  a.resid = norms + size_t(rounds - 1) * nb * kNsSlices; a.nresid = kNsSlices; a.resid_max = kNsAccept2;
   if ((rc = launch_gj(a, nb, st))) return rc;
   // one Newton step X <- X + X (I - T X) with float64 residuals
-  double *res = work, *X64 = work + mat;
   const unsigned grid = unsigned(nb) * (K / 32) * (K / 64);
-  const int64_t n = int64_t(mat);
-  hipLaunchKernelGGL(eye64_kernel, dim3(unsigned((n + 255) / 256)), dim3(256), 0, st, res, K, n);
-  hipLaunchKernelGGL((bgemm_f64mfma_kernel<float, float>), dim3(grid), dim3(256), 0, st, T, Tinv, res, K, -1.0, 1.0);
-  hipLaunchKernelGGL((bgemm_f64mfma_kernel<float, double>), dim3(grid), dim3(256), 0, st, Tinv, res, X64, K, 1.0, 0.0);
-  hipLaunchKernelGGL(add64_kernel, dim3(unsigned((n + 255) / 256)), dim3(256), 0, st, X64, n, Tinv);
+  hipLaunchKernelGGL((bgemm_f64mfma_kernel<float, float, kF64Residual>), dim3(grid), dim3(256), 0, st, T, X, res, K, 1.0, 0.0,
+                     static_cast<float*>(nullptr));
+  hipLaunchKernelGGL((bgemm_f64mfma_kernel<float, double, kF64Step>), dim3(grid), dim3(256), 0, st, X, res,
+                     static_cast<double*>(nullptr), K, 1.0, 0.0, Tinv);
   CAFEQ_CHECK_LAUNCH();
   RhoRequest rho[2];
   int nrho = 0;

@@ -17,7 +17,10 @@ struct GjArgs {
   const float* sum32 = nullptr;   // optional with sum64: the same sum rounded to float32 (gj_spd256_kernel reads this)
   float* out;            // [nb][K][K]
   int* status; int status_stride, status_offset;
-  const int* need = nullptr;      // optional [nb]: blocks whose entry is 0 are already done
+  // optional [nb][nresid]: shares of a squared residual; a block whose sum is at most resid_max is done (status 0)
+  const float* resid = nullptr;
+  int nresid = 0;
+  float resid_max = 0.f;
 };
 
 // Compile-time loop: f(integral_constant<int, I>) for I in [B, E).
@@ -330,7 +333,14 @@ __device__ void gj_panel_body(const GjArgs& a, const int b, GjShared<K, S>& sh) 
 template <int K, int RT, int CT, typename S, bool PIV>
 __global__ __launch_bounds__((K / RT) * (K / CT)) void gj_panel_kernel(const GjArgs a) {
   __shared__ __align__(16) GjShared<K, S> sh;
-  if (a.need && !a.need[blockIdx.x]) return;       // uniform over the workgroup
+  if (a.resid) {
+    float t = 0.f;
+    for (int q = 0; q < a.nresid; ++q) t += a.resid[size_t(blockIdx.x) * a.nresid + q];
+    if (t <= a.resid_max) {                        // uniform over the workgroup (a NaN is not done)
+      if (a.status && threadIdx.x == 0) a.status[size_t(blockIdx.x) * a.status_stride + a.status_offset] = 0;
+      return;
+    }
+  }
   gj_panel_body<K, RT, CT, S, PIV>(a, int(blockIdx.x), sh);
 }
 

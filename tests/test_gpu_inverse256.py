@@ -1,0 +1,75 @@
+"""GPU parity: blocks of 256 through cafeq_block_inverse over the distances from a rotation at which its paths change
+(rounds copied, one to five Newton rounds, elimination), over numbers of blocks, and warm-started inside a loop."""
+import numpy as np
+import pytest
+
+from paper_2511_19705_amd import workloads as WL
+
+pytestmark = pytest.mark.gpu
+K = 256
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    from paper_2511_19705_amd import cafeq
+    return torch, cafeq
+
+
+@pytest.mark.parametrize("nb", [1, 3, 11])
+def test_distances_from_a_rotation(env, nb):
+    torch, cafeq = env
+    rng = np.random.default_rng(70 + nb)
+    H = WL.haar_blocks(nb, K, 71).astype(np.float64)
+    scale = 10.0 ** rng.uniform(-3, 3, nb)
+    eps = np.resize([0.05, 0.0, 0.3, 1e-4, 0.01, 0.1, 0.15, 0.2, 0.6, 1.0, 3.0], nb)
+    T = np.stack([scale[b] * H[b] @ (np.eye(K) + eps[b] / np.sqrt(K) * rng.standard_normal((K, K))) for b in range(nb)])
+    T = T.astype(np.float32)
+    Tinv, status = cafeq.block_inverse(torch.from_numpy(T).to("cuda:0"))
+    torch.cuda.synchronize()
+    assert int(status.abs().sum()) == 0
+    got = Tinv.cpu().numpy().astype(np.float64)
+    for b in range(nb):
+        ref = np.linalg.inv(T[b].astype(np.float64))
+        # float32 rounding of the result and what the last step leaves of a residual of 3e-4 (its square, times
+        # ||X||_2 <= sqrt(K) max |x|); eliminated blocks: the float32 elimination's residual, squared likewise
+        tol = (2.0 ** -23 + 9e-8 * np.sqrt(K)) * np.abs(ref).max()
+        assert np.abs(got[b] - ref).max() <= tol, (b, eps[b], np.abs(got[b] - ref).max() / np.abs(ref).max())
+    again, _ = cafeq.block_inverse(torch.from_numpy(np.ascontiguousarray(T[::-1])).to("cuda:0"))
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(again.cpu().numpy()[::-1], Tinv.cpu().numpy())
+
+
+@pytest.mark.parametrize("lr", [1e-4, 3e-3, 3e-2])
+def test_the_loop_keeps_an_inverse(env, lr):
+    """Small steps: two warm rounds; the largest: blocks beyond them, which the elimination takes."""
+    torch, cafeq = env
+    A, B, T = WL.small_pair(200, 512, K, 1, 78, eps=0.0)
+    Td = torch.from_numpy(T.copy()).to("cuda:0")
+    Tinv, hist, status = cafeq.optimize_pair(torch.from_numpy(A).to("cuda:0"), torch.from_numpy(B).to("cuda:0"), Td, 4, 64,
+                                             1, 5.0, lr=lr, steps=4)
+    torch.cuda.synchronize()
+    assert int(status.abs().sum()) == 0 and bool(torch.isfinite(hist).all())
+    got, Tf = Tinv.cpu().numpy().astype(np.float64), Td.cpu().numpy().astype(np.float64)
+    for b in range(T.shape[0]):
+        ref = np.linalg.inv(Tf[b])
+        assert np.abs(got[b] - ref).max() <= (2.0 ** -23 + 9e-8 * np.sqrt(K)) * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("bad", ["zero", "nan", "inf"])
+def test_blocks_without_an_inverse_leave_the_others_alone(env, bad):
+    torch, cafeq = env
+    T = WL.perturbed_blocks(3, K, 79, eps=0.05)
+    ref = np.linalg.inv(T.astype(np.float64))
+    if bad == "zero":
+        T[1] = 0.0
+    else:
+        T[1, 3, 5] = np.nan if bad == "nan" else np.inf
+    Tinv, status = cafeq.block_inverse(torch.from_numpy(T).to("cuda:0"))
+    torch.cuda.synchronize()
+    st = status.cpu().numpy()
+    assert st[0] == 0 and st[2] == 0
+    if bad == "zero":
+        assert st[1] == 1 and float(Tinv[1].abs().max()) == 0.0
+    for b in (0, 2):
+        np.testing.assert_allclose(Tinv[b].cpu().numpy(), ref[b], rtol=0, atol=2.0 ** -22 * np.abs(ref[b]).max())
