@@ -111,14 +111,16 @@ __device__ __forceinline__ void rho_body(const RhoJob& jb, const int nb, double*
   }
 }
 
-// grid: (nb, njobs + nrho, z): with z > 1 (few blocks) the K / 32 stages of a block go to a workgroup each.
+// grid: (nb, njobs + nrho, z): with z > 1 (few blocks, and blocks of 256, which a workgroup cannot hold in registers) the
+// K / 32 stages of a block go to a workgroup each.
 template <int K>
 __global__ __launch_bounds__(kSplitThreads) void split_planes_kernel(const SplitJobs js) {
   // stages' planes are assembled in LDS in their final order and leave as whole 16-byte vectors
   constexpr int kLdsB = K == 32 ? 33 * 1024 : 64 * 1024;
   __shared__ __align__(16) unsigned char lds[kLdsB];
   __shared__ float wmx[kSplitThreads / 64], line[256];
-  constexpr int NST = K / 32, QPS = K * 8, NQ = (K * K / 4 + kSplitThreads - 1) / kSplitThreads;   // stages, quads a stage, a thread
+  constexpr int NST = K / 32, QPS = K * 8;                                 // stages, quads a stage
+  constexpr int NQ = K == 256 ? QPS / kSplitThreads : (K * K / 4 + kSplitThreads - 1) / kSplitThreads;   // quads a thread
   const int tid = threadIdx.x;
   // partial headers that no workgroup of the core writes (slots nobody owns) must read as empty
   if (js.hdr) {
@@ -134,7 +136,7 @@ __global__ __launch_bounds__(kSplitThreads) void split_planes_kernel(const Split
   const SplitJob jb = js.job[blockIdx.y];
   const int nplanes = jb.nplanes;
   const float* sb = jb.src + size_t(blockIdx.x) * K * K;
-  const bool whole = gridDim.z == 1;
+  const bool whole = K < 256 && gridDim.z == 1;
   const int stage0 = whole ? 0 : int(blockIdx.z), nquad = whole ? K * K / 4 : QPS;
   // a quad: four inputs that are adjacent in the plane (e = 0..3 of one (row, step, half, u)): one 128-bit load (or four
   // coalesced loads of a transposed source) and one 64-bit LDS store per plane
@@ -472,48 +474,33 @@ __global__ __launch_bounds__(256) void single_tail_kernel(const ReduceArgs ra, c
 // ---------------------------------------------------------------------------------------
 // batched k x k product  C_b = alpha * op(A_b) op(B_b) + beta * C_b   (64 x 64 tile / workgroup)
 // ---------------------------------------------------------------------------------------
-template <bool TA, bool TB>
-__global__ __launch_bounds__(256) void bgemm_kernel(const float* __restrict__ A, const float* __restrict__ B,
-                                                     float* __restrict__ C, int K, float alpha, float beta) {
-  __shared__ float sa[16][68];   // [l][i]
-  __shared__ float sb[16][68];   // [l][j]
-  const int tpr = K / 64;
-  const int b = blockIdx.x / (tpr * tpr), tile = blockIdx.x % (tpr * tpr);
-  const int i0 = (tile / tpr) * 64, j0 = (tile % tpr) * 64;
-  const float* Ab = A + size_t(b) * K * K;
-  const float* Bb = B + size_t(b) * K * K;
-  float* Cb = C + size_t(b) * K * K;
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  float acc[4][4] = {};
-  for (int l0 = 0; l0 < K; l0 += 16) {
-    for (int e = threadIdx.x; e < 16 * 64; e += 256) {
-      const int l = e / 64, i = e % 64;
-      sa[l][i] = TA ? Ab[(l0 + l) * K + i0 + i] : Ab[(i0 + i) * K + l0 + l];
-      sb[l][i] = TB ? Bb[(j0 + i) * K + l0 + l] : Bb[(l0 + l) * K + j0 + i];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int l = 0; l < 16; ++l) {
-      float av[4], bv[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) { av[u] = sa[l][ty * 4 + u]; bv[u] = sb[l][tx * 4 + u]; }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = fmaf(av[u], bv[v], acc[u][v]);
-    }
-    __syncthreads();
+// What the update needs of the element's old state, requested before the products it follows (behind them every load
+// waited for the stores of the element before it, which may alias: 16 latencies in a row, 32 us instead of 17 for the 72
+// blocks of 128 of the 2B-shaped pair).
+struct UpdateOld { float t, m, v; };
+__device__ __forceinline__ UpdateOld update_load(const UpdateHook& u, size_t at) {
+  UpdateOld o{0.f, 0.f, 0.f};
+  if (u.T) {
+    o.t = u.T[at];
+    if (u.m) { o.m = u.m[at]; o.v = u.v[at]; }
   }
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      float* dst = Cb + (i0 + ty * 4 + u) * K + j0 + tx * 4 + v;
-      *dst = alpha * acc[u][v] + (beta != 0.f ? beta * *dst : 0.f);
-    }
+  return o;
+}
+// (the arithmetic of adam_kernel / div_dev_kernel and sgd_kernel, on the gradient still in its register)
+__device__ __forceinline__ void update_store(const UpdateHook& u, size_t at, float g, const UpdateOld& o, float denom) {
+  if (u.m) {
+    const float mi = u.beta1 * o.m + u.omb1 * g;
+    const float vi = u.beta2 * o.v + u.omb2 * g * g;
+    u.m[at] = mi;
+    u.v[at] = vi;
+    u.T[at] = o.t - u.lr * (mi * u.c1) / (sqrtf(vi * u.c2) + u.eps);
+  } else {
+    const float gd = u.denom ? g / denom : g;
+    u.T[at] = o.t - u.lr * gd;
+  }
 }
 
-// Same product on the matrix cores (v_mfma_f32_32x32x2_f32) for K a multiple of 64: one 64 x 64
+// On the matrix cores (v_mfma_f32_32x32x2_f32) for K a multiple of 64: one 64 x 64
 // output tile per workgroup, four waves of one 32 x 32 tile each, the operand panels staged in
 // LDS as [contraction index][64 tile indices] (row stride 65 floats: transposing stores, whose
 // lanes walk the contraction index, and the MFMA operand reads, whose lane halves take rows l
@@ -521,24 +508,19 @@ __global__ __launch_bounds__(256) void bgemm_kernel(const float* __restrict__ A,
 // 128 the learning loops run on take one chunk -- every load of the workgroup is in flight at once and
 // there is one barrier -- at 65 KB of LDS, two workgroups per compute unit.
 template <bool TA, bool TB, int CH>
-// D: where the beta term is read (null: C itself); skip: optional per-block flags, a block whose flag is set is
-// left alone.
 __global__ __launch_bounds__(256) void bgemm_mfma_kernel(const float* __restrict__ A, const float* __restrict__ B,
                                                           float* __restrict__ C, int K, float alpha, float beta,
-                                                          const AdamHook adam, const float* __restrict__ D,
-                                                          const int* __restrict__ skip) {
+                                                          const UpdateHook up) {
   constexpr int LD = 65;
   extern __shared__ __align__(16) float bsm[];
   float* sa = bsm;
   float* sb = bsm + CH * LD;
   const int tpr = K / 64;
   const int b = blockIdx.x / (tpr * tpr), tile = blockIdx.x % (tpr * tpr);
-  if (skip && skip[b]) return;
   const int i0 = (tile / tpr) * 64, j0 = (tile % tpr) * 64;
   const float* Ab = A + size_t(b) * K * K;
   const float* Bb = B + size_t(b) * K * K;
   float* Cb = C + size_t(b) * K * K;
-  const float* Db = (D ? D : C) + size_t(b) * K * K;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ln = lane & 31, h = lane >> 5;
   const int wi = wave >> 1, wj = wave & 1;
   floatx16 acc;
@@ -551,8 +533,15 @@ __global__ __launch_bounds__(256) void bgemm_mfma_kernel(const float* __restrict
   if (beta != 0.f) {
 #pragma unroll
     for (int v = 0; v < 16; ++v)
-      cold[v] = Db[(i0 + wi * 32 + 8 * (v / 4) + 4 * h + (v % 4)) * K + j0 + wj * 32 + ln];
+      cold[v] = Cb[(i0 + wi * 32 + 8 * (v / 4) + 4 * h + (v % 4)) * K + j0 + wj * 32 + ln];
   }
+  UpdateOld old[16];
+  if (up.T) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      old[v] = update_load(up, size_t(b) * K * K + size_t(i0 + wi * 32 + 8 * (v / 4) + 4 * h + (v % 4)) * K + j0 + wj * 32 + ln);
+  }
+  const float denom = up.T && up.denom ? *up.denom : 1.f;
   for (int l0 = 0; l0 < K; l0 += CH) {
     // sa[l][i] = op(A)[i0 + i][l0 + l];  sb[l][j] = op(B)[l0 + l][j0 + j]: four consecutive elements of the
     // operand's rows per load, all loads of the chunk issued before the first LDS store
@@ -566,6 +555,7 @@ __global__ __launch_bounds__(256) void bgemm_mfma_kernel(const float* __restrict
       if (TB) { const int j = e / CH, l = e % CH; vb[u] = *reinterpret_cast<const float4*>(Bb + (j0 + j) * K + l0 + l); }
       else    { const int l = e >> 6, j = e & 63; vb[u] = *reinterpret_cast<const float4*>(Bb + (l0 + l) * K + j0 + j); }
     }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < NV; ++u) {
       const int e = (tid + u * 256) * 4;
@@ -588,14 +578,8 @@ __global__ __launch_bounds__(256) void bgemm_mfma_kernel(const float* __restrict
   for (int v = 0; v < 16; ++v) {
     const int i = i0 + wi * 32 + 8 * (v / 4) + 4 * h + (v % 4), j = j0 + wj * 32 + ln;
     const float g = alpha * acc[v] + (beta != 0.f ? beta * cold[v] : 0.f);
-    if (adam.T) {
-      // (the arithmetic of adam_kernel, on the gradient still in its register)
-      const size_t at = size_t(b) * K * K + size_t(i) * K + j;
-      const float mi = adam.beta1 * adam.m[at] + adam.omb1 * g;
-      const float vi = adam.beta2 * adam.v[at] + adam.omb2 * g * g;
-      adam.m[at] = mi;
-      adam.v[at] = vi;
-      adam.T[at] -= adam.lr * (mi * adam.c1) / (sqrtf(vi * adam.c2) + adam.eps);
+    if (up.T) {
+      update_store(up, size_t(b) * K * K + size_t(i) * K + j, g, old[v], denom);
     } else {
       Cb[i * K + j] = g;
     }
@@ -616,7 +600,7 @@ constexpr size_t chain_lds(int K) { return size_t(K * (K + 1) + 2 * K * kChainLd
 template <int K>
 __global__ __launch_bounds__(4 * K) void bgemm_chain_kernel(const float* __restrict__ P, const float* __restrict__ G,
                                                             float* __restrict__ C, float alpha, float beta,
-                                                            const AdamHook adam) {
+                                                            const UpdateHook up) {
   static_assert(K == 64 || K == 128, "slices of 64 rows");
   constexpr int kChainLdP = K + 1, NT = 4 * K, WJ = K / 32, SL = K / 64;   // threads, column tiles, slices per block
   extern __shared__ __align__(16) float csm[];
@@ -665,6 +649,14 @@ __global__ __launch_bounds__(4 * K) void bgemm_chain_kernel(const float* __restr
 #pragma unroll
     for (int v = 0; v < 16; ++v) xw[8 * (v / 4) + 4 * h + (v % 4)] = acc[v];
   }
+  // (in flight under the second product)
+  UpdateOld was[16];
+  if (up.T) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      was[v] = update_load(up, size_t(b) * K * K + size_t(i0 + wi * 32 + 8 * (v / 4) + 4 * h + (v % 4)) * K + wj * 32 + ln);
+  }
+  const float denom = up.T && up.denom ? *up.denom : 1.f;
   __syncthreads();
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
@@ -680,23 +672,57 @@ __global__ __launch_bounds__(4 * K) void bgemm_chain_kernel(const float* __restr
   for (int v = 0; v < 16; ++v) {
     const int i = i0 + wi * 32 + 8 * (v / 4) + 4 * h + (v % 4), j = wj * 32 + ln;
     const float gr = alpha * acc[v] + (beta != 0.f ? beta * cold[v] : 0.f);
-    if (adam.T) {
-      // (the arithmetic of adam_kernel, on the gradient still in its register)
-      const size_t at = size_t(b) * K * K + size_t(i) * K + j;
-      const float mi = adam.beta1 * adam.m[at] + adam.omb1 * gr;
-      const float vi = adam.beta2 * adam.v[at] + adam.omb2 * gr * gr;
-      adam.m[at] = mi;
-      adam.v[at] = vi;
-      adam.T[at] -= adam.lr * (mi * adam.c1) / (sqrtf(vi * adam.c2) + adam.eps);
+    if (up.T) {
+      update_store(up, size_t(b) * K * K + size_t(i) * K + j, gr, was[v], denom);
     } else {
       Cb[i * K + j] = gr;
     }
   }
 }
 
+// Blocks of 32, a workgroup per block: C = beta C + alpha (P^T G) P^T with X = P^T G in LDS (two launches with X in
+// memory before: 45 blocks 4.7 + 4.1 us, now 5.9).
+__global__ __launch_bounds__(256) void bgemm_chain32_kernel(const float* __restrict__ P, const float* __restrict__ G,
+                                                            float* __restrict__ C, float alpha, float beta,
+                                                            const UpdateHook up) {
+  constexpr int K = 32;
+  __shared__ float sp[K][K + 1], sg[K][K + 1], sx[K][K + 1];
+  const size_t base = size_t(blockIdx.x) * K * K;
+  const int tid = threadIdx.x;
+  float cold[4];
+  UpdateOld old[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int e = tid + 256 * u;
+    sp[e / K][e % K] = P[base + e];
+    sg[e / K][e % K] = G[base + e];
+    cold[u] = beta != 0.f ? C[base + e] : 0.f;
+    old[u] = update_load(up, base + e);
+  }
+  const float denom = up.T && up.denom ? *up.denom : 1.f;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int i = (tid + 256 * u) / K, j = tid % K;
+    float acc = 0.f;
+#pragma unroll
+    for (int l = 0; l < K; ++l) acc = fmaf(sp[l][i], sg[l][j], acc);
+    sx[i][j] = acc;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int e = tid + 256 * u, i = e / K, j = e % K;
+    float acc = 0.f;
+#pragma unroll
+    for (int l = 0; l < K; ++l) acc = fmaf(sx[i][l], sp[j][l], acc);
+    const float g = alpha * acc + (beta != 0.f ? beta * cold[u] : 0.f);
+    if (up.T) update_store(up, base + e, g, old[u], denom);
+    else C[base + e] = g;
+  }
+}
 
-// K == 32: one 32 x 32 tile per workgroup, thread per output element group
-template <bool TA, bool TB>
+// K == 32: one 32 x 32 product per workgroup, C = alpha A B + beta C
 __global__ __launch_bounds__(256) void bgemm32_kernel(const float* __restrict__ A, const float* __restrict__ B,
                                                        float* __restrict__ C, float alpha, float beta) {
   constexpr int K = 32;
@@ -705,9 +731,8 @@ __global__ __launch_bounds__(256) void bgemm32_kernel(const float* __restrict__ 
   const float* Bb = B + size_t(blockIdx.x) * K * K;
   float* Cb = C + size_t(blockIdx.x) * K * K;
   for (int e = threadIdx.x; e < K * K; e += 256) {
-    const int r = e / K, c = e % K;
-    sa[r][c] = TA ? Ab[c * K + r] : Ab[e];   // sa[i][l]
-    sb[r][c] = TB ? Bb[c * K + r] : Bb[e];   // sb[l][j]
+    sa[e / K][e % K] = Ab[e];
+    sb[e / K][e % K] = Bb[e];
   }
   __syncthreads();
   for (int e = threadIdx.x; e < K * K; e += 256) {
@@ -742,7 +767,7 @@ int launch_split_planes_multi(const SplitRequest* req, int n, int K, int nb, hip
                        rho[i].rG && rho[i].G > K ? rho[i].G / K : 1};
   }
   // one workgroup per (block, job) when those fill the chip; else one per (block, job, stage)
-  const dim3 grid(nb, n + nrho, n == 0 || nb * n >= 128 ? 1 : K / 32);
+  const dim3 grid(nb, n + nrho, n == 0 || (K < 256 && nb * n >= 128) ? 1 : K / 32);
   switch (K) {
     case 32: hipLaunchKernelGGL(split_planes_kernel<32>, grid, dim3(kSplitThreads), 0, st, js); break;
     case 64: hipLaunchKernelGGL(split_planes_kernel<64>, grid, dim3(kSplitThreads), 0, st, js); break;
@@ -838,19 +863,11 @@ int launch_reduce_losses(int kind, const float* hdrA, int nslotA, const float* h
   return CAFEQ_OK;
 }
 int launch_bgemm(bool ta, bool tb, const float* A, const float* B, float* C, int K, int nb, float alpha,
-                 float beta, hipStream_t st, const AdamHook* adam, const float* D, const int* skip) {
-  AdamHook hook;
-  hook.T = nullptr;
-  if (adam) {
-    if (K == 32) return CAFEQ_ERR_INVALID_ARG;
-    hook = *adam;
-  }
-  if ((D || skip) && K == 32) return CAFEQ_ERR_INVALID_ARG;
+                 float beta, hipStream_t st, const UpdateHook* hook) {
+  const UpdateHook up = hook ? *hook : UpdateHook{};
   if (K == 32) {
-#define CAFEQ_G32(TA, TB) hipLaunchKernelGGL((bgemm32_kernel<TA, TB>), dim3(nb), dim3(256), 0, st, A, B, C, alpha, beta)
-    if (ta && tb) CAFEQ_G32(true, true); else if (ta) CAFEQ_G32(true, false);
-    else if (tb) CAFEQ_G32(false, true); else CAFEQ_G32(false, false);
-#undef CAFEQ_G32
+    if (hook || ta || tb) return CAFEQ_ERR_INVALID_ARG;
+    hipLaunchKernelGGL(bgemm32_kernel, dim3(nb), dim3(256), 0, st, A, B, C, alpha, beta);
   } else {
     const unsigned grid = unsigned(nb) * (K / 64) * (K / 64);
     if (K % 128 == 0) {
@@ -867,13 +884,13 @@ int launch_bgemm(bool ta, bool tb, const float* A, const float* B, float* C, int
         if (!ok) return CAFEQ_ERR_LAUNCH;
         attr_set = true;
       }
-#define CAFEQ_G128(TA, TB) hipLaunchKernelGGL((bgemm_mfma_kernel<TA, TB, CH>), dim3(grid), dim3(256), lds, st, A, B, C, K, alpha, beta, hook, D, skip)
+#define CAFEQ_G128(TA, TB) hipLaunchKernelGGL((bgemm_mfma_kernel<TA, TB, CH>), dim3(grid), dim3(256), lds, st, A, B, C, K, alpha, beta, up)
       if (ta && tb) CAFEQ_G128(true, true); else if (ta) CAFEQ_G128(true, false);
       else if (tb) CAFEQ_G128(false, true); else CAFEQ_G128(false, false);
 #undef CAFEQ_G128
     } else {
       constexpr size_t lds = 2 * 64 * 65 * sizeof(float);
-#define CAFEQ_G64(TA, TB) hipLaunchKernelGGL((bgemm_mfma_kernel<TA, TB, 64>), dim3(grid), dim3(256), lds, st, A, B, C, K, alpha, beta, hook, D, skip)
+#define CAFEQ_G64(TA, TB) hipLaunchKernelGGL((bgemm_mfma_kernel<TA, TB, 64>), dim3(grid), dim3(256), lds, st, A, B, C, K, alpha, beta, up)
       if (ta && tb) CAFEQ_G64(true, true); else if (ta) CAFEQ_G64(true, false);
       else if (tb) CAFEQ_G64(false, true); else CAFEQ_G64(false, false);
 #undef CAFEQ_G64
@@ -882,17 +899,15 @@ int launch_bgemm(bool ta, bool tb, const float* A, const float* B, float* C, int
   CAFEQ_CHECK_LAUNCH();
   return CAFEQ_OK;
 }
-// C = beta C + alpha (P^T G) P^T per block; x1: scratch of nb K K floats for block sizes other than 128
+// C = beta C + alpha P^T G P^T per block; x1: scratch of nb K K floats for blocks of 256
 int launch_bgemm_chain(const float* P, const float* G, float* x1, float* C, int K, int nb, float alpha, float beta,
-                       hipStream_t st, const AdamHook* adam) {
-  if (K != 128 && K != 64) {
+                       hipStream_t st, const UpdateHook* hook) {
+  if (K == 256) {
     const int rc = launch_bgemm(true, false, P, G, x1, K, nb, 1.f, 0.f, st);
     if (rc) return rc;
-    return launch_bgemm(false, true, x1, P, C, K, nb, alpha, beta, st, adam);
+    return launch_bgemm(false, true, x1, P, C, K, nb, alpha, beta, st, hook);
   }
-  AdamHook hook;
-  hook.T = nullptr;
-  if (adam) hook = *adam;
+  const UpdateHook up = hook ? *hook : UpdateHook{};
   static std::atomic<bool> attr_set{false};
   if (!attr_set) {
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(bgemm_chain_kernel<128>),
@@ -902,10 +917,16 @@ int launch_bgemm_chain(const float* P, const float* G, float* x1, float* C, int 
       return CAFEQ_ERR_LAUNCH;
     attr_set = true;
   }
-  if (K == 128)
-    hipLaunchKernelGGL(bgemm_chain_kernel<128>, dim3(unsigned(nb) * 2), dim3(512), chain_lds(128), st, P, G, C, alpha, beta, hook);
-  else
-    hipLaunchKernelGGL(bgemm_chain_kernel<64>, dim3(unsigned(nb)), dim3(256), chain_lds(64), st, P, G, C, alpha, beta, hook);
+  switch (K) {
+    case 32: hipLaunchKernelGGL(bgemm_chain32_kernel, dim3(unsigned(nb)), dim3(256), 0, st, P, G, C, alpha, beta, up); break;
+    case 64:
+      hipLaunchKernelGGL(bgemm_chain_kernel<64>, dim3(unsigned(nb)), dim3(256), chain_lds(64), st, P, G, C, alpha, beta, up);
+      break;
+    case 128:
+      hipLaunchKernelGGL(bgemm_chain_kernel<128>, dim3(unsigned(nb) * 2), dim3(512), chain_lds(128), st, P, G, C, alpha, beta, up);
+      break;
+    default: return CAFEQ_ERR_UNSUPPORTED;
+  }
   CAFEQ_CHECK_LAUNCH();
   return CAFEQ_OK;
 }

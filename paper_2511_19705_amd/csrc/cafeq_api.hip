@@ -599,7 +599,10 @@ int check_opt(const cafeq_opt_cfg* opt) {
 
 static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* x, const cafeq_quant_cfg* cfg,
                      float lse_t, float* losses, float* gradT, int8_t* codesU, float* scalesU, int8_t* codesV,
-                     float* scalesV, void* ws, void* stream, const AdamHook* adam);
+                     float* scalesV, void* ws, void* stream, const UpdateHook* hook);
+
+static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_quant_cfg* cfg, float* losses, float* gradT,
+                       int8_t* codes, float* scales, void* ws, void* stream, const UpdateHook* hook);
 
 int cafeq_optimize_single(const cafeq_mat* W, float* T, float* Tinv, int k, int nb, int rep,
                           const cafeq_quant_cfg* cfg, const cafeq_opt_cfg* opt, float* history, int* status,
@@ -613,9 +616,17 @@ int cafeq_optimize_single(const cafeq_mat* W, float* T, float* Tinv, int k, int 
   const int64_t n = int64_t(nb) * k * k;
   cafeq_xform x{T, Tinv, k, nb, rep};
   if ((rc = launch_fill(history, 0.f, int64_t(opt->steps) * 8, st))) return rc;
+  // without a regulariser to add in between, the step rides in the epilogue of the gradient's last kernel
+  const bool fuse = !(opt->lambda_orth > 0.f) && !small_m(k);
   for (int s = 0; s < opt->steps; ++s) {
     float* h = history + size_t(s) * 8;
     if ((rc = loop_inverse(s, T, k, nb, Tinv, status, w.sub, stream))) return rc;
+    if (fuse) {
+      UpdateHook hook{};
+      hook.T = T; hook.lr = opt->lr; hook.denom = opt->normalize ? h + 2 : nullptr;
+      if ((rc = single_impl(W, &x, cfg, h, w.grad, nullptr, nullptr, w.sub, stream, &hook))) return rc;
+      continue;
+    }
     if ((rc = cafeq_proxy_loss_fwd_bwd(W, &x, cfg, h, w.grad, nullptr, nullptr, w.sub, stream))) return rc;
     // surrogate / ||W||^2 (history[s][2]) when normalised, then the regulariser's gradient on top
     if (opt->normalize && (rc = launch_div_by_device_scalar(w.grad, h + 2, n, st))) return rc;
@@ -640,14 +651,14 @@ int cafeq_optimize_pair(const cafeq_mat* A, const cafeq_mat* B, float* T, float*
   cafeq_xform x{T, Tinv, k, nb, rep};
   if ((rc = launch_fill(history, 0.f, int64_t(opt->steps) * 8, st))) return rc;
   if ((rc = launch_fill(moments, 0.f, 2 * n, st))) return rc;
-  const bool fuse_adam = !(opt->lambda_orth > 0.f) && (k == 64 || k == 128 || k == 256);
+  const bool fuse_adam = !(opt->lambda_orth > 0.f) && !small_m(k);
   for (int s = 0; s < opt->steps; ++s) {
     float* h = history + size_t(s) * 8;
     if ((rc = loop_inverse(s, T, k, nb, Tinv, status, w.sub, stream))) return rc;
     if (fuse_adam) {
       // the Adam step rides in the epilogue of the gradient's last kernel (no regulariser to add in between)
       if (!(opt->beta1 >= 0.0 && opt->beta1 < 1.0 && opt->beta2 >= 0.0 && opt->beta2 < 1.0)) return CAFEQ_ERR_INVALID_ARG;
-      AdamHook hook;
+      UpdateHook hook{};
       hook.T = T; hook.m = moments; hook.v = moments + n;
       hook.lr = float(opt->lr); hook.beta1 = float(opt->beta1); hook.omb1 = float(1.0 - opt->beta1);
       hook.beta2 = float(opt->beta2); hook.omb2 = float(1.0 - opt->beta2); hook.eps = float(opt->eps);
@@ -947,14 +958,16 @@ int cafeq_apply_transform(const cafeq_mat* W, const cafeq_xform* x, int axis, in
   return launch_core(x->k, x->k, axis, p, st);
 }
 
-int cafeq_proxy_loss_fwd_bwd(const cafeq_mat* W, const cafeq_xform* x, const cafeq_quant_cfg* cfg,
-                             float* losses, float* gradT, int8_t* codes, float* scales, void* ws,
-                             void* stream) {
+// hook (learning loop only; blocks of 32 and more): the last kernel of the gradient applies the gradient-descent step
+// to T instead of storing the gradient (gradT is then scratch)
+static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_quant_cfg* cfg, float* losses, float* gradT,
+                       int8_t* codes, float* scales, void* ws, void* stream, const UpdateHook* hook) {
   int rc = check_mat(W);
   if (rc) return rc;
   rc = check_cfg(cfg, true, true);
   if (rc) return rc;
   if (x && small_m(x->k)) {
+    if (hook) return CAFEQ_ERR_INVALID_ARG;
     if ((rc = check_small_xform(x, true))) return rc;
     if ((rc = check_axis_len(W, x, cfg->axis))) return rc;
     if (!ws) return CAFEQ_ERR_WORKSPACE;
@@ -1051,16 +1064,22 @@ int cafeq_proxy_loss_fwd_bwd(const cafeq_mat* W, const cafeq_xform* x, const caf
         return rc;
     }
     if (owner && (rc = launch_build_mmid(p, K, gp.Gk, nb, x->Tinv, col ? 1 : 0, w.mmid, st))) return rc;
-    if ((rc = launch_bgemm_chain(x->Tinv, w.mmid, w.x1, gradT, K, nb, -2.f, 1.f, st))) return rc;
+    if ((rc = launch_bgemm_chain(x->Tinv, w.mmid, w.x1, gradT, K, nb, -2.f, 1.f, st, hook))) return rc;
   }
   return CAFEQ_OK;
 }
 
-// adam (learning loop only; blocks of 64 and more): the last kernel of the gradient applies the Adam step to T, m
+int cafeq_proxy_loss_fwd_bwd(const cafeq_mat* W, const cafeq_xform* x, const cafeq_quant_cfg* cfg,
+                             float* losses, float* gradT, int8_t* codes, float* scales, void* ws,
+                             void* stream) {
+  return single_impl(W, x, cfg, losses, gradT, codes, scales, ws, stream, nullptr);
+}
+
+// hook (learning loop only; blocks of 32 and more): the last kernel of the gradient applies the Adam step to T, m
 // and v instead of storing the gradient (gradT is then scratch)
 static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* x, const cafeq_quant_cfg* cfg,
                      float lse_t, float* losses, float* gradT, int8_t* codesU, float* scalesU, int8_t* codesV,
-                     float* scalesV, void* ws, void* stream, const AdamHook* adam) {
+                     float* scalesV, void* ws, void* stream, const UpdateHook* hook) {
   int rc = check_mat(A);
   if (rc) return rc;
   rc = check_mat(B);
@@ -1069,7 +1088,7 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
   if (rc) return rc;
   if (x && small_m(x->k)) {
     // (row-blocks that share a small block do not line up with blocks of 32: rep must be 1 here)
-    if (adam) return CAFEQ_ERR_INVALID_ARG;
+    if (hook) return CAFEQ_ERR_INVALID_ARG;
     if ((rc = check_small_xform(x, true))) return rc;
     if (x->rep != 1) return CAFEQ_ERR_UNSUPPORTED;
     if (A->cols != int64_t(x->nb) * x->k || B->rows != A->cols) return CAFEQ_ERR_BAD_SHAPE;
@@ -1183,13 +1202,13 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
     la.hdrA = w.hdrA; la.nslotA = int(pa.nslot); la.hdrB = w.hdrB; la.nslotB = int(pb.nslot); la.kind = kLossLse;
     la.t = lse_t; la.ngroups = ngroups; la.losses = losses; la.lse_ms = w.lse_ms;
     if ((rc = launch_grad_owner_timed(jobs, 2, kLossLse, 0.f, lse_t, w.lse_ms, st, &la))) return rc;
-    if ((rc = launch_bgemm_chain(x->Tinv, w.gp, w.x1, gradT, K, nb, -1.f, 1.f, st, adam))) return rc;
+    if ((rc = launch_bgemm_chain(x->Tinv, w.gp, w.x1, gradT, K, nb, -1.f, 1.f, st, hook))) return rc;
   } else if (grad) {
     // member A into gradT; member B: G_P of transform block b sums its rep row-blocks; d/dT = -P^T G_P P^T
     if ((rc = launch_reduce_grad_pair(ag, ga.Gk, qa.fused, qa.two ? w.member_ref : nullptr, gradT, bg, gb.Gk, qb.fused,
                                       qb.two ? w.member_ref + 1 : nullptr, w.gp, K, nb, w.lse_ms, st)))
       return rc;
-    if ((rc = launch_bgemm_chain(x->Tinv, w.gp, w.x1, gradT, K, nb, -1.f, 1.f, st, adam))) return rc;
+    if ((rc = launch_bgemm_chain(x->Tinv, w.gp, w.x1, gradT, K, nb, -1.f, 1.f, st, hook))) return rc;
   }
   return CAFEQ_OK;
 }

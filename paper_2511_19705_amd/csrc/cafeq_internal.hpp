@@ -108,15 +108,15 @@ int launch_single_tail(const CoreParams& pgrad, const CoreParams& ploss, int K, 
                        int nslot, float* losses, double* lse_ms, hipStream_t st);
 int launch_reduce_losses(int kind, const float* hdrA, int nslotA, const float* hdrB, int nslotB, float beta,
                          float t, int64_t ngroups, float* losses, double* lse_ms, hipStream_t st);
-// Adam step applied by the product's epilogue instead of storing the product: the value alpha op(A) op(B) + beta C is
-// taken as the gradient of element [b][i][j] and T, m, v are updated in place (C is only read).  K >= 64.
-struct AdamHook { float *T, *m, *v; float lr, beta1, omb1, beta2, omb2, eps, c1, c2; };
-// C = alpha op(A) op(B) + beta D per block (D null: C); skip: per-block flags, set = leave the block alone
+// Update of the transform applied by the last product's epilogue instead of storing the product: the value
+// alpha op(A) op(B) + beta C is taken as the gradient of element [b][i][j] and T (and m, v) are updated in place (C is
+// only read).  m != null: the Adam step.  m == null: gradient descent, the gradient first divided by *denom if given.
+struct UpdateHook { float *T, *m, *v; float lr, beta1, omb1, beta2, omb2, eps, c1, c2; const float* denom; };
+// C = alpha op(A) op(B) + beta C per block
 int launch_bgemm(bool ta, bool tb, const float* A, const float* B, float* C, int K, int nb, float alpha,
-                 float beta, hipStream_t st, const AdamHook* adam = nullptr, const float* D = nullptr,
-                 const int* skip = nullptr);
+                 float beta, hipStream_t st, const UpdateHook* hook = nullptr);
 int launch_bgemm_chain(const float* P, const float* G, float* x1, float* C, int K, int nb, float alpha, float beta,
-                       hipStream_t st, const AdamHook* adam = nullptr);
+                       hipStream_t st, const UpdateHook* hook = nullptr);
 // adaptive_kernels.hip
 int launch_gram_pair(int axis, const float* X, const int8_t* codes, const float* scales, int64_t rows,
                      int64_t cols, int K, int G, int nb, int rep, int64_t chunk, int nchunk, float* partial,
