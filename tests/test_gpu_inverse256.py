@@ -35,7 +35,7 @@ def test_distances_from_a_rotation(env, nb):
         # ||X||_2 <= sqrt(K) max |x|); eliminated blocks: the float32 elimination's residual, squared likewise
         tol = (2.0 ** -23 + 9e-8 * np.sqrt(K)) * np.abs(ref).max()
         assert np.abs(got[b] - ref).max() <= tol, (b, eps[b], np.abs(got[b] - ref).max() / np.abs(ref).max())
-    again, _ = cafeq.block_inverse(torch.from_numpy(np.ascontiguousarray(T[::-1])).to("cuda:0"))
+    again, _ = cafeq.block_inverse(torch.from_numpy(T[::-1].copy()).to("cuda:0"))
     torch.cuda.synchronize()
     np.testing.assert_array_equal(again.cpu().numpy()[::-1], Tinv.cpu().numpy())
 
