@@ -376,7 +376,7 @@ void fill_common(CoreParams* p, const cafeq_mat* W, const CorePlan& pl, int rep)
 // where the loss pass over prepared weights finds them
 void set_prepared(CoreParams* p, const cafeq_mat* W, int axis) {
   const bool col = axis == CAFEQ_AXIS_COL;
-  const PreparedLayout l = prepared_layout(col ? W->rows : W->cols, col ? W->cols : W->rows);
+  const PreparedLayout l = prepared_layout(col ? W->rows : W->cols, col ? W->cols : W->rows, W->dtype);
   const unsigned char* base = static_cast<const unsigned char*>(W->prepared);
   p->prep_wsq = reinterpret_cast<const float*>(base);
   p->prep_lscale = reinterpret_cast<const float*>(base + l.off_lscale);
@@ -432,11 +432,12 @@ bool grad_owner_eligible(const cafeq_mat* const* mats, const PassPlans* const* p
 GradOwnerJob grad_owner_job(const cafeq_mat* W, int axis, const PassPlans& pp, const MemberWs& m, float* out,
                             int transpose_out) {
   const bool col = axis == CAFEQ_AXIS_COL;
-  const PreparedLayout l = prepared_layout(col ? W->rows : W->cols, col ? W->cols : W->rows);
+  const PreparedLayout l = prepared_layout(col ? W->rows : W->cols, col ? W->cols : W->rows, W->dtype);
   GradOwnerJob j;
   j.gtiles = static_cast<const unsigned char*>(W->prepared) + l.off_gtiles;
   j.rec = m.grec; j.rG = m.rGreal; j.out = out;
   j.nlines = pp.gpass.nlines; j.nseg = pp.gpass.nseg; j.grp = pp.gp.G; j.transpose_out = transpose_out;
+  j.parts = prepared_parts(W->dtype);
   return j;
 }
 
@@ -451,7 +452,7 @@ int run_grad_pass(int K, int axis, const cafeq_mat* W, int rep, const PassPlans&
   if (W->prepared && K == 128) {
     // the prepared copy also holds the weights in the operand order of this contraction
     const bool col = axis == CAFEQ_AXIS_COL;
-    const PreparedLayout l = prepared_layout(col ? W->rows : W->cols, col ? W->cols : W->rows);
+    const PreparedLayout l = prepared_layout(col ? W->rows : W->cols, col ? W->cols : W->rows, W->dtype);
     pg->prep_gtiles = static_cast<const unsigned char*>(W->prepared) + l.off_gtiles;
     return launch_grad_v2_timed(*pg, st);
   }
@@ -833,7 +834,7 @@ size_t cafeq_prepared_bytes(const cafeq_mat* W, int axis) {
   const bool col = axis == CAFEQ_AXIS_COL;
   const int64_t nlines = col ? W->rows : W->cols, naxis = col ? W->cols : W->rows;
   if (naxis % 128 != 0) return 0;
-  return prepared_layout(nlines, naxis).bytes;
+  return prepared_layout(nlines, naxis, W->dtype).bytes;
 }
 
 int cafeq_prepare_weights(const cafeq_mat* W, int axis, void* prepared, void* stream) {
@@ -1120,8 +1121,9 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
   const bool asym = is_minmax(cfg);
   const bool v2A = v2_eligible(A, K, ga, cfg), v2B = v2_eligible(B, K, gb, cfg);
   // both loss passes over prepared weights in one launch, each member on half of the chip: when neither writes
-  // codes or scales and both use the same group length
-  const bool pair_launch = v2A && v2B && !codesU && !scalesU && !codesV && !scalesV && ga.Gk == gb.Gk;
+  // codes or scales and both use the same group length and storage type
+  const bool pair_launch = v2A && v2B && !codesU && !scalesU && !codesV && !scalesV && ga.Gk == gb.Gk &&
+                           A->dtype == B->dtype;
   PassPlans qa, qb;
   if ((rc = plan_passes(K, ga, A->rows, A->cols, grad, &qa, v2A, asym, pair_launch ? 2 : 1))) return rc;
   if ((rc = plan_passes(K, gb, B->cols, B->rows, grad, &qb, v2B, asym, pair_launch ? 2 : 1))) return rc;

@@ -59,17 +59,20 @@ int device_cu_count();
 // loss_v2.hip: loss pass over prepared weights (128 x 128 blocks, groups up to 128)
 // header (||W||^2), per-line factors, the loss pass's tiles, their partial sums, the gradient pass's tiles
 struct PreparedLayout { int64_t nlp, nseg, ntiles; size_t off_lscale, off_planes, off_partial, off_gtiles, bytes; };
-PreparedLayout prepared_layout(int64_t nlines, int64_t naxis);
+// 16-bit parts per weight in the prepared copies: two for float32, one for bfloat16, whose eight significant bits one
+// float16 (loss pass) or bfloat16 (gradient pass) holds -- its second part was zeros, half the bytes of both passes.
+__host__ __device__ constexpr int prepared_parts(int dtype) { return dtype == CAFEQ_BF16 ? 1 : 2; }
+PreparedLayout prepared_layout(int64_t nlines, int64_t naxis, int dtype);
 int launch_prepare(const cafeq_mat* W, int axis, void* prepared, hipStream_t st);
 // gradient pass over prepared weights (blocks of 128; grad_v2.hip): p.prep_gtiles, p.rec, p.grp as launch_grad_pass
-size_t prepared_gtiles_bytes(int64_t nlines, int64_t naxis);
+size_t prepared_gtiles_bytes(int64_t nlines, int64_t naxis, int dtype);
 int launch_prepare_gtiles(const cafeq_mat* W, int axis, unsigned char* gtiles, hipStream_t st);
 int launch_grad_v2(const CoreParams& p, hipStream_t st);
 // the same with one workgroup per (matrix, block of 128) and the gradient written in its final form (no partials):
 // up to two matrices per launch; the coefficients must be final when it starts (kLossLse: lse_ms = {m*, S})
 struct GradOwnerJob {
   const unsigned char* gtiles; const float2* rec; const float* rG; float* out;
-  int64_t nlines; int nseg, grp, transpose_out;
+  int64_t nlines; int nseg, grp, transpose_out, parts;
 };
 struct LossArgs;   // loss_reduce.hpp; fold != nullptr: the loss reduction runs inside the launch
 int launch_grad_v2_owner(const GradOwnerJob* jobs, int n, int loss_kind, float beta, float lse_t, const double* lse_ms,

@@ -5,7 +5,7 @@
 // The weights do not change over a learning run, so cafeq_prepare_weights also stores them in the form THIS
 // contraction consumes -- it runs over the lines, so the matrix instruction wants, per input, eight consecutive
 // lines side by side, i.e. the transpose of what the loss pass reads.  Per tile of 128 lines x 128 inputs:
-//   [step of 16 lines: 8][tile of 32 inputs: 4][part: hi, mid][lane: 64][16 bytes]
+//   [step of 16 lines: 8][tile of 32 inputs: 4][part: hi, mid (bfloat16 weights: hi alone)][lane: 64][16 bytes]
 // with lane = input % 32 + 32 * (line / 8 % 2) holding the bfloat16 parts of lines 8 (line / 8) .. + 7: one
 // contiguous kilobyte per operand of v_mfma_f32_32x32x16_bf16, so a wave loads its operands from memory
 // straight into registers (no float32 split, no transposition through LDS in the hot loop).
@@ -16,7 +16,8 @@
 // refilled with the next tile's step as soon as it has been used, so a wave keeps 16 KB in flight; the S
 // operands are shared through LDS, where they sit in operand order too: the area is zeroed once, per tile every
 // lane drops its line's coefficient parts (two bytes each) where the line's arg-max falls, and takes them out
-// again afterwards.  Three part products (S lo x W hi, S hi x W mid, S hi x W hi), float32 accumulation; one partial per
+// again afterwards.  Three part products (S lo x W hi, S hi x W mid, S hi x W hi; without the second for bfloat16
+// weights, WP = 1), float32 accumulation; one partial per
 // (workgroup, block) in the layout of the generic gradient pass, reduced in fixed order by reduce_grad_kernel.
 #include <atomic>
 
@@ -32,6 +33,7 @@ constexpr int kGvOperandB = 1024;                 // one matrix-instruction oper
 constexpr int kGvSbufB = 4 * 8 * 2 * kGvOperandB; // S operands of a tile: [tile row 4][step 8][part 2]
 constexpr int kGvLds = kGvSbufB + 64;
 
+template <int WP>
 __global__ __launch_bounds__(kThreads, 2) void grad_v2_kernel(const CoreParams p) {
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* sbuf = smem;
@@ -117,13 +119,13 @@ __global__ __launch_bounds__(kThreads, 2) void grad_v2_kernel(const CoreParams p
   int woff[2] = {-1, -1};   // where this lane's coefficients sit in the S area (-1: nowhere)
 
   // ---- the W side: the operands of the wave's input tile, one register set per step of a tile
-  const unsigned char* gbase = p.prep_gtiles + wave * 2 * kGvOperandB + lane * 16;
-  auto tile_ptr = [&](int sg_, int ms_) { return gbase + (int64_t(sg_) * mt_per_seg + ms_) * int64_t(8 * 4 * 2 * kGvOperandB); };
-  uintx4 breg[8][2];   // [step][part]
+  const unsigned char* gbase = p.prep_gtiles + wave * WP * kGvOperandB + lane * 16;
+  auto tile_ptr = [&](int sg_, int ms_) { return gbase + (int64_t(sg_) * mt_per_seg + ms_) * int64_t(8 * 4 * WP * kGvOperandB); };
+  uintx4 breg[8][WP];   // [step][part]
   auto load_step = [&](const unsigned char* tp, int s) {
 #pragma unroll
-    for (int part = 0; part < 2; ++part)
-      breg[s][part] = *reinterpret_cast<const uintx4*>(tp + (s * 4 * 2 + part) * kGvOperandB);
+    for (int part = 0; part < WP; ++part)
+      breg[s][part] = *reinterpret_cast<const uintx4*>(tp + (s * 4 * WP + part) * kGvOperandB);
   };
 
   const unsigned char* tile = tile_ptr(seg, mis);
@@ -195,15 +197,18 @@ __global__ __launch_bounds__(kThreads, 2) void grad_v2_kernel(const CoreParams p
     read_s(ash, 0, 0);
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
-      const bf16x8 bh = as_bf16x8(breg[s][0]), bm = as_bf16x8(breg[s][1]);
+      const bf16x8 bh = as_bf16x8(breg[s][0]);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int i = 0; i < 4; ++i) gt[i] = CAFEQ_MFMA_BF16(asl[i], bh, gt[i]);
       __builtin_amdgcn_sched_barrier(0);
       if (s + 1 < 8) read_s(asl, s + 1, 1);
       __builtin_amdgcn_sched_barrier(0);
+      if constexpr (WP == 2) {
+        const bf16x8 bm = as_bf16x8(breg[s][1]);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) gt[i] = CAFEQ_MFMA_BF16(ash[i], bm, gt[i]);
+        for (int i = 0; i < 4; ++i) gt[i] = CAFEQ_MFMA_BF16(ash[i], bm, gt[i]);
+      }
 #pragma unroll
       for (int i = 0; i < 4; ++i) gt[i] = CAFEQ_MFMA_BF16(ash[i], bh, gt[i]);
       __builtin_amdgcn_sched_barrier(0);
@@ -244,14 +249,14 @@ struct GvOwnerArgs {
   LossArgs la;
 };
 
-__global__ __launch_bounds__(512, 1) void grad_v2_owner_kernel(const GvOwnerArgs a) {
+template <int WP>
+__device__ __forceinline__ void grad_v2_owner_body(const GvOwnerArgs& a, const int mi) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int ln = lane & 31, h = lane >> 5;
   const int half = wave >> 2, wq = wave & 3;
   unsigned char* sbuf = smem + half * kGvSbufB;
 
-  const int mi = (a.nmem > 1 && int(blockIdx.x) >= a.m[0].nseg) ? 1 : 0;
   const GvMember& M = a.m[mi];
   const int seg = int(blockIdx.x) - (mi ? a.m[0].nseg : 0);
   const int mt_per_seg = M.mt_per_seg;
@@ -296,13 +301,13 @@ __global__ __launch_bounds__(512, 1) void grad_v2_owner_kernel(const GvOwnerArgs
   int woff[2] = {-1, -1};
 
   // ---- the W side
-  const unsigned char* gbase = M.gtiles + wq * 2 * kGvOperandB + lane * 16;
-  auto tile_ptr = [&](int ms_) { return gbase + (int64_t(seg) * mt_per_seg + ms_) * int64_t(8 * 4 * 2 * kGvOperandB); };
-  uintx4 breg[8][2];
+  const unsigned char* gbase = M.gtiles + wq * WP * kGvOperandB + lane * 16;
+  auto tile_ptr = [&](int ms_) { return gbase + (int64_t(seg) * mt_per_seg + ms_) * int64_t(8 * 4 * WP * kGvOperandB); };
+  uintx4 breg[8][WP];
   auto load_step = [&](const unsigned char* tp, int s) {
 #pragma unroll
-    for (int part = 0; part < 2; ++part)
-      breg[s][part] = *reinterpret_cast<const uintx4*>(tp + (s * 4 * 2 + part) * kGvOperandB);
+    for (int part = 0; part < WP; ++part)
+      breg[s][part] = *reinterpret_cast<const uintx4*>(tp + (s * 4 * WP + part) * kGvOperandB);
   };
   // (a half without a tile of its own -- the odd half of a block with one tile -- reads tile 0 and skips the work)
   int mis = half < mt_per_seg ? half : 0;
@@ -372,7 +377,7 @@ __global__ __launch_bounds__(512, 1) void grad_v2_owner_kernel(const GvOwnerArgs
     read_s(ash, 0, 0);
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
-      const bf16x8 bh = as_bf16x8(breg[s][0]), bm = as_bf16x8(breg[s][1]);
+      const bf16x8 bh = as_bf16x8(breg[s][0]);
       __builtin_amdgcn_sched_barrier(0);
       // (an inactive half multiplies zeros: its S area is empty)
 #pragma unroll
@@ -380,8 +385,11 @@ __global__ __launch_bounds__(512, 1) void grad_v2_owner_kernel(const GvOwnerArgs
       __builtin_amdgcn_sched_barrier(0);
       if (s + 1 < 8) read_s(asl, s + 1, 1);
       __builtin_amdgcn_sched_barrier(0);
+      if constexpr (WP == 2) {
+        const bf16x8 bm = as_bf16x8(breg[s][1]);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) gt[i] = CAFEQ_MFMA_BF16(ash[i], bm, gt[i]);
+        for (int i = 0; i < 4; ++i) gt[i] = CAFEQ_MFMA_BF16(ash[i], bm, gt[i]);
+      }
 #pragma unroll
       for (int i = 0; i < 4; ++i) gt[i] = CAFEQ_MFMA_BF16(ash[i], bh, gt[i]);
       __builtin_amdgcn_sched_barrier(0);
@@ -419,6 +427,41 @@ __global__ __launch_bounds__(512, 1) void grad_v2_owner_kernel(const GvOwnerArgs
   }
 }
 
+// WPA, WPB: parts of the members' weights
+template <int WPA, int WPB>
+__global__ __launch_bounds__(512, 1) void grad_v2_owner_kernel(const GvOwnerArgs a) {
+  const int mi = (a.nmem > 1 && int(blockIdx.x) >= a.m[0].nseg) ? 1 : 0;
+  if constexpr (WPA == WPB) grad_v2_owner_body<WPA>(a, mi);
+  else if (mi == 0) grad_v2_owner_body<WPA>(a, 0);
+  else grad_v2_owner_body<WPB>(a, 1);
+}
+template <int WPA, int WPB>
+int launch_owner(const GvOwnerArgs& a, int nwg, hipStream_t st) {
+  static std::atomic<bool> attr_set{false};   // per instantiation
+  if (!attr_set) {
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(grad_v2_owner_kernel<WPA, WPB>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+      return CAFEQ_ERR_LAUNCH;
+    attr_set = true;
+  }
+  hipLaunchKernelGGL((grad_v2_owner_kernel<WPA, WPB>), dim3(unsigned(nwg)), dim3(512), 2 * kGvSbufB + 5 * 8 * sizeof(double), st, a);
+  CAFEQ_CHECK_LAUNCH();
+  return CAFEQ_OK;
+}
+template <int WP>
+int launch_partials(const CoreParams& p, hipStream_t st) {
+  static std::atomic<bool> attr_set{false};   // per instantiation
+  if (!attr_set) {
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(grad_v2_kernel<WP>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            160 * 1024) != hipSuccess)
+      return CAFEQ_ERR_LAUNCH;
+    attr_set = true;
+  }
+  hipLaunchKernelGGL(grad_v2_kernel<WP>, dim3(unsigned(p.nwg)), dim3(kThreads), kGvLds, st, p);
+  CAFEQ_CHECK_LAUNCH();
+  return CAFEQ_OK;
+}
+
 // One workgroup per tile of 128 lines x 128 inputs: the bfloat16 hi + mid parts of every weight (hi = the
 // round-to-nearest of the value, mid = that of the remainder: 16 significant bits), in operand order.
 struct GtileArgs {
@@ -429,7 +472,8 @@ struct GtileArgs {
 __global__ __launch_bounds__(256) void prepare_gtiles_kernel(const GtileArgs a) {
   const int64_t tix = blockIdx.x;
   const int64_t seg = tix / a.nmt, mis = tix - seg * a.nmt;
-  unsigned char* tp = a.gtiles + tix * int64_t(8 * 4 * 2 * kGvOperandB);
+  const int parts = prepared_parts(a.dtype);
+  unsigned char* tp = a.gtiles + tix * int64_t(8 * 4 * parts * kGvOperandB);
   for (int s = 0; s < 8; ++s) {
     const int lane = threadIdx.x & 63, mt = threadIdx.x >> 6;
     const int ln = lane & 31, h = lane >> 5;
@@ -451,17 +495,17 @@ __global__ __launch_bounds__(256) void prepare_gtiles_kernel(const GtileArgs a) 
       hi[e2] = pack_bf16(x[2 * e2], x[2 * e2 + 1]);
       mid[e2] = pack_bf16(x[2 * e2] - bf16_lo_f32(hi[e2]), x[2 * e2 + 1] - bf16_hi_f32(hi[e2]));
     }
-    unsigned char* op = tp + ((s * 4 + mt) * 2) * kGvOperandB + lane * 16;
+    unsigned char* op = tp + ((s * 4 + mt) * parts) * kGvOperandB + lane * 16;
     *reinterpret_cast<uint4*>(op) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-    *reinterpret_cast<uint4*>(op + kGvOperandB) = make_uint4(mid[0], mid[1], mid[2], mid[3]);
+    if (parts == 2) *reinterpret_cast<uint4*>(op + kGvOperandB) = make_uint4(mid[0], mid[1], mid[2], mid[3]);
   }
 }
 
 }  // namespace
 
-size_t prepared_gtiles_bytes(int64_t nlines, int64_t naxis) {
+size_t prepared_gtiles_bytes(int64_t nlines, int64_t naxis, int dtype) {
   const int64_t nmt = (nlines + kGvLines - 1) / kGvLines;
-  return size_t(nmt) * size_t(naxis / 128) * size_t(8 * 4 * 2 * kGvOperandB);
+  return size_t(nmt) * size_t(naxis / 128) * size_t(8 * 4 * prepared_parts(dtype) * kGvOperandB);
 }
 
 int launch_prepare_gtiles(const cafeq_mat* W, int axis, unsigned char* gtiles, hipStream_t st) {
@@ -503,31 +547,15 @@ int launch_grad_v2_owner(const GradOwnerJob* jobs, int n, int loss_kind, float b
   } else {
     a.la = LossArgs{};
   }
-  static std::atomic<bool> attr_set{false};
-  if (!attr_set) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(grad_v2_owner_kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
-      return CAFEQ_ERR_LAUNCH;
-    attr_set = true;
-  }
-  hipLaunchKernelGGL(grad_v2_owner_kernel, dim3(unsigned(nwg)), dim3(512), 2 * kGvSbufB + 5 * 8 * sizeof(double), st, a);
-  CAFEQ_CHECK_LAUNCH();
-  return CAFEQ_OK;
+  const int pa = jobs[0].parts, pb = jobs[n - 1].parts;
+  if (pa == 1) return pb == 1 ? launch_owner<1, 1>(a, nwg, st) : launch_owner<1, 2>(a, nwg, st);
+  return pb == 1 ? launch_owner<2, 1>(a, nwg, st) : launch_owner<2, 2>(a, nwg, st);
 }
 
 int launch_grad_v2(const CoreParams& p, hipStream_t st) {
   if (!p.prep_gtiles || !p.rec || !p.slot_grad || p.grp < 32 || p.grp % 32 != 0) return CAFEQ_ERR_INVALID_ARG;
   if (p.mt_per_seg != (p.nlines + kGvLines - 1) / kGvLines) return CAFEQ_ERR_INVALID_ARG;
-  static std::atomic<bool> attr_set{false};
-  if (!attr_set) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(grad_v2_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            160 * 1024) != hipSuccess)
-      return CAFEQ_ERR_LAUNCH;
-    attr_set = true;
-  }
-  hipLaunchKernelGGL(grad_v2_kernel, dim3(unsigned(p.nwg)), dim3(kThreads), kGvLds, st, p);
-  CAFEQ_CHECK_LAUNCH();
-  return CAFEQ_OK;
+  return prepared_parts(p.dtype) == 1 ? launch_partials<1>(p, st) : launch_partials<2>(p, st);
 }
 
 }  // namespace cafeq

@@ -35,7 +35,11 @@ namespace {
 constexpr int kV2Waves = 8;
 constexpr int kV2Threads = kV2Waves * 64;
 constexpr int kV2MacroLines = kV2Waves * 32;
-constexpr int kV2TileBytes = 32 * 128 * 4;            // one prepared tile: [8 steps][2 parts][64 lanes][16 B]
+// one prepared tile: [8 steps][parts][64 lanes][16 B].  Two parts for float32 weights, one for bfloat16: eight significant
+// bits are a float16 number (what lies below 2^-24 of a line scaled to 2^4 is below the second part's reach as well), so
+// the second part was zeros: half the bytes, four products a strip and step instead of five, the same results bit for bit
+// (27B-shaped pair: loss pass 406 -> 342 us, gradient pass 352 -> 246 us; codes of its gate 237 -> 189 us).
+constexpr int v2_tile_bytes(int parts) { return 32 * 128 * 2 * parts; }
 constexpr int kV2PlaneBytes = 4 * 2 * 128 * 64;        // one operand (T or T^-1) of one block: 64 KB
 constexpr int kV2Lds = 2 * kV2PlaneBytes + kV2Waves * kHdrFloats * 4 + 64;
 
@@ -47,8 +51,8 @@ __device__ __forceinline__ uint32_t pack_f16(float x0, float x1) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, halfx2));
 }
 
-// bidx: the workgroup's index among the p.nwg workgroups that share the matrix
-template <int G, int AXIS, bool REC, bool OUT>
+// bidx: the workgroup's index among the p.nwg workgroups that share the matrix; WP: parts of the prepared weights
+template <int G, int AXIS, bool REC, bool OUT, int WP>
 __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned bidx) {
   constexpr int L = 128, KT = 4, NGRP = L / G, RPG = G / 2;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -82,13 +86,13 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
   // They are requested a whole vector phase ahead of their use (at the start of the vector phase of the strip
   // before, across run boundaries too), so that their latency never reaches the matrix pipe: requested at the
   // start of the matrix phase they had only the inverse transform (about a microsecond) to arrive in.
-  uintx4 wq[16];
+  uintx4 wq[8 * WP];
   float lsc_nx = 0.f;
   auto request_strip = [&](int sg, int64_t strip) {   // strip: the wave's strip inside segment sg
     lsc_nx = p.prep_lscale[int64_t(sg) * nlp + strip * 32 + ln];
-    const unsigned char* tp = p.prep_planes + (int64_t(sg) * (nlp / 32) + strip) * kV2TileBytes + lane * 16;
+    const unsigned char* tp = p.prep_planes + (int64_t(sg) * (nlp / 32) + strip) * v2_tile_bytes(WP) + lane * 16;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) wq[i] = *reinterpret_cast<const uintx4*>(tp + i * 1024);
+    for (int i = 0; i < 8 * WP; ++i) wq[i] = *reinterpret_cast<const uintx4*>(tp + i * 1024);
   };
   // (The variants that write codes or scales keep their requests at the start of the matrix phase: their vector
   // phase has no registers to hold a strip in flight.)
@@ -155,9 +159,11 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
         const int t = i >> 3, c = i & 7;
         return *reinterpret_cast<const uintx4*>(((c & 1) ? b1 : b0) + (c >> 1) * (2 * 128 * 64) + pl * (128 * 64) + t * (32 * 64));
       };
-      uintx4 fh[3], fl[3];
-      fh[0] = frag(0, 0); fl[0] = frag(0, 1);
-      fh[1] = frag(1, 0); fl[1] = frag(1, 1);
+      // (three products a step cover two steps of LDS latency, two products four)
+      constexpr int DF = WP == 2 ? 2 : 4;
+      uintx4 fh[DF + 1], fl[DF + 1];
+#pragma unroll
+      for (int i = 0; i < DF; ++i) { fh[i] = frag(i, 0); fl[i] = frag(i, 1); }
 #pragma unroll
       for (int t = 0; t < KT; ++t) {
         floatx16 a;
@@ -166,12 +172,12 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
           const int i = 8 * t + c;
-          if (i + 2 < 8 * KT) { fh[(i + 2) % 3] = frag(i + 2, 0); fl[(i + 2) % 3] = frag(i + 2, 1); }
-          __builtin_amdgcn_sched_barrier(0);     // the reads of step + 2 are issued before this step's products
-          const halfx8 xh = as_halfx8(fh[i % 3]), xl = as_halfx8(fl[i % 3]);
-          const halfx8 vbh = as_halfx8(wq[2 * c]), vbl = as_halfx8(wq[2 * c + 1]);
+          if (i + DF < 8 * KT) { fh[(i + DF) % (DF + 1)] = frag(i + DF, 0); fl[(i + DF) % (DF + 1)] = frag(i + DF, 1); }
+          __builtin_amdgcn_sched_barrier(0);     // the reads of step + DF are issued before this step's products
+          const halfx8 xh = as_halfx8(fh[i % (DF + 1)]), xl = as_halfx8(fl[i % (DF + 1)]);
+          const halfx8 vbh = as_halfx8(wq[WP * c]);
           a = CAFEQ_MFMA_F16(xl, vbh, a);
-          a = CAFEQ_MFMA_F16(xh, vbl, a);
+          if constexpr (WP == 2) a = CAFEQ_MFMA_F16(xh, as_halfx8(wq[WP * c + 1]), a);
           a = CAFEQ_MFMA_F16(xh, vbh, a);
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -453,18 +459,18 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
   }
 }
 
-template <int G, int AXIS, bool REC, bool OUT>
+template <int G, int AXIS, bool REC, bool OUT, int WP>
 __global__ __launch_bounds__(kV2Threads, 1) void loss_v2_kernel(const CoreParams p) {
-  loss_v2_body<G, AXIS, REC, OUT>(p, blockIdx.x);
+  loss_v2_body<G, AXIS, REC, OUT, WP>(p, blockIdx.x);
 }
 
 // Both members of a pair in one launch (no codes or scales requested): the first pa.nwg workgroups take member
 // A, the others member B.  With one workgroup per compute unit in total, half of the chip streams each member
 // and the ranges of the two members end together -- one kernel tail instead of two.
-template <int G, bool REC>
+template <int G, bool REC, int WP>
 __global__ __launch_bounds__(kV2Threads, 1) void loss_v2_pair_kernel(const CoreParams pa, const CoreParams pb) {
-  if (blockIdx.x < unsigned(pa.nwg)) loss_v2_body<G, CAFEQ_AXIS_COL, REC, false>(pa, blockIdx.x);
-  else loss_v2_body<G, CAFEQ_AXIS_ROW, REC, false>(pb, blockIdx.x - unsigned(pa.nwg));
+  if (blockIdx.x < unsigned(pa.nwg)) loss_v2_body<G, CAFEQ_AXIS_COL, REC, false, WP>(pa, blockIdx.x);
+  else loss_v2_body<G, CAFEQ_AXIS_ROW, REC, false, WP>(pb, blockIdx.x - unsigned(pa.nwg));
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -515,7 +521,8 @@ __global__ __launch_bounds__(256) void prepare_tiles_kernel(const PrepArgs a) {
   ex = ex < 32 ? 32 : (ex > 254 ? 254 : ex);        // lines of (almost) zeros: any scale will do
   const float wsc = __uint_as_float(uint32_t(257 - ex) << 23);          // 2^(3 - (ex - 127)): largest magnitude in [2^3, 2^4)
   if (c == 0) a.lscale[int64_t(seg) * a.nlp + strip * 32 + li] = __uint_as_float(uint32_t(ex - 3) << 23);
-  unsigned char* tp = a.planes + tix * int64_t(kV2TileBytes) + c * 2048;
+  const int parts = prepared_parts(a.dtype);
+  unsigned char* tp = a.planes + tix * int64_t(v2_tile_bytes(parts)) + c * 1024 * parts;
 #pragma unroll
   for (int hh = 0; hh < 2; ++hh) {
     uint32_t hi[4], lo[4];
@@ -534,7 +541,7 @@ __global__ __launch_bounds__(256) void prepare_tiles_kernel(const PrepArgs a) {
       lo[e2] = lb[0] | (lb[1] << 16);
     }
     *reinterpret_cast<uint4*>(tp + (hh * 32 + li) * 16) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-    *reinterpret_cast<uint4*>(tp + 1024 + (hh * 32 + li) * 16) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+    if (parts == 2) *reinterpret_cast<uint4*>(tp + 1024 + (hh * 32 + li) * 16) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
   }
   sq = wave_sum(sq);
   if ((t & 63) == 0) red[t >> 6] = sq;
@@ -556,9 +563,9 @@ __global__ __launch_bounds__(256) void prepare_sum_kernel(const double* __restri
   if (threadIdx.x == 0) out[0] = float(red[0]);
 }
 
-template <int G, int AXIS, bool REC, bool OUT>
+template <int G, int AXIS, bool REC, bool OUT, int WP>
 int launch_v2_v(const CoreParams& p, hipStream_t st) {
-  auto kern = loss_v2_kernel<G, AXIS, REC, OUT>;
+  auto kern = loss_v2_kernel<G, AXIS, REC, OUT, WP>;
   static std::atomic<bool> attr_set{false};   // per instantiation
   if (!attr_set) {
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -570,25 +577,29 @@ int launch_v2_v(const CoreParams& p, hipStream_t st) {
   CAFEQ_CHECK_LAUNCH();
   return CAFEQ_OK;
 }
+template <int G, int AXIS, int WP>
+int launch_v2_p(const CoreParams& p, hipStream_t st) {
+  if (p.codes || p.scales)
+    return p.rec ? launch_v2_v<G, AXIS, true, true, WP>(p, st) : launch_v2_v<G, AXIS, false, true, WP>(p, st);
+  return p.rec ? launch_v2_v<G, AXIS, true, false, WP>(p, st) : launch_v2_v<G, AXIS, false, false, WP>(p, st);
+}
 template <int G, int AXIS>
 int launch_v2_t(const CoreParams& p, hipStream_t st) {
-  if (p.codes || p.scales)
-    return p.rec ? launch_v2_v<G, AXIS, true, true>(p, st) : launch_v2_v<G, AXIS, false, true>(p, st);
-  return p.rec ? launch_v2_v<G, AXIS, true, false>(p, st) : launch_v2_v<G, AXIS, false, false>(p, st);
+  return prepared_parts(p.dtype) == 1 ? launch_v2_p<G, AXIS, 1>(p, st) : launch_v2_p<G, AXIS, 2>(p, st);
 }
 
 }  // namespace
 
-PreparedLayout prepared_layout(int64_t nlines, int64_t naxis) {
+PreparedLayout prepared_layout(int64_t nlines, int64_t naxis, int dtype) {
   PreparedLayout l;
   l.nlp = (nlines + kV2MacroLines - 1) / kV2MacroLines * kV2MacroLines;
   l.nseg = naxis / 128;
   l.ntiles = l.nseg * (l.nlp / 32);
   l.off_lscale = 256;
   l.off_planes = align_up(l.off_lscale + size_t(l.nseg) * l.nlp * sizeof(float), 256);
-  l.off_partial = l.off_planes + size_t(l.ntiles) * kV2TileBytes;
+  l.off_partial = l.off_planes + size_t(l.ntiles) * v2_tile_bytes(prepared_parts(dtype));
   l.off_gtiles = align_up(l.off_partial + size_t(l.ntiles) * sizeof(double), 256);
-  l.bytes = align_up(l.off_gtiles + prepared_gtiles_bytes(nlines, naxis), 256);
+  l.bytes = align_up(l.off_gtiles + prepared_gtiles_bytes(nlines, naxis, dtype), 256);
   return l;
 }
 
@@ -596,7 +607,7 @@ int launch_prepare(const cafeq_mat* W, int axis, void* prepared, hipStream_t st)
   const bool col = axis == CAFEQ_AXIS_COL;
   const int64_t nlines = col ? W->rows : W->cols, naxis = col ? W->cols : W->rows;
   if (naxis % 128 != 0) return CAFEQ_ERR_BAD_SHAPE;
-  const PreparedLayout l = prepared_layout(nlines, naxis);
+  const PreparedLayout l = prepared_layout(nlines, naxis, W->dtype);
   unsigned char* base = static_cast<unsigned char*>(prepared);
   PrepArgs a;
   a.W = W->data; a.dtype = W->dtype; a.rows = W->rows; a.cols = W->cols; a.ld = W->ld; a.axis = axis;
@@ -611,9 +622,9 @@ int launch_prepare(const cafeq_mat* W, int axis, void* prepared, hipStream_t st)
 }
 
 namespace {
-template <int G, bool REC>
-int launch_v2_pair_v(const CoreParams& pa, const CoreParams& pb, hipStream_t st) {
-  auto kern = loss_v2_pair_kernel<G, REC>;
+template <int G, bool REC, int WP>
+int launch_v2_pair_w(const CoreParams& pa, const CoreParams& pb, hipStream_t st) {
+  auto kern = loss_v2_pair_kernel<G, REC, WP>;
   static std::atomic<bool> attr_set{false};   // per instantiation
   if (!attr_set) {
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -625,16 +636,20 @@ int launch_v2_pair_v(const CoreParams& pa, const CoreParams& pb, hipStream_t st)
   CAFEQ_CHECK_LAUNCH();
   return CAFEQ_OK;
 }
+template <int G, bool REC>
+int launch_v2_pair_v(const CoreParams& pa, const CoreParams& pb, hipStream_t st) {
+  return prepared_parts(pa.dtype) == 1 ? launch_v2_pair_w<G, REC, 1>(pa, pb, st) : launch_v2_pair_w<G, REC, 2>(pa, pb, st);
+}
 }  // namespace
 
-// Both members of a pair (member A on its columns, member B on its rows) in one launch; same group length and
-// the same choice of records for both, no codes or scales.
+// Both members of a pair (member A on its columns, member B on its rows) in one launch; same group length, storage type
+// and choice of records for both, no codes or scales.
 int launch_loss_v2_pair(int G, const CoreParams& pa, const CoreParams& pb, hipStream_t st) {
   for (const CoreParams* p : {&pa, &pb})
     if (!p->prep_planes || !p->prep_lscale || !p->prep_wsq || !p->fscale || !p->fscale_inv || !p->slot_hdr || p->codes ||
         p->scales)
       return CAFEQ_ERR_INVALID_ARG;
-  if ((pa.rec != nullptr) != (pb.rec != nullptr)) return CAFEQ_ERR_INVALID_ARG;
+  if ((pa.rec != nullptr) != (pb.rec != nullptr) || pa.dtype != pb.dtype) return CAFEQ_ERR_INVALID_ARG;
   const bool rec = pa.rec != nullptr;
   switch (G) {
     case 32: return rec ? launch_v2_pair_v<32, true>(pa, pb, st) : launch_v2_pair_v<32, false>(pa, pb, st);
