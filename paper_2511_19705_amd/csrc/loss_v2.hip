@@ -26,6 +26,7 @@
 // cores take denormal float16 inputs exactly, so small entries lose nothing).  Inverse: the error E as ONE
 // float16 part (round to nearest even: 2^-12 relative, zero mean) times T^-1 as hi + lo (2^-22 relative: a
 // fixed operand's rounding would otherwise bias every element the same way).
+#include "gj_panel.hpp"   // StaticFor
 #include "xform_core.hpp"
 
 namespace cafeq {
@@ -49,6 +50,31 @@ typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack_f16(float x0, float x1) {
   floatx2 v = {x0, x1};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, halfx2));
+}
+
+// Four arg-max scans, one step each: where |z| > |best|, best = z and its index J (strictly greater: the lowest index
+// wins).  A mask that a comparison leaves in scalar registers may be read two instructions later at the earliest; one scan
+// at a time, as the compiler arranges them, has a wait behind each of a strip's 64 comparisons (70 of the vector phase's
+// 680 issue slots, each two slots long).  Four comparisons side by side fill that distance: at least three instructions
+// lie between each and its first reader.
+template <int J>
+__device__ __forceinline__ void argmax4(float (&b)[4], int (&j)[4], float z0, float z1, float z2, float z3) {
+  uint64_t m0, m1, m2, m3;
+  asm("v_cmp_gt_f32_e64 %8, |%12|, |%0|\n\t"
+      "v_cmp_gt_f32_e64 %9, |%13|, |%1|\n\t"
+      "v_cmp_gt_f32_e64 %10, |%14|, |%2|\n\t"
+      "v_cmp_gt_f32_e64 %11, |%15|, |%3|\n\t"
+      "v_cndmask_b32_e64 %0, %0, %12, %8\n\t"
+      "v_cndmask_b32_e64 %4, %4, %16, %8\n\t"
+      "v_cndmask_b32_e64 %1, %1, %13, %9\n\t"
+      "v_cndmask_b32_e64 %5, %5, %16, %9\n\t"
+      "v_cndmask_b32_e64 %2, %2, %14, %10\n\t"
+      "v_cndmask_b32_e64 %6, %6, %16, %10\n\t"
+      "v_cndmask_b32_e64 %3, %3, %15, %11\n\t"
+      "v_cndmask_b32_e64 %7, %7, %16, %11"
+      : "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]), "+v"(j[0]), "+v"(j[1]), "+v"(j[2]), "+v"(j[3]), "=&s"(m0), "=&s"(m1),
+        "=&s"(m2), "=&s"(m3)
+      : "v"(z0), "v"(z1), "v"(z2), "v"(z3), "n"(J));
 }
 
 // bidx: the workgroup's index among the p.nwg workgroups that share the matrix; WP: parts of the prepared weights
@@ -238,17 +264,33 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
       const float usc2 = usc * usc;
       const float dsc = usc * fsi;  // inverse-transformed error: accumulator units -> units of W
       float e2 = 0.f;               // sum of squared errors of this strip in accumulator units
+      // signed value at the arg-max of each tile of 32 and its index in the tile (without the lane-half term)
+      float tz[KT];
+      int tj[KT];
+      if constexpr (REC) {
+        // (the first step is the compiler's, which knows how long after a matrix instruction its results may be read)
+#pragma unroll
+        for (int t = 0; t < KT; ++t) {
+          tz[t] = fabsf(acc[t][0]) > 0.f ? acc[t][0] : 0.f;
+          tj[t] = 0;
+        }
+        auto step = [&](auto rc) __attribute__((always_inline)) {
+          constexpr int R = decltype(rc)::value;
+          argmax4<8 * (R / 4) + R % 4>(tz, tj, acc[0][R], acc[1][R], acc[2][R], acc[3][R]);
+        };
+        StaticFor<1, 16>::run(step);
+      }
 #pragma unroll
       for (int gi = 0; gi < NGRP; ++gi) {
         float zs = 0.f;
         int jf = 0;
         if constexpr (REC) {
-          // signed value at the arg-max and its index (without the lane-half term): an immediate per register
+          constexpr int TPG = G / 32;
+          zs = tz[gi * TPG];
+          jf = 32 * gi * TPG + tj[gi * TPG];
 #pragma unroll
-          for (int f = gi * RPG; f < (gi + 1) * RPG; ++f) {
-            const float z = acc[f / 16][f % 16];
-            if (fabsf(z) > fabsf(zs)) { zs = z; jf = 8 * (f / 4) + (f % 4); }
-          }
+          for (int t = gi * TPG + 1; t < (gi + 1) * TPG; ++t)
+            if (fabsf(tz[t]) > fabsf(zs)) { zs = tz[t]; jf = 32 * t + tj[t]; }
         } else {
           float a0 = 0.f;
 #pragma unroll
@@ -366,9 +408,10 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
     // Phase fences.  The compiler may move register-only work across a barrier; the empty asm statements take a
     // phase's results as in-out operands, so that everything that produces them stays before the barrier and
     // everything that consumes them after it (the scale factor included: the wait for its load belongs to the
-    // matrix phase, so that the vector phase never waits on the memory counter).
+    // matrix phase, so that the vector phase never waits on the memory counter; the running sum of the inverse phase too,
+    // whose 64 multiply-adds belong into the shadow of its products and not into the vector phase).
     auto fence_m = [&]() {
-      asm volatile("" : "+v"(usc), "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));
+      asm volatile("" : "+v"(usc), "+v"(s_l2), "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));
       __builtin_amdgcn_s_barrier();
     };
     auto fence_v = [&]() {
