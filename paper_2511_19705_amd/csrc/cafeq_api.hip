@@ -1013,7 +1013,7 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
   SingleWs w = carve_single(ws, pp, nb, grad);
   const QGrid grid = grid_for(cfg);
   const float beta = beta_for(cfg, grid);
-  const bool f16 = !asym && core_forward_f16(K, gp.Gk, cfg->bits);
+  const bool f16 = core_forward_f16(K, gp.Gk, cfg->bits);
 
   CoreParams p;
   fill_common(&p, W, pl, x->rep);
@@ -1136,7 +1136,7 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
   DualWs w = carve_dual(ws, qa, qb, nb, grad);
   const QGrid grid = grid_for(cfg);
   // the gradient-free pass over 128 x 128 blocks (one block per segment) takes half-precision forward operands
-  const bool f16A = !asym && core_forward_f16(K, ga.Gk, cfg->bits), f16B = !asym && core_forward_f16(K, gb.Gk, cfg->bits);
+  const bool f16A = core_forward_f16(K, ga.Gk, cfg->bits), f16B = core_forward_f16(K, gb.Gk, cfg->bits);
 
   {
     const SplitRequest req[4] = {{x->T, w.a.pfwd, 1, kFwdPlanes, f16A ? w.a.fs : nullptr, v2A ? 1 : 0, v2A ? 4 : 14},

@@ -44,14 +44,6 @@ constexpr int v2_tile_bytes(int parts) { return 32 * 128 * 2 * parts; }
 constexpr int kV2PlaneBytes = 4 * 2 * 128 * 64;        // one operand (T or T^-1) of one block: 64 KB
 constexpr int kV2Lds = 2 * kV2PlaneBytes + kV2Waves * kHdrFloats * 4 + 64;
 
-// REC: write the arg-max records (the gradient pass follows); OUT: write scales and / or codes
-typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
-// (x0, x1) -> packed float16 pair, round to nearest even (one v_cvt_pk_f16_f32), x0 in the low half
-__device__ __forceinline__ uint32_t pack_f16(float x0, float x1) {
-  floatx2 v = {x0, x1};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, halfx2));
-}
-
 // Four arg-max scans, one step each: where |z| > |best|, best = z and its index J (strictly greater: the lowest index
 // wins).  A mask that a comparison leaves in scalar registers may be read two instructions later at the earliest; one scan
 // at a time, as the compiler arranges them, has a wait behind each of a strip's 64 comparisons (70 of the vector phase's
@@ -77,7 +69,8 @@ __device__ __forceinline__ void argmax4(float (&b)[4], int (&j)[4], float z0, fl
       : "v"(z0), "v"(z1), "v"(z2), "v"(z3), "n"(J));
 }
 
-// bidx: the workgroup's index among the p.nwg workgroups that share the matrix; WP: parts of the prepared weights
+// bidx: the workgroup's index among the p.nwg workgroups that share the matrix; WP: parts of the prepared weights;
+// REC: write the arg-max records (the gradient pass follows); OUT: write scales and / or codes
 template <int G, int AXIS, bool REC, bool OUT, int WP>
 __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned bidx) {
   constexpr int L = 128, KT = 4, NGRP = L / G, RPG = G / 2;

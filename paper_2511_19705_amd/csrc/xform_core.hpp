@@ -174,6 +174,12 @@ __device__ __forceinline__ halfx8 as_halfx8(uint32_t a, uint32_t b, uint32_t c, 
   return __builtin_bit_cast(halfx8, v);
 }
 __device__ __forceinline__ halfx8 as_halfx8(uintx4 v) { return __builtin_bit_cast(halfx8, v); }
+typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
+// (x0, x1) -> packed float16 pair, round to nearest even (one v_cvt_pk_f16_f32), x0 in the low half
+__device__ __forceinline__ uint32_t pack_f16(float x0, float x1) {
+  floatx2 v = {x0, x1};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, halfx2));
+}
 #define CAFEQ_MFMA_F16(A, B, C) __builtin_amdgcn_mfma_f32_32x32x16_f16((A), (B), (C), 0, 0, 0)
 
 // s_waitcnt vmcnt(n) for a value of n that is a compile-time constant after unrolling (n is
@@ -260,7 +266,10 @@ __device__ __forceinline__ void load_strip(const CoreParams& p, float (&wreg)[L 
 // each by a power of two that puts its largest magnitude into [2^14, 2^15) -- with three part products
 // (hi.hi, hi.lo, lo.hi; relative error per term below 2^-20, the same order as the float32
 // accumulation) instead of six bfloat16 ones; the accumulators are scaled back before anything reads
-// them.  The inverse transform keeps the bfloat16 parts.
+// them.  The inverse transform keeps the bfloat16 parts.  The weights' parts are truncated on the symmetric grid (the
+// common deficit cancels in z / absmax) and rounded to nearest on the min/max grid, whose codes count from a minimum:
+// there what the parts leave out (7e-8 of a term, rms) is below what float32 accumulation adds, and half the products
+// round half as often: rms error of the transform 1.44e-7, with six bfloat16 products 1.8e-7 (blocks of 128).
 // LONGG: the variant for groups that span several segments (CoreParams::gspan; one group per segment inside
 // the kernel): its record-only sweep and its loss sweep with the group's absmax taken from the combined records.
 // ASYM: the min/max grid of Eq. (1) instead of the symmetric absmax grid (gradient-free variants only: the
@@ -268,7 +277,7 @@ __device__ __forceinline__ void load_strip(const CoreParams& p, float (&wreg)[L 
 template <int K, int G, int AXIS, bool GRAD, bool F16 = false, bool LONGG = false, bool ASYM = false>
 __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) void xform_core_kernel(const CoreParams p) {
   static_assert(!F16 || (!GRAD && Geo<K, G>::NBLK == 1), "half-precision forward: gradient-free, one block per segment");
-  static_assert(!ASYM || (!GRAD && !F16), "min/max grid: gradient-free, full-precision forward");
+  static_assert(!ASYM || !GRAD, "min/max grid: gradient-free");
   static_assert(!LONGG || (!GRAD && Geo<K, G>::NGRP == 1), "long groups: gradient-free, one group per segment");
   using g = Geo<K, G>;
   constexpr bool GRAD_ON = GRAD && g::GRAD_OK;
@@ -484,10 +493,16 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
             const float x0 = wreg[8 * c + 2 * i], x1 = wreg[8 * c + 2 * i + 1];
             if (p.do_inverse) s_wsq = fmaf(x0, x0, fmaf(x1, x1, s_wsq));
             const float y0 = x0 * wsc, y1 = x1 * wsc;
-            const auto hh = __builtin_amdgcn_cvt_pkrtz(y0, y1);
-            const auto hl = __builtin_amdgcn_cvt_pkrtz(y0 - float(hh[0]), y1 - float(hh[1]));
-            bh[i] = __builtin_bit_cast(uint32_t, hh);
-            bl[i] = __builtin_bit_cast(uint32_t, hl);
+            if constexpr (ASYM) {
+              bh[i] = pack_f16(y0, y1);
+              const halfx2 hh = __builtin_bit_cast(halfx2, bh[i]);
+              bl[i] = pack_f16(y0 - float(hh[0]), y1 - float(hh[1]));
+            } else {
+              const auto hh = __builtin_amdgcn_cvt_pkrtz(y0, y1);
+              const auto hl = __builtin_amdgcn_cvt_pkrtz(y0 - float(hh[0]), y1 - float(hh[1]));
+              bh[i] = __builtin_bit_cast(uint32_t, hh);
+              bl[i] = __builtin_bit_cast(uint32_t, hl);
+            }
           }
           const halfx8 vbh = as_halfx8(bh[0], bh[1], bh[2], bh[3]);
           const halfx8 vbl = as_halfx8(bl[0], bl[1], bl[2], bl[3]);

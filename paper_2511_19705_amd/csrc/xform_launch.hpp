@@ -77,18 +77,24 @@ int launch_core_k(int G, int axis, const CoreParams& p, hipStream_t st) {
 }
 
 // The variants for the min/max grid of Eq. (1) (instantiated in translation units of their own): gradient-free,
-// full-precision forward, with and without groups that span segments.
+// with and without groups that span segments.
 template <int K, int G, int AXIS>
 int launch_core_asym_t(const CoreParams& p, hipStream_t st) {
   const size_t lds = core_lds_bytes_t<K, G>(false);
   if (lds == 0 || lds > kMaxLds) return CAFEQ_ERR_UNSUPPORTED;
-  if (p.do_grad || p.fscale) return CAFEQ_ERR_INVALID_ARG;
+  if (p.do_grad || (p.fscale && !core_has_f16<K, G>())) return CAFEQ_ERR_INVALID_ARG;
   if (p.longg) {
     if constexpr (G >= K && (G == K || G == 128)) {
+      if constexpr (core_has_f16<K, G>()) {
+        if (p.fscale) return launch_core_v<K, G, AXIS, false, true, true, true>(p, lds, st);
+      }
       return launch_core_v<K, G, AXIS, false, false, true, true>(p, lds, st);
     } else {
       return CAFEQ_ERR_UNSUPPORTED;
     }
+  }
+  if constexpr (core_has_f16<K, G>()) {
+    if (p.fscale) return launch_core_v<K, G, AXIS, false, true, false, true>(p, lds, st);
   }
   return launch_core_v<K, G, AXIS, false, false, false, true>(p, lds, st);
 }
