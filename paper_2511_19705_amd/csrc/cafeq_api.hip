@@ -417,8 +417,9 @@ int run_core(int K, int axis, const GroupPlan& gp, CoreParams p, float2* rec, fl
 
 // Whether the gradient passes of a call can run with one workgroup per (matrix, block) and write the gradient in
 // its final form (grad_v2.hip): prepared weights, blocks of 128, no row-blocks sharing a transform block, and
-// enough blocks for most of the chip (up to four rounds of workgroups: the 27B-shaped (down, up) pair, 576 blocks,
-// measured 328 us this way against 350 for the partial sums and their reduction).
+// enough blocks for half of the chip (up to four rounds of workgroups: the 27B-shaped (down, up) pair, 576 blocks,
+// measured 328 us this way against 350 for the partial sums and their reduction; the 2B-shaped one, 144 blocks, 59
+// against 59 + 17 + 6 us with the loss reduction's launch, which this way does without).
 bool grad_owner_eligible(const cafeq_mat* const* mats, const PassPlans* const* pps, int n, int K, int rep) {
   if (K != 128 || rep != 1) return false;
   int64_t jobs = 0;
@@ -427,7 +428,7 @@ bool grad_owner_eligible(const cafeq_mat* const* mats, const PassPlans* const* p
     jobs += pps[i]->gpass.nseg;
   }
   const int cus = device_cu_count();
-  return jobs <= 4 * int64_t(cus) && jobs * 5 >= int64_t(cus) * 3;
+  return jobs <= 4 * int64_t(cus) && jobs * 2 >= int64_t(cus);
 }
 GradOwnerJob grad_owner_job(const cafeq_mat* W, int axis, const PassPlans& pp, const MemberWs& m, float* out,
                             int transpose_out) {

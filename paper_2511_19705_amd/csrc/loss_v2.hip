@@ -113,9 +113,10 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
 #pragma unroll
     for (int i = 0; i < 8 * WP; ++i) wq[i] = *reinterpret_cast<const uintx4*>(tp + i * 1024);
   };
-  // (The variants that write codes or scales keep their requests at the start of the matrix phase: their vector
-  // phase has no registers to hold a strip in flight.)
-  constexpr bool EARLY = !OUT;
+  // (The variants that write codes or scales from two-part weights keep their requests at the start of the matrix phase:
+  // their vector phase has no registers to hold a strip in flight.  One part fits: codes of the 27B-shaped gate in
+  // bfloat16 185 -> 173 us.)
+  constexpr bool EARLY = !OUT || WP == 1;
   // (16-byte code stores need the code matrix aligned to 16 bytes; its row length is a multiple of 128)
   const bool wide_codes = OUT && (reinterpret_cast<uintptr_t>(p.codes) & 15) == 0;
   if constexpr (EARLY) {
