@@ -860,7 +860,7 @@ __global__ __launch_bounds__(1024) void ns_init_kernel(const float* __restrict__
   }
 }
 // One Newton round X' = X + X R, R = I - T X, of blocks of 256 in one launch: columns j of X' need columns j of R and all
-// of X, columns j of R those of X and all of T, so a workgroup owns sixteen columns and streams T and X as matrix
+// of X, columns j of R those of X and all of T, so a workgroup owns SL columns and streams T and X as matrix
 // operands with no exchange between workgroups.  Eight waves, 32 rows each: a wave holds 16 rows of T (64 floats a lane)
 // per tile, scales each row by a power of two and splits it into two float16 parts; the slice of X sits in LDS the
 // same way (scaled per column), three part products (22 significant bits: R carries an error of about 1e-7 an entry).  The
@@ -868,33 +868,51 @@ __global__ __launch_bounds__(1024) void ns_init_kernel(const float* __restrict__
 // of operands per workgroup, and splitting them: 21 us for 8 blocks, 3-5 us when it copies.  (As two batched products on
 // the float32 matrix pipe, with launches that measured the residual, a warm start took 12 launches and 107 us, now 5 and
 // 70 us; 8 Adam steps on the 9B-shaped (V, O) pair 3700 -> 3050 us with the cold start's elimination avoided.)
-//   cur[b][16]: the slices' shares of ||R||_F^2.  prev: those of the round before (null: none).  A block whose last measured
-//   residual was below 1e-3 (its correction left less than 1e-6 and the parts' 3e-5) or is beyond any contraction to
-//   count on (||R||_F >= 3, a NaN) is copied, with its residual.  An entry that leaves float16's range makes R infinite.
-constexpr int kNsSlices = 16;
+// SL = 16 as long as those workgroups are at most one per compute unit (16 blocks), else 64, which split every row of T and
+// X a quarter as often: a cold start 5 % off rotations takes 120 us for 8 blocks, 207 us for 32 and 675 us for 144 (150, 246
+// and 867 us on the float32 products; sixteen columns for 144 blocks: nine rounds of workgroups a Newton round).
+//   cur[b][256 / SL]: the slices' shares of ||R||_F^2.  prev: those of the round before (null: none).  A block whose last
+//   measured residual was below 1e-3 (its correction left less than 1e-6 and the parts' 3e-5) or is beyond any contraction
+//   to count on (||R||_F >= 3, a NaN) is copied, with its residual.  An entry that leaves float16's range makes R infinite.
 constexpr float kNsAccept2 = 2.25e-4f;   // ||R||_F^2 before the last correction: 1.5e-2 leaves 2.3e-4 and the parts' 3e-5
+template <int SL>
+struct NsRound {
+  static constexpr int NC = SL / 16, NSL = 256 / SL, LD = 256 + 8;      // column tiles; slices per block; row of the LDS copies
+  static constexpr size_t bytes = size_t(3) * SL * LD * 2 + (8 * SL + 8) * sizeof(float);
+};
+template <int SL>
 __global__ __launch_bounds__(512) void ns256_round_kernel(const float* __restrict__ T, const float* __restrict__ X,
                                                           float* __restrict__ Xout, int nb, const float* __restrict__ prev,
                                                           float* __restrict__ cur) {
-  constexpr int K = 256, SL = K / kNsSlices, LD = K + 8;
+  constexpr int K = 256, LD = NsRound<SL>::LD, NC = NsRound<SL>::NC, NSL = NsRound<SL>::NSL;
   typedef float floatx4 __attribute__((ext_vector_type(4)));
-  __shared__ __align__(16) uint16_t xh[SL * LD], xl[SL * LD], rh[SL * LD];   // X^T in two parts, R^T in one: [column][row]
-  __shared__ float cmax[8][SL], red[8];
+  extern __shared__ __align__(16) unsigned char nsr_lds[];
+  uint16_t* xh = reinterpret_cast<uint16_t*>(nsr_lds);   // X^T in two parts, R^T in one: [column][row]
+  uint16_t* xl = xh + SL * LD;
+  uint16_t* rh = xl + SL * LD;
+  float* cmax = reinterpret_cast<float*>(rh + SL * LD);  // [8][SL]
+  float* red = cmax + 8 * SL;
   const int b = int(blockIdx.x) % nb, sl = int(blockIdx.x) / nb, j0 = sl * SL;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ln = lane & 15, lg = lane >> 4;
   const float* Tb = T + size_t(b) * K * K;
   const float* Xb = X + size_t(b) * K * K;
   float* Ob = Xout + size_t(b) * K * K;
-  // this thread's eight elements of the slice
+  // this thread's elements of the slice: columns 16 q + c .. + 7 of row l
   const int l = tid >> 1, c = (tid & 1) * 8;
-  const float4 s0 = *reinterpret_cast<const float4*>(Xb + l * K + j0 + c), s1 = *reinterpret_cast<const float4*>(Xb + l * K + j0 + c + 4);
+  float4 sv[NC][2];
+#pragma unroll
+  for (int q = 0; q < NC; ++q)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) sv[q][u] = *reinterpret_cast<const float4*>(Xb + l * K + j0 + 16 * q + c + 4 * u);
   if (prev) {
     float fp = 0.f;
-    for (int q = 0; q < kNsSlices; ++q) fp += prev[b * kNsSlices + q];
+    for (int q = 0; q < NSL; ++q) fp += prev[b * NSL + q];
     if (!(fp < 9.f) || fp <= 1e-6f) {            // uniform over the block
-      *reinterpret_cast<float4*>(Ob + l * K + j0 + c) = s0;
-      *reinterpret_cast<float4*>(Ob + l * K + j0 + c + 4) = s1;
-      if (tid == 0) cur[b * kNsSlices + sl] = sl == 0 ? fp : 0.f;
+#pragma unroll
+      for (int q = 0; q < NC; ++q)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) *reinterpret_cast<float4*>(Ob + l * K + j0 + 16 * q + c + 4 * u) = sv[q][u];
+      if (tid == 0) cur[b * NSL + sl] = sl == 0 ? fp : 0.f;
       return;
     }
   }
@@ -927,44 +945,51 @@ __global__ __launch_bounds__(512) void ns256_round_kernel(const float* __restric
   load_rows(Tb, i0, t0);
   load_rows(Tb, i0 + 16, t1);
   __builtin_amdgcn_sched_barrier(0);
-  float xs[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
-  {
+#pragma unroll
+  for (int q = 0; q < NC; ++q) {
+    const float x[8] = {sv[q][0].x, sv[q][0].y, sv[q][0].z, sv[q][0].w, sv[q][1].x, sv[q][1].y, sv[q][1].z, sv[q][1].w};
     float m[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      m[e] = fabsf(xs[e]);
+      m[e] = fabsf(x[e]);
 #pragma unroll
       for (int o = 2; o < 64; o *= 2) m[e] = fmaxf(m[e], __shfl_xor(m[e], o));
     }
     if (lane < 2)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) cmax[wave][c + e] = m[e];
+      for (int e = 0; e < 8; ++e) cmax[wave * SL + 16 * q + c + e] = m[e];
   }
   __syncthreads();
+  auto column_max = [&](int j) __attribute__((always_inline)) {
+    float m = cmax[j];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    float m = cmax[0][c + e];
+    for (int w = 1; w < 8; ++w) m = fmaxf(m, cmax[w * SL + j]);
+    return m;
+  };
 #pragma unroll
-    for (int w = 1; w < 8; ++w) m = fmaxf(m, cmax[w][c + e]);
-    float inv;
-    const float y = xs[e] * pow2_scale(m, &inv);
-    const _Float16 hi = _Float16(y), lo = _Float16(y - float(hi));
-    xh[(c + e) * LD + l] = __builtin_bit_cast(uint16_t, hi);
-    xl[(c + e) * LD + l] = __builtin_bit_cast(uint16_t, lo);
+  for (int q = 0; q < NC; ++q) {
+    const float x[8] = {sv[q][0].x, sv[q][0].y, sv[q][0].z, sv[q][0].w, sv[q][1].x, sv[q][1].y, sv[q][1].z, sv[q][1].w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int j = 16 * q + c + e;
+      float inv;
+      const float y = x[e] * pow2_scale(column_max(j), &inv);
+      const _Float16 hi = _Float16(y), lo = _Float16(y - float(hi));
+      xh[j * LD + l] = __builtin_bit_cast(uint16_t, hi);
+      xl[j * LD + l] = __builtin_bit_cast(uint16_t, lo);
+    }
   }
-  float inv_c;                                   // this lane's column
-  {
-    float m = cmax[0][ln];
+  float inv_c[NC];                               // this lane's columns
 #pragma unroll
-    for (int w = 1; w < 8; ++w) m = fmaxf(m, cmax[w][ln]);
-    (void)pow2_scale(m, &inv_c);
-  }
+  for (int n = 0; n < NC; ++n) (void)pow2_scale(column_max(16 * n + ln), &inv_c[n]);
   __syncthreads();
   float f2 = 0.f;
   auto residual = [&](const float4 (&u)[16], int i) __attribute__((always_inline)) {
     float inv_r;
     const float sc = row_scale(u, &inv_r);
-    floatx4 acc = {0.f, 0.f, 0.f, 0.f}, low = {0.f, 0.f, 0.f, 0.f};
+    floatx4 acc[NC], low[NC];
+#pragma unroll
+    for (int n = 0; n < NC; ++n) acc[n] = low[n] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
       const float y[8] = {u[2 * s].x * sc, u[2 * s].y * sc, u[2 * s].z * sc, u[2 * s].w * sc,
@@ -975,24 +1000,30 @@ __global__ __launch_bounds__(512) void ns256_round_kernel(const float* __restric
         ah[e] = _Float16(y[e]);
         al[e] = _Float16(y[e] - float(ah[e]));
       }
-      const halfx8 bh = as_halfx8(*reinterpret_cast<const uintx4*>(xh + ln * LD + 32 * s + 8 * lg));
-      const halfx8 bl = as_halfx8(*reinterpret_cast<const uintx4*>(xl + ln * LD + 32 * s + 8 * lg));
-      low = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, bh, low, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bh, acc, 0, 0, 0);
-      low = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bl, low, 0, 0, 0);
-    }
-    // element r: row i + 4 lg + r, column j0 + ln
-    float rv[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const float back = __shfl(inv_r, 4 * lg + r) * inv_c;
-      rv[r] = (i + 4 * lg + r == j0 + ln ? 1.f : 0.f) - (acc[r] + low[r]) * back;
-      f2 = fmaf(rv[r], rv[r], f2);
+      for (int n = 0; n < NC; ++n) {
+        const halfx8 bh = as_halfx8(*reinterpret_cast<const uintx4*>(xh + (16 * n + ln) * LD + 32 * s + 8 * lg));
+        const halfx8 bl = as_halfx8(*reinterpret_cast<const uintx4*>(xl + (16 * n + ln) * LD + 32 * s + 8 * lg));
+        low[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, bh, low[n], 0, 0, 0);
+        acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bh, acc[n], 0, 0, 0);
+        low[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bl, low[n], 0, 0, 0);
+      }
     }
-    uint32_t p[4];
+    float back[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) p[r] = __builtin_bit_cast(uint16_t, _Float16(rv[r] * 0x1p14f));
-    *reinterpret_cast<uint2*>(rh + ln * LD + i + 4 * lg) = make_uint2(p[0] | (p[1] << 16), p[2] | (p[3] << 16));
+    for (int r = 0; r < 4; ++r) back[r] = __shfl(inv_r, 4 * lg + r);
+    // element r: row i + 4 lg + r, column j0 + 16 n + ln
+#pragma unroll
+    for (int n = 0; n < NC; ++n) {
+      uint32_t p[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float rv = (i + 4 * lg + r == j0 + 16 * n + ln ? 1.f : 0.f) - (acc[n][r] + low[n][r]) * (back[r] * inv_c[n]);
+        f2 = fmaf(rv, rv, f2);
+        p[r] = __builtin_bit_cast(uint16_t, _Float16(rv * 0x1p14f));
+      }
+      *reinterpret_cast<uint2*>(rh + (16 * n + ln) * LD + i + 4 * lg) = make_uint2(p[0] | (p[1] << 16), p[2] | (p[3] << 16));
+    }
   };
   // (the rows of X for the correction are requested as soon as the rows of T have left their registers)
   residual(t0, i0);
@@ -1002,9 +1033,13 @@ __global__ __launch_bounds__(512) void ns256_round_kernel(const float* __restric
   residual(t1, i0 + 16);
   __builtin_amdgcn_sched_barrier(0);
   load_rows(Xb, i0 + 16, t1);
-  float old[8];
+  float old[2][NC][4];
 #pragma unroll
-  for (int r = 0; r < 8; ++r) old[r] = Xb[(i0 + 16 * (r / 4) + 4 * lg + r % 4) * K + j0 + ln];
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int n = 0; n < NC; ++n)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) old[t][n][r] = Xb[(i0 + 16 * t + 4 * lg + r) * K + j0 + 16 * n + ln];
   __builtin_amdgcn_sched_barrier(0);
   f2 = wave_sum(f2);
   if (lane == 0) red[wave] = f2;
@@ -1012,12 +1047,14 @@ __global__ __launch_bounds__(512) void ns256_round_kernel(const float* __restric
   if (tid == 0) {
     float t = red[0];
     for (int w = 1; w < 8; ++w) t += red[w];
-    cur[b * kNsSlices + sl] = t;
+    cur[b * NSL + sl] = t;
   }
-  auto correct = [&](const float4 (&u)[16], int i, const float* o) __attribute__((always_inline)) {
+  auto correct = [&](const float4 (&u)[16], int i, const float (&o)[NC][4]) __attribute__((always_inline)) {
     float inv_r;
     const float sc = row_scale(u, &inv_r);
-    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    floatx4 acc[NC];
+#pragma unroll
+    for (int n = 0; n < NC; ++n) acc[n] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
       const float y[8] = {u[2 * s].x * sc, u[2 * s].y * sc, u[2 * s].z * sc, u[2 * s].w * sc,
@@ -1025,17 +1062,20 @@ __global__ __launch_bounds__(512) void ns256_round_kernel(const float* __restric
       halfx8 ah;
 #pragma unroll
       for (int e = 0; e < 8; ++e) ah[e] = _Float16(y[e]);
-      const halfx8 bh = as_halfx8(*reinterpret_cast<const uintx4*>(rh + ln * LD + 32 * s + 8 * lg));
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bh, acc, 0, 0, 0);
+#pragma unroll
+      for (int n = 0; n < NC; ++n)
+        acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+            ah, as_halfx8(*reinterpret_cast<const uintx4*>(rh + (16 * n + ln) * LD + 32 * s + 8 * lg)), acc[n], 0, 0, 0);
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const float back = __shfl(inv_r, 4 * lg + r) * 0x1p-14f;
-      Ob[(i + 4 * lg + r) * K + j0 + ln] = fmaf(acc[r], back, o[r]);
+#pragma unroll
+      for (int n = 0; n < NC; ++n) Ob[(i + 4 * lg + r) * K + j0 + 16 * n + ln] = fmaf(acc[n][r], back, o[n][r]);
     }
   };
-  correct(t0, i0, old);
-  correct(t1, i0 + 16, old + 4);
+  correct(t0, i0, old[0]);
+  correct(t1, i0 + 16, old[1]);
 }
 
 }  // namespace
@@ -1194,21 +1234,34 @@ int launch_inverse256(const float* T, int nb, double* work, float* Tinv, float* 
   const size_t mat = size_t(nb) * K * K;
   double* res = work;
   float* buf[2] = {reinterpret_cast<float*>(work + mat), reinterpret_cast<float*>(work + mat) + mat};
-  float* norms = reinterpret_cast<float*>(work);             // [round][nb][kNsSlices]
+  float* norms = reinterpret_cast<float*>(work);             // [round][nb][slices]
+  const bool narrow = int64_t(nb) * NsRound<16>::NSL <= device_cu_count();
+  const int nsl = narrow ? NsRound<16>::NSL : NsRound<64>::NSL;
+  static std::atomic<bool> attr_set{false};
+  if (!attr_set) {
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(ns256_round_kernel<64>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            int(NsRound<64>::bytes)) != hipSuccess)
+      return CAFEQ_ERR_LAUNCH;
+    attr_set = true;
+  }
   if (!warm) hipLaunchKernelGGL(ns_init_kernel, dim3(nb, K / 32), dim3(1024), 0, st, T, buf[0], K);
   const int rounds = warm ? kWarm : kCold;
   const float* X = warm ? Tinv : buf[0];
   for (int r = 0; r < rounds; ++r) {
     float* Xn = X == buf[0] ? buf[1] : buf[0];
-    hipLaunchKernelGGL(ns256_round_kernel, dim3(unsigned(nb) * kNsSlices), dim3(512), 0, st, T, X, Xn, nb,
-                       r ? norms + size_t(r - 1) * nb * kNsSlices : nullptr, norms + size_t(r) * nb * kNsSlices);
+    const float* prev = r ? norms + size_t(r - 1) * nb * nsl : nullptr;
+    float* cur = norms + size_t(r) * nb * nsl;
+    if (narrow)
+      hipLaunchKernelGGL(ns256_round_kernel<16>, dim3(unsigned(nb) * nsl), dim3(512), NsRound<16>::bytes, st, T, X, Xn, nb, prev, cur);
+    else
+      hipLaunchKernelGGL(ns256_round_kernel<64>, dim3(unsigned(nb) * nsl), dim3(512), NsRound<64>::bytes, st, T, X, Xn, nb, prev, cur);
     X = Xn;
   }
   CAFEQ_CHECK_LAUNCH();
   GjArgs a;
   a.K = K; a.nz = 0; a.T = T; a.partial = nullptr; a.out = const_cast<float*>(X);
   a.status = status; a.status_stride = 1; a.status_offset = 0;
-  a.resid = norms + size_t(rounds - 1) * nb * kNsSlices; a.nresid = kNsSlices; a.resid_max = kNsAccept2;
+  a.resid = norms + size_t(rounds - 1) * nb * nsl; a.nresid = nsl; a.resid_max = kNsAccept2;
   if ((rc = launch_gj(a, nb, st))) return rc;
   // one Newton step X <- X + X (I - T X) with float64 residuals
   const unsigned grid = unsigned(nb) * (K / 32) * (K / 64);

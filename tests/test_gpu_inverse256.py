@@ -16,7 +16,7 @@ def env():
     return torch, cafeq
 
 
-@pytest.mark.parametrize("nb", [1, 3, 11])
+@pytest.mark.parametrize("nb", [1, 3, 16, 17])           # 16 and 17: either side of the slice width's rule
 def test_distances_from_a_rotation(env, nb):
     torch, cafeq = env
     rng = np.random.default_rng(70 + nb)
