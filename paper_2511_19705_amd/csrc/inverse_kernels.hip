@@ -20,14 +20,10 @@
 namespace cafeq {
 namespace {
 
-// (x0, x1) as a float16 pair and what that leaves of them; rounded towards zero: one packed instruction, and the low
-// part takes up the difference
-__device__ __forceinline__ uint32_t pack_rtz(float x0, float x1) {
-  return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(x0, x1));
-}
-__device__ __forceinline__ uint32_t pack_rtz_rest(float x0, float x1, uint32_t hi) {
+// what a float16 pair (pack_f16: rounded to nearest, a magnitude beyond float16's range to infinity) leaves of (x0, x1)
+__device__ __forceinline__ uint32_t pack_f16_rest(float x0, float x1, uint32_t hi) {
   const halfx2 p = __builtin_bit_cast(halfx2, hi);
-  return pack_rtz(x0 - float(p[0]), x1 - float(p[1]));
+  return pack_f16(x0 - float(p[0]), x1 - float(p[1]));
 }
 
 // Four signed bytes d1..d4 of round(x 2^30), |x| < 1: x = d1 2^-6 + d2 2^-14 + d3 2^-22 + d4 2^-30 up to 2^-31 (exact
@@ -52,7 +48,9 @@ typedef int intx16 __attribute__((ext_vector_type(16)));
 // registers and its 32 rows of T as A operands.  R = I - T X runs on two float16 parts per operand, three products
 // (22 significant bits: R carries an absolute error of about 1e-7, its Frobenius norm of 1e-5 at k = 128); the
 // correction X R, second order in what its rounding loses, on one part each.  T and X are scaled by powers of two
-// that keep the parts inside float16's range; an entry that leaves it makes R infinite, which no bound accepts.
+// that keep the parts inside float16's range; an entry that leaves it has an infinite high and an opposite infinite low
+// part, their column of R is not a number, and no bound accepts that.  (The parts are rounded to nearest.  Rounded towards
+// zero they saturate, and R belongs to another X than the one that is updated.)
 // LDS: X^T in two parts and R^T in one, as the accumulator layout delivers them (four consecutive rows of a column per
 // lane), and X in one part: 136 KB at k = 128.
 //   WARM 0: start from T^T / alpha.  WARM 1: start from the inverse already in Tinv.
@@ -149,8 +147,8 @@ __global__ __launch_bounds__(NsShape<K>::NW * 64) void ns_inverse_kernel(const f
     uintx4 ph, pl;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      ph[e] = pack_rtz(y[2 * e], y[2 * e + 1]);
-      pl[e] = pack_rtz_rest(y[2 * e], y[2 * e + 1], ph[e]);
+      ph[e] = pack_f16(y[2 * e], y[2 * e + 1]);
+      pl[e] = pack_f16_rest(y[2 * e], y[2 * e + 1], ph[e]);
     }
     th[s] = as_halfx8(ph);
     tl[s] = as_halfx8(pl);
@@ -185,9 +183,9 @@ __global__ __launch_bounds__(NsShape<K>::NW * 64) void ns_inverse_kernel(const f
         const float a0 = x[t][4 * g], a1 = x[t][4 * g + 1], a2 = x[t][4 * g + 2], a3 = x[t][4 * g + 3];
         const int o = (j0 + 32 * t) * LDH + i0 + 8 * g, q = (i0 + 8 * g) * LDH + j0 + 32 * t;
         uint2 ph, pl;
-        ph.x = pack_rtz(a0, a1); ph.y = pack_rtz(a2, a3);
-        pl.x = pack_rtz_rest(a0, a1, ph.x);
-        pl.y = pack_rtz_rest(a2, a3, ph.y);
+        ph.x = pack_f16(a0, a1); ph.y = pack_f16(a2, a3);
+        pl.x = pack_f16_rest(a0, a1, ph.x);
+        pl.y = pack_f16_rest(a2, a3, ph.y);
         *reinterpret_cast<uint2*>(xth + o) = ph;
         *reinterpret_cast<uint2*>(xtl + o) = pl;
         xr[q] = uint16_t(ph.x); xr[q + LDH] = uint16_t(ph.x >> 16);
@@ -232,8 +230,8 @@ __global__ __launch_bounds__(NsShape<K>::NW * 64) void ns_inverse_kernel(const f
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         uint2 pk;
-        pk.x = pack_rtz(acc[t][4 * g], acc[t][4 * g + 1]);
-        pk.y = pack_rtz(acc[t][4 * g + 2], acc[t][4 * g + 3]);
+        pk.x = pack_f16(acc[t][4 * g], acc[t][4 * g + 1]);
+        pk.y = pack_f16(acc[t][4 * g + 2], acc[t][4 * g + 3]);
         *reinterpret_cast<uint2*>(rt + (j0 + 32 * t) * LDH + i0 + 8 * g) = pk;
       }
     __syncthreads();
@@ -367,8 +365,8 @@ __global__ __launch_bounds__(NsShape<K>::NW * 64) void ns_inverse_kernel(const f
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           uint2 pk;
-          pk.x = pack_rtz(float(tot[t][4 * q]) * rs, float(tot[t][4 * q + 1]) * rs);
-          pk.y = pack_rtz(float(tot[t][4 * q + 2]) * rs, float(tot[t][4 * q + 3]) * rs);
+          pk.x = pack_f16(float(tot[t][4 * q]) * rs, float(tot[t][4 * q + 1]) * rs);
+          pk.y = pack_f16(float(tot[t][4 * q + 2]) * rs, float(tot[t][4 * q + 3]) * rs);
           *reinterpret_cast<uint2*>(rt + (j0 + 32 * t) * LDH + i0 + 8 * q) = pk;
         }
       __syncthreads();

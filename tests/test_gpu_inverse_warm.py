@@ -1,0 +1,46 @@
+"""GPU parity: the inverse of a learning loop's iteration, which starts from the one before.  The loops hand back the
+inverse of their last transform, made from scratch, so this one is called by its name in the library."""
+import ctypes
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def warm():
+    import torch
+    from paper_2511_19705_amd import cafeq
+    fn = cafeq.lib["_ZN5cafeq25launch_block_inverse_warmEPKfiiPdPfPiP12ihipStream_t"]
+    fn.restype = ctypes.c_int
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int] + [ctypes.c_void_p] * 4
+
+    def call(T, X0):
+        """(inverse of T from the start X0, status), as float64 and int arrays"""
+        nb, k, _ = T.shape
+        Td, X = torch.from_numpy(T).to("cuda:0"), torch.from_numpy(X0).to("cuda:0")
+        status = torch.full((nb,), 7, dtype=torch.int32, device="cuda:0")
+        work = torch.zeros(2 * nb * k * k, dtype=torch.float64, device="cuda:0")     # as cafeq_workspace_bytes has it
+        rc = fn(Td.data_ptr(), k, nb, work.data_ptr(), X.data_ptr(), status.data_ptr(), torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert rc == 0
+        return X.cpu().numpy().astype(np.float64), status.cpu().numpy()
+    return call
+
+
+@pytest.mark.parametrize("k", [32, 64, 128, 256])
+@pytest.mark.parametrize("entry", [98300.0, 65500.0, 65519.0, 65521.0, 131000.0, 3e5])
+def test_entries_beyond_the_range_of_float16(warm, k, entry):
+    """A signed permutation with one entry small enough that its inverse's, scaled as the iteration scales it (by 256 for a
+    largest |T| of 1), lies about float16's largest number: 98300 is 65504 and 32796, which float16 has not."""
+    rng = np.random.default_rng(k)
+    T = np.eye(k)[rng.permutation(k)] * rng.choice([-1.0, 1.0], (k, 1))
+    T[5] *= 256.0 / entry
+    T = T[None].astype(np.float32)
+    ref = np.linalg.inv(T.astype(np.float64))
+    got, status = warm(T, ref.astype(np.float32))
+    assert status[0] == 0
+    # (an entry per row and column: float32 rounding of each)
+    assert np.abs(got - ref).max(initial=0, where=ref == 0) == 0
+    np.testing.assert_allclose(got[ref != 0], ref[ref != 0], rtol=2.0 ** -22)
