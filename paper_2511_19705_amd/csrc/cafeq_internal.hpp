@@ -129,8 +129,7 @@ int launch_gj_solve(int K, int nb, int nz, const float* partial, double* work, f
 int launch_inverse256(const float* T, int nb, double* work, float* Tinv, float* rho_row, float* rho_col, int* status,
                       bool warm, hipStream_t st);
 // inverse_kernels.hip
-// inside a learning loop: Tinv holds the previous inverse on entry (Newton warm start, elimination as fallback);
-// accurate to about 3e-6 relative
+// inside a learning loop: Tinv holds the previous inverse on entry (Newton warm start, elimination as fallback)
 int launch_block_inverse_warm(const float* T, int K, int nb, double* work, float* Tinv, int* status, hipStream_t st);
 int launch_block_inverse(const float* T, int K, int nb, double* work, float* Tinv, float* rho_row,
                          float* rho_col, int* status, hipStream_t st);

@@ -54,16 +54,14 @@ typedef int intx16 __attribute__((ext_vector_type(16)));
 // LDS: X^T in two parts and R^T in one, as the accumulator layout delivers them (four consecutive rows of a column per
 // lane), and X in one part: 136 KB at k = 128.
 //   WARM 0: start from T^T / alpha.  WARM 1: start from the inverse already in Tinv.
-//   REFINE: the round that starts at ||R||_F <= 3e-3 is the last; one Newton step with an exact residual follows, which
-//           leaves ||R||_F^2 <= 4e-10: the result carries its rounding to float32 only, like the float64 elimination's.
-//           The exact residual runs on the 8-bit integer matrix pipe: T and X as four signed base-256 digits of 31-bit
-//           fixed-point values, the thirteen digit products of weight >= 2^-44 summed in 32-bit integers; R is known to
-//           be below 2^-14, so it is the sum modulo 2^32 (the identity drops out).  That is 1.7 k cycles per 32 x 32 tile
-//           at k = 128; v_mfma_f64_16x16x4_f64, which sustains about a third of its published rate here, took 25 k (29 us
-//           for 112 blocks even on four workgroups per block).
-//           A block of 64 or 128 that is a rotation to float32 accuracy (max |I - T T^T| <= 2e-6) gets T^T itself.
-//   !REFINE (learning loops): a round that promises max |R^2| <= 4e-6 is the last; what remains is below the 16-bit
-//           operand parts the loss pass makes of the inverse.
+// The round that starts at ||R||_F <= 3e-3 is the last; one Newton step with an exact residual follows, which leaves
+// ||R||_F^2 <= 4e-10: the result carries its rounding to float32 only, like the float64 elimination's.
+// The exact residual runs on the 8-bit integer matrix pipe: T and X as four signed base-256 digits of 31-bit
+// fixed-point values, the thirteen digit products of weight >= 2^-44 summed in 32-bit integers; R is known to
+// be below 2^-14, so it is the sum modulo 2^32 (the identity drops out).  That is 1.7 k cycles per 32 x 32 tile
+// at k = 128; v_mfma_f64_16x16x4_f64, which sustains about a third of its published rate here, took 25 k (29 us
+// for 112 blocks even on four workgroups per block).
+// A block of 64 or 128 that is a rotation to float32 accuracy (max |I - T T^T| <= 2e-6) gets T^T itself.
 // tiles of 32 columns per wave: at k = 128 two, so that eight waves have the registers for their rows of T (sixteen
 // waves of one tile spilled 35)
 template <int K>
@@ -76,7 +74,7 @@ struct NsShape {
   static constexpr int LDS = K + 4;      // floats per row of T on its way to the registers
   static_assert(K * LDS * 4 <= 3 * K * LDH * 2, "and so does T");
 };
-template <int K, int WARM, bool REFINE>
+template <int K, int WARM>
 __global__ __launch_bounds__(NsShape<K>::NW * 64) void ns_inverse_kernel(const float* __restrict__ T,
                                                                          float* __restrict__ Tinv,
                                                                          int* __restrict__ status) {
@@ -240,19 +238,11 @@ __global__ __launch_bounds__(NsShape<K>::NW * 64) void ns_inverse_kernel(const f
     for (int w = 1; w < NW; ++w) { rmax = fmaxf(rmax, red[w]); fro2 += red[NW + w]; }
     rmax *= 0x1p-14f;
     fro2 *= 0x1p-28f;
-    bool last;
-    if constexpr (REFINE) {
-      // R_new = R^2: a contraction at every round, or none to count on (a start outside, a NaN, noise above the bound)
-      if (!(fro2 < (WARM ? 0.25f : 9.f)) || (it > 0 && !(fro2 < 0.7f * prev))) break;
-      if (K != 32 && unit && it == 0 && rmax <= 2e-6f) { result = kTranspose; break; }
-      last = fro2 <= 9e-6f;                      // then ||R||_F <= 9e-6 and what the parts lose, below 2e-5
-      prev = fro2;
-    } else {
-      if (!(fro2 < 0.25f)) break;                // ||R||_2 <= ||R||_F
-      if (rmax <= 4e-6f) { result = kConverged; break; }
-      last = fminf(float(K) * rmax * rmax, fro2) <= 4e-6f;
-      if (it == 2 && !last) break;
-    }
+    // R_new = R^2: a contraction at every round, or none to count on (a start outside, a NaN, noise above the bound)
+    if (!(fro2 < (WARM ? 0.25f : 9.f)) || (it > 0 && !(fro2 < 0.7f * prev))) break;
+    if (K != 32 && unit && it == 0 && rmax <= 2e-6f) { result = kTranspose; break; }
+    const bool last = fro2 <= 9e-6f;             // then ||R||_F <= 9e-6 and what the parts lose, below 2e-5
+    prev = fro2;
 #pragma unroll
     for (int t = 0; t < TPW; ++t)
 #pragma unroll
@@ -281,115 +271,113 @@ __global__ __launch_bounds__(NsShape<K>::NW * 64) void ns_inverse_kernel(const f
     gj_panel_body<K, 4, 4 * TPW, double, true>(a, b, *reinterpret_cast<GjShared<K, double>*>(ns_lds));
     return;
   }
-  if constexpr (REFINE) {
-    if (result == kConverged) {
-      float xm = 0.f;
+  if (result == kConverged) {
+    float xm = 0.f;
 #pragma unroll
-      for (int t = 0; t < TPW; ++t)
+    for (int t = 0; t < TPW; ++t)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) xm = fmaxf(xm, fabsf(x[t][v]));
-      xm = cluster_allmax<64>(xm);
-      // T again, as digits of 2^-ex T: A operands, sixteen contraction indices per lane and step
-      __syncthreads();                           // (slower waves are still reading red and the last round's operands)
-      if (lane == 0) red[wave] = xm;
-      stage_t();
-      __syncthreads();
-      intx4 td[4][K / 32];
+      for (int v = 0; v < 16; ++v) xm = fmaxf(xm, fabsf(x[t][v]));
+    xm = cluster_allmax<64>(xm);
+    // T again, as digits of 2^-ex T: A operands, sixteen contraction indices per lane and step
+    __syncthreads();                           // (slower waves are still reading red and the last round's operands)
+    if (lane == 0) red[wave] = xm;
+    stage_t();
+    __syncthreads();
+    intx4 td[4][K / 32];
 #pragma unroll
-      for (int s = 0; s < K / 32; ++s)
+    for (int s = 0; s < K / 32; ++s)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const float4 u = *reinterpret_cast<const float4*>(trow + 32 * s + 16 * h + 4 * g);
-          const float sc = ldexpf(1.f, -ex), y[4] = {u.x * sc, u.y * sc, u.z * sc, u.w * sc};
-          uint32_t d[4];
-          digit_words(y, d);
+      for (int g = 0; g < 4; ++g) {
+        const float4 u = *reinterpret_cast<const float4*>(trow + 32 * s + 16 * h + 4 * g);
+        const float sc = ldexpf(1.f, -ex), y[4] = {u.x * sc, u.y * sc, u.z * sc, u.w * sc};
+        uint32_t d[4];
+        digit_words(y, d);
 #pragma unroll
-          for (int p = 0; p < 4; ++p) td[p][s][g] = int(d[p]);
-        }
-      xm = red[0];
+        for (int p = 0; p < 4; ++p) td[p][s][g] = int(d[p]);
+      }
+    xm = red[0];
 #pragma unroll
-      for (int w = 1; w < NW; ++w) xm = fmaxf(xm, red[w]);
-      int exx = 0;
-      (void)frexpf(xm, &exx);
-      exx = exx > 6 ? exx : 6;                   // 2^(exx - 20): what |R| has to stay below (see g)
-      const float sd = ldexpf(1.f, -exx);
-      unsigned char* dig = ns_lds;               // [digit][j][LDG]: X^T
-      __syncthreads();                           // every wave has its rows of T
+    for (int w = 1; w < NW; ++w) xm = fmaxf(xm, red[w]);
+    int exx = 0;
+    (void)frexpf(xm, &exx);
+    exx = exx > 6 ? exx : 6;                   // 2^(exx - 20): what |R| has to stay below (see g)
+    const float sd = ldexpf(1.f, -exx);
+    unsigned char* dig = ns_lds;               // [digit][j][LDG]: X^T
+    __syncthreads();                           // every wave has its rows of T
 #pragma unroll
-      for (int t = 0; t < TPW; ++t)
+    for (int t = 0; t < TPW; ++t)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const float y[4] = {x[t][4 * g] * sd, x[t][4 * g + 1] * sd, x[t][4 * g + 2] * sd, x[t][4 * g + 3] * sd};
-          uint32_t d[4];
-          digit_words(y, d);
+      for (int g = 0; g < 4; ++g) {
+        const float y[4] = {x[t][4 * g] * sd, x[t][4 * g + 1] * sd, x[t][4 * g + 2] * sd, x[t][4 * g + 3] * sd};
+        uint32_t d[4];
+        digit_words(y, d);
 #pragma unroll
-          for (int p = 0; p < 4; ++p)
-            *reinterpret_cast<uint32_t*>(dig + (p * K + j0 + 32 * t) * S::LDG + i0 + 8 * g) = d[p];
-        }
-      __syncthreads();
-      // one sum per weight 2^-12, 2^-20, .. 2^-44 (neighbouring matrix instructions then do not depend on each other),
-      // folded largest first: tot = 256 tot + the next weight's sum, modulo 2^32
-      intx16 tot[TPW];
+        for (int p = 0; p < 4; ++p)
+          *reinterpret_cast<uint32_t*>(dig + (p * K + j0 + 32 * t) * S::LDG + i0 + 8 * g) = d[p];
+      }
+    __syncthreads();
+    // one sum per weight 2^-12, 2^-20, .. 2^-44 (neighbouring matrix instructions then do not depend on each other),
+    // folded largest first: tot = 256 tot + the next weight's sum, modulo 2^32
+    intx16 tot[TPW];
 #pragma unroll
-      for (int t = 0; t < TPW; ++t) {
-        intx16 part[5];
+    for (int t = 0; t < TPW; ++t) {
+      intx16 part[5];
 #pragma unroll
-        for (int w = 0; w < 5; ++w)
+      for (int w = 0; w < 5; ++w)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) part[w][v] = 0;
+        for (int v = 0; v < 16; ++v) part[w][v] = 0;
 #pragma unroll
-        for (int s = 0; s < K / 32; ++s) {
-          intx4 xd[4];
+      for (int s = 0; s < K / 32; ++s) {
+        intx4 xd[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          xd[q] = *reinterpret_cast<const intx4*>(dig + (q * K + j0 + 32 * t) * S::LDG + 32 * s + 16 * h);
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
 #pragma unroll
           for (int q = 0; q < 4; ++q)
-            xd[q] = *reinterpret_cast<const intx4*>(dig + (q * K + j0 + 32 * t) * S::LDG + 32 * s + 16 * h);
-#pragma unroll
-          for (int p = 0; p < 4; ++p)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              if (p + q < 5) part[p + q] = __builtin_amdgcn_mfma_i32_32x32x32_i8(td[p][s], xd[q], part[p + q], 0, 0, 0);
-        }
-        tot[t] = part[0];
-#pragma unroll
-        for (int w = 1; w < 5; ++w)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) tot[t][v] = int((uint32_t(tot[t][v]) << 8) + uint32_t(part[w][v]));
+            if (p + q < 5) part[p + q] = __builtin_amdgcn_mfma_i32_32x32x32_i8(td[p][s], xd[q], part[p + q], 0, 0, 0);
       }
-      __syncthreads();                           // every wave is done with the digits
-      // T X is 2^g times the digits' sum (x itself carries sX = 2^(7 + ex)): the identity is 2^(44 - g), zero modulo
-      // 2^32 for every x that float16 holds (g <= 9), and R = -2^(g - 44) tot for |R| < 2^(g - 13); handed on as 2^20 R
-      const int g = exx - 7;
-      const float rs = -ldexpf(1.f, g - 24), back = 0x1p-20f;
+      tot[t] = part[0];
 #pragma unroll
-      for (int t = 0; t < TPW; ++t)
+      for (int w = 1; w < 5; ++w)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          uint2 pk;
-          pk.x = pack_f16(float(tot[t][4 * q]) * rs, float(tot[t][4 * q + 1]) * rs);
-          pk.y = pack_f16(float(tot[t][4 * q + 2]) * rs, float(tot[t][4 * q + 3]) * rs);
-          *reinterpret_cast<uint2*>(rt + (j0 + 32 * t) * LDH + i0 + 8 * q) = pk;
-        }
-      __syncthreads();
-      floatx16 acc[TPW];
-#pragma unroll
-      for (int t = 0; t < TPW; ++t)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
-      // (xr: X before the last round's update; the difference is of third order)
-#pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        const halfx8 av = as_halfx8(*reinterpret_cast<const uintx4*>(xr + (i0 - 4 * h + ln) * LDH + 16 * s + 8 * h));
-#pragma unroll
-        for (int t = 0; t < TPW; ++t) {
-          const halfx8 bv = as_halfx8(*reinterpret_cast<const uintx4*>(rt + (j0 + 32 * t) * LDH + 16 * s + 8 * h));
-          acc[t] = CAFEQ_MFMA_F16(av, bv, acc[t]);
-        }
-      }
-#pragma unroll
-      for (int t = 0; t < TPW; ++t)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) x[t][v] = fmaf(acc[t][v], back, x[t][v]);
+        for (int v = 0; v < 16; ++v) tot[t][v] = int((uint32_t(tot[t][v]) << 8) + uint32_t(part[w][v]));
     }
+    __syncthreads();                           // every wave is done with the digits
+    // T X is 2^g times the digits' sum (x itself carries sX = 2^(7 + ex)): the identity is 2^(44 - g), zero modulo
+    // 2^32 for every x that float16 holds (g <= 9), and R = -2^(g - 44) tot for |R| < 2^(g - 13); handed on as 2^20 R
+    const int g = exx - 7;
+    const float rs = -ldexpf(1.f, g - 24), back = 0x1p-20f;
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        uint2 pk;
+        pk.x = pack_f16(float(tot[t][4 * q]) * rs, float(tot[t][4 * q + 1]) * rs);
+        pk.y = pack_f16(float(tot[t][4 * q + 2]) * rs, float(tot[t][4 * q + 3]) * rs);
+        *reinterpret_cast<uint2*>(rt + (j0 + 32 * t) * LDH + i0 + 8 * q) = pk;
+      }
+    __syncthreads();
+    floatx16 acc[TPW];
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
+    // (xr: X before the last round's update; the difference is of third order)
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const halfx8 av = as_halfx8(*reinterpret_cast<const uintx4*>(xr + (i0 - 4 * h + ln) * LDH + 16 * s + 8 * h));
+#pragma unroll
+      for (int t = 0; t < TPW; ++t) {
+        const halfx8 bv = as_halfx8(*reinterpret_cast<const uintx4*>(rt + (j0 + 32 * t) * LDH + 16 * s + 8 * h));
+        acc[t] = CAFEQ_MFMA_F16(av, bv, acc[t]);
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) x[t][v] = fmaf(acc[t][v], back, x[t][v]);
   }
 #pragma unroll
   for (int t = 0; t < TPW; ++t)
@@ -398,19 +386,19 @@ __global__ __launch_bounds__(NsShape<K>::NW * 64) void ns_inverse_kernel(const f
   if (status && tid == 0) status[b] = 0;
 }
 
-template <int K, int WARM, bool REFINE>
+template <int K, int WARM>
 int launch_ns(const float* T, int nb, float* Tinv, int* status, hipStream_t st) {
   constexpr size_t lds = NsShape<K>::bytes;
   if (lds > 64 * 1024) {
     static std::atomic<bool> attr_set{false};
     if (!attr_set) {
-      if (hipFuncSetAttribute(reinterpret_cast<const void*>(ns_inverse_kernel<K, WARM, REFINE>),
+      if (hipFuncSetAttribute(reinterpret_cast<const void*>(ns_inverse_kernel<K, WARM>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) != hipSuccess)
         return CAFEQ_ERR_LAUNCH;
       attr_set = true;
     }
   }
-  hipLaunchKernelGGL((ns_inverse_kernel<K, WARM, REFINE>), dim3(nb), dim3(NsShape<K>::NW * 64), lds, st, T, Tinv, status);
+  hipLaunchKernelGGL((ns_inverse_kernel<K, WARM>), dim3(nb), dim3(NsShape<K>::NW * 64), lds, st, T, Tinv, status);
   CAFEQ_CHECK_LAUNCH();
   return CAFEQ_OK;
 }
@@ -420,9 +408,9 @@ int launch_block_inverse(const float* T, int K, int nb, double* work, float* Tin
                          int* status, hipStream_t st) {
   int rc = CAFEQ_ERR_UNSUPPORTED;
   switch (K) {
-    case 32: rc = launch_ns<32, 0, true>(T, nb, Tinv, status, st); break;
-    case 64: rc = launch_ns<64, 0, true>(T, nb, Tinv, status, st); break;
-    case 128: rc = launch_ns<128, 0, true>(T, nb, Tinv, status, st); break;
+    case 32: rc = launch_ns<32, 0>(T, nb, Tinv, status, st); break;
+    case 64: rc = launch_ns<64, 0>(T, nb, Tinv, status, st); break;
+    case 128: rc = launch_ns<128, 0>(T, nb, Tinv, status, st); break;
     case 256: return launch_inverse256(T, nb, work, Tinv, rho_row, rho_col, status, false, st);
   }
   if (rc) return rc;
@@ -437,9 +425,9 @@ int launch_block_inverse(const float* T, int K, int nb, double* work, float* Tin
 // The inverse inside a learning loop: Tinv holds the previous iteration's inverse on entry.
 int launch_block_inverse_warm(const float* T, int K, int nb, double* work, float* Tinv, int* status, hipStream_t st) {
   switch (K) {
-    case 32: return launch_ns<32, 1, true>(T, nb, Tinv, status, st);
-    case 64: return launch_ns<64, 1, false>(T, nb, Tinv, status, st);
-    case 128: return launch_ns<128, 1, false>(T, nb, Tinv, status, st);
+    case 32: return launch_ns<32, 1>(T, nb, Tinv, status, st);
+    case 64: return launch_ns<64, 1>(T, nb, Tinv, status, st);
+    case 128: return launch_ns<128, 1>(T, nb, Tinv, status, st);
     case 256: return launch_inverse256(T, nb, work, Tinv, nullptr, nullptr, status, true, st);
     default: return CAFEQ_ERR_UNSUPPORTED;
   }

@@ -44,3 +44,26 @@ def test_entries_beyond_the_range_of_float16(warm, k, entry):
     # (an entry per row and column: float32 rounding of each)
     assert np.abs(got - ref).max(initial=0, where=ref == 0) == 0
     np.testing.assert_allclose(got[ref != 0], ref[ref != 0], rtol=2.0 ** -22)
+
+
+def _conditioned(k, nb, cond, rng):
+    """Blocks of condition number `cond`, singular values evenly spread over their logarithm, 1 in the root mean square."""
+    U, V = (np.linalg.qr(rng.standard_normal((nb, k, k)))[0] for _ in range(2))
+    s = float(cond) ** (-np.arange(k) / (k - 1))
+    return (U * (s / np.sqrt((s * s).mean()))) @ V
+
+
+@pytest.mark.parametrize("k", [32, 64, 128, 256])
+@pytest.mark.parametrize("cond", [1, 3, 10, 30, 100])
+@pytest.mark.parametrize("step", [0.0, 1e-6, 1e-4, 1e-3, 1e-2])
+def test_the_loops_inverse_carries_its_rounding_alone(warm, k, cond, step):
+    """T a step of equal size in every entry (as Adam makes it) from the T whose inverse the iteration starts at."""
+    rng = np.random.default_rng(1000 * k + cond)
+    T0 = _conditioned(k, 5, cond, rng).astype(np.float32)
+    T = (T0 + step / (cond * np.sqrt(k)) * rng.choice([-1.0, 1.0], T0.shape)).astype(np.float32)
+    got, status = warm(T, np.linalg.inv(T0.astype(np.float64)).astype(np.float32))
+    assert not status.any()
+    ref = np.linalg.inv(T.astype(np.float64))
+    # rounding to float32 is at most 2^-24 of every entry (and half of that in the root mean square)
+    err = np.linalg.norm(got - ref, axis=(1, 2)) / np.linalg.norm(ref, axis=(1, 2))
+    assert err.max() <= 2.0 ** -24, err.max()
