@@ -131,8 +131,8 @@ size_t cafeq_workspace_bytes(int call_id, const cafeq_mat* a, const cafeq_mat* b
 
 /* Blockwise inverse and the squared norms the surrogate needs (paper Sec. 4.1: the
  * (M^-1)_{ij}^2 factors).  Tinv[nb][k][k] = T^-1 per block, to float32 rounding.  Blocks near a scaled rotation (up to
- * 128) are inverted by Newton's iteration X <- X + X (I - T X) from T^T ||T||_F^-2 k, used only where the residual it
- * measures promises ||I - T X||_F <= 2e-5, with a last step on an exact residual; every other block by Gauss-Jordan
+ * 128) are inverted by Newton's iteration X <- X + X (I - T X) from T^T ||T||_F^-2 k, used only where it measures
+ * ||I - T X||_F <= 2e-5 before its last step, whose residual is exact; every other block by Gauss-Jordan
  * elimination with partial pivoting, float64 internally.  A block of 64 or 128 verified to be a rotation to float32
  * accuracy -- max |I - T T^T| <= 2e-6 -- is inverted by transposition.  Blocks of 256 are eliminated in float32 with one
  * Newton step on float64 residuals, and those near a scaled rotation are first tried with Newton-Schulz rounds from

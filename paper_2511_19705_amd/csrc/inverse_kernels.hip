@@ -12,7 +12,7 @@
 // the products and the rest splitting, LDS and barriers.  Measured, blocks 5 % off rotations, against a launch that
 // checked for rotations and one that eliminated the others: 112 blocks of 128 11 + 111 -> 30 us (57 k cycles: start 14 k,
 // three rounds 28 k, the exact step 15 k), 288 blocks (more than one per compute unit) 26 + 198 -> 60 us, 144 blocks of
-// 64 5 + 36 -> 11.5 us, 8 blocks of 32 16.6 -> 6.9 us; the learning loops' warm start at 72 blocks of 128 30 + 5 -> 18 us.
+// 64 5 + 36 -> 11.5 us, 8 blocks of 32 16.6 -> 7.5 us; the learning loops' warm start at 72 blocks of 128 30 + 5 -> 23.5 us.
 #include <atomic>
 
 #include "gj_panel.hpp"
@@ -54,11 +54,12 @@ typedef int intx16 __attribute__((ext_vector_type(16)));
 // LDS: X^T in two parts and R^T in one, as the accumulator layout delivers them (four consecutive rows of a column per
 // lane), and X in one part: 136 KB at k = 128.
 //   WARM 0: start from T^T / alpha.  WARM 1: start from the inverse already in Tinv.
-// The round that starts at ||R||_F <= 3e-3 is the last; one Newton step with an exact residual follows, which leaves
-// ||R||_F^2 <= 4e-10: the result carries its rounding to float32 only, like the float64 elimination's.
+// The round that starts at ||R||_F <= 3e-3 is the last; one Newton step with an exact residual follows, which measures
+// ||R||_F <= 2e-5 (else the block is eliminated) and leaves its square: the result carries its rounding to float32 only,
+// like the float64 elimination's.
 // The exact residual runs on the 8-bit integer matrix pipe: T and X as four signed base-256 digits of 31-bit
-// fixed-point values, the thirteen digit products of weight >= 2^-44 summed in 32-bit integers; R is known to
-// be below 2^-14, so it is the sum modulo 2^32 (the identity drops out).  That is 1.7 k cycles per 32 x 32 tile
+// fixed-point values, the thirteen digit products of weight >= 2^-44 summed in 32-bit integers, one sum a weight, and the
+// sums taken from the identity one after the other.  That is 1.7 k cycles per 32 x 32 tile
 // at k = 128; v_mfma_f64_16x16x4_f64, which sustains about a third of its published rate here, took 25 k (29 us
 // for 112 blocks even on four workgroups per block).
 // A block of 64 or 128 that is a rotation to float32 accuracy (max |I - T T^T| <= 2e-6) gets T^T itself.
@@ -72,6 +73,11 @@ struct NsShape {
   static constexpr size_t bytes = it > gj ? it : gj;
   static_assert(4 * K * LDG <= 3 * K * LDH * 2, "the digits lie over X^T and R^T");
   static constexpr int LDS = K + 4;      // floats per row of T on its way to the registers
+  // log2 max|T| max|X| up to which the exact residual's digits are used.  At k = 32, where the elimination costs no more than
+  // two rounds, as far as they reach its precision (off float64 2.5e-8 in the root mean square; condition 10 is 1, at 100
+  // 2.57e-8, at 1000 3.8e-8).  64 and 128 are bounded by the residual they measure, which eliminates from condition 300 or
+  // so on (2.58e-8 at condition 100); 9: what float16 holds of X.
+  static constexpr int kMaxShift = K == 32 ? 1 : 9;
   static_assert(K * LDS * 4 <= 3 * K * LDH * 2, "and so does T");
 };
 template <int K, int WARM>
@@ -241,7 +247,7 @@ __global__ __launch_bounds__(NsShape<K>::NW * 64) void ns_inverse_kernel(const f
     // R_new = R^2: a contraction at every round, or none to count on (a start outside, a NaN, noise above the bound)
     if (!(fro2 < (WARM ? 0.25f : 9.f)) || (it > 0 && !(fro2 < 0.7f * prev))) break;
     if (K != 32 && unit && it == 0 && rmax <= 2e-6f) { result = kTranspose; break; }
-    const bool last = fro2 <= 9e-6f;             // then ||R||_F <= 9e-6 and what the parts lose, below 2e-5
+    const bool last = fro2 <= 9e-6f;             // then ||R||_F <= 9e-6 and what the parts lose: 2e-5 is expected
     prev = fro2;
 #pragma unroll
     for (int t = 0; t < TPW; ++t)
@@ -263,15 +269,8 @@ __global__ __launch_bounds__(NsShape<K>::NW * 64) void ns_inverse_kernel(const f
     if (last) { result = kConverged; break; }
   }
 
-  if (result == kEliminate) {
-    __syncthreads();                             // LDS changes hands
-    GjArgs a;
-    a.K = K; a.nz = 0; a.T = T; a.partial = nullptr; a.out = Tinv;
-    a.status = status; a.status_stride = 1; a.status_offset = 0;
-    gj_panel_body<K, 4, 4 * TPW, double, true>(a, b, *reinterpret_cast<GjShared<K, double>*>(ns_lds));
-    return;
-  }
-  if (result == kConverged) {
+  // the step with the exact residual; false: X is not the inverse it was taken for
+  auto refine = [&]() __attribute__((always_inline)) {
     float xm = 0.f;
 #pragma unroll
     for (int t = 0; t < TPW; ++t)
@@ -283,6 +282,16 @@ __global__ __launch_bounds__(NsShape<K>::NW * 64) void ns_inverse_kernel(const f
     if (lane == 0) red[wave] = xm;
     stage_t();
     __syncthreads();
+    xm = red[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) xm = fmaxf(xm, red[w]);
+    int exx = 0;
+    (void)frexpf(xm, &exx);
+    // T X is 2^sh times the sum of the digits' products (x itself carries sX = 2^(7 + ex)); what lies below the digits is
+    // 2^(sh - 31) or so of it
+    const int sh = exx - 7;
+    if (sh > NsShape<K>::kMaxShift) return false;
+    const float sd = ldexpf(1.f, -exx);
     intx4 td[4][K / 32];
 #pragma unroll
     for (int s = 0; s < K / 32; ++s)
@@ -295,13 +304,6 @@ __global__ __launch_bounds__(NsShape<K>::NW * 64) void ns_inverse_kernel(const f
 #pragma unroll
         for (int p = 0; p < 4; ++p) td[p][s][g] = int(d[p]);
       }
-    xm = red[0];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) xm = fmaxf(xm, red[w]);
-    int exx = 0;
-    (void)frexpf(xm, &exx);
-    exx = exx > 6 ? exx : 6;                   // 2^(exx - 20): what |R| has to stay below (see g)
-    const float sd = ldexpf(1.f, -exx);
     unsigned char* dig = ns_lds;               // [digit][j][LDG]: X^T
     __syncthreads();                           // every wave has its rows of T
 #pragma unroll
@@ -316,9 +318,12 @@ __global__ __launch_bounds__(NsShape<K>::NW * 64) void ns_inverse_kernel(const f
           *reinterpret_cast<uint32_t*>(dig + (p * K + j0 + 32 * t) * S::LDG + i0 + 8 * g) = d[p];
       }
     __syncthreads();
-    // one sum per weight 2^-12, 2^-20, .. 2^-44 (neighbouring matrix instructions then do not depend on each other),
-    // folded largest first: tot = 256 tot + the next weight's sum, modulo 2^32
-    intx16 tot[TPW];
+    // one sum per weight 2^-12, 2^-20, .. 2^-44 (neighbouring matrix instructions then do not depend on each other), each
+    // below 2^23 (the first digits are at most 64), taken from the identity largest first: what is left after each is small
+    // enough to be exact in float32
+    uint2 rp[TPW][4];                          // 2^20 R
+    const float rs = ldexpf(1.f, 20 + sh), back = 0x1p-20f;
+    float f2 = 0.f;
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
       intx16 part[5];
@@ -338,26 +343,33 @@ __global__ __launch_bounds__(NsShape<K>::NW * 64) void ns_inverse_kernel(const f
           for (int q = 0; q < 4; ++q)
             if (p + q < 5) part[p + q] = __builtin_amdgcn_mfma_i32_32x32x32_i8(td[p][s], xd[q], part[p + q], 0, 0, 0);
       }
-      tot[t] = part[0];
+      const float one = j0 + 32 * t - ln == i0 - 4 * h ? ldexpf(1.f, -sh) : 0.f;
 #pragma unroll
-      for (int w = 1; w < 5; ++w)
+      for (int g = 0; g < 4; ++g) {
+        float u[4];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) tot[t][v] = int((uint32_t(tot[t][v]) << 8) + uint32_t(part[w][v]));
+        for (int e = 0; e < 4; ++e) {
+          const int v = 4 * g + e;
+          u[e] = fmaf(float(part[0][v]), -0x1p-12f, 8 * g + e + 4 * h == ln ? one : 0.f);
+          u[e] = fmaf(float(part[1][v]), -0x1p-20f, u[e]);
+          u[e] = fmaf(float(part[2][v]), -0x1p-28f, u[e]);
+          u[e] = fmaf(float(part[3][v] * 256 + part[4][v]), -0x1p-44f, u[e]) * rs;
+          f2 = fmaf(u[e], u[e], f2);
+        }
+        rp[t][g] = make_uint2(pack_f16(u[0], u[1]), pack_f16(u[2], u[3]));
+      }
     }
+    f2 = wave_sum(f2);
+    if (lane == 0) red[NW + wave] = f2;
     __syncthreads();                           // every wave is done with the digits
-    // T X is 2^g times the digits' sum (x itself carries sX = 2^(7 + ex)): the identity is 2^(44 - g), zero modulo
-    // 2^32 for every x that float16 holds (g <= 9), and R = -2^(g - 44) tot for |R| < 2^(g - 13); handed on as 2^20 R
-    const int g = exx - 7;
-    const float rs = -ldexpf(1.f, g - 24), back = 0x1p-20f;
+    f2 = red[NW];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) f2 += red[NW + w];
+    if (!(f2 * 0x1p-40f <= 4e-10f)) return false;
 #pragma unroll
     for (int t = 0; t < TPW; ++t)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        uint2 pk;
-        pk.x = pack_f16(float(tot[t][4 * q]) * rs, float(tot[t][4 * q + 1]) * rs);
-        pk.y = pack_f16(float(tot[t][4 * q + 2]) * rs, float(tot[t][4 * q + 3]) * rs);
-        *reinterpret_cast<uint2*>(rt + (j0 + 32 * t) * LDH + i0 + 8 * q) = pk;
-      }
+      for (int g = 0; g < 4; ++g) *reinterpret_cast<uint2*>(rt + (j0 + 32 * t) * LDH + i0 + 8 * g) = rp[t][g];
     __syncthreads();
     floatx16 acc[TPW];
 #pragma unroll
@@ -378,11 +390,24 @@ __global__ __launch_bounds__(NsShape<K>::NW * 64) void ns_inverse_kernel(const f
     for (int t = 0; t < TPW; ++t)
 #pragma unroll
       for (int v = 0; v < 16; ++v) x[t][v] = fmaf(acc[t][v], back, x[t][v]);
+    return true;
+  };
+  if (result == kConverged && !refine()) result = kEliminate;
+  if (result == kEliminate) {
+    __syncthreads();                             // LDS changes hands
+    GjArgs a;
+    a.K = K; a.nz = 0; a.T = T; a.partial = nullptr; a.out = Tinv;
+    a.status = status; a.status_stride = 1; a.status_offset = 0;
+    gj_panel_body<K, 4, 4 * TPW, double, true>(a, b, *reinterpret_cast<GjShared<K, double>*>(ns_lds));
+    return;
   }
+  // (an offset of its own: with the one of the warm start's loads their addresses stayed in registers all the way)
+  int at = i0 * K + j0;
+  asm volatile("" : "+v"(at));
 #pragma unroll
   for (int t = 0; t < TPW; ++t)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) Ob[(i0 + 8 * (v / 4) + (v % 4)) * K + j0 + 32 * t] = x[t][v] * inv_sX;
+    for (int v = 0; v < 16; ++v) Ob[at + (8 * (v / 4) + (v % 4)) * K + 32 * t] = x[t][v] * inv_sX;
   if (status && tid == 0) status[b] = 0;
 }
 

@@ -67,3 +67,19 @@ def test_the_loops_inverse_carries_its_rounding_alone(warm, k, cond, step):
     # rounding to float32 is at most 2^-24 of every entry (and half of that in the root mean square)
     err = np.linalg.norm(got - ref, axis=(1, 2)) / np.linalg.norm(ref, axis=(1, 2))
     assert err.max() <= 2.0 ** -24, err.max()
+
+
+def test_ill_conditioned_blocks_of_32_are_left_to_the_elimination(warm):
+    """Condition 300 and 1000: the digits of the exact residual no longer reach float32 rounding."""
+    rng = np.random.default_rng(5)
+    for cond in (300, 1000):
+        T0 = _conditioned(32, 9, cond, rng).astype(np.float32)
+        T = (T0 + 1e-4 / cond * rng.choice([-1.0, 1.0], T0.shape)).astype(np.float32)
+        got, status = warm(T, np.linalg.inv(T0.astype(np.float64)).astype(np.float32))
+        assert not status.any()
+        ref = np.linalg.inv(T.astype(np.float64))
+        err = np.linalg.norm(got - ref, axis=(1, 2)) / np.linalg.norm(ref, axis=(1, 2))
+        # rounding alone: uniform up to 2^-24 of the leading power of two, 2^-24 / sqrt(3) in the root mean square, of entries
+        # of 1.47 leading powers of two (mantissas uniform in their logarithm): 2.35e-8, and a fifth for the spread over the
+        # few large entries of a block
+        assert err.max() <= 2.8e-8, (cond, err)
