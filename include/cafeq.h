@@ -134,9 +134,9 @@ size_t cafeq_workspace_bytes(int call_id, const cafeq_mat* a, const cafeq_mat* b
  * 128) are inverted by Newton's iteration X <- X + X (I - T X) from T^T ||T||_F^-2 k, used only where it measures
  * ||I - T X||_F <= 2e-5 before its last step, whose residual is exact; every other block by Gauss-Jordan
  * elimination with partial pivoting, float64 internally.  A block of 64 or 128 verified to be a rotation to float32
- * accuracy -- max |I - T T^T| <= 2e-6 -- is inverted by transposition.  Blocks of 256 are eliminated in float32 with one
- * Newton step on float64 residuals, and those near a scaled rotation are first tried with Newton-Schulz rounds from
- * T^T ||T||_F^-2 k, kept only where ||I - T X||_F <= 3e-4 afterwards.  rho_row[nb*k] / rho_col[nb*k] (either may be NULL):
+ * accuracy -- max |I - T T^T| <= 2e-6 -- is inverted by transposition.  Blocks of 256 are eliminated in float32, those near
+ * a scaled rotation first tried with Newton-Schulz rounds from T^T ||T||_F^-2 k, kept only where ||I - T X||_F <= 1.5e-2
+ * before the last; a Newton step on the float64 residual of either follows, and a second one where that is above 3e-4.  rho_row[nb*k] / rho_col[nb*k] (either may be NULL):
  * squared row / column norms of Tinv.  status[nb] (may be NULL): 0 ok, 1 singular to
  * working precision (Tinv, rho_row and rho_col of that block are then zero).
  * k as in cafeq_xform (else CAFEQ_ERR_UNSUPPORTED). */

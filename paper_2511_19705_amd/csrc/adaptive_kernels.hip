@@ -727,17 +727,32 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 // What becomes of the product: kF64Plain C = alpha A B + beta C; kF64Residual C = I - A B; kF64Step F = A + A B and
 // kF64Solve F = I - (C + A B), rounded to float32 once (launches of their own for the identity, the sum and the difference
 // took 5 us each).
-enum { kF64Plain, kF64Residual, kF64Step, kF64Solve };
+// norms [block][tile] of the residual and the step: the tiles' shares of ||I - A B||_F^2.  kF64Residual writes them (null:
+// it does not); kF64Step writes F2 as well as F where their sum is above kStepTwice2 (F2 null: never).  The Again variants,
+// the second step of such blocks, leave every other block alone.
+enum { kF64Plain, kF64Residual, kF64Step, kF64Solve, kF64ResidualAgain, kF64StepAgain };
+constexpr float kStepTwice2 = 9e-8f;       // ||I - T X||_F <= 3e-4: its square is float32 rounding
+constexpr int kF64Tiles256 = (256 / 32) * (256 / 64);
 template <typename AT, typename BT, int EPI = kF64Plain>
 __global__ __launch_bounds__(256) void bgemm_f64mfma_kernel(const AT* __restrict__ A, const BT* __restrict__ B,
                                                              double* __restrict__ C, int K, double alpha, double beta,
-                                                             float* __restrict__ F) {
+                                                             float* __restrict__ F, float* __restrict__ norms = nullptr,
+                                                             float* __restrict__ F2 = nullptr) {
+  constexpr bool RES = EPI == kF64Residual || EPI == kF64ResidualAgain, STEP = EPI == kF64Step || EPI == kF64StepAgain;
   constexpr int LC = 64;
   __shared__ double sa[32][LC + 2];   // [i][l]   (row strides chosen so that the operand reads of 32 lanes cover
   __shared__ double sb[LC][80];       // [l][j]    all banks once)
   const int tpc = K / 64, tpr = K / 32;
   const int b = blockIdx.x / (tpr * tpc), tile = blockIdx.x % (tpr * tpc);
   const int i0 = (tile / tpc) * 32, j0 = (tile % tpc) * 64;
+  bool twice = false;
+  if constexpr (STEP || EPI == kF64ResidualAgain) {
+    float t = 0.f;
+#pragma unroll
+    for (int q = 0; q < kF64Tiles256; ++q) t += norms[size_t(b) * kF64Tiles256 + q];
+    twice = !(t <= kStepTwice2);               // uniform over the block
+    if (EPI != kF64Step && !twice) return;
+  }
   const AT* Ab = A + size_t(b) * K * K;
   const BT* Bb = B + size_t(b) * K * K;
   double* Cb = C + size_t(b) * K * K;
@@ -786,6 +801,7 @@ __global__ __launch_bounds__(256) void bgemm_f64mfma_kernel(const AT* __restrict
     }
     __syncthreads();
   }
+  float f2 = 0.f;
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -793,14 +809,27 @@ __global__ __launch_bounds__(256) void bgemm_f64mfma_kernel(const AT* __restrict
       const int i = i0 + 16 * ti + lk + 4 * r, j = j0 + 16 * (tj0 + t) + li, at = i * K + j;
       if constexpr (EPI == kF64Plain) {
         Cb[at] = alpha * acc[t][r] + (beta != 0.0 ? beta * Cb[at] : 0.0);
-      } else if constexpr (EPI == kF64Residual) {
-        Cb[at] = (i == j ? 1.0 : 0.0) - acc[t][r];
-      } else if constexpr (EPI == kF64Step) {
-        F[size_t(b) * K * K + at] = float(double(Ab[at]) + acc[t][r]);
+      } else if constexpr (RES) {
+        const double u = (i == j ? 1.0 : 0.0) - acc[t][r];
+        Cb[at] = u;
+        f2 = fmaf(float(u), float(u), f2);
+      } else if constexpr (STEP) {
+        const float u = float(double(Ab[at]) + acc[t][r]);
+        F[size_t(b) * K * K + at] = u;
+        if (EPI == kF64Step && twice && F2) F2[size_t(b) * K * K + at] = u;
       } else {
         F[size_t(b) * K * K + at] = float((i == j ? 1.0 : 0.0) - (acc[t][r] + Cb[at]));
       }
     }
+  if constexpr (EPI == kF64Residual) {
+    if (norms) {                               // (the LDS is free: a barrier ends the last chunk)
+      float* red = reinterpret_cast<float*>(&sa[0][0]);
+      f2 = wave_sum(f2);
+      if (lane == 0) red[w] = f2;
+      __syncthreads();
+      if (tid == 0) norms[size_t(b) * kF64Tiles256 + tile] = (red[0] + red[1]) + (red[2] + red[3]);
+    }
+  }
 }
 
 // S64, R64 and a second copy of R64 (the residual's starting value) from the chunk partials; optionally S64
@@ -874,7 +903,7 @@ __global__ __launch_bounds__(1024) void ns_init_kernel(const float* __restrict__
 //   cur[b][256 / SL]: the slices' shares of ||R||_F^2.  prev: those of the round before (null: none).  A block whose last
 //   measured residual was below 1e-3 (its correction left less than 1e-6 and the parts' 3e-5) or is beyond any contraction
 //   to count on (||R||_F >= 3, a NaN) is copied, with its residual.  An entry that leaves float16's range makes R infinite.
-constexpr float kNsAccept2 = 2.25e-4f;   // ||R||_F^2 before the last correction: 1.5e-2 leaves 2.3e-4 and the parts' 3e-5
+constexpr float kNsAccept2 = 2.25e-4f;   // ||R||_F^2 before the last correction: 1.5e-2 leaves 2.3e-4 and what the parts lose
 template <int SL>
 struct NsRound {
   static constexpr int NC = SL / 16, NSL = 256 / SL, LD = 256 + 8;      // column tiles; slices per block; row of the LDS copies
@@ -1219,14 +1248,19 @@ int launch_gj_solve(int K, int nb, int nz, const float* partial, double* work, f
 }
 
 // Blocks of 256.  Newton rounds (ns256_round_kernel) from X0 = T^T / alpha (cold: up to five) or from the inverse already
-// in Tinv (warm: inside a learning loop, two), accepted per block when the residual measured before the last correction
-// is at most 1.5e-2: a round squares it, so what enters the last step is below 3e-4 -- an a-posteriori bound, so a start
-// that was not good enough only costs the rounds; a block that meets it early is copied through the rest.  Every other
-// block is eliminated in float32 (one compute unit each, 283 us).  Either way one Newton step with float64 residuals
-// follows and brings the result to float32 rounding accuracy (it squares the residual).
+// in Tinv (warm: inside a learning loop, two), used per block when the residual measured before the last correction is at
+// most 1.5e-2: a round squares it and adds what its 16-bit operands lose, 2^-12 of it times ||T|| ||X||, which shows in the
+// residual before (its own parts lose 2^-23 of ||T|| ||X||) long before it could undo the contraction; a block that meets
+// the bound early is copied through the rest.  Every other block is eliminated in float32 (one compute unit each, 283 us).
+// Either way the float64 residual of the X at hand follows and a Newton step with it, which squares it; where that residual
+// is above 3e-4 (conditions from several hundred on, whichever way X came about), a second one.  With one step alone
+// eliminated blocks of condition 1e3 were 1.1e-6 off, of 1e4 1.2e-4; now 2.6e-8.  Blocks that need no second step pay
+// two launches that return at once.
 // Five rounds: they reach blocks with ||I - T X0||_2 up to about 0.7 (three left 0.05-perturbed rotations next to the
 // elimination, whose 283 us one block of a call is enough to pay).
-// work: 2 nb K K doubles: the float64 residual (before it the rounds' residual norms), then two float32 matrices.
+// work: 2 nb K K doubles: the float64 residual (before it the rounds' residual norms), then two float32 matrices; and
+// nb kF64Tiles256 floats, the float64 residual's norms.
+size_t inverse256_workspace_bytes(int nb) { return size_t(nb) * (size_t(2) * 256 * 256 * sizeof(double) + kF64Tiles256 * sizeof(float)); }
 int launch_inverse256(const float* T, int nb, double* work, float* Tinv, float* rho_row, float* rho_col, int* status,
                       bool warm, hipStream_t st) {
   constexpr int K = 256, kCold = 5, kWarm = 2;
@@ -1263,12 +1297,18 @@ int launch_inverse256(const float* T, int nb, double* work, float* Tinv, float* 
   a.status = status; a.status_stride = 1; a.status_offset = 0;
   a.resid = norms + size_t(rounds - 1) * nb * nsl; a.nresid = nsl; a.resid_max = kNsAccept2;
   if ((rc = launch_gj(a, nb, st))) return rc;
-  // one Newton step X <- X + X (I - T X) with float64 residuals
+  // Newton steps X <- X + X (I - T X) with float64 residuals
   const unsigned grid = unsigned(nb) * (K / 32) * (K / 64);
+  float* rnorm = reinterpret_cast<float*>(work + 2 * mat);
+  float* X1 = X == buf[0] ? buf[1] : buf[0];
   hipLaunchKernelGGL((bgemm_f64mfma_kernel<float, float, kF64Residual>), dim3(grid), dim3(256), 0, st, T, X, res, K, 1.0, 0.0,
-                     static_cast<float*>(nullptr));
+                     static_cast<float*>(nullptr), rnorm);
   hipLaunchKernelGGL((bgemm_f64mfma_kernel<float, double, kF64Step>), dim3(grid), dim3(256), 0, st, X, res,
-                     static_cast<double*>(nullptr), K, 1.0, 0.0, Tinv);
+                     static_cast<double*>(nullptr), K, 1.0, 0.0, Tinv, rnorm, X1);
+  hipLaunchKernelGGL((bgemm_f64mfma_kernel<float, float, kF64ResidualAgain>), dim3(grid), dim3(256), 0, st, T, X1, res, K, 1.0,
+                     0.0, static_cast<float*>(nullptr), rnorm);
+  hipLaunchKernelGGL((bgemm_f64mfma_kernel<float, double, kF64StepAgain>), dim3(grid), dim3(256), 0, st, X1, res,
+                     static_cast<double*>(nullptr), K, 1.0, 0.0, Tinv, rnorm);
   CAFEQ_CHECK_LAUNCH();
   RhoRequest rho[2];
   int nrho = 0;

@@ -763,6 +763,7 @@ size_t cafeq_workspace_bytes(int call_id, const cafeq_mat* a, const cafeq_mat* b
       return align_up(size_t(x->nb) * kFwdPlanes * x->k * x->k * sizeof(uint16_t), 256);
     case CAFEQ_CALL_BLOCK_INVERSE:
       if (!x) return 0;
+      if (x->k == 256) return align_up(inverse256_workspace_bytes(x->nb), 256);
       return align_up(size_t(x->nb) * x->k * 2 * x->k * sizeof(double), 256);
     case CAFEQ_CALL_PROXY_LOSS: {
       if (!a || !x || !cfg) return 0;

@@ -126,6 +126,7 @@ int launch_gram_pair(int axis, const float* X, const int8_t* codes, const float*
                      hipStream_t st);
 int launch_gj_solve(int K, int nb, int nz, const float* partial, double* work, float* Sinv, float* R,
                     float* out, int* status, int status_stride, int status_offset, hipStream_t st);
+size_t inverse256_workspace_bytes(int nb);
 int launch_inverse256(const float* T, int nb, double* work, float* Tinv, float* rho_row, float* rho_col, int* status,
                       bool warm, hipStream_t st);
 // inverse_kernels.hip

@@ -21,7 +21,7 @@ def warm():
         nb, k, _ = T.shape
         Td, X = torch.from_numpy(T).to("cuda:0"), torch.from_numpy(X0).to("cuda:0")
         status = torch.full((nb,), 7, dtype=torch.int32, device="cuda:0")
-        work = torch.zeros(2 * nb * k * k, dtype=torch.float64, device="cuda:0")     # as cafeq_workspace_bytes has it
+        work = torch.zeros(cafeq.workspace_bytes(4, cafeq.Mat(), x=cafeq.Xform(0, 0, k, nb, 1)), dtype=torch.uint8, device="cuda:0")
         rc = fn(Td.data_ptr(), k, nb, work.data_ptr(), X.data_ptr(), status.data_ptr(), torch.cuda.current_stream().cuda_stream)
         torch.cuda.synchronize()
         assert rc == 0
@@ -83,3 +83,37 @@ def test_ill_conditioned_blocks_of_32_are_left_to_the_elimination(warm):
         # of 1.47 leading powers of two (mantissas uniform in their logarithm): 2.35e-8, and a fifth for the spread over the
         # few large entries of a block
         assert err.max() <= 2.8e-8, (cond, err)
+
+
+@pytest.mark.parametrize("k", [32, 64, 128, 256])
+@pytest.mark.parametrize("small", [1.0, 0.1, 0.01, 1e-3, 1e-4])
+def test_starts_on_either_side_of_every_bound(warm, k, small):
+    """Rotated blocks [[1, 0.7], [0, small]], starts X0 = T^-1 (I - E) with ||E||_F from 0 to 2: residuals on either side of
+    the bounds, whose corrections take 16-bit operands of an X that amplifies what they lose by up to 0.7 / small."""
+    rng = np.random.default_rng(k)
+    size = np.concatenate([[0.0], np.geomspace(1e-3, 2.0, 14), np.geomspace(0.05, 0.6, 9)])
+    T = np.linalg.qr(rng.standard_normal((len(size), k, k)))[0] @ np.kron(np.eye(k // 2), [[1.0, 0.7], [0.0, small]])
+    T = T.astype(np.float32)
+    ref = np.linalg.inv(T.astype(np.float64))
+    E = rng.standard_normal(T.shape)
+    E *= (size / np.linalg.norm(E, axis=(1, 2)))[:, None, None]
+    got, status = warm(T, (ref @ (np.eye(k) - E)).astype(np.float32))
+    assert not status.any()
+    err = np.linalg.norm(got - ref, axis=(1, 2)) / np.linalg.norm(ref, axis=(1, 2))
+    # rounding to float32; k = 256: and the square of a residual ||I - T X||_F of up to 3e-4
+    assert err.max() <= 2.0 ** -24 + (9e-8 if k == 256 else 0.0), list(zip(size.round(4), err))
+
+
+@pytest.mark.parametrize("small", [1e-2, 1e-3, 1e-4])
+def test_eliminated_blocks_of_256_carry_their_rounding_alone(small):
+    """The same blocks through cafeq_block_inverse: no rotation is near, all are eliminated, in float32."""
+    import torch
+    from paper_2511_19705_amd import cafeq
+    k, rng = 256, np.random.default_rng(9)
+    T = np.linalg.qr(rng.standard_normal((3, k, k)))[0] @ np.kron(np.eye(k // 2), [[1.0, 0.7], [0.0, small]])
+    T = T.astype(np.float32)
+    X, status = cafeq.block_inverse(torch.from_numpy(T).to("cuda:0"))
+    assert not status.any()
+    ref = np.linalg.inv(T.astype(np.float64))
+    err = np.linalg.norm(X.cpu().numpy() - ref, axis=(1, 2)) / np.linalg.norm(ref, axis=(1, 2))
+    assert err.max() <= 2.0 ** -24 + 9e-8, err
