@@ -70,7 +70,8 @@ typedef enum { CAFEQ_Q_SYM_ABSMAX = 0, CAFEQ_Q_ASYM_MINMAX = 1 } cafeq_qmode;
 /* Row-major matrix view. data: device pointer, 16-byte aligned; ld in elements, a
  * multiple of 4 (float32) or 8 (bfloat16); dtype: cafeq_dtype.
  * prepared: NULL, or a device buffer written by cafeq_prepare_weights() for this matrix (same data,
- * shape and the axis the call transforms).  The weights are constant over the thousands of loss
+ * storage type, shape and the axis the call transforms; its layout and size follow from them, and nothing in
+ * the descriptor tells a call that they differ).  The weights are constant over the thousands of loss
  * evaluations of a learning run (paper Sec. 4.1, Sec. 4.2); with a prepared copy the loss pass of
  * cafeq_proxy_loss_fwd_bwd / cafeq_dual_proxy_loss_fwd_bwd / cafeq_optimize_* reads them in the form
  * the matrix cores consume (where a kernel for it exists: blocks of 128, groups up to 128, up to

@@ -131,9 +131,26 @@ def _ptr(t):
     return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
 
 
-def mat(t, prepared=None):
+def _prepared_ptr(m, prepared, axis):
+    """Address of a prepared copy of m, transformed along `axis` (None: whichever it was made for), for its descriptor.
+    A copy made from the same values in the other storage type has another layout and is not read: the call runs on the
+    weights themselves.  A buffer too small for either is refused: the kernels would read past its end."""
+    have = prepared.numel() * prepared.element_size()
+    other = Mat(m.data, m.rows, m.cols, m.ld, BF16 if m.dtype == F32 else F32, 0)
+    axes = (AXIS_COL, AXIS_ROW) if axis is None else (axis,)
+    need = [int(lib.cafeq_prepared_bytes(ctypes.byref(m), a)) for a in axes]
+    if have in need:
+        return prepared.data_ptr()
+    if have in [int(lib.cafeq_prepared_bytes(ctypes.byref(other), a)) for a in axes]:
+        return 0
+    if have < max(need):
+        raise CafeqError("the prepared copy holds %d bytes, that of this matrix %d: made for another one?" % (have, max(need)))
+    return prepared.data_ptr()
+
+
+def mat(t, prepared=None, axis=None):
     """Descriptor of a 2-D CUDA tensor (float32 or bfloat16, unit column stride); `prepared`: the buffer
-    prepare_weights() returned for it, or None."""
+    prepare_weights() returned for it and the axis the call transforms, or None."""
     if t.dim() != 2 or t.stride(1) != 1 or not t.is_cuda:
         raise CafeqError("need a 2-D CUDA tensor with unit column stride")
     if t.dtype == torch.float32:
@@ -142,7 +159,10 @@ def mat(t, prepared=None):
         dt = BF16
     else:
         raise CafeqError("dtype must be float32 or bfloat16")
-    return Mat(t.data_ptr(), t.shape[0], t.shape[1], t.stride(0), dt, prepared.data_ptr() if prepared is not None else 0)
+    m = Mat(t.data_ptr(), t.shape[0], t.shape[1], t.stride(0), dt, 0)
+    if prepared is not None:
+        m.prepared = _prepared_ptr(m, prepared, axis)
+    return m
 
 
 def xform(T, Tinv, rep=1):
@@ -242,7 +262,7 @@ def proxy_loss_fwd_bwd(W, T, Tinv, bits, group, axis=AXIS_COL, rep=1, want_grad=
                        prepared=None, mode=Q_SYM):
     """Returns (losses[4], gradT or None, codes or None, scales or None).  With mode=Q_MINMAX the codes are
     unsigned bytes and `scales` is [2][...]: the scales, then the group minima."""
-    m = mat(W, prepared)
+    m = mat(W, prepared, axis)
     x = xform(T, Tinv, rep)
     cfg = QuantCfg(bits, group, axis, mode)
     dev = W.device
@@ -267,7 +287,7 @@ def dual_proxy_loss_fwd_bwd(A, B, T, Tinv, bits, group, rep=1, lse_t=5.0, want_g
                             prepared=(None, None), mode=Q_SYM):
     """Returns (losses[6], gradT or None, (codesU, scalesU, codesV, scalesV) or None); mode as in
     proxy_loss_fwd_bwd."""
-    ma, mb = mat(A, prepared[0]), mat(B, prepared[1])
+    ma, mb = mat(A, prepared[0], AXIS_COL), mat(B, prepared[1], AXIS_ROW)
     x = xform(T, Tinv, rep)
     cfg = QuantCfg(bits, group, 0, mode)
     dev = A.device
@@ -391,7 +411,7 @@ def optimize_single(W, T, bits, group, axis=AXIS_COL, rep=1, lr=1.0, steps=10, l
 def optimize_pair(A, B, T, bits, group, rep=1, lse_t=5.0, lr=1e-2, steps=10, lambda_orth=0.0, beta1=0.1,
                   beta2=0.999, eps=1e-8, prepared=(None, None), mode=Q_SYM):
     """Adam on the LogSumExp surrogate, T updated in place.  Returns (Tinv, history[steps][8], status)."""
-    ma, mb = mat(A, prepared[0]), mat(B, prepared[1])
+    ma, mb = mat(A, prepared[0], AXIS_COL), mat(B, prepared[1], AXIS_ROW)
     nb, k, _ = T.shape
     Tinv = torch.empty_like(T)
     x = Xform(_ptr(T), _ptr(Tinv), k, nb, rep)

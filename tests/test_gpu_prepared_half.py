@@ -66,3 +66,35 @@ def test_pair_and_mixed_storage(env, nb, d_model):
         scale = float(got[0][1].abs().max())
         assert float((other[1] - got[0][1]).abs().max()) <= 1e-5 * scale
     assert cafeq.prepare_weights(A, 0).numel() < 0.55 * cafeq.prepare_weights(A.float(), 0).numel()
+
+
+@pytest.mark.parametrize("axis", [0, 1])
+def test_a_copy_of_the_other_storage_type_is_not_read(env, axis):
+    """Its layout and size differ: the result is that over the weights themselves."""
+    torch, cafeq = env
+    W = _weights(torch, (264, 3 * K) if axis == 0 else (3 * K, 264), 71)
+    T, P = _blocks(torch, cafeq, 3, 72)
+    for X, other in ((W, W.float()), (W.float(), W)):
+        got = cafeq.proxy_loss_fwd_bwd(X, T, P, 4, 128, axis, prepared=cafeq.prepare_weights(other, axis))
+        ref = cafeq.proxy_loss_fwd_bwd(X, T, P, 4, 128, axis)
+        assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+
+
+def test_a_copy_of_a_smaller_matrix_is_refused(env):
+    torch, cafeq = env
+    W, small = _weights(torch, (600, 3 * K), 73).float(), _weights(torch, (300, 3 * K), 74).float()
+    T, P = _blocks(torch, cafeq, 3, 75)
+    prep = cafeq.prepare_weights(small, 0)
+    with pytest.raises(cafeq.CafeqError):
+        cafeq.proxy_loss_fwd_bwd(W, T, P, 4, 128, 0, prepared=prep)
+    B = _weights(torch, (3 * K, 600), 76).float()
+    for bad in ((prep, None), (None, cafeq.prepare_weights(B[:, :256].contiguous(), 1))):
+        with pytest.raises(cafeq.CafeqError):
+            cafeq.dual_proxy_loss_fwd_bwd(W, B, T, P, 4, 128, prepared=bad)
+        with pytest.raises(cafeq.CafeqError):
+            cafeq.optimize_pair(W, B, T.clone(), 4, 128, prepared=bad, steps=1)
+    # a pooled buffer may be larger than the copy in it
+    room = torch.zeros(cafeq.prepare_weights(W, 0).numel() + 4096, dtype=torch.uint8, device="cuda:0")
+    room[:-4096] = cafeq.prepare_weights(W, 0)
+    got, ref = (cafeq.proxy_loss_fwd_bwd(W, T, P, 4, 128, 0, prepared=p) for p in (room, cafeq.prepare_weights(W, 0)))
+    assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
