@@ -1123,9 +1123,8 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
   const bool asym = is_minmax(cfg);
   const bool v2A = v2_eligible(A, K, ga, cfg), v2B = v2_eligible(B, K, gb, cfg);
   // both loss passes over prepared weights in one launch, each member on half of the chip: when neither writes
-  // codes or scales and both use the same group length and storage type
-  const bool pair_launch = v2A && v2B && !codesU && !scalesU && !codesV && !scalesV && ga.Gk == gb.Gk &&
-                           A->dtype == B->dtype;
+  // codes or scales and both use the same group length
+  const bool pair_launch = v2A && v2B && !codesU && !scalesU && !codesV && !scalesV && ga.Gk == gb.Gk;
   PassPlans qa, qb;
   if ((rc = plan_passes(K, ga, A->rows, A->cols, grad, &qa, v2A, asym, pair_launch ? 2 : 1))) return rc;
   if ((rc = plan_passes(K, gb, B->cols, B->rows, grad, &qb, v2B, asym, pair_launch ? 2 : 1))) return rc;

@@ -504,10 +504,11 @@ __global__ __launch_bounds__(kV2Threads, 1) void loss_v2_kernel(const CoreParams
 // Both members of a pair in one launch (no codes or scales requested): the first pa.nwg workgroups take member
 // A, the others member B.  With one workgroup per compute unit in total, half of the chip streams each member
 // and the ranges of the two members end together -- one kernel tail instead of two.
-template <int G, bool REC, int WP>
+// WPA, WPB: parts of the members' weights.
+template <int G, bool REC, int WPA, int WPB>
 __global__ __launch_bounds__(kV2Threads, 1) void loss_v2_pair_kernel(const CoreParams pa, const CoreParams pb) {
-  if (blockIdx.x < unsigned(pa.nwg)) loss_v2_body<G, CAFEQ_AXIS_COL, REC, false, WP>(pa, blockIdx.x);
-  else loss_v2_body<G, CAFEQ_AXIS_ROW, REC, false, WP>(pb, blockIdx.x - unsigned(pa.nwg));
+  if (blockIdx.x < unsigned(pa.nwg)) loss_v2_body<G, CAFEQ_AXIS_COL, REC, false, WPA>(pa, blockIdx.x);
+  else loss_v2_body<G, CAFEQ_AXIS_ROW, REC, false, WPB>(pb, blockIdx.x - unsigned(pa.nwg));
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -659,9 +660,9 @@ int launch_prepare(const cafeq_mat* W, int axis, void* prepared, hipStream_t st)
 }
 
 namespace {
-template <int G, bool REC, int WP>
+template <int G, bool REC, int WPA, int WPB>
 int launch_v2_pair_w(const CoreParams& pa, const CoreParams& pb, hipStream_t st) {
-  auto kern = loss_v2_pair_kernel<G, REC, WP>;
+  auto kern = loss_v2_pair_kernel<G, REC, WPA, WPB>;
   static std::atomic<bool> attr_set{false};   // per instantiation
   if (!attr_set) {
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -675,18 +676,20 @@ int launch_v2_pair_w(const CoreParams& pa, const CoreParams& pb, hipStream_t st)
 }
 template <int G, bool REC>
 int launch_v2_pair_v(const CoreParams& pa, const CoreParams& pb, hipStream_t st) {
-  return prepared_parts(pa.dtype) == 1 ? launch_v2_pair_w<G, REC, 1>(pa, pb, st) : launch_v2_pair_w<G, REC, 2>(pa, pb, st);
+  const bool oa = prepared_parts(pa.dtype) == 1, ob = prepared_parts(pb.dtype) == 1;
+  if (oa) return ob ? launch_v2_pair_w<G, REC, 1, 1>(pa, pb, st) : launch_v2_pair_w<G, REC, 1, 2>(pa, pb, st);
+  return ob ? launch_v2_pair_w<G, REC, 2, 1>(pa, pb, st) : launch_v2_pair_w<G, REC, 2, 2>(pa, pb, st);
 }
 }  // namespace
 
-// Both members of a pair (member A on its columns, member B on its rows) in one launch; same group length, storage type
-// and choice of records for both, no codes or scales.
+// Both members of a pair (member A on its columns, member B on its rows) in one launch; same group length and
+// the same choice of records for both, no codes or scales.
 int launch_loss_v2_pair(int G, const CoreParams& pa, const CoreParams& pb, hipStream_t st) {
   for (const CoreParams* p : {&pa, &pb})
     if (!p->prep_planes || !p->prep_lscale || !p->prep_wsq || !p->fscale || !p->fscale_inv || !p->slot_hdr || p->codes ||
         p->scales)
       return CAFEQ_ERR_INVALID_ARG;
-  if ((pa.rec != nullptr) != (pb.rec != nullptr) || pa.dtype != pb.dtype) return CAFEQ_ERR_INVALID_ARG;
+  if ((pa.rec != nullptr) != (pb.rec != nullptr)) return CAFEQ_ERR_INVALID_ARG;
   const bool rec = pa.rec != nullptr;
   switch (G) {
     case 32: return rec ? launch_v2_pair_v<32, true>(pa, pb, st) : launch_v2_pair_v<32, false>(pa, pb, st);

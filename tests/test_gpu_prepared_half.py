@@ -60,7 +60,7 @@ def test_pair_and_mixed_storage(env, nb, d_model):
         got.append(cafeq.dual_proxy_loss_fwd_bwd(a, b, T, P, 4, 128, prepared=prep))
     for other in got[1:2]:
         assert torch.equal(got[0][0], other[0]) and torch.equal(got[0][1], other[1])
-    # mixed types take the members' loss passes in launches of their own: other partial sums of the losses
+    # (mixed types: test_mixed_storage_takes_one_launch)
     for other in got[2:]:
         np.testing.assert_allclose(other[0].cpu().numpy(), got[0][0].cpu().numpy(), rtol=1e-6)
         scale = float(got[0][1].abs().max())
@@ -98,3 +98,23 @@ def test_a_copy_of_a_smaller_matrix_is_refused(env):
     room[:-4096] = cafeq.prepare_weights(W, 0)
     got, ref = (cafeq.proxy_loss_fwd_bwd(W, T, P, 4, 128, 0, prepared=p) for p in (room, cafeq.prepare_weights(W, 0)))
     assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+
+
+@pytest.mark.parametrize("nb,d_model", [(5, 200), (80, 136)])
+@pytest.mark.parametrize("grad", [False, True])
+def test_mixed_storage_takes_one_launch(env, nb, d_model, grad):
+    """Both members' loss passes, whatever their storage types, and so the same partial sums: equal bit for bit."""
+    torch, cafeq = env
+    A, B = _weights(torch, (d_model, nb * K), 51 + nb), _weights(torch, (nb * K, d_model), 52 + nb)
+    T, P = _blocks(torch, cafeq, nb, 53 + nb)
+    ref = None
+    for a, b in ((A, B), (A, B.float()), (A.float(), B)):
+        prep = (cafeq.prepare_weights(a, 0), cafeq.prepare_weights(b, 1))
+        timer = cafeq.LaunchTimer(4)
+        with timer:
+            losses, g, _ = cafeq.dual_proxy_loss_fwd_bwd(a, b, T, P, 4, 128, want_grad=grad, prepared=prep)
+            torch.cuda.synchronize()
+        assert timer.table.seen == 1
+        ref = ref or (losses, g)
+        assert torch.equal(losses, ref[0])
+        _same(torch, g, ref[1])
