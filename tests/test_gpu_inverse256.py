@@ -73,3 +73,42 @@ def test_blocks_without_an_inverse_leave_the_others_alone(env, bad):
         assert st[1] == 1 and float(Tinv[1].abs().max()) == 0.0
     for b in (0, 2):
         np.testing.assert_allclose(Tinv[b].cpu().numpy(), ref[b], rtol=0, atol=2.0 ** -22 * np.abs(ref[b]).max())
+
+
+@pytest.mark.parametrize("lr", [1e-4, 3e-3, 3e-2])
+def test_the_loops_losses_follow_inverses_from_scratch(env, lr):
+    """The inverse that the loop works with, not the one it hands back: every step's losses depend on it, and are those of
+    evaluations at inverses from scratch and the update as a call of its own."""
+    torch, cafeq = env
+    steps = 4
+    A, B, T = (torch.from_numpy(x).to("cuda:0") for x in WL.small_pair(200, 512, K, 1, 78, eps=0.0))
+    Td = T.clone()
+    _, hist, _ = cafeq.optimize_pair(A, B, Td, 4, 64, 1, 5.0, lr=lr, steps=steps)
+    m, v = torch.zeros_like(T), torch.zeros_like(T)
+    for s in range(steps):
+        P, _ = cafeq.block_inverse(T)
+        losses, grad, _ = cafeq.dual_proxy_loss_fwd_bwd(A, B, T, P, 4, 64, 1, 5.0)
+        # entries of T with gradients at the level of rounding may go another way from the first update on
+        np.testing.assert_allclose(hist[s, :5].cpu().numpy(), losses[:5].cpu().numpy(), rtol=1e-6 if s == 0 else 1e-4)
+        cafeq.adam_update(T, grad, m, v, s + 1, lr, 0.1, 0.999, 1e-8)
+    assert float(((Td - T).double() ** 2).mean().sqrt()) <= 0.01 * lr
+
+
+@pytest.mark.parametrize("lr", [1e-4, 3e-3])
+def test_the_loops_losses_follow_the_oracle(env, lr):
+    """(At 3e-2 the second step has moved T by half of itself, to condition 12: codes and arg-maxima go other ways in float64,
+    and l2B is 1.3e-3 off, by evaluations at inverses from scratch as well.)"""
+    from oracle import cafeq_oracle as O
+    from tests import parity
+    torch, cafeq = env
+    steps = 4
+    A, B, T = WL.small_pair(200, 512, K, 1, 78, eps=0.0)
+    T_ref, h_ref = O.optimize_pair(A, B, T, 4, 64, 1, 5.0, lr, steps)
+    Td = torch.from_numpy(T.copy()).to("cuda:0")
+    _, hist, _ = cafeq.optimize_pair(torch.from_numpy(A).to("cuda:0"), torch.from_numpy(B).to("cuda:0"), Td, 4, 64, 1, 5.0,
+                                     lr=lr, steps=steps)
+    hist = hist.cpu().numpy().astype(np.float64)
+    for s in range(steps):
+        for c, name in enumerate(("errU_sq", "errV_sq", "l2A_sq", "l2B_sq", "lse")):
+            parity.check_scalar(hist[s, c], h_ref[s, c], rel=5e-4, what="step %d %s" % (s, name))
+    assert np.sqrt(((Td.cpu().numpy() - T_ref) ** 2).mean()) <= 0.05 * lr
