@@ -267,9 +267,12 @@ __device__ __forceinline__ void load_strip(const CoreParams& p, float (&wreg)[L 
 // (hi.hi, hi.lo, lo.hi; relative error per term below 2^-20, the same order as the float32
 // accumulation) instead of six bfloat16 ones; the accumulators are scaled back before anything reads
 // them.  The inverse transform keeps the bfloat16 parts.  The weights' parts are truncated on the symmetric grid (the
-// common deficit cancels in z / absmax) and rounded to nearest on the min/max grid, whose codes count from a minimum:
-// there what the parts leave out (7e-8 of a term, rms) is below what float32 accumulation adds, and half the products
-// round half as often: rms error of the transform 1.44e-7, with six bfloat16 products 1.8e-7 (blocks of 128).
+// common deficit cancels in z / absmax); on the min/max grid, whose codes count from a minimum, they are rounded to nearest
+// and a third part holds the rest (exactly, down to 2^-16 of the line's largest magnitude), in a fourth product with the
+// operand's high part: a transform whose entries are float16 numbers (the identity, a signed permutation) moves the weights
+// exactly, as the six bfloat16 products do.  Elsewhere two thirds of the products round less often: group minima of
+// rotations 5 % off are 5.6e-8 of their range off float64 in the root mean square (7.1e-8 with six products; blocks of 128),
+// identities 1e-4 off 5.3e-8 (6.2e-8), 1e-2 off 7.6e-8 (6.9e-8: there the operand's own two parts show).
 // LONGG: the variant for groups that span several segments (CoreParams::gspan; one group per segment inside
 // the kernel): its record-only sweep and its loss sweep with the group's absmax taken from the combined records.
 // ASYM: the min/max grid of Eq. (1) instead of the symmetric absmax grid (gradient-free variants only: the
@@ -487,7 +490,7 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
       for (int c2 = 0; c2 < 2; ++c2) {
         const int c = 2 * sg + c2;                   // MFMA step within the segment: inputs 16c..16c+15
         if constexpr (F16) {
-          uint32_t bh[4], bl[4];
+          uint32_t bh[4], bl[4], br[4] = {0, 0, 0, 0};
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const float x0 = wreg[8 * c + 2 * i], x1 = wreg[8 * c + 2 * i + 1];
@@ -496,7 +499,10 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
             if constexpr (ASYM) {
               bh[i] = pack_f16(y0, y1);
               const halfx2 hh = __builtin_bit_cast(halfx2, bh[i]);
-              bl[i] = pack_f16(y0 - float(hh[0]), y1 - float(hh[1]));
+              const float r0 = y0 - float(hh[0]), r1 = y1 - float(hh[1]);
+              bl[i] = pack_f16(r0, r1);
+              const halfx2 hl = __builtin_bit_cast(halfx2, bl[i]);
+              br[i] = pack_f16(r0 - float(hl[0]), r1 - float(hl[1]));
             } else {
               const auto hh = __builtin_amdgcn_cvt_pkrtz(y0, y1);
               const auto hl = __builtin_amdgcn_cvt_pkrtz(y0 - float(hh[0]), y1 - float(hh[1]));
@@ -513,6 +519,11 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
             const unsigned char* ap = sbase + t * (32 * 64) + ao;
             xh[t] = as_halfx8(*reinterpret_cast<const uintx4*>(ap));
             xl[t] = as_halfx8(*reinterpret_cast<const uintx4*>(ap + PLANEB));
+          }
+          if constexpr (ASYM) {
+            const halfx8 vbr = as_halfx8(br[0], br[1], br[2], br[3]);
+#pragma unroll
+            for (int t = 0; t < KT; ++t) acc[blk * KT + t] = CAFEQ_MFMA_F16(xh[t], vbr, acc[blk * KT + t]);
           }
 #pragma unroll
           for (int t = 0; t < KT; ++t) acc[blk * KT + t] = CAFEQ_MFMA_F16(xl[t], vbh, acc[blk * KT + t]);

@@ -125,3 +125,30 @@ def test_minmax_optimize_single_first_step(env):
     parity.check_scalar(h[0, 0], ref["l2_sq"], what="l2_sq")
     parity.check_scalar(h[0, 3], O.surrogate(W, T, P, 4, 128, O.COL, mode=O.ASYM, want_grad=False)[0], what="surrogate")
     assert h[2, 3] < h[0, 3]
+
+
+@pytest.mark.parametrize("k", [32, 64, 128, 256])
+@pytest.mark.parametrize("axis", [0, 1])
+@pytest.mark.parametrize("group,bits", [(128, 4), (0, 4), (0, 2), (128, 8)])
+@pytest.mark.parametrize("transform", ["identity", "signed permutation", "powers of two"])
+def test_transforms_that_only_move_the_weights_give_the_plain_quantizers_codes(env, k, axis, group, bits, transform):
+    """Every product and sum is exact: codes, scales and minima are those of cafeq_rtn_quantize_minmax on the moved weights."""
+    torch, cafeq = env
+    if group and group < k:
+        group = k
+    nb, rng = 1024 // k, np.random.default_rng(k + bits)
+    W = _dev(torch, WL.student_t3((300, nb * k) if axis == 0 else (nb * k, 300), 1300 + k))
+    T = np.stack([np.eye(k)] * nb)
+    if transform != "identity":
+        T = np.stack([np.eye(k)[rng.permutation(k)] * rng.choice([-1.0, 1.0], (k, 1)) for _ in range(nb)])
+    if transform == "powers of two":
+        T *= 2.0 ** rng.integers(-2, 3, (nb, k, 1))
+    T = _dev(torch, T.astype(np.float32))
+    P, _ = cafeq.block_inverse(T)
+    M = torch.block_diag(*T.double())
+    Z = (W.double() @ M if axis == 0 else M @ W.double()).float()
+    c_ref, s_ref, m_ref, _ = cafeq.rtn_quantize_minmax(Z, bits, group, axis)
+    losses, _, codes, scales = cafeq.proxy_loss_fwd_bwd(W, T, P, bits, group, axis, want_grad=False, want_codes=True,
+                                                        mode=cafeq.Q_MINMAX)
+    assert torch.equal(scales[0], s_ref) and torch.equal(scales[1], m_ref)
+    assert torch.equal(codes, c_ref)
