@@ -12,8 +12,8 @@ which are constant over a learning run, are also held in the library's prepared 
 Prints ONE JSON line: weight-elements/s over the whole job; the roofline of the dominant kernel (the loss
 pass), its duration measured with HIP events recorded on the launch stream around every launch inside the
 timed region; the CPU oracle timed on the host cores on a bounded sample; and a `secondary` list with the
-same step under other conditions (a transform part-way through learning, whose inverse takes the elimination
-kernel; the unprepared path) and the other workloads (plain quantizer, single matrix, Alg. 1, the 27B-shaped
+same step under other conditions (a transform part-way through learning, whose inverse takes Newton's
+iteration; the unprepared path) and the other workloads (plain quantizer, single matrix, Alg. 1, the 27B-shaped
 layer).  `--workload NAME` prints the line of one secondary workload alone.
 """
 from __future__ import annotations
@@ -242,11 +242,11 @@ def pair_workload(args, secondary=True):
     if secondary:
         sec = []
         n2 = max(10, args.steps // 4)
-        # the same step with a transform part-way through learning: every block goes through the elimination
+        # the same step with a transform part-way through learning: every block goes through Newton's iteration
         Tm = torch.from_numpy(WL.perturbed_blocks(cfg["T"].shape[0], k, 304, 0.05)).to(dev)
         d2 = _timed(torch, make_step(Tm, prep), n2, 3)
         sec.append({"workload": "c3_pair_midlearning", "what": "same step, T = rotation x (I + 0.05 G / sqrt(k)): inverse by "
-                    "elimination", "steps": n2, "ms_per_step": d2 / n2 * 1e3, "value": elems * n2 / d2, "unit": "weight-elements/s"})
+                    "Newton's iteration", "steps": n2, "ms_per_step": d2 / n2 * 1e3, "value": elems * n2 / d2, "unit": "weight-elements/s"})
         d3 = _timed(torch, make_step(T, (None, None)), n2, 3)
         sec.append({"workload": "c3_pair_unprepared", "what": "same step without prepared weights (float32 weights split per "
                     "call)", "steps": n2, "ms_per_step": d3 / n2 * 1e3, "value": elems * n2 / d3, "unit": "weight-elements/s"})

@@ -862,39 +862,34 @@ int launch_reduce_losses(int kind, const float* hdrA, int nslotA, const float* h
   CAFEQ_CHECK_LAUNCH();
   return CAFEQ_OK;
 }
+// Transposed operands for blocks of 256 alone (the smaller blocks' chains take both products in one launch).
 int launch_bgemm(bool ta, bool tb, const float* A, const float* B, float* C, int K, int nb, float alpha,
                  float beta, hipStream_t st, const UpdateHook* hook) {
   const UpdateHook up = hook ? *hook : UpdateHook{};
+  if ((ta && tb) || ((ta || tb) && K != 256) || (hook && K == 32)) return CAFEQ_ERR_INVALID_ARG;
+  const unsigned grid = unsigned(nb) * (K / 64) * (K / 64);
   if (K == 32) {
-    if (hook || ta || tb) return CAFEQ_ERR_INVALID_ARG;
     hipLaunchKernelGGL(bgemm32_kernel, dim3(nb), dim3(256), 0, st, A, B, C, alpha, beta);
+  } else if (K == 64) {
+    hipLaunchKernelGGL((bgemm_mfma_kernel<false, false, 64>), dim3(grid), dim3(256), 2 * 64 * 65 * sizeof(float), st, A, B, C, K,
+                       alpha, beta, up);
   } else {
-    const unsigned grid = unsigned(nb) * (K / 64) * (K / 64);
-    if (K % 128 == 0) {
-      constexpr int CH = 128;
-      constexpr size_t lds = 2 * CH * 65 * sizeof(float);
-      static std::atomic<bool> attr_set{false};
-      if (!attr_set) {
-        bool ok = true;
+    constexpr int CH = 128;
+    constexpr size_t lds = 2 * CH * 65 * sizeof(float);
+    static std::atomic<bool> attr_set{false};
+    if (!attr_set) {
+      bool ok = true;
 #define CAFEQ_ATTR(TA, TB)                                                                                     \
   ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(bgemm_mfma_kernel<TA, TB, CH>),                 \
                                  hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) == hipSuccess
-        CAFEQ_ATTR(true, true); CAFEQ_ATTR(true, false); CAFEQ_ATTR(false, true); CAFEQ_ATTR(false, false);
+      CAFEQ_ATTR(true, false); CAFEQ_ATTR(false, true); CAFEQ_ATTR(false, false);
 #undef CAFEQ_ATTR
-        if (!ok) return CAFEQ_ERR_LAUNCH;
-        attr_set = true;
-      }
-#define CAFEQ_G128(TA, TB) hipLaunchKernelGGL((bgemm_mfma_kernel<TA, TB, CH>), dim3(grid), dim3(256), lds, st, A, B, C, K, alpha, beta, up)
-      if (ta && tb) CAFEQ_G128(true, true); else if (ta) CAFEQ_G128(true, false);
-      else if (tb) CAFEQ_G128(false, true); else CAFEQ_G128(false, false);
-#undef CAFEQ_G128
-    } else {
-      constexpr size_t lds = 2 * 64 * 65 * sizeof(float);
-#define CAFEQ_G64(TA, TB) hipLaunchKernelGGL((bgemm_mfma_kernel<TA, TB, 64>), dim3(grid), dim3(256), lds, st, A, B, C, K, alpha, beta, up)
-      if (ta && tb) CAFEQ_G64(true, true); else if (ta) CAFEQ_G64(true, false);
-      else if (tb) CAFEQ_G64(false, true); else CAFEQ_G64(false, false);
-#undef CAFEQ_G64
+      if (!ok) return CAFEQ_ERR_LAUNCH;
+      attr_set = true;
     }
+#define CAFEQ_G128(TA, TB) hipLaunchKernelGGL((bgemm_mfma_kernel<TA, TB, CH>), dim3(grid), dim3(256), lds, st, A, B, C, K, alpha, beta, up)
+    if (ta) CAFEQ_G128(true, false); else if (tb) CAFEQ_G128(false, true); else CAFEQ_G128(false, false);
+#undef CAFEQ_G128
   }
   CAFEQ_CHECK_LAUNCH();
   return CAFEQ_OK;
