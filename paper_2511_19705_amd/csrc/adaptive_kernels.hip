@@ -895,11 +895,11 @@ __global__ __launch_bounds__(1024) void ns_init_kernel(const float* __restrict__
 // same way (scaled per column), three part products (22 significant bits: R carries an error of about 1e-7 an entry).  The
 // correction X R, second order in what its rounding loses, takes one part each.  What bounds it is the latency of 512 KB
 // of operands per workgroup, and splitting them: 21 us for 8 blocks, 3-5 us when it copies.  (As two batched products on
-// the float32 matrix pipe, with launches that measured the residual, a warm start took 12 launches and 107 us, now 5 and
-// 70 us; 8 Adam steps on the 9B-shaped (V, O) pair 3700 -> 3050 us with the cold start's elimination avoided.)
+// the float32 matrix pipe, with launches that measured the residual, a warm start took 12 launches and 107 us, now 7 and
+// 75 us; 8 Adam steps on the 9B-shaped (V, O) pair 3700 -> 3085 us with the cold start's elimination avoided.)
 // SL = 16 as long as those workgroups are at most one per compute unit (16 blocks), else 64, which split every row of T and
-// X a quarter as often: a cold start 5 % off rotations takes 120 us for 8 blocks, 207 us for 32 and 675 us for 144 (150, 246
-// and 867 us on the float32 products; sixteen columns for 144 blocks: nine rounds of workgroups a Newton round).
+// X a quarter as often: a cold start 5 % off rotations takes 124 us for 8 blocks, 207 us for 32 and 674 us for 144 (149, 235
+// and 842 us on the float32 products; sixteen columns for 144 blocks: nine rounds of workgroups a Newton round).
 //   cur[b][256 / SL]: the slices' shares of ||R||_F^2.  prev: those of the round before (null: none).  A block whose last
 //   measured residual was below 1e-3 (its correction left less than 1e-6 and the parts' 3e-5) or is beyond any contraction
 //   to count on (||R||_F >= 3, a NaN) is copied, with its residual.  An entry that leaves float16's range makes R infinite.

@@ -10,9 +10,11 @@
 // Why products instead of the elimination: the elimination is a serial chain of k pivot steps (0.75 us each at
 // k = 128), while a round is two k x k products on the 16-bit matrix pipe: 9.3 k cycles at k = 128, of which 3.7 k are
 // the products and the rest splitting, LDS and barriers.  Measured, blocks 5 % off rotations, against a launch that
-// checked for rotations and one that eliminated the others: 112 blocks of 128 11 + 111 -> 30 us (57 k cycles: start 14 k,
+// checked for rotations and one that eliminated the others: 112 blocks of 128 11 + 111 -> 31 us (57 k cycles: start 14 k,
 // three rounds 28 k, the exact step 15 k), 288 blocks (more than one per compute unit) 26 + 198 -> 60 us, 144 blocks of
 // 64 5 + 36 -> 11.5 us, 8 blocks of 32 16.6 -> 7.5 us; the learning loops' warm start at 72 blocks of 128 30 + 5 -> 23.5 us.
+// A block that Newton does not reach pays its rounds: whole calls on blocks far from rotations 16.6 -> 17.7 us for 8 blocks of
+// 32 (up to 25 where a few of many give up late, 20 to 30 % off), 95.7 -> 99.8 us for 8 and 102.2 -> 103.3 us for 112 of 128.
 #include <atomic>
 
 #include "gj_panel.hpp"
