@@ -42,7 +42,8 @@ def test_distances_from_a_rotation(env, nb):
 
 @pytest.mark.parametrize("lr", [1e-4, 3e-3, 3e-2])
 def test_the_loop_keeps_an_inverse(env, lr):
-    """Small steps: two warm rounds; the largest: blocks beyond them, which the elimination takes."""
+    """The inverse handed back is that of the final T, from scratch, whichever way the loop's own came about (small steps: two
+    warm rounds; the largest: the elimination)."""
     torch, cafeq = env
     A, B, T = WL.small_pair(200, 512, K, 1, 78, eps=0.0)
     Td = torch.from_numpy(T.copy()).to("cuda:0")

@@ -125,7 +125,7 @@ def test_pair_adam_follows_the_oracle(env, k, group, rep, lam):
 @pytest.mark.parametrize("k,lr", [(64, 6e-3), (128, 6e-3), (64, 2e-2), (128, 2e-2)])
 def test_pair_adam_with_large_steps_follows_the_oracle(env, k, lr):
     """Inside the loop the inverse is warm-started from the previous iteration's; steps this large make the
-    warm start take all its rounds (k = 64 at 6e-3) or hand the block to the elimination (the others)."""
+    warm start take several rounds (k = 64 at 6e-3) or hand the block to the elimination (the others)."""
     torch, cafeq = env
     steps = 5
     A, B, T0 = WL.small_pair(136, 256, k, 1, 990 + k, eps=0.03)
