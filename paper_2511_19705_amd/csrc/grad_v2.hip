@@ -487,6 +487,8 @@ __global__ __launch_bounds__(256) void prepare_gtiles_kernel(const GtileArgs a) 
         const int64_t off = a.axis == CAFEQ_AXIS_COL ? line * a.ld + ax : ax * a.ld + line;
         x[e] = a.dtype == CAFEQ_F32 ? static_cast<const float*>(a.W)[off]
                                     : bf16_bits_to_f32(static_cast<const uint16_t*>(a.W)[off]);
+        // (an infinity's second part is not a number: with one part, neither is the first)
+        if (parts == 1 && fabsf(x[e]) == INFINITY) x[e] = NAN;
       }
     }
     uint32_t hi[4], mid[4];

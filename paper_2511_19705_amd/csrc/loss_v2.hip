@@ -573,7 +573,8 @@ __global__ __launch_bounds__(256) void prepare_tiles_kernel(const PrepArgs a) {
         const float y = x[8 * hh + 2 * e2 + u] * wsc;
         const _Float16 p0 = _Float16(y);
         const _Float16 p1 = _Float16(y - float(p0));
-        hb[u] = __builtin_bit_cast(uint16_t, p0);
+        // (one part: the second is zero, or not a number behind an infinity, which then is none either, as in two parts)
+        hb[u] = __builtin_bit_cast(uint16_t, parts == 1 && !(p1 == _Float16(0)) ? p1 : p0);
         lb[u] = __builtin_bit_cast(uint16_t, p1);
       }
       hi[e2] = hb[0] | (hb[1] << 16);

@@ -118,3 +118,19 @@ def test_mixed_storage_takes_one_launch(env, nb, d_model, grad):
         ref = ref or (losses, g)
         assert torch.equal(losses, ref[0])
         _same(torch, g, ref[1])
+
+
+@pytest.mark.parametrize("nb", [4, 160])
+@pytest.mark.parametrize("axis", [0, 1])
+def test_infinite_weights_act_as_those_of_a_float32_copy(env, nb, axis):
+    torch, cafeq = env
+    W = _weights(torch, (136, nb * K) if axis == 0 else (nb * K, 136), 81 + axis)
+    W.view(-1)[[5, 700, 9001]] = torch.tensor([float("inf"), float("-inf"), float("inf")], dtype=W.dtype, device=W.device)
+    W.view(-1)[1234] = float("nan")
+    T, P = _blocks(torch, cafeq, nb, 82)
+    for grad in (True, False):
+        got = [cafeq.proxy_loss_fwd_bwd(X, T, P, 4, 64, axis, want_grad=grad, want_codes=not grad,
+                                        prepared=cafeq.prepare_weights(X, axis)) for X in (W, W.float())]
+        for a, b in zip(*got):
+            if a is not None:
+                np.testing.assert_array_equal(a.cpu().numpy(), b.cpu().numpy())     # (not-a-numbers in the same places)
