@@ -214,8 +214,10 @@ int cafeq_apply_transform(const cafeq_mat* W, const cafeq_xform* x, int axis, in
  * along `axis` (0 if the axis length is not a multiple of 128); about rows * cols * 8 bytes for float32, half
  * of that for bfloat16: one copy in the order the loss pass contracts (over the axis), one in the order the gradient
  * pass contracts (over the lines; bfloat16 hi + mid parts, tiles of 128 lines x 128 axis indices; read by the
- * gradient pass for blocks of 128 whatever the group and grid).  bfloat16 weights are one part in either.  The
- * layout belongs to the build of the library that wrote the buffer.
+ * gradient pass for blocks of 128 with shorter groups, whatever the grid).  bfloat16 weights are one part in either.  For
+ * the row axis half as much again: the weights as they are, a line's axis indices side by side (along columns they lie so
+ * in W), for the gradient of groups no shorter than the block.  The layout belongs to the build of the library that wrote
+ * the buffer.
  * cafeq_prepare_weights fills it (device memory, 256-byte aligned, owned by the caller).  The loss pass's copy:
  * per tile of 32 lines x 128 axis indices two float16 parts of every element -- the line's segment scaled
  * by a power of two so that its largest magnitude lies in [2^3, 2^4), hi = fl16(y), lo = fl16(y - hi):

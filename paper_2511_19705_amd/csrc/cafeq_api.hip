@@ -4,6 +4,7 @@
 
 #include "xform_core.hpp"
 #include "loss_reduce.hpp"
+#include "mmid.hpp"
 
 using namespace cafeq;
 namespace cafeq {
@@ -12,6 +13,7 @@ int launch_grad_owner_timed(const GradOwnerJob* jobs, int n, int loss_kind, floa
                             hipStream_t st, const LossArgs* fold);
 int launch_grad_v2_timed(const CoreParams& p, hipStream_t st);
 int launch_grad_pass_timed(int K, int axis, const CoreParams& p, hipStream_t st);
+int launch_grad_gather_timed(int K, const GradGatherJob* jobs, int n, const LossArgs& la, const VArgs* va, hipStream_t st);
 }  // namespace cafeq
 
 namespace {
@@ -143,7 +145,7 @@ bool core_forward_f16(int K, int G, int bits) { return K == 128 && G <= 128 && b
 // faster (blocks of 128), and for groups that span several segments.
 // asym: the min/max grid of Eq. (1); its kernel variants are gradient-free, so the gradient always takes the
 // second pass.
-struct PassPlans { CorePlan first, gpass; GroupPlan gp; bool two, fused, v2, asym; };
+struct PassPlans { CorePlan first, gpass; GroupPlan gp; bool two, fused, v2, asym, gather; };
 bool is_minmax(const cafeq_quant_cfg* cfg) { return cfg->mode == CAFEQ_Q_ASYM_MINMAX; }
 // levels and the surrogate's constant for either grid (Sec. 4.1: 1 / (2^b - 1)^2 for Eq. (1); a quarter of the
 // squared step of the symmetric grid)
@@ -171,20 +173,41 @@ void make_v2_plan(CorePlan* pl, int share = 1) {
   pl->nwg = int(nwg);
   pl->nslot = pl->nwg + pl->nseg;
 }
+// Whether the gradient can come from the arg-max records by gathering lines (grad_gather.hip): a line's inputs lie side by
+// side (columns, or rows with the prepared line-major copy) and a block meets one group per line, or is one of 256, whose
+// product with the matrix of zeros (grad_core.hpp) runs one wave per SIMD.  Gradient passes with their reductions, product /
+// by records: 9B-shaped pair (blocks of 128) 97 / 90 us, 27B-shaped in bfloat16 246 / 165, 2B-shaped 59 / 42; 2304 x 9216
+// whole channels 48 / 16; 9B-shaped (V, O) pair, blocks of 256 and groups of 64, whose lines are read four times, 99 / 70.
+// Blocks of 128 with groups of 64 would read every line twice: 97 / about 150.
+bool gather_possible(int K, const GroupPlan& gp, bool lines) { return lines && (gp.G >= K || K == 256); }
+// A single matrix whose gradient the loss pass can form on the way (blocks of 32 and 64): by records from 8 M weights on.
+// Whole evaluations, on the way / by records: blocks of 32, groups of 32, 4.2 M weights 33 / 40 us, 21 M 97 / 90; blocks of
+// 64, groups of 128, 4.2 M 37.0 / 38.2, 21 M 93 / 83.
+bool gather_single(int K, const GroupPlan& gp, bool lines, bool asym, int64_t weights) {
+  const bool on_the_way = K <= 64 && gp.gspan == 1 && core_lds_bytes(K, gp.Gk, true) != 0 && !asym;
+  return gather_possible(K, gp, lines) && (!on_the_way || weights >= (int64_t(1) << 23));
+}
+bool has_lines(const cafeq_mat* W, int axis) {
+  if (axis == CAFEQ_AXIS_COL) return grad_gather_fits(W->rows, W->ld, 128, W->dtype);
+  return W->prepared && grad_gather_fits(W->cols, 128, prepared_layout(W->cols, W->rows, W->dtype, axis).nlp * 128, W->dtype);
+}
 int plan_passes(int K, const GroupPlan& gp, int64_t nlines, int64_t naxis, bool grad, PassPlans* pp,
-                bool v2 = false, bool asym = false, int v2_share = 1) {
+                bool v2 = false, bool asym = false, int v2_share = 1, bool gather = false) {
   pp->gp = gp;
   pp->v2 = v2;
   pp->asym = asym;
   const size_t fl = core_lds_bytes(K, gp.Gk, true);
   const bool fused_ok = fl != 0 && fl <= 160 * 1024 && gp.gspan == 1 && !(K == 128 && gp.Gk <= 128) && !asym;
-  pp->two = grad && !fused_ok;
-  pp->fused = grad && fused_ok;
+  pp->gather = grad && gather;
+  pp->two = grad && (!fused_ok || gather);
+  pp->fused = grad && fused_ok && !gather;
   int rc = make_plan(K, gp.Gk, nlines, naxis, &pp->first, pp->fused);
   if (rc) return rc;
   if (v2) make_v2_plan(&pp->first, v2_share);
-  if (pp->two) return make_grad_plan(K, nlines, naxis, &pp->gpass);
+  if (pp->two && !fused_ok && naxis % 128 != 0) return CAFEQ_ERR_UNSUPPORTED;
+  if (pp->two && !pp->gather) return make_grad_plan(K, nlines, naxis, &pp->gpass);
   pp->gpass = pp->first;
+  if (pp->gather) pp->gpass.nslot = 0;   // no partials
   return CAFEQ_OK;
 }
 
@@ -194,6 +217,7 @@ struct MemberWs {
   uint16_t *pfwd, *pinv;
   float2 *rec, *grec;
   float2 *rec_mm, *grec_mm;   // min/max grid with groups that span segments
+  uint2* sorted; int* start;  // gradient pass by records
 };
 void carve_member(Carver& c, const PassPlans& pp, int nb, bool grad, bool want_rG, MemberWs* w) {
   const CorePlan& pl = pp.first;
@@ -211,6 +235,8 @@ void carve_member(Carver& c, const PassPlans& pp, int nb, bool grad, bool want_r
   w->rec_mm = c.take<float2>(mm ? size_t(pl.naxis / pl.G) * size_t(pl.nlines) : 0);
   w->grec_mm = c.take<float2>(mm ? size_t(pl.naxis / pp.gp.G) * size_t(pl.nlines) : 0);
   if (!mm) w->rec_mm = w->grec_mm = nullptr;
+  w->sorted = c.take<uint2>(pp.gather ? grad_gather_entries(pl.K, pp.gp.G, pl.naxis, pl.nlines) : 0);
+  w->start = c.take<int>(pp.gather ? grad_gather_starts(pl.K, pp.gp.G, pl.naxis) : 0);
 }
 
 struct SingleWs {
@@ -376,7 +402,7 @@ void fill_common(CoreParams* p, const cafeq_mat* W, const CorePlan& pl, int rep)
 // where the loss pass over prepared weights finds them
 void set_prepared(CoreParams* p, const cafeq_mat* W, int axis) {
   const bool col = axis == CAFEQ_AXIS_COL;
-  const PreparedLayout l = prepared_layout(col ? W->rows : W->cols, col ? W->cols : W->rows, W->dtype);
+  const PreparedLayout l = prepared_layout(col ? W->rows : W->cols, col ? W->cols : W->rows, W->dtype, axis);
   const unsigned char* base = static_cast<const unsigned char*>(W->prepared);
   p->prep_wsq = reinterpret_cast<const float*>(base);
   p->prep_lscale = reinterpret_cast<const float*>(base + l.off_lscale);
@@ -416,8 +442,8 @@ int run_core(int K, int axis, const GroupPlan& gp, CoreParams p, float2* rec, fl
 }
 
 // Whether the gradient passes of a call can run with one workgroup per (matrix, block) and write the gradient in
-// its final form (grad_v2.hip): prepared weights, blocks of 128, no row-blocks sharing a transform block, and
-// enough blocks (up to four rounds of workgroups: the 27B-shaped (down, up) pair, 576 blocks, measured 328 us this way
+// its final form (grad_v2.hip; groups shorter than the block, the others go by records): prepared weights, blocks of 128, no
+// row-blocks sharing a transform block, and enough blocks (up to four rounds of workgroups: the 27B-shaped (down, up) pair, 576 blocks, measured 328 us this way
 // against 350 for the partial sums and their reduction; the 2B-shaped one, 144 blocks, 59 against 59 + 17 + 6 us with the
 // loss reduction's launch, which this way does without).  Whole evaluations this way against partial sums, matrices of
 // 1000 / 2304 / 4608 lines: pairs of 128 blocks 85 / 138 / 214 us against 103 / 155 / 220, of 80 82 / 111 / 180 against
@@ -437,12 +463,27 @@ bool grad_owner_eligible(const cafeq_mat* const* mats, const PassPlans* const* p
 GradOwnerJob grad_owner_job(const cafeq_mat* W, int axis, const PassPlans& pp, const MemberWs& m, float* out,
                             int transpose_out) {
   const bool col = axis == CAFEQ_AXIS_COL;
-  const PreparedLayout l = prepared_layout(col ? W->rows : W->cols, col ? W->cols : W->rows, W->dtype);
+  const PreparedLayout l = prepared_layout(col ? W->rows : W->cols, col ? W->cols : W->rows, W->dtype, axis);
   GradOwnerJob j;
   j.gtiles = static_cast<const unsigned char*>(W->prepared) + l.off_gtiles;
   j.rec = m.grec; j.rG = m.rGreal; j.out = out;
   j.nlines = pp.gpass.nlines; j.nseg = pp.gpass.nseg; j.grp = pp.gp.G; j.transpose_out = transpose_out;
   j.parts = prepared_parts(W->dtype);
+  return j;
+}
+
+GradGatherJob grad_gather_job(const cafeq_mat* W, int axis, int nb, int rep, const PassPlans& pp, const MemberWs& m, float* out,
+                              int transpose_out) {
+  GradGatherJob j;
+  j.dtype = W->dtype; j.nlines = pp.first.nlines; j.nb = nb; j.rep = rep; j.grp = pp.gp.G; j.transpose_out = transpose_out;
+  j.rec = m.grec; j.rG = m.rGreal; j.out = out; j.sorted = m.sorted; j.start = m.start;
+  if (axis == CAFEQ_AXIS_COL) {
+    j.W = W->data; j.line_stride = W->ld; j.seg_stride = 128;
+  } else {
+    const PreparedLayout l = prepared_layout(W->cols, W->rows, W->dtype, axis);
+    j.W = static_cast<const unsigned char*>(W->prepared) + l.off_lines;
+    j.line_stride = 128; j.seg_stride = l.nlp * 128;
+  }
   return j;
 }
 
@@ -457,7 +498,7 @@ int run_grad_pass(int K, int axis, const cafeq_mat* W, int rep, const PassPlans&
   if (W->prepared && K == 128) {
     // the prepared copy also holds the weights in the operand order of this contraction
     const bool col = axis == CAFEQ_AXIS_COL;
-    const PreparedLayout l = prepared_layout(col ? W->rows : W->cols, col ? W->cols : W->rows, W->dtype);
+    const PreparedLayout l = prepared_layout(col ? W->rows : W->cols, col ? W->cols : W->rows, W->dtype, axis);
     pg->prep_gtiles = static_cast<const unsigned char*>(W->prepared) + l.off_gtiles;
     return launch_grad_v2_timed(*pg, st);
   }
@@ -522,6 +563,9 @@ int launch_grad_v2_timed(const CoreParams& p, hipStream_t st) {
 }
 int launch_grad_pass_timed(int K, int axis, const CoreParams& p, hipStream_t st) {
   return timed_launch(st, [&] { return launch_grad_pass(K, axis, p, st); }, 1);
+}
+int launch_grad_gather_timed(int K, const GradGatherJob* jobs, int n, const LossArgs& la, const VArgs* va, hipStream_t st) {
+  return timed_launch(st, [&] { return launch_grad_gather(K, jobs, n, la, va, st); }, 1);
 }
 size_t core_lds_bytes(int K, int G, bool do_grad) {
   switch (K) {
@@ -781,6 +825,8 @@ size_t cafeq_workspace_bytes(int call_id, const cafeq_mat* a, const cafeq_mat* b
       size_t bytes = carve_single(nullptr, pn, x->nb, false).bytes;
       // (where the gradient has no kernel the forward-only size is still reported)
       if (!plan_passes(x->k, gp, nlines, naxis, true, &pg, false, mm)) bytes = std::max(bytes, carve_single(nullptr, pg, x->nb, true).bytes);
+      if (gather_possible(x->k, gp, true) && !plan_passes(x->k, gp, nlines, naxis, true, &pg, false, mm, 1, true))
+        bytes = std::max(bytes, carve_single(nullptr, pg, x->nb, true).bytes);
       return bytes;
     }
     case CAFEQ_CALL_DUAL_PROXY_LOSS: {
@@ -795,6 +841,10 @@ size_t cafeq_workspace_bytes(int call_id, const cafeq_mat* a, const cafeq_mat* b
       size_t bytes = carve_dual(nullptr, na, nbp, x->nb, false).bytes;
       if (!plan_passes(x->k, ga, a->rows, a->cols, true, &qa, false, mm) &&
           !plan_passes(x->k, gb, b->cols, b->rows, true, &qb, false, mm))
+        bytes = std::max(bytes, carve_dual(nullptr, qa, qb, x->nb, true).bytes);
+      if (gather_possible(x->k, ga, true) && gather_possible(x->k, gb, true) &&
+          !plan_passes(x->k, ga, a->rows, a->cols, true, &qa, false, mm, 1, true) &&
+          !plan_passes(x->k, gb, b->cols, b->rows, true, &qb, false, mm, 1, true))
         bytes = std::max(bytes, carve_dual(nullptr, qa, qb, x->nb, true).bytes);
       return bytes;
     }
@@ -840,7 +890,7 @@ size_t cafeq_prepared_bytes(const cafeq_mat* W, int axis) {
   const bool col = axis == CAFEQ_AXIS_COL;
   const int64_t nlines = col ? W->rows : W->cols, naxis = col ? W->cols : W->rows;
   if (naxis % 128 != 0) return 0;
-  return prepared_layout(nlines, naxis, W->dtype).bytes;
+  return prepared_layout(nlines, naxis, W->dtype, axis).bytes;
 }
 
 int cafeq_prepare_weights(const cafeq_mat* W, int axis, void* prepared, void* stream) {
@@ -1008,7 +1058,7 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
   const bool asym = is_minmax(cfg);
   const bool v2 = v2_eligible(W, K, gp, cfg);
   PassPlans pp;
-  rc = plan_passes(K, gp, nlines, naxis, grad, &pp, v2, asym);
+  rc = plan_passes(K, gp, nlines, naxis, grad, &pp, v2, asym, 1, gather_single(K, gp, has_lines(W, cfg->axis), asym, nlines * naxis));
   if (rc) return rc;
   const CorePlan& pl = pp.first;
   {
@@ -1045,7 +1095,7 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
     return rc;
   const cafeq_mat* mats[1] = {W};
   const PassPlans* pps[1] = {&pp};
-  const bool owner = grad && grad_owner_eligible(mats, pps, 1, K, x->rep);
+  const bool owner = grad && !pp.gather && grad_owner_eligible(mats, pps, 1, K, x->rep);
   // (with one workgroup per block in the gradient pass, its first workgroup reduces the losses: one launch less)
   // (with gradient partials, the loss reduction rides in the launch that reduces them)
   if (!grad && (rc = launch_reduce_losses(kLossSur, w.slot_hdr, int(pl.nslot), nullptr, 0, beta, 0.f, 0, losses,
@@ -1055,7 +1105,15 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
     // path through Z (fused into the pass above, or a second pass over the weights from its
     // arg-max records), then the path through rho(P): -2 P^T Mmid P^T
     CoreParams pg = p;
-    if (owner) {
+    if (pp.gather) {
+      // (with the middle factor of the rho path and the loss reduction)
+      const GradGatherJob job = grad_gather_job(W, cfg->axis, nb, x->rep, pp, w.m, gradT, col ? 1 : 0);
+      const VArgs va = mmid_args(p, K, gp.Gk, x->Tinv, col ? 1 : 0, w.mmid);
+      LossArgs la{};
+      la.hdrA = w.slot_hdr; la.nslotA = int(pl.nslot); la.kind = kLossSur; la.beta = beta; la.losses = losses;
+      la.lse_ms = w.lse_ms;
+      if ((rc = launch_grad_gather_timed(K, &job, 1, la, &va, st))) return rc;
+    } else if (owner) {
       const GradOwnerJob job = grad_owner_job(W, cfg->axis, pp, w.m, gradT, col ? 1 : 0);
       LossArgs la{};
       la.hdrA = w.slot_hdr; la.nslotA = int(pl.nslot); la.kind = kLossSur; la.beta = beta; la.losses = losses;
@@ -1130,8 +1188,9 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
   // codes or scales and both use the same group length
   const bool pair_launch = v2A && v2B && !codesU && !scalesU && !codesV && !scalesV && ga.Gk == gb.Gk;
   PassPlans qa, qb;
-  if ((rc = plan_passes(K, ga, A->rows, A->cols, grad, &qa, v2A, asym, pair_launch ? 2 : 1))) return rc;
-  if ((rc = plan_passes(K, gb, B->cols, B->rows, grad, &qb, v2B, asym, pair_launch ? 2 : 1))) return rc;
+  const bool gather = gather_possible(K, ga, has_lines(A, CAFEQ_AXIS_COL)) && gather_possible(K, gb, has_lines(B, CAFEQ_AXIS_ROW));
+  if ((rc = plan_passes(K, ga, A->rows, A->cols, grad, &qa, v2A, asym, pair_launch ? 2 : 1, gather))) return rc;
+  if ((rc = plan_passes(K, gb, B->cols, B->rows, grad, &qb, v2B, asym, pair_launch ? 2 : 1, gather))) return rc;
   const CorePlan &pa = qa.first, &pb = qb.first;
   {
     const size_t la = core_lds_bytes(K, ga.Gk, qa.fused), lb = core_lds_bytes(K, gb.Gk, qb.fused);
@@ -1171,7 +1230,7 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
   b.mins = asym && scalesV ? scalesV + (B->rows / gb.G) * B->cols : nullptr;
   const cafeq_mat* mats[2] = {A, B};
   const PassPlans* pps[2] = {&qa, &qb};
-  const bool owner = grad && grad_owner_eligible(mats, pps, 2, K, x->rep);
+  const bool owner = grad && !gather && grad_owner_eligible(mats, pps, 2, K, x->rep);
 
   if (pair_launch) {
     set_prepared(&a, A, CAFEQ_AXIS_COL);
@@ -1184,22 +1243,31 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
     return rc;
   }
   ag = a;
-  if (!owner && qa.two && (rc = run_grad_pass(K, CAFEQ_AXIS_COL, A, 1, qa, w.a, kLossLse, 0.f, lse_t, w.hdrA, int(pa.nslot),
+  if (!gather && !owner && qa.two && (rc = run_grad_pass(K, CAFEQ_AXIS_COL, A, 1, qa, w.a, kLossLse, 0.f, lse_t, w.hdrA, int(pa.nslot),
                                               w.member_ref, &ag, st)))
     return rc;
   if (!pair_launch && (rc = run_core(K, CAFEQ_AXIS_ROW, gb, b, w.b.rec, w.b.grec, qb.two, st, v2B ? B : nullptr, w.b.rec_mm,
                                      w.b.grec_mm)))
     return rc;
   bg = b;
-  if (!owner && qb.two && (rc = run_grad_pass(K, CAFEQ_AXIS_ROW, B, x->rep, qb, w.b, kLossLse, 0.f, lse_t, w.hdrB, int(pb.nslot),
+  if (!gather && !owner && qb.two && (rc = run_grad_pass(K, CAFEQ_AXIS_ROW, B, x->rep, qb, w.b, kLossLse, 0.f, lse_t, w.hdrB, int(pb.nslot),
                                               w.member_ref + 1, &bg, st)))
     return rc;
 
   const int64_t ngroups = A->rows * (A->cols / ga.G) + (B->rows / gb.G) * B->cols;
-  if (!owner && (rc = launch_reduce_losses(kLossLse, w.hdrA, int(pa.nslot), w.hdrB, int(pb.nslot), 0.f, lse_t, ngroups,
+  if (!owner && !(grad && gather) && (rc = launch_reduce_losses(kLossLse, w.hdrA, int(pa.nslot), w.hdrB, int(pb.nslot), 0.f, lse_t, ngroups,
                                            losses, w.lse_ms, st)))
     return rc;
-  if (grad && owner) {
+  if (grad && gather) {
+    // both members' gradients row by row from the records; d/dT = -P^T G_P P^T follows
+    const GradGatherJob jobs[2] = {grad_gather_job(A, CAFEQ_AXIS_COL, nb, 1, qa, w.a, gradT, 1),
+                                   grad_gather_job(B, CAFEQ_AXIS_ROW, nb, x->rep, qb, w.b, w.gp, 0)};
+    LossArgs la{};
+    la.hdrA = w.hdrA; la.nslotA = int(pa.nslot); la.hdrB = w.hdrB; la.nslotB = int(pb.nslot); la.kind = kLossLse;
+    la.t = lse_t; la.ngroups = ngroups; la.losses = losses; la.lse_ms = w.lse_ms;
+    if ((rc = launch_grad_gather_timed(K, jobs, 2, la, nullptr, st))) return rc;
+    if ((rc = launch_bgemm_chain(x->Tinv, w.gp, w.x1, gradT, K, nb, -1.f, 1.f, st, hook))) return rc;
+  } else if (grad && owner) {
     // both members' gradient passes in one launch: one workgroup per block writes member A's share into gradT
     // (transposed) and member B's G_P; d/dT = -P^T G_P P^T follows.  The pair's LogSumExp has to be known to
     // them: every workgroup reduces the partial headers itself, the first also writes the losses.

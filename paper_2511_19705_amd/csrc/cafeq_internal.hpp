@@ -57,12 +57,13 @@ size_t core_lds_bytes_k256(int G, bool do_grad);
 int device_cu_count();
 
 // loss_v2.hip: loss pass over prepared weights (128 x 128 blocks, groups up to 128)
-// header (||W||^2), per-line factors, the loss pass's tiles, their partial sums, the gradient pass's tiles
-struct PreparedLayout { int64_t nlp, nseg, ntiles; size_t off_lscale, off_planes, off_partial, off_gtiles, bytes; };
+// header (||W||^2), per-line factors, the loss pass's tiles, their partial sums, the gradient pass's tiles; for matrices
+// transformed along their rows also the weights as they are, line by line: [nseg][nlp][128]
+struct PreparedLayout { int64_t nlp, nseg, ntiles; size_t off_lscale, off_planes, off_partial, off_gtiles, off_lines, bytes; };
 // 16-bit parts per weight in the prepared copies: two for float32, one for bfloat16, whose eight significant bits one
 // float16 (loss pass) or bfloat16 (gradient pass) holds -- its second part was zeros, half the bytes of both passes.
 __host__ __device__ constexpr int prepared_parts(int dtype) { return dtype == CAFEQ_BF16 ? 1 : 2; }
-PreparedLayout prepared_layout(int64_t nlines, int64_t naxis, int dtype);
+PreparedLayout prepared_layout(int64_t nlines, int64_t naxis, int dtype, int axis);
 int launch_prepare(const cafeq_mat* W, int axis, void* prepared, hipStream_t st);
 // gradient pass over prepared weights (blocks of 128; grad_v2.hip): p.prep_gtiles, p.rec, p.grp as launch_grad_pass
 size_t prepared_gtiles_bytes(int64_t nlines, int64_t naxis, int dtype);
@@ -77,6 +78,19 @@ struct GradOwnerJob {
 struct LossArgs;   // loss_reduce.hpp; fold != nullptr: the loss reduction runs inside the launch
 int launch_grad_v2_owner(const GradOwnerJob* jobs, int n, int loss_kind, float beta, float lse_t, const double* lse_ms,
                          hipStream_t st, const LossArgs* fold = nullptr);
+// gradient pass by records (grad_gather.hip): lines as they lie (element (line, axis index a) at line * line_stride +
+// a / 128 * seg_stride + a % 128); sorted, start: scratch of grad_gather_entries / grad_gather_starts elements
+struct GradGatherJob {
+  const void* W; int dtype; int64_t line_stride, seg_stride;
+  const float2* rec; const float* rG; float* out; uint2* sorted; int* start;
+  int64_t nlines; int nb, rep, grp, transpose_out;
+};
+bool grad_gather_fits(int64_t nlines, int64_t line_stride, int64_t seg_stride, int dtype);
+size_t grad_gather_entries(int K, int grp, int64_t naxis, int64_t nlines);
+size_t grad_gather_starts(int K, int grp, int64_t naxis);
+// la: the call's loss reduction; va (single matrices; may be null): the middle factor of the rho path, both in the same launches
+struct VArgs;   // mmid.hpp
+int launch_grad_gather(int K, const GradGatherJob* jobs, int n, const LossArgs& la, const VArgs* va, hipStream_t st);
 int launch_loss_v2(int G, int axis, const CoreParams& p, hipStream_t st);
 int launch_loss_prepared(int G, int axis, const CoreParams& p, hipStream_t st);   // ... with the caller's timing events
 // both members of a pair in one launch (loss_v2.hip), plain and with the caller's timing events

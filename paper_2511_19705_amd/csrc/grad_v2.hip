@@ -479,17 +479,35 @@ __global__ __launch_bounds__(256) void prepare_gtiles_kernel(const GtileArgs a) 
     const int ln = lane & 31, h = lane >> 5;
     const int64_t ax = seg * 128 + 32 * mt + ln, line0 = mis * kGvLines + 16 * s + 8 * h;
     float x[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int64_t line = line0 + e;
-      x[e] = 0.f;
-      if (line < a.nlines) {
-        const int64_t off = a.axis == CAFEQ_AXIS_COL ? line * a.ld + ax : ax * a.ld + line;
-        x[e] = a.dtype == CAFEQ_F32 ? static_cast<const float*>(a.W)[off]
-                                    : bf16_bits_to_f32(static_cast<const uint16_t*>(a.W)[off]);
-        // (an infinity's second part is not a number: with one part, neither is the first)
-        if (parts == 1 && fabsf(x[e]) == INFINITY) x[e] = NAN;
+    if (a.axis == CAFEQ_AXIS_ROW && line0 + 8 <= a.nlines) {
+      // (the eight lines lie side by side: ld is a multiple of a vector, line0 of eight)
+      const int64_t off = ax * a.ld + line0;
+      float4 v0, v1;
+      if (a.dtype == CAFEQ_F32) {
+        v0 = load4(static_cast<const float*>(a.W) + off);
+        v1 = load4(static_cast<const float*>(a.W) + off + 4);
+      } else {
+        v0 = load4(static_cast<const uint16_t*>(a.W) + off);
+        v1 = load4(static_cast<const uint16_t*>(a.W) + off + 4);
       }
+      x[0] = v0.x; x[1] = v0.y; x[2] = v0.z; x[3] = v0.w; x[4] = v1.x; x[5] = v1.y; x[6] = v1.z; x[7] = v1.w;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int64_t line = line0 + e;
+        x[e] = 0.f;
+        if (line < a.nlines) {
+          const int64_t off = a.axis == CAFEQ_AXIS_COL ? line * a.ld + ax : ax * a.ld + line;
+          x[e] = a.dtype == CAFEQ_F32 ? static_cast<const float*>(a.W)[off]
+                                      : bf16_bits_to_f32(static_cast<const uint16_t*>(a.W)[off]);
+        }
+      }
+    }
+    if (parts == 1) {
+      // (an infinity's second part is not a number: with one part, neither is the first)
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (fabsf(x[e]) == INFINITY) x[e] = NAN;
     }
     uint32_t hi[4], mid[4];
 #pragma unroll

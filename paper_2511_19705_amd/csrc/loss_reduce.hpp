@@ -3,7 +3,7 @@
 // are relative to per-slot references).  One body, two users: the stand-alone kernel of one workgroup, and the
 // gradient pass with one workgroup per block, whose workgroups each repeat it (a few hundred headers from the
 // memory-side cache) instead of waiting for a launch of its own; only the workgroup told to writes the results.
-// The first 256 threads of the NT-thread workgroup walk the headers -- the summation order does not depend on NT.
+// All NT threads of the workgroup walk the headers.
 #pragma once
 #include "xform_core.hpp"
 
@@ -24,7 +24,6 @@ template <int NT>
 __device__ __forceinline__ void reduce_losses_body(const LossArgs& a, double* red, bool write, double* m_out,
                                                    double* s_out) {
   constexpr int NW = NT / 64;
-  const bool walker = threadIdx.x < kLossThreads;
   // four sums and one maximum over the workgroup, fixed order
   auto reduce5 = [&](double& v0, double& v1, double& v2, double& v3, double& vmax) {
     for (int k = 1; k < 64; k <<= 1) {
@@ -38,6 +37,7 @@ __device__ __forceinline__ void reduce_losses_body(const LossArgs& a, double* re
     __syncthreads();
     v0 = v1 = v2 = v3 = 0;
     vmax = -INFINITY;
+#pragma unroll 2
     for (int k = 0; k < NW; ++k) {
       v0 += red[k]; v1 += red[NW + k]; v2 += red[2 * NW + k]; v3 += red[3 * NW + k];
       vmax = fmax(vmax, red[4 * NW + k]);
@@ -46,11 +46,9 @@ __device__ __forceinline__ void reduce_losses_body(const LossArgs& a, double* re
   };
   if (a.kind == kLossSur) {
     double l2 = 0, ez = 0, ws = 0, su = 0, dummy = -INFINITY;
-    if (walker) {
-      for (int i = threadIdx.x; i < a.nslotA; i += kLossThreads) {
-        const float* h = a.hdrA + size_t(i) * kHdrFloats;
-        l2 += h[kHdrL2]; ez += h[kHdrErrZ]; ws += h[kHdrWsq]; su += h[kHdrSur];
-      }
+    for (int i = threadIdx.x; i < a.nslotA; i += NT) {
+      const float4 h = *reinterpret_cast<const float4*>(a.hdrA + size_t(i) * kHdrFloats);
+      l2 += h.x; ez += h.y; ws += h.z; su += h.w;
     }
     reduce5(l2, ez, ws, su, dummy);
     if (write && threadIdx.x == 0) {
@@ -61,35 +59,50 @@ __device__ __forceinline__ void reduce_losses_body(const LossArgs& a, double* re
   }
   // one pass over both members' headers: four sums and the largest reference; each thread keeps
   // its slots' (sum of exponentials, reference) pairs for the second step
-  constexpr int kMaxPer = 8;                       // slots per thread held in registers
+  constexpr int kMaxPer = 4;                       // slots per thread held in registers
   const int ntot = a.nslotA + a.nslotB;
   double ezA = 0, ezB = 0, l2A = 0, l2B = 0, m = -INFINITY;
   float sur[kMaxPer], mref[kMaxPer];
-  int cnt = 0;
-  if (walker) {
-    for (int i = threadIdx.x; i < ntot; i += kLossThreads, ++cnt) {
-      const bool isA = i < a.nslotA;
-      const float* h = isA ? a.hdrA + size_t(i) * kHdrFloats : a.hdrB + size_t(i - a.nslotA) * kHdrFloats;
-      const float ez = h[kHdrErrZ], l2 = h[kHdrL2], su = h[kHdrSur], mr = h[kHdrMref];
-      if (isA) { ezA += ez; l2A += l2; } else { ezB += ez; l2B += l2; }
-      m = fmax(m, double(mr));
-      if (cnt < kMaxPer) { sur[cnt] = su; mref[cnt] = mr; }
+  // (a header's first four fields in one request, every thread's headers -- up to kMaxPer -- in flight together)
+  static_assert(kHdrL2 == 0 && kHdrErrZ == 1 && kHdrSur == 3 && kHdrFloats % 4 == 0, "header layout");
+  float4 f[kMaxPer];
+#pragma unroll
+  for (int c = 0; c < kMaxPer; ++c) {
+    const int i = int(threadIdx.x) + c * NT;
+    f[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+    mref[c] = -INFINITY;
+    if (i < ntot) {
+      const float* h = i < a.nslotA ? a.hdrA + size_t(i) * kHdrFloats : a.hdrB + size_t(i - a.nslotA) * kHdrFloats;
+      f[c] = *reinterpret_cast<const float4*>(h);
+      mref[c] = h[kHdrMref];
     }
+  }
+#pragma unroll
+  for (int c = 0; c < kMaxPer; ++c) {
+    const int i = int(threadIdx.x) + c * NT;
+    if (i < ntot) {
+      if (i < a.nslotA) { ezA += f[c].y; l2A += f[c].x; } else { ezB += f[c].y; l2B += f[c].x; }
+      m = fmax(m, double(mref[c]));
+    }
+    sur[c] = f[c].w;
+  }
+  for (int i = int(threadIdx.x) + kMaxPer * NT; i < ntot; i += NT) {
+    const bool isA = i < a.nslotA;
+    const float* h = isA ? a.hdrA + size_t(i) * kHdrFloats : a.hdrB + size_t(i - a.nslotA) * kHdrFloats;
+    const float ez = h[kHdrErrZ], l2 = h[kHdrL2], mr = h[kHdrMref];
+    if (isA) { ezA += ez; l2A += l2; } else { ezB += ez; l2B += l2; }
+    m = fmax(m, double(mr));
   }
   reduce5(ezA, ezB, l2A, l2B, m);
   // global normaliser of the exponentials
   double s = 0;
-  cnt = 0;
-  if (walker) {
-    for (int i = threadIdx.x; i < ntot; i += kLossThreads, ++cnt) {
-      float su, mr;
-      if (cnt < kMaxPer) { su = sur[cnt]; mr = mref[cnt]; }
-      else {
-        const float* h = i < a.nslotA ? a.hdrA + size_t(i) * kHdrFloats : a.hdrB + size_t(i - a.nslotA) * kHdrFloats;
-        su = h[kHdrSur]; mr = h[kHdrMref];
-      }
-      if (su > 0.f) s += double(su) * exp(double(a.t) * (double(mr) - m));
-    }
+#pragma unroll
+  for (int c = 0; c < kMaxPer; ++c)
+    if (int(threadIdx.x) + c * NT < ntot && sur[c] > 0.f) s += double(sur[c]) * exp(double(a.t) * (double(mref[c]) - m));
+  for (int i = int(threadIdx.x) + kMaxPer * NT; i < ntot; i += NT) {
+    const float* h = i < a.nslotA ? a.hdrA + size_t(i) * kHdrFloats : a.hdrB + size_t(i - a.nslotA) * kHdrFloats;
+    const float su = h[kHdrSur], mr = h[kHdrMref];
+    if (su > 0.f) s += double(su) * exp(double(a.t) * (double(mr) - m));
   }
   double z1 = 0, z2 = 0, z3 = 0, zm = -INFINITY;
   reduce5(s, z1, z2, z3, zm);

@@ -519,6 +519,7 @@ struct PrepArgs {
   const void* W; int dtype; int64_t rows, cols, ld; int axis;
   int64_t nlines, nlp; int nseg;
   unsigned char* planes; float* lscale; double* partial;
+  unsigned char* lines;   // line-major copy (may be null)
 };
 
 __global__ __launch_bounds__(256) void prepare_tiles_kernel(const PrepArgs a) {
@@ -543,6 +544,21 @@ __global__ __launch_bounds__(256) void prepare_tiles_kernel(const PrepArgs a) {
     tile[li][m] = v;
   }
   __syncthreads();
+  if (a.lines) {
+    // (a bfloat16's bits are the upper half of its float32's)
+    for (int r = 0; r < 4; ++r) {
+      const int li = r * 8 + (t >> 5), m = 4 * (t & 31);
+      const int64_t at = (int64_t(seg) * a.nlp + strip * 32 + li) * 128 + m;
+      const float* s = &tile[li][m];
+      if (a.dtype == CAFEQ_F32) {
+        *reinterpret_cast<float4*>(a.lines + at * 4) = make_float4(s[0], s[1], s[2], s[3]);
+      } else {
+        *reinterpret_cast<uint2*>(a.lines + at * 2) =
+            make_uint2(__float_as_uint(s[0]) >> 16 | (__float_as_uint(s[1]) & 0xFFFF0000u),
+                       __float_as_uint(s[2]) >> 16 | (__float_as_uint(s[3]) & 0xFFFF0000u));
+      }
+    }
+  }
   const int li = t >> 3, c = t & 7;
   float x[16];
   float mx = 0.f;
@@ -630,7 +646,7 @@ int launch_v2_t(const CoreParams& p, hipStream_t st) {
 
 }  // namespace
 
-PreparedLayout prepared_layout(int64_t nlines, int64_t naxis, int dtype) {
+PreparedLayout prepared_layout(int64_t nlines, int64_t naxis, int dtype, int axis) {
   PreparedLayout l;
   l.nlp = (nlines + kV2MacroLines - 1) / kV2MacroLines * kV2MacroLines;
   l.nseg = naxis / 128;
@@ -639,7 +655,9 @@ PreparedLayout prepared_layout(int64_t nlines, int64_t naxis, int dtype) {
   l.off_planes = align_up(l.off_lscale + size_t(l.nseg) * l.nlp * sizeof(float), 256);
   l.off_partial = l.off_planes + size_t(l.ntiles) * v2_tile_bytes(prepared_parts(dtype));
   l.off_gtiles = align_up(l.off_partial + size_t(l.ntiles) * sizeof(double), 256);
-  l.bytes = align_up(l.off_gtiles + prepared_gtiles_bytes(nlines, naxis, dtype), 256);
+  l.off_lines = align_up(l.off_gtiles + prepared_gtiles_bytes(nlines, naxis, dtype), 256);
+  const size_t lines = axis == CAFEQ_AXIS_ROW ? size_t(l.nseg) * l.nlp * 128 * (dtype == CAFEQ_BF16 ? 2 : 4) : 0;
+  l.bytes = align_up(l.off_lines + lines, 256);
   return l;
 }
 
@@ -647,13 +665,14 @@ int launch_prepare(const cafeq_mat* W, int axis, void* prepared, hipStream_t st)
   const bool col = axis == CAFEQ_AXIS_COL;
   const int64_t nlines = col ? W->rows : W->cols, naxis = col ? W->cols : W->rows;
   if (naxis % 128 != 0) return CAFEQ_ERR_BAD_SHAPE;
-  const PreparedLayout l = prepared_layout(nlines, naxis, W->dtype);
+  const PreparedLayout l = prepared_layout(nlines, naxis, W->dtype, axis);
   unsigned char* base = static_cast<unsigned char*>(prepared);
   PrepArgs a;
   a.W = W->data; a.dtype = W->dtype; a.rows = W->rows; a.cols = W->cols; a.ld = W->ld; a.axis = axis;
   a.nlines = nlines; a.nlp = l.nlp; a.nseg = int(l.nseg);
   a.planes = base + l.off_planes; a.lscale = reinterpret_cast<float*>(base + l.off_lscale);
   a.partial = reinterpret_cast<double*>(base + l.off_partial);
+  a.lines = col ? nullptr : base + l.off_lines;
   hipLaunchKernelGGL(prepare_tiles_kernel, dim3(unsigned(l.ntiles)), dim3(256), 0, st, a);
   CAFEQ_CHECK_LAUNCH();
   hipLaunchKernelGGL(prepare_sum_kernel, dim3(1), dim3(256), 0, st, a.partial, l.ntiles, reinterpret_cast<float*>(base));
