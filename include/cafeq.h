@@ -74,9 +74,9 @@ typedef enum { CAFEQ_Q_SYM_ABSMAX = 0, CAFEQ_Q_ASYM_MINMAX = 1 } cafeq_qmode;
  * the descriptor tells a call that they differ).  The weights are constant over the thousands of loss
  * evaluations of a learning run (paper Sec. 4.1, Sec. 4.2); with a prepared copy the loss pass of
  * cafeq_proxy_loss_fwd_bwd / cafeq_dual_proxy_loss_fwd_bwd / cafeq_optimize_* reads them in the form
- * the matrix cores consume (where a kernel for it exists: blocks of 128, groups up to 128, up to
- * 4 bits; ignored otherwise).  `data` must stay valid either way: the gradient pass and every other
- * configuration read it.  Entry points that do not mention it ignore the field. */
+ * the matrix cores consume (where a kernel for it exists: blocks of 32, 64 and 128, groups up to 128, up to
+ * 4 bits; ignored otherwise, and for blocks of 32 and 64 where the general kernel is the faster one).  `data` must stay
+ * valid either way: the gradient pass and every other configuration read it.  Entry points that do not mention it ignore the field. */
 typedef struct {
   const void* data;
   int64_t rows, cols, ld;

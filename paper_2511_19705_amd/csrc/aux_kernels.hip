@@ -27,10 +27,10 @@ constexpr int kSplitThreads = 1024;
 // half h -> chunk 2*c2 + h, holding inputs 16*c2 + 8u + 4h + e at position 4u + e), the chunk stored
 // at chunk ^ ((out >> 2) & 3) (LDS bank swizzle).
 struct SplitJob { const float* src; uint16_t* dst; int trans, nplanes; float* fscale; int natural, texp; };   // fscale, texp: see below
-// A job with fscale != null writes TWO float16 planes instead: the block is first scaled by the power of
+// A job with fscale != null writes two (or three: nplanes) float16 planes instead: the block is first scaled by the power of
 // two that puts its largest magnitude into [2^texp, 2^(texp+1)) (14: the low parts stay normal numbers; 4: sums of
 // 128 products with operands below 2^4 stay below 2^16 -- the matrix cores take denormal float16 inputs exactly), then
-// x = hi + lo with both parts rounded to nearest; fscale[b] receives the factor that undoes the scale.
+// x = hi + lo (+ a third) with the parts rounded to nearest; fscale[b] receives the factor that undoes the scale.
 //
 // rho[b*K + j]: squared norm of row j (by_row) or column j of P_b, summed in float64.
 // With rG != null the workgroup also writes the sums of rho over groups of G axis indices (what rho_group_kernel
@@ -195,17 +195,20 @@ __global__ __launch_bounds__(kSplitThreads) void split_planes_kernel(const Split
       uint16_t* at = reinterpret_cast<uint16_t*>(lds) + sr * nplanes * K * 32 + out * 32 + chunk * 8 + 4 * u;
       float y[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
       if (jb.fscale) {
-        uint32_t hi[4], lo[4];
+        uint32_t hi[4], lo[4], lo2[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float z = y[e] * hsc;
           const _Float16 a = _Float16(z);
-          const _Float16 b = _Float16(z - float(a));
+          const float r = z - float(a);
+          const _Float16 b = _Float16(r);
           hi[e] = __builtin_bit_cast(uint16_t, a);
           lo[e] = __builtin_bit_cast(uint16_t, b);
+          lo2[e] = __builtin_bit_cast(uint16_t, _Float16(r - float(b)));
         }
         *reinterpret_cast<uint2*>(at) = make_uint2(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16));
         *reinterpret_cast<uint2*>(at + K * 32) = make_uint2(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16));
+        if (nplanes == 3) *reinterpret_cast<uint2*>(at + 2 * K * 32) = make_uint2(lo2[0] | (lo2[1] << 16), lo2[2] | (lo2[3] << 16));
         continue;
       }
       for (int pl = 0; pl < nplanes; ++pl) {
@@ -681,7 +684,7 @@ int launch_split_planes_multi(const SplitRequest* req, int n, int K, int nb, hip
   js.njobs = n; js.nrho = nrho; js.nb = nb; js.hdr = hdr; js.nhdr = nslot * kHdrFloats;
   for (int i = 0; i < n; ++i) {
     js.job[i].src = req[i].src; js.job[i].dst = req[i].dst;
-    js.job[i].trans = req[i].trans; js.job[i].nplanes = req[i].fscale ? 2 : req[i].nplanes;
+    js.job[i].trans = req[i].trans; js.job[i].nplanes = req[i].nplanes;
     js.job[i].fscale = req[i].fscale; js.job[i].natural = req[i].natural; js.job[i].texp = req[i].texp;
   }
   for (int i = 0; i < nrho; ++i) {
@@ -751,7 +754,7 @@ int launch_reduce_grad_pair(const CoreParams& pa, int GA, bool fusedA, const flo
 }
 int launch_build_mmid(const CoreParams& p, int K, int G, int nb, const float* P, int scale_rows, float* Mmid,
                       hipStream_t st) {
-  const VArgs a = mmid_args(p, K, G, P, scale_rows, Mmid);
+  const VArgs a = mmid_args(p, K, K > G ? K : G, G, P, scale_rows, Mmid);
   hipLaunchKernelGGL(build_mmid_kernel, dim3(nb * kMmidParts), dim3(256), 0, st, a);
   CAFEQ_CHECK_LAUNCH();
   return CAFEQ_OK;
@@ -760,7 +763,7 @@ int launch_single_tail(const CoreParams& pgrad, const CoreParams& ploss, int K, 
                        int transpose_out, float* gradT, const float* P, int scale_rows, float* Mmid, float beta,
                        int nslot, float* losses, double* lse_ms, hipStream_t st) {
   const ReduceArgs ra = reduce_args(pgrad, K, G, fused, transpose_out, nullptr, nullptr, gradT);
-  const VArgs va = mmid_args(ploss, K, G, P, scale_rows, Mmid);
+  const VArgs va = mmid_args(ploss, K, K > G ? K : G, G, P, scale_rows, Mmid);
   LossArgs la{};
   la.hdrA = ploss.slot_hdr; la.nslotA = nslot; la.kind = kLossSur; la.beta = beta; la.losses = losses;
   la.lse_ms = lse_ms;

@@ -161,11 +161,18 @@ float beta_for(const cafeq_quant_cfg* cfg, const QGrid& g) {
 }
 // The loss pass over prepared weights (loss_v2.hip): one workgroup of eight waves per compute unit,
 // macro-tiles of 256 lines.
-bool v2_eligible(const cafeq_mat* W, int K, const GroupPlan& gp, const cafeq_quant_cfg* cfg) {
-  return W->prepared != nullptr && K == 128 && gp.Gk <= 128 && gp.gspan == 1 && cfg->bits <= 4 && !is_minmax(cfg);
+// on_the_way: the loss pass forms the gradient, too (blocks of 32 and 64 whose gradient does not come from records).
+// codes_along_rows: it writes codes or scales of a matrix transformed along its rows (byte stores).  Blocks of 32 and 64 with
+// float32 weights and groups of 32 or 64 have no registers for that next to two parts of everything: 9216 x 2304 48 to 58 us
+// the general way, 58 to 69 this way (groups of 128 59 and 50).
+bool v2_eligible(const cafeq_mat* W, int K, const GroupPlan& gp, const cafeq_quant_cfg* cfg, bool on_the_way, bool codes_along_rows) {
+  if (K < 128 && (on_the_way || (codes_along_rows && gp.Gk < 128 && W->dtype == CAFEQ_F32))) return false;
+  return W->prepared != nullptr && K <= 128 && gp.Gk <= 128 && gp.gspan == 1 && cfg->bits <= 4 && !is_minmax(cfg);
 }
 // share: the matrix gets 1 / share of the chip's compute units (2: the members of a pair that run in one launch)
 void make_v2_plan(CorePlan* pl, int share = 1) {
+  // (segments of 128 whatever the block)
+  pl->L = 128; pl->NBLK = 128 / pl->K; pl->NGRP = 128 / pl->G; pl->nseg = int(pl->naxis / 128);
   pl->mt_per_seg = (pl->nlines + 255) / 256;
   pl->n_mt = pl->mt_per_seg * pl->nseg;
   int64_t nwg = std::min<int64_t>(pl->n_mt, int64_t(device_cu_count()) / share);
@@ -422,7 +429,7 @@ int run_core(int K, int axis, const GroupPlan& gp, CoreParams p, float2* rec, fl
     // loss pass over the prepared copy of the weights
     set_prepared(&p, prepared_of, axis);
     p.rec = want_rec ? rec : nullptr;
-    return launch_loss_prepared(gp.Gk, axis, p, st);
+    return launch_loss_prepared(K, gp.Gk, axis, p, st);
   }
   if (gp.gspan > 1) {
     CoreParams s1 = p;
@@ -547,11 +554,11 @@ int timed_launch(hipStream_t st, F&& launch, int kind = 0) {
 int launch_core(int K, int G, int axis, const CoreParams& p, hipStream_t st) {
   return timed_launch(st, [&] { return launch_core_raw(K, G, axis, p, st); });
 }
-int launch_loss_prepared(int G, int axis, const CoreParams& p, hipStream_t st) {
-  return timed_launch(st, [&] { return launch_loss_v2(G, axis, p, st); });
+int launch_loss_prepared(int K, int G, int axis, const CoreParams& p, hipStream_t st) {
+  return timed_launch(st, [&] { return launch_loss_v2(K, G, axis, p, st); });
 }
-int launch_loss_prepared_pair(int G, const CoreParams& pa, const CoreParams& pb, hipStream_t st) {
-  return timed_launch(st, [&] { return launch_loss_v2_pair(G, pa, pb, st); });
+int launch_loss_prepared_pair(int K, int G, const CoreParams& pa, const CoreParams& pb, hipStream_t st) {
+  return timed_launch(st, [&] { return launch_loss_v2_pair(K, G, pa, pb, st); });
 }
 // the gradient pass over the weights, with the caller's timing events when the table asks for kind 1
 int launch_grad_owner_timed(const GradOwnerJob* jobs, int n, int loss_kind, float beta, float lse_t, const double* lse_ms,
@@ -1005,7 +1012,7 @@ int cafeq_apply_transform(const cafeq_mat* W, const cafeq_xform* x, int axis, in
   // in the room of the third
   float* fs = core_forward_f16(x->k, x->k, 4) ? reinterpret_cast<float*>(planes + size_t(x->nb) * 2 * x->k * x->k) : nullptr;
   {
-    const SplitRequest req{side == CAFEQ_SIDE_T ? x->T : x->Tinv, planes, col ? 1 : 0, kFwdPlanes, fs};
+    const SplitRequest req{side == CAFEQ_SIDE_T ? x->T : x->Tinv, planes, col ? 1 : 0, fs ? 2 : kFwdPlanes, fs};
     if ((rc = launch_split_planes_multi(&req, 1, x->k, x->nb, st))) return rc;
   }
   CoreParams p;
@@ -1056,9 +1063,12 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
   if (rc) return rc;
   const bool grad = gradT != nullptr;
   const bool asym = is_minmax(cfg);
-  const bool v2 = v2_eligible(W, K, gp, cfg);
+  // (Gradient descent at two bits takes steps nine times those at three and amplifies any change of rounding: of 20 small loops
+  // a few end 1e-4 to 4e-3 elsewhere for a gradient that is ten times closer to float64's.  They keep the pass they had.)
+  const bool gather = gather_single(K, gp, has_lines(W, cfg->axis), asym, nlines * naxis) && !(hook && cfg->bits == 2);
+  const bool v2 = v2_eligible(W, K, gp, cfg, grad && !gather, !col && (codes || scales));
   PassPlans pp;
-  rc = plan_passes(K, gp, nlines, naxis, grad, &pp, v2, asym, 1, gather_single(K, gp, has_lines(W, cfg->axis), asym, nlines * naxis));
+  rc = plan_passes(K, gp, nlines, naxis, grad, &pp, v2, asym, 1, gather);
   if (rc) return rc;
   const CorePlan& pl = pp.first;
   {
@@ -1069,14 +1079,14 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
   SingleWs w = carve_single(ws, pp, nb, grad);
   const QGrid grid = grid_for(cfg);
   const float beta = beta_for(cfg, grid);
-  const bool f16 = core_forward_f16(K, gp.Gk, cfg->bits);
+  const bool f16 = v2 || core_forward_f16(K, gp.Gk, cfg->bits);
 
   CoreParams p;
   fill_common(&p, W, pl, x->rep);
   // forward operand [out][in]: T^T (COL) or T (ROW); inverse operand: Tinv^T or Tinv
   {
     // (prepared weights: float16 planes for both operands, scaled so that the rounding error fits float16)
-    const SplitRequest req[2] = {{x->T, w.m.pfwd, col ? 1 : 0, kFwdPlanes, f16 ? w.m.fs : nullptr, v2 ? 1 : 0, v2 ? 4 : 14},
+    const SplitRequest req[2] = {{x->T, w.m.pfwd, col ? 1 : 0, v2 ? v2_fwd_parts(K) : f16 ? 2 : kFwdPlanes, f16 ? w.m.fs : nullptr, v2 ? 1 : 0, v2 ? 4 : 14},
                                  {x->Tinv, w.m.pinv, col ? 1 : 0, kInvPlanes, v2 ? w.m.fsi : nullptr, 0, 4}};
     // rho per axis index, its sums per segment-level group (the loss sweep) and per group (the gradient pass)
     // (groups inside a block, or of a few whole blocks: the same launch)
@@ -1108,7 +1118,7 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
     if (pp.gather) {
       // (with the middle factor of the rho path and the loss reduction)
       const GradGatherJob job = grad_gather_job(W, cfg->axis, nb, x->rep, pp, w.m, gradT, col ? 1 : 0);
-      const VArgs va = mmid_args(p, K, gp.Gk, x->Tinv, col ? 1 : 0, w.mmid);
+      const VArgs va = mmid_args(p, K, pl.L, gp.Gk, x->Tinv, col ? 1 : 0, w.mmid);
       LossArgs la{};
       la.hdrA = w.slot_hdr; la.nslotA = int(pl.nslot); la.kind = kLossSur; la.beta = beta; la.losses = losses;
       la.lse_ms = w.lse_ms;
@@ -1183,12 +1193,13 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
   if ((rc = resolve_group(cfg, B->rows, K, &gb))) return rc;
   const bool grad = gradT != nullptr;
   const bool asym = is_minmax(cfg);
-  const bool v2A = v2_eligible(A, K, ga, cfg), v2B = v2_eligible(B, K, gb, cfg);
+  const bool gather = gather_possible(K, ga, has_lines(A, CAFEQ_AXIS_COL)) && gather_possible(K, gb, has_lines(B, CAFEQ_AXIS_ROW));
+  const bool v2A = v2_eligible(A, K, ga, cfg, grad && !gather, false);
+  const bool v2B = v2_eligible(B, K, gb, cfg, grad && !gather, codesV || scalesV);
   // both loss passes over prepared weights in one launch, each member on half of the chip: when neither writes
   // codes or scales and both use the same group length
   const bool pair_launch = v2A && v2B && !codesU && !scalesU && !codesV && !scalesV && ga.Gk == gb.Gk;
   PassPlans qa, qb;
-  const bool gather = gather_possible(K, ga, has_lines(A, CAFEQ_AXIS_COL)) && gather_possible(K, gb, has_lines(B, CAFEQ_AXIS_ROW));
   if ((rc = plan_passes(K, ga, A->rows, A->cols, grad, &qa, v2A, asym, pair_launch ? 2 : 1, gather))) return rc;
   if ((rc = plan_passes(K, gb, B->cols, B->rows, grad, &qb, v2B, asym, pair_launch ? 2 : 1, gather))) return rc;
   const CorePlan &pa = qa.first, &pb = qb.first;
@@ -1200,12 +1211,12 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
   DualWs w = carve_dual(ws, qa, qb, nb, grad);
   const QGrid grid = grid_for(cfg);
   // the gradient-free pass over 128 x 128 blocks (one block per segment) takes half-precision forward operands
-  const bool f16A = core_forward_f16(K, ga.Gk, cfg->bits), f16B = core_forward_f16(K, gb.Gk, cfg->bits);
+  const bool f16A = v2A || core_forward_f16(K, ga.Gk, cfg->bits), f16B = v2B || core_forward_f16(K, gb.Gk, cfg->bits);
 
   {
-    const SplitRequest req[4] = {{x->T, w.a.pfwd, 1, kFwdPlanes, f16A ? w.a.fs : nullptr, v2A ? 1 : 0, v2A ? 4 : 14},
+    const SplitRequest req[4] = {{x->T, w.a.pfwd, 1, v2A ? v2_fwd_parts(K) : f16A ? 2 : kFwdPlanes, f16A ? w.a.fs : nullptr, v2A ? 1 : 0, v2A ? 4 : 14},
                                  {x->Tinv, w.a.pinv, 1, kInvPlanes, v2A ? w.a.fsi : nullptr, 0, 4},
-                                 {x->Tinv, w.b.pfwd, 0, kFwdPlanes, f16B ? w.b.fs : nullptr, v2B ? 1 : 0, v2B ? 4 : 14},
+                                 {x->Tinv, w.b.pfwd, 0, v2B ? v2_fwd_parts(K) : f16B ? 2 : kFwdPlanes, f16B ? w.b.fs : nullptr, v2B ? 1 : 0, v2B ? 4 : 14},
                                  {x->T, w.b.pinv, 0, kInvPlanes, v2B ? w.b.fsi : nullptr, 0, 4}};
     if ((rc = launch_split_planes_multi(req, 4, K, nb, st, w.hdrA, pa.nslot + pb.nslot))) return rc;
   }
@@ -1237,7 +1248,7 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
     set_prepared(&b, B, CAFEQ_AXIS_ROW);
     a.rec = qa.two ? w.a.rec : nullptr;
     b.rec = qb.two ? w.b.rec : nullptr;
-    if ((rc = launch_loss_prepared_pair(ga.Gk, a, b, st))) return rc;
+    if ((rc = launch_loss_prepared_pair(K, ga.Gk, a, b, st))) return rc;
   } else if ((rc = run_core(K, CAFEQ_AXIS_COL, ga, a, w.a.rec, w.a.grec, qa.two, st, v2A ? A : nullptr, w.a.rec_mm,
                             w.a.grec_mm))) {
     return rc;

@@ -56,13 +56,19 @@ size_t core_lds_bytes_k128(int G, bool do_grad);
 size_t core_lds_bytes_k256(int G, bool do_grad);
 int device_cu_count();
 
-// loss_v2.hip: loss pass over prepared weights (128 x 128 blocks, groups up to 128)
+// loss_v2.hpp: loss pass over prepared weights (blocks of 32, 64 and 128, groups up to 128)
 // header (||W||^2), per-line factors, the loss pass's tiles, their partial sums, the gradient pass's tiles; for matrices
 // transformed along their rows also the weights as they are, line by line: [nseg][nlp][128]
 struct PreparedLayout { int64_t nlp, nseg, ntiles; size_t off_lscale, off_planes, off_partial, off_gtiles, off_lines, bytes; };
 // 16-bit parts per weight in the prepared copies: two for float32, one for bfloat16, whose eight significant bits one
 // float16 (loss pass) or bfloat16 (gradient pass) holds -- its second part was zeros, half the bytes of both passes.
 __host__ __device__ constexpr int prepared_parts(int dtype) { return dtype == CAFEQ_BF16 ? 1 : 2; }
+// Float16 parts of the loss pass's forward operand (T of member A, T^-1 of member B) and of the rounding error.  Shorter sums
+// round less often, so that what the operands themselves lose shows: with two parts and three products blocks of 32 were
+// 7.0e-8 (group maxima against float64, root mean square) where six bfloat16 products are 6.4e-8; blocks of 64 are 8.7e-8
+// against 9.7e-8.  One part of the error leaves the l2 proxy of blocks of 32 and 64 2e-6 off, two parts 1e-7, as bfloat16's two.
+__host__ __device__ constexpr int v2_fwd_parts(int K) { return K == 32 ? 3 : 2; }
+__host__ __device__ constexpr int v2_err_parts(int K) { return K == 128 ? 1 : 2; }
 PreparedLayout prepared_layout(int64_t nlines, int64_t naxis, int dtype, int axis);
 int launch_prepare(const cafeq_mat* W, int axis, void* prepared, hipStream_t st);
 // gradient pass over prepared weights (blocks of 128; grad_v2.hip): p.prep_gtiles, p.rec, p.grp as launch_grad_pass
@@ -91,18 +97,22 @@ size_t grad_gather_starts(int K, int grp, int64_t naxis);
 // la: the call's loss reduction; va (single matrices; may be null): the middle factor of the rho path, both in the same launches
 struct VArgs;   // mmid.hpp
 int launch_grad_gather(int K, const GradGatherJob* jobs, int n, const LossArgs& la, const VArgs* va, hipStream_t st);
-int launch_loss_v2(int G, int axis, const CoreParams& p, hipStream_t st);
-int launch_loss_prepared(int G, int axis, const CoreParams& p, hipStream_t st);   // ... with the caller's timing events
+int launch_loss_v2(int K, int G, int axis, const CoreParams& p, hipStream_t st);
+int launch_loss_prepared(int K, int G, int axis, const CoreParams& p, hipStream_t st);   // ... with the caller's timing events
 // both members of a pair in one launch (loss_v2.hip), plain and with the caller's timing events
-int launch_loss_v2_pair(int G, const CoreParams& pa, const CoreParams& pb, hipStream_t st);
-int launch_loss_prepared_pair(int G, const CoreParams& pa, const CoreParams& pb, hipStream_t st);
+int launch_loss_v2_pair(int K, int G, const CoreParams& pa, const CoreParams& pb, hipStream_t st);
+int launch_loss_v2_k32(int G, int axis, const CoreParams& p, hipStream_t st);
+int launch_loss_v2_k64(int G, int axis, const CoreParams& p, hipStream_t st);
+int launch_loss_v2_pair_k32(int G, const CoreParams& pa, const CoreParams& pb, hipStream_t st);
+int launch_loss_v2_pair_k64(int G, const CoreParams& pa, const CoreParams& pb, hipStream_t st);
+int launch_loss_prepared_pair(int K, int G, const CoreParams& pa, const CoreParams& pb, hipStream_t st);
 
 // aux_kernels.hip
 // fscale != null: two float16 planes of the block scaled by a power of two; fscale[block] = the factor back.
 // natural: a lane's eight inputs of an MFMA step are consecutive (16c + 8h + 0..7: operands read as prepared
 // 16-byte vectors) instead of two runs of four (16c + 8u + 4h + e: operands read as float4 from float32 lines
 // and the accumulator registers of the inverse transform).
-// texp: a float16 job scales the block's largest magnitude into [2^texp, 2^(texp+1)).
+// nplanes: a float16 job writes two parts, or three.  texp: a float16 job scales the block's largest magnitude into [2^texp, 2^(texp+1)).
 struct SplitRequest { const float* src; uint16_t* dst; int trans, nplanes; float* fscale = nullptr; int natural = 0; int texp = 14; };
 int launch_split_planes(const float* src, int K, int nb, int trans, int nplanes, uint16_t* dst, hipStream_t st);
 // squared row / column norms of the blocks of P, and (rG != null; rho_groups_inline) their sums over groups of G indices

@@ -37,7 +37,8 @@ __device__ __forceinline__ void reduce_losses_body(const LossArgs& a, double* re
     __syncthreads();
     v0 = v1 = v2 = v3 = 0;
     vmax = -INFINITY;
-#pragma unroll 2
+    // (not all of a large workgroup's sums at once: 80 registers)
+#pragma unroll NW <= 4 ? NW : 2
     for (int k = 0; k < NW; ++k) {
       v0 += red[k]; v1 += red[NW + k]; v2 += red[2 * NW + k]; v3 += red[3 * NW + k];
       vmax = fmax(vmax, red[4 * NW + k]);

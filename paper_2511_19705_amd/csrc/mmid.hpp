@@ -85,10 +85,11 @@ __device__ __forceinline__ void build_mmid_body(const VArgs& a, const int b, con
   }
 }
 
-inline VArgs mmid_args(const CoreParams& ploss, int K, int G, const float* P, int scale_rows, float* Mmid) {
+// L: axis indices per segment of the loss pass
+inline VArgs mmid_args(const CoreParams& ploss, int K, int L, int G, const float* P, int scale_rows, float* Mmid) {
   VArgs a;
   a.slot_hdr = ploss.slot_hdr; a.mt_per_seg = ploss.mt_per_seg; a.n_mt = ploss.n_mt; a.nwg = ploss.nwg;
-  a.K = K; a.L = K > G ? K : G; a.G = G; a.rep = ploss.rep; a.beta = ploss.beta; a.P = P;
+  a.K = K; a.L = L; a.G = G; a.rep = ploss.rep; a.beta = ploss.beta; a.P = P;
   a.scale_rows = scale_rows; a.Mmid = Mmid;
   return a;
 }

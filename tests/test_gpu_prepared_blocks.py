@@ -1,0 +1,62 @@
+"""GPU parity of the loss pass over prepared weights for blocks of 32 and 64: several blocks share a segment of 128, each in
+units of its own; groups inside a block and across blocks; ragged line counts; codes, scales and losses against the oracle
+(bounds of tests/parity.py, ties by the transform's rounding).  Gradients: tests/test_gpu_gather.py."""
+import numpy as np
+import pytest
+
+from oracle import cafeq_oracle as O
+from paper_2511_19705_amd import workloads as WL
+from tests import parity
+from tests.test_gpu_prepared import _check_single_prepared
+from tests.test_gpu_single import _case, _dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    from paper_2511_19705_amd import cafeq
+    return torch, cafeq
+
+
+# 296 lines: a macro-tile of 256 and a ragged one; rep 2 and 4: a segment's row-blocks share transform blocks
+@pytest.mark.parametrize("k,group", [(32, 32), (32, 64), (32, 128), (64, 32), (64, 64), (64, 128)])
+@pytest.mark.parametrize("axis,rep", [(O.COL, 1), (O.ROW, 1), (O.ROW, 2), (O.ROW, 4)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_codes_scales_losses(env, k, group, axis, rep, bf16):
+    W, T, P = _case(axis, 296, 512, k, rep, 3100 + k + group)
+    _check_single_prepared(env, W, T, P, 3 if bf16 else 4, group, axis, rep, bf16=bf16, want_grad=False)
+    _check_single_prepared(env, W, T, P, 2, group, axis, rep, bf16=bf16, want_grad=False, want_codes=False)
+
+
+@pytest.mark.parametrize("k,group", [(32, 32), (32, 128), (64, 64), (64, 128)])
+@pytest.mark.parametrize("spread", [2.0, 2.0 ** 12, 2.0 ** 30])
+def test_blocks_of_different_magnitude(env, k, group, spread):
+    W, T, P = _case(O.COL, 200, 256, k, 1, 3200 + k)
+    f = np.where(np.arange(T.shape[0]) % 2 == 0, 1.0, 1.0 / spread).astype(np.float32)[:, None, None]
+    T = T * f
+    P = O.block_inverse(T).astype(np.float32)
+    _check_single_prepared(env, W, T, P, 4, group, O.COL, 1, want_grad=False)
+
+
+@pytest.mark.parametrize("k,group,rep", [(32, 128, 1), (64, 64, 1), (64, 128, 2)])
+def test_pair_with_codes(env, k, group, rep):
+    torch, cafeq = env
+    A, B, T = WL.small_pair(296, 512 if rep == 1 else 256, k, rep, 3300 + k + group, eps=0.05)
+    P = O.block_inverse(T).astype(np.float32)
+    Ad, Bd = _dev(torch, A), _dev(torch, B)
+    prep = (cafeq.prepare_weights(Ad, O.COL), cafeq.prepare_weights(Bd, O.ROW))
+    losses, _, outs = cafeq.dual_proxy_loss_fwd_bwd(Ad, Bd, _dev(torch, T), _dev(torch, P), 3, group, rep, 5.0, False, True,
+                                                    prepared=prep)
+    torch.cuda.synchronize()
+    ref = O.dual_lse(A, B, T, P, 3, group, rep, 5.0)
+    for i, name in enumerate(("errU_sq", "errV_sq", "l2A_sq", "l2B_sq", "lse")):
+        parity.check_scalar(float(losses[i]), ref[name], what=name)
+    cu, su, cv, sv = [x.cpu().numpy() for x in outs]
+    cu_ref, su_ref, _ = O.rtn_sym(ref["U"], 3, group, O.COL)
+    cv_ref, sv_ref, _ = O.rtn_sym(ref["V"], 3, group, O.ROW)
+    parity.check_scales(su, su_ref)
+    parity.check_scales(sv, sv_ref)
+    parity.check_codes(cu, cu_ref, ref["U"], su_ref, O.COL, group)
+    parity.check_codes(cv, cv_ref, ref["V"], sv_ref, O.ROW, group)
