@@ -24,7 +24,10 @@ namespace cafeq {
 namespace {
 
 constexpr int kGgThreads = 256, kGgWaves = kGgThreads / kWave;
-constexpr int kGgFlight = 8;                         // a wave requests this many lines at a time, one request ahead of its use
+constexpr int kGgFlight = 8;                         // a wave requests this many lines at a time ...
+// ... and has this many requests in flight (registers: K / 64 a line.  20 blocks of 64, a wave's 50 to 500 lines: 2 deep 37 us, 8 deep 29;
+// 27B-shaped pair in bfloat16 147, 142)
+constexpr int gather_ring(int K) { return K == 256 ? 2 : K == 128 ? 3 : 8; }
 constexpr int kGsThreads = 512, kGsWaves = kGsThreads / kWave;
 constexpr int kGsFlight = 9;                         // records in flight per lane: those of 4608 lines stay in registers
 constexpr int kGsList = 5120;                        // entries of a list that is put together in LDS (40 KB)
@@ -275,36 +278,38 @@ __device__ __forceinline__ int gather_share(const uint2* __restrict__ sorted, co
     if (lane == 0) prev = before;
     const uint64_t turn = __ballot(row != prev);      // entries that begin another row
     before = __builtin_amdgcn_readlane(row, 63);
-    Raw<K, E> v[2][kGgFlight];
-    auto request = [&](int buf, int g) {
+    // eight lines at a time, the requests of RING of them ahead of their use
+    constexpr int RING = gather_ring(K);
+    Raw<K, E> v[RING][kGgFlight];
+    auto request = [&](int grp) {
 #pragma unroll
       for (int u = 0; u < kGgFlight; ++u) {
         // (a scalar base and the lane's offset, kept apart: no address to compute per lane)
-        uint64_t at = lines + (uint64_t(uint32_t(__builtin_amdgcn_readlane(off_hi, g + u))) << 32 |
-                               uint32_t(__builtin_amdgcn_readlane(off_lo, g + u)));
+        const int i = grp * kGgFlight + u;
+        uint64_t at = lines + (uint64_t(uint32_t(__builtin_amdgcn_readlane(off_hi, i))) << 32 |
+                               uint32_t(__builtin_amdgcn_readlane(off_lo, i)));
         uint32_t own = loff;
         asm("" : "+s"(at), "+v"(own));
         const auto src = reinterpret_cast<GlobalPtr<typename Raw<K, E>::V>>(reinterpret_cast<GlobalPtr<unsigned char>>(at) + own);
-        if constexpr (ONCE) v[buf][u].v = __builtin_nontemporal_load(src);
-        else v[buf][u].v = *src;
+        if constexpr (ONCE) v[grp % RING][u].v = __builtin_nontemporal_load(src);
+        else v[grp % RING][u].v = *src;
       }
     };
-    auto consume = [&](int buf, int g) {
-      const uint32_t turns = __builtin_amdgcn_readfirstlane(uint32_t(turn >> g));
+    auto consume = [&](int grp) {
+      const uint32_t turns = __builtin_amdgcn_readfirstlane(uint32_t(turn >> (grp * kGgFlight)));
 #pragma unroll
       for (int u = 0; u < kGgFlight; ++u) {
-        if (turns >> u & 1) { put(); cur = __builtin_amdgcn_readlane(row, g + u); }
-        const float c = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(coef), g + u));
+        const int i = grp * kGgFlight + u;
+        if (turns >> u & 1) { put(); cur = __builtin_amdgcn_readlane(row, i); }
+        const float c = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(coef), i));
 #pragma unroll
-        for (int x = 0; x < NX; ++x) acc[x] = fmaf(c, v[buf][u].get(x), acc[x]);
+        for (int x = 0; x < NX; ++x) acc[x] = fmaf(c, v[grp % RING][u].get(x), acc[x]);
       }
     };
-    request(0, 0);
-    for (int g = 0; g < cnt; g += 2 * kGgFlight) {
-      request(1, g + kGgFlight);
-      consume(0, g);
-      if (g + 2 * kGgFlight < cnt) request(0, g + 2 * kGgFlight);
-      if (g + kGgFlight < cnt) consume(1, g + kGgFlight);
+#pragma unroll
+    for (int g = 0; g < 64 / kGgFlight + RING - 1; ++g) {
+      if (g * kGgFlight < cnt && g < 64 / kGgFlight) request(g);
+      if (g >= RING - 1 && (g - RING + 1) * kGgFlight < cnt) consume(g - RING + 1);
     }
   }
   put();
