@@ -521,18 +521,27 @@ __global__ __launch_bounds__(256) void bgemm_mfma_kernel(const float* __restrict
 // the second's B operand (lanes along a column) without bank conflicts; G goes from memory straight into the
 // registers of the wave that multiplies by it; X passes through LDS transposed.
 // (Blocks of 64: one workgroup of four waves per block, the same scheme.)
+// XP: parts in which X passes through LDS, the waves of one column tile at a time.  Whole, the workgroup takes 100 KB and has the
+// compute unit to itself; in four parts 75 KB and 128 registers, so that two share it, the same sums in the same order.  The
+// two workgroups of a block sit behind one L2 (fetched per launch at 112 blocks 37.7 -> 23.0 MB).  Bound: latency of load, LDS
+// and the chain of matrix instructions (7.8 us of them a workgroup).  288 blocks (three rounds of workgroups as one a
+// compute unit) 55.7 -> 49.6 us in parts, -> 44.6 with the order; 112 blocks 19.5 -> 17.7 by the order alone.
 constexpr int kChainLdX = 33;
-constexpr size_t chain_lds(int K) { return size_t(K * (K + 1) + 2 * K * kChainLdX) * sizeof(float); }
-template <int K>
-__global__ __launch_bounds__(4 * K) void bgemm_chain_kernel(const float* __restrict__ P, const float* __restrict__ G,
+constexpr size_t chain_lds(int K, int XP) { return size_t(K * (K + 1) + 2 * (K / XP) * kChainLdX) * sizeof(float); }
+template <int K, int XP>
+__global__ __launch_bounds__(4 * K, XP > 1 ? 4 : 1) void bgemm_chain_kernel(const float* __restrict__ P, const float* __restrict__ G,
                                                             float* __restrict__ C, float alpha, float beta,
                                                             const UpdateHook up) {
   static_assert(K == 64 || K == 128, "slices of 64 rows");
+  static_assert(XP == 1 || XP == K / 32, "a part of X is what the waves of one column tile hold");
   constexpr int kChainLdP = K + 1, NT = 4 * K, WJ = K / 32, SL = K / 64;   // threads, column tiles, slices per block
   extern __shared__ __align__(16) float csm[];
   float* sp = csm;                          // P[r][c]
-  float* sx = csm + K * kChainLdP;          // [2 row halves][l][32 rows]: X^T of the workgroup's slice
-  const int b = blockIdx.x / SL, i0 = (blockIdx.x % SL) * 64;
+  float* sx = csm + K * kChainLdP;          // [2 row halves][l][32 rows]: X^T of the workgroup's slice, or of one part of l
+  // the slices of a block eight workgroups apart, i.e. behind one L2, which then fetches P and G once
+  const unsigned grp = blockIdx.x / (8 * SL), in = blockIdx.x % (8 * SL);
+  const bool whole = (grp + 1) * 8 * SL <= gridDim.x;
+  const int b = grp * 8 + (whole ? in % 8 : in / SL), i0 = (whole ? in / 8 : in % SL) * 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ln = lane & 31, h = lane >> 5;
   const int wi = wave / WJ, wj = wave % WJ;
   const float* Pb = P + size_t(b) * K * K;
@@ -570,11 +579,14 @@ __global__ __launch_bounds__(4 * K) void bgemm_chain_kernel(const float* __restr
 #pragma unroll
     for (int t = 0; t < K / 2; ++t) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[2 * t * kChainLdP], g[t], acc, 0, 0, 0);
   }
-  {
-    float* xw = sx + wi * (K * kChainLdX) + (wj * 32 + ln) * kChainLdX;
+  constexpr int KX = K / XP;                // rows of X^T in LDS at a time
+  auto put_x = [&](const floatx16& x) __attribute__((always_inline)) {
+    float* xw = sx + wi * (KX * kChainLdX) + ((XP == 1 ? wj * 32 : 0) + ln) * kChainLdX;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) xw[8 * (v / 4) + 4 * h + (v % 4)] = acc[v];
-  }
+    for (int v = 0; v < 16; ++v) xw[8 * (v / 4) + 4 * h + (v % 4)] = x[v];
+  };
+  const floatx16 x = acc;
+  if (XP == 1 || wj == 0) put_x(x);
   // (in flight under the second product)
   UpdateOld was[16];
   if (up.T) {
@@ -588,11 +600,18 @@ __global__ __launch_bounds__(4 * K) void bgemm_chain_kernel(const float* __restr
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
   {
     // Y[i][j] = sum_l X[i][l] P[j][l]
-    const float* pa = sx + wi * (K * kChainLdX) + h * kChainLdX + ln;
+    const float* pa = sx + wi * (KX * kChainLdX) + h * kChainLdX + ln;
     const float* pb = sp + (wj * 32 + ln) * kChainLdP + h;
+    for (int p = 0; p < XP; ++p) {
+      if (p > 0) {
+        __syncthreads();                    // (the part before is still being read)
+        if (wj == p) put_x(x);
+        __syncthreads();
+      }
 #pragma unroll 8
-    for (int t = 0; t < K / 2; ++t)
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[2 * t * kChainLdX], pb[2 * t], acc, 0, 0, 0);
+      for (int t = 0; t < KX / 2; ++t)
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[2 * t * kChainLdX], pb[p * KX + 2 * t], acc, 0, 0, 0);
+    }
   }
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
@@ -825,20 +844,27 @@ int launch_bgemm_chain(const float* P, const float* G, float* x1, float* C, int 
   const UpdateHook up = hook ? *hook : UpdateHook{};
   static std::atomic<bool> attr_set{false};
   if (!attr_set) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(bgemm_chain_kernel<128>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, int(chain_lds(128))) != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void*>(bgemm_chain_kernel<64>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, int(chain_lds(64))) != hipSuccess)
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(bgemm_chain_kernel<128, 1>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, int(chain_lds(128, 1))) != hipSuccess ||
+        hipFuncSetAttribute(reinterpret_cast<const void*>(bgemm_chain_kernel<128, 4>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, int(chain_lds(128, 4))) != hipSuccess ||
+        hipFuncSetAttribute(reinterpret_cast<const void*>(bgemm_chain_kernel<64, 1>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, int(chain_lds(64, 1))) != hipSuccess)
       return CAFEQ_ERR_LAUNCH;
     attr_set = true;
   }
   switch (K) {
     case 32: hipLaunchKernelGGL(bgemm_chain32_kernel, dim3(unsigned(nb)), dim3(256), 0, st, P, G, C, alpha, beta, up); break;
     case 64:
-      hipLaunchKernelGGL(bgemm_chain_kernel<64>, dim3(unsigned(nb)), dim3(256), chain_lds(64), st, P, G, C, alpha, beta, up);
+      hipLaunchKernelGGL((bgemm_chain_kernel<64, 1>), dim3(unsigned(nb)), dim3(256), chain_lds(64, 1), st, P, G, C, alpha, beta, up);
       break;
     case 128:
-      hipLaunchKernelGGL(bgemm_chain_kernel<128>, dim3(unsigned(nb) * 2), dim3(512), chain_lds(128), st, P, G, C, alpha, beta, up);
+      // more workgroups than compute units: the form of which two fit one (288 blocks 55.7 -> 49.6 us); fewer gain nothing from
+      // a second place and would wait at six more barriers
+      if (2 * int64_t(nb) > device_cu_count())
+        hipLaunchKernelGGL((bgemm_chain_kernel<128, 4>), dim3(unsigned(nb) * 2), dim3(512), chain_lds(128, 4), st, P, G, C, alpha, beta, up);
+      else
+        hipLaunchKernelGGL((bgemm_chain_kernel<128, 1>), dim3(unsigned(nb) * 2), dim3(512), chain_lds(128, 1), st, P, G, C, alpha, beta, up);
       break;
     default: return CAFEQ_ERR_UNSUPPORTED;
   }
