@@ -226,11 +226,10 @@ def pair_workload(args, secondary=True):
             "bound": "hbm", "achieved": 4.0 * g_el / g_s / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": 4.0 * g_el / g_s / 1e9 / HBM_PEAK_GBS,
             "traffic": measured_traffic("loss_prepared_c3_pair.md", "gradient_traffic_bytes_per_launch"),
-            "kernel": "grad_v2_owner_kernel (gradient pass over prepared weights, one workgroup per member and block)",
+            "kernel": "sort_records_kernel + grad_gather_kernel (gradient pass by records: lines gathered row by row of the block)",
             "launches": len(gd), "launches_in_timed_region": int(gtimer.table.seen),
             "weight_elements_per_launch": g_el, "avg_launch_us": g_s * 1e6,
-            "algorithmic_bytes_per_element": 4, "algorithmic_flop_per_element": 2 * k,
-            "executed_part_product_tflops": 3.0 * 2.0 * k * g_el / g_s / 1e12}
+            "algorithmic_bytes_per_element": 4, "algorithmic_flop_per_element": 2}
     # what this machine's memory system delivers to plain streaming kernels on data that no cache holds (the published
     # 8 TB/s stays the roofline's peak; these two figures say how far any kernel gets towards it here)
     probe = memory_probe(torch, dev, cafeq)
