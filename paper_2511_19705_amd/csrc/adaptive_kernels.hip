@@ -743,7 +743,8 @@ __global__ __launch_bounds__(256) void bgemm_f64mfma_kernel(const AT* __restrict
   __shared__ double sa[32][LC + 2];   // [i][l]   (row strides chosen so that the operand reads of 32 lanes cover
   __shared__ double sb[LC][80];       // [l][j]    all banks once)
   const int tpc = K / 64, tpr = K / 32;
-  const int b = blockIdx.x / (tpr * tpc), tile = blockIdx.x % (tpr * tpc);
+  int b, tile;
+  block_and_part(blockIdx.x, tpr * tpc, gridDim.x, &b, &tile);
   const int i0 = (tile / tpc) * 32, j0 = (tile % tpc) * 64;
   bool twice = false;
   if constexpr (STEP || EPI == kF64ResidualAgain) {

@@ -442,7 +442,8 @@ __global__ __launch_bounds__(256) void bgemm_mfma_kernel(const float* __restrict
   float* sa = bsm;
   float* sb = bsm + CH * LD;
   const int tpr = K / 64;
-  const int b = blockIdx.x / (tpr * tpr), tile = blockIdx.x % (tpr * tpr);
+  int b, tile;
+  block_and_part(blockIdx.x, tpr * tpr, gridDim.x, &b, &tile);
   const int i0 = (tile / tpr) * 64, j0 = (tile % tpr) * 64;
   const float* Ab = A + size_t(b) * K * K;
   const float* Bb = B + size_t(b) * K * K;
@@ -538,10 +539,9 @@ __global__ __launch_bounds__(4 * K, XP > 1 ? 4 : 1) void bgemm_chain_kernel(cons
   extern __shared__ __align__(16) float csm[];
   float* sp = csm;                          // P[r][c]
   float* sx = csm + K * kChainLdP;          // [2 row halves][l][32 rows]: X^T of the workgroup's slice, or of one part of l
-  // the slices of a block eight workgroups apart, i.e. behind one L2, which then fetches P and G once
-  const unsigned grp = blockIdx.x / (8 * SL), in = blockIdx.x % (8 * SL);
-  const bool whole = (grp + 1) * 8 * SL <= gridDim.x;
-  const int b = grp * 8 + (whole ? in % 8 : in / SL), i0 = (whole ? in / 8 : in % SL) * 64;
+  int b, slice;
+  block_and_part(blockIdx.x, SL, gridDim.x, &b, &slice);
+  const int i0 = slice * 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ln = lane & 31, h = lane >> 5;
   const int wi = wave / WJ, wj = wave % WJ;
   const float* Pb = P + size_t(b) * K * K;

@@ -100,4 +100,14 @@ __device__ __forceinline__ uint32_t pack4(float q0, float q1, float q2, float q3
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// Workgroup `id` of `total` = blocks * parts -> (block, part): the parts of a block eight apart, i.e. behind one L2 (workgroups go
+// round the eight XCDs in turn), which then fetches what they share once.
+// Adam on the 9B-shaped (V, O) pair, blocks of 256 as 16 or 32 tiles: 2785 -> 2767 us; 112 blocks of 128 in halves: 19.5 -> 17.7 us a launch.
+__device__ __forceinline__ void block_and_part(unsigned id, unsigned parts, unsigned total, int* block, int* part) {
+  const unsigned grp = id / (8 * parts), in = id % (8 * parts);
+  const bool whole = (grp + 1) * 8 * parts <= total;
+  *block = int(grp * 8 + (whole ? in % 8 : in / parts));
+  *part = int(whole ? in / 8 : in % parts);
+}
+
 }  // namespace cafeq
