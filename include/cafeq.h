@@ -236,7 +236,8 @@ int cafeq_prepare_weights(const cafeq_mat* W, int axis, void* prepared, void* st
  *               for per-group scales (a_G: group absmax of Z, rho_j: squared norm of the
  *               row (AXIS_COL) / column (AXIS_ROW) j of Tinv)
  *   gradT[nb][k][k] (may be NULL: forward only) = d L_sur / d T with Tinv = T^-1,
- *               absmax differentiated at its arg-max element.
+ *               absmax differentiated at its arg-max element.  A weight that is infinite or not a number leaves the
+ *               losses not finite and its block's gradient not a number at its input, for every output.
  *   codes / scales (may be NULL): Q(Z) as in cafeq_rtn_quantize.
  * Groups: 32, 64, 128 or 256 elements (max(group, k) must divide the axis), or any longer group that is a
  * multiple of k and divides the axis -- group = 0, the whole channel (the per-channel setting of the paper's

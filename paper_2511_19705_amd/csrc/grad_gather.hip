@@ -9,13 +9,11 @@
 // reduction, which a pair's coefficients wait for, and a single matrix' middle factor ride in it.
 // grad_gather_kernel: a workgroup owns a few rows of a unit, its waves take equal shares of the rows' entries, whatever the
 // distribution of the arg-max over the rows is.  A wave works on one line at a time -- row, coefficient and address in scalar
-// registers, eight to sixteen lines in flight -- and a row that several waves share is put together in the waves' order.
+// registers, sixteen to 64 lines in flight (gather_ring) -- and a row that several waves share is put together in the waves' order.
 // No partials: the rows leave in their final place.  The lines come from the matrix itself (columns: a line's inputs lie
 // side by side) or from the line-major copy among the prepared weights (rows).
 //
 // Bound: memory, 4 K (2 K) bytes per line and block, once.
-#include <atomic>
-
 #include "cafeq_internal.hpp"
 #include "loss_reduce.hpp"
 #include "mmid.hpp"
@@ -316,6 +314,37 @@ __device__ __forceinline__ int gather_share(const uint2* __restrict__ sorted, co
   return first;
 }
 
+// The products with S's zeros that the gather leaves out matter where a weight is infinite or not a number: there they are not
+// numbers, in all rows of the block.  Such a weight spoils the member's sum of squared rounding errors -- every transformed
+// value of its line and block is not a number -- which the launch before this one has reduced: a finite sum rules them out,
+// and only otherwise are the block's lines read once more, whole.
+// (The kernel's arguments are fetched anew, block and member worked out anew: kept until here -- the compiler would -- they take
+// blocks of 256 from 94 registers to 97, i.e. a wave per SIMD.)
+template <int K>
+__device__ __forceinline__ void spoiled_inputs(float* tile) {
+  unsigned id = blockIdx.x;
+  auto args = (const __attribute__((address_space(4))) GatherArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(id), "+s"(args));
+  const auto& a = *args;
+  const int mi = (a.nmem > 1 && id >= a.m[0].nwg) ? 1 : 0;
+  if (fabsf(a.la.losses[a.loss_kind == kLossSur ? 1 : mi]) < INFINITY) return;   // (uniform)
+  const auto& M = a.m[mi];
+  const int b = int((mi ? id - a.m[0].nwg : id) / unsigned(K / M.rows)), m = int(threadIdx.x) % K;
+  bool bad = false;
+  for (int q = b * M.rep; q < (b + 1) * M.rep; ++q) {
+    const int64_t ax = int64_t(q) * K + m, at = (ax >> 7) * M.seg_stride + (ax & 127);
+#pragma unroll 1
+    for (int64_t line = int(threadIdx.x) / K; line < M.nlines; line += kGgThreads / K) {
+      const int64_t i = at + line * M.line_stride;
+      const float w = M.bf16 ? bf16_bits_to_f32(static_cast<const uint16_t*>(M.W)[i]) : static_cast<const float*>(M.W)[i];
+      bad |= !(fabsf(w) < INFINITY);
+    }
+  }
+  if (bad)
+    for (int r = 0; r < M.rows; ++r) tile[r * gather_row_floats(K) + m] = NAN;
+  __syncthreads();
+}
+
 template <int K, bool ONCE>
 __global__ __launch_bounds__(kGgThreads) void grad_gather_kernel(const GatherArgs a) {
   constexpr int NX = lane_inputs<K>(), LDT = gather_row_floats(K), LW = K / 4;
@@ -364,6 +393,7 @@ __global__ __launch_bounds__(kGgThreads) void grad_gather_kernel(const GatherArg
     }
   }
   __syncthreads();
+  spoiled_inputs<K>(tile);
   float* dst = M.out + size_t(b) * K * K;
   if (M.transpose_out) {
     const int rq = rows / 4;
