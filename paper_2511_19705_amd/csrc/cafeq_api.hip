@@ -161,12 +161,11 @@ float beta_for(const cafeq_quant_cfg* cfg, const QGrid& g) {
 }
 // The loss pass over prepared weights (loss_v2.hip): one workgroup of eight waves per compute unit,
 // macro-tiles of 256 lines.
-// on_the_way: the loss pass forms the gradient, too (blocks of 32 and 64 whose gradient does not come from records).
 // codes_along_rows: it writes codes or scales of a matrix transformed along its rows (byte stores).  Blocks of 32 and 64 with
 // float32 weights and groups of 32 or 64 have no registers for that next to two parts of everything: 9216 x 2304 48 to 58 us
 // the general way, 58 to 69 this way (groups of 128 59 and 50).
-bool v2_eligible(const cafeq_mat* W, int K, const GroupPlan& gp, const cafeq_quant_cfg* cfg, bool on_the_way, bool codes_along_rows) {
-  if (K < 128 && (on_the_way || (codes_along_rows && gp.Gk < 128 && W->dtype == CAFEQ_F32))) return false;
+bool v2_eligible(const cafeq_mat* W, int K, const GroupPlan& gp, const cafeq_quant_cfg* cfg, bool codes_along_rows) {
+  if (K < 128 && codes_along_rows && gp.Gk < 128 && W->dtype == CAFEQ_F32) return false;
   return W->prepared != nullptr && K <= 128 && gp.Gk <= 128 && gp.gspan == 1 && cfg->bits <= 4 && !is_minmax(cfg);
 }
 // share: the matrix gets 1 / share of the chip's compute units (2: the members of a pair that run in one launch)
@@ -180,6 +179,46 @@ void make_v2_plan(CorePlan* pl, int share = 1) {
   pl->nwg = int(nwg);
   pl->nslot = pl->nwg + pl->nseg;
 }
+// rounds of workgroups that the loss pass takes over prepared weights and in the general kernel
+bool v2_rounds(int K, int G, int64_t nlines, int64_t naxis, int share, int64_t* here, int64_t* there) {
+  CorePlan pl;
+  if (make_plan(K, G, nlines, naxis, &pl, false)) return false;
+  *there = (pl.n_mt + pl.nwg - 1) / pl.nwg;
+  make_v2_plan(&pl, share);
+  *here = (pl.n_mt + pl.nwg - 1) / pl.nwg;
+  return true;
+}
+// Whether the loss pass over prepared weights is the faster one (blocks of 128: always; blocks of 32 and 64: not where there
+// are few of its tiles).  Both kernels take as long as their rounds of workgroups do: one a compute unit and tiles of 256 lines x
+// 128 indices here, two a unit and 128 lines x one segment of max(K, G) indices there.  Losses alone, the general kernel's
+// time / this one's in us: 1152 x 512 (two rounds here, one there) at k = 32, groups of 32 11 / 22 and at k = 64, groups of
+// 64 13 / 20; 2304 x 2304 (two and two) at k = 32, groups of 32 18 / 22, k = 64, groups of 64 21 / 21, of 128 31 / 20; 2304 x 9216
+// at k = 32, groups of 32 (three and eleven) 42 / 42; 36864 x 4608 (21 and 81) 270 / 177, at k = 64 (and 41) 293 / 178.
+bool v2_pays(const cafeq_mat* W, int K, const GroupPlan& gp, int64_t nlines, int64_t naxis, bool out, bool along_rows) {
+  if (K == 128) return true;
+  int64_t here, there;
+  if (!v2_rounds(K, gp.Gk, nlines, naxis, 1, &here, &there)) return false;
+  const bool bf16 = W->dtype == CAFEQ_BF16, more = here > 1;
+  // (two tiles of 256 for 304 lines: 304 x 36864 at k = 32, groups of 64 44 / 50, in bfloat16 46 / 44)
+  if (K == 32 && !bf16 && 2 * ((nlines + 255) / 256 * 256) > 3 * nlines) return false;
+  switch (std::max(K, gp.Gk)) {
+    case 128: return there >= 1 + int(more || (out && along_rows && !bf16));
+    case 64: return there >= 2 + int(more && (K == 32 || !bf16 || out || nlines < 512));
+    // (groups of 32: the vector phase's time is in the groups, of which neither kernel has fewer)
+    default: return there >= (bf16 && !(out && along_rows) ? 3 + int(more) : 3 * here + 1);
+  }
+}
+// The same for a pair whose members share a launch, half of the chip each, against two launches: 600 x 512 at k = 32, groups
+// of 32 18 / 24, 3584 x 512 21 / 20, 4608 x 1024 35 / 28; groups of 64 256 x 2304 22 / 28, else from 22 / 22 down.
+bool v2_pair_pays(const cafeq_mat* A, const cafeq_mat* B, int K, const GroupPlan& gp) {
+  if (std::max(K, gp.Gk) == 128) return true;
+  int64_t ha, ta, hb, tb;
+  if (!v2_rounds(K, gp.Gk, A->rows, A->cols, 2, &ha, &ta) || !v2_rounds(K, gp.Gk, B->cols, B->rows, 2, &hb, &tb)) return false;
+  const bool few = ha + hb > 2, bf16 = A->dtype == CAFEQ_BF16 && B->dtype == CAFEQ_BF16;
+  if (std::max(K, gp.Gk) == 64) return (bf16 && K == 64) || ta + tb > 2 || !few;
+  return ta + tb >= 2 + int(!bf16) + int(few);
+}
+
 // Whether the gradient can come from the arg-max records by gathering lines (grad_gather.hip): a line's inputs lie side by
 // side (columns, or rows with the prepared line-major copy) and a block meets one group per line, or is one of 256, whose
 // product with the matrix of zeros (grad_core.hpp) runs one wave per SIMD.  Gradient passes with their reductions, product /
@@ -1065,8 +1104,9 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
   const bool asym = is_minmax(cfg);
   // (Gradient descent at two bits takes steps nine times those at three and amplifies any change of rounding: of 20 small loops
   // a few end 1e-4 to 4e-3 elsewhere for a gradient that is ten times closer to float64's.  They keep the pass they had.)
+  bool v2 = v2_eligible(W, K, gp, cfg, !col && (codes || scales)) && v2_pays(W, K, gp, nlines, naxis, codes || scales, !col);
   const bool gather = gather_single(K, gp, has_lines(W, cfg->axis), asym, nlines * naxis) && !(hook && cfg->bits == 2);
-  const bool v2 = v2_eligible(W, K, gp, cfg, grad && !gather, !col && (codes || scales));
+  if (K < 128 && grad && !gather) v2 = false;   // (the loss pass forms the gradient on its way)
   PassPlans pp;
   rc = plan_passes(K, gp, nlines, naxis, grad, &pp, v2, asym, 1, gather);
   if (rc) return rc;
@@ -1194,11 +1234,17 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
   const bool grad = gradT != nullptr;
   const bool asym = is_minmax(cfg);
   const bool gather = gather_possible(K, ga, has_lines(A, CAFEQ_AXIS_COL)) && gather_possible(K, gb, has_lines(B, CAFEQ_AXIS_ROW));
-  const bool v2A = v2_eligible(A, K, ga, cfg, grad && !gather, false);
-  const bool v2B = v2_eligible(B, K, gb, cfg, grad && !gather, codesV || scalesV);
+  bool v2A = v2_eligible(A, K, ga, cfg, false), v2B = v2_eligible(B, K, gb, cfg, codesV || scalesV);
   // both loss passes over prepared weights in one launch, each member on half of the chip: when neither writes
   // codes or scales and both use the same group length
-  const bool pair_launch = v2A && v2B && !codesU && !scalesU && !codesV && !scalesV && ga.Gk == gb.Gk;
+  bool pair_launch = v2A && v2B && !codesU && !scalesU && !codesV && !scalesV && ga.Gk == gb.Gk;
+  if (pair_launch) {
+    v2A = v2B = pair_launch = v2_pair_pays(A, B, K, ga);
+  } else {
+    v2A = v2A && v2_pays(A, K, ga, A->rows, A->cols, codesU || scalesU, false);
+    v2B = v2B && v2_pays(B, K, gb, B->cols, B->rows, codesV || scalesV, true);
+  }
+  if (K < 128 && grad && !gather) v2A = v2B = pair_launch = false;   // (the loss passes form the gradients on their way)
   PassPlans qa, qb;
   if ((rc = plan_passes(K, ga, A->rows, A->cols, grad, &qa, v2A, asym, pair_launch ? 2 : 1, gather))) return rc;
   if ((rc = plan_passes(K, gb, B->cols, B->rows, grad, &qb, v2B, asym, pair_launch ? 2 : 1, gather))) return rc;

@@ -60,3 +60,54 @@ def test_pair_with_codes(env, k, group, rep):
     parity.check_scales(sv, sv_ref)
     parity.check_codes(cu, cu_ref, ref["U"], su_ref, O.COL, group)
     parity.check_codes(cv, cv_ref, ref["V"], sv_ref, O.ROW, group)
+
+
+# Sizes from which the pass over prepared weights is taken whatever the group (below, groups of 32 and 64 go through the general
+# kernel: tests/test_gpu_routes.py): other bits than the general kernel's, the same bounds.  3400 lines: 13 macro-tiles, a ragged one
+@pytest.mark.parametrize("k,group", [(32, 32), (32, 64), (32, 128), (64, 32), (64, 64), (64, 128)])
+@pytest.mark.parametrize("axis,rep,bf16,codes", [(O.COL, 1, False, True), (O.COL, 1, True, True), (O.ROW, 1, False, False), (O.ROW, 2, True, True),
+                                                 (O.ROW, 4, False, False)])
+def test_sizes_that_take_the_prepared_pass(env, k, group, axis, rep, bf16, codes):
+    torch, cafeq = env
+    W, T, P = _case(axis, 3400, 2048, k, rep, 3400 + k + group)
+    _check_single_prepared(env, W, T, P, 3 if bf16 else 4, group, axis, rep, bf16=bf16, want_grad=False, want_codes=codes)
+    if codes:
+        _differs_from_the_general_kernel(torch, cafeq, W, T, P, 3 if bf16 else 4, group, axis, rep, bf16)
+
+
+def _differs_from_the_general_kernel(torch, cafeq, W, T, P, bits, group, axis, rep, bf16):
+    """(in the last bits of some of the scales)"""
+    Wd = _dev(torch, W).to(torch.bfloat16 if bf16 else torch.float32)
+    a, b = (cafeq.proxy_loss_fwd_bwd(Wd, _dev(torch, T), _dev(torch, P), bits, group, axis, rep, want_grad=False, want_codes=True, prepared=p)[3]
+            for p in (cafeq.prepare_weights(Wd, axis), None))
+    assert not torch.equal(a, b)
+
+
+@pytest.mark.parametrize("k", [32, 64])
+@pytest.mark.parametrize("spread", [2.0 ** 12, 2.0 ** 30])
+def test_blocks_of_different_magnitude_take_the_prepared_pass(env, k, spread):
+    torch, cafeq = env
+    W, T, P = _case(O.COL, 3400, 2048, k, 1, 3450 + k)
+    T = T * np.where(np.arange(T.shape[0]) % 2 == 0, 1.0, 1.0 / spread).astype(np.float32)[:, None, None]
+    P = O.block_inverse(T).astype(np.float32)
+    _check_single_prepared(env, W, T, P, 4, k, O.COL, 1, want_grad=False)
+    _differs_from_the_general_kernel(torch, cafeq, W, T, P, 4, k, O.COL, 1, False)
+
+
+# member B's codes are byte stores along its rows: from two rounds of the general kernel's workgroups on
+@pytest.mark.parametrize("k,group", [(32, 128), (64, 128), (64, 64)])
+def test_large_pair_with_codes(env, k, group):
+    torch, cafeq = env
+    A, B, T = WL.small_pair(4608, 2048, k, 1, 3500 + k + group, eps=0.05)
+    P = O.block_inverse(T).astype(np.float32)
+    Ad, Bd = _dev(torch, A), _dev(torch, B)
+    prep = (cafeq.prepare_weights(Ad, O.COL), cafeq.prepare_weights(Bd, O.ROW))
+    losses, _, outs = cafeq.dual_proxy_loss_fwd_bwd(Ad, Bd, _dev(torch, T), _dev(torch, P), 3, group, 1, 5.0, False, True, prepared=prep)
+    torch.cuda.synchronize()
+    ref = O.dual_lse(A, B, T, P, 3, group, 1, 5.0, want_grad=False)
+    for i, name in enumerate(("errU_sq", "errV_sq", "l2A_sq", "l2B_sq", "lse")):
+        parity.check_scalar(float(losses[i]), ref[name], what=name)
+    for c, s, z, axis in ((outs[0], outs[1], "U", O.COL), (outs[2], outs[3], "V", O.ROW)):
+        c_ref, s_ref, _ = O.rtn_sym(ref[z], 3, group, axis)
+        parity.check_scales(s.cpu().numpy(), s_ref)
+        parity.check_codes(c.cpu().numpy(), c_ref, ref[z], s_ref, axis, group)
