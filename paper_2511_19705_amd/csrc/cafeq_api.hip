@@ -226,12 +226,35 @@ bool v2_pair_pays(const cafeq_mat* A, const cafeq_mat* B, int K, const GroupPlan
 // whole channels 48 / 16; 9B-shaped (V, O) pair, blocks of 256 and groups of 64, whose lines are read four times, 99 / 70.
 // Blocks of 128 with groups of 64 would read every line twice: 97 / about 150.
 bool gather_possible(int K, const GroupPlan& gp, bool lines) { return lines && (gp.G >= K || K == 256); }
-// A single matrix whose gradient the loss pass can form on the way (blocks of 32 and 64): by records from 8 M weights on.
-// Whole evaluations, on the way / by records: blocks of 32, groups of 32, 4.2 M weights 33 / 40 us, 21 M 97 / 90; blocks of
-// 64, groups of 128, 4.2 M 37.0 / 38.2, 21 M 93 / 83.
-bool gather_single(int K, const GroupPlan& gp, bool lines, bool asym, int64_t weights) {
-  const bool on_the_way = K <= 64 && gp.gspan == 1 && core_lds_bytes(K, gp.Gk, true) != 0 && !asym;
-  return gather_possible(K, gp, lines) && (!on_the_way || weights >= (int64_t(1) << 23));
+// Whether that is the faster way.  A workgroup sorts the records of one block (of a block's group where those are shorter), so that
+// few blocks of many lines leave the chip to a few workgroups, where the product spreads over lines as well.  Whole
+// evaluations in us, the other way / by records:
+//   groups from 128 on at k = 256, longer than 128 elsewhere: by records throughout (36864 x 256 at k = 256 205 / 190; whole channels
+//   at k = 128 159 / 136).  k = 256, groups of 64 (every line four times): 36864 x 1024 357 / 360, x 256 204 / 215; groups of 32 (eight
+//   times): 4608 x 1024 132 / 121, 2304 x 4608 .99, 2304 x 9216 298 / 318, 36864 x 4608 1384 / 1671, in bfloat16 1387 / 1280.
+//   k = 128, groups of 128: 14336 x 1024 .97, 36864 x 256 118 / 110, x 1024 164 / 171, x 4608 580 / 507, and with prepared weights, whose product
+//   reads tiles in its own order, 127 / 142 and 385 / 393.
+//   k = 32 and 64 in one matrix, where the loss pass forms the gradient on its way: 14336 x 1024 (k = 32) 68 / 85, 36864 x 2304
+//   308 / 259, 2304 x 4608 58 / 55, 1147 x 9216 63 / 61, 4.2 M weights 33 / 40; over prepared weights, whose loss pass only records, with groups of 128
+//   (bfloat16: of 64) 36864 x 1024 113 / 107, 9216 x 1024 57 / 50.  On the min/max grid, a pass of its own either way: groups of 32 1147 x 512
+//   31 / 25, 4608 x 256 33 / 37, 2304 x 9216 83 / 86, 36864 x 1024 120 / 184; 64 36864 x 1024 118 / 140, 14336 x 512 66 / 61.
+//   Pairs (prepared: two launches less): 4608 x 256 at k = 32, groups of 32 48 / 56, 2304 x 512 47 / 46; else by records throughout.
+bool gather_pays(const cafeq_mat* W, int K, const GroupPlan& gp, int64_t nlines, int64_t naxis, bool asym, bool pair, bool v2) {
+  const int64_t weights = nlines * naxis;
+  const bool bf16 = W->dtype == CAFEQ_BF16;
+  const bool on_the_way = !pair && K <= 64 && gp.gspan == 1 && core_lds_bytes(K, gp.Gk, true) != 0 && !asym;
+  if (on_the_way && weights < (int64_t(1) << 23)) return false;
+  if (K == 256 && gp.G == 64) return bf16 || nlines <= 64 * naxis;
+  if (K == 256 && gp.G == 32) return bf16 ? nlines <= 36 * naxis : nlines <= 24 * naxis && weights < 12000000;
+  if (K == 256 || gp.G > 128 || gp.gspan > 1) return true;
+  if (K == 128) return nlines <= 16384 || naxis <= 256 || (!W->prepared && naxis >= 2048);
+  if (pair) return asym || gp.G > 32 || nlines <= 6 * naxis;
+  if (asym) {
+    if (gp.G == 32) return (nlines <= 2304 && naxis <= 4608) || (nlines <= 8192 && weights >= 64000000);
+    return gp.G == 128 || nlines <= 30 * naxis;
+  }
+  if (v2 && (gp.G == 128 || (gp.G == 64 && bf16))) return naxis >= 1024;
+  return naxis >= 2048 && weights >= 10000000;
 }
 bool has_lines(const cafeq_mat* W, int axis) {
   if (axis == CAFEQ_AXIS_COL) return grad_gather_fits(W->rows, W->ld, 128, W->dtype);
@@ -1105,7 +1128,8 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
   // (Gradient descent at two bits takes steps nine times those at three and amplifies any change of rounding: of 20 small loops
   // a few end 1e-4 to 4e-3 elsewhere for a gradient that is ten times closer to float64's.  They keep the pass they had.)
   bool v2 = v2_eligible(W, K, gp, cfg, !col && (codes || scales)) && v2_pays(W, K, gp, nlines, naxis, codes || scales, !col);
-  const bool gather = gather_single(K, gp, has_lines(W, cfg->axis), asym, nlines * naxis) && !(hook && cfg->bits == 2);
+  const bool gather = gather_possible(K, gp, has_lines(W, cfg->axis)) && gather_pays(W, K, gp, nlines, naxis, asym, false, v2) &&
+                      !(hook && cfg->bits == 2);
   if (K < 128 && grad && !gather) v2 = false;   // (the loss pass forms the gradient on its way)
   PassPlans pp;
   rc = plan_passes(K, gp, nlines, naxis, grad, &pp, v2, asym, 1, gather);
@@ -1233,7 +1257,8 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
   if ((rc = resolve_group(cfg, B->rows, K, &gb))) return rc;
   const bool grad = gradT != nullptr;
   const bool asym = is_minmax(cfg);
-  const bool gather = gather_possible(K, ga, has_lines(A, CAFEQ_AXIS_COL)) && gather_possible(K, gb, has_lines(B, CAFEQ_AXIS_ROW));
+  const bool gather = gather_possible(K, ga, has_lines(A, CAFEQ_AXIS_COL)) && gather_possible(K, gb, has_lines(B, CAFEQ_AXIS_ROW)) &&
+                      gather_pays(A, K, ga, A->rows, A->cols, asym, true, false) && gather_pays(B, K, gb, B->cols, B->rows, asym, true, false);
   bool v2A = v2_eligible(A, K, ga, cfg, false), v2B = v2_eligible(B, K, gb, cfg, codesV || scalesV);
   // both loss passes over prepared weights in one launch, each member on half of the chip: when neither writes
   // codes or scales and both use the same group length
