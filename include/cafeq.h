@@ -341,7 +341,10 @@ typedef struct {
  * step, before its update:
  *   single: l2_sq, err_z_sq, w_sq, surrogate, penalty, 0, 0, 0     (gradient descent)
  *   pair:   errU_sq, errV_sq, l2A_sq, l2B_sq, lse, n_groups, penalty, 0   (Adam)
- * moments (pair): 2*nb*k*k floats of optimiser state, zeroed by the call. */
+ * moments (pair): 2*nb*k*k floats of optimiser state, zeroed by the call.
+ * A step takes the gradient that an evaluation returns, bit for bit, but for a single matrix at two bits: there the loop's
+ * gradient is always the product over the weights' 16-bit parts (about 1e-5 relative), where an evaluation may
+ * sum the lines themselves (about 1e-7): steps at two bits amplify the difference into other transforms. */
 int cafeq_optimize_single(const cafeq_mat* W, float* T, float* Tinv, int k, int nb, int rep,
                           const cafeq_quant_cfg* cfg, const cafeq_opt_cfg* opt, float* history,
                           int* status, void* ws, void* stream);

@@ -721,7 +721,7 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
                      float* scalesV, void* ws, void* stream, const UpdateHook* hook);
 
 static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_quant_cfg* cfg, float* losses, float* gradT,
-                       int8_t* codes, float* scales, void* ws, void* stream, const UpdateHook* hook);
+                       int8_t* codes, float* scales, void* ws, void* stream, const UpdateHook* hook, bool loop);
 
 int cafeq_optimize_single(const cafeq_mat* W, float* T, float* Tinv, int k, int nb, int rep,
                           const cafeq_quant_cfg* cfg, const cafeq_opt_cfg* opt, float* history, int* status,
@@ -743,10 +743,10 @@ int cafeq_optimize_single(const cafeq_mat* W, float* T, float* Tinv, int k, int 
     if (fuse) {
       UpdateHook hook{};
       hook.T = T; hook.lr = opt->lr; hook.denom = opt->normalize ? h + 2 : nullptr;
-      if ((rc = single_impl(W, &x, cfg, h, w.grad, nullptr, nullptr, w.sub, stream, &hook))) return rc;
+      if ((rc = single_impl(W, &x, cfg, h, w.grad, nullptr, nullptr, w.sub, stream, &hook, true))) return rc;
       continue;
     }
-    if ((rc = cafeq_proxy_loss_fwd_bwd(W, &x, cfg, h, w.grad, nullptr, nullptr, w.sub, stream))) return rc;
+    if ((rc = single_impl(W, &x, cfg, h, w.grad, nullptr, nullptr, w.sub, stream, nullptr, true))) return rc;
     // surrogate / ||W||^2 (history[s][2]) when normalised, then the regulariser's gradient on top
     if (opt->normalize && (rc = launch_div_by_device_scalar(w.grad, h + 2, n, st))) return rc;
     if (opt->lambda_orth > 0.f &&
@@ -1085,9 +1085,9 @@ int cafeq_apply_transform(const cafeq_mat* W, const cafeq_xform* x, int axis, in
 }
 
 // hook (learning loop only; blocks of 32 and more): the last kernel of the gradient applies the gradient-descent step
-// to T instead of storing the gradient (gradT is then scratch)
+// to T instead of storing the gradient (gradT is then scratch).  loop: called from a learning loop, with a hook or without.
 static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_quant_cfg* cfg, float* losses, float* gradT,
-                       int8_t* codes, float* scales, void* ws, void* stream, const UpdateHook* hook) {
+                       int8_t* codes, float* scales, void* ws, void* stream, const UpdateHook* hook, bool loop) {
   int rc = check_mat(W);
   if (rc) return rc;
   rc = check_cfg(cfg, true, true);
@@ -1105,8 +1105,7 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
     if ((rc = launch_embed_blocks(x->T, x->k, x->nb, x->rep, int(nb32), w.T32, st))) return rc;
     if ((rc = launch_embed_blocks(x->Tinv, x->k, x->nb, x->rep, int(nb32), w.P32, st))) return rc;
     const cafeq_xform x32{w.T32, w.P32, 32, int(nb32), 1};
-    if ((rc = cafeq_proxy_loss_fwd_bwd(W, &x32, cfg, losses, gradT ? w.G32 : nullptr, codes, scales, w.sub, stream)))
-      return rc;
+    if ((rc = single_impl(W, &x32, cfg, losses, gradT ? w.G32 : nullptr, codes, scales, w.sub, stream, nullptr, loop))) return rc;
     return gradT ? launch_gather_blocks(w.G32, x->k, x->nb, x->rep, gradT, st) : CAFEQ_OK;
   }
   rc = check_xform(x, true);
@@ -1125,11 +1124,13 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
   if (rc) return rc;
   const bool grad = gradT != nullptr;
   const bool asym = is_minmax(cfg);
-  // (Gradient descent at two bits takes steps nine times those at three and amplifies any change of rounding: of 20 small loops
-  // a few end 1e-4 to 4e-3 elsewhere for a gradient that is ten times closer to float64's.  They keep the pass they had.)
+  // Gradient descent at two bits takes steps nine times those at three and amplifies what rounds: of 60 loops of eight steps 22
+  // end more than 1e-5 (and up to 1) elsewhere by records than by the product, 10 where the weights move by half a unit in
+  // their last place, although the gradient itself is ten times closer to float64's.  These loops, with or without a regulariser and
+  // whatever the block, keep the product, and with it the transforms they have always ended at; evaluations do not depend on the bits.
   bool v2 = v2_eligible(W, K, gp, cfg, !col && (codes || scales)) && v2_pays(W, K, gp, nlines, naxis, codes || scales, !col);
   const bool gather = gather_possible(K, gp, has_lines(W, cfg->axis)) && gather_pays(W, K, gp, nlines, naxis, asym, false, v2) &&
-                      !(hook && cfg->bits == 2);
+                      !(loop && cfg->bits == 2);
   if (K < 128 && grad && !gather) v2 = false;   // (the loss pass forms the gradient on its way)
   PassPlans pp;
   rc = plan_passes(K, gp, nlines, naxis, grad, &pp, v2, asym, 1, gather);
@@ -1211,7 +1212,7 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
 int cafeq_proxy_loss_fwd_bwd(const cafeq_mat* W, const cafeq_xform* x, const cafeq_quant_cfg* cfg,
                              float* losses, float* gradT, int8_t* codes, float* scales, void* ws,
                              void* stream) {
-  return single_impl(W, x, cfg, losses, gradT, codes, scales, ws, stream, nullptr);
+  return single_impl(W, x, cfg, losses, gradT, codes, scales, ws, stream, nullptr, false);
 }
 
 // hook (learning loop only; blocks of 32 and more): the last kernel of the gradient applies the Adam step to T, m
