@@ -59,7 +59,8 @@ __global__ __launch_bounds__(256) void prepare_tiles_kernel(const PrepArgs a) {
 #pragma unroll
   for (int e = 0; e < 16; ++e) {
     x[e] = tile[li][16 * c + e];
-    mx = fmaxf(mx, fabsf(x[e]));
+    // (an infinity must not set the scale: the line's other blocks of 32 or 64 would be scaled away)
+    if (fabsf(x[e]) < INFINITY) mx = fmaxf(mx, fabsf(x[e]));
     sq += double(x[e]) * x[e];
   }
   mx = fmaxf(mx, __shfl_xor(mx, 1));

@@ -111,3 +111,25 @@ def test_large_pair_with_codes(env, k, group):
         c_ref, s_ref, _ = O.rtn_sym(ref[z], 3, group, axis)
         parity.check_scales(s.cpu().numpy(), s_ref)
         parity.check_codes(c.cpu().numpy(), c_ref, ref[z], s_ref, axis, group)
+
+
+# (its own block's transformed values are not numbers; nothing else of the line's 128 inputs depends on it)
+@pytest.mark.parametrize("k", [32, 64])
+@pytest.mark.parametrize("axis,bf16", [(O.COL, False), (O.COL, True), (O.ROW, True)])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_an_infinite_weight_leaves_its_lines_other_blocks_alone(env, k, axis, bf16, value):
+    torch, cafeq = env
+    W, T, P = _case(axis, 3400, 2048, k, 1, 3600 + k)
+    outs = []
+    for v in (value, 0.0):
+        W[(70, 300) if axis == O.COL else (300, 70)] = v
+        Wd = _dev(torch, W).to(torch.bfloat16 if bf16 else torch.float32)
+        _, _, codes, scales = cafeq.proxy_loss_fwd_bwd(Wd, _dev(torch, T), _dev(torch, P), 4, k, axis, want_grad=False, want_codes=True,
+                                                       prepared=cafeq.prepare_weights(Wd, axis))
+        outs.append([x.cpu().numpy() if axis == O.COL else x.cpu().numpy().T for x in (codes, scales)])
+    g = 300 // k
+    for codes, scales in outs:
+        codes[70, g * k:(g + 1) * k] = 0
+        scales[70, g] = 0
+    np.testing.assert_array_equal(outs[0][0], outs[1][0])
+    np.testing.assert_array_equal(outs[0][1], outs[1][1])
