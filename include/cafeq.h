@@ -222,7 +222,9 @@ int cafeq_apply_transform(const cafeq_mat* W, const cafeq_xform* x, int axis, in
  * per tile of 32 lines x 128 axis indices two float16 parts of every element -- the line's segment scaled
  * by a power of two so that its largest magnitude lies in [2^3, 2^4), hi = fl16(y), lo = fl16(y - hi):
  * 22 significant bits -- in the order the loss kernel's matrix instructions read them, the per-line
- * factors that undo the scaling, and ||W||_F^2 (float64 sum).  To be called again whenever W changes. */
+ * factors that undo the scaling, and ||W||_F^2 (float64 sum).  Where 32 or 64 of a line's 128 are more than 2^5 (bfloat16:
+ * 2^8) smaller than its largest, the loss pass of blocks that short splits the line anew from W (along rows from the copy of
+ * the weights as they are), each block with a scale of its own.  To be called again whenever W changes. */
 size_t cafeq_prepared_bytes(const cafeq_mat* W, int axis);
 int cafeq_prepare_weights(const cafeq_mat* W, int axis, void* prepared, void* stream);
 

@@ -162,10 +162,10 @@ float beta_for(const cafeq_quant_cfg* cfg, const QGrid& g) {
 // The loss pass over prepared weights (loss_v2.hip): one workgroup of eight waves per compute unit,
 // macro-tiles of 256 lines.
 // codes_along_rows: it writes codes or scales of a matrix transformed along its rows (byte stores).  Blocks of 32 and 64 with
-// float32 weights and groups of 32 or 64 have no registers for that next to two parts of everything: 9216 x 2304 48 to 58 us
-// the general way, 58 to 69 this way (groups of 128 59 and 50).
+// float32 weights have no registers for that next to two parts of everything: 9216 x 2304, groups of 32 and 64 48 to 58 us
+// the general way, 58 to 69 this way; groups of 128 54 and 56 at k = 32, 58 and 50 at k = 64.
 bool v2_eligible(const cafeq_mat* W, int K, const GroupPlan& gp, const cafeq_quant_cfg* cfg, bool codes_along_rows) {
-  if (K < 128 && codes_along_rows && gp.Gk < 128 && W->dtype == CAFEQ_F32) return false;
+  if (K < 128 && codes_along_rows && W->dtype == CAFEQ_F32 && !(K == 64 && gp.Gk == 128)) return false;
   return W->prepared != nullptr && K <= 128 && gp.Gk <= 128 && gp.gspan == 1 && cfg->bits <= 4 && !is_minmax(cfg);
 }
 // share: the matrix gets 1 / share of the chip's compute units (2: the members of a pair that run in one launch)
@@ -463,7 +463,7 @@ void fill_common(CoreParams* p, const cafeq_mat* W, const CorePlan& pl, int rep)
   p->fscale = nullptr;
   p->longg = 0; p->gspan = 1; p->grec = nullptr; p->grp = 0;
   p->prep_planes = nullptr; p->prep_lscale = nullptr; p->prep_wsq = nullptr; p->fscale_inv = nullptr;
-  p->prep_gtiles = nullptr;
+  p->prep_gtiles = nullptr; p->prep_lines = nullptr;
   p->asym = 0; p->mins = nullptr; p->rec_mm = nullptr; p->grec_mm = nullptr;
   p->grid = make_grid(4);
 }
@@ -476,6 +476,7 @@ void set_prepared(CoreParams* p, const cafeq_mat* W, int axis) {
   p->prep_wsq = reinterpret_cast<const float*>(base);
   p->prep_lscale = reinterpret_cast<const float*>(base + l.off_lscale);
   p->prep_planes = base + l.off_planes;
+  p->prep_lines = col ? nullptr : base + l.off_lines;
 }
 
 // Forward sweep(s) of the fused core over one matrix.  `p` holds everything but the group bookkeeping.  For

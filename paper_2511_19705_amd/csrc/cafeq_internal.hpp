@@ -64,9 +64,12 @@ struct PreparedLayout { int64_t nlp, nseg, ntiles; size_t off_lscale, off_planes
 // float16 (loss pass) or bfloat16 (gradient pass) holds -- its second part was zeros, half the bytes of both passes.
 __host__ __device__ constexpr int prepared_parts(int dtype) { return dtype == CAFEQ_BF16 ? 1 : 2; }
 // Float16 parts of the loss pass's forward operand (T of member A, T^-1 of member B) and of the rounding error.  Shorter sums
-// round less often, so that what the operands themselves lose shows: with two parts and three products blocks of 32 were
-// 7.0e-8 (group maxima against float64, root mean square) where six bfloat16 products are 6.4e-8; blocks of 64 are 8.7e-8
-// against 9.7e-8.  One part of the error leaves the l2 proxy of blocks of 32 and 64 2e-6 off, two parts 1e-7, as bfloat16's two.
+// round less often, so that what the operands themselves lose shows: with two parts of T blocks of 32 were 7.0e-8 off.
+// Against float64, six bfloat16 products of three-part operands / this (eight float32 matrices of 2304 x 9216, 4 bits): scales,
+// root mean square (largest), groups of the block's length -- Student-t weights with outliers of twenty times, blocks of 32
+// 6.4e-8 (5.1e-7) / 6.2e-8 (4.9e-7), of 64 9.7e-8 (7.8e-7) / 8.5e-8 (6.9e-7); columns of twenty times the others' size 6.3e-8 / 6.3e-8
+// and 9.8e-8 / 9.0e-8, of a thousand times 6.4e-8 / 6.6e-8 and 9.5e-8 / 1.0e-7; codes that differ, of 1.7e8 Student-t weights,
+// 41 / 41 and 35 / 34.  One part of the error leaves the l2 proxy of blocks of 32 and 64 2e-6 off, two parts 1e-7, as bfloat16's two.
 __host__ __device__ constexpr int v2_fwd_parts(int K) { return K == 32 ? 3 : 2; }
 __host__ __device__ constexpr int v2_err_parts(int K) { return K == 128 ? 1 : 2; }
 PreparedLayout prepared_layout(int64_t nlines, int64_t naxis, int dtype, int axis);

@@ -63,14 +63,22 @@ __global__ __launch_bounds__(256) void prepare_tiles_kernel(const PrepArgs a) {
     if (fabsf(x[e]) < INFINITY) mx = fmaxf(mx, fabsf(x[e]));
     sq += double(x[e]) * x[e];
   }
+  const int parts = prepared_parts(a.dtype);
   mx = fmaxf(mx, __shfl_xor(mx, 1));
+  const float mx32 = mx;
   mx = fmaxf(mx, __shfl_xor(mx, 2));
+  const float mx64 = mx;
   mx = fmaxf(mx, __shfl_xor(mx, 4));
   int ex = int(__float_as_uint(mx) >> 23);
   ex = ex < 32 ? 32 : (ex > 254 ? 254 : ex);        // lines of (almost) zeros: any scale will do
   const float wsc = __uint_as_float(uint32_t(257 - ex) << 23);          // 2^(3 - (ex - 127)): largest magnitude in [2^3, 2^4)
-  if (c == 0) a.lscale[int64_t(seg) * a.nlp + strip * 32 + li] = __uint_as_float(uint32_t(ex - 3) << 23);
-  const int parts = prepared_parts(a.dtype);
+  // 32 or 64 inputs that are so much smaller than the segment's largest that their parts end before their bits do (the second
+  // part at 2^-24; bfloat16's eight bits end long before): marked in the line's scale (rescale_strip, loss_v2.hpp)
+  const float least = mx * (parts == 2 ? 0x1p-5f : 0x1p-8f);
+  uint32_t far = (mx32 > 0.f && mx32 < least ? kFar32 : 0u) | (mx64 > 0.f && mx64 < least ? kFar64 : 0u);
+  far |= __shfl_xor(far, 2);
+  far |= __shfl_xor(far, 4);
+  if (c == 0) a.lscale[int64_t(seg) * a.nlp + strip * 32 + li] = __uint_as_float(uint32_t(ex - 3) << 23 | far);
   unsigned char* tp = a.planes + tix * int64_t(v2_tile_bytes(parts)) + c * 1024 * parts;
 #pragma unroll
   for (int hh = 0; hh < 2; ++hh) {
@@ -80,12 +88,7 @@ __global__ __launch_bounds__(256) void prepare_tiles_kernel(const PrepArgs a) {
       uint32_t hb[2], lb[2];
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        const float y = x[8 * hh + 2 * e2 + u] * wsc;
-        const _Float16 p0 = _Float16(y);
-        const _Float16 p1 = _Float16(y - float(p0));
-        // (one part: the second is zero, or not a number behind an infinity, which then is none either, as in two parts)
-        hb[u] = __builtin_bit_cast(uint16_t, parts == 1 && !(p1 == _Float16(0)) ? p1 : p0);
-        lb[u] = __builtin_bit_cast(uint16_t, p1);
+        weight_parts(x[8 * hh + 2 * e2 + u] * wsc, parts == 1, &hb[u], &lb[u]);
       }
       hi[e2] = hb[0] | (hb[1] << 16);
       lo[e2] = lb[0] | (lb[1] << 16);

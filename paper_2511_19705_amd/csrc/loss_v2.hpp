@@ -28,7 +28,9 @@
 // = absmax / (2 qmax) <= 2^15 in accumulator units, is a float16 number without any rescaling (the matrix
 // cores take denormal float16 inputs exactly, so small entries lose nothing).  Inverse: the error E as ONE
 // float16 part (round to nearest even: 2^-12 relative, zero mean) times T^-1 as hi + lo (2^-22 relative: a
-// fixed operand's rounding would otherwise bias every element the same way).
+// fixed operand's rounding would otherwise bias every element the same way).  Blocks of 32 and 64 take the error in two parts,
+// blocks of 32 the forward operand in three (v2_fwd_parts), and a block that is far smaller than its line's others a scale of its
+// own (rescale_strip: Student-t weights with outliers, 2304 x 9216 at k = 64, evaluation 75.5 -> 80.3 us for it, Gaussian ones nothing).
 #pragma once
 #include <atomic>
 
@@ -76,6 +78,17 @@ __device__ __forceinline__ void argmax4(float (&b)[4], int (&j)[4], float z0, fl
       : "v"(z0), "v"(z1), "v"(z2), "v"(z3), "n"(J));
 }
 
+// Marks in a line's scale, a power of two: 32 (64) of its inputs are far smaller than the segment's largest
+constexpr uint32_t kFar32 = 1, kFar64 = 2;
+// A scaled weight as float16 parts.  (One part: the second is zero, or not a number behind an infinity, which then is none
+// either, as in two parts.)
+__device__ __forceinline__ void weight_parts(float y, bool one, uint32_t* hi, uint32_t* lo) {
+  const _Float16 p0 = _Float16(y);
+  const _Float16 p1 = _Float16(y - float(p0));
+  *hi = __builtin_bit_cast(uint16_t, one && !(p1 == _Float16(0)) ? p1 : p0);
+  *lo = __builtin_bit_cast(uint16_t, p1);
+}
+
 // bidx: the workgroup's index among the p.nwg workgroups that share the matrix; WP: parts of the prepared weights;
 // REC: write the arg-max records (the gradient pass follows); OUT: write scales and / or codes
 template <int K, int G, int AXIS, bool REC, bool OUT, int WP>
@@ -119,11 +132,68 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
   // start of the matrix phase they had only the inverse transform (about a microsecond) to arrive in.
   uintx4 wq[8 * WP];
   float lsc_nx = 0.f;
+  // (NB > 1) a line's blocks against the line's scale: a byte of binary exponent each, zero but in strips that rescale_strip took
+  int xe = 0;
+  auto xe_of = [&](int b) { return int(uint32_t(xe) << (24 - 8 * b)) >> 24; };
   auto request_strip = [&](int sg, int64_t strip) {   // strip: the wave's strip inside segment sg
     lsc_nx = p.prep_lscale[int64_t(sg) * nlp + strip * 32 + ln];
     const unsigned char* tp = p.prep_planes + (int64_t(sg) * (nlp / 32) + strip) * v2_tile_bytes(WP) + lane * 16;
 #pragma unroll
     for (int i = 0; i < 8 * WP; ++i) wq[i] = *reinterpret_cast<const uintx4*>(tp + i * 1024);
+  };
+  // Blocks of 32 and 64 share their line's scale with the segment's other blocks.  One that is far smaller would keep few of
+  // its bits (a thousand times: maxima to 5e-7, against 6e-8).  Such lines are marked in their scale; a strip that holds one --
+  // one in a hundred at k = 64, one in twenty at k = 32 where weights are Student-t with outliers of twenty times -- is split anew
+  // from the weights themselves, every block with a scale of its own.
+  auto rescale_strip = [&](int sg, int64_t strip) {
+    if constexpr (NB > 1) {
+      xe = 0;
+      if (!__any((__float_as_uint(lsc_nx) & (K == 32 ? kFar32 : kFar64)) != 0)) return;
+      // (nothing of this is worth a register in the other strips: kept apart from what could be worked out ahead)
+      int own = lane;
+      int64_t ld = p.ld, nl = p.nlines;
+      const void* src = AXIS == CAFEQ_AXIS_COL ? p.W : p.prep_lines;
+      asm volatile("" : "+v"(own), "+s"(ld), "+s"(nl), "+s"(src));
+      const int64_t line = strip * 32 + (own & 31);
+      const bool in = line < nl;
+      const int64_t at = (AXIS == CAFEQ_AXIS_COL ? (in ? line : 0) * ld + int64_t(sg) * L : (int64_t(sg) * nlp + line) * L) + 8 * (own >> 5);
+      // the weights as they are, where their parts will be: a step's eight inputs
+#pragma unroll
+      for (int i = 0; i < 8 * WP; ++i)
+        wq[i] = *reinterpret_cast<const uintx4*>(static_cast<const unsigned char*>(src) + (at + 16 * (i / WP)) * (2 * WP) + 16 * (i % WP));
+      auto input = [&](int cw, int e) {
+        const uint32_t u = WP == 2 ? wq[2 * cw + e / 4][e % 4] : (e & 1 ? wq[cw][e / 2] & 0xFFFF0000u : wq[cw][e / 2] << 16);
+        return in ? __uint_as_float(u) : 0.f;
+      };
+      const int exl = int(__float_as_uint(lsc_nx) >> 23 & 255u) + 3;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        float mx = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8 * CB; ++i) {
+          const float x = fabsf(input(CB * b + i / 8, i % 8));
+          if (x < INFINITY) mx = fmaxf(mx, x);
+        }
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        int ex = int(__float_as_uint(mx) >> 23);
+        ex = ex < 32 ? 32 : (ex > 254 ? 254 : ex);
+        // (a group's step in the units of its smallest block stays a number)
+        if (ex < exl - (G > K ? 60 : 127)) ex = exl - (G > K ? 60 : 127);
+        xe |= ((ex - exl) & 255) << (8 * b);
+        const float wsc = __uint_as_float(uint32_t(257 - ex) << 23);
+#pragma unroll
+        for (int cw = CB * b; cw < CB * (b + 1); ++cw) {
+          uint32_t hi[8], lo[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) weight_parts(input(cw, e) * wsc, WP == 1, &hi[e], &lo[e]);
+#pragma unroll
+          for (int e2 = 0; e2 < 4; ++e2) {
+            wq[WP * cw][e2] = hi[2 * e2] | (hi[2 * e2 + 1] << 16);
+            if constexpr (WP == 2) wq[2 * cw + 1][e2] = lo[2 * e2] | (lo[2 * e2 + 1] << 16);
+          }
+        }
+      }
+    }
   };
   // (The variants that write codes or scales from two-part weights keep their requests at the start of the matrix phase:
   // their vector phase has no registers to hold a strip in flight.  One part fits: codes of the 27B-shaped gate in
@@ -286,13 +356,13 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
         }
         dp = a;
         if constexpr (NB > 1) if (t > 0 && t % BT == 0) {   // the block before is complete
-          l2s = fmaf(l2, cl2[t / BT - 1], l2s);
+          l2s = fmaf(l2, ldexpf(cl2[t / BT - 1], 2 * xe_of(t / BT - 1)), l2s);
           l2 = 0.f;
         }
       }
 #pragma unroll
       for (int v = 0; v < 16; ++v) l2 = fmaf(dp[v], dp[v], l2);
-      if constexpr (NB > 1) l2 = fmaf(l2, cl2[NB - 1], l2s);
+      if constexpr (NB > 1) l2 = fmaf(l2, ldexpf(cl2[NB - 1], 2 * xe_of(NB - 1)), l2s);
       s_l2 = fmaf(l2, usc2_strip, s_l2);
     };
     // vector phase: the quantizer on strip m (accumulators -> error).  The accumulators hold Z / usc with usc a
@@ -308,6 +378,7 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
       const float dsc = usc * fsi[0];  // (NB == 1) inverse-transformed error: accumulator units -> units of W
       float e2 = 0.f;               // sum of squared errors of this strip in accumulator units
       constexpr bool SPAN = G > K;  // groups of several blocks
+      auto rx = [&](int b) { return ldexpf(rel[b], xe_of(b)); };   // (NB > 1) a block's units in those of segment and line
       // signed value at the arg-max of each tile of 32 and its index in the tile (without the lane-half term)
       float tz[KT];
       int tj[KT];
@@ -330,11 +401,11 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
         int jf = 0;
         constexpr int TPG = G / 32;
         // the group's units: its block's, or the segment's
-        const float usg = NB == 1 || SPAN ? usc : usc * rel[gi * TPG / BT];
+        const float usg = NB == 1 || SPAN ? usc : usc * rx(gi * TPG / BT);
         if constexpr (REC) {
           if constexpr (SPAN) {
 #pragma unroll
-            for (int t = gi * TPG; t < (gi + 1) * TPG; ++t) tz[t] *= rel[t / BT];
+            for (int t = gi * TPG; t < (gi + 1) * TPG; ++t) tz[t] *= rx(t / BT);
           }
           zs = tz[gi * TPG];
           jf = 32 * gi * TPG + tj[gi * TPG];
@@ -346,12 +417,12 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
 #pragma unroll
           for (int f = gi * RPG; f < (gi + 1) * RPG; f += 2) {
             if (SPAN && f % (16 * BT) == 0 && f > gi * RPG) {      // the next block
-              zs = fmaxf(zs, a0 * rel[f / (16 * BT) - 1]);
+              zs = fmaxf(zs, a0 * rx(f / (16 * BT) - 1));
               a0 = 0.f;
             }
             a0 = fmaxf(fmaxf(fabsf(acc[f / 16][f % 16]), fabsf(acc[(f + 1) / 16][(f + 1) % 16])), a0);
           }
-          zs = SPAN ? fmaxf(zs, a0 * rel[((gi + 1) * TPG - 1) / BT]) : a0;
+          zs = SPAN ? fmaxf(zs, a0 * rx(((gi + 1) * TPG - 1) / BT)) : a0;
         }
         float as = fabsf(zs);       // absmax in the group's units
         {
@@ -381,8 +452,8 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
 #pragma unroll
         for (int f2 = gi * RPG / 2; f2 < (gi + 1) * RPG / 2; ++f2) {
           if (SPAN && f2 % (8 * BT) == 0) {              // a block's first elements: the group's grid in its units
-            inv = inv0 * rel[f2 / (8 * BT)];
-            s = s0 * inv_rel[f2 / (8 * BT)];
+            inv = inv0 * rx(f2 / (8 * BT));
+            s = s0 * ldexpf(inv_rel[f2 / (8 * BT)], -xe_of(f2 / (8 * BT)));
           }
           float er[2];
 #pragma unroll
@@ -408,7 +479,7 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
           } else {
             e2b = fmaf(er[0], er[0], fmaf(er[1], er[1], e2b));
             if (f2 % (8 * BT) == 8 * BT - 1 || f2 == (gi + 1) * RPG / 2 - 1) {
-              e2 = fmaf(e2b, rel[f2 / (8 * BT)] * rel[f2 / (8 * BT)], e2);
+              e2 = fmaf(e2b, rx(f2 / (8 * BT)) * rx(f2 / (8 * BT)), e2);
               e2b = 0.f;
             }
           }
@@ -505,8 +576,9 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
     if (grp == 1) __builtin_amdgcn_s_barrier();
     {
       if constexpr (!EARLY) request_strip(seg, int64_t(mis0) * kV2Waves + wave);
+      rescale_strip(seg, int64_t(mis0) * kV2Waves + wave);
       forward();
-      usc = lsc_nx * fsc;
+      usc = __uint_as_float(__float_as_uint(lsc_nx) & 0x7F800000u) * fsc;   // (without the marks)
       fence_m();
       if constexpr (EARLY) request_next(0);
       usc2_prev = epilogue(0);
@@ -519,9 +591,10 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
       if constexpr (!EARLY) request_strip(seg, int64_t(mis0 + m) * kV2Waves + wave);
       __builtin_amdgcn_s_setprio(3);
       inverse(usc2_prev);
+      rescale_strip(seg, int64_t(mis0 + m) * kV2Waves + wave);
       forward();
       __builtin_amdgcn_s_setprio(0);
-      usc = lsc_nx * fsc;
+      usc = __uint_as_float(__float_as_uint(lsc_nx) & 0x7F800000u) * fsc;   // (without the marks)
       fence_m();
       if constexpr (EARLY) request_next(m);
       usc2_prev = epilogue(m);

@@ -134,6 +134,7 @@ struct CoreParams {
   // loss pass over prepared weights (loss_v2.hip): tiles of two float16 parts, per-line factors, ||W||^2
   const unsigned char* prep_planes;
   const float* prep_lscale;
+  const unsigned char* prep_lines;   // row axis: the weights line by line
   const float* prep_wsq;
   const float* fscale_inv;  // per-block factor of the float16 inverse operand planes
   // gradient pass over prepared weights (grad_v2.hip): tiles of 128 lines x 128 inputs in operand order

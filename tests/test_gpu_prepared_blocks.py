@@ -133,3 +133,35 @@ def test_an_infinite_weight_leaves_its_lines_other_blocks_alone(env, k, axis, bf
         scales[70, g] = 0
     np.testing.assert_array_equal(outs[0][0], outs[1][0])
     np.testing.assert_array_equal(outs[0][1], outs[1][1])
+
+
+# Blocks of inputs far smaller than their neighbours in the segment of 128: every block's scales and codes are as exact as if it were
+# alone.  The first 64 lines only, so that strips of both kinds meet, and one line of strip 40
+@pytest.mark.parametrize("k,group", [(32, 32), (32, 64), (32, 128), (64, 32), (64, 64), (64, 128)])
+@pytest.mark.parametrize("axis,bf16,factor", [(O.COL, False, 2.0 ** -10), (O.COL, False, 2.0 ** -45), (O.COL, True, 2.0 ** -20),
+                                              (O.ROW, False, 2.0 ** -20), (O.ROW, True, 2.0 ** -45)])
+def test_inputs_of_different_magnitude(env, k, group, axis, bf16, factor):
+    W, T, P = _case(axis, 3400, 2048, k, 1, 3700 + k + group)
+    V = W if axis == O.COL else W.T
+    small = (np.arange(2048) // k) % 3 != 1
+    for line in list(range(64)) + [1285]:
+        V[line, small] *= np.float32(factor)
+    codes = axis == O.COL or bf16 or (k, group) == (64, 128)          # (along rows from float32 weights: the general kernel's)
+    _check_single_prepared(env, W, T, P, 4, group, axis, 1, bf16=bf16, want_grad=False, want_codes=codes)
+    if not codes:
+        _check_losses_of_the_small_blocks(env, W, T, P, group, k, small)
+
+
+def _check_losses_of_the_small_blocks(env, W, T, P, group, k, small):
+    """Lines of small blocks alone: their errors are the losses (rows, no codes)."""
+    torch, cafeq = env
+    W = W.copy()
+    W[:, 64:1280] = 0.0
+    W[:, 1344:] = 0.0
+    W[~small] *= np.float32(2.0 ** -3)
+    Wd = _dev(torch, W)
+    losses, _, _, _ = cafeq.proxy_loss_fwd_bwd(Wd, _dev(torch, T), _dev(torch, P), 4, group, O.ROW, 1, want_grad=False,
+                                               prepared=cafeq.prepare_weights(Wd, O.ROW))
+    ref = O.proxy_l2(W, T, P, 4, group, O.ROW, 1)
+    parity.check_scalar(float(losses[0]), ref["l2_sq"], what="l2_sq")
+    parity.check_scalar(float(losses[1]), ref["err_z_sq"], what="err_z_sq")
