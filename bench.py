@@ -276,7 +276,7 @@ def pair_workload(args, secondary=True):
 # ----------------------------------------------------------------------------------------------------
 def core_workload(args):
     """c3_optimize : Adam iterations on the 9B-shaped pair (inverse + paired fwd+bwd + update), prepared weights
-       c2_single   : single-matrix fwd+bwd on the 2B-shaped down projection (k = 64, fused gradient)
+       c2_single   : single-matrix fwd+bwd on the 2B-shaped down projection (k = 64, gradient by records)
        c4_adaptive : Alg. 1 iterations on the 9B-shaped attention V/O pair (k = 256)"""
     import numpy as np
     import torch
@@ -311,7 +311,7 @@ def core_workload(args):
                 P, _ = cafeq.block_inverse(T)
                 cafeq.proxy_loss_fwd_bwd(W, T, P, cfg["bits"][0], cfg["group"], 0, 1, want_grad=True)
         metric = "proxy-loss fwd+bwd weight-elements/s (2B-shaped down projection, single transform)"
-        flop_el, parts, kern, name = 6 * k, 12, "xform_core_kernel<64,128,COL,true> (fused)", cfg["name"]
+        flop_el, parts, kern, name = 4 * k, 9, "xform_core_kernel<64,128,COL,false> (loss pass; the gradient comes by records)", cfg["name"]
 
         def cpu():
             from oracle import cafeq_oracle as O

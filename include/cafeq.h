@@ -75,8 +75,10 @@ typedef enum { CAFEQ_Q_SYM_ABSMAX = 0, CAFEQ_Q_ASYM_MINMAX = 1 } cafeq_qmode;
  * evaluations of a learning run (paper Sec. 4.1, Sec. 4.2); with a prepared copy the loss pass of
  * cafeq_proxy_loss_fwd_bwd / cafeq_dual_proxy_loss_fwd_bwd / cafeq_optimize_* reads them in the form
  * the matrix cores consume (where a kernel for it exists: blocks of 32, 64 and 128, groups up to 128, up to
- * 4 bits; ignored otherwise, and for blocks of 32 and 64 where the general kernel is the faster one).  `data` must stay
- * valid either way: the gradient pass and every other configuration read it.  Entry points that do not mention it ignore the field. */
+ * 4 bits, the symmetric grid; the general kernel otherwise, and for blocks of 32 and 64 where it is the faster one), and the
+ * gradient pass takes what it reads from the copy, too: tiles for blocks of 128, along rows the weights line by line whatever
+ * block, group, bits and grid.  `data` must stay valid and unchanged either way: either pass may read it instead, and every other
+ * configuration does.  Entry points that do not mention it ignore the field. */
 typedef struct {
   const void* data;
   int64_t rows, cols, ld;
@@ -214,10 +216,11 @@ int cafeq_apply_transform(const cafeq_mat* W, const cafeq_xform* x, int axis, in
  * along `axis` (0 if the axis length is not a multiple of 128); about rows * cols * 8 bytes for float32, half
  * of that for bfloat16: one copy in the order the loss pass contracts (over the axis), one in the order the gradient
  * pass contracts (over the lines; bfloat16 hi + mid parts, tiles of 128 lines x 128 axis indices; read by the
- * gradient pass for blocks of 128 with shorter groups, whatever the grid).  bfloat16 weights are one part in either.  For
- * the row axis half as much again: the weights as they are, a line's axis indices side by side (along columns they lie so
- * in W), for the gradient of groups no shorter than the block.  The layout belongs to the build of the library that wrote
- * the buffer.
+ * gradient pass for blocks of 128 with shorter groups, for few blocks of many lines with groups of 128 and by learning loops at
+ * two bits, whatever the grid).  bfloat16 weights are one part in either.  For the row axis half as much again: the weights as
+ * they are, a line's axis indices side by side (along columns they lie so in W), for the gradient of groups no shorter than the
+ * block.  All of it is written whatever block and group the calls will have: the copy is made before either is known.  The layout
+ * belongs to the build of the library that wrote the buffer.
  * cafeq_prepare_weights fills it (device memory, 256-byte aligned, owned by the caller).  The loss pass's copy:
  * per tile of 32 lines x 128 axis indices two float16 parts of every element -- the line's segment scaled
  * by a power of two so that its largest magnitude lies in [2^3, 2^4), hi = fl16(y), lo = fl16(y - hi):
@@ -251,7 +254,7 @@ int cafeq_prepare_weights(const cafeq_mat* W, int axis, void* prepared, void* st
  * and takes the constant the paper prints for that grid, beta = 1/(2^b - 1)^2 (Sec. 4.1); codes are then
  * unsigned bytes in [0, 2^b - 1] and `scales` holds twice as many floats: the scales, then the group minima
  * in the same layout.  On this grid the gradient always runs as the second pass (axis a multiple of 128),
- * and a prepared copy of the weights is ignored. */
+ * and the loss pass ignores a prepared copy of the weights. */
 int cafeq_proxy_loss_fwd_bwd(const cafeq_mat* W, const cafeq_xform* x,
                              const cafeq_quant_cfg* cfg, float* losses, float* gradT,
                              int8_t* codes, float* scales, void* ws, void* stream);

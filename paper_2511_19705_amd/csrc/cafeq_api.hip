@@ -512,14 +512,12 @@ int run_core(int K, int axis, const GroupPlan& gp, CoreParams p, float2* rec, fl
 }
 
 // Whether the gradient passes of a call can run with one workgroup per (matrix, block) and write the gradient in
-// its final form (grad_v2.hip; groups shorter than the block, the others go by records): prepared weights, blocks of 128, no
-// row-blocks sharing a transform block, and enough blocks (up to four rounds of workgroups: the 27B-shaped (down, up) pair, 576 blocks, measured 328 us this way
-// against 350 for the partial sums and their reduction; the 2B-shaped one, 144 blocks, 59 against 59 + 17 + 6 us with the
-// loss reduction's launch, which this way does without).  Whole evaluations this way against partial sums, matrices of
-// 1000 / 2304 / 4608 lines: pairs of 128 blocks 85 / 138 / 214 us against 103 / 155 / 220, of 80 82 / 111 / 180 against
-// 92 / 126 / 171: from half of the chip on.  Single matrices, whose partial sums are reduced with the losses and the middle
-// factor in one launch: 128 blocks 91 / 144 / 218 us against 92 / 143 / 210, 144 blocks 113 / 165 / 249 against
-// 122 / 168 / 253: from nine sixteenths on.
+// its final form (grad_v2.hip; groups shorter than the block, the others mostly go by records): prepared weights, blocks of 128,
+// no row-blocks sharing a transform block, and enough blocks, up to four rounds of workgroups.  Whole evaluations this way against
+// partial sums, groups of 64, matrices of 1000 / 2304 / 4608 lines: pairs of 128 blocks in both 81 / 133 / 208 us against 101 / 155 / 219,
+// of 64 68 / 100 / 156 against 74 / 109 / 151, of 512 231 / 390 us against 260 / 420: from half of the chip on.  Single matrices,
+// whose partial sums are reduced with the losses and the middle factor in one launch: 128 blocks 87 / 141 / 213 us against
+// 88 / 141 / 211, 144 blocks 105 / 157 / 240 against 119 / 162 / 247: from nine sixteenths on.
 bool grad_owner_eligible(const cafeq_mat* const* mats, const PassPlans* const* pps, int n, int K, int rep) {
   if (K != 128 || rep != 1) return false;
   int64_t jobs = 0;

@@ -28,7 +28,8 @@ def test_line_counts(env, lines, axis):
     _check_single_prepared(env, W, T, P, 4, 128, axis, 1, want_codes=False)
 
 
-# 8 M weights and more: blocks that the loss pass forms the gradient of on its way below that
+# 8.4 M weights over prepared copies: blocks of 64 with groups of 128 by records; blocks of 32 with groups of 32 still beside the loss
+# pass (by records from 10 M on: tests/test_gpu_routes.py)
 @pytest.mark.parametrize("k,group,lines,naxis", [(32, 32, 4100, 2048), (64, 128, 4100, 2048), (64, 256, 200, 512), (256, 256, 200, 512),
                                                  (256, 64, 333, 512), (256, 0, 200, 768), (128, 512, 131, 1024)])
 @pytest.mark.parametrize("bf16", [False, True])

@@ -75,8 +75,8 @@ def test_prepared_scaled_magnitudes_zero_lines_and_single_entries(env):
 
 
 def test_prepared_falls_back_where_no_kernel_exists(env):
-    # blocks of 64 and grids of more than 4 bits have no prepared-weights kernel: the call must give the
-    # unprepared path's results (the prepared copy is ignored), not an error
+    # blocks of 64 whose gradient the loss pass forms on its way (below 8 M weights) and grids of more than 4 bits are not read from
+    # the prepared copy: the call must give the unprepared path's results, not an error
     torch, cafeq = env
     W, T, P = _case(O.COL, 200, 512, 64, 1, 1160)
     Wd = _dev(torch, W)

@@ -1,6 +1,7 @@
 """GPU parity of the loss pass over prepared weights for blocks of 32 and 64: several blocks share a segment of 128, each in
 units of its own; groups inside a block and across blocks; ragged line counts; codes, scales and losses against the oracle
-(bounds of tests/parity.py, ties by the transform's rounding).  Gradients: tests/test_gpu_gather.py."""
+(bounds of tests/parity.py, ties by the transform's rounding).  Small matrices take that pass with groups of 128 and the general
+kernel, prepared copy or not, with shorter ones; the larger ones below take it throughout.  Gradients: tests/test_gpu_gather.py."""
 import numpy as np
 import pytest
 
