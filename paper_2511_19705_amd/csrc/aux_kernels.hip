@@ -158,22 +158,32 @@ __global__ __launch_bounds__(kSplitThreads) void split_planes_kernel(const Split
   }
   float hsc = 1.f;   // float16 job: the block's scale
   if (jb.fscale) {
-    if (whole) {
+    // (an infinite entry must not set the scale: the block's other outputs would be scaled away.  Looked for only where there is one)
+    for (int finite = 0; finite < 2; ++finite) {
+      m = 0.f;
+      auto take = [&](float4 v) {
+        if (finite) {
+          for (float e : {v.x, v.y, v.z, v.w})
+            if (fabsf(e) < INFINITY) m = fmaxf(m, fabsf(e));
+        } else {
+          m = fmaxf(fmaxf(m, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w)));
+        }
+      };
+      if (whole) {
 #pragma unroll
-      for (int q = 0; q < NQ; ++q)
-        m = fmaxf(fmaxf(m, fmaxf(fabsf(x[q].x), fabsf(x[q].y))), fmaxf(fabsf(x[q].z), fabsf(x[q].w)));
-    } else {
-      for (int e = tid * 4; e < K * K; e += kSplitThreads * 4) {
-        const float4 v = *reinterpret_cast<const float4*>(sb + e);
-        m = fmaxf(fmaxf(m, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w)));
+        for (int q = 0; q < NQ; ++q) take(x[q]);
+      } else {
+        for (int e = tid * 4; e < K * K; e += kSplitThreads * 4) take(*reinterpret_cast<const float4*>(sb + e));
       }
-    }
-    m = cluster_allmax<64>(m);
-    if ((tid & 63) == 0) wmx[tid >> 6] = m;
-    __syncthreads();
-    m = 0.f;
+      m = cluster_allmax<64>(m);
+      if (finite) __syncthreads();                                         // (the maxima before have been read)
+      if ((tid & 63) == 0) wmx[tid >> 6] = m;
+      __syncthreads();
+      m = 0.f;
 #pragma unroll
-    for (int i = 0; i < kSplitThreads / 64; ++i) m = fmaxf(m, wmx[i]);
+      for (int i = 0; i < kSplitThreads / 64; ++i) m = fmaxf(m, wmx[i]);
+      if (m < INFINITY) break;                                             // (uniform)
+    }
     int ex = int(__float_as_uint(m) >> 23);
     ex = ex < 32 ? 32 : (ex > 254 ? 254 : ex);
     hsc = __uint_as_float(uint32_t(254 + jb.texp - ex) << 23);             // 2^(texp - (ex - 127))

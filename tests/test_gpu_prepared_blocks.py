@@ -166,3 +166,21 @@ def _check_losses_of_the_small_blocks(env, W, T, P, group, k, small):
     ref = O.proxy_l2(W, T, P, 4, group, O.ROW, 1)
     parity.check_scalar(float(losses[0]), ref["l2_sq"], what="l2_sq")
     parity.check_scalar(float(losses[1]), ref["err_z_sq"], what="err_z_sq")
+
+
+# (blocks of 128 likewise: their forward operand is two float16 parts with or without a prepared copy)
+@pytest.mark.parametrize("k", [32, 64, 128])
+@pytest.mark.parametrize("value", [np.inf, -np.inf])
+def test_an_infinite_entry_of_a_block_leaves_the_other_outputs_alone(env, k, value):
+    torch, cafeq = env
+    W, T, P = _case(O.COL, 3400, 2048, k, 1, 3800 + k)
+    Wd, Pd = _dev(torch, W), _dev(torch, P)
+    prep = cafeq.prepare_weights(Wd, O.COL)
+    outs = []
+    for v in (value, 0.0):
+        T[3, 1, 2] = v
+        _, _, codes, scales = cafeq.proxy_loss_fwd_bwd(Wd, _dev(torch, T), Pd, 4, 32, O.COL, want_grad=False, want_codes=True, prepared=prep)
+        codes[:, 3 * k:3 * k + 32] = 0                       # (the output's own group)
+        scales[:, 3 * k // 32] = 0
+        outs.append((codes, scales))
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
