@@ -70,7 +70,7 @@ __global__ __launch_bounds__(256) void prepare_tiles_kernel(const PrepArgs a) {
   const float mx64 = mx;
   mx = fmaxf(mx, __shfl_xor(mx, 4));
   int ex = int(__float_as_uint(mx) >> 23);
-  ex = ex < 32 ? 32 : (ex > 254 ? 254 : ex);        // lines of (almost) zeros: any scale will do
+  ex = ex < 4 ? 4 : (ex > 254 ? 254 : ex);          // (the scale and the factor back stay normal numbers)
   const float wsc = __uint_as_float(uint32_t(257 - ex) << 23);          // 2^(3 - (ex - 127)): largest magnitude in [2^3, 2^4)
   // 32 or 64 inputs that are so much smaller than the segment's largest that their parts end before their bits do (the second
   // part at 2^-24; bfloat16's eight bits end long before): marked in the line's scale (rescale_strip, loss_v2.hpp)

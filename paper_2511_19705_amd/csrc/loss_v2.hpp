@@ -176,7 +176,7 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
         }
         mx = fmaxf(mx, __shfl_xor(mx, 32));
         int ex = int(__float_as_uint(mx) >> 23);
-        ex = ex < 32 ? 32 : (ex > 254 ? 254 : ex);
+        ex = ex < 4 ? 4 : (ex > 254 ? 254 : ex);
         // (a group's step in the units of its smallest block stays a number)
         if (ex < exl - (G > K ? 60 : 127)) ex = exl - (G > K ? 60 : 127);
         xe |= ((ex - exl) & 255) << (8 * b);

@@ -184,3 +184,20 @@ def test_an_infinite_entry_of_a_block_leaves_the_other_outputs_alone(env, k, val
         scales[:, 3 * k // 32] = 0
         outs.append((codes, scales))
     assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+
+
+# the line's scale at the lower end of float32's range (the losses, squares, are zeros there)
+@pytest.mark.parametrize("k", [32, 64, 128])
+@pytest.mark.parametrize("factor", [1e-30, 1e-34])
+def test_small_weights(env, k, factor):
+    torch, cafeq = env
+    W, T, P = _case(O.COL, 3400, 2048, k, 1, 3900 + k)
+    W = (W * np.float32(factor)).astype(np.float32)
+    Wd = _dev(torch, W)
+    _, _, codes, scales = cafeq.proxy_loss_fwd_bwd(Wd, _dev(torch, T), _dev(torch, P), 4, 32, O.COL, want_grad=False, want_codes=True,
+                                                   prepared=cafeq.prepare_weights(Wd, O.COL))
+    Z = O.blockdiag_apply(W, T, O.COL, 1)
+    c_ref, s_ref, _ = O.rtn_sym(Z, 4, 32, O.COL)
+    parity.check_scales(scales.cpu().numpy(), s_ref)
+    tol = parity.tie_tolerance(W, T, O.COL, 1, Z, s_ref, 32, parity.forward_unit(k, 32, 4))
+    parity.check_codes(codes.cpu().numpy(), c_ref, Z, s_ref, O.COL, 32, tie_tol=tol)
