@@ -465,7 +465,9 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
             // at most 2e-6 of the error's own size on grids of up to 4 bits).
             const float q = __builtin_rintf(__fmul_rn(z, inv));
             er[e] = fmaf(q, s, -z);
-            if constexpr (OUT) acc[f / 16][f % 16] = q;            // kept for the optional code output
+            // kept for the optional code output; a value that is not a number gets the grid's lowest code, as in the
+            // general pass (blocks of 128 write 0 for it)
+            if constexpr (OUT) acc[f / 16][f % 16] = NB == 1 ? q : fmaxf(q, p.grid.qmin);
           }
           ebf[f2] = pack_f16(er[0], er[1]);
           if constexpr (EP == 2) {

@@ -201,3 +201,21 @@ def test_small_weights(env, k, factor):
     parity.check_scales(scales.cpu().numpy(), s_ref)
     tol = parity.tie_tolerance(W, T, O.COL, 1, Z, s_ref, 32, parity.forward_unit(k, 32, 4))
     parity.check_codes(codes.cpu().numpy(), c_ref, Z, s_ref, O.COL, 32, tie_tol=tol)
+
+
+# a block of values that are not numbers has the codes that it has without a prepared copy (the grid's lowest)
+@pytest.mark.parametrize("k,group", [(32, 32), (32, 128), (64, 64), (64, 128)])
+@pytest.mark.parametrize("axis,bf16,bits", [(O.COL, False, 4), (O.COL, True, 2), (O.ROW, True, 3)])
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_codes_of_a_block_that_is_not_a_number(env, k, group, axis, bf16, bits, value):
+    torch, cafeq = env
+    rows, cols = (3456, 2048) if axis == O.COL else (2048, 3456)
+    W, T, P = _case(axis, rows, cols, k, 1, 4000 + k)
+    W[(1700, 700) if axis == O.COL else (700, 1700)] = value
+    Wd = _dev(torch, W)
+    Wd = Wd.to(torch.bfloat16) if bf16 else Wd
+    lo = 700 // k * k
+    block = (slice(1700, 1701), slice(lo, lo + k)) if axis == O.COL else (slice(lo, lo + k), slice(1700, 1701))
+    codes = [cafeq.proxy_loss_fwd_bwd(Wd, _dev(torch, T), _dev(torch, P), bits, group, axis, want_grad=False, want_codes=True,
+                                      prepared=p)[2][block] for p in (None, cafeq.prepare_weights(Wd, axis))]
+    assert torch.equal(codes[0], codes[1])
