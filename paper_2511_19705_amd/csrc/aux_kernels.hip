@@ -26,11 +26,12 @@ constexpr int kSplitThreads = 1024;
 // with the 32 inputs of a row arranged as four 16-byte chunks (MFMA step c2 = (in % 32) / 16, lane
 // half h -> chunk 2*c2 + h, holding inputs 16*c2 + 8u + 4h + e at position 4u + e), the chunk stored
 // at chunk ^ ((out >> 2) & 3) (LDS bank swizzle).
-struct SplitJob { const float* src; uint16_t* dst; int trans, nplanes; float* fscale; int natural, texp; };   // fscale, texp: see below
+struct SplitJob { const float* src; uint16_t* dst; int trans, nplanes; float* fscale; int natural, texp, minus_one; };   // fscale, texp: see below
 // A job with fscale != null writes two (or three: nplanes) float16 planes instead: the block is first scaled by the power of
 // two that puts its largest magnitude into [2^texp, 2^(texp+1)) (14: the low parts stay normal numbers; 4: sums of
 // 128 products with operands below 2^4 stay below 2^16 -- the matrix cores take denormal float16 inputs exactly), then
 // x = hi + lo (+ a third) with the parts rounded to nearest; fscale[b] receives the factor that undoes the scale.
+// minus_one (K = 256): the planes hold src_b - I.
 //
 // rho[b*K + j]: squared norm of row j (by_row) or column j of P_b, summed in float64.
 // With rG != null the workgroup also writes the sums of rho over groups of G axis indices (what rho_group_kernel
@@ -156,6 +157,23 @@ __global__ __launch_bounds__(kSplitThreads) void split_planes_kernel(const Split
       }
     }
   }
+  // (K = 256; a block's elements in runs of four along a row)
+  auto off_identity = [&](float4 v, int row, int col) {
+    if constexpr (K == 256) {
+      if (jb.minus_one) {
+        v.x -= row == col ? 1.f : 0.f; v.y -= row == col + 1 ? 1.f : 0.f;
+        v.z -= row == col + 2 ? 1.f : 0.f; v.w -= row == col + 3 ? 1.f : 0.f;
+      }
+    }
+    return v;
+  };
+  if constexpr (K == 256) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int qd = (tid + q * kSplitThreads) % QPS;
+      x[q] = jb.trans ? off_identity(x[q], qd % K, 32 * stage0 + 4 * (qd / K)) : off_identity(x[q], qd >> 3, 32 * stage0 + 4 * (qd & 7));
+    }
+  }
   float hsc = 1.f;   // float16 job: the block's scale
   if (jb.fscale) {
     // (an infinite entry must not set the scale: the block's other outputs would be scaled away.  Looked for only where there is one)
@@ -173,7 +191,9 @@ __global__ __launch_bounds__(kSplitThreads) void split_planes_kernel(const Split
 #pragma unroll
         for (int q = 0; q < NQ; ++q) take(x[q]);
       } else {
-        for (int e = tid * 4; e < K * K; e += kSplitThreads * 4) take(*reinterpret_cast<const float4*>(sb + e));
+#pragma unroll 8
+        for (int e = tid * 4; e < K * K; e += kSplitThreads * 4)
+          take(off_identity(*reinterpret_cast<const float4*>(sb + e), e / K, e % K));
       }
       m = cluster_allmax<64>(m);
       if (finite) __syncthreads();                                         // (the maxima before have been read)
@@ -733,10 +753,6 @@ int launch_split_planes_multi(const SplitRequest* req, int n, int K, int nb, hip
   CAFEQ_CHECK_LAUNCH();
   return CAFEQ_OK;
 }
-int launch_split_planes(const float* src, int K, int nb, int trans, int nplanes, uint16_t* dst, hipStream_t st) {
-  SplitRequest r{src, dst, trans, nplanes};
-  return launch_split_planes_multi(&r, 1, K, nb, st);
-}
 int launch_rho_groups(const float* rho, int K, int rep, int G, int64_t ngroups, float* rG, hipStream_t st) {
   const int wpg = G >= 1024 ? kRhoGroupWaves : 1, per = kRhoGroupWaves / wpg;
   hipLaunchKernelGGL(rho_group_kernel, dim3(unsigned((ngroups + per - 1) / per)), dim3(kRhoGroupWaves * kWave), 0, st, rho,
@@ -785,6 +801,7 @@ int launch_build_mmid(const CoreParams& p, int K, int G, int nb, const float* P,
                       hipStream_t st) {
   const VArgs a = mmid_args(p, K, K > G ? K : G, G, P, scale_rows, Mmid);
   hipLaunchKernelGGL(build_mmid_kernel, dim3(nb * kMmidParts), dim3(256), 0, st, a);
+    js.job[i].minus_one = req[i].minus_one;
   CAFEQ_CHECK_LAUNCH();
   return CAFEQ_OK;
 }

@@ -36,6 +36,8 @@ int launch_core_k32(int G, int axis, const CoreParams& p, hipStream_t st);
 int launch_core_k64(int G, int axis, const CoreParams& p, hipStream_t st);
 int launch_core_k128(int G, int axis, const CoreParams& p, hipStream_t st);
 int launch_core_k256(int G, int axis, const CoreParams& p, hipStream_t st);
+// xform256.hip: blocks of 256, groups inside the block, symmetric grid (p.fscale, p.fscale_inv: float16 planes, two parts each)
+int launch_xform256(int G, int axis, const CoreParams& p, hipStream_t st);
 // the same on the min/max grid of Eq. (1) (p.asym; gradient-free variants)
 int launch_core_asym_k32(int G, int axis, const CoreParams& p, hipStream_t st);
 int launch_core_asym_k64(int G, int axis, const CoreParams& p, hipStream_t st);
@@ -116,8 +118,8 @@ int launch_loss_prepared_pair(int K, int G, const CoreParams& pa, const CorePara
 // 16-byte vectors) instead of two runs of four (16c + 8u + 4h + e: operands read as float4 from float32 lines
 // and the accumulator registers of the inverse transform).
 // nplanes: a float16 job writes two parts, or three.  texp: a float16 job scales the block's largest magnitude into [2^texp, 2^(texp+1)).
-struct SplitRequest { const float* src; uint16_t* dst; int trans, nplanes; float* fscale = nullptr; int natural = 0; int texp = 14; };
-int launch_split_planes(const float* src, int K, int nb, int trans, int nplanes, uint16_t* dst, hipStream_t st);
+// minus_one (K = 256): of src - I instead of src.
+struct SplitRequest { const float* src; uint16_t* dst; int trans, nplanes; float* fscale = nullptr; int natural = 0; int texp = 14; int minus_one = 0; };
 // squared row / column norms of the blocks of P, and (rG != null; rho_groups_inline) their sums over groups of G indices
 struct RhoRequest { const float* P; float* rho; int by_row; float* rG = nullptr; int G = 0, rep = 1; };
 bool rho_groups_inline(int K, int nb, int G, int rep);

@@ -53,31 +53,6 @@ constexpr int v2_tile_bytes(int parts) { return 32 * 128 * 2 * parts; }
 // operand planes of a segment (T and T^-1, 64 KB each for blocks of 128), the waves' sums
 constexpr int v2_lds(int K) { return (2 * v2_fwd_parts(K) + 4) * 128 * K + kV2Waves * kHdrFloats * 4 + 64; }
 
-// Four arg-max scans, one step each: where |z| > |best|, best = z and its index J (strictly greater: the lowest index
-// wins).  A mask that a comparison leaves in scalar registers may be read two instructions later at the earliest; one scan
-// at a time, as the compiler arranges them, has a wait behind each of a strip's 64 comparisons (70 of the vector phase's
-// 680 issue slots, each two slots long).  Four comparisons side by side fill that distance: at least three instructions
-// lie between each and its first reader.
-template <int J>
-__device__ __forceinline__ void argmax4(float (&b)[4], int (&j)[4], float z0, float z1, float z2, float z3) {
-  uint64_t m0, m1, m2, m3;
-  asm("v_cmp_gt_f32_e64 %8, |%12|, |%0|\n\t"
-      "v_cmp_gt_f32_e64 %9, |%13|, |%1|\n\t"
-      "v_cmp_gt_f32_e64 %10, |%14|, |%2|\n\t"
-      "v_cmp_gt_f32_e64 %11, |%15|, |%3|\n\t"
-      "v_cndmask_b32_e64 %0, %0, %12, %8\n\t"
-      "v_cndmask_b32_e64 %4, %4, %16, %8\n\t"
-      "v_cndmask_b32_e64 %1, %1, %13, %9\n\t"
-      "v_cndmask_b32_e64 %5, %5, %16, %9\n\t"
-      "v_cndmask_b32_e64 %2, %2, %14, %10\n\t"
-      "v_cndmask_b32_e64 %6, %6, %16, %10\n\t"
-      "v_cndmask_b32_e64 %3, %3, %15, %11\n\t"
-      "v_cndmask_b32_e64 %7, %7, %16, %11"
-      : "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]), "+v"(j[0]), "+v"(j[1]), "+v"(j[2]), "+v"(j[3]), "=&s"(m0), "=&s"(m1),
-        "=&s"(m2), "=&s"(m3)
-      : "v"(z0), "v"(z1), "v"(z2), "v"(z3), "n"(J));
-}
-
 // Marks in a line's scale, a power of two: 32 (64) of its inputs are far smaller than the segment's largest
 constexpr uint32_t kFar32 = 1, kFar64 = 2;
 // A scaled weight as float16 parts.  (One part: the second is zero, or not a number behind an infinity, which then is none

@@ -187,6 +187,31 @@ __device__ __forceinline__ uint32_t pack_f16(float x0, float x1) {
 // clamped to the counter's 6 bits; a smaller n only waits for more).
 #define CAFEQ_VMW(N) case N: asm volatile("s_waitcnt vmcnt(" #N ")" ::: "memory"); break;
 __device__ __forceinline__ void vm_wait(int n) {
+// Four arg-max scans, one step each: where |z| > |best|, best = z and its index J (strictly greater: the lowest index
+// wins).  A mask that a comparison leaves in scalar registers may be read two instructions later at the earliest; one scan
+// at a time, as the compiler arranges them, has a wait behind each of a strip's 64 comparisons (70 of the vector phase's
+// 680 issue slots, each two slots long).  Four comparisons side by side fill that distance: at least three instructions
+// lie between each and its first reader.
+template <int J>
+__device__ __forceinline__ void argmax4(float (&b)[4], int (&j)[4], float z0, float z1, float z2, float z3) {
+  uint64_t m0, m1, m2, m3;
+  asm("v_cmp_gt_f32_e64 %8, |%12|, |%0|\n\t"
+      "v_cmp_gt_f32_e64 %9, |%13|, |%1|\n\t"
+      "v_cmp_gt_f32_e64 %10, |%14|, |%2|\n\t"
+      "v_cmp_gt_f32_e64 %11, |%15|, |%3|\n\t"
+      "v_cndmask_b32_e64 %0, %0, %12, %8\n\t"
+      "v_cndmask_b32_e64 %4, %4, %16, %8\n\t"
+      "v_cndmask_b32_e64 %1, %1, %13, %9\n\t"
+      "v_cndmask_b32_e64 %5, %5, %16, %9\n\t"
+      "v_cndmask_b32_e64 %2, %2, %14, %10\n\t"
+      "v_cndmask_b32_e64 %6, %6, %16, %10\n\t"
+      "v_cndmask_b32_e64 %3, %3, %15, %11\n\t"
+      "v_cndmask_b32_e64 %7, %7, %16, %11"
+      : "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]), "+v"(j[0]), "+v"(j[1]), "+v"(j[2]), "+v"(j[3]), "=&s"(m0), "=&s"(m1),
+        "=&s"(m2), "=&s"(m3)
+      : "v"(z0), "v"(z1), "v"(z2), "v"(z3), "n"(J));
+}
+
   switch (n > 63 ? 63 : n) {
     CAFEQ_VMW(0) CAFEQ_VMW(1) CAFEQ_VMW(2) CAFEQ_VMW(3) CAFEQ_VMW(4) CAFEQ_VMW(5) CAFEQ_VMW(6) CAFEQ_VMW(7)
     CAFEQ_VMW(8) CAFEQ_VMW(9) CAFEQ_VMW(10) CAFEQ_VMW(11) CAFEQ_VMW(12) CAFEQ_VMW(13) CAFEQ_VMW(14) CAFEQ_VMW(15)

@@ -1,0 +1,65 @@
+"""GPU parity of the pass over blocks of 256 whose groups lie inside a block (csrc/xform256.hip): two waves share a strip of 32
+lines, so row counts around its strips and macro-tiles of 128, every group length (256: one group for both waves), both axes, shared
+blocks, bfloat16 storage, grids of 2 to 8 bits; lines and blocks of any magnitude; transforms that only move weights."""
+import numpy as np
+import pytest
+
+from oracle import cafeq_oracle as O
+from paper_2511_19705_amd import workloads as WL
+from tests import parity
+from tests.test_gpu_single import _case, _check_single, _dev
+
+pytestmark = pytest.mark.gpu
+K = 256
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    from paper_2511_19705_amd import cafeq
+    return torch, cafeq
+
+
+@pytest.mark.parametrize("group,lines,axis,rep,bits,bf16", [
+    (32, 4, O.COL, 1, 4, False), (64, 32, O.ROW, 1, 3, False), (128, 36, O.COL, 1, 2, False), (256, 128, O.ROW, 2, 4, False),
+    (256, 132, O.COL, 1, 3, False), (64, 260, O.ROW, 2, 8, False), (128, 300, O.COL, 1, 8, True), (32, 392, O.ROW, 1, 2, True),
+    (64, 1, O.COL, 1, 4, True), (256, 96, O.COL, 1, 8, False)])
+def test_ragged_lines_and_groups(env, group, lines, axis, rep, bits, bf16):
+    W, T, P = _case(axis, lines, 1024, K, rep, 7000 + group + lines)
+    _check_single(env, W, T, P, bits, group, axis, rep, bf16=bf16)
+
+
+@pytest.mark.parametrize("axis", [O.COL, O.ROW])
+def test_magnitudes(env, axis):
+    """Lines of zeros, of one entry and scaled over 24 orders of magnitude; a transform of 1e-6 (bounds relative to each line)."""
+    torch, cafeq = env
+    W, T, P = _case(axis, 136, 512, K, 1, 7100)
+    L = W if axis == O.COL else W.T
+    L *= (10.0 ** np.linspace(-12, 12, 136)[:, None]).astype(np.float32)
+    L[5], L[6, 1:] = 0.0, 0.0
+    T = (T * 1e-6).astype(np.float32)
+    P = O.block_inverse(T).astype(np.float32)
+    Z = cafeq.apply_transform(_dev(torch, W), _dev(torch, T), _dev(torch, P), axis, cafeq.SIDE_T, 1).cpu().numpy()
+    ref = O.blockdiag_apply(W, T, axis, 1)
+    bound = O.blockdiag_apply(np.abs(W), np.abs(T), axis, 1) * (K * 2.0 ** -24)
+    assert np.all(np.abs(Z - ref) <= bound + 1e-300)
+    losses, _, codes, scales = cafeq.proxy_loss_fwd_bwd(_dev(torch, W), _dev(torch, T), _dev(torch, P), 4, 64, axis, want_grad=False, want_codes=True)
+    c_ref, s_ref, _ = O.rtn_sym(ref, 4, 64, axis)
+    parity.check_scales(scales.cpu().numpy(), s_ref)
+    parity.check_codes(codes.cpu().numpy(), c_ref, ref, s_ref, axis, 64, tie_tol=parity.tie_tolerance(W, T, axis, 1, ref, s_ref, 64, parity.forward_unit(K, 64, 4)))
+    parity.check_scalar(float(losses[0]), O.proxy_l2(W, T, P, 4, 64, axis, 1)["l2_sq"], what="l2_sq")
+
+
+@pytest.mark.parametrize("axis,group", [(O.COL, 64), (O.ROW, 256)])
+def test_moved_weights_are_moved_exactly(env, axis, group):
+    """Signed permutations: codes and scales are those of the moved matrix, bit for bit."""
+    torch, cafeq = env
+    rng = np.random.default_rng(7200)
+    T = np.stack([np.eye(K)[rng.permutation(K)] * rng.choice([-1.0, 1.0], (K, 1)) for _ in range(2)]).astype(np.float32)
+    W = WL.student_t3((200, 2 * K) if axis == O.COL else (2 * K, 200), 7201)
+    moved = O.blockdiag_apply(W, T, axis, 1).astype(np.float32)
+    _, _, codes, scales = cafeq.proxy_loss_fwd_bwd(_dev(torch, W), _dev(torch, T), _dev(torch, np.ascontiguousarray(T.transpose(0, 2, 1))), 4, group, axis,
+                                                   want_grad=False, want_codes=True)
+    c_ref, s_ref, _ = O.rtn_sym(moved, 4, group, axis)
+    np.testing.assert_array_equal(scales.cpu().numpy(), s_ref.astype(np.float32))
+    np.testing.assert_array_equal(codes.cpu().numpy(), c_ref)
