@@ -735,6 +735,7 @@ int launch_split_planes_multi(const SplitRequest* req, int n, int K, int nb, hip
     js.job[i].src = req[i].src; js.job[i].dst = req[i].dst;
     js.job[i].trans = req[i].trans; js.job[i].nplanes = req[i].nplanes;
     js.job[i].fscale = req[i].fscale; js.job[i].natural = req[i].natural; js.job[i].texp = req[i].texp;
+    js.job[i].minus_one = req[i].minus_one;
   }
   for (int i = 0; i < nrho; ++i) {
     if (rho[i].rG && !rho_groups_inline(K, nb, rho[i].G, rho[i].rep)) return CAFEQ_ERR_INVALID_ARG;
@@ -801,7 +802,6 @@ int launch_build_mmid(const CoreParams& p, int K, int G, int nb, const float* P,
                       hipStream_t st) {
   const VArgs a = mmid_args(p, K, K > G ? K : G, G, P, scale_rows, Mmid);
   hipLaunchKernelGGL(build_mmid_kernel, dim3(nb * kMmidParts), dim3(256), 0, st, a);
-    js.job[i].minus_one = req[i].minus_one;
   CAFEQ_CHECK_LAUNCH();
   return CAFEQ_OK;
 }

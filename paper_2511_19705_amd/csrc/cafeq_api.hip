@@ -1381,6 +1381,14 @@ int cafeq_dual_proxy_loss_fwd_bwd(const cafeq_mat* A, const cafeq_mat* B, const 
   return dual_impl(A, B, x, cfg, lse_t, losses, gradT, codesU, scalesU, codesV, scalesV, ws, stream, nullptr);
 }
 
+// the correction's operand planes (two float16 parts, of what it adds to the identity: the factors in the room of the third plane)
+static int split_correction(const AdaptiveWs& w, int k, int nb, const GroupPlan& gp, CoreParams* p, hipStream_t st) {
+  float* fs = core_halves(k, gp, false) ? reinterpret_cast<float*>(w.planes + size_t(nb) * 2 * k * k) : nullptr;
+  const SplitRequest req{w.Cmat, w.planes, 0, fs ? 2 : kFwdPlanes, fs, 0, 14, fs ? 1 : 0};
+  p->Afwd = w.planes; p->Ainv = nullptr; p->fscale = fs;
+  return launch_split_planes_multi(&req, 1, k, nb, st);
+}
+
 int cafeq_adaptive_round_step(const float* U, const float* V, int64_t rowsA, int64_t colsA, int64_t rowsB,
                               int64_t colsB, const cafeq_quant_cfg* cfg, int k, int nb, int rep, int half,
                               int8_t* codesU, float* scalesU, int8_t* codesV, float* scalesV, int* status,
@@ -1392,14 +1400,6 @@ int cafeq_adaptive_round_step(const float* U, const float* V, int64_t rowsA, int
   if (!supported_block(k)) return CAFEQ_ERR_UNSUPPORTED;
   if (nb <= 0 || rep <= 0 || rowsA <= 0 || colsB <= 0) return CAFEQ_ERR_BAD_SHAPE;
   if (colsA != int64_t(nb) * k || rowsB != int64_t(nb) * rep * k || colsB % 4 != 0) return CAFEQ_ERR_BAD_SHAPE;
-// the correction's operand planes (two float16 parts, of what it adds to the identity: the factors in the room of the third plane)
-static int split_correction(const AdaptiveWs& w, int k, int nb, const GroupPlan& gp, CoreParams* p, hipStream_t st) {
-  float* fs = core_halves(k, gp, false) ? reinterpret_cast<float*>(w.planes + size_t(nb) * 2 * k * k) : nullptr;
-  const SplitRequest req{w.Cmat, w.planes, 0, fs ? 2 : kFwdPlanes, fs, 0, 14, fs ? 1 : 0};
-  p->Afwd = w.planes; p->Ainv = nullptr; p->fscale = fs;
-  return launch_split_planes_multi(&req, 1, k, nb, st);
-}
-
   if (!aligned16(U) || !aligned16(V) || !aligned16(codesU) || !aligned16(codesV) || !aligned16(scalesU) ||
       !aligned16(scalesV))
     return CAFEQ_ERR_BAD_ALIGN;
@@ -1419,7 +1419,7 @@ static int split_correction(const AdaptiveWs& w, int k, int nb, const GroupPlan&
     cafeq_mat mv{V, rowsB, colsB, colsB, CAFEQ_F32};
     CoreParams p;
     fill_common(&p, &mv, ap.planV, rep);
-    if ((rc = split_correction(w, k, nb, ap.ga, &p, st))) return rc;
+    if ((rc = split_correction(w, k, nb, ap.gb, &p, st))) return rc;
     p.grid = grid; p.codes = codesV; p.scales = scalesV;
     if ((rc = run_core(k, CAFEQ_AXIS_ROW, ap.gb, p, w.rec, w.grec, false, st))) return rc;
   }
@@ -1432,7 +1432,7 @@ static int split_correction(const AdaptiveWs& w, int k, int nb, const GroupPlan&
     cafeq_mat mu{U, rowsA, colsA, colsA, CAFEQ_F32};
     CoreParams p;
     fill_common(&p, &mu, ap.planU, 1);
-    if ((rc = split_correction(w, k, nb, ap.gb, &p, st))) return rc;
+    if ((rc = split_correction(w, k, nb, ap.ga, &p, st))) return rc;
     p.grid = grid; p.codes = codesU; p.scales = scalesU;
     if ((rc = run_core(k, CAFEQ_AXIS_COL, ap.ga, p, w.rec, w.grec, false, st))) return rc;
   }

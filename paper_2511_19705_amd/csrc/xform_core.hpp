@@ -183,10 +183,6 @@ __device__ __forceinline__ uint32_t pack_f16(float x0, float x1) {
 }
 #define CAFEQ_MFMA_F16(A, B, C) __builtin_amdgcn_mfma_f32_32x32x16_f16((A), (B), (C), 0, 0, 0)
 
-// s_waitcnt vmcnt(n) for a value of n that is a compile-time constant after unrolling (n is
-// clamped to the counter's 6 bits; a smaller n only waits for more).
-#define CAFEQ_VMW(N) case N: asm volatile("s_waitcnt vmcnt(" #N ")" ::: "memory"); break;
-__device__ __forceinline__ void vm_wait(int n) {
 // Four arg-max scans, one step each: where |z| > |best|, best = z and its index J (strictly greater: the lowest index
 // wins).  A mask that a comparison leaves in scalar registers may be read two instructions later at the earliest; one scan
 // at a time, as the compiler arranges them, has a wait behind each of a strip's 64 comparisons (70 of the vector phase's
@@ -212,6 +208,10 @@ __device__ __forceinline__ void argmax4(float (&b)[4], int (&j)[4], float z0, fl
       : "v"(z0), "v"(z1), "v"(z2), "v"(z3), "n"(J));
 }
 
+// s_waitcnt vmcnt(n) for a value of n that is a compile-time constant after unrolling (n is
+// clamped to the counter's 6 bits; a smaller n only waits for more).
+#define CAFEQ_VMW(N) case N: asm volatile("s_waitcnt vmcnt(" #N ")" ::: "memory"); break;
+__device__ __forceinline__ void vm_wait(int n) {
   switch (n > 63 ? 63 : n) {
     CAFEQ_VMW(0) CAFEQ_VMW(1) CAFEQ_VMW(2) CAFEQ_VMW(3) CAFEQ_VMW(4) CAFEQ_VMW(5) CAFEQ_VMW(6) CAFEQ_VMW(7)
     CAFEQ_VMW(8) CAFEQ_VMW(9) CAFEQ_VMW(10) CAFEQ_VMW(11) CAFEQ_VMW(12) CAFEQ_VMW(13) CAFEQ_VMW(14) CAFEQ_VMW(15)
