@@ -655,46 +655,172 @@ __global__ __launch_bounds__(4 * K, XP > 1 ? 4 : 1) void bgemm_chain_kernel(cons
   }
 }
 
-// Blocks of 32, a workgroup per block: C = beta C + alpha (P^T G) P^T with X = P^T G in LDS (two launches with X in
-// memory before: 45 blocks 4.7 + 4.1 us, now 5.9).
+// Blocks of 32, a workgroup per block: (P^T G) P^T, X = P^T G in LDS (two launches with X in memory before: 45 blocks 4.7 + 4.1 us).  A thread
+// takes four neighbouring elements of a row, so that a step of either sum is one broadcast and one 16-byte read for four
+// multiply-adds (an element at a time, eight reads for them: the launch below 9.8 us at 8 blocks and 11.4 at 90, now 5.5 and 6.5).
+constexpr int kC32Ld = 36;                  // floats a row (16-byte vectors; eight rows of a wave in different banks)
+struct Chain32Lds {
+  float p[32 * kC32Ld], pt[32 * kC32Ld], g[32 * kC32Ld], x[32 * kC32Ld];   // P, P^T, G, X
+};
+// the thread's four elements of P (row tid / 8, columns 4 (tid % 8) ..) into both orders
+__device__ __forceinline__ void chain32_put(Chain32Lds& s, const float4 p) {
+  const int i = int(threadIdx.x) >> 3, j = 4 * (int(threadIdx.x) & 7);
+  *reinterpret_cast<float4*>(s.p + i * kC32Ld + j) = p;
+  s.pt[j * kC32Ld + i] = p.x; s.pt[(j + 1) * kC32Ld + i] = p.y; s.pt[(j + 2) * kC32Ld + i] = p.z; s.pt[(j + 3) * kC32Ld + i] = p.w;
+}
+// P, P^T and G are in LDS, behind a barrier: the thread's four elements of the product
+__device__ __forceinline__ float4 chain32(Chain32Lds& s) {
+  const int i = int(threadIdx.x) >> 3, j = 4 * (int(threadIdx.x) & 7);
+  auto product = [&](const float* a, int sa, const float* b) __attribute__((always_inline)) {
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int l = 0; l < 32; ++l) {
+      const float x = a[l * sa];
+      const float4 y = *reinterpret_cast<const float4*>(b + l * kC32Ld);
+      acc.x = fmaf(x, y.x, acc.x); acc.y = fmaf(x, y.y, acc.y); acc.z = fmaf(x, y.z, acc.z); acc.w = fmaf(x, y.w, acc.w);
+    }
+    return acc;
+  };
+  *reinterpret_cast<float4*>(s.x + i * kC32Ld + j) = product(s.p + i, kC32Ld, s.g + j);   // X[i][j] = sum_l P[l][i] G[l][j]
+  __syncthreads();
+  return product(s.x + i * kC32Ld, 1, s.pt + j);                                         // Y[i][j] = sum_l X[i][l] P[j][l]
+}
+struct UpdateOld4 { float4 t, m, v; };
+__device__ __forceinline__ UpdateOld4 update_load4(const UpdateHook& u, size_t at) {
+  UpdateOld4 o{};
+  if (u.T) {
+    o.t = *reinterpret_cast<const float4*>(u.T + at);
+    if (u.m) { o.m = *reinterpret_cast<const float4*>(u.m + at); o.v = *reinterpret_cast<const float4*>(u.v + at); }
+  }
+  return o;
+}
+__device__ __forceinline__ void update_store4(const UpdateHook& u, size_t at, float4 g, const UpdateOld4& o, float denom) {
+  update_store(u, at, g.x, UpdateOld{o.t.x, o.m.x, o.v.x}, denom);
+  update_store(u, at + 1, g.y, UpdateOld{o.t.y, o.m.y, o.v.y}, denom);
+  update_store(u, at + 2, g.z, UpdateOld{o.t.z, o.m.z, o.v.z}, denom);
+  update_store(u, at + 3, g.w, UpdateOld{o.t.w, o.m.w, o.v.w}, denom);
+}
+// C = beta C + alpha (P^T G) P^T
 __global__ __launch_bounds__(256) void bgemm_chain32_kernel(const float* __restrict__ P, const float* __restrict__ G,
                                                             float* __restrict__ C, float alpha, float beta,
                                                             const UpdateHook up) {
-  constexpr int K = 32;
-  __shared__ float sp[K][K + 1], sg[K][K + 1], sx[K][K + 1];
-  const size_t base = size_t(blockIdx.x) * K * K;
-  const int tid = threadIdx.x;
-  float cold[4];
-  UpdateOld old[4];
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int e = tid + 256 * u;
-    sp[e / K][e % K] = P[base + e];
-    sg[e / K][e % K] = G[base + e];
-    cold[u] = beta != 0.f ? C[base + e] : 0.f;
-    old[u] = update_load(up, base + e);
-  }
+  __shared__ __align__(16) Chain32Lds s;
+  const size_t at = size_t(blockIdx.x) * 1024 + 4 * threadIdx.x;
+  const float4 p = *reinterpret_cast<const float4*>(P + at), g = *reinterpret_cast<const float4*>(G + at);
+  const float4 cold = beta != 0.f ? *reinterpret_cast<const float4*>(C + at) : make_float4(0.f, 0.f, 0.f, 0.f);
+  const UpdateOld4 old = update_load4(up, at);
   const float denom = up.T && up.denom ? *up.denom : 1.f;
+  chain32_put(s, p);
+  *reinterpret_cast<float4*>(s.g + (threadIdx.x >> 3) * kC32Ld + 4 * (threadIdx.x & 7)) = g;
   __syncthreads();
+  const float4 y = chain32(s);
+  const float4 r = beta != 0.f ? make_float4(alpha * y.x + beta * cold.x, alpha * y.y + beta * cold.y, alpha * y.z + beta * cold.z,
+                                             alpha * y.w + beta * cold.w)
+                               : make_float4(alpha * y.x, alpha * y.y, alpha * y.z, alpha * y.w);
+  if (up.T) update_store4(up, at, r, old, denom);
+  else *reinterpret_cast<float4*>(C + at) = r;
+}
+
+// What follows the loss / gradient kernel of a single matrix with blocks of 32, in one launch: a workgroup per block sums its
+// partials, forms the middle factor and adds its way through the inverse (the work of single_tail_kernel and
+// bgemm_chain32_kernel, sums in their order, nothing of it through memory in between); one more workgroup reduces the losses.
+// A gradient-descent step that divides by ||W||^2 sums it from the headers itself, in that workgroup's order.
+// Bound: the latencies of headers and partials, each with eight requests in flight: 5.5 us at
+// 8 blocks, 6.5 at 90, against 4.0 + 5.7 and 4.9 + 5.7 in two launches.
+__global__ __launch_bounds__(256) void tail_chain32_kernel(const ReduceArgs ra, const VArgs va, const LossArgs la, const float* __restrict__ P,
+                                                           const UpdateHook up) {
+  constexpr int K = 32;
+  __shared__ __align__(16) Chain32Lds s;
+  __shared__ __align__(16) float v[K];
+  __shared__ double red[5 * (kLossThreads / 64)];
+  const int tid = threadIdx.x;
+  if (blockIdx.x == 0) {
+    double m, sm;
+    reduce_losses_body<kLossThreads>(la, red, true, &m, &sm);
+    return;
+  }
+  const int b = int(blockIdx.x) - 1, i = tid >> 3, j = 4 * (tid & 7);
+  const size_t at = size_t(b) * K * K + 4 * tid;
+  const float4 p = *reinterpret_cast<const float4*>(P + at);
+  const UpdateOld4 old = update_load4(up, at);
+  double wsq = 0;
+  if (up.denom) {
+    float t[4];
+    for (int k0 = tid; k0 < la.nslotA; k0 += 4 * kLossThreads) {
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int i = (tid + 256 * u) / K, j = tid % K;
-    float acc = 0.f;
+      for (int u = 0; u < 4; ++u) t[u] = k0 + u * kLossThreads < la.nslotA ? la.hdrA[size_t(k0 + u * kLossThreads) * kHdrFloats + kHdrWsq] : 0.f;
 #pragma unroll
-    for (int l = 0; l < K; ++l) acc = fmaf(sp[l][i], sg[l][j], acc);
-    sx[i][j] = acc;
+      for (int u = 0; u < 4; ++u) wsq += t[u];
+    }
+  }
+  // the middle factor's v: thread n (of every 32 the same) index n, the headers' order
+  double vn = 0;
+  for (int q = b * va.rep; q < (b + 1) * va.rep; ++q) {
+    // (segments and groups of 32 to 256: powers of two)
+    const int64_t ax = int64_t(q) * K + tid % K, seg = ax >> __builtin_ctz(va.L);
+    const float* h0 = va.slot_hdr + seg * kHdrFloats + kHdrVa2 + ((int(ax) & (va.L - 1)) >> __builtin_ctz(va.G));
+    int lo, hi;
+    seg_wg_range(seg, va.mt_per_seg, va.n_mt, va.nwg, &lo, &hi);
+    for (int w0 = lo; w0 < hi; w0 += 8) {
+      float t[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) t[u] = w0 + u < hi ? h0[int64_t(w0 + u) * kHdrFloats] : 0.f;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) vn += t[u];
+    }
+  }
+  // the gradient's partials: four inputs of output row i
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int q = b * ra.rep; q < (b + 1) * ra.rep; ++q) {
+    const int64_t ax = int64_t(q) * K, seg = ax >> __builtin_ctz(ra.seg_len);
+    const float* part = ra.slot_grad + seg * ra.part_floats + (int(ax) & (ra.seg_len - 1)) * K + 4 * tid;
+    int lo, hi;
+    seg_wg_range(seg, ra.mt_per_seg, ra.n_mt, ra.nwg, &lo, &hi);
+    for (int w0 = lo; w0 < hi; w0 += 8) {
+      float4 t[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        t[u] = w0 + u < hi ? *reinterpret_cast<const float4*>(part + int64_t(w0 + u) * ra.part_floats) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) { acc.x += t[u].x; acc.y += t[u].y; acc.z += t[u].z; acc.w += t[u].w; }
+    }
+  }
+  if (tid < K) v[tid] = float(vn * va.beta);
+  chain32_put(s, p);
+  if (up.denom) {
+#pragma unroll
+    for (int k = 1; k < 64; k <<= 1) wsq += __shfl_xor(wsq, k);
+    if ((tid & 63) == 0) red[tid >> 6] = wsq;
   }
   __syncthreads();
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int e = tid + 256 * u, i = e / K, j = e % K;
-    float acc = 0.f;
-#pragma unroll
-    for (int l = 0; l < K; ++l) acc = fmaf(sx[i][l], sp[j][l], acc);
-    const float g = alpha * acc + (beta != 0.f ? beta * cold[u] : 0.f);
-    if (up.T) update_store(up, base + e, g, old[u], denom);
-    else C[base + e] = g;
+  {
+    float4 g = p;
+    if (va.scale_rows) {
+      const float f = v[i];
+      g.x *= f; g.y *= f; g.z *= f; g.w *= f;
+    } else {
+      const float4 f = *reinterpret_cast<const float4*>(v + j);
+      g.x *= f.x; g.y *= f.y; g.z *= f.z; g.w *= f.w;
+    }
+    *reinterpret_cast<float4*>(s.g + i * kC32Ld + j) = g;
   }
+  __syncthreads();
+  const float4 y = chain32(s);
+  if (ra.transpose_out) {
+    // out[m][j] = acc[j][m]: through G's room, which the first product is done with
+    s.g[j * kC32Ld + i] = acc.x; s.g[(j + 1) * kC32Ld + i] = acc.y; s.g[(j + 2) * kC32Ld + i] = acc.z; s.g[(j + 3) * kC32Ld + i] = acc.w;
+    __syncthreads();
+    acc = *reinterpret_cast<const float4*>(s.g + i * kC32Ld + j);
+  }
+  const float4 r = make_float4(-2.f * y.x + acc.x, -2.f * y.y + acc.y, -2.f * y.z + acc.z, -2.f * y.w + acc.w);
+  float denom = 1.f;
+  if (up.denom) {
+    double t = 0;
+    for (int k = 0; k < kLossThreads / 64; ++k) t += red[k];
+    denom = float(t);
+  }
+  if (up.T) update_store4(up, at, r, old, denom);
+  else *reinterpret_cast<float4*>(ra.out + at) = r;
 }
 
 // K == 32: one 32 x 32 product per workgroup, C = alpha A B + beta C
@@ -816,6 +942,21 @@ int launch_single_tail(const CoreParams& pgrad, const CoreParams& ploss, int K, 
   const int nred_x = nb, nred_y = (K * K + 1023) / 1024;
   hipLaunchKernelGGL(single_tail_kernel, dim3(unsigned(nred_x * nred_y + nb * kMmidParts + 1)), dim3(256), 0, st, ra, va, la,
                      nred_x, nred_y, nb);
+  CAFEQ_CHECK_LAUNCH();
+  return CAFEQ_OK;
+}
+// the same with the gradient's way through the inverse and the update (blocks of 32; hook->denom, if any: losses[2])
+int launch_tail_chain32(const CoreParams& pgrad, const CoreParams& ploss, int G, bool fused, int nb, int transpose_out, float* gradT,
+                        const float* P, int scale_rows, float beta, int nslot, float* losses, double* lse_ms, hipStream_t st,
+                        const UpdateHook* hook) {
+  constexpr int K = 32;
+  if (hook && hook->denom && hook->denom != losses + 2) return CAFEQ_ERR_INVALID_ARG;
+  const ReduceArgs ra = reduce_args(pgrad, K, G, fused, transpose_out, nullptr, nullptr, gradT);
+  const VArgs va = mmid_args(ploss, K, K > G ? K : G, G, P, scale_rows, nullptr);
+  LossArgs la{};
+  la.hdrA = ploss.slot_hdr; la.nslotA = nslot; la.kind = kLossSur; la.beta = beta; la.losses = losses;
+  la.lse_ms = lse_ms;
+  hipLaunchKernelGGL(tail_chain32_kernel, dim3(unsigned(nb + 1)), dim3(256), 0, st, ra, va, la, P, hook ? *hook : UpdateHook{});
   CAFEQ_CHECK_LAUNCH();
   return CAFEQ_OK;
 }

@@ -1200,6 +1200,9 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
       if (pp.two &&
           (rc = run_grad_pass(K, cfg->axis, W, x->rep, pp, w.m, kLossSur, beta, 0.f, nullptr, 0, nullptr, &pg, st)))
         return rc;
+      if (K == 32)
+        return launch_tail_chain32(pg, p, gp.Gk, pp.fused, nb, col ? 1 : 0, gradT, x->Tinv, col ? 1 : 0, beta, int(pl.nslot), losses, w.lse_ms,
+                                   st, hook);
       // gradient reduction, the middle factor of the rho path and the loss reduction in one launch
       if ((rc = launch_single_tail(pg, p, K, gp.Gk, pp.fused, nb, col ? 1 : 0, gradT, x->Tinv, col ? 1 : 0, w.mmid, beta,
                                    int(pl.nslot), losses, w.lse_ms, st)))

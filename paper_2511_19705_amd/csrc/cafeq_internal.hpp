@@ -144,6 +144,10 @@ int launch_reduce_losses(int kind, const float* hdrA, int nslotA, const float* h
 // alpha op(A) op(B) + beta C is taken as the gradient of element [b][i][j] and T (and m, v) are updated in place (C is
 // only read).  m != null: the Adam step.  m == null: gradient descent, the gradient first divided by *denom if given.
 struct UpdateHook { float *T, *m, *v; float lr, beta1, omb1, beta2, omb2, eps, c1, c2; const float* denom; };
+// blocks of 32: launch_single_tail with the gradient's way through the inverse, and the update, in the same launch
+int launch_tail_chain32(const CoreParams& pgrad, const CoreParams& ploss, int G, bool fused, int nb, int transpose_out, float* gradT,
+                        const float* P, int scale_rows, float beta, int nslot, float* losses, double* lse_ms, hipStream_t st,
+                        const UpdateHook* hook);
 // C = alpha op(A) op(B) + beta C per block
 int launch_bgemm(bool ta, bool tb, const float* A, const float* B, float* C, int K, int nb, float alpha,
                  float beta, hipStream_t st, const UpdateHook* hook = nullptr);

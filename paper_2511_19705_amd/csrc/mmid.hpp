@@ -7,7 +7,17 @@
 namespace cafeq {
 
 // workgroups whose chunk of macro-tiles intersects segment `seg`: [lo, hi)
+// (the divisions, a few hundred instructions each in 64 bits, in 32 where they fit)
 __device__ __forceinline__ void seg_wg_range(int64_t seg, int64_t mt_per_seg, int64_t n_mt, int nwg, int* lo, int* hi) {
+  if (uint64_t(n_mt) * uint64_t(nwg + 1) < (uint64_t(1) << 32)) {
+    const uint32_t n = uint32_t(n_mt), g = uint32_t(nwg), t0 = uint32_t(seg * mt_per_seg), t1 = t0 + uint32_t(mt_per_seg);
+    // the last workgroup that begins at or before t0, the first that begins at or behind t1: w n / g rounded down is
+    // below t where w n < t g
+    const uint32_t a = ((t0 + 1) * g - 1) / n, b = (t1 * g + n - 1) / n;
+    *lo = int(a < g ? a : g - 1);
+    *hi = int(b < g ? b : g);
+    return;
+  }
   const int64_t t0 = seg * mt_per_seg, t1 = t0 + mt_per_seg;
   int a = int((t0 * nwg) / n_mt);
   while (a > 0 && chunk_begin(a, n_mt, nwg) > t0) --a;
