@@ -288,6 +288,7 @@ struct MemberWs {
   uint16_t *pfwd, *pinv;
   float2 *rec, *grec;
   float2 *rec_mm, *grec_mm;   // min/max grid with groups that span segments
+  float* zkeep;               // groups that span segments: the transformed weights between the sweeps
   uint2* sorted; int* start;  // gradient pass by records
 };
 void carve_member(Carver& c, const PassPlans& pp, int nb, bool grad, bool want_rG, MemberWs* w) {
@@ -306,6 +307,7 @@ void carve_member(Carver& c, const PassPlans& pp, int nb, bool grad, bool want_r
   w->rec_mm = c.take<float2>(mm ? size_t(pl.naxis / pl.G) * size_t(pl.nlines) : 0);
   w->grec_mm = c.take<float2>(mm ? size_t(pl.naxis / pp.gp.G) * size_t(pl.nlines) : 0);
   if (!mm) w->rec_mm = w->grec_mm = nullptr;
+  w->zkeep = big && pl.K >= kKeepBlock ? c.take<float>(size_t(pl.n_mt) * kMacroLines * size_t(pl.L)) : nullptr;
   w->sorted = c.take<uint2>(pp.gather ? grad_gather_entries(pl.K, pp.gp.G, pl.naxis, pl.nlines) : 0);
   w->start = c.take<int>(pp.gather ? grad_gather_starts(pl.K, pp.gp.G, pl.naxis) : 0);
 }
@@ -466,6 +468,7 @@ void fill_common(CoreParams* p, const cafeq_mat* W, const CorePlan& pl, int rep)
   p->longg = 0; p->gspan = 1; p->grec = nullptr; p->grp = 0;
   p->prep_planes = nullptr; p->prep_lscale = nullptr; p->prep_wsq = nullptr; p->fscale_inv = nullptr;
   p->prep_gtiles = nullptr; p->prep_lines = nullptr;
+  p->zkeep = nullptr; p->sweep = 0;
   p->asym = 0; p->mins = nullptr; p->rec_mm = nullptr; p->grec_mm = nullptr;
   p->grid = make_grid(4);
 }
@@ -484,11 +487,11 @@ void set_prepared(CoreParams* p, const cafeq_mat* W, int axis) {
 // Forward sweep(s) of the fused core over one matrix.  `p` holds everything but the group bookkeeping.  For
 // groups inside a segment this is one launch.  For groups that span gspan segments: a forward-only sweep that
 // records every segment's arg-max, the combination of the records per group, then the sweep proper, which
-// takes each group's absmax from the combined records (both sweeps run the same kernel variant, so they see
-// bit-identical transformed weights).
+// takes each group's absmax from the combined records (both sweeps run the same kernel variant, or the second one reads what the
+// first one left in zkeep, so they see bit-identical transformed weights).
 int run_core(int K, int axis, const GroupPlan& gp, CoreParams p, float2* rec, float2* grec, bool want_rec,
              hipStream_t st, const cafeq_mat* prepared_of = nullptr, float2* rec_mm = nullptr,
-             float2* grec_mm = nullptr) {
+             float2* grec_mm = nullptr, float* zkeep = nullptr) {
   int rc;
   if (prepared_of) {
     // loss pass over the prepared copy of the weights
@@ -499,13 +502,14 @@ int run_core(int K, int axis, const GroupPlan& gp, CoreParams p, float2* rec, fl
   if (gp.gspan > 1) {
     CoreParams s1 = p;
     s1.do_inverse = 0; s1.do_grad = 0; s1.codes = nullptr; s1.scales = nullptr; s1.Zout = nullptr;
-    s1.slot_hdr = nullptr; s1.slot_grad = nullptr; s1.rec = rec; s1.longg = 1; s1.gspan = 1; s1.grec = nullptr;
+    s1.slot_hdr = zkeep ? p.slot_hdr : nullptr; s1.slot_grad = nullptr; s1.zkeep = zkeep; s1.sweep = zkeep ? 1 : 0; s1.rec = rec; s1.longg = 1; s1.gspan = 1; s1.grec = nullptr;
     s1.mins = nullptr; s1.rec_mm = p.asym ? rec_mm : nullptr;
     if (p.asym && (!rec_mm || !grec_mm)) return CAFEQ_ERR_INVALID_ARG;
     if ((rc = launch_core(K, gp.Gk, axis, s1, st))) return rc;
     if ((rc = launch_combine_records(rec, gp.gspan, gp.Gk, p.nlines, (p.nseg / gp.gspan), grec, st,
                                      p.asym ? rec_mm : nullptr, p.asym ? grec_mm : nullptr)))
       return rc;
+    p.zkeep = zkeep; p.sweep = zkeep ? 2 : 0;
     p.longg = 1; p.gspan = gp.gspan; p.grec = grec; p.rec = nullptr; p.grec_mm = p.asym ? grec_mm : nullptr;
   } else {
     p.rec = want_rec ? rec : nullptr;
@@ -1168,7 +1172,7 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
   p.rG = w.m.rG; p.codes = codes; p.scales = scales; p.slot_grad = w.m.slot_grad; p.slot_hdr = w.slot_hdr;
   p.asym = asym ? 1 : 0;
   p.mins = asym && scales ? scales + nlines * (naxis / gp.G) : nullptr;   // the minima follow the scales
-  if ((rc = run_core(K, cfg->axis, gp, p, w.m.rec, w.m.grec, pp.two, st, v2 ? W : nullptr, w.m.rec_mm, w.m.grec_mm)))
+  if ((rc = run_core(K, cfg->axis, gp, p, w.m.rec, w.m.grec, pp.two, st, v2 ? W : nullptr, w.m.rec_mm, w.m.grec_mm, w.m.zkeep)))
     return rc;
   const cafeq_mat* mats[1] = {W};
   const PassPlans* pps[1] = {&pp};
@@ -1328,7 +1332,7 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
     b.rec = qb.two ? w.b.rec : nullptr;
     if ((rc = launch_loss_prepared_pair(K, ga.Gk, a, b, st))) return rc;
   } else if ((rc = run_core(K, CAFEQ_AXIS_COL, ga, a, w.a.rec, w.a.grec, qa.two, st, v2A ? A : nullptr, w.a.rec_mm,
-                            w.a.grec_mm))) {
+                            w.a.grec_mm, w.a.zkeep))) {
     return rc;
   }
   ag = a;
@@ -1336,7 +1340,7 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
                                               w.member_ref, &ag, st)))
     return rc;
   if (!pair_launch && (rc = run_core(K, CAFEQ_AXIS_ROW, gb, b, w.b.rec, w.b.grec, qb.two, st, v2B ? B : nullptr, w.b.rec_mm,
-                                     w.b.grec_mm)))
+                                     w.b.grec_mm, w.b.zkeep)))
     return rc;
   bg = b;
   if (!gather && !owner && qb.two && (rc = run_grad_pass(K, CAFEQ_AXIS_ROW, B, x->rep, qb, w.b, kLossLse, 0.f, lse_t, w.hdrB, int(pb.nslot),

@@ -94,6 +94,13 @@ struct Geo {
 
 enum : int { kLossSur = 0, kLossLse = 1 };
 
+// Groups that span segments: from this block size on the loss sweep of a loss call reads the transformed weights that the
+// record sweep left (4 bytes a weight written, which the memory-side cache mostly still holds) instead of transforming again.
+// Evaluations transforming again / keeping, us: 2304 x 9216 whole channels, k = 32 120 / 117, on the min/max grid 123 / 123, 300 x 1024
+// 51 / 54; k = 64 130 / 124, 135 / 128, 57 / 53; k = 128 164 / 155, 82 / 77 (min/max, sweeps 53 + 53 -> 52 + 39); k = 256 536 / 485, 294 / 263;
+// 2B-shaped pair in bfloat16 at k = 128 303 / 235, 9B-shaped (V, O) pair 417 / 356, at k = 32 the 2B-shaped 197 / 200.
+constexpr int kKeepBlock = 64;
+
 struct CoreParams {
   const void* W;
   int dtype;
@@ -147,6 +154,10 @@ struct CoreParams {
   float* mins;
   float2* rec_mm;           // [nseg][nlines] (record sweep of the long-group variant)
   const float2* grec_mm;    // [groups][nlines] (loss sweep with gspan > 1)
+  // Groups that span segments, loss calls: the record sweep leaves the transformed weights here, [macro-tile][wave][step of eight
+  // indices][lane][4], and ||W||^2 in the headers; the loss sweep takes them from there instead of transforming again.
+  float* zkeep;
+  int sweep;                // 1, 2: which of the two (0: neither keeps nor takes)
 };
 
 __device__ __forceinline__ int64_t chunk_begin(int64_t w, int64_t n_mt, int64_t nwg) {
@@ -303,10 +314,18 @@ __device__ __forceinline__ void load_strip(const CoreParams& p, float (&wreg)[L 
 // the kernel): its record-only sweep and its loss sweep with the group's absmax taken from the combined records.
 // ASYM: the min/max grid of Eq. (1) instead of the symmetric absmax grid (gradient-free variants only: the
 // gradient of the surrogate depends on the grid through a constant alone and runs from the records).
-template <int K, int G, int AXIS, bool GRAD, bool F16 = false, bool LONGG = false, bool ASYM = false>
+// SWEEP, the two sweeps of a loss call over groups that span segments, apart: 1 the record sweep, which leaves the transformed
+// weights in CoreParams::zkeep, 2 the loss sweep from there, without a forward transform; 0 whatever the parameters say.
+template <int K, int G, int AXIS, bool GRAD, bool F16 = false, bool LONGG = false, bool ASYM = false, int SWEEP = 0>
 __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) void xform_core_kernel(const CoreParams p) {
   static_assert(!F16 || (!GRAD && Geo<K, G>::NBLK == 1), "half-precision forward: gradient-free, one block per segment");
   static_assert(!ASYM || !GRAD, "min/max grid: gradient-free");
+  static_assert(SWEEP == 0 || (LONGG && K >= kKeepBlock), "sweeps: groups that span segments");
+  constexpr bool ZIN = SWEEP == 2, keep = SWEEP == 1;
+  static_assert(!ZIN || !F16, "no forward transform");
+  const bool do_inverse = SWEEP == 0 ? p.do_inverse != 0 : ZIN;
+  int8_t* const out_codes = keep ? nullptr : p.codes;
+  float* const out_scales = keep ? nullptr : p.scales;
   static_assert(!LONGG || (!GRAD && Geo<K, G>::NGRP == 1), "long groups: gradient-free, one group per segment");
   using g = Geo<K, G>;
   constexpr bool GRAD_ON = GRAD && g::GRAD_OK;
@@ -343,7 +362,7 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
   constexpr int FWDP = F16 ? 2 : kFwdPlanes;                 // operand planes of a forward stage
   constexpr int NFW = FWDP * PLANEB / 16 / kThreads;         // loads every wave issues per forward stage
   constexpr int NIW = kInvPlanes * PLANEB / 16 / kThreads;   // ... per inverse stage (K = 32: some waves one more)
-  constexpr int NWL = AXIS == CAFEQ_AXIS_COL ? L / 8 : L / 2; // load instructions of one strip's weights
+  constexpr int NWL = AXIS == CAFEQ_AXIS_COL || ZIN ? L / 8 : L / 2; // load instructions of one strip's weights
   const uint32_t voff = uint32_t(tid) * 16u;
   auto blk_id = [&](int sg_, int blk) {
     const int gb = sg_ * NBLK + blk;
@@ -373,8 +392,8 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
 #pragma unroll
   for (int i = 0; i < NBLK; ++i) cb[i] = nbk[i] = blk_id(seg_first, i);
 
-  dma(p.Afwd, FWDP, cb[0], 0, 0);
-  if (D == 2) dma(p.Afwd, FWDP, cb[1 / KT], 1 % KT, 1);
+  dma(ZIN ? p.Ainv : p.Afwd, ZIN ? kInvPlanes : FWDP, cb[0], 0, 0);
+  if (D == 2) dma(ZIN ? p.Ainv : p.Afwd, ZIN ? kInvPlanes : FWDP, cb[1 / KT], 1 % KT, 1);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
 
@@ -415,6 +434,7 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
 #pragma unroll
       for (int ww = 0; ww < kNW; ++ww) t += hred[ww * kHdrFloats + tid];
       if (tid == kHdrMref) t = m_ref;
+      if (ZIN && tid == kHdrWsq) t = p.slot_hdr[slot * kHdrFloats + kHdrWsq];   // (the sweep before)
       p.slot_hdr[slot * kHdrFloats + tid] = t;
     }
     if constexpr (GRAD_ON) if (p.do_grad) {
@@ -446,13 +466,27 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
   // ---- weights of a strip, loaded one macro-tile ahead (after the last use of the previous
   // strip's weights)
   float wreg[L / 2];
-  auto load_w = [&](int seg, int mis) { load_strip<L, AXIS>(p, wreg, seg, mis, wave, ln, h); };
+  auto kept = [&](int seg, int mis) {
+    return reinterpret_cast<float4*>(p.zkeep) + ((int64_t(seg) * mt_per_seg + mis) * kNW + wave_u) * (L / 8) * 64 + lane;
+  };
+  auto load_w = [&](int seg, int mis) {
+    if constexpr (ZIN) {
+      const float4* src = kept(seg, mis);
+#pragma unroll
+      for (int c = 0; c < L / 8; ++c) {
+        const float4 v = src[c * 64];
+        wreg[4 * c] = v.x; wreg[4 * c + 1] = v.y; wreg[4 * c + 2] = v.z; wreg[4 * c + 3] = v.w;
+      }
+    } else {
+      load_strip<L, AXIS>(p, wreg, seg, mis, wave, ln, h);
+    }
+  };
   load_w(seg_first, mis_first);
 
   int seg = seg_first, mis = mis_first;
   for (int64_t mt = mt0; mt < mt1; ++mt) {
     if (seg != cur_seg) {
-      if (p.do_inverse || p.do_grad) flush(cur_seg);   // partial buffers exist only for loss calls
+      if (do_inverse || p.do_grad || keep) flush(cur_seg);   // partial buffers exist only for loss calls
       cur_seg = seg;
     }
     const int64_t line = int64_t(mis) * kMacroLines + wave * kStripLines + ln;
@@ -493,12 +527,12 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
+      for (int v = 0; v < 16; ++v) acc[t][v] = ZIN ? wreg[16 * t + v] : 0.f;
     const int swz = (ln >> 2) & 3;
     const int aoff0 = ln * 64 + ((h ^ swz) << 4), aoff1 = ln * 64 + (((2 + h) ^ swz) << 4);
     unsigned char* wcol = wst + (wave * kStripLines + ln) * 2;
 #pragma unroll
-    for (int sg = 0; sg < NT; ++sg) {               // stage = 32 inputs; sg / KT is the block
+    for (int sg = 0; sg < (ZIN ? 0 : NT); ++sg) {   // stage = 32 inputs; sg / KT is the block
       int nw = NFW;
       {
         const int tq = sg + D, dst = stage == 0 ? NSTG - 1 : stage - 1;
@@ -506,7 +540,7 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
           dma(p.Afwd, FWDP, cb[tq / KT], tq % KT, dst);
         } else {
           nw = NIW;
-          if (p.do_inverse) dma(p.Ainv, kInvPlanes, cb[(tq - NT) / KT], (tq - NT) % KT, dst);
+          if (do_inverse) dma(p.Ainv, kInvPlanes, cb[(tq - NT) / KT], (tq - NT) % KT, dst);
           else dma(p.Afwd, FWDP, nbk[(tq - NT) / KT], (tq - NT) % KT, dst);
         }
       }
@@ -520,7 +554,7 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const float x0 = wreg[8 * c + 2 * i], x1 = wreg[8 * c + 2 * i + 1];
-            if (p.do_inverse) s_wsq = fmaf(x0, x0, fmaf(x1, x1, s_wsq));
+            if (do_inverse || keep) s_wsq = fmaf(x0, x0, fmaf(x1, x1, s_wsq));
             const float y0 = x0 * wsc, y1 = x1 * wsc;
             if constexpr (ASYM) {
               bh[i] = pack_f16(y0, y1);
@@ -562,7 +596,7 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const float x0 = wreg[8 * c + 2 * i], x1 = wreg[8 * c + 2 * i + 1];
-          if (p.do_inverse) s_wsq = fmaf(x0, x0, fmaf(x1, x1, s_wsq));
+          if (do_inverse || keep) s_wsq = fmaf(x0, x0, fmaf(x1, x1, s_wsq));
           const uint32_t ph = pack_bf16(x0, x1);
           const float r0 = x0 - bf16_lo_f32(ph), r1 = x1 - bf16_hi_f32(ph);
           const uint32_t pm = pack_bf16(r0, r1);
@@ -623,8 +657,15 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
         for (int v = 0; v < 16; ++v) acc[t][v] *= usc;
     }
 
+    if (keep) {
+      float4* dst = kept(seg, mis);
+#pragma unroll
+      for (int c = 0; c < L / 8; ++c)
+        dst[c * 64] = make_float4(acc[c / 4][4 * (c % 4)], acc[c / 4][4 * (c % 4) + 1], acc[c / 4][4 * (c % 4) + 2], acc[c / 4][4 * (c % 4) + 3]);
+    }
+
     // ---- optional raw output Z
-    if (p.Zout && valid) {
+    if (SWEEP == 0 && p.Zout && valid) {
       if (AXIS == CAFEQ_AXIS_COL) {
         float* dst = p.Zout + line * p.cols + ax0 + 4 * h;
 #pragma unroll
@@ -647,10 +688,10 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
     }
 
     float err[L / 2];   // quantization error E = dequant(Q(Z)) - Z, same layout as the accumulators
-    const bool want_q = p.codes || p.scales || p.do_inverse || (LONGG && p.rec);
-    const bool big = LONGG && p.gspan > 1;                           // the group spans several segments
+    const bool want_q = keep || out_codes || out_scales || do_inverse || (LONGG && p.rec);
+    const bool big = LONGG && (ZIN || (!keep && p.gspan > 1));                           // the group spans several segments
     const bool first_of_group = !big || seg % p.gspan == 0;          // group-level sums are taken once
-    const bool lse_on = p.loss_kind == kLossLse && p.do_inverse;
+    const bool lse_on = p.loss_kind == kLossLse && do_inverse;
     if (want_q) {
       // ---- per-group absmax (+ argmax), codes, error in place
       float gz[NGRP];   // signed value at the arg-max element
@@ -699,12 +740,12 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
           }
         }
         gz[gi] = zs; gj[gi] = j;
-        if constexpr (LONGG) if (!(p.codes || p.scales || p.do_inverse)) continue;   // record-only sweep
+        if constexpr (LONGG) if (!(out_codes || out_scales || do_inverse)) continue;   // record-only sweep
         // symmetric grid: steps of absmax / qmax around zero; Eq. (1): steps of (max - min) / levels from min
         const float span = ASYM ? mx - mn : a;
         const float inv = grid_inv(span, p.grid.qmax);
         const float s = grid_scale(span, p.grid.qmax);
-        if (p.scales && valid && h == 0 && first_of_group) {
+        if (out_scales && valid && h == 0 && first_of_group) {
           int64_t at;
           if (big) {
             const int64_t gidx = seg / p.gspan, ng = p.nseg / p.gspan;
@@ -713,7 +754,7 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
             const int64_t gidx = ax0 / G + gi;   // group index along the axis
             at = AXIS == CAFEQ_AXIS_COL ? line * (p.cols / G) + gidx : gidx * p.cols + line;
           }
-          p.scales[at] = s;
+          out_scales[at] = s;
           if constexpr (ASYM) if (p.mins) p.mins[at] = mn;
         }
 #pragma unroll
@@ -736,22 +777,23 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
           }
           qpk[f4] = pack4(q[0], q[1], q[2], q[3]);
         }
-        if (p.do_inverse) {
+        if (do_inverse) {
           const float a2 = a * a;
           if (h == 0) s_va2[gi] += a2;
           if (p.loss_kind == kLossSur && h == 0) s_sur = fmaf(a2, p.rG[seg * NGRP + gi], s_sur);
         }
       }
 
-      if (p.codes && valid) {
+      asm volatile("" : "+v"(s_errz));   // (summed here, not where the inverse transform has no registers for the errors)
+      if (out_codes && valid) {
 #pragma unroll
         for (int f4 = 0; f4 < L / 8; ++f4) {
           const int j0 = 8 * f4 + 4 * h;
           if (AXIS == CAFEQ_AXIS_COL) {
-            *reinterpret_cast<uint32_t*>(p.codes + line * p.cols + ax0 + j0) = qpk[f4];
+            *reinterpret_cast<uint32_t*>(out_codes + line * p.cols + ax0 + j0) = qpk[f4];
           } else {
             // uniform row pointer + 32-bit lane offset
-            int8_t* rowp = p.codes + (ax0 + 8 * f4) * p.cols;
+            int8_t* rowp = out_codes + (ax0 + 8 * f4) * p.cols;
             const uint32_t loff = uint32_t(4 * h) * uint32_t(p.cols) + uint32_t(line);
 #pragma unroll
             for (int e = 0; e < 4; ++e) rowp[loff + uint32_t(e) * uint32_t(p.cols)] = int8_t(qpk[f4] >> (8 * e));
@@ -860,11 +902,11 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
 
     // ---- the next strip's weights: wreg and the W parts are dead from here on (the staged
     // copy is read by the other waves, protected by the barriers of the inverse phase)
-    if (!p.do_inverse) load_w(pseg, pmis);
+    if (!do_inverse) load_w(pseg, pmis);
 
     // ---- inverse transform of the error and the l2 proxy: same stage order; the error registers
     // 8c..8c+7 of the lane are the B operand of step c, split on the fly into hi + mid
-    if (p.do_inverse) {
+    if (do_inverse) {
       // B operand of MFMA step c: the lane's error registers 8c..8c+7 as bfloat16 hi and mid parts
       auto split_e = [&](int c, bf16x8& vh, bf16x8& vm) {
         uint32_t eh[4], em[4];
@@ -897,8 +939,8 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
             if (tq < NT) {
               dma(p.Ainv, kInvPlanes, cb[tq / KT], tq % KT, dst);
             } else {
-              nw = NFW;
-              dma(p.Afwd, FWDP, nbk[(tq - NT) / KT], (tq - NT) % KT, dst);
+              if (!ZIN) nw = NFW;
+              dma(ZIN ? p.Ainv : p.Afwd, ZIN ? kInvPlanes : FWDP, nbk[(tq - NT) / KT], (tq - NT) % KT, dst);
             }
           }
           // The next strip's weights, right behind the first inverse stage's fill: they are
@@ -951,7 +993,7 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
     for (int i = 0; i < NBLK; ++i) cb[i] = nbk[i];
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the last macro-tile's (unused) prefetches
-  if (p.do_inverse || p.do_grad) flush(cur_seg);
+  if (do_inverse || p.do_grad || keep) flush(cur_seg);
 }
 
 }  // namespace cafeq

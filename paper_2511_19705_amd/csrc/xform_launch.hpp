@@ -18,9 +18,9 @@ constexpr size_t core_lds_bytes_t(bool do_grad) {
 template <int K, int G>
 constexpr bool core_has_f16() { return K == 128 && Geo<K, G>::NBLK == 1; }
 
-template <int K, int G, int AXIS, bool GRAD, bool F16 = false, bool LONGG = false, bool ASYM = false>
+template <int K, int G, int AXIS, bool GRAD, bool F16 = false, bool LONGG = false, bool ASYM = false, int SWEEP = 0>
 int launch_core_v(const CoreParams& p, size_t lds, hipStream_t st) {
-  auto kern = xform_core_kernel<K, G, AXIS, GRAD, F16, LONGG, ASYM>;
+  auto kern = xform_core_kernel<K, G, AXIS, GRAD, F16, LONGG, ASYM, SWEEP>;
   static std::atomic<bool> attr_set{false};   // per instantiation
   if (!attr_set) {
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -33,6 +33,17 @@ int launch_core_v(const CoreParams& p, size_t lds, hipStream_t st) {
   return CAFEQ_OK;
 }
 
+// the sweeps of a loss call over groups that span segments
+template <int K, int G, int AXIS, bool ASYM>
+int launch_sweep(const CoreParams& p, size_t lds, hipStream_t st) {
+  if (!p.zkeep || !p.slot_hdr || (p.sweep == 1 && !p.rec) || (p.sweep == 2 && (!p.grec || !p.do_inverse))) return CAFEQ_ERR_INVALID_ARG;
+  if (p.sweep == 2) return launch_core_v<K, G, AXIS, false, false, true, ASYM, 2>(p, lds, st);
+  if constexpr (core_has_f16<K, G>()) {
+    if (p.fscale) return launch_core_v<K, G, AXIS, false, true, true, ASYM, 1>(p, lds, st);
+  }
+  return launch_core_v<K, G, AXIS, false, false, true, ASYM, 1>(p, lds, st);
+}
+
 template <int K, int G, int AXIS>
 int launch_core_t(const CoreParams& p, hipStream_t st) {
   const size_t lds = core_lds_bytes_t<K, G>(p.do_grad != 0);
@@ -43,6 +54,9 @@ int launch_core_t(const CoreParams& p, hipStream_t st) {
   if (p.longg) {
     if constexpr (G >= K && (G == K || G == 128)) {
       if (p.do_grad) return CAFEQ_ERR_INVALID_ARG;
+      if constexpr (K >= kKeepBlock) {
+        if (p.sweep) return launch_sweep<K, G, AXIS, false>(p, lds, st);
+      }
       if constexpr (core_has_f16<K, G>()) {
         if (p.fscale) return launch_core_v<K, G, AXIS, false, true, true>(p, lds, st);
       }
@@ -85,10 +99,9 @@ int launch_core_asym_t(const CoreParams& p, hipStream_t st) {
   if (p.do_grad || (p.fscale && !core_has_f16<K, G>())) return CAFEQ_ERR_INVALID_ARG;
   if (p.longg) {
     if constexpr (G >= K && (G == K || G == 128)) {
-      if constexpr (core_has_f16<K, G>()) {
-        if (p.fscale) return launch_core_v<K, G, AXIS, false, true, true, true>(p, lds, st);
-      }
-      return launch_core_v<K, G, AXIS, false, false, true, true>(p, lds, st);
+      // (larger blocks: loss calls alone come here, and they keep the transformed weights)
+      if constexpr (K >= kKeepBlock) return p.sweep ? launch_sweep<K, G, AXIS, true>(p, lds, st) : int(CAFEQ_ERR_INVALID_ARG);
+      else return launch_core_v<K, G, AXIS, false, false, true, true>(p, lds, st);
     } else {
       return CAFEQ_ERR_UNSUPPORTED;
     }
