@@ -467,6 +467,7 @@ void fill_common(CoreParams* p, const cafeq_mat* W, const CorePlan& pl, int rep)
   p->fscale = nullptr;
   p->longg = 0; p->gspan = 1; p->grec = nullptr; p->grp = 0;
   p->prep_planes = nullptr; p->prep_lscale = nullptr; p->prep_wsq = nullptr; p->fscale_inv = nullptr;
+  p->Tfwd = p->Tback = nullptr;
   p->prep_gtiles = nullptr; p->prep_lines = nullptr;
   p->zkeep = nullptr; p->sweep = 0;
   p->asym = 0; p->mins = nullptr; p->rec_mm = nullptr; p->grec_mm = nullptr;
@@ -1295,7 +1296,8 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
   const bool halvesA = core_halves(K, ga, asym), halvesB = core_halves(K, gb, asym);
   const bool f16A = v2A || halvesA || core_forward_f16(K, ga.Gk, cfg->bits), f16B = v2B || halvesB || core_forward_f16(K, gb.Gk, cfg->bits);
 
-  {
+  // (a pass over both members that splits its operands itself: no planes, and every header is written by it)
+  if (!(pair_launch && pair_splits_planes(K))) {
     const SplitRequest req[4] = {{x->T, w.a.pfwd, 1, v2A ? v2_fwd_parts(K) : f16A ? 2 : kFwdPlanes, f16A ? w.a.fs : nullptr, v2A ? 1 : 0, v2A ? 4 : 14},
                                  {x->Tinv, w.a.pinv, 1, kInvPlanes, v2A || halvesA ? w.a.fsi : nullptr, 0, v2A ? 4 : 14},
                                  {x->Tinv, w.b.pfwd, 0, v2B ? v2_fwd_parts(K) : f16B ? 2 : kFwdPlanes, f16B ? w.b.fs : nullptr, v2B ? 1 : 0, v2B ? 4 : 14},
@@ -1328,6 +1330,8 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
   if (pair_launch) {
     set_prepared(&a, A, CAFEQ_AXIS_COL);
     set_prepared(&b, B, CAFEQ_AXIS_ROW);
+    a.Tfwd = b.Tback = x->T;
+    a.Tback = b.Tfwd = x->Tinv;
     a.rec = qa.two ? w.a.rec : nullptr;
     b.rec = qb.two ? w.b.rec : nullptr;
     if ((rc = launch_loss_prepared_pair(K, ga.Gk, a, b, st))) return rc;

@@ -156,8 +156,8 @@ int launch_prepare(const cafeq_mat* W, int axis, void* prepared, hipStream_t st)
 // the same choice of records for both, no codes or scales.
 int launch_loss_v2_pair(int K, int G, const CoreParams& pa, const CoreParams& pb, hipStream_t st) {
   for (const CoreParams* p : {&pa, &pb})
-    if (!p->prep_planes || !p->prep_lscale || !p->prep_wsq || !p->fscale || !p->fscale_inv || !p->slot_hdr || p->codes ||
-        p->scales)
+    if (!p->prep_planes || !p->prep_lscale || !p->prep_wsq || !p->slot_hdr || p->codes || p->scales ||
+        (pair_splits_planes(K) ? !p->Tfwd || !p->Tback : !p->fscale || !p->fscale_inv))
       return CAFEQ_ERR_INVALID_ARG;
   if ((pa.rec != nullptr) != (pb.rec != nullptr)) return CAFEQ_ERR_INVALID_ARG;
   switch (K) {

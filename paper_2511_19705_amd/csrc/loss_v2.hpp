@@ -66,7 +66,9 @@ __device__ __forceinline__ void weight_parts(float y, bool one, uint32_t* hi, ui
 
 // bidx: the workgroup's index among the p.nwg workgroups that share the matrix; WP: parts of the prepared weights;
 // REC: write the arg-max records (the gradient pass follows); OUT: write scales and / or codes
-template <int K, int G, int AXIS, bool REC, bool OUT, int WP>
+// SELF (blocks of 128): the operand planes are split here, from T and T^-1 themselves -- the same bytes to read as the planes, once per
+// workgroup and segment -- instead of by a launch of their own
+template <int K, int G, int AXIS, bool REC, bool OUT, int WP, bool SELF = false>
 __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned bidx) {
   constexpr int L = 128, KT = 4, NGRP = L / G, RPG = G / 2;
   // blocks per segment, output tiles and steps of 16 inputs of a block
@@ -181,6 +183,81 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
     request_strip(sg, (mt0 - int64_t(sg) * mt_per_seg) * kV2Waves + wave);
   }
 
+  // (SELF) block b's planes into LDS, as split_planes_kernel (aux_kernels.hip) writes them: scaled by the power of two that puts the largest
+  // finite magnitude into [2^4, 2^5), two float16 parts; the factors back.  A thread takes one 16-byte vector of every stage.
+  auto split_block = [&](int b, float* fwd_back, float* inv_back) __attribute__((always_inline)) {
+    constexpr bool TR = AXIS == CAFEQ_AXIS_COL;    // the operands' rows are the blocks' columns
+    static_assert(!SELF || (K == 128 && FP == 2), "blocks of 128");
+    // (transposed: lanes along a row of the block, a contraction index each; else four lanes along 128 bytes of a row)
+    const int out = TR ? tid & 127 : tid >> 2, cq = TR ? tid >> 7 : tid & 3, c2 = cq >> 1, hh = cq & 1;
+    float x[2][4][8];
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+      const float* src = (o ? p.Tback : p.Tfwd) + int64_t(b) * K * K;
+#pragma unroll
+      for (int st = 0; st < 4; ++st)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          // inputs in runs of four: forward eight side by side, back two runs eight apart (the accumulators' order)
+          const int in = 32 * st + 16 * c2 + (o ? 8 * u + 4 * hh : 8 * hh + 4 * u);
+          if constexpr (TR) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[o][st][4 * u + e] = src[(in + e) * K + out];
+          } else {
+            const float4 v = *reinterpret_cast<const float4*>(src + out * K + in);
+            x[o][st][4 * u] = v.x; x[o][st][4 * u + 1] = v.y; x[o][st][4 * u + 2] = v.z; x[o][st][4 * u + 3] = v.w;
+          }
+        }
+    }
+    float mx[2];
+    for (int finite = 0; finite < 2; ++finite) {   // (infinite entries are looked for only where there is one)
+#pragma unroll
+      for (int o = 0; o < 2; ++o) {
+        float m = 0.f;
+#pragma unroll
+        for (int st = 0; st < 4; ++st)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float a = fabsf(x[o][st][e]);
+            m = fmaxf(m, finite && !(a < INFINITY) ? 0.f : a);
+          }
+        m = cluster_allmax<64>(m);
+        if (lane == 0) hred[wave * kHdrFloats + o] = m;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int o = 0; o < 2; ++o) {
+        mx[o] = hred[o];
+#pragma unroll
+        for (int ww = 1; ww < kV2Waves; ++ww) mx[o] = fmaxf(mx[o], hred[ww * kHdrFloats + o]);
+      }
+      if (mx[0] < INFINITY && mx[1] < INFINITY) break;
+      __syncthreads();
+    }
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+      int ex = int(__float_as_uint(mx[o]) >> 23);
+      ex = ex < 32 ? 32 : (ex > 254 ? 254 : ex);
+      const float sc = __uint_as_float(uint32_t(258 - ex) << 23);
+      *(o ? inv_back : fwd_back) = __uint_as_float(uint32_t(ex - 4) << 23);
+      unsigned char* at = (o ? liv : lfw) + out * 64 + ((cq ^ ((out >> 2) & 3)) << 4);
+#pragma unroll
+      for (int st = 0; st < 4; ++st) {
+        uintx4 hi, lo;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float y0 = x[o][st][2 * i] * sc, y1 = x[o][st][2 * i + 1] * sc;
+          const uint32_t both = pack_f16(y0, y1);
+          const halfx2 hb = __builtin_bit_cast(halfx2, both);
+          hi[i] = both;
+          lo[i] = pack_f16(y0 - float(hb[0]), y1 - float(hb[1]));
+        }
+        *reinterpret_cast<uintx4*>(at + st * (2 * K * 64)) = hi;
+        *reinterpret_cast<uintx4*>(at + st * (2 * K * 64) + K * 64) = lo;
+      }
+    }
+  };
+
   for (int64_t mt = mt0; mt < mt1;) {
     const int seg = int(mt / mt_per_seg);
     const int mis0 = int(mt - int64_t(seg) * mt_per_seg);
@@ -194,16 +271,19 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       bid[i] = p.rep != 1 ? (seg * NB + i) / p.rep : seg * NB + i;   // (rep is 1 on the column axis)
-      fsc = fmaxf(fsc, p.fscale[bid[i]]);
-      fsi[i] = p.fscale_inv[bid[i]];
+      if constexpr (!SELF) {
+        fsc = fmaxf(fsc, p.fscale[bid[i]]);
+        fsi[i] = p.fscale_inv[bid[i]];
+      }
     }
+    if constexpr (SELF) split_block(bid[0], &fsc, &fsi[0]);
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       rel[i] = NB == 1 ? 1.f : p.fscale[bid[i]] / fsc;
       inv_rel[i] = NB == 1 ? 1.f : fsc / p.fscale[bid[i]];
       cl2[i] = (rel[i] * fsi[i]) * (rel[i] * fsi[i]);       // (NB > 1) squared transformed error: segment's units -> per line's
     }
-    {
+    if constexpr (!SELF) {
       constexpr int NF = FPLB / (16 * kV2Threads), NI = IPLB / (16 * kV2Threads);   // vectors per thread
       static_assert(FPLB % (16 * kV2Threads) == 0 && IPLB % (16 * kV2Threads) == 0, "whole vectors");
       uintx4 tf[NF], ti[NI];
@@ -629,6 +709,13 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
     }
     mt += n;
   }
+  if constexpr (SELF) {
+    // a range that ends with its segment leaves the header behind its last one to nobody (workgroup w + 1 begins a segment
+    // further): it must read as empty (otherwise the planes' launch resets the headers)
+    const int last = int((mt1 - 1) / mt_per_seg);
+    if (mt1 == int64_t(last + 1) * mt_per_seg && tid < kHdrFloats)
+      p.slot_hdr[(w + last + 1) * kHdrFloats + tid] = tid == kHdrMref ? -INFINITY : 0.f;
+  }
 }
 
 template <int K, int G, int AXIS, bool REC, bool OUT, int WP>
@@ -642,8 +729,9 @@ __global__ __launch_bounds__(kV2Threads, 1) void loss_v2_kernel(const CoreParams
 // WPA, WPB: parts of the members' weights.
 template <int K, int G, bool REC, int WPA, int WPB>
 __global__ __launch_bounds__(kV2Threads, 1) void loss_v2_pair_kernel(const CoreParams pa, const CoreParams pb) {
-  if (blockIdx.x < unsigned(pa.nwg)) loss_v2_body<K, G, CAFEQ_AXIS_COL, REC, false, WPA>(pa, blockIdx.x);
-  else loss_v2_body<K, G, CAFEQ_AXIS_ROW, REC, false, WPB>(pb, blockIdx.x - unsigned(pa.nwg));
+  constexpr bool SELF = pair_splits_planes(K);
+  if (blockIdx.x < unsigned(pa.nwg)) loss_v2_body<K, G, CAFEQ_AXIS_COL, REC, false, WPA, SELF>(pa, blockIdx.x);
+  else loss_v2_body<K, G, CAFEQ_AXIS_ROW, REC, false, WPB, SELF>(pb, blockIdx.x - unsigned(pa.nwg));
 }
 
 template <int K, int G, int AXIS, bool REC, bool OUT, int WP>
