@@ -523,36 +523,44 @@ __global__ __launch_bounds__(512) void gj_spd256_kernel(const GjArgs a) {
       for (int r = 0; r < 16; ++r) pan[half][rbase + 8 * (r >> 2) + (r & 3)][q_own] = reg[jt][r];
     }
   };
-  // wave 0: D = P^-1 in place, P = rows 16 t .. of pan[buf]; row (lane % 16) of the pivot block per lane (the
-  // upper lanes repeat the lower sixteen)
+  // wave 0: D = P^-1, P = rows 16 t .. of pan[buf]; lane 16 g + r holds row r, columns 4 g .. of the pivot block, and, for the
+  // four steps whose pivots they are, columns 4 q .. of its row too (sp), so that a step needs no other lanes than the sixteen
+  // of its row: the pivot row's values come by DPP, eight multiply-adds a step.  (A whole row per lane, the pivot row through
+  // scalar lane reads: sixteen of those and sixteen multiply-adds, CHAIN_MEASURED.)
   auto chain = [&](const int t, const int buf) __attribute__((always_inline)) {
-    float prow[NB];
-#pragma unroll
-    for (int c4 = 0; c4 < NB / 4; ++c4) {
-      const float4 v = *reinterpret_cast<const float4*>(&pan[buf][NB * t + (lane & 15)][4 * c4]);
-      prow[4 * c4] = v.x; prow[4 * c4 + 1] = v.y; prow[4 * c4 + 2] = v.z; prow[4 * c4 + 3] = v.w;
+    const int r = lane & 15, g = lane >> 4;
+    float own[4], sp[4];
+    {
+      const float4 v = *reinterpret_cast<const float4*>(&pan[buf][NB * t + r][4 * g]);
+      own[0] = v.x; own[1] = v.y; own[2] = v.z; own[3] = v.w;
     }
     bool dd = false;
+    auto step = [&](auto s_c) __attribute__((always_inline)) {
+      constexpr int s = decltype(s_c)::value, q = s / 4, e = s % 4;
+      if constexpr (e == 0) {
+        if constexpr (q > 0) {
 #pragma unroll
-    for (int s = 0; s < NB; ++s) {
-      const float pv = read_lane(prow[s], s);
+          for (int c = 0; c < 4; ++c) own[c] = g == q - 1 ? sp[c] : own[c];
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) sp[c] = __shfl(own[c], 16 * q + r);
+      }
+      const float pv = dpp_mov<0x150 + s>(sp[e]);             // row_newbcast: lane s of each sixteen
       dd = dd || !(pv > tol);
       // reciprocal of the pivot: hardware estimate (2^-22) + one Newton step
       float ipiv = __builtin_amdgcn_rcpf(pv);
       ipiv = ipiv * (2.f - pv * ipiv);
-      float rowp[NB];
+      const bool isp = r == s;
+      const float f = (isp ? 1.f - pv : -sp[e]) * ipiv;
 #pragma unroll
-      for (int c = 0; c < NB; ++c) rowp[c] = c == s ? 1.f : read_lane(prow[c], s);
-      const bool isp = (lane & 15) == s;
-      const float f = (isp ? 1.f - pv : -prow[s]) * ipiv;
+      for (int c = 0; c < 4; ++c) {
+        own[c] = fmaf(f, dpp_mov<0x150 + s>(own[c]), own[c]);  // (columns 4 q ..: replaced by sp after their steps)
+        sp[c] = c == e ? (isp ? 1.f : 0.f) + f : fmaf(f, dpp_mov<0x150 + s>(sp[c]), sp[c]);
+      }
+    };
+    StaticFor<0, NB>::run(step);
 #pragma unroll
-      for (int c = 0; c < NB; ++c)
-        prow[c] = c == s ? (isp ? 1.f : 0.f) + f : fma_s(f, rowp[c], prow[c]);
-    }
-    if (lane < 16) {
-#pragma unroll
-      for (int c = 0; c < NB; ++c) dsm[buf][lane][c] = prow[c];
-    }
+    for (int c = 0; c < 4; ++c) dsm[buf][r][4 * g + c] = g == 3 ? sp[c] : own[c];
     if (dd && lane == 0) deadflag = 1;
   };
   // The wave that holds them splits the pivot rows 16 t + c, as they are now, into the B operands xb[half].
