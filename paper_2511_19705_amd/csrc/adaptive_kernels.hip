@@ -513,10 +513,12 @@ __global__ __launch_bounds__(512) void gj_spd256_kernel(const GjArgs a) {
     for (int r = 0; r < 16; ++r) reg[j][r] *= scale;
   const float tol = anorm * scale * (a.partial ? 1e-5f : 1e-6f);
 
-  // (every panel is a compile-time variant: tile and register indices are constants)
+  // Two panels, one tile of columns, are a turn of the loop; between turns the tiles move down by one, so that register
+  // indices are constants: reg[p] is tile (jt + p) % 8 in turn jt.  (All sixteen panels written out were 156 KB of code that ran
+  // once and came from memory as it ran: 70.3 us, now 66.5.)
   // the panel's columns, as they are now, into pan[half] (lanes that hold them: ln - 16 half in 0..15)
-  auto own_write = [&](auto t_c) __attribute__((always_inline)) {
-    constexpr int half = decltype(t_c)::value % 2, jt = decltype(t_c)::value / 2;
+  auto own_write = [&](auto half_c, auto p_c) __attribute__((always_inline)) {
+    constexpr int half = decltype(half_c)::value, jt = decltype(p_c)::value;
     const int q_own = ln - NB * half;
     if (q_own >= 0 && q_own < NB) {
 #pragma unroll
@@ -526,7 +528,7 @@ __global__ __launch_bounds__(512) void gj_spd256_kernel(const GjArgs a) {
   // wave 0: D = P^-1, P = rows 16 t .. of pan[buf]; lane 16 g + r holds row r, columns 4 g .. of the pivot block, and, for the
   // four steps whose pivots they are, columns 4 q .. of its row too (sp), so that a step needs no other lanes than the sixteen
   // of its row: the pivot row's values come by DPP, eight multiply-adds a step.  (A whole row per lane, the pivot row through
-  // scalar lane reads: sixteen of those and sixteen multiply-adds, CHAIN_MEASURED.)
+  // scalar lane reads: sixteen of those and sixteen multiply-adds: solves of 75.3 instead of 70.3 us.)
   auto chain = [&](const int t, const int buf) __attribute__((always_inline)) {
     const int r = lane & 15, g = lane >> 4;
     float own[4], sp[4];
@@ -566,7 +568,7 @@ __global__ __launch_bounds__(512) void gj_spd256_kernel(const GjArgs a) {
   // The wave that holds them splits the pivot rows 16 t + c, as they are now, into the B operands xb[half].
   // Lane (ln, h) holds, for each of its columns, c = 8 g + 4 h + i (g = 0, 1; i = 0..3) in register
   // 4 (2 half + g) + i: the eight contraction indices of lane half h, in operand order.
-  auto publish = [&](auto half_c) __attribute__((always_inline)) {
+  auto publish = [&](auto half_c, const int jt) __attribute__((always_inline)) {
     constexpr int half = decltype(half_c)::value;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -575,7 +577,7 @@ __global__ __launch_bounds__(512) void gj_spd256_kernel(const GjArgs a) {
       for (int e = 0; e < 8; ++e) xv[e] = reg[j][8 * half + e];
       uintx4 xh, xm, xl;
       split3_bf16(xv, xh, xm, xl);
-      unsigned char* dst = xb + half * kXbB + (size_t(h) * K + 32 * j + ln) * 16;
+      unsigned char* dst = xb + half * kXbB + (h * K + 32 * ((jt + j) & 7) + ln) * 16;
       *reinterpret_cast<uintx4*>(dst) = xh;
       *reinterpret_cast<uintx4*>(dst + 2 * K * 16) = xm;
       *reinterpret_cast<uintx4*>(dst + 4 * K * 16) = xl;
@@ -585,10 +587,11 @@ __global__ __launch_bounds__(512) void gj_spd256_kernel(const GjArgs a) {
   // tile that holds the next panel and hands that panel's columns over, so that wave 0 can invert the next pivot
   // block, after its own share of the update, while the slower waves are still multiplying: one barrier per panel.
   // (Measured without effect: a raised priority for wave 0; the inversion ahead of the rest of wave 0's update.)
-  auto panel = [&](auto t_c) __attribute__((always_inline)) {
-    constexpr int t = decltype(t_c)::value, half = t % 2, jt = t / 2, buf = half, nhalf = 1 - half, c0 = NB * half;
-    constexpr int nt = t + 1, njt = nt / 2;
-    constexpr bool has_next = nt < K / NB;
+  auto panel = [&](auto half_c, const int jt) __attribute__((always_inline)) {
+    constexpr int half = decltype(half_c)::value, buf = half, nhalf = 1 - half, c0 = NB * half;
+    constexpr int np = half;                 // the register tile of the next panel
+    const int t = 2 * jt + half, nt = t + 1, njt = nt / 2;
+    const bool has_next = nt < K / NB;
     const int q_own = ln - c0;
     const bool owner = q_own >= 0 && q_own < NB;
     float av[8], dv[8];
@@ -635,7 +638,7 @@ __global__ __launch_bounds__(512) void gj_spd256_kernel(const GjArgs a) {
     const bf16x8 a0 = as_bf16x8(uh), a1 = as_bf16x8(um), a2 = as_bf16x8(ul);
     auto update = [&](auto j_c) __attribute__((always_inline)) {
       constexpr int j = decltype(j_c)::value;
-      const unsigned char* pb = xb + buf * kXbB + (size_t(h) * K + 32 * j + ln) * 16;
+      const unsigned char* pb = xb + buf * kXbB + (h * K + 32 * ((jt + j) & 7) + ln) * 16;
       const bf16x8 b0 = as_bf16x8(*reinterpret_cast<const uintx4*>(pb));
       const bf16x8 b1 = as_bf16x8(*reinterpret_cast<const uintx4*>(pb + 2 * K * 16));
       const bf16x8 b2 = as_bf16x8(*reinterpret_cast<const uintx4*>(pb + 4 * K * 16));
@@ -650,13 +653,13 @@ __global__ __launch_bounds__(512) void gj_spd256_kernel(const GjArgs a) {
       reg[j] = d;
     };
     auto others = [&](auto j_c) __attribute__((always_inline)) {
-      if constexpr (!has_next || decltype(j_c)::value != njt) update(j_c);
+      if constexpr (decltype(j_c)::value != np) update(j_c);
     };
-    if constexpr (has_next) {
-      update(std::integral_constant<int, njt>{});
-      // (the next panel's columns lie in the other half of the lanes of tile njt: the replacement of this
+    update(std::integral_constant<int, np>{});
+    if (has_next) {
+      // (the next panel's columns lie in the other half of the lanes of this tile, or in the next one: the replacement of this
       // panel's own columns below does not touch them)
-      own_write(std::integral_constant<int, nt>{});
+      own_write(std::integral_constant<int, nhalf>{}, std::integral_constant<int, np>{});
       // (every lane of the wave stores the count: each lane's own panel entries are released by its own store)
       if (w == njt) __hip_atomic_store(&ready, nt, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
@@ -669,10 +672,10 @@ __global__ __launch_bounds__(512) void gj_spd256_kernel(const GjArgs a) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) cn[8 * half + e] = dsm[buf][8 * (e >> 2) + 4 * h + (e & 3)][q_own];
       }
-      reg[jt] = cn;
+      reg[0] = cn;
     }
-    if constexpr (has_next) {
-      if (w == njt) publish(std::integral_constant<int, nhalf>{});
+    if (has_next) {
+      if (w == njt) publish(std::integral_constant<int, nhalf>{}, jt);
       if (w == 0) {
         // the pivot block of the next panel is part of what wave njt handed over; the wait is bounded (a wave
         // that never saw the hand-over marks the block as failed and goes on)
@@ -687,15 +690,25 @@ __global__ __launch_bounds__(512) void gj_spd256_kernel(const GjArgs a) {
     }
     __syncthreads();
   };
-  own_write(std::integral_constant<int, 0>{});
+  const std::integral_constant<int, 0> first{};
+  const std::integral_constant<int, 1> second{};
+  own_write(first, first);
   if (tid == 0) ready = 0;
   __syncthreads();
   if (w == 0) {
     chain(0, 0);
-    publish(std::integral_constant<int, 0>{});
+    publish(first, 0);
   }
   __syncthreads();
-  StaticFor<0, K / NB>::run(panel);
+#pragma unroll 1
+  for (int jt = 0; jt < K / 32; ++jt) {
+    panel(first, jt);
+    panel(second, jt);
+    const floatx16 r0 = reg[0];
+#pragma unroll
+    for (int j = 0; j < 7; ++j) reg[j] = reg[j + 1];
+    reg[7] = r0;
+  }
   __syncthreads();
   const bool dead = deadflag != 0;
   if (a.status && tid == 0) a.status[size_t(b) * a.status_stride + a.status_offset] = dead ? 1 : 0;
