@@ -467,7 +467,7 @@ void fill_common(CoreParams* p, const cafeq_mat* W, const CorePlan& pl, int rep)
   p->fscale = nullptr;
   p->longg = 0; p->gspan = 1; p->grec = nullptr; p->grp = 0;
   p->prep_planes = nullptr; p->prep_lscale = nullptr; p->prep_wsq = nullptr; p->fscale_inv = nullptr;
-  p->Tfwd = p->Tback = nullptr;
+  p->Tfwd = p->Tback = nullptr; p->rG_out = nullptr;
   p->prep_gtiles = nullptr; p->prep_lines = nullptr;
   p->zkeep = nullptr; p->sweep = 0;
   p->asym = 0; p->mins = nullptr; p->rec_mm = nullptr; p->grec_mm = nullptr;
@@ -1156,7 +1156,8 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
   CoreParams p;
   fill_common(&p, W, pl, x->rep);
   // forward operand [out][in]: T^T (COL) or T (ROW); inverse operand: Tinv^T or Tinv
-  {
+  // (a pass that splits them itself: no planes, and it writes every header and rG)
+  if (!(v2 && v2_splits_planes(K, false, codes || scales))) {
     // (prepared weights: float16 planes for both operands, scaled so that the rounding error fits float16)
     const SplitRequest req[2] = {{x->T, w.m.pfwd, col ? 1 : 0, v2 ? v2_fwd_parts(K) : f16 ? 2 : kFwdPlanes, f16 ? w.m.fs : nullptr, v2 ? 1 : 0, v2 ? 4 : 14},
                                  {x->Tinv, w.m.pinv, col ? 1 : 0, kInvPlanes, v2 || halves ? w.m.fsi : nullptr, 0, v2 ? 4 : 14}};
@@ -1170,6 +1171,7 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
   }
   p.Afwd = w.m.pfwd; p.Ainv = w.m.pinv; p.fscale = f16 ? w.m.fs : nullptr; p.fscale_inv = v2 || halves ? w.m.fsi : nullptr;
   p.grid = grid; p.do_inverse = 1; p.do_grad = pp.fused ? 1 : 0; p.loss_kind = kLossSur; p.beta = beta;
+  p.Tfwd = x->T; p.Tback = x->Tinv; p.rG_out = w.m.rG;
   p.rG = w.m.rG; p.codes = codes; p.scales = scales; p.slot_grad = w.m.slot_grad; p.slot_hdr = w.slot_hdr;
   p.asym = asym ? 1 : 0;
   p.mins = asym && scales ? scales + nlines * (naxis / gp.G) : nullptr;   // the minima follow the scales
@@ -1296,8 +1298,8 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
   const bool halvesA = core_halves(K, ga, asym), halvesB = core_halves(K, gb, asym);
   const bool f16A = v2A || halvesA || core_forward_f16(K, ga.Gk, cfg->bits), f16B = v2B || halvesB || core_forward_f16(K, gb.Gk, cfg->bits);
 
-  // (a pass over both members that splits its operands itself: no planes, and every header is written by it)
-  if (!(pair_launch && pair_splits_planes(K))) {
+  // (passes that split their operands themselves: no planes, and every header is written by them)
+  if (!(pair_launch && v2_splits_planes(K, true, false))) {
     const SplitRequest req[4] = {{x->T, w.a.pfwd, 1, v2A ? v2_fwd_parts(K) : f16A ? 2 : kFwdPlanes, f16A ? w.a.fs : nullptr, v2A ? 1 : 0, v2A ? 4 : 14},
                                  {x->Tinv, w.a.pinv, 1, kInvPlanes, v2A || halvesA ? w.a.fsi : nullptr, 0, v2A ? 4 : 14},
                                  {x->Tinv, w.b.pfwd, 0, v2B ? v2_fwd_parts(K) : f16B ? 2 : kFwdPlanes, f16B ? w.b.fs : nullptr, v2B ? 1 : 0, v2B ? 4 : 14},
@@ -1323,6 +1325,8 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
   b.fscale = f16B ? w.b.fs : nullptr; b.fscale_inv = v2B || halvesB ? w.b.fsi : nullptr;
   b.asym = asym ? 1 : 0;
   b.mins = asym && scalesV ? scalesV + (B->rows / gb.G) * B->cols : nullptr;
+  a.Tfwd = b.Tback = x->T;
+  a.Tback = b.Tfwd = x->Tinv;
   const cafeq_mat* mats[2] = {A, B};
   const PassPlans* pps[2] = {&qa, &qb};
   const bool owner = grad && !gather && grad_owner_eligible(mats, pps, 2, K, x->rep);
@@ -1330,8 +1334,6 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
   if (pair_launch) {
     set_prepared(&a, A, CAFEQ_AXIS_COL);
     set_prepared(&b, B, CAFEQ_AXIS_ROW);
-    a.Tfwd = b.Tback = x->T;
-    a.Tback = b.Tfwd = x->Tinv;
     a.rec = qa.two ? w.a.rec : nullptr;
     b.rec = qb.two ? w.b.rec : nullptr;
     if ((rc = launch_loss_prepared_pair(K, ga.Gk, a, b, st))) return rc;

@@ -74,10 +74,12 @@ __host__ __device__ constexpr int prepared_parts(int dtype) { return dtype == CA
 // 41 / 41 and 35 / 34.  One part of the error leaves the l2 proxy of blocks of 32 and 64 2e-6 off, two parts 1e-7, as bfloat16's two.
 __host__ __device__ constexpr int v2_fwd_parts(int K) { return K == 32 ? 3 : 2; }
 __host__ __device__ constexpr int v2_err_parts(int K) { return K == 128 ? 1 : 2; }
-// Whether the pass over both members splits the operand planes itself (loss_v2.hpp; no launch for them then).  Evaluations with a
-// launch for the planes / without, us: 9B-shaped pair 275 / 264, 27B-shaped in bfloat16 578 / 546, 2B-shaped 157 / 149, 600 lines of 2048
-// 74 / 68, 264 of 512 84 / 80, 256 of 36864 240 / 213.  (Blocks of 32 and 64 share a segment: not built.)
-__host__ __device__ constexpr bool pair_splits_planes(int K) { return K == 128; }
+// Whether the loss pass over prepared weights splits the operand planes itself (loss_v2.hpp; no launch for them then): both members
+// of a pair in one launch, blocks of 64 and 128, and single matrices at blocks of 64 that want no codes.  Evaluations with a launch
+// for the planes / without, us: 9B-shaped pair 275 / 264, 27B-shaped in bfloat16 578 / 546, 2B-shaped 157 / 149, at k = 64 114 / 108, 600 lines of
+// 2048 74 / 68, 264 of 512 84 / 80, 256 of 36864 240 / 213; single 2304 x 9216 at k = 64 85 / 82, in bfloat16 77 / 76, 36864 x 1024 137 / 133, at
+// k = 128 119 / 119.  Passes that write codes have no registers for it: 36864 x 4608 in bfloat16 at k = 64 328 / 351, at k = 128 225 / 222.
+__host__ __device__ constexpr bool v2_splits_planes(int K, bool pair, bool out) { return pair ? K == 64 || K == 128 : K == 64 && !out; }
 PreparedLayout prepared_layout(int64_t nlines, int64_t naxis, int dtype, int axis);
 int launch_prepare(const cafeq_mat* W, int axis, void* prepared, hipStream_t st);
 // gradient pass over prepared weights (blocks of 128; grad_v2.hip): p.prep_gtiles, p.rec, p.grp as launch_grad_pass

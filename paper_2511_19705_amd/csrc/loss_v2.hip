@@ -156,8 +156,8 @@ int launch_prepare(const cafeq_mat* W, int axis, void* prepared, hipStream_t st)
 // the same choice of records for both, no codes or scales.
 int launch_loss_v2_pair(int K, int G, const CoreParams& pa, const CoreParams& pb, hipStream_t st) {
   for (const CoreParams* p : {&pa, &pb})
-    if (!p->prep_planes || !p->prep_lscale || !p->prep_wsq || !p->slot_hdr || p->codes || p->scales ||
-        (pair_splits_planes(K) ? !p->Tfwd || !p->Tback : !p->fscale || !p->fscale_inv))
+    if (!p->prep_planes || !p->prep_lscale || !p->prep_wsq || !p->slot_hdr || p->codes || p->scales || p->loss_kind != kLossLse ||
+        (v2_splits_planes(K, true, false) ? !p->Tfwd || !p->Tback : !p->fscale || !p->fscale_inv))
       return CAFEQ_ERR_INVALID_ARG;
   if ((pa.rec != nullptr) != (pb.rec != nullptr)) return CAFEQ_ERR_INVALID_ARG;
   switch (K) {
@@ -169,7 +169,9 @@ int launch_loss_v2_pair(int K, int G, const CoreParams& pa, const CoreParams& pb
 }
 
 int launch_loss_v2(int K, int G, int axis, const CoreParams& p, hipStream_t st) {
-  if (!p.prep_planes || !p.prep_lscale || !p.prep_wsq || !p.fscale || !p.fscale_inv || !p.slot_hdr) return CAFEQ_ERR_INVALID_ARG;
+  if (!p.prep_planes || !p.prep_lscale || !p.prep_wsq || !p.slot_hdr ||
+      (v2_splits_planes(K, false, p.codes || p.scales) ? !p.Tfwd || !p.Tback || (p.loss_kind == kLossSur && !p.rG_out) : !p.fscale || !p.fscale_inv))
+    return CAFEQ_ERR_INVALID_ARG;
   switch (K) {
     case 32: return launch_loss_v2_k32(G, axis, p, st);
     case 64: return launch_loss_v2_k64(G, axis, p, st);

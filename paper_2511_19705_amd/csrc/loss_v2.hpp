@@ -51,7 +51,7 @@ constexpr int kV2MacroLines = kV2Waves * 32;
 // 223 -> 174 us).
 constexpr int v2_tile_bytes(int parts) { return 32 * 128 * 2 * parts; }
 // operand planes of a segment (T and T^-1, 64 KB each for blocks of 128), the waves' sums
-constexpr int v2_lds(int K) { return (2 * v2_fwd_parts(K) + 4) * 128 * K + kV2Waves * kHdrFloats * 4 + 64; }
+constexpr int v2_lds(int K) { return (2 * v2_fwd_parts(K) + 4) * 128 * K + kV2Waves * kHdrFloats * 4 + 64 + kV2Waves * 4 * 8; }
 
 // Marks in a line's scale, a power of two: 32 (64) of its inputs are far smaller than the segment's largest
 constexpr uint32_t kFar32 = 1, kFar64 = 2;
@@ -66,9 +66,10 @@ __device__ __forceinline__ void weight_parts(float y, bool one, uint32_t* hi, ui
 
 // bidx: the workgroup's index among the p.nwg workgroups that share the matrix; WP: parts of the prepared weights;
 // REC: write the arg-max records (the gradient pass follows); OUT: write scales and / or codes
-// SELF (blocks of 128): the operand planes are split here, from T and T^-1 themselves -- the same bytes to read as the planes, once per
-// workgroup and segment -- instead of by a launch of their own
-template <int K, int G, int AXIS, bool REC, bool OUT, int WP, bool SELF = false>
+// SELF (blocks of 64 and 128): the operand planes are split here, from T and T^-1 themselves -- the same bytes to read as the planes, once
+// per workgroup and segment -- instead of by a launch of their own, and the groups' sums of rho are taken on the way;
+// PAIR: a member of a pair (kLossLse)
+template <int K, int G, int AXIS, bool REC, bool OUT, int WP, bool SELF, bool PAIR>
 __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned bidx) {
   constexpr int L = 128, KT = 4, NGRP = L / G, RPG = G / 2;
   // blocks per segment, output tiles and steps of 16 inputs of a block
@@ -92,7 +93,7 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
   if (mt0 >= mt1) return;
   const int mt_per_seg = int(p.mt_per_seg);       // macro-tiles of 256 lines per segment
   const int64_t nlp = int64_t(mt_per_seg) * kV2MacroLines;
-  const bool lse_on = p.loss_kind == kLossLse;
+  const bool lse_on = PAIR || p.loss_kind == kLossLse;
   const int swz = (ln >> 2) & 3;
   const int aoff0 = ln * 64 + ((h ^ swz) << 4), aoff1 = ln * 64 + (((2 + h) ^ swz) << 4);
   bool wsq_pending = w == 0;
@@ -183,79 +184,122 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
     request_strip(sg, (mt0 - int64_t(sg) * mt_per_seg) * kV2Waves + wave);
   }
 
-  // (SELF) block b's planes into LDS, as split_planes_kernel (aux_kernels.hip) writes them: scaled by the power of two that puts the largest
-  // finite magnitude into [2^4, 2^5), two float16 parts; the factors back.  A thread takes one 16-byte vector of every stage.
-  auto split_block = [&](int b, float* fwd_back, float* inv_back) __attribute__((always_inline)) {
+  // (SELF) the segment's planes into LDS, as split_planes_kernel (aux_kernels.hip) writes them: a block scaled by the power of two that
+  // puts its largest finite magnitude into [2^4, 2^5), two float16 parts; the factors back.  A thread takes one 16-byte vector of
+  // each of a block's stages (K = 64: of one of the two).  With want_rg also the sums of T^-1's squares over each group's
+  // indices, the contraction's: into rg, and to memory for the gradient pass (workgroups that share a segment write the same).
+  double* rsum = reinterpret_cast<double*>(hred + kV2Waves * kHdrFloats + 16);   // [8 waves][4]
+  auto split_blocks = [&](const int (&bid)[NB], float (&fwd_back)[NB], float (&inv_back)[NB], bool want_rg, int sg, float (&rg)[NGRP])
+      __attribute__((always_inline)) {
     constexpr bool TR = AXIS == CAFEQ_AXIS_COL;    // the operands' rows are the blocks' columns
-    static_assert(!SELF || (K == 128 && FP == 2), "blocks of 128");
+    static_assert(!SELF || ((K == 128 || K == 64) && FP == 2), "blocks of 64 and 128");
+    constexpr int NS = K == 128 ? 4 : 1, LK = K == 128 ? 7 : 6;
     // (transposed: lanes along a row of the block, a contraction index each; else four lanes along 128 bytes of a row)
-    const int out = TR ? tid & 127 : tid >> 2, cq = TR ? tid >> 7 : tid & 3, c2 = cq >> 1, hh = cq & 1;
-    float x[2][4][8];
+    const int out = TR ? tid & (K - 1) : (tid >> 2) & (K - 1), cq = TR ? (tid >> LK) & 3 : tid & 3, c2 = cq >> 1, hh = cq & 1;
+    const int st0 = K == 128 ? 0 : wave >> 2;
+    float x[2][NB][NS][8];
 #pragma unroll
-    for (int o = 0; o < 2; ++o) {
-      const float* src = (o ? p.Tback : p.Tfwd) + int64_t(b) * K * K;
+    for (int o = 0; o < 2; ++o)
 #pragma unroll
-      for (int st = 0; st < 4; ++st)
+      for (int b = 0; b < NB; ++b) {
+        const float* src = (o ? p.Tback : p.Tfwd) + int64_t(bid[b]) * K * K;
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          // inputs in runs of four: forward eight side by side, back two runs eight apart (the accumulators' order)
-          const int in = 32 * st + 16 * c2 + (o ? 8 * u + 4 * hh : 8 * hh + 4 * u);
-          if constexpr (TR) {
+        for (int st = 0; st < NS; ++st)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) x[o][st][4 * u + e] = src[(in + e) * K + out];
-          } else {
-            const float4 v = *reinterpret_cast<const float4*>(src + out * K + in);
-            x[o][st][4 * u] = v.x; x[o][st][4 * u + 1] = v.y; x[o][st][4 * u + 2] = v.z; x[o][st][4 * u + 3] = v.w;
+          for (int u = 0; u < 2; ++u) {
+            // inputs in runs of four: forward eight side by side, back two runs eight apart (the accumulators' order)
+            const int in = 32 * (st0 + st) + 16 * c2 + (o ? 8 * u + 4 * hh : 8 * hh + 4 * u);
+            float (&y)[8] = x[o][b][st];
+            if constexpr (TR) {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) y[4 * u + e] = src[(in + e) * K + out];
+            } else {
+              const float4 v = *reinterpret_cast<const float4*>(src + out * K + in);
+              y[4 * u] = v.x; y[4 * u + 1] = v.y; y[4 * u + 2] = v.z; y[4 * u + 3] = v.w;
+            }
           }
+      }
+    if (want_rg) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int st = 0; st < NS; ++st) {
+          double t = 0;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) t += double(x[1][b][st][e]) * x[1][b][st][e];
+          t = wave_sum(t);
+          if (lane == 0) rsum[wave * 4 + b * NS + st] = t;
         }
     }
-    float mx[2];
+    float mx[2][NB];
     for (int finite = 0; finite < 2; ++finite) {   // (infinite entries are looked for only where there is one)
 #pragma unroll
-      for (int o = 0; o < 2; ++o) {
-        float m = 0.f;
+      for (int o = 0; o < 2; ++o)
 #pragma unroll
-        for (int st = 0; st < 4; ++st)
+        for (int b = 0; b < NB; ++b) {
+          float m = 0.f;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const float a = fabsf(x[o][st][e]);
-            m = fmaxf(m, finite && !(a < INFINITY) ? 0.f : a);
-          }
-        m = cluster_allmax<64>(m);
-        if (lane == 0) hred[wave * kHdrFloats + o] = m;
-      }
-      __syncthreads();
+          for (int st = 0; st < NS; ++st)
 #pragma unroll
-      for (int o = 0; o < 2; ++o) {
-        mx[o] = hred[o];
-#pragma unroll
-        for (int ww = 1; ww < kV2Waves; ++ww) mx[o] = fmaxf(mx[o], hred[ww * kHdrFloats + o]);
-      }
-      if (mx[0] < INFINITY && mx[1] < INFINITY) break;
-      __syncthreads();
-    }
-#pragma unroll
-    for (int o = 0; o < 2; ++o) {
-      int ex = int(__float_as_uint(mx[o]) >> 23);
-      ex = ex < 32 ? 32 : (ex > 254 ? 254 : ex);
-      const float sc = __uint_as_float(uint32_t(258 - ex) << 23);
-      *(o ? inv_back : fwd_back) = __uint_as_float(uint32_t(ex - 4) << 23);
-      unsigned char* at = (o ? liv : lfw) + out * 64 + ((cq ^ ((out >> 2) & 3)) << 4);
-#pragma unroll
-      for (int st = 0; st < 4; ++st) {
-        uintx4 hi, lo;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float y0 = x[o][st][2 * i] * sc, y1 = x[o][st][2 * i + 1] * sc;
-          const uint32_t both = pack_f16(y0, y1);
-          const halfx2 hb = __builtin_bit_cast(halfx2, both);
-          hi[i] = both;
-          lo[i] = pack_f16(y0 - float(hb[0]), y1 - float(hb[1]));
+            for (int e = 0; e < 8; ++e) {
+              const float a = fabsf(x[o][b][st][e]);
+              m = fmaxf(m, finite && !(a < INFINITY) ? 0.f : a);
+            }
+          m = cluster_allmax<64>(m);
+          if (lane == 0) hred[wave * kHdrFloats + o * NB + b] = m;
         }
-        *reinterpret_cast<uintx4*>(at + st * (2 * K * 64)) = hi;
-        *reinterpret_cast<uintx4*>(at + st * (2 * K * 64) + K * 64) = lo;
+      __syncthreads();
+      bool all = true;
+#pragma unroll
+      for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          mx[o][b] = hred[o * NB + b];
+#pragma unroll
+          for (int ww = 1; ww < kV2Waves; ++ww) mx[o][b] = fmaxf(mx[o][b], hred[ww * kHdrFloats + o * NB + b]);
+          all = all && mx[o][b] < INFINITY;
+        }
+      if (all) break;
+      __syncthreads();
+    }
+    if (want_rg) {
+#pragma unroll
+      for (int gi = 0; gi < NGRP; ++gi) {
+        double t = 0;
+        for (int ww = 0; ww < kV2Waves; ++ww)
+#pragma unroll
+          for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int st = 0; st < NS; ++st)
+              if ((b * K + 32 * (K == 128 ? st : ww >> 2)) / G == gi) t += rsum[ww * 4 + b * NS + st];
+        rg[gi] = float(t);
+        if (tid == 0) p.rG_out[int64_t(sg) * NGRP + gi] = rg[gi];
       }
     }
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        int ex = int(__float_as_uint(mx[o][b]) >> 23);
+        ex = ex < 32 ? 32 : (ex > 254 ? 254 : ex);
+        const float sc = __uint_as_float(uint32_t(258 - ex) << 23);
+        (o ? inv_back[b] : fwd_back[b]) = __uint_as_float(uint32_t(ex - 4) << 23);
+        unsigned char* at = (o ? liv + b * IBLKB : lfw + b * FBLKB) + st0 * (2 * K * 64) + out * 64 + ((cq ^ ((out >> 2) & 3)) << 4);
+#pragma unroll
+        for (int st = 0; st < NS; ++st) {
+          uintx4 hi, lo;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float y0 = x[o][b][st][2 * i] * sc, y1 = x[o][b][st][2 * i + 1] * sc;
+            const uint32_t both = pack_f16(y0, y1);
+            const halfx2 hb = __builtin_bit_cast(halfx2, both);
+            hi[i] = both;
+            lo[i] = pack_f16(y0 - float(hb[0]), y1 - float(hb[1]));
+          }
+          *reinterpret_cast<uintx4*>(at + st * (2 * K * 64)) = hi;
+          *reinterpret_cast<uintx4*>(at + st * (2 * K * 64) + K * 64) = lo;
+        }
+      }
   };
 
   for (int64_t mt = mt0; mt < mt1;) {
@@ -267,20 +311,23 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
     // rel[i] of the segment's, the largest -- and a group that spans blocks is measured in the segment's: the factors, powers
     // of two, are applied to its maxima and to the reciprocal and the step that each block's elements see.
     int bid[NB];
-    float fsc = 0.f, fsi[NB], rel[NB], inv_rel[NB], cl2[NB];
+    float fsc = 0.f, fsf[NB], fsi[NB], rel[NB], inv_rel[NB], cl2[NB];
+    float rgs[NGRP];          // (SELF) the segment's groups: sums of rho
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       bid[i] = p.rep != 1 ? (seg * NB + i) / p.rep : seg * NB + i;   // (rep is 1 on the column axis)
       if constexpr (!SELF) {
-        fsc = fmaxf(fsc, p.fscale[bid[i]]);
+        fsf[i] = p.fscale[bid[i]];
         fsi[i] = p.fscale_inv[bid[i]];
       }
     }
-    if constexpr (SELF) split_block(bid[0], &fsc, &fsi[0]);
+    if constexpr (SELF) split_blocks(bid, fsf, fsi, !PAIR && !lse_on, seg, rgs);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) fsc = fmaxf(fsc, fsf[i]);
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
-      rel[i] = NB == 1 ? 1.f : p.fscale[bid[i]] / fsc;
-      inv_rel[i] = NB == 1 ? 1.f : fsc / p.fscale[bid[i]];
+      rel[i] = NB == 1 ? 1.f : fsf[i] / fsc;
+      inv_rel[i] = NB == 1 ? 1.f : fsc / fsf[i];
       cl2[i] = (rel[i] * fsi[i]) * (rel[i] * fsi[i]);       // (NB > 1) squared transformed error: segment's units -> per line's
     }
     if constexpr (!SELF) {
@@ -543,7 +590,7 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
         }
         const float a2 = a * a;
         if (h == 0) s_va2[gi] += a2;
-        if (!lse_on && h == 0) s_sur = fmaf(a2, p.rG[seg * NGRP + gi], s_sur);
+        if (!PAIR && !lse_on && h == 0) s_sur = fmaf(a2, SELF ? rgs[gi] : p.rG[seg * NGRP + gi], s_sur);
         if (lse_on) {
           // exponentials relative to this wave's running reference
           const float am = valid ? a : 0.f;
@@ -720,7 +767,7 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
 
 template <int K, int G, int AXIS, bool REC, bool OUT, int WP>
 __global__ __launch_bounds__(kV2Threads, 1) void loss_v2_kernel(const CoreParams p) {
-  loss_v2_body<K, G, AXIS, REC, OUT, WP>(p, blockIdx.x);
+  loss_v2_body<K, G, AXIS, REC, OUT, WP, v2_splits_planes(K, false, OUT), false>(p, blockIdx.x);
 }
 
 // Both members of a pair in one launch (no codes or scales requested): the first pa.nwg workgroups take member
@@ -729,9 +776,9 @@ __global__ __launch_bounds__(kV2Threads, 1) void loss_v2_kernel(const CoreParams
 // WPA, WPB: parts of the members' weights.
 template <int K, int G, bool REC, int WPA, int WPB>
 __global__ __launch_bounds__(kV2Threads, 1) void loss_v2_pair_kernel(const CoreParams pa, const CoreParams pb) {
-  constexpr bool SELF = pair_splits_planes(K);
-  if (blockIdx.x < unsigned(pa.nwg)) loss_v2_body<K, G, CAFEQ_AXIS_COL, REC, false, WPA, SELF>(pa, blockIdx.x);
-  else loss_v2_body<K, G, CAFEQ_AXIS_ROW, REC, false, WPB, SELF>(pb, blockIdx.x - unsigned(pa.nwg));
+  constexpr bool SELF = v2_splits_planes(K, true, false);
+  if (blockIdx.x < unsigned(pa.nwg)) loss_v2_body<K, G, CAFEQ_AXIS_COL, REC, false, WPA, SELF, true>(pa, blockIdx.x);
+  else loss_v2_body<K, G, CAFEQ_AXIS_ROW, REC, false, WPB, SELF, true>(pb, blockIdx.x - unsigned(pa.nwg));
 }
 
 template <int K, int G, int AXIS, bool REC, bool OUT, int WP>

@@ -144,7 +144,8 @@ struct CoreParams {
   const unsigned char* prep_lines;   // row axis: the weights line by line
   const float* prep_wsq;
   const float* fscale_inv;  // per-block factor of the float16 inverse operand planes
-  const float *Tfwd, *Tback;  // pairs over prepared weights whose pass splits its operand planes itself: T / T^-1 of member A, T^-1 / T of B
+  const float *Tfwd, *Tback;  // passes over prepared weights that split their operand planes themselves: what they transform with, there and back
+  float* rG_out;              // (kLossSur) rG, which such a pass also writes
   // gradient pass over prepared weights (grad_v2.hip): tiles of 128 lines x 128 inputs in operand order
   const unsigned char* prep_gtiles;
   // The min/max grid of Eq. (1) (ASYM kernel variant): grid.qmax = 2^b - 1 levels, grid.qmin = 0; the scale
