@@ -75,6 +75,11 @@ int resolve_group(const cafeq_quant_cfg* cfg, int64_t naxis, int K, GroupPlan* g
   return CAFEQ_OK;
 }
 
+// Workgroups for n macro-tiles on `slots` places: one each while they fit, else a multiple of eight (ranges that follow each other then
+// sit behind one L2).  Down to a multiple of eight in either case, a few tiles were left for a second round.
+// Evaluations, us: 1152 x 1152 76 / 71, 300 x 1152 75 / 66, pairs 300 x 1664 76 / 67, at k = 256 2304 x 2304 329 / 282; whole channels 700 x 3328 99 / 92.
+int workgroups(int64_t n, int64_t slots) { return int(n <= slots || slots <= 8 ? std::min(n, slots) : slots - slots % 8); }
+
 // grad: the launch will ask for the fused gradient.  Without it, segments of up to 128 run two
 // workgroups per compute unit.
 int make_plan(int K, int G, int64_t nlines, int64_t naxis, CorePlan* pl, bool grad = true) {
@@ -88,9 +93,7 @@ int make_plan(int K, int G, int64_t nlines, int64_t naxis, CorePlan* pl, bool gr
   pl->mt_per_seg = (nlines + kMacroLines - 1) / kMacroLines;
   pl->n_mt = pl->mt_per_seg * pl->nseg;
   const int per_cu = (!grad && pl->L <= 128) ? 2 : 1;
-  int64_t nwg = std::min<int64_t>(pl->n_mt, int64_t(device_cu_count()) * per_cu);
-  if (nwg > 8) nwg -= nwg % 8;
-  pl->nwg = int(nwg);
+  pl->nwg = workgroups(pl->n_mt, int64_t(device_cu_count()) * per_cu);
   pl->nslot = pl->nwg + pl->nseg;
   pl->slot_grad_floats = size_t(pl->NBLK) * K * K;
   return CAFEQ_OK;
@@ -176,18 +179,21 @@ void make_v2_plan(CorePlan* pl, int share = 1) {
   pl->L = 128; pl->NBLK = 128 / pl->K; pl->NGRP = 128 / pl->G; pl->nseg = int(pl->naxis / 128);
   pl->mt_per_seg = (pl->nlines + 255) / 256;
   pl->n_mt = pl->mt_per_seg * pl->nseg;
-  int64_t nwg = std::min<int64_t>(pl->n_mt, int64_t(device_cu_count()) / share);
-  if (nwg > 8) nwg -= nwg % 8;
-  pl->nwg = int(nwg);
+  pl->nwg = workgroups(pl->n_mt, int64_t(device_cu_count()) / share);
   pl->nslot = pl->nwg + pl->nseg;
 }
-// rounds of workgroups that the loss pass takes over prepared weights and in the general kernel
+// rounds of workgroups that the loss pass takes over prepared weights and in the general kernel (in multiples of eight, as both
+// ran when the lines below were drawn)
 bool v2_rounds(int K, int G, int64_t nlines, int64_t naxis, int share, int64_t* here, int64_t* there) {
   CorePlan pl;
   if (make_plan(K, G, nlines, naxis, &pl, false)) return false;
-  *there = (pl.n_mt + pl.nwg - 1) / pl.nwg;
+  auto rounds = [&]() {
+    const int64_t nwg = pl.nwg > 8 ? pl.nwg - pl.nwg % 8 : pl.nwg;
+    return (pl.n_mt + nwg - 1) / nwg;
+  };
+  *there = rounds();
   make_v2_plan(&pl, share);
-  *here = (pl.n_mt + pl.nwg - 1) / pl.nwg;
+  *here = rounds();
   return true;
 }
 // Whether the loss pass over prepared weights is the faster one (blocks of 128: always; blocks of 32 and 64: not where there
