@@ -63,3 +63,21 @@ def test_moved_weights_are_moved_exactly(env, axis, group):
     c_ref, s_ref, _ = O.rtn_sym(moved, 4, group, axis)
     np.testing.assert_array_equal(scales.cpu().numpy(), s_ref.astype(np.float32))
     np.testing.assert_array_equal(codes.cpu().numpy(), c_ref)
+
+
+@pytest.mark.parametrize("axis,group", [(O.COL, 32), (O.ROW, 64), (O.COL, 128), (O.ROW, 256)])
+def test_bfloat16_weights_are_read_as_their_float32_values(env, axis, group):
+    """bfloat16 storage multiplies one float16 part where float32 storage multiplies three: of a value that bfloat16 holds the other two
+    are zero (or below the last bit of either), so codes, scales and errors are the same bits, for lines whose weights span 36 binades
+    too; a line with an infinity is not a number in either."""
+    torch, cafeq = env
+    W, T, P = _case(axis, 136, 512, K, 1, 7300 + group)
+    L = W if axis == O.COL else W.T
+    L[8:40] *= np.exp2(-np.random.default_rng(7301).integers(0, 37, (32, 512))).astype(np.float32)
+    L[40:72] *= np.float32(1e-30)
+    L[77, 300] = np.inf
+    W16 = _dev(torch, W).to(torch.bfloat16)
+    got = [cafeq.proxy_loss_fwd_bwd(w, _dev(torch, T), _dev(torch, P), 4, group, axis, want_grad=False, want_codes=True) for w in (W16, W16.float())]
+    assert torch.equal(got[0][2], got[1][2])
+    for a, b in zip(got[0][:1] + got[0][3:], got[1][:1] + got[1][3:]):
+        np.testing.assert_array_equal(a.cpu().numpy(), b.cpu().numpy())
