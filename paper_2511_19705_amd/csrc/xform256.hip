@@ -3,16 +3,16 @@
 //
 // A strip of 32 lines x one block is the work of TWO waves, 128 outputs each.  One wave holding all 256 (xform_core.hpp)
 // needs 128 accumulators, 128 errors and 128 weights a lane: one wave per SIMD, 184 to 288 bytes of scratch a lane, and nothing
-// that runs beside its matrix instructions.  With half of each a wave fits 256 registers without scratch, and the two waves
-// of a strip share a SIMD: one splits operands or quantizes while the other feeds the matrix pipe.
+// that runs beside its matrix instructions.  With half of each a wave fits 256 registers (loss passes over float32
+// weights keep 0 to 80 bytes a lane in scratch, the others none), and the two waves of a strip share a SIMD: one splits operands or quantizes while the other feeds the matrix pipe.
 //
 // What a half needs of the other goes through LDS: the operands of the contraction.  A stage is 32 contraction indices; the wave
-// that holds them (weights going forward, errors going back) splits them into two float16 parts in the operand's own lane order,
+// that holds them (weights going forward, errors going back) splits them into one to three float16 parts in the operand's own lane order,
 // 16 bytes a lane and part, one stage ahead, and both waves read them back.  The transform's planes (float16, two parts) stream
 // through a ring of three stages, as in xform_core.hpp, one barrier a stage.
 //
 // Arithmetic: both contractions on float16 parts rounded to nearest; the weights and the errors scaled per line, the blocks per
-// block, by powers of two.  Forward: two parts of T, three of the weights (four products: a transform that only moves weights
+// block, by powers of two.  Forward: two parts of T, three of float32 weights (four products: a transform that only moves weights
 // moves them exactly), a stage's products in a sum of their own, so that one rounding in eight is at the size of the result.  Z
 // against float64, in units of its line's root mean square, this / six bfloat16 products into one sum: rotations, 5 and 50 %
 // off them 9.6e-8 / 2.4e-7; identities 1e-4 off 9.9e-8 / 1.6e-7, 1e-2 off 1.14e-7 / 1.86e-7.  Back: two parts each, three
