@@ -31,7 +31,7 @@ struct SplitJob { const float* src; uint16_t* dst; int trans, nplanes; float* fs
 // two that puts its largest magnitude into [2^texp, 2^(texp+1)) (14: the low parts stay normal numbers; 4: sums of
 // 128 products with operands below 2^4 stay below 2^16 -- the matrix cores take denormal float16 inputs exactly), then
 // x = hi + lo (+ a third) with the parts rounded to nearest; fscale[b] receives the factor that undoes the scale.
-// minus_one (K = 256): the planes hold src_b - I.
+// minus_one (K = 256, bfloat16 planes): of src_b - I.
 //
 // rho[b*K + j]: squared norm of row j (by_row) or column j of P_b, summed in float64.
 // With rG != null the workgroup also writes the sums of rho over groups of G axis indices (what rho_group_kernel
@@ -157,21 +157,13 @@ __global__ __launch_bounds__(kSplitThreads) void split_planes_kernel(const Split
       }
     }
   }
-  // (K = 256; a block's elements in runs of four along a row)
-  auto off_identity = [&](float4 v, int row, int col) {
-    if constexpr (K == 256) {
-      if (jb.minus_one) {
-        v.x -= row == col ? 1.f : 0.f; v.y -= row == col + 1 ? 1.f : 0.f;
-        v.z -= row == col + 2 ? 1.f : 0.f; v.w -= row == col + 3 ? 1.f : 0.f;
-      }
-    }
-    return v;
-  };
   if constexpr (K == 256) {
+    if (jb.minus_one) {
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int qd = (tid + q * kSplitThreads) % QPS;
-      x[q] = jb.trans ? off_identity(x[q], qd % K, 32 * stage0 + 4 * (qd / K)) : off_identity(x[q], qd >> 3, 32 * stage0 + 4 * (qd & 7));
+      for (int q = 0; q < NQ; ++q) {
+        const int qd = tid + q * kSplitThreads, d = jb.trans ? qd % K - 32 * stage0 - 4 * (qd / K) : (qd >> 3) - 32 * stage0 - 4 * (qd & 7);
+        x[q].x -= d == 0 ? 1.f : 0.f; x[q].y -= d == 1 ? 1.f : 0.f; x[q].z -= d == 2 ? 1.f : 0.f; x[q].w -= d == 3 ? 1.f : 0.f;
+      }
     }
   }
   float hsc = 1.f;   // float16 job: the block's scale
@@ -191,9 +183,7 @@ __global__ __launch_bounds__(kSplitThreads) void split_planes_kernel(const Split
 #pragma unroll
         for (int q = 0; q < NQ; ++q) take(x[q]);
       } else {
-#pragma unroll 8
-        for (int e = tid * 4; e < K * K; e += kSplitThreads * 4)
-          take(off_identity(*reinterpret_cast<const float4*>(sb + e), e / K, e % K));
+        for (int e = tid * 4; e < K * K; e += kSplitThreads * 4) take(*reinterpret_cast<const float4*>(sb + e));
       }
       m = cluster_allmax<64>(m);
       if (finite) __syncthreads();                                         // (the maxima before have been read)

@@ -140,8 +140,6 @@ struct Carver {
 // (two float16 parts carry 22 of float32's 24 bits; the error that leaves in z / scale grows with the number of
 // levels, so finer grids keep the six-product bfloat16 forward).
 bool core_forward_f16(int K, int G, int bits) { return K == 128 && G <= 128 && bits <= 4; }
-// Blocks of 256 with groups inside the block on the symmetric grid: xform256.hip, both operands' planes in two float16 parts.
-bool core_halves(int K, const GroupPlan& gp, bool asym) { return K == 256 && gp.gspan == 1 && !asym; }
 
 // Plans of one matrix for a call with / without gradient: `first` is the pass that computes the losses,
 // `gpass` the pass that writes the gradient partials (== first when the gradient is fused into it).
@@ -1084,7 +1082,7 @@ int cafeq_apply_transform(const cafeq_mat* W, const cafeq_xform* x, int axis, in
   uint16_t* planes = static_cast<uint16_t*>(ws);
   // half-precision forward operands where the kernel variant exists: two planes, and the per-block factors
   // in the room of the third
-  float* fs = core_forward_f16(x->k, x->k, 4) || x->k == 256 ? reinterpret_cast<float*>(planes + size_t(x->nb) * 2 * x->k * x->k) : nullptr;
+  float* fs = core_forward_f16(x->k, x->k, 4) ? reinterpret_cast<float*>(planes + size_t(x->nb) * 2 * x->k * x->k) : nullptr;
   {
     const SplitRequest req{side == CAFEQ_SIDE_T ? x->T : x->Tinv, planes, col ? 1 : 0, fs ? 2 : kFwdPlanes, fs};
     if ((rc = launch_split_planes_multi(&req, 1, x->k, x->nb, st))) return rc;
@@ -1156,8 +1154,7 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
   SingleWs w = carve_single(ws, pp, nb, grad);
   const QGrid grid = grid_for(cfg);
   const float beta = beta_for(cfg, grid);
-  const bool halves = core_halves(K, gp, asym);
-  const bool f16 = v2 || halves || core_forward_f16(K, gp.Gk, cfg->bits);
+  const bool f16 = v2 || core_forward_f16(K, gp.Gk, cfg->bits);
 
   CoreParams p;
   fill_common(&p, W, pl, x->rep);
@@ -1166,7 +1163,7 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
   if (!(v2 && v2_splits_planes(K, false, codes || scales))) {
     // (prepared weights: float16 planes for both operands, scaled so that the rounding error fits float16)
     const SplitRequest req[2] = {{x->T, w.m.pfwd, col ? 1 : 0, v2 ? v2_fwd_parts(K) : f16 ? 2 : kFwdPlanes, f16 ? w.m.fs : nullptr, v2 ? 1 : 0, v2 ? 4 : 14},
-                                 {x->Tinv, w.m.pinv, col ? 1 : 0, kInvPlanes, v2 || halves ? w.m.fsi : nullptr, 0, v2 ? 4 : 14}};
+                                 {x->Tinv, w.m.pinv, col ? 1 : 0, kInvPlanes, v2 ? w.m.fsi : nullptr, 0, 4}};
     // rho per axis index, its sums per segment-level group (the loss sweep) and per group (the gradient pass)
     // (groups inside a block, or of a few whole blocks: the same launch)
     const bool rg_inline = rho_groups_inline(K, nb, gp.Gk, x->rep);
@@ -1175,7 +1172,7 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
     if (!rg_inline && (rc = launch_rho_groups(w.rho, K, x->rep, gp.Gk, naxis / gp.Gk, w.m.rG, st))) return rc;
     if (grad && gp.gspan > 1 && (rc = launch_rho_groups(w.rho, K, x->rep, gp.G, naxis / gp.G, w.m.rGreal, st))) return rc;
   }
-  p.Afwd = w.m.pfwd; p.Ainv = w.m.pinv; p.fscale = f16 ? w.m.fs : nullptr; p.fscale_inv = v2 || halves ? w.m.fsi : nullptr;
+  p.Afwd = w.m.pfwd; p.Ainv = w.m.pinv; p.fscale = f16 ? w.m.fs : nullptr; p.fscale_inv = v2 ? w.m.fsi : nullptr;
   p.grid = grid; p.do_inverse = 1; p.do_grad = pp.fused ? 1 : 0; p.loss_kind = kLossSur; p.beta = beta;
   p.Tfwd = x->T; p.Tback = x->Tinv; p.rG_out = w.m.rG;
   p.rG = w.m.rG; p.codes = codes; p.scales = scales; p.slot_grad = w.m.slot_grad; p.slot_hdr = w.slot_hdr;
@@ -1301,15 +1298,14 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
   DualWs w = carve_dual(ws, qa, qb, nb, grad);
   const QGrid grid = grid_for(cfg);
   // the gradient-free pass over 128 x 128 blocks (one block per segment) takes half-precision forward operands
-  const bool halvesA = core_halves(K, ga, asym), halvesB = core_halves(K, gb, asym);
-  const bool f16A = v2A || halvesA || core_forward_f16(K, ga.Gk, cfg->bits), f16B = v2B || halvesB || core_forward_f16(K, gb.Gk, cfg->bits);
+  const bool f16A = v2A || core_forward_f16(K, ga.Gk, cfg->bits), f16B = v2B || core_forward_f16(K, gb.Gk, cfg->bits);
 
   // (passes that split their operands themselves: no planes, and every header is written by them)
   if (!(pair_launch && v2_splits_planes(K, true, false))) {
     const SplitRequest req[4] = {{x->T, w.a.pfwd, 1, v2A ? v2_fwd_parts(K) : f16A ? 2 : kFwdPlanes, f16A ? w.a.fs : nullptr, v2A ? 1 : 0, v2A ? 4 : 14},
-                                 {x->Tinv, w.a.pinv, 1, kInvPlanes, v2A || halvesA ? w.a.fsi : nullptr, 0, v2A ? 4 : 14},
+                                 {x->Tinv, w.a.pinv, 1, kInvPlanes, v2A ? w.a.fsi : nullptr, 0, 4},
                                  {x->Tinv, w.b.pfwd, 0, v2B ? v2_fwd_parts(K) : f16B ? 2 : kFwdPlanes, f16B ? w.b.fs : nullptr, v2B ? 1 : 0, v2B ? 4 : 14},
-                                 {x->T, w.b.pinv, 0, kInvPlanes, v2B || halvesB ? w.b.fsi : nullptr, 0, v2B ? 4 : 14}};
+                                 {x->T, w.b.pinv, 0, kInvPlanes, v2B ? w.b.fsi : nullptr, 0, 4}};
     if ((rc = launch_split_planes_multi(req, 4, K, nb, st, w.hdrA, pa.nslot + pb.nslot))) return rc;
   }
   // Each member: the loss pass, then (two-pass gradient) straight away the gradient pass over
@@ -1321,14 +1317,14 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
   a.Afwd = w.a.pfwd; a.Ainv = w.a.pinv;
   a.grid = grid; a.do_inverse = 1; a.do_grad = qa.fused ? 1 : 0; a.loss_kind = kLossLse; a.lse_t = lse_t;
   a.codes = codesU; a.scales = scalesU; a.slot_grad = w.a.slot_grad; a.slot_hdr = w.hdrA;
-  a.fscale = f16A ? w.a.fs : nullptr; a.fscale_inv = v2A || halvesA ? w.a.fsi : nullptr;
+  a.fscale = f16A ? w.a.fs : nullptr; a.fscale_inv = v2A ? w.a.fsi : nullptr;
   a.asym = asym ? 1 : 0;
   a.mins = asym && scalesU ? scalesU + A->rows * (A->cols / ga.G) : nullptr;   // the minima follow the scales
   fill_common(&b, B, pb, x->rep);
   b.Afwd = w.b.pfwd; b.Ainv = w.b.pinv;
   b.grid = grid; b.do_inverse = 1; b.do_grad = qb.fused ? 1 : 0; b.loss_kind = kLossLse; b.lse_t = lse_t;
   b.codes = codesV; b.scales = scalesV; b.slot_grad = w.b.slot_grad; b.slot_hdr = w.hdrB;
-  b.fscale = f16B ? w.b.fs : nullptr; b.fscale_inv = v2B || halvesB ? w.b.fsi : nullptr;
+  b.fscale = f16B ? w.b.fs : nullptr; b.fscale_inv = v2B ? w.b.fsi : nullptr;
   b.asym = asym ? 1 : 0;
   b.mins = asym && scalesV ? scalesV + (B->rows / gb.G) * B->cols : nullptr;
   a.Tfwd = b.Tback = x->T;
@@ -1400,11 +1396,10 @@ int cafeq_dual_proxy_loss_fwd_bwd(const cafeq_mat* A, const cafeq_mat* B, const 
   return dual_impl(A, B, x, cfg, lse_t, losses, gradT, codesU, scalesU, codesV, scalesV, ws, stream, nullptr);
 }
 
-// the correction's operand planes (two float16 parts, of what it adds to the identity: the factors in the room of the third plane)
+// The correction's operand planes; for xform256.hip (blocks of 256, groups inside the block) of what it adds to the identity
 static int split_correction(const AdaptiveWs& w, int k, int nb, const GroupPlan& gp, CoreParams* p, hipStream_t st) {
-  float* fs = core_halves(k, gp, false) ? reinterpret_cast<float*>(w.planes + size_t(nb) * 2 * k * k) : nullptr;
-  const SplitRequest req{w.Cmat, w.planes, 0, fs ? 2 : kFwdPlanes, fs, 0, 14, fs ? 1 : 0};
-  p->Afwd = w.planes; p->Ainv = nullptr; p->fscale = fs;
+  const SplitRequest req{w.Cmat, w.planes, 0, kFwdPlanes, nullptr, 0, 14, k == 256 && gp.gspan == 1};
+  p->Afwd = w.planes; p->Ainv = nullptr;
   return launch_split_planes_multi(&req, 1, k, nb, st);
 }
 

@@ -36,7 +36,7 @@ int launch_core_k32(int G, int axis, const CoreParams& p, hipStream_t st);
 int launch_core_k64(int G, int axis, const CoreParams& p, hipStream_t st);
 int launch_core_k128(int G, int axis, const CoreParams& p, hipStream_t st);
 int launch_core_k256(int G, int axis, const CoreParams& p, hipStream_t st);
-// xform256.hip: blocks of 256, groups inside the block, symmetric grid (p.fscale, p.fscale_inv: float16 planes, two parts each)
+// xform256.hip: blocks of 256, groups inside the block, symmetric grid
 int launch_xform256(int G, int axis, const CoreParams& p, hipStream_t st);
 // the same on the min/max grid of Eq. (1) (p.asym; gradient-free variants)
 int launch_core_asym_k32(int G, int axis, const CoreParams& p, hipStream_t st);

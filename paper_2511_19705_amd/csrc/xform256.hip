@@ -3,24 +3,26 @@
 //
 // A strip of 32 lines x one block is the work of TWO waves, 128 outputs each.  One wave holding all 256 (xform_core.hpp)
 // needs 128 accumulators, 128 errors and 128 weights a lane: one wave per SIMD, 184 to 288 bytes of scratch a lane, and nothing
-// that runs beside its matrix instructions.  With half of each a wave fits 256 registers (loss passes over float32
-// weights keep 0 to 80 bytes a lane in scratch, the others none), and the two waves of a strip share a SIMD: one splits operands or quantizes while the other feeds the matrix pipe.
+// that runs beside its matrix instructions.  With half of each a wave fits 256 registers without scratch, and the two waves of a strip
+// share a SIMD: one splits operands or quantizes while the other feeds the matrix pipe.
 //
 // What a half needs of the other goes through LDS: the operands of the contraction.  A stage is 32 contraction indices; the wave
-// that holds them (weights going forward, errors going back) splits them into one to three float16 parts in the operand's own lane order,
-// 16 bytes a lane and part, one stage ahead, and both waves read them back.  The transform's planes (float16, two parts) stream
-// through a ring of three stages, as in xform_core.hpp, one barrier a stage.
+// that holds them (weights going forward, errors going back) splits them into one to three bfloat16 parts in the operand's own lane order,
+// 16 bytes a lane and part, one stage ahead, and both waves read them back.  The transform's planes (bfloat16, three parts going
+// forward, two going back) stream through 96 KB of LDS, two stages of 48 KB and then three of 32, one barrier a stage.
 //
-// Arithmetic: both contractions on float16 parts rounded to nearest; the weights and the errors scaled per line, the blocks per
-// block, by powers of two.  Forward: two parts of T, three of float32 weights (four products: a transform that only moves weights
-// moves them exactly), a stage's products in a sum of their own, so that one rounding in eight is at the size of the result.  Z
-// against float64, in units of its line's root mean square, this / six bfloat16 products into one sum: rotations, 5 and 50 %
-// off them 9.6e-8 / 2.4e-7; identities 1e-4 off 9.9e-8 / 1.6e-7, 1e-2 off 1.14e-7 / 1.86e-7.  Back: two parts each, three
-// products.  Corrections of adaptive rounding: two parts each of the weights and of what the correction adds to the identity.
+// Arithmetic: the bfloat16 parts of xform_core.hpp, unscaled: every operand keeps float32's range and going forward all of its 24 bits,
+// however far it lies below the rest of its line or block, and a transform that only moves weights moves them exactly.  (Two and three
+// float16 parts, scaled per line and block, are a third fewer products, but hold nothing below 2^-39 of the largest and all bits only
+// down to 2^-14 of it.)  Forward: six products, a stage's in a sum of their own, so that one rounding in
+// eight is at the size of the result.  Z against float64, in units of its line's root mean square, this / all products into one sum:
+// rotations, 5 and 50 % off them 9.1e-8 / 2.4e-7; identities 1e-4 off 1.0e-7 / 1.6e-7, 1e-2 off 9.9e-8 / 1.9e-7; identities and
+// permutations exact.  Back: two parts each, three products.
+// Adaptive rounding multiplies by what the correction adds to the identity.
 //
-// Bound: issue and LDS.  A stage is 24 (forward: 32) matrix instructions a wave, two waves a SIMD, against 20 (22) KB of operands read
-// a wave.  9B-shaped (V, O) pair, groups of 64, loss passes 56 + 110 -> 38 + 67 us (one wave per strip, xform_core.hpp, before);
-// the corrected weights' codes 47 + 80 -> 27 + 42.
+// Bound: issue of matrix instructions, 48 a stage and wave going forward and 24 going back, two waves a SIMD, against 30 (20) KB of
+// operands read a wave.  9B-shaped (V, O) pair, groups of 64, loss passes 56 + 110 -> 40 + 75 us (one wave per strip, xform_core.hpp,
+// before; on float16 parts 37 + 66); the corrected weights' codes 47 + 80 -> 34 + 57.
 #include "gj_panel.hpp"   // StaticFor
 #include "xform_launch.hpp"
 
@@ -28,42 +30,38 @@ namespace cafeq {
 namespace {
 
 constexpr int kXhK = 256, kXhWaves = 8, kXhThreads = kXhWaves * 64;
-constexpr int kXhPlane = kXhK * 64, kXhStage = 2 * kXhPlane, kXhRing = 3;   // bytes: a part of a stage, a stage; stages in LDS
+constexpr int kXhPlane = kXhK * 64, kXhFwd = kFwdPlanes * kXhPlane, kXhBack = kInvPlanes * kXhPlane;   // bytes: a part of a stage, stages
+constexpr int kXhRing = 2 * kXhFwd;
+static_assert(kXhRing == 3 * kXhBack, "two stages going forward, three going back");
 constexpr int kXhSlot = 4 * 2 * 3 * 1024;                                   // operands of a stage: [strip][step][part][lane][16 B]
-constexpr int kXhOpnd = kXhRing * kXhStage, kXhXch = kXhOpnd + 2 * kXhSlot; // LDS offsets
-constexpr int kXhHdr = kXhXch + 4 * 256 * 4;
+constexpr int kXhOpnd = kXhRing, kXhXch = kXhOpnd + 2 * kXhSlot;            // LDS offsets
+constexpr int kXhHdr = kXhXch + 2 * 256 * 4;
 constexpr int kXhLds = kXhHdr + (kXhWaves * kHdrFloats + kXhWaves) * 4;
+// Where stage s lies.  Going forward in halves of the ring, stage 0 in the second and stage 7 in the first; going back in thirds, stage 0 in
+// the last, which stage 7 of the way there does not touch, and stage 7 in the first, which stage 0 of the next way there does not.
+constexpr int fwd_at(int s) { return ((s + 1) & 1) * kXhFwd; }
+constexpr int back_at(int s) { return (s + 2) % 3 * kXhBack; }
 static_assert(kXhLds <= 160 * 1024, "one workgroup per compute unit");
 static_assert(kMacroLines == 4 * 32, "four strips a workgroup");
-
-// the power of two that puts a magnitude m into [2^14, 2^15), and the factor back (zeros, denormals, infinities: any)
-__device__ __forceinline__ void line_scale(float m, float* there, float* back) {
-  int e = int(__float_as_uint(m) >> 23);
-  e = e < 32 ? 32 : (e > 254 ? 254 : e);
-  *there = __uint_as_float(uint32_t(268 - e) << 23);
-  *back = __uint_as_float(uint32_t(e - 14) << 23);
-}
 
 // What a launch does: Z alone; a loss call (errors, inverse transform, partial sums); codes and scales of corrected weights
 // (adaptive rounding), whose transform is the identity plus a small correction: the planes hold the correction alone, and
 // the weights themselves are added to its product
 enum XhMode { kXhApply, kXhLoss, kXhCorrect };
-// B16: bfloat16 weights, whose eight significant bits are one part: the other two are zeros, and without them a forward stage is
-// 16 matrix instructions instead of 32 with the same sums.  Loss pass of 2304 x 9216, groups of 256, with its gradient: 430 ->
-// 406 us a call; (V, O) pair of d_model 3584, groups of 64: 334 -> 292; codes of 36864 x 4608, groups of 128: 912 -> 765.
+// B16: bfloat16 weights, one part themselves: the other two are zeros, and without them a forward stage is 24 matrix instructions
+// instead of 48 with the same sums.  Loss pass of 2304 x 9216, groups of 256, with its gradient: 420 -> 403 us a call; (V, O) pair of
+// d_model 3584, groups of 64: 312 -> 296; codes of 36864 x 4608, groups of 128: 913 -> 789.
 template <int G, int AXIS, XhMode MODE, bool B16>
 __global__ __launch_bounds__(kXhThreads, 2) void xform256_kernel(const CoreParams p) {
   constexpr bool INV = MODE == kXhLoss;
   constexpr int K = kXhK, KT = 4, NST = 8;           // tiles of a wave, stages of a block
-  constexpr int WP = MODE == kXhCorrect ? 2 : B16 ? 1 : 3;   // float16 parts of a weight
+  constexpr int WP = B16 ? 1 : 3;                    // parts of a weight
   static_assert(MODE != kXhCorrect || !B16, "adaptive rounding works on float32");
   constexpr int TPG = G >= 128 ? 4 : G / 32;         // tiles of one of the wave's groups
   constexpr int NG = 4 / TPG;                        // groups of a wave (G = 256: its half of the one)
   constexpr int NGS = G == 256 ? 1 : 2 * NG;         // groups of a segment
   extern __shared__ __align__(16) unsigned char smem[];
-  float* wmx = reinterpret_cast<float*>(smem + kXhXch);       // [2 halves][128 lines]: largest weight, ...
-  float* zmx = wmx + 256;                                     // ... largest transformed weight,
-  float* zsg = zmx + 256;                                     // (G = 256) the value there
+  float* zsg = reinterpret_cast<float*>(smem + kXhXch);       // (G = 256) [2 halves][128 lines]: largest transformed weight
   int* zix = reinterpret_cast<int*>(zsg + 256);               // and its index
   float* hred = reinterpret_cast<float*>(smem + kXhHdr);      // [8][kHdrFloats]
   float* wvm = hred + kXhWaves * kHdrFloats;                  // [8]
@@ -84,15 +82,14 @@ __global__ __launch_bounds__(kXhThreads, 2) void xform256_kernel(const CoreParam
   auto blk_id = [&](int sg) { return AXIS == CAFEQ_AXIS_ROW && p.rep != 1 ? sg / p.rep : sg; };
   int cb = blk_id(seg);
 
-  // stage s of block b into ring stage `dst`, asynchronously (opaque to the compiler, which would otherwise drain it before every
-  // LDS read; the ring starts at LDS address 0)
+  // stage s of block b to LDS address `to`, asynchronously (opaque to the compiler, which would otherwise drain it before every LDS read)
   const uint32_t voff = uint32_t(tid) * 16u;
-  constexpr int NF = kXhStage / 16 / kXhThreads;     // requests of a wave and stage
-  auto dma = [&](const uint16_t* base, int b, int s, int dst) {
-    const unsigned char* src = reinterpret_cast<const unsigned char*>(base) + (int64_t(b) * NST + s) * kXhStage;
-    const uint32_t at = uint32_t(dst) * kXhStage + uint32_t(wave) * 1024u;
+  constexpr int NFB = kXhBack / 16 / kXhThreads;      // requests of a wave and stage, going back
+  auto dma = [&](const uint16_t* base, int bytes, int b, int s, int to) __attribute__((always_inline)) {
+    const unsigned char* src = reinterpret_cast<const unsigned char*>(base) + (int64_t(b) * NST + s) * bytes;
+    const uint32_t at = uint32_t(to) + uint32_t(wave) * 1024u;
 #pragma unroll
-    for (int i = 0; i < NF; ++i)
+    for (int i = 0; i < bytes / (16 * kXhThreads); ++i)
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                    :: "s"(at + uint32_t(i) * (kXhThreads * 16u)), "v"(voff), "s"(src + i * (kXhThreads * 16)) : "memory");
   };
@@ -134,7 +131,7 @@ __global__ __launch_bounds__(kXhThreads, 2) void xform256_kernel(const CoreParam
     }
   };
   // sixteen values of a stage (tile s % 4 of the wave that holds it) into the operand slot of stage s
-  auto put = [&](auto parts, const float* x, float sc, int s) __attribute__((always_inline)) {
+  auto put = [&](auto parts, const float* x, int s) __attribute__((always_inline)) {
     constexpr int NP = decltype(parts)::value;
     unsigned char* at = smem + kXhOpnd + (s & 1) * kXhSlot + strip * (kXhSlot / 4) + lane * 16;
 #pragma unroll
@@ -144,89 +141,83 @@ __global__ __launch_bounds__(kXhThreads, 2) void xform256_kernel(const CoreParam
       for (int i = 0; i < 4; ++i) {
         float y0 = x[8 * c2 + 2 * i], y1 = x[8 * c2 + 2 * i + 1];
         asm volatile("" : "+v"(y0), "+v"(y1));       // (not ahead of the branch that this stands in: no registers there)
-        y0 *= sc; y1 *= sc;
+        // (of an infinity the other parts are not a number, and so is all that it meets)
+        if constexpr (NP == 1) { y0 = fmaf(0.f, y0, y0); y1 = fmaf(0.f, y1, y1); }
 #pragma unroll
         for (int pl = 0; pl < NP; ++pl) {
-          const uint32_t both = pack_f16(y0, y1);
-          const halfx2 hh = __builtin_bit_cast(halfx2, both);
-          y0 -= float(hh[0]); y1 -= float(hh[1]);
-          u[pl][i] = both;
+          u[pl][i] = pack_bf16(y0, y1);
+          y0 -= bf16_lo_f32(u[pl][i]); y1 -= bf16_hi_f32(u[pl][i]);
         }
       }
 #pragma unroll
       for (int pl = 0; pl < NP; ++pl) *reinterpret_cast<uintx4*>(at + (c2 * 3 + pl) * 1024) = u[pl];
     }
   };
-  // the products of a stage: the wave's four tiles of 32 outputs, two steps of 16 contraction indices; `between` runs
-  // once the first step's operands are requested
+  // the products of a stage whose planes lie at `at`: the wave's four tiles of 32 outputs, two steps of 16 contraction indices; `between`
+  // runs once the first step's operands are requested
   const int swz = (ln >> 2) & 3;
   const int ao[2] = {ln * 64 + ((h ^ swz) << 4), ln * 64 + (((2 + h) ^ swz) << 4)};
-  auto products = [&](auto parts, floatx16 (&c)[KT], floatx16& late, int st, int s, auto&& between) __attribute__((always_inline)) {
-    constexpr int NP = decltype(parts)::value;
-    const unsigned char* a = smem + st * kXhStage + half * (128 * 64);
+  auto products = [&](auto ahead, floatx16 (&c)[KT], floatx16& late, int at, int s, auto&& between) __attribute__((always_inline)) {
+    constexpr bool FWD = decltype(ahead)::value;
+    constexpr int NP = FWD ? WP : 2, XP = FWD ? kFwdPlanes : kInvPlanes;   // parts of the weights (errors), of the transform
+    const unsigned char* a = smem + at + half * (128 * 64);
     const unsigned char* b = smem + kXhOpnd + (s & 1) * kXhSlot + strip * (kXhSlot / 4) + lane * 16;
-    halfx8 y[2][NP], x[2][2][2];                     // x: [tile's parity][step][part]
-    auto read = [&](int t) {
+    bf16x8 y[2][NP], x[2][XP];                       // x: [step]
+    auto read = [&](int i) {
 #pragma unroll
-      for (int c2 = 0; c2 < 2; ++c2)
-#pragma unroll
-        for (int pl = 0; pl < 2; ++pl)
-          x[t % 2][c2][pl] = as_halfx8(*reinterpret_cast<const uintx4*>(a + t * (32 * 64) + ao[c2] + pl * kXhPlane));
+      for (int pl = 0; pl < XP; ++pl)
+        x[i % 2][pl] = as_bf16x8(*reinterpret_cast<const uintx4*>(a + (i / 2) * (32 * 64) + ao[i % 2] + pl * kXhPlane));
     };
 #pragma unroll
     for (int c2 = 0; c2 < 2; ++c2)
 #pragma unroll
-      for (int pl = 0; pl < NP; ++pl) y[c2][pl] = as_halfx8(*reinterpret_cast<const uintx4*>(b + (c2 * 3 + pl) * 1024));
+      for (int pl = 0; pl < NP; ++pl) y[c2][pl] = as_bf16x8(*reinterpret_cast<const uintx4*>(b + (c2 * 3 + pl) * 1024));
     read(0);
     between();
-    if (NP != 2 && s > 0) { c[KT - 1] += late; asm volatile("" : "+v"(c[KT - 1])); }
+    if (FWD && s > 0) { c[KT - 1] += late; asm volatile("" : "+v"(c[KT - 1])); }
     floatx16 sum[2];
-    // (the next tile's operands are requested before this one's products; fences keep the compiler from holding more of them)
+    // (the next step's operands are requested before this one's products; fences keep the compiler from holding more of them)
 #pragma unroll
-    for (int t = 0; t < KT; ++t) {
-      if (t + 1 < KT) read(t + 1);
+    for (int i = 0; i < 2 * KT; ++i) {
+      const int t = i / 2, c2 = i % 2;
+      if (i + 1 < 2 * KT) read(i + 1);
       __builtin_amdgcn_sched_barrier(0);
-      const auto& xt = x[t % 2];
-      if constexpr (NP != 2) {
-        // (going forward: added to the tile's sum once the next tile's products are on their way)
+      if constexpr (FWD) {
+        // (added to the tile's sum once the next tile's products are on their way)
         floatx16& l = sum[t % 2];
+        if (c2 == 0) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) l[v] = 0.f;
-#pragma unroll
-        for (int c2 = 0; c2 < 2; ++c2) {
-          l = CAFEQ_MFMA_F16(xt[c2][0], y[c2][0], l);
+          for (int v = 0; v < 16; ++v) l[v] = 0.f;
         }
-#pragma unroll
-        for (int c2 = 0; c2 < 2; ++c2) {
-          l = CAFEQ_MFMA_F16(xt[c2][1], y[c2][0], l);
-          if constexpr (NP == 3) {
-            l = CAFEQ_MFMA_F16(xt[c2][0], y[c2][1], l);
-            l = CAFEQ_MFMA_F16(xt[c2][0], y[c2][2], l);
-          }
+        // (smallest terms first)
+        l = CAFEQ_MFMA_BF16(x[c2][2], y[c2][0], l);
+        if constexpr (NP == 3) {
+          l = CAFEQ_MFMA_BF16(x[c2][0], y[c2][2], l);
+          l = CAFEQ_MFMA_BF16(x[c2][1], y[c2][1], l);
         }
-        if (t > 0) {
+        l = CAFEQ_MFMA_BF16(x[c2][1], y[c2][0], l);
+        if constexpr (NP == 3) l = CAFEQ_MFMA_BF16(x[c2][0], y[c2][1], l);
+        l = CAFEQ_MFMA_BF16(x[c2][0], y[c2][0], l);
+        if (c2 == 0 && t > 0) {
           c[t - 1] += sum[(t + 1) % 2];
           asm volatile("" : "+v"(c[t - 1]));               // (now, and not at the end of the loop)
         }
       } else {
-#pragma unroll
-        for (int c2 = 0; c2 < 2; ++c2) {
-          c[t] = CAFEQ_MFMA_F16(xt[c2][1], y[c2][0], c[t]);
-          c[t] = CAFEQ_MFMA_F16(xt[c2][0], y[c2][1], c[t]);
-          c[t] = CAFEQ_MFMA_F16(xt[c2][0], y[c2][0], c[t]);
-        }
+        c[t] = CAFEQ_MFMA_BF16(x[c2][1], y[c2][0], c[t]);
+        c[t] = CAFEQ_MFMA_BF16(x[c2][0], y[c2][1], c[t]);
+        c[t] = CAFEQ_MFMA_BF16(x[c2][0], y[c2][0], c[t]);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    if constexpr (NP != 2) late = sum[(KT - 1) % 2];
+    if constexpr (FWD) late = sum[(KT - 1) % 2];
   };
+  const std::integral_constant<bool, true> ahead{};
+  const std::integral_constant<bool, false> backward{};
   const std::integral_constant<int, WP> wparts{};
   const std::integral_constant<int, 2> eparts{};
 
-  dma(p.Afwd, cb, 0, 0);
-  dma(p.Afwd, cb, 1, 1);
+  dma(p.Afwd, kXhFwd, cb, 0, fwd_at(0));
   load_w(seg, mis, 0, 16);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the barriers below stand before the first use)
 
   // running sums per lane
   float s_l2 = 0.f, s_errz = 0.f, s_wsq = 0.f, s_sur = 0.f, s_va2[NG], m_ref = -INFINITY;
@@ -259,7 +250,6 @@ __global__ __launch_bounds__(kXhThreads, 2) void xform256_kernel(const CoreParam
     m_ref = -INFINITY;
   };
 
-  int st = 0;                                        // ring stage in use
   for (int64_t mt = mt0; mt < mt1; ++mt) {
     if (seg != cur_seg) {
       if constexpr (INV) flush(cur_seg);
@@ -274,28 +264,17 @@ __global__ __launch_bounds__(kXhThreads, 2) void xform256_kernel(const CoreParam
     const bool has_next = mt + 1 < mt1;
     const int pseg = has_next ? nseg_ : seg, pmis = has_next ? nmis : mis, nbk = blk_id(pseg);
 
-    // ---- the lines' scales, from both halves' largest weights
     if (!valid) {
 #pragma unroll
       for (int f = 0; f < 64; ++f) wreg[f] = 0.f;
     }
-    float m = 0.f;
-#pragma unroll
-    for (int f = 0; f < 64; ++f) m = fmaxf(m, fabsf(wreg[f]));
     if constexpr (INV) {
 #pragma unroll
       for (int f = 0; f < 64; ++f) s_wsq = fmaf(wreg[f], wreg[f], s_wsq);
     }
     asm volatile("" : "+v"(s_wsq));                  // (sums are taken where they stand, not where registers are short)
-    m = fmaxf(m, __shfl_xor(m, 32));
-    if (h == 0) wmx[mine] = m;
-    __syncthreads();
-    float wsc, usc;
-    m = fmaxf(m, wmx[other]);
-    line_scale(m, &wsc, &usc);
-    if (WP == 1 && m == INFINITY) wsc = NAN;         // (what an infinity's second part makes of its line)
-    usc *= p.fscale[cb];
-    if (half == 0) put(wparts, wreg, wsc, 0);
+    if (half == 0) put(wparts, wreg, 0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // stage 0 has landed
     __syncthreads();
 
     // ---- forward transform
@@ -307,23 +286,23 @@ __global__ __launch_bounds__(kXhThreads, 2) void xform256_kernel(const CoreParam
     floatx16 late;
 #pragma unroll
     for (int s = 0; s < NST; ++s) {
-      const int dst = st == 0 ? kXhRing - 1 : st - 1;
-      if (s + 2 < NST) dma(p.Afwd, cb, s + 2, dst);
-      else if (INV) dma(p.Ainv, cb, s + 2 - NST, dst);
-      else dma(p.Afwd, nbk, s + 2 - NST, dst);
-      products(wparts, acc, late, st, s, [&]() __attribute__((always_inline)) {
-        if (s + 1 < NST && half == (s + 1) / 4) put(wparts, wreg + 16 * ((s + 1) % 4), wsc, s + 1);
+      if (s + 1 < NST) dma(p.Afwd, kXhFwd, cb, s + 1, fwd_at(s + 1));
+      else if (INV) dma(p.Ainv, kXhBack, cb, 0, back_at(0));
+      else dma(p.Afwd, kXhFwd, nbk, 0, fwd_at(0));
+      products(ahead, acc, late, fwd_at(s), s, [&]() __attribute__((always_inline)) {
+        if (s + 1 < NST && half == (s + 1) / 4) put(wparts, wreg + 16 * ((s + 1) % 4), s + 1);
       });
-      vm_wait(NF);                                   // the next stage has landed: only this step's fill is younger
+      vm_wait(0);                                    // the next stage has landed
       __syncthreads();
-      st = st == kXhRing - 1 ? 0 : st + 1;
     }
-    if constexpr (WP != 2) acc[KT - 1] += late;
+    if constexpr (INV) dma(p.Ainv, kXhBack, cb, 1, back_at(1));
+    acc[KT - 1] += late;
+    if constexpr (MODE == kXhCorrect) {
 #pragma unroll
-    for (int t = 0; t < KT; ++t)
+      for (int t = 0; t < KT; ++t)
 #pragma unroll
-      for (int v = 0; v < 16; ++v)
-        acc[t][v] = MODE == kXhCorrect ? fmaf(acc[t][v], usc, wreg[16 * t + v]) : acc[t][v] * usc;
+        for (int v = 0; v < 16; ++v) acc[t][v] += wreg[16 * t + v];
+    }
     if constexpr (!INV) load_w(pseg, pmis, 0, 16);
 
     if constexpr (MODE == kXhApply) {
@@ -360,7 +339,7 @@ __global__ __launch_bounds__(kXhThreads, 2) void xform256_kernel(const CoreParam
         argmax4<8 * (R / 4) + R % 4>(tz, tj, acc[0][R], acc[1][R], acc[2][R], acc[3][R]);
       };
       StaticFor<1, 16>::run(step);
-      float gz[NG], zl = 0.f;
+      float gz[NG], zl = 0.f;                        // zl: the line's largest
       int gj[NG];
 #pragma unroll
       for (int gi = 0; gi < NG; ++gi) {
@@ -377,17 +356,14 @@ __global__ __launch_bounds__(kXhThreads, 2) void xform256_kernel(const CoreParam
         gj[gi] = G == 256 ? j + 128 * half : j - gi * G;      // index inside the group
         zl = fmaxf(zl, fabsf(zs));
       }
-      if constexpr (INV || G == 256) {
-        if (h == 0) {
-          zmx[mine] = zl;
-          if constexpr (G == 256) { zsg[mine] = gz[0]; zix[mine] = gj[0]; }
-        }
+      if (G == 256 || lse) {
+        if constexpr (G == 256)
+          if (h == 0) { zsg[mine] = gz[0]; zix[mine] = gj[0]; }
         if (lse) {
           const float wm = cluster_allmax<64>(valid ? zl : 0.f);
           if (lane == 0) wvm[wave] = wm;
         }
         __syncthreads();
-        zl = fmaxf(zl, zmx[other]);
         if constexpr (G == 256) {
           const float oz = zsg[other];
           const int oj = zix[other];
@@ -403,11 +379,6 @@ __global__ __launch_bounds__(kXhThreads, 2) void xform256_kernel(const CoreParam
             m_ref = nm;
           }
         }
-      }
-      float esc = 0.f, eus = 0.f;                    // the errors' scale: none exceeds the line's largest value
-      if constexpr (INV) {
-        line_scale(zl, &esc, &eus);
-        eus *= p.fscale_inv[cb];
       }
 #pragma unroll
       for (int gi = 0; gi < NG; ++gi) {
@@ -464,7 +435,7 @@ __global__ __launch_bounds__(kXhThreads, 2) void xform256_kernel(const CoreParam
 #pragma unroll
         for (int f = 0; f < 64; ++f) err[f] = acc[f / 16][f % 16];
         asm volatile("" : "+v"(s_errz));
-        if (half == 0) put(eparts, err, esc, 0);
+        if (half == 0) put(eparts, err, 0);
         __syncthreads();
         floatx16 d[KT];
 #pragma unroll
@@ -473,25 +444,23 @@ __global__ __launch_bounds__(kXhThreads, 2) void xform256_kernel(const CoreParam
           for (int v = 0; v < 16; ++v) d[t][v] = 0.f;
 #pragma unroll
         for (int s = 0; s < NST; ++s) {
-          const int dst = st == 0 ? kXhRing - 1 : st - 1;
-          if (s + 2 < NST) dma(p.Ainv, cb, s + 2, dst);
-          else dma(p.Afwd, nbk, s + 2 - NST, dst);
+          if (s + 2 < NST) dma(p.Ainv, kXhBack, cb, s + 2, back_at(s + 2));
+          else if (s + 1 == NST) dma(p.Afwd, kXhFwd, nbk, 0, fwd_at(0));
           // the next strip's weights, where the errors leave their registers, behind the step's fill
           if (s >= 4) load_w(pseg, pmis, 4 * (s - 4), 4 * (s - 3));
-          products(eparts, d, d[0], st, s, [&]() __attribute__((always_inline)) {
-            if (s + 1 < NST && half == (s + 1) / 4) put(eparts, err + 16 * ((s + 1) % 4), esc, s + 1);
+          products(backward, d, d[0], back_at(s), s, [&]() __attribute__((always_inline)) {
+            if (s + 1 < NST && half == (s + 1) / 4) put(eparts, err + 16 * ((s + 1) % 4), s + 1);
           });
           // younger than the next stage's fill: this step's, and this step's and the last one's weights
-          vm_wait(NF + (s >= 4 ? 4 * NWL : 0) + (s >= 5 ? 4 * NWL : 0));
+          if (s + 1 < NST) vm_wait((s + 2 < NST ? NFB : 0) + (s >= 4 ? 4 * NWL : 0) + (s >= 5 ? 4 * NWL : 0));
           __syncthreads();
-          st = st == kXhRing - 1 ? 0 : st + 1;
         }
         float l2 = 0.f;
 #pragma unroll
         for (int t = 0; t < KT; ++t)
 #pragma unroll
           for (int v = 0; v < 16; ++v) l2 = fmaf(d[t][v], d[t][v], l2);
-        s_l2 += (l2 * eus) * eus;
+        s_l2 += l2;
       }
     }
     seg = nseg_;
@@ -533,7 +502,7 @@ int launch_x256(int axis, const CoreParams& p, hipStream_t st) {
 }  // namespace
 
 int launch_xform256(int G, int axis, const CoreParams& p, hipStream_t st) {
-  if (!p.fscale || !p.Afwd || p.do_grad || (p.do_inverse && (!p.Ainv || !p.fscale_inv))) return CAFEQ_ERR_INVALID_ARG;
+  if (p.fscale || !p.Afwd || p.do_grad || (p.do_inverse && !p.Ainv)) return CAFEQ_ERR_INVALID_ARG;
   if (p.Zout)
     return axis == CAFEQ_AXIS_COL ? launch_x256<256, CAFEQ_AXIS_COL, kXhApply>(p, st) : launch_x256<256, CAFEQ_AXIS_ROW, kXhApply>(p, st);
   switch (G) {
