@@ -128,7 +128,9 @@ int cafeq_version(void);
 
 /* Bytes of scratch the given call needs for these arguments (0 on invalid input).
  * `a` is the only matrix for single-matrix calls; `b` and `x` may be NULL where the
- * call does not use them.  Only shapes are read, data pointers are ignored. */
+ * call does not use them.  Only shapes are read, data pointers are ignored.  Loss calls and learning loops with groups that are
+ * none of 32, 64, 128 and 256 (whole channels) keep the transformed weights there, blocks of 64 and more: 4 bytes a weight, lines
+ * rounded up to 128; for a pair those of the larger member. */
 size_t cafeq_workspace_bytes(int call_id, const cafeq_mat* a, const cafeq_mat* b,
                              const cafeq_xform* x, const cafeq_quant_cfg* cfg);
 

@@ -295,7 +295,12 @@ struct MemberWs {
   float* zkeep;               // groups that span segments: the transformed weights between the sweeps
   uint2* sorted; int* start;  // gradient pass by records
 };
-void carve_member(Carver& c, const PassPlans& pp, int nb, bool grad, bool want_rG, MemberWs* w) {
+size_t zkeep_floats(const PassPlans& pp) {
+  const CorePlan& pl = pp.first;
+  return pp.gp.gspan > 1 && pl.K >= kKeepBlock ? size_t(pl.n_mt) * kMacroLines * size_t(pl.L) : 0;
+}
+// zkeep: room for zkeep_floats(pp); members whose sweeps run one after the other share it
+void carve_member(Carver& c, const PassPlans& pp, int nb, bool grad, bool want_rG, float* zkeep, MemberWs* w) {
   const CorePlan& pl = pp.first;
   const bool big = pp.gp.gspan > 1;
   w->fs = c.take<float>(nb);
@@ -311,7 +316,7 @@ void carve_member(Carver& c, const PassPlans& pp, int nb, bool grad, bool want_r
   w->rec_mm = c.take<float2>(mm ? size_t(pl.naxis / pl.G) * size_t(pl.nlines) : 0);
   w->grec_mm = c.take<float2>(mm ? size_t(pl.naxis / pp.gp.G) * size_t(pl.nlines) : 0);
   if (!mm) w->rec_mm = w->grec_mm = nullptr;
-  w->zkeep = big && pl.K >= kKeepBlock ? c.take<float>(size_t(pl.n_mt) * kMacroLines * size_t(pl.L)) : nullptr;
+  w->zkeep = zkeep_floats(pp) ? zkeep : nullptr;
   w->sorted = c.take<uint2>(pp.gather ? grad_gather_entries(pl.K, pp.gp.G, pl.naxis, pl.nlines) : 0);
   w->start = c.take<int>(pp.gather ? grad_gather_starts(pl.K, pp.gp.G, pl.naxis) : 0);
 }
@@ -329,7 +334,7 @@ SingleWs carve_single(void* ws, const PassPlans& pp, int nb, bool grad) {
   w.slot_hdr = c.take<float>(size_t(pl.nslot) * kHdrFloats);
   w.mmid = c.take<float>(grad ? size_t(nb) * pl.K * pl.K : 0);
   w.x1 = c.take<float>(grad ? size_t(nb) * pl.K * pl.K : 0);
-  carve_member(c, pp, nb, grad, true, &w.m);
+  carve_member(c, pp, nb, grad, true, c.take<float>(zkeep_floats(pp)), &w.m);
   w.bytes = c.off;
   return w;
 }
@@ -347,8 +352,9 @@ DualWs carve_dual(void* ws, const PassPlans& qa, const PassPlans& qb, int nb, bo
   w.hdrB = w.hdrA ? w.hdrA + size_t(qa.first.nslot) * kHdrFloats : nullptr;
   w.gp = c.take<float>(grad ? size_t(nb) * K * K : 0);
   w.x1 = c.take<float>(grad ? size_t(nb) * K * K : 0);
-  carve_member(c, qa, nb, grad, false, &w.a);
-  carve_member(c, qb, nb, grad, false, &w.b);
+  float* zkeep = c.take<float>(std::max(zkeep_floats(qa), zkeep_floats(qb)));
+  carve_member(c, qa, nb, grad, false, zkeep, &w.a);
+  carve_member(c, qb, nb, grad, false, zkeep, &w.b);
   w.bytes = c.off;
   return w;
 }

@@ -118,3 +118,24 @@ def test_argument_errors_of_every_entry_point_are_reported_before_any_launch():
     lib.cafeq_strerror.restype = ctypes.c_char_p
     for code in range(-8, 1):
         assert len(lib.cafeq_strerror(code)) > 0
+
+
+def test_members_of_a_pair_share_the_room_for_their_transformed_weights():
+    """Groups that span segments, blocks of 64 and more: 4 bytes a weight, of the larger member alone."""
+    if not os.path.exists(LIB):
+        pytest.skip("library not built")
+    from paper_2511_19705_amd import cafeq
+    ref = ctypes.byref
+
+    def size(call, k, rep, axis, *shapes):
+        mats = [cafeq.Mat(4096, r, c, c, cafeq.F32, None) for r, c in shapes]
+        naxis = mats[0].cols if axis == cafeq.AXIS_COL else mats[0].rows
+        x = cafeq.Xform(None, None, k, naxis // (k * (rep if axis == cafeq.AXIS_ROW else 1)), rep)
+        cfg = cafeq.QuantCfg(4, 0, axis, cafeq.Q_SYM)
+        return cafeq.lib.cafeq_workspace_bytes(call, ref(mats[0]), ref(mats[1]) if len(mats) > 1 else None, ref(x), ref(cfg))
+
+    for k, rep in ((64, 1), (128, 1), (128, 2), (256, 2)):
+        A, B = (4096, 4096), (4096 * rep, 4096)
+        pair = size(cafeq.CALL_DUAL, k, rep, cafeq.AXIS_COL, A, B)
+        alone = size(cafeq.CALL_PROXY, k, 1, cafeq.AXIS_COL, A), size(cafeq.CALL_PROXY, k, rep, cafeq.AXIS_ROW, B)
+        assert 0 < pair < sum(alone) - 3.8 * 4096 * 4096
