@@ -147,3 +147,11 @@ def test_bfloat16_weights_are_read_as_their_float32_values(env, axis, group):
             a, b = ((x[i] if axis == O.COL else x[i].T).copy() for x in (was, now))
             a[77, K // per:] = b[77, K // per:] = 0
             np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("nb", [16, 17, 33])
+@pytest.mark.parametrize("axis", [O.COL, O.ROW])
+def test_gradient_through_the_inverse_of_many_blocks(env, nb, axis):
+    """Up to 16 blocks (16 tiles each, 256 compute units) take the contraction of P^T G in two halves side by side, more in two turns."""
+    W, T, P = _case(axis, 24, nb * K, K, 1, 7600 + nb)
+    _check_single(env, W, T, P, 4, 128, axis, 1)
