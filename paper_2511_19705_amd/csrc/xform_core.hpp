@@ -325,9 +325,11 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
   static_assert(SWEEP == 0 || (LONGG && K >= kKeepBlock), "sweeps: groups that span segments");
   constexpr bool ZIN = SWEEP == 2, keep = SWEEP == 1;
   static_assert(!ZIN || !F16, "no forward transform");
-  const bool do_inverse = SWEEP == 0 ? p.do_inverse != 0 : ZIN;
-  int8_t* const out_codes = keep ? nullptr : p.codes;
-  float* const out_scales = keep ? nullptr : p.scales;
+  // (The parameters themselves at each use: in locals, or behind lambdas, they cost the instances with a gradient scalar registers.
+  // 4608 x 9216 at k = 64 and 8 bits, groups of 32: locals 184 us, this 179; 3624 x 17536 pair: lambdas 511, this 506)
+#define CAFEQ_DO_INVERSE (SWEEP == 0 ? p.do_inverse != 0 : ZIN)
+#define CAFEQ_CODES (keep ? nullptr : p.codes)
+#define CAFEQ_SCALES (keep ? nullptr : p.scales)
   static_assert(!LONGG || (!GRAD && Geo<K, G>::NGRP == 1), "long groups: gradient-free, one group per segment");
   using g = Geo<K, G>;
   constexpr bool GRAD_ON = GRAD && g::GRAD_OK;
@@ -488,7 +490,7 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
   int seg = seg_first, mis = mis_first;
   for (int64_t mt = mt0; mt < mt1; ++mt) {
     if (seg != cur_seg) {
-      if (do_inverse || p.do_grad || keep) flush(cur_seg);   // partial buffers exist only for loss calls
+      if (CAFEQ_DO_INVERSE || p.do_grad || keep) flush(cur_seg);   // partial buffers exist only for loss calls
       cur_seg = seg;
     }
     const int64_t line = int64_t(mis) * kMacroLines + wave * kStripLines + ln;
@@ -542,7 +544,7 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
           dma(p.Afwd, FWDP, cb[tq / KT], tq % KT, dst);
         } else {
           nw = NIW;
-          if (do_inverse) dma(p.Ainv, kInvPlanes, cb[(tq - NT) / KT], (tq - NT) % KT, dst);
+          if (CAFEQ_DO_INVERSE) dma(p.Ainv, kInvPlanes, cb[(tq - NT) / KT], (tq - NT) % KT, dst);
           else dma(p.Afwd, FWDP, nbk[(tq - NT) / KT], (tq - NT) % KT, dst);
         }
       }
@@ -556,7 +558,7 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const float x0 = wreg[8 * c + 2 * i], x1 = wreg[8 * c + 2 * i + 1];
-            if (do_inverse || keep) s_wsq = fmaf(x0, x0, fmaf(x1, x1, s_wsq));
+            if (CAFEQ_DO_INVERSE || keep) s_wsq = fmaf(x0, x0, fmaf(x1, x1, s_wsq));
             const float y0 = x0 * wsc, y1 = x1 * wsc;
             if constexpr (ASYM) {
               bh[i] = pack_f16(y0, y1);
@@ -598,7 +600,7 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const float x0 = wreg[8 * c + 2 * i], x1 = wreg[8 * c + 2 * i + 1];
-          if (do_inverse || keep) s_wsq = fmaf(x0, x0, fmaf(x1, x1, s_wsq));
+          if (CAFEQ_DO_INVERSE || keep) s_wsq = fmaf(x0, x0, fmaf(x1, x1, s_wsq));
           const uint32_t ph = pack_bf16(x0, x1);
           const float r0 = x0 - bf16_lo_f32(ph), r1 = x1 - bf16_hi_f32(ph);
           const uint32_t pm = pack_bf16(r0, r1);
@@ -690,10 +692,10 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
     }
 
     float err[L / 2];   // quantization error E = dequant(Q(Z)) - Z, same layout as the accumulators
-    const bool want_q = keep || out_codes || out_scales || do_inverse || (LONGG && p.rec);
+    const bool want_q = keep || CAFEQ_CODES || CAFEQ_SCALES || CAFEQ_DO_INVERSE || (LONGG && p.rec);
     const bool big = LONGG && (ZIN || (!keep && p.gspan > 1));                           // the group spans several segments
     const bool first_of_group = !big || seg % p.gspan == 0;          // group-level sums are taken once
-    const bool lse_on = p.loss_kind == kLossLse && do_inverse;
+    const bool lse_on = p.loss_kind == kLossLse && CAFEQ_DO_INVERSE;
     if (want_q) {
       // ---- per-group absmax (+ argmax), codes, error in place
       float gz[NGRP];   // signed value at the arg-max element
@@ -742,12 +744,12 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
           }
         }
         gz[gi] = zs; gj[gi] = j;
-        if constexpr (LONGG) if (!(out_codes || out_scales || do_inverse)) continue;   // record-only sweep
+        if constexpr (LONGG) if (!(CAFEQ_CODES || CAFEQ_SCALES || CAFEQ_DO_INVERSE)) continue;   // record-only sweep
         // symmetric grid: steps of absmax / qmax around zero; Eq. (1): steps of (max - min) / levels from min
         const float span = ASYM ? mx - mn : a;
         const float inv = grid_inv(span, p.grid.qmax);
         const float s = grid_scale(span, p.grid.qmax);
-        if (out_scales && valid && h == 0 && first_of_group) {
+        if (CAFEQ_SCALES && valid && h == 0 && first_of_group) {
           int64_t at;
           if (big) {
             const int64_t gidx = seg / p.gspan, ng = p.nseg / p.gspan;
@@ -756,7 +758,7 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
             const int64_t gidx = ax0 / G + gi;   // group index along the axis
             at = AXIS == CAFEQ_AXIS_COL ? line * (p.cols / G) + gidx : gidx * p.cols + line;
           }
-          out_scales[at] = s;
+          CAFEQ_SCALES[at] = s;
           if constexpr (ASYM) if (p.mins) p.mins[at] = mn;
         }
 #pragma unroll
@@ -779,23 +781,25 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
           }
           qpk[f4] = pack4(q[0], q[1], q[2], q[3]);
         }
-        if (do_inverse) {
+        if (CAFEQ_DO_INVERSE) {
           const float a2 = a * a;
           if (h == 0) s_va2[gi] += a2;
           if (p.loss_kind == kLossSur && h == 0) s_sur = fmaf(a2, p.rG[seg * NGRP + gi], s_sur);
         }
       }
 
-      asm volatile("" : "+v"(s_errz));   // (summed here, not where the inverse transform has no registers for the errors)
-      if (out_codes && valid) {
+      // (summed here, not where the inverse transform has no registers for the errors: segments of 256 116 -> 107 us for 2304 x 9216 at
+      // k = 32, 121 -> 117 at k = 64.  Elsewhere there are registers, and the fence costs 2 to 5 %: 79.3 -> 83.4 with codes at k = 64)
+      if constexpr (SWEEP != 0 || L > 128) asm volatile("" : "+v"(s_errz));
+      if (CAFEQ_CODES && valid) {
 #pragma unroll
         for (int f4 = 0; f4 < L / 8; ++f4) {
           const int j0 = 8 * f4 + 4 * h;
           if (AXIS == CAFEQ_AXIS_COL) {
-            *reinterpret_cast<uint32_t*>(out_codes + line * p.cols + ax0 + j0) = qpk[f4];
+            *reinterpret_cast<uint32_t*>(CAFEQ_CODES + line * p.cols + ax0 + j0) = qpk[f4];
           } else {
             // uniform row pointer + 32-bit lane offset
-            int8_t* rowp = out_codes + (ax0 + 8 * f4) * p.cols;
+            int8_t* rowp = CAFEQ_CODES + (ax0 + 8 * f4) * p.cols;
             const uint32_t loff = uint32_t(4 * h) * uint32_t(p.cols) + uint32_t(line);
 #pragma unroll
             for (int e = 0; e < 4; ++e) rowp[loff + uint32_t(e) * uint32_t(p.cols)] = int8_t(qpk[f4] >> (8 * e));
@@ -904,11 +908,11 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
 
     // ---- the next strip's weights: wreg and the W parts are dead from here on (the staged
     // copy is read by the other waves, protected by the barriers of the inverse phase)
-    if (!do_inverse) load_w(pseg, pmis);
+    if (!CAFEQ_DO_INVERSE) load_w(pseg, pmis);
 
     // ---- inverse transform of the error and the l2 proxy: same stage order; the error registers
     // 8c..8c+7 of the lane are the B operand of step c, split on the fly into hi + mid
-    if (do_inverse) {
+    if (CAFEQ_DO_INVERSE) {
       // B operand of MFMA step c: the lane's error registers 8c..8c+7 as bfloat16 hi and mid parts
       auto split_e = [&](int c, bf16x8& vh, bf16x8& vm) {
         uint32_t eh[4], em[4];
@@ -995,7 +999,10 @@ __global__ __launch_bounds__(kThreads, (!GRAD && Geo<K, G>::L <= 128) ? 2 : 1) v
     for (int i = 0; i < NBLK; ++i) cb[i] = nbk[i];
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the last macro-tile's (unused) prefetches
-  if (do_inverse || p.do_grad || keep) flush(cur_seg);
+  if (CAFEQ_DO_INVERSE || p.do_grad || keep) flush(cur_seg);
+#undef CAFEQ_DO_INVERSE
+#undef CAFEQ_CODES
+#undef CAFEQ_SCALES
 }
 
 }  // namespace cafeq
