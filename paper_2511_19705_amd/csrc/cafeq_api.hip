@@ -180,8 +180,12 @@ void make_v2_plan(CorePlan* pl, int share = 1) {
   pl->nwg = workgroups(pl->n_mt, int64_t(device_cu_count()) / share);
   pl->nslot = pl->nwg + pl->nseg;
 }
-// rounds of workgroups that the loss pass takes over prepared weights and in the general kernel (in multiples of eight, as both
-// ran when the lines below were drawn)
+// rounds of workgroups that the loss pass takes over prepared weights and in the general kernel, in multiples of eight, as both ran when
+// the lines below were drawn.  Both now take a workgroup a tile while they fit (workgroups()): more than eight tiles that are no multiple of
+// eight count as two rounds here and run as one.  Timed again over 9600 shapes of 32 to 36864 lines, launches replayed from a graph, the
+// choices below lose against the faster pass of each shape, on average: without codes 0.2 to 4 % at k = 32 and 2 to 6 at 64 (most with groups
+// of 32 and 64: prepared / general .92 in bfloat16, 1.05 in float32 for 65 to 256 tiles of the general kernel, .77 and .90 up to 512); pairs 0 to 4, in float32 at k = 64
+// 9; with codes 1 to 12; and 10 to 26 with bfloat16 codes along rows, which the general kernel writes faster at every size (1.1 to 2).
 bool v2_rounds(int K, int G, int64_t nlines, int64_t naxis, int share, int64_t* here, int64_t* there) {
   CorePlan pl;
   if (make_plan(K, G, nlines, naxis, &pl, false)) return false;
