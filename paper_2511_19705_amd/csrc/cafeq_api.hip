@@ -517,7 +517,9 @@ int run_core(int K, int axis, const GroupPlan& gp, CoreParams p, float2* rec, fl
   if (gp.gspan > 1) {
     CoreParams s1 = p;
     s1.do_inverse = 0; s1.do_grad = 0; s1.codes = nullptr; s1.scales = nullptr; s1.Zout = nullptr;
-    s1.slot_hdr = zkeep ? p.slot_hdr : nullptr; s1.slot_grad = nullptr; s1.zkeep = zkeep; s1.sweep = zkeep ? 1 : 0; s1.rec = rec; s1.longg = 1; s1.gspan = 1; s1.grec = nullptr;
+    s1.slot_hdr = zkeep ? p.slot_hdr : nullptr; s1.slot_grad = nullptr;
+    s1.zkeep = zkeep; s1.sweep = zkeep ? 1 : 0;
+    s1.rec = rec; s1.longg = 1; s1.gspan = 1; s1.grec = nullptr;
     s1.mins = nullptr; s1.rec_mm = p.asym ? rec_mm : nullptr;
     if (p.asym && (!rec_mm || !grec_mm)) return CAFEQ_ERR_INVALID_ARG;
     if ((rc = launch_core(K, gp.Gk, axis, s1, st))) return rc;
@@ -1307,7 +1309,7 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
   hipStream_t st = static_cast<hipStream_t>(stream);
   DualWs w = carve_dual(ws, qa, qb, nb, grad);
   const QGrid grid = grid_for(cfg);
-  // the gradient-free pass over 128 x 128 blocks (one block per segment) takes half-precision forward operands
+  // float16 forward operands: passes over prepared weights, and the gradient-free general pass over blocks of 128 (one block per segment)
   const bool f16A = v2A || core_forward_f16(K, ga.Gk, cfg->bits), f16B = v2B || core_forward_f16(K, gb.Gk, cfg->bits);
 
   // (passes that split their operands themselves: no planes, and every header is written by them)

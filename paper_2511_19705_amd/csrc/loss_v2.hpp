@@ -51,7 +51,7 @@ constexpr int kV2MacroLines = kV2Waves * 32;
 // 223 -> 174 us).
 constexpr int v2_tile_bytes(int parts) { return 32 * 128 * 2 * parts; }
 // operand planes of a segment (T and T^-1, 64 KB each for blocks of 128), the waves' sums
-constexpr int v2_lds(int K) { return (2 * v2_fwd_parts(K) + 4) * 128 * K + kV2Waves * kHdrFloats * 4 + 64 + kV2Waves * 4 * 8; }
+constexpr int v2_lds(int K) { return (2 * v2_fwd_parts(K) + 4) * 128 * K + kV2Waves * kHdrFloats * 4 + 64 + kV2Waves * 2 * 8; }
 
 // Marks in a line's scale, a power of two: 32 (64) of its inputs are far smaller than the segment's largest
 constexpr uint32_t kFar32 = 1, kFar64 = 2;
@@ -186,13 +186,14 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
 
   // (SELF) the segment's planes into LDS, as split_planes_kernel (aux_kernels.hip) writes them: a block scaled by the power of two that
   // puts its largest finite magnitude into [2^4, 2^5), two float16 parts; the factors back.  A thread takes one 16-byte vector of
-  // each of a block's stages (K = 64: of one of the two).  With want_rg also the sums of T^-1's squares over each group's
-  // indices, the contraction's: into rg, and to memory for the gradient pass (workgroups that share a segment write the same).
-  double* rsum = reinterpret_cast<double*>(hred + kV2Waves * kHdrFloats + 16);   // [8 waves][4]
+  // each of a block's stages (K = 64: of one of the two).  With want_rg (single matrices: blocks of 64) also the sums of T^-1's
+  // squares over each group's indices, the contraction's: into rg, and to memory for the gradient pass (workgroups that share a segment write
+  // the same).
+  double* rsum = reinterpret_cast<double*>(hred + kV2Waves * kHdrFloats + 16);   // [8 waves][2]
   auto split_blocks = [&](const int (&bid)[NB], float (&fwd_back)[NB], float (&inv_back)[NB], bool want_rg, int sg, float (&rg)[NGRP])
       __attribute__((always_inline)) {
     constexpr bool TR = AXIS == CAFEQ_AXIS_COL;    // the operands' rows are the blocks' columns
-    static_assert(!SELF || ((K == 128 || K == 64) && FP == 2), "blocks of 64 and 128");
+    static_assert(!SELF || ((PAIR && K == 128 || K == 64) && FP == 2), "blocks of 64, pairs' blocks of 128");
     constexpr int NS = K == 128 ? 4 : 1, LK = K == 128 ? 7 : 6;
     // (transposed: lanes along a row of the block, a contraction index each; else four lanes along 128 bytes of a row)
     const int out = TR ? tid & (K - 1) : (tid >> 2) & (K - 1), cq = TR ? (tid >> LK) & 3 : tid & 3, c2 = cq >> 1, hh = cq & 1;
@@ -221,15 +222,13 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
       }
     if (want_rg) {
 #pragma unroll
-      for (int b = 0; b < NB; ++b)
+      for (int b = 0; b < NB; ++b) {
+        double t = 0;
 #pragma unroll
-        for (int st = 0; st < NS; ++st) {
-          double t = 0;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) t += double(x[1][b][st][e]) * x[1][b][st][e];
-          t = wave_sum(t);
-          if (lane == 0) rsum[wave * 4 + b * NS + st] = t;
-        }
+        for (int e = 0; e < 8; ++e) t += double(x[1][b][0][e]) * x[1][b][0][e];
+        t = wave_sum(t);
+        if (lane == 0) rsum[wave * 2 + b] = t;
+      }
     }
     float mx[2][NB];
     for (int finite = 0; finite < 2; ++finite) {   // (infinite entries are looked for only where there is one)
@@ -269,9 +268,7 @@ __device__ __forceinline__ void loss_v2_body(const CoreParams& p, const unsigned
         for (int ww = 0; ww < kV2Waves; ++ww)
 #pragma unroll
           for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int st = 0; st < NS; ++st)
-              if ((b * K + 32 * (K == 128 ? st : ww >> 2)) / G == gi) t += rsum[ww * 4 + b * NS + st];
+            if ((b * K + 32 * (ww >> 2)) / G == gi) t += rsum[ww * 2 + b];
         rg[gi] = float(t);
         if (tid == 0) p.rG_out[int64_t(sg) * NGRP + gi] = rg[gi];
       }

@@ -105,10 +105,10 @@ struct CoreParams {
   const void* W;
   int dtype;
   int64_t rows, cols, ld;
-  const uint16_t* Afwd;  // [nb][K/32 stages][3 planes][K][32] bf16: forward operand in ring-stage order
-  const uint16_t* Ainv;  // [nb][K/32 stages][2 planes][K][32] bf16: inverse operand
-  const float* fscale;   // half-precision forward (F16 variant; else null): Afwd holds two float16 planes per stage of
-                         // the block scaled by a power of two, fscale[block] is the factor that undoes that scale
+  const uint16_t* Afwd;  // forward operand in ring-stage order, [nb][K/32 stages][parts][K][32]: three bfloat16 parts, or, where fscale is set,
+                         // two float16 parts (three for prepared passes over blocks of 32) of the block scaled by a power of two
+  const uint16_t* Ainv;  // inverse operand, [nb][K/32 stages][2 parts][K][32]: bfloat16, float16 scaled likewise where fscale_inv is set
+  const float* fscale;   // [nb]: the factors that undo the forward operand's scales (F16 variant, prepared passes; else null)
   int rep;               // AXIS_ROW: row-block q uses block q / rep
   int nseg;
   int64_t nlines;
