@@ -333,7 +333,7 @@ def core_workload(args):
         elems = A.numel() + B.numel()
         run = lambda n: cafeq.optimize_pair(A, B, T, bits, g, rep, 5.0, 1e-3, n)
         metric = "learning iterations, weight-elements/s (Adam on the LogSumExp surrogate, 9B-shaped attention V/O pair, blocks of 256)"
-        flop_el, parts, kern, name = 4 * k, 9, "xform_core_kernel<256,64,*,false,true> (loss pass)", cfg["name"] + "_adam"
+        flop_el, parts, kern, name = 4 * k, 9, "xform256_kernel<64,*,loss> (loss pass)", cfg["name"] + "_adam"
 
         def cpu():
             from oracle import cafeq_oracle as O
@@ -357,7 +357,7 @@ def core_workload(args):
                 P, _ = cafeq.block_inverse(T)
                 cafeq.dual_proxy_loss_fwd_bwd(A, B, T, P, bits, g, rep, 5.0, want_grad=True)
         metric = "proxy-loss fwd+bwd weight-elements/s (9B-shaped attention V/O pair, per-head 256 x 256 dual transform)"
-        flop_el, parts, kern, name = 4 * k, 9, "xform_core_kernel<256,64,*,false,true> (loss pass)", cfg["name"] + "_dual"
+        flop_el, parts, kern, name = 4 * k, 9, "xform256_kernel<64,*,loss> (loss pass)", cfg["name"] + "_dual"
 
         def cpu():
             from oracle import cafeq_oracle as O
@@ -385,7 +385,7 @@ def core_workload(args):
             for _ in range(n):
                 cafeq.adaptive_round_step(U, V, cu, su, cv, sv, bits, g, k, rep, half=0)
         metric = "adaptive-rounding iterations, weight-elements/s (Alg. 1, 9B-shaped attention V/O pair)"
-        flop_el, parts, kern, name = 2 * k, 6, "xform_core_kernel<256,64,*,false> (transform + requantize)", cfg["name"]
+        flop_el, parts, kern, name = 2 * k, 6, "xform256_kernel<64,*,correct> (transform + requantize)", cfg["name"]
 
         def cpu():
             from oracle import cafeq_oracle as O
