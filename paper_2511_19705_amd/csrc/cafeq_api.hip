@@ -12,6 +12,7 @@ namespace cafeq {
 int launch_grad_owner_timed(const GradOwnerJob* jobs, int n, int loss_kind, float beta, float lse_t, const double* lse_ms,
                             hipStream_t st, const LossArgs* fold);
 int launch_grad_v2_timed(const CoreParams& p, hipStream_t st);
+int launch_core32_timed(int axis, const CoreParams& p, hipStream_t st);
 int launch_grad_pass_timed(int K, int axis, const CoreParams& p, hipStream_t st);
 int launch_grad_gather_timed(int K, const GradGatherJob* jobs, int n, const LossArgs& la, const VArgs* va, hipStream_t st);
 }  // namespace cafeq
@@ -81,7 +82,7 @@ int resolve_group(const cafeq_quant_cfg* cfg, int64_t naxis, int K, GroupPlan* g
 int workgroups(int64_t n, int64_t slots) { return int(n <= slots || slots <= 8 ? std::min(n, slots) : slots - slots % 8); }
 
 // grad: the launch will ask for the fused gradient.  Without it, segments of up to 128 run two
-// workgroups per compute unit.
+// workgroups per compute unit; segments of 32 do in either case.
 int make_plan(int K, int G, int64_t nlines, int64_t naxis, CorePlan* pl, bool grad = true) {
   if (!supported_block(K)) return CAFEQ_ERR_UNSUPPORTED;
   if (!(G == 32 || G == 64 || G == 128 || G == 256)) return CAFEQ_ERR_UNSUPPORTED;
@@ -92,7 +93,7 @@ int make_plan(int K, int G, int64_t nlines, int64_t naxis, CorePlan* pl, bool gr
   pl->nseg = int(naxis / pl->L);
   pl->mt_per_seg = (nlines + kMacroLines - 1) / kMacroLines;
   pl->n_mt = pl->mt_per_seg * pl->nseg;
-  const int per_cu = (!grad && pl->L <= 128) ? 2 : 1;
+  const int per_cu = pl->L == 32 || (!grad && pl->L <= 128) ? 2 : 1;
   pl->nwg = workgroups(pl->n_mt, int64_t(device_cu_count()) * per_cu);
   pl->nslot = pl->nwg + pl->nseg;
   pl->slot_grad_floats = size_t(pl->NBLK) * K * K;
@@ -148,7 +149,7 @@ bool core_forward_f16(int K, int G, int bits) { return K == 128 && G <= 128 && b
 // faster (blocks of 128), and for groups that span several segments.
 // asym: the min/max grid of Eq. (1); its kernel variants are gradient-free, so the gradient always takes the
 // second pass.
-struct PassPlans { CorePlan first, gpass; GroupPlan gp; bool two, fused, v2, asym, gather; };
+struct PassPlans { CorePlan first, gpass; GroupPlan gp; bool two, fused, v2, asym, gather, core32; };
 bool is_minmax(const cafeq_quant_cfg* cfg) { return cfg->mode == CAFEQ_Q_ASYM_MINMAX; }
 // levels and the surrogate's constant for either grid (Sec. 4.1: 1 / (2^b - 1)^2 for Eq. (1); a quarter of the
 // squared step of the symmetric grid)
@@ -278,6 +279,7 @@ int plan_passes(int K, const GroupPlan& gp, int64_t nlines, int64_t naxis, bool 
   const size_t fl = core_lds_bytes(K, gp.Gk, true);
   const bool fused_ok = fl != 0 && fl <= 160 * 1024 && gp.gspan == 1 && !(K == 128 && gp.Gk <= 128) && !asym;
   pp->gather = grad && gather;
+  pp->core32 = K == 32 && gp.G == 32 && !v2 && !asym;   // (a kernel of its own, which needs no prepared planes: core32.hip)
   pp->two = grad && (!fused_ok || gather);
   pp->fused = grad && fused_ok && !gather;
   int rc = make_plan(K, gp.Gk, nlines, naxis, &pp->first, pp->fused);
@@ -506,8 +508,12 @@ void set_prepared(CoreParams* p, const cafeq_mat* W, int axis) {
 // first one left in zkeep, so they see bit-identical transformed weights).
 int run_core(int K, int axis, const GroupPlan& gp, CoreParams p, float2* rec, float2* grec, bool want_rec,
              hipStream_t st, const cafeq_mat* prepared_of = nullptr, float2* rec_mm = nullptr,
-             float2* grec_mm = nullptr, float* zkeep = nullptr) {
+             float2* grec_mm = nullptr, float* zkeep = nullptr, bool core32 = false) {
   int rc;
+  if (core32) {
+    p.rec = want_rec ? rec : nullptr;
+    return launch_core32_timed(axis, p, st);
+  }
   if (prepared_of) {
     // loss pass over the prepared copy of the weights
     set_prepared(&p, prepared_of, axis);
@@ -637,6 +643,9 @@ int timed_launch(hipStream_t st, F&& launch, int kind = 0) {
 }  // namespace
 int launch_core(int K, int G, int axis, const CoreParams& p, hipStream_t st) {
   return timed_launch(st, [&] { return launch_core_raw(K, G, axis, p, st); });
+}
+int launch_core32_timed(int axis, const CoreParams& p, hipStream_t st) {
+  return timed_launch(st, [&] { return launch_core32(axis, p, st); });
 }
 int launch_loss_prepared(int K, int G, int axis, const CoreParams& p, hipStream_t st) {
   return timed_launch(st, [&] { return launch_loss_v2(K, G, axis, p, st); });
@@ -1172,7 +1181,7 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
   fill_common(&p, W, pl, x->rep);
   // forward operand [out][in]: T^T (COL) or T (ROW); inverse operand: Tinv^T or Tinv
   // (a pass that splits them itself: no planes, and it writes every header and rG)
-  if (!(v2 && v2_splits_planes(K, false, codes || scales))) {
+  if (!pp.core32 && !(v2 && v2_splits_planes(K, false, codes || scales))) {
     // (prepared weights: float16 planes for both operands, scaled so that the rounding error fits float16)
     const SplitRequest req[2] = {{x->T, w.m.pfwd, col ? 1 : 0, v2 ? v2_fwd_parts(K) : f16 ? 2 : kFwdPlanes, f16 ? w.m.fs : nullptr, v2 ? 1 : 0, v2 ? 4 : 14},
                                  {x->Tinv, w.m.pinv, col ? 1 : 0, kInvPlanes, v2 ? w.m.fsi : nullptr, 0, 4}};
@@ -1190,7 +1199,7 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
   p.rG = w.m.rG; p.codes = codes; p.scales = scales; p.slot_grad = w.m.slot_grad; p.slot_hdr = w.slot_hdr;
   p.asym = asym ? 1 : 0;
   p.mins = asym && scales ? scales + nlines * (naxis / gp.G) : nullptr;   // the minima follow the scales
-  if ((rc = run_core(K, cfg->axis, gp, p, w.m.rec, w.m.grec, pp.two, st, v2 ? W : nullptr, w.m.rec_mm, w.m.grec_mm, w.m.zkeep)))
+  if ((rc = run_core(K, cfg->axis, gp, p, w.m.rec, w.m.grec, pp.two, st, v2 ? W : nullptr, w.m.rec_mm, w.m.grec_mm, w.m.zkeep, pp.core32)))
     return rc;
   const cafeq_mat* mats[1] = {W};
   const PassPlans* pps[1] = {&pp};
@@ -1313,12 +1322,14 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
   const bool f16A = v2A || core_forward_f16(K, ga.Gk, cfg->bits), f16B = v2B || core_forward_f16(K, gb.Gk, cfg->bits);
 
   // (passes that split their operands themselves: no planes, and every header is written by them)
-  if (!(pair_launch && v2_splits_planes(K, true, false))) {
+  if (!(pair_launch && v2_splits_planes(K, true, false)) && !(qa.core32 && qb.core32)) {
     const SplitRequest req[4] = {{x->T, w.a.pfwd, 1, v2A ? v2_fwd_parts(K) : f16A ? 2 : kFwdPlanes, f16A ? w.a.fs : nullptr, v2A ? 1 : 0, v2A ? 4 : 14},
                                  {x->Tinv, w.a.pinv, 1, kInvPlanes, v2A ? w.a.fsi : nullptr, 0, 4},
                                  {x->Tinv, w.b.pfwd, 0, v2B ? v2_fwd_parts(K) : f16B ? 2 : kFwdPlanes, f16B ? w.b.fs : nullptr, v2B ? 1 : 0, v2B ? 4 : 14},
                                  {x->T, w.b.pinv, 0, kInvPlanes, v2B ? w.b.fsi : nullptr, 0, 4}};
-    if ((rc = launch_split_planes_multi(req, 4, K, nb, st, w.hdrA, pa.nslot + pb.nslot))) return rc;
+    // (of the members whose pass reads planes)
+    const int first = qa.core32 ? 2 : 0, last = qb.core32 ? 2 : 4;
+    if ((rc = launch_split_planes_multi(req + first, last - first, K, nb, st, w.hdrA, pa.nslot + pb.nslot))) return rc;
   }
   // Each member: the loss pass, then (two-pass gradient) straight away the gradient pass over
   // the same weights, while they are still in the memory-side cache.  The gradient pass takes
@@ -1352,7 +1363,7 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
     b.rec = qb.two ? w.b.rec : nullptr;
     if ((rc = launch_loss_prepared_pair(K, ga.Gk, a, b, st))) return rc;
   } else if ((rc = run_core(K, CAFEQ_AXIS_COL, ga, a, w.a.rec, w.a.grec, qa.two, st, v2A ? A : nullptr, w.a.rec_mm,
-                            w.a.grec_mm, w.a.zkeep))) {
+                            w.a.grec_mm, w.a.zkeep, qa.core32))) {
     return rc;
   }
   ag = a;
@@ -1360,7 +1371,7 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
                                               w.member_ref, &ag, st)))
     return rc;
   if (!pair_launch && (rc = run_core(K, CAFEQ_AXIS_ROW, gb, b, w.b.rec, w.b.grec, qb.two, st, v2B ? B : nullptr, w.b.rec_mm,
-                                     w.b.grec_mm, w.b.zkeep)))
+                                     w.b.grec_mm, w.b.zkeep, qb.core32)))
     return rc;
   bg = b;
   if (!gather && !owner && qb.two && (rc = run_grad_pass(K, CAFEQ_AXIS_ROW, B, x->rep, qb, w.b, kLossLse, 0.f, lse_t, w.hdrB, int(pb.nslot),

@@ -33,6 +33,7 @@ struct CoreParams;
 // has no instantiation or its LDS footprint does not fit.
 int launch_core(int K, int G, int axis, const CoreParams& p, hipStream_t st);
 int launch_core_k32(int G, int axis, const CoreParams& p, hipStream_t st);
+int launch_core32(int axis, const CoreParams& p, hipStream_t st);   // loss calls with groups of 32 over blocks of 32, symmetric grid
 int launch_core_k64(int G, int axis, const CoreParams& p, hipStream_t st);
 int launch_core_k128(int G, int axis, const CoreParams& p, hipStream_t st);
 int launch_core_k256(int G, int axis, const CoreParams& p, hipStream_t st);

@@ -65,7 +65,9 @@ int launch_core_t(const CoreParams& p, hipStream_t st) {
       return CAFEQ_ERR_UNSUPPORTED;
     }
   }
-  if constexpr (Geo<K, G>::GRAD_OK) {
+  if constexpr (K == 32 && G == 32) {
+    if (p.do_grad) return CAFEQ_ERR_UNSUPPORTED;   // core32.hip
+  } else if constexpr (Geo<K, G>::GRAD_OK) {
     if (p.do_grad) return launch_core_v<K, G, AXIS, true>(p, lds, st);
   }
   if constexpr (core_has_f16<K, G>()) {

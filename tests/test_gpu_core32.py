@@ -1,0 +1,45 @@
+"""GPU parity of the loss pass over blocks of 32 with groups of 32 where a workgroup walks several macro-tiles: ranges that end inside a
+segment, with one and across several, in both axes, shared row-blocks among them, every output it writes; and weights that are not
+finite, whose products with the gradient's zeros are not numbers either.  Against the oracle, with the bounds of tests/parity.py."""
+import numpy as np
+import pytest
+
+from oracle import cafeq_oracle as O
+from paper_2511_19705_amd import workloads as WL
+from tests.test_gpu_dual import _check_dual
+from tests.test_gpu_single import _case, _check_single, _dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    from paper_2511_19705_amd import cafeq
+    return torch, cafeq
+
+
+# macro-tiles of 128 lines on two workgroups a compute unit (512): 3 a segment x 200, 1 x 550, 14 x 40
+@pytest.mark.parametrize("axis,lines,naxis,rep", [(O.COL, 300, 6400, 1), (O.ROW, 100, 17600, 1), (O.ROW, 1700, 1280, 2), (O.COL, 2900, 800, 1)])
+def test_single(env, axis, lines, naxis, rep):
+    W, T, P = _case(axis, lines, naxis, 32, rep, 9300 + lines)
+    _check_single(env, W, T, P, 4, 32, axis, rep)
+
+
+def test_pair(env):
+    A, B, T = WL.small_pair(300, 6400, 32, 1, 9400, eps=0.05)
+    _check_dual(env, A, B, T, 3, 32, 1, flip_slack=True)
+
+
+@pytest.mark.parametrize("axis", [O.COL, O.ROW])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_not_finite(env, axis, value):
+    torch, cafeq = env
+    W, T, P = _case(axis, 200, 128, 32, 1, 9500)
+    W[(70, 45) if axis == O.COL else (45, 70)] = value            # input 13 of block 1
+    losses, grad, _, _ = cafeq.proxy_loss_fwd_bwd(_dev(torch, W), _dev(torch, T), _dev(torch, P), 4, 32, axis)
+    assert not np.isfinite(losses.cpu().numpy()[1])
+    bad = ~np.isfinite(grad.cpu().numpy())
+    if axis == O.ROW:
+        bad = bad.transpose(0, 2, 1)
+    assert bad[1, 13].all() and not bad[[0, 2, 3]].any()
