@@ -123,12 +123,15 @@ def _check(rc):
         raise CafeqError("cafeq call failed: %s (%d)" % (lib.cafeq_strerror(rc).decode(), rc))
 
 
+# The smallest calls wait for the host (256 x 256, blocks of 32: three launches, 23 us of the GPU): torch.cuda.current_stream(), which
+# makes a Stream object, took 2.8 us a call, the handle alone takes 0.1; integers as pointers 0.05 us against 0.14 for ctypes objects.
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """Handle of the current device's current stream."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _prepared_ptr(m, prepared, axis):
