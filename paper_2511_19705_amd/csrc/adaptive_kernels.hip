@@ -15,7 +15,8 @@
 //                      output stripe, chunk of the contraction range); codes are dequantized
 //                      on the fly; chunk partials are written out, not atomically added.
 //   gram_pair16_kernel : the same pair for heads of 128 and 256 on the 16-bit matrix pipe, operands
-//                      split exactly into three bfloat16 parts.
+//                      split exactly into three bfloat16 parts (groups of 32);
+//   gram_pair_codes_kernel : with the codes themselves on one side (longer groups).
 //   gj_panel_kernel  : (gj_panel.hpp) sums the chunk partials of S in float64 and inverts it by register-
 //                      resident Gauss-Jordan elimination.  C = I - S^-1 R follows as a batched product.
 //   gj_spd256_kernel : the inversion of S for heads of 256 as a block elimination whose products
@@ -358,6 +359,191 @@ __global__ __launch_bounds__(512) void gram_pair16_kernel(const GramArgs a) {
   LoadSet L0, L1;
   unsigned char* buf0 = gsm;
   unsigned char* buf1 = gsm + kG16BufB;
+  issue(L0, t0);
+  issue(L1, t0 + 16);
+  commit(L0, buf0);
+  for (int64_t t = t0; t < t1; t += 32) {
+    __syncthreads();                       // buf0 holds step t; buf1's readers (step t - 16) are done
+    issue(L0, t + 32);
+    products(buf0);
+    if (t + 16 < t1) {
+      commit(L1, buf1);
+      __syncthreads();                     // buf1 holds step t + 16; buf0's readers are done
+      issue(L1, t + 48);
+      products(buf1);
+      if (t + 32 < t1) commit(L0, buf0);
+    }
+  }
+
+  // partial[b][z][0|1][row][col]
+  float* out = a.partial + ((size_t(b) * gridDim.z + z) * 2) * size_t(K) * K;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int col = 128 * qJ + (tc0 + u) * 32 + ln;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int row = 128 * qI + ta * 32 + 8 * (v / 4) + 4 * h + (v % 4);
+      out[size_t(row) * K + col] = accS[u][v];
+      out[size_t(K) * K + size_t(row) * K + col] = accR[u][v];
+    }
+  }
+}
+
+// The same pair for groups of 64 and more.  Along the contraction a value is code x scale, and a code is exact in ONE bfloat16 part, so
+// with the scale s[t][group of i] taken over to the other operand,
+//     S[i][j] = sum_t q[t][i] (s[t][i] Xq[t][j]),   R[i][j] = sum_t q[t][i] (s[t][i] E[t][j]),
+// a product needs three part products instead of six, and the row side no split at all.  The right operands then belong to the row's
+// group: V = 2 versions of them in a quadrant of 128 rows at groups of 64, one from 128 on.  Groups of 32 would need four versions, eight
+// splits where the kernel above has three, and stay there.  The scales of i are divided by a power of two near the head's first one
+// (and so are S and R, of which S^-1 R alone is used): the right operands keep the exponents of Xq and E.
+// A thread takes four contraction indices of one free index a step, for every version.  Along rows four lanes read a row's 64 bytes: 16
+// cache lines a request.  With eight indices a thread (32 lines a request) the line lookups, 1024 and with the row side's codes 1280
+// a step, were what the kernel took its time for: 104 us with six part products, 117 with three.
+// 9B-shaped (V, O) pair, blocks of 256 and groups of 64: 62 + 104 -> 46.6 + 76.5 us.  Against float64 S is 8e-8 off (1.5e-7 with six
+// products and their roundings), R 1.5e-7 (2.2e-7), S^-1 R 2.5e-7 (4e-7).
+// Bound: a step's splits, LDS stores and matrix instructions between two barriers (2.9 k cycles along rows, of which matrix 0.8 k).
+constexpr int kGqHalfB = 128 * 16 + 128;                       // a part's half of a step: 128 free indices x 8 bfloat16 (both halves' rows in other banks)
+constexpr int kGqPlaneB = 2 * kGqHalfB;
+constexpr size_t gq_buf(int V) { return size_t(1 + 6 * V) * kGqPlaneB; }   // the rows' codes; per version Xq and E in three parts
+template <int AXIS, int K, int V>
+__global__ __launch_bounds__(512) void gram_pair_codes_kernel(const GramArgs a) {
+  static_assert((K == 128 || K == 256) && (V == 1 || V == 2), "quadrants of 128");
+  constexpr int QUADS = K / 128;
+  constexpr bool COL = AXIS == CAFEQ_AXIS_COL;
+  extern __shared__ __align__(16) unsigned char gsm[];
+  const int b = blockIdx.x, qI = blockIdx.y / QUADS, qJ = blockIdx.y % QUADS;
+  const int z = blockIdx.z;                      // (row-block within head, chunk)
+  const int qi = z / a.nchunk, ch = z % a.nchunk;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), ln = lane & 31, h = lane >> 5;
+  const int64_t t0 = int64_t(ch) * a.chunk;
+  const int64_t t1 = t0 + a.chunk < a.tlen ? t0 + a.chunk : a.tlen;
+  const int64_t f0 = COL ? int64_t(b) * K : (int64_t(b) * a.rep + qi) * K;
+  const int64_t C = a.cols, cg = C / a.G;
+  float unit;                                    // 2^-e: s 2^-e in [1, 2) for the head's first scale
+  {
+    const float s0 = a.scales[COL ? f0 / a.G : (int64_t(b) * a.rep * K / a.G) * C];
+    const int e = int(__float_as_uint(s0) >> 23) & 255;
+    unit = e > 0 && e < 254 ? __uint_as_float(uint32_t(254 - e) << 23) : 1.f;
+  }
+
+  // loader role: free index, quarter of the step's 16 contraction indices
+  const int idx = COL ? (tid & 127) : tid >> 2, qt = COL ? (wave >> 1) : (tid & 3);
+  const int64_t jbase = f0 + 128 * qJ, ibase = f0 + 128 * qI;
+  // groups of this wave's columns (64 or 16 neighbours lie in one) and of the rows
+  const int64_t gj = (jbase + (COL ? 64 * (wave & 1) : 16 * wave)) / a.G, gi0 = ibase / a.G, gi1 = V == 2 ? (ibase + 64) / a.G : gi0;
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  int64_t gl = gj;                               // the group whose scales the lane asks for (columns)
+  if ((lane >> 2 & 3) == 1) gl = gi0;
+  if ((lane >> 2 & 3) > 1) gl = gi1;
+  struct LoadSet {
+    f32x4 lx, sj, si0, si1;                      // (columns: ls, a lane a scale, in place of sj and si)
+    uintx4 lc, rc;                               // codes (rows: four in the first word)
+    float ls;
+    int ok;                                      // contraction indices of the thread's four that exist
+  };
+  auto issue = [&](LoadSet& L, int64_t t) __attribute__((always_inline)) {
+    if (COL) {
+      // uniform bases of the step's first row plus 32-bit lane offsets (rows past the chunk: its last row, dropped)
+      const int64_t tb = t < t1 ? t : t1 - 1;
+      const int rmax = t < t1 ? int(t1 - 1 - t < 15 ? t1 - 1 - t : 15) : -1, last = rmax >= 0 ? rmax : 0;
+      const float* bx = a.X + tb * C + jbase;
+      const int8_t *bc = a.codes + tb * C + jbase, *br = a.codes + tb * C + ibase;
+      L.ok = rmax + 1 - 4 * qt;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = 4 * qt + e < last ? 4 * qt + e : last;
+        const uint32_t off = uint32_t(r) * uint32_t(C) + uint32_t(idx);
+        L.lc[e] = uint32_t(uint8_t(bc[off]));
+        L.rc[e] = uint32_t(uint8_t(br[off]));
+        L.lx[e] = bx[off];
+      }
+      // lanes 0 .. 3 the columns' scales of the quarter's rows, 4 .. 7 and 8 .. 11 the rows'
+      const int r0 = 4 * qt + (lane & 3), r = r0 < last ? r0 : last;
+      L.ls = a.scales[(tb + r) * cg + gl];
+    } else {
+      const int64_t tt = t + 4 * qt, c = tt < t1 ? tt : t1 - 4;       // tlen and chunk are multiples of 4
+      L.ok = tt < t1 ? 4 : 0;
+      L.lc[0] = *reinterpret_cast<const uint32_t*>(a.codes + (jbase + idx) * C + c);
+      L.rc[0] = *reinterpret_cast<const uint32_t*>(a.codes + (ibase + idx) * C + c);
+      L.lx = *reinterpret_cast<const f32x4*>(a.X + (jbase + idx) * C + c);
+      L.sj = *reinterpret_cast<const f32x4*>(a.scales + gj * C + c);
+      L.si0 = *reinterpret_cast<const f32x4*>(a.scales + gi0 * C + c);
+      if (V == 2) L.si1 = *reinterpret_cast<const f32x4*>(a.scales + gi1 * C + c);
+    }
+  };
+  // four values' three parts to one 8-byte place in each of three planes
+  auto put = [](const float (&x)[4], unsigned char* at) __attribute__((always_inline)) {
+    uint32_t p[3][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float x0 = x[2 * i], x1 = x[2 * i + 1];
+      p[0][i] = pack_bf16(x0, x1);
+      const float r0 = x0 - bf16_lo_f32(p[0][i]), r1 = x1 - bf16_hi_f32(p[0][i]);
+      p[1][i] = pack_bf16(r0, r1);
+      p[2][i] = pack_bf16(r0 - bf16_lo_f32(p[1][i]), r1 - bf16_hi_f32(p[1][i]));
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2*>(at + k * kGqPlaneB) = make_uint2(p[k][0], p[k][1]);
+  };
+  auto commit = [&](const LoadSet& L, unsigned char* buf) __attribute__((always_inline)) {
+    unsigned char* dst = buf + (qt >> 1) * kGqHalfB + idx * 16 + (qt & 1) * 8;
+    float xq[4], er[4], rcode[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int code = COL ? int(int8_t(L.lc[e])) : int(int8_t(L.lc[0] >> (8 * e)));
+      const float sj = COL ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(L.ls), e)) : L.sj[e];
+      xq[e] = __fmul_rn(float(code), sj);
+      er[e] = xq[e] - L.lx[e];
+      rcode[e] = float(COL ? int(int8_t(L.rc[e])) : int(int8_t(L.rc[0] >> (8 * e))));
+      if (!(e < L.ok)) xq[e] = er[e] = 0.f;
+    }
+    *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16(rcode[0], rcode[1]), pack_bf16(rcode[2], rcode[3]));
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      float y[4], f[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float si = (COL ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(L.ls), 4 + 4 * v + e)) : v ? L.si1[e] : L.si0[e]) * unit;
+        y[e] = xq[e] * si;
+        f[e] = er[e] * si;
+      }
+      put(y, dst + (1 + 6 * v) * kGqPlaneB);
+      put(f, dst + (4 + 6 * v) * kGqPlaneB);
+    }
+  };
+
+  const int ta = wave >> 1, tc0 = 2 * (wave & 1);
+  floatx16 accS[2], accR[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) { accS[u][v] = 0.f; accR[u][v] = 0.f; }
+  auto products = [&](const unsigned char* buf) __attribute__((always_inline)) {
+    const unsigned char* pa = buf + h * kGqHalfB + ln * 16;
+    const bf16x8 ax = as_bf16x8(*reinterpret_cast<const uintx4*>(pa + ta * 512));
+    bf16x8 bq[2][3], be[2][3];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const unsigned char* pb = pa + (1 + (V == 2 ? 6 * (ta >> 1) : 0)) * kGqPlaneB + (tc0 + u) * 512;
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        bq[u][p] = as_bf16x8(*reinterpret_cast<const uintx4*>(pb + p * kGqPlaneB));
+        be[u][p] = as_bf16x8(*reinterpret_cast<const uintx4*>(pb + (3 + p) * kGqPlaneB));
+      }
+    }
+    // (smallest terms first)
+#pragma unroll
+    for (int p = 2; p >= 0; --p)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        accS[u] = CAFEQ_MFMA_BF16(ax, bq[u][p], accS[u]);
+        accR[u] = CAFEQ_MFMA_BF16(ax, be[u][p], accR[u]);
+      }
+  };
+  // (buffers, requests and barriers as in the kernel above)
+  LoadSet L0, L1;
+  unsigned char* buf0 = gsm;
+  unsigned char* buf1 = gsm + gq_buf(V);
   issue(L0, t0);
   issue(L1, t0 + 16);
   commit(L0, buf0);
@@ -1186,27 +1372,28 @@ int launch_gram(int axis, const float* X, const int8_t* codes, const float* scal
   a.tlen = axis == CAFEQ_AXIS_COL ? rows : cols;
   a.chunk = chunk; a.nchunk = nchunk; a.partial = partial;
   if (!triple && (K == 128 || K == 256)) {
-    // heads of 128 and 256: the 16-bit kernel, one workgroup per (head, quadrant of 128 x 128, chunk)
+    // heads of 128 and 256: the 16-bit kernels, one workgroup per (head, quadrant of 128 x 128, chunk)
     const dim3 g16(nb, (K / 128) * (K / 128), a.rep * nchunk);
     static std::atomic<bool> attr_set{false};
-    if (!attr_set) {
-      bool ok = true;
-#define CAFEQ_ATTR16(AX, KK)                                                                                    \
-  ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(gram_pair16_kernel<AX, KK>),                    \
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(kG16Lds)) == hipSuccess
-      CAFEQ_ATTR16(CAFEQ_AXIS_COL, 128); CAFEQ_ATTR16(CAFEQ_AXIS_COL, 256);
-      CAFEQ_ATTR16(CAFEQ_AXIS_ROW, 128); CAFEQ_ATTR16(CAFEQ_AXIS_ROW, 256);
-#undef CAFEQ_ATTR16
-      if (!ok) return CAFEQ_ERR_LAUNCH;
-      attr_set = true;
-    }
-    if (axis == CAFEQ_AXIS_COL) {
-      if (K == 128) hipLaunchKernelGGL((gram_pair16_kernel<CAFEQ_AXIS_COL, 128>), g16, dim3(512), kG16Lds, st, a);
-      else hipLaunchKernelGGL((gram_pair16_kernel<CAFEQ_AXIS_COL, 256>), g16, dim3(512), kG16Lds, st, a);
-    } else {
-      if (K == 128) hipLaunchKernelGGL((gram_pair16_kernel<CAFEQ_AXIS_ROW, 128>), g16, dim3(512), kG16Lds, st, a);
-      else hipLaunchKernelGGL((gram_pair16_kernel<CAFEQ_AXIS_ROW, 256>), g16, dim3(512), kG16Lds, st, a);
-    }
+    const size_t lds = G % 64 ? kG16Lds : 2 * gq_buf(G == 64 ? 2 : 1);
+    bool ok = true;
+    const bool set = !attr_set;
+    auto run = [&](auto kern, bool mine) {
+      if (set) ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 2 * int(gq_buf(2))) == hipSuccess;
+      if (mine && ok) hipLaunchKernelGGL(kern, g16, dim3(512), lds, st, a);
+    };
+#define CAFEQ_GRAM16(AX, KK)                                                        \
+  {                                                                                 \
+    const bool here = axis == AX && K == KK;                                        \
+    run(gram_pair16_kernel<AX, KK>, here && G % 64 != 0);                           \
+    run(gram_pair_codes_kernel<AX, KK, 1>, here && G % 64 == 0 && G != 64);         \
+    run(gram_pair_codes_kernel<AX, KK, 2>, here && G == 64);                        \
+  }
+    CAFEQ_GRAM16(CAFEQ_AXIS_COL, 128) CAFEQ_GRAM16(CAFEQ_AXIS_COL, 256)
+    CAFEQ_GRAM16(CAFEQ_AXIS_ROW, 128) CAFEQ_GRAM16(CAFEQ_AXIS_ROW, 256)
+#undef CAFEQ_GRAM16
+    if (!ok) return CAFEQ_ERR_LAUNCH;
+    attr_set = true;
     CAFEQ_CHECK_LAUNCH();
     return CAFEQ_OK;
   }
