@@ -329,7 +329,9 @@ __device__ __forceinline__ void spoiled_inputs(float* tile) {
   const int mi = (a.nmem > 1 && id >= a.m[0].nwg) ? 1 : 0;
   if (fabsf(a.la.losses[a.loss_kind == kLossSur ? 1 : mi]) < INFINITY) return;   // (uniform)
   const auto& M = a.m[mi];
-  const int b = int((mi ? id - a.m[0].nwg : id) / unsigned(K / M.rows)), m = int(threadIdx.x) % K;
+  int b, part;
+  block_and_part(mi ? id - a.m[0].nwg : id, unsigned(K / M.rows), M.nwg, &b, &part);
+  const int m = int(threadIdx.x) % K;
   bool bad = false;
   for (int q = b * M.rep; q < (b + 1) * M.rep; ++q) {
     const int64_t ax = int64_t(q) * K + m, at = (ax >> 7) * M.seg_stride + (ax & 127);
@@ -357,7 +359,9 @@ __global__ __launch_bounds__(kGgThreads) void grad_gather_kernel(const GatherArg
   const GatherMember& M = a.m[mi];
   if (mi) id -= a.m[0].nwg;
   const int rows = M.rows, per = K / rows;
-  const int b = int(id / unsigned(per)), j0 = int(id % unsigned(per)) * rows;   // block, first row
+  int b, share;
+  block_and_part(id, unsigned(per), M.nwg, &b, &share);
+  const int j0 = share * rows;                                                   // block, first row
   const int upb = K / M.unit_rows, u0 = j0 / M.unit_rows, r0 = j0 % M.unit_rows; // units per block, the rows' unit, first row in it
   float* tile = gsm;                                  // [rows][LDT]
   float* part = tile + rows * LDT + wave * K;         // [wave][K]: a share's first row, begun by a wave before
