@@ -552,32 +552,25 @@ __global__ __launch_bounds__(256 * KS) void bgemm_mfma_kernel(const float* __res
   }
 }
 
-// The gradient's way through the inverse in one launch for blocks of 128: C = beta C + alpha (P^T G) P^T per block
+// The gradient's way through the inverse in one launch for blocks of 64: C = beta C + alpha (P^T G) P^T per block
 // (Sec. 4.1 / 4.2: d/dT of a function of P = T^-1 is -P^T (d/dP) P^T).  Row i of the result needs row i of
-// X = P^T G only, so a workgroup that owns 64 rows computes its slice of X and then its slice of X P^T with no
-// exchange between workgroups: two workgroups per block, eight waves of one 32 x 32 tile each, both products on
-// v_mfma_f32_32x32x2_f32 in the arithmetic (and summation order) of bgemm_mfma_kernel.  P is staged once in LDS,
-// row-major with a row stride of 129 floats, which serves the first product's A operand (lanes along a row) and
+// X = P^T G only, so a workgroup of four waves of one 32 x 32 tile each computes X and then X P^T without any exchange between
+// workgroups, both products on v_mfma_f32_32x32x2_f32 in the arithmetic (and summation order) of bgemm_mfma_kernel.  P is staged once
+// in LDS, row-major with a row stride of 65 floats, which serves the first product's A operand (lanes along a row) and
 // the second's B operand (lanes along a column) without bank conflicts; G goes from memory straight into the
 // registers of the wave that multiplies by it; X passes through LDS transposed.
-// (Blocks of 64: one workgroup of four waves per block, the same scheme.)
-// XP: parts in which X passes through LDS, the waves of one column tile at a time.  Whole, the workgroup takes 100 KB and has the
-// compute unit to itself; in four parts 75 KB and 128 registers, so that two share it, the same sums in the same order.  The
-// two workgroups of a block sit behind one L2 (fetched per launch at 112 blocks 37.7 -> 23.0 MB).  Bound: latency of load, LDS
-// and the chain of matrix instructions (7.8 us of them a workgroup).  288 blocks (three rounds of workgroups as one a
-// compute unit) 55.7 -> 49.6 us in parts, -> 44.6 with the order; 112 blocks 19.5 -> 17.7 by the order alone.
+// Bound: latency of load, LDS and the chain of matrix instructions.
 constexpr int kChainLdX = 33;
-constexpr size_t chain_lds(int K, int XP) { return size_t(K * (K + 1) + 2 * (K / XP) * kChainLdX) * sizeof(float); }
-template <int K, int XP>
-__global__ __launch_bounds__(4 * K, XP > 1 ? 4 : 1) void bgemm_chain_kernel(const float* __restrict__ P, const float* __restrict__ G,
+constexpr size_t chain_lds(int K) { return size_t(K * (K + 1) + 2 * K * kChainLdX) * sizeof(float); }
+template <int K>
+__global__ __launch_bounds__(4 * K) void bgemm_chain_kernel(const float* __restrict__ P, const float* __restrict__ G,
                                                             float* __restrict__ C, float alpha, float beta,
                                                             const UpdateHook up) {
-  static_assert(K == 64 || K == 128, "slices of 64 rows");
-  static_assert(XP == 1 || XP == K / 32, "a part of X is what the waves of one column tile hold");
+  static_assert(K == 64, "a block is one slice of 64 rows");
   constexpr int kChainLdP = K + 1, NT = 4 * K, WJ = K / 32, SL = K / 64;   // threads, column tiles, slices per block
   extern __shared__ __align__(16) float csm[];
   float* sp = csm;                          // P[r][c]
-  float* sx = csm + K * kChainLdP;          // [2 row halves][l][32 rows]: X^T of the workgroup's slice, or of one part of l
+  float* sx = csm + K * kChainLdP;          // [2 row halves][l][32 rows]: X^T of the workgroup's slice
   int b, slice;
   block_and_part(blockIdx.x, SL, gridDim.x, &b, &slice);
   const int i0 = slice * 64;
@@ -618,14 +611,11 @@ __global__ __launch_bounds__(4 * K, XP > 1 ? 4 : 1) void bgemm_chain_kernel(cons
 #pragma unroll
     for (int t = 0; t < K / 2; ++t) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[2 * t * kChainLdP], g[t], acc, 0, 0, 0);
   }
-  constexpr int KX = K / XP;                // rows of X^T in LDS at a time
-  auto put_x = [&](const floatx16& x) __attribute__((always_inline)) {
-    float* xw = sx + wi * (KX * kChainLdX) + ((XP == 1 ? wj * 32 : 0) + ln) * kChainLdX;
+  {
+    float* xw = sx + wi * (K * kChainLdX) + (wj * 32 + ln) * kChainLdX;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) xw[8 * (v / 4) + 4 * h + (v % 4)] = x[v];
-  };
-  const floatx16 x = acc;
-  if (XP == 1 || wj == 0) put_x(x);
+    for (int v = 0; v < 16; ++v) xw[8 * (v / 4) + 4 * h + (v % 4)] = acc[v];
+  }
   // (in flight under the second product)
   UpdateOld was[16];
   if (up.T) {
@@ -639,18 +629,11 @@ __global__ __launch_bounds__(4 * K, XP > 1 ? 4 : 1) void bgemm_chain_kernel(cons
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
   {
     // Y[i][j] = sum_l X[i][l] P[j][l]
-    const float* pa = sx + wi * (KX * kChainLdX) + h * kChainLdX + ln;
+    const float* pa = sx + wi * (K * kChainLdX) + h * kChainLdX + ln;
     const float* pb = sp + (wj * 32 + ln) * kChainLdP + h;
-    for (int p = 0; p < XP; ++p) {
-      if (p > 0) {
-        __syncthreads();                    // (the part before is still being read)
-        if (wj == p) put_x(x);
-        __syncthreads();
-      }
 #pragma unroll 8
-      for (int t = 0; t < KX / 2; ++t)
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[2 * t * kChainLdX], pb[p * KX + 2 * t], acc, 0, 0, 0);
-    }
+    for (int t = 0; t < K / 2; ++t)
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[2 * t * kChainLdX], pb[2 * t], acc, 0, 0, 0);
   }
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
@@ -660,6 +643,143 @@ __global__ __launch_bounds__(4 * K, XP > 1 ? 4 : 1) void bgemm_chain_kernel(cons
       update_store(up, size_t(b) * K * K + size_t(i) * K + j, gr, was[v], denom);
     } else {
       Cb[i * K + j] = gr;
+    }
+  }
+}
+
+// The same for blocks of 128 on the 16-bit matrix pipe: every operand split exactly into three bfloat16 parts, the six part products of
+// weight >= 2^-24, float32 accumulation -- six instructions of 32 cycles where eight of 64 do the float32 product.  A workgroup owns 64 rows
+// of a block.  It splits its slice of P^T once for all waves (48 KB of LDS, 16-byte operands [part][step of 16][half][row][8]); G's columns are
+// split by the wave that multiplies by them, two waves each, and so are P's rows, as they come from memory.  The first product
+// is taken as X^T = G^T P: a lane then holds four consecutive contraction indices of the second one, which go to the slice's place in LDS.
+// Bound: the splits (880 vector instructions a wave) next to 96 matrix instructions, requests and stores of 4 bytes a lane at both ends
+// (72 blocks, 22 k cycles: requests 4, P^T 1.3, first product 4.4, exchange 2, second 8, stores 3; with Adam's state 29 k).
+// On v_mfma_f32_32x32x2_f32 / here: 72 blocks 15.7 / 13.2 us, with Adam 20.0 / 18.1, 112 17.4 / 15.2, 288 50 / 37.5.
+constexpr int kC16Part = 8 * 2 * 64 * 16;
+__device__ __forceinline__ void split3_pair(float x0, float x1, uint32_t& a, uint32_t& b, uint32_t& c) {
+  a = pack_bf16(x0, x1);
+  const float r0 = x0 - bf16_lo_f32(a), r1 = x1 - bf16_hi_f32(a);
+  b = pack_bf16(r0, r1);
+  c = pack_bf16(r0 - bf16_lo_f32(b), r1 - bf16_hi_f32(b));
+}
+// TWO: two workgroups a compute unit, 128 registers a wave (what the update needs of the old state then comes in two halves).
+template <bool TWO>
+__global__ __launch_bounds__(512, TWO ? 4 : 2) void bgemm_chain16_kernel(const float* __restrict__ P, const float* __restrict__ G, float* __restrict__ C,
+                                                               float alpha, float beta, const UpdateHook up) {
+  constexpr int K = 128;
+  __shared__ __align__(16) unsigned char op[3 * kC16Part];
+  int b, slice;
+  block_and_part(blockIdx.x, 2, gridDim.x, &b, &slice);
+  const int i0 = slice * 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), ln = lane & 31, h = lane >> 5;
+  const int wi = wave >> 2, wj = wave & 3;
+  const float* Pb = P + size_t(b) * K * K;
+  const float* Gb = G + size_t(b) * K * K;
+  float* Cb = C + size_t(b) * K * K;
+  struct Parts { bf16x8 hi, mid, lo; };
+  auto split8 = [](const float* x) __attribute__((always_inline)) {
+    uintx4 a, m, l;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      uint32_t u, v, w;
+      split3_pair(x[2 * i], x[2 * i + 1], u, v, w);
+      a[i] = u; m[i] = v; l[i] = w;
+    }
+    return Parts{as_bf16x8(a), as_bf16x8(m), as_bf16x8(l)};
+  };
+  auto load3 = [&](int step, int row) __attribute__((always_inline)) {
+    const unsigned char* at = op + ((step * 2 + h) * 64 + row) * 16;
+    return Parts{as_bf16x8(*reinterpret_cast<const uintx4*>(at)), as_bf16x8(*reinterpret_cast<const uintx4*>(at + kC16Part)),
+                 as_bf16x8(*reinterpret_cast<const uintx4*>(at + 2 * kC16Part))};
+  };
+  auto six = [](const Parts& x, const Parts& y, floatx16 d) __attribute__((always_inline)) {
+    d = CAFEQ_MFMA_BF16(x.lo, y.hi, d);
+    d = CAFEQ_MFMA_BF16(x.hi, y.lo, d);
+    d = CAFEQ_MFMA_BF16(x.mid, y.mid, d);
+    d = CAFEQ_MFMA_BF16(x.mid, y.hi, d);
+    d = CAFEQ_MFMA_BF16(x.hi, y.mid, d);
+    return CAFEQ_MFMA_BF16(x.hi, y.hi, d);
+  };
+  // the slice of P^T: this thread's row, contraction indices 16 wave .. + 15; and the wave's columns of G
+  float v[16], g[64];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) v[e] = Pb[(16 * wave + e) * K + i0 + lane];
+#pragma unroll
+  for (int s = 0; s < 8; ++s)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) g[8 * s + e] = Gb[(16 * s + 8 * h + e) * K + wj * 32 + ln];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const Parts t = split8(v + 8 * q);
+    unsigned char* at = op + ((wave * 2 + q) * 64 + lane) * 16;
+    *reinterpret_cast<uintx4*>(at) = __builtin_bit_cast(uintx4, t.hi);
+    *reinterpret_cast<uintx4*>(at + kC16Part) = __builtin_bit_cast(uintx4, t.mid);
+    *reinterpret_cast<uintx4*>(at + 2 * kC16Part) = __builtin_bit_cast(uintx4, t.lo);
+  }
+  __syncthreads();
+  floatx16 x;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) x[r] = 0.f;
+#pragma unroll
+  for (int s = 0; s < 8; ++s) x = six(split8(g + 8 * s), load3(s, wi * 32 + ln), x);
+  // rows of P for the second product, half of them ahead of the exchange
+  float p[64];
+  auto request = [&](int s0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = s0; s < s0 + 4; ++s)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const float4 t = *reinterpret_cast<const float4*>(Pb + (wj * 32 + ln) * K + 16 * s + 8 * h + 4 * u);
+        p[8 * s + 4 * u] = t.x; p[8 * s + 4 * u + 1] = t.y; p[8 * s + 4 * u + 2] = t.z; p[8 * s + 4 * u + 3] = t.w;
+      }
+  };
+  request(0);
+  __syncthreads();                          // (the slice of P^T is still being read)
+  // X[i = 32 wi + ln][l = 32 wj + 8 q + 4 h + e], e < 4, in register 4 q + e
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    uint32_t a[2], m[2], l[2];
+    split3_pair(x[4 * q], x[4 * q + 1], a[0], m[0], l[0]);
+    split3_pair(x[4 * q + 2], x[4 * q + 3], a[1], m[1], l[1]);
+    unsigned char* at = op + (((2 * wj + (q >> 1)) * 2 + (q & 1)) * 64 + wi * 32 + ln) * 16 + 8 * h;
+    *reinterpret_cast<uint2*>(at) = make_uint2(a[0], a[1]);
+    *reinterpret_cast<uint2*>(at + kC16Part) = make_uint2(m[0], m[1]);
+    *reinterpret_cast<uint2*>(at + 2 * kC16Part) = make_uint2(l[0], l[1]);
+  }
+  __syncthreads();
+  request(4);
+  floatx16 y;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) y[r] = 0.f;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) y = six(load3(s, wi * 32 + ln), split8(p + 8 * s), y);
+  constexpr int EB = TWO ? 8 : 16;          // elements of the result whose old state is held at a time
+  float cold[EB];
+  UpdateOld was[EB];
+  auto place = [&](int r) __attribute__((always_inline)) { return (i0 + wi * 32 + 8 * (r / 4) + 4 * h + (r % 4)) * K + wj * 32 + ln; };
+  auto old_state = [&](int r0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < EB; ++r) {
+      cold[r] = beta != 0.f ? Cb[place(r0 + r)] : 0.f;
+      if (up.T) was[r] = update_load(up, size_t(b) * K * K + size_t(place(r0 + r)));
+    }
+  };
+  const float denom = up.T && up.denom ? *up.denom : 1.f;
+  // (in flight under the rest of the product)
+  if (!TWO) old_state(0);
+#pragma unroll
+  for (int s = 4; s < 8; ++s) {
+    if (TWO && s == 6) old_state(0);
+    y = six(load3(s, wi * 32 + ln), split8(p + 8 * s), y);
+  }
+#pragma unroll
+  for (int r0 = 0; r0 < 16; r0 += EB) {
+    if (r0 > 0) old_state(r0);
+#pragma unroll
+    for (int r = 0; r < EB; ++r) {
+      const float gr = alpha * y[r0 + r] + (beta != 0.f ? beta * cold[r] : 0.f);
+      if (up.T) update_store(up, size_t(b) * K * K + size_t(place(r0 + r)), gr, was[r], denom);
+      else Cb[place(r0 + r)] = gr;
     }
   }
 }
@@ -1033,29 +1153,17 @@ int launch_bgemm_chain(const float* P, const float* G, float* x1, float* C, int 
     return launch_bgemm(false, true, x1, P, C, K, nb, alpha, beta, st, hook);
   }
   const UpdateHook up = hook ? *hook : UpdateHook{};
-  static std::atomic<bool> attr_set{false};
-  if (!attr_set) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(bgemm_chain_kernel<128, 1>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, int(chain_lds(128, 1))) != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void*>(bgemm_chain_kernel<128, 4>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, int(chain_lds(128, 4))) != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void*>(bgemm_chain_kernel<64, 1>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, int(chain_lds(64, 1))) != hipSuccess)
-      return CAFEQ_ERR_LAUNCH;
-    attr_set = true;
-  }
   switch (K) {
     case 32: hipLaunchKernelGGL(bgemm_chain32_kernel, dim3(unsigned(nb)), dim3(256), 0, st, P, G, C, alpha, beta, up); break;
     case 64:
-      hipLaunchKernelGGL((bgemm_chain_kernel<64, 1>), dim3(unsigned(nb)), dim3(256), chain_lds(64, 1), st, P, G, C, alpha, beta, up);
+      hipLaunchKernelGGL(bgemm_chain_kernel<64>, dim3(unsigned(nb)), dim3(256), chain_lds(64), st, P, G, C, alpha, beta, up);
       break;
     case 128:
-      // more workgroups than compute units: the form of which two fit one (288 blocks 55.7 -> 49.6 us); fewer gain nothing from
-      // a second place and would wait at six more barriers
+      // more workgroups than compute units: the form of which two fit one
       if (2 * int64_t(nb) > device_cu_count())
-        hipLaunchKernelGGL((bgemm_chain_kernel<128, 4>), dim3(unsigned(nb) * 2), dim3(512), chain_lds(128, 4), st, P, G, C, alpha, beta, up);
+        hipLaunchKernelGGL(bgemm_chain16_kernel<true>, dim3(unsigned(nb) * 2), dim3(512), 0, st, P, G, C, alpha, beta, up);
       else
-        hipLaunchKernelGGL((bgemm_chain_kernel<128, 1>), dim3(unsigned(nb) * 2), dim3(512), chain_lds(128, 1), st, P, G, C, alpha, beta, up);
+        hipLaunchKernelGGL(bgemm_chain16_kernel<false>, dim3(unsigned(nb) * 2), dim3(512), 0, st, P, G, C, alpha, beta, up);
       break;
     default: return CAFEQ_ERR_UNSUPPORTED;
   }

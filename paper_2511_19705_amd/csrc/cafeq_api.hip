@@ -242,7 +242,8 @@ bool gather_possible(int K, const GroupPlan& gp, bool lines) { return lines && (
 // evaluations in us, the other way / by records:
 //   groups from 128 on at k = 256, longer than 128 elsewhere: by records throughout (36864 x 256 at k = 256 205 / 190; whole channels
 //   at k = 128 159 / 136).  k = 256, groups of 64 (every line four times): 36864 x 1024 357 / 360, x 256 204 / 215; groups of 32 (eight
-//   times): 4608 x 1024 132 / 121, 2304 x 4608 .99, 2304 x 9216 298 / 318, 36864 x 4608 1384 / 1671, in bfloat16 1387 / 1280.
+//   times): 4608 x 1024 132 / 121, 2304 x 4608 .99, and with a block's lines behind one L2 2304 x 9216 478 / 454 (inverse and all), pairs
+//   3584 x 4096 425 / 381, 4608 x 14336 1274 / 1486; 36864 x 4608 1384 / 1671, in bfloat16 1387 / 1280.
 //   k = 128, groups of 128: 14336 x 1024 .97, 36864 x 256 118 / 110, x 1024 164 / 171, x 4608 580 / 507, and with prepared weights, whose product
 //   reads tiles in its own order, 127 / 142 and 385 / 393.
 //   k = 32 and 64 in one matrix, where the loss pass forms the gradient on its way: 14336 x 1024 (k = 32) 68 / 85, 36864 x 2304
@@ -256,7 +257,7 @@ bool gather_pays(const cafeq_mat* W, int K, const GroupPlan& gp, int64_t nlines,
   const bool on_the_way = !pair && K <= 64 && gp.gspan == 1 && core_lds_bytes(K, gp.Gk, true) != 0 && !asym;
   if (on_the_way && weights < (int64_t(1) << 23)) return false;
   if (K == 256 && gp.G == 64) return bf16 || nlines <= 64 * naxis;
-  if (K == 256 && gp.G == 32) return bf16 ? nlines <= 36 * naxis : nlines <= 24 * naxis && weights < 12000000;
+  if (K == 256 && gp.G == 32) return bf16 ? nlines <= 36 * naxis : nlines <= 24 * naxis && weights < 24000000;
   if (K == 256 || gp.G > 128 || gp.gspan > 1) return true;
   if (K == 128) return nlines <= 16384 || naxis <= 256 || (!W->prepared && naxis >= 2048);
   if (pair) return asym || gp.G > 32 || nlines <= 6 * naxis;
