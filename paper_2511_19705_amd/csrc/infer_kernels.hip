@@ -263,11 +263,6 @@ int cafeq_infer_single(const float* X, int n, int64_t ldx, const cafeq_xform* xf
   GemvArgs a;
   a.codes = codes; a.scales = scales; a.out = out; a.in = in; a.ldy = ldy; a.ldp = ldp;
   a.g = int(g); a.ngrp = int(in / g);
-  // about two workgroups per compute unit, whole batches of rows each
-  int64_t rpw = (out + 511) / 512;
-  rpw = (rpw + kRowsMax - 1) / kRowsMax * kRowsMax;
-  a.rows_per_wg = int(rpw);
-  const unsigned nwg = unsigned((out + rpw - 1) / rpw);
   for (int t0 = 0; t0 < n;) {
     const int left = n - t0;
     int T = 0, CH = 0, nt = 0;
@@ -275,6 +270,15 @@ int cafeq_infer_single(const float* X, int n, int64_t ldx, const cafeq_xform* xf
     else if (left >= 2 && pick_shape(in, 4, &T, &CH)) nt = 2;
     else if (pick_shape(in, 8, &T, &CH)) nt = 1;
     else return CAFEQ_ERR_UNSUPPORTED;
+    // Whole batches of rows each.  Two workgroups of six to eight waves fill a compute unit with requests; narrower ones (rows of up to
+    // 5120 codes, or in several chunks a thread) take as many as make sixteen waves of it.  At two / at sixteen waves, us: 14336 x 3584 16.9 / 14.2,
+    // 9216 x 2304 11.5 / 9.0, 14336 x 1536 and two tokens 18.8 / 11.3, 2304 x 9216 10.0 / 9.2; of six waves 14336 x 10752 34 / 41, of eight
+    // 4608 x 36864 51 / 54.
+    const int waves = T / kWave;
+    const int64_t want = waves <= 5 ? 4096 / waves : 512;
+    const int64_t rpw = ((out + want - 1) / want + kRowsMax - 1) / kRowsMax * kRowsMax;
+    a.rows_per_wg = int(rpw);
+    const unsigned nwg = unsigned((out + rpw - 1) / rpw);
     a.xp = xp + int64_t(t0) * ldp;
     a.y = Y + int64_t(t0) * ldy;
     const int rc = nt == 4 ? launch_gemv_nt<4>(a, T, CH, nwg, st)
