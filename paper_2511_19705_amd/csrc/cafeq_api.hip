@@ -14,7 +14,8 @@ int launch_grad_owner_timed(const GradOwnerJob* jobs, int n, int loss_kind, floa
 int launch_grad_v2_timed(const CoreParams& p, hipStream_t st);
 int launch_core32_timed(int axis, const CoreParams& p, hipStream_t st);
 int launch_grad_pass_timed(int K, int axis, const CoreParams& p, hipStream_t st);
-int launch_grad_gather_timed(int K, const GradGatherJob* jobs, int n, const LossArgs& la, const VArgs* va, hipStream_t st);
+int launch_grad_gather_timed(int K, const GradGatherJob* jobs, int n, const LossArgs& la, const VArgs* va, hipStream_t st,
+                             const RhoGroups* rho = nullptr);
 }  // namespace cafeq
 
 namespace {
@@ -665,8 +666,8 @@ int launch_grad_v2_timed(const CoreParams& p, hipStream_t st) {
 int launch_grad_pass_timed(int K, int axis, const CoreParams& p, hipStream_t st) {
   return timed_launch(st, [&] { return launch_grad_pass(K, axis, p, st); }, 1);
 }
-int launch_grad_gather_timed(int K, const GradGatherJob* jobs, int n, const LossArgs& la, const VArgs* va, hipStream_t st) {
-  return timed_launch(st, [&] { return launch_grad_gather(K, jobs, n, la, va, st); }, 1);
+int launch_grad_gather_timed(int K, const GradGatherJob* jobs, int n, const LossArgs& la, const VArgs* va, hipStream_t st, const RhoGroups* rho) {
+  return timed_launch(st, [&] { return launch_grad_gather(K, jobs, n, la, va, st, rho); }, 1);
 }
 size_t core_lds_bytes(int K, int G, bool do_grad) {
   switch (K) {
@@ -1192,7 +1193,8 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
     const RhoRequest rho{x->Tinv, w.rho, col ? 1 : 0, rg_inline ? w.m.rG : nullptr, gp.Gk, x->rep};
     if ((rc = launch_split_planes_multi(req, 2, K, nb, st, w.slot_hdr, pl.nslot, &rho, 1))) return rc;
     if (!rg_inline && (rc = launch_rho_groups(w.rho, K, x->rep, gp.Gk, naxis / gp.Gk, w.m.rG, st))) return rc;
-    if (grad && gp.gspan > 1 && (rc = launch_rho_groups(w.rho, K, x->rep, gp.G, naxis / gp.G, w.m.rGreal, st))) return rc;
+    // (by records the launch that sorts them takes these sums along)
+    if (grad && !gather && gp.gspan > 1 && (rc = launch_rho_groups(w.rho, K, x->rep, gp.G, naxis / gp.G, w.m.rGreal, st))) return rc;
   }
   p.Afwd = w.m.pfwd; p.Ainv = w.m.pinv; p.fscale = f16 ? w.m.fs : nullptr; p.fscale_inv = v2 ? w.m.fsi : nullptr;
   p.grid = grid; p.do_inverse = 1; p.do_grad = pp.fused ? 1 : 0; p.loss_kind = kLossSur; p.beta = beta;
@@ -1221,7 +1223,8 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
       LossArgs la{};
       la.hdrA = w.slot_hdr; la.nslotA = int(pl.nslot); la.kind = kLossSur; la.beta = beta; la.losses = losses;
       la.lse_ms = w.lse_ms;
-      if ((rc = launch_grad_gather_timed(K, &job, 1, la, &va, st))) return rc;
+      const RhoGroups rho{w.rho, w.m.rGreal, 31 - __builtin_clz(unsigned(K)), x->rep, gp.G, unsigned(naxis / gp.G)};
+      if ((rc = launch_grad_gather_timed(K, &job, 1, la, &va, st, gp.gspan > 1 ? &rho : nullptr))) return rc;
     } else if (owner) {
       const GradOwnerJob job = grad_owner_job(W, cfg->axis, pp, w.m, gradT, col ? 1 : 0);
       LossArgs la{};

@@ -108,7 +108,10 @@ size_t grad_gather_entries(int K, int grp, int64_t naxis, int64_t nlines);
 size_t grad_gather_starts(int K, int grp, int64_t naxis);
 // la: the call's loss reduction; va (single matrices; may be null): the middle factor of the rho path, both in the same launches
 struct VArgs;   // mmid.hpp
-int launch_grad_gather(int K, const GradGatherJob* jobs, int n, const LossArgs& la, const VArgs* va, hipStream_t st);
+// sums of rho over ngroups groups of G axis indices (index a -> block (a / K) / rep, a % K; K = 1 << lk), for a launch to take along
+struct RhoGroups { const float* rho; float* rG; int lk, rep, G; unsigned ngroups; };
+int launch_grad_gather(int K, const GradGatherJob* jobs, int n, const LossArgs& la, const VArgs* va, hipStream_t st,
+                       const RhoGroups* rho = nullptr);
 int launch_loss_v2(int K, int G, int axis, const CoreParams& p, hipStream_t st);
 int launch_loss_prepared(int K, int G, int axis, const CoreParams& p, hipStream_t st);   // ... with the caller's timing events
 // both members of a pair in one launch (loss_v2.hip), plain and with the caller's timing events

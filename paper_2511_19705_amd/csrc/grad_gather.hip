@@ -51,6 +51,7 @@ struct GatherArgs {
   LossArgs la;                       // the call's loss reduction
   unsigned ntail;                    // single matrices: kMmidParts workgroups per block for the middle factor, or 0
   VArgs va;
+  RhoGroups rho;                     // sums of rho over groups that span segments, a workgroup each (ngroups 0: none)
 };
 
 // ---------------------------------------------------------------------------------------------------
@@ -182,6 +183,24 @@ __global__ __launch_bounds__(kGsThreads, 6) void sort_records_kernel(const Gathe
     return;
   }
   id -= a.ntail;
+  if (id < a.rho.ngroups) {
+    // (what the gather takes its coefficients from; the addends' order: a thread's, the wave's, the waves')
+    double acc = 0;
+#pragma unroll 8
+    for (int e = int(threadIdx.x); e < a.rho.G; e += kGsThreads) {
+      const int64_t ax = int64_t(id) * a.rho.G + e;
+      acc += a.rho.rho[((ax >> a.rho.lk) / a.rho.rep << a.rho.lk) + (ax & ((1 << a.rho.lk) - 1))];
+    }
+    acc = wave_sum(acc);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int w = 1; w < kGsWaves; ++w) acc += red[w];
+      a.rho.rG[id] = float(acc);
+    }
+    return;
+  }
+  id -= a.rho.ngroups;
   const int mi = id >= a.m[0].nunit ? 1 : 0;
   const GatherMember& M = a.m[mi];
   if (mi) id -= a.m[0].nunit;
@@ -437,7 +456,7 @@ size_t grad_gather_starts(int K, int grp, int64_t naxis) {
   return size_t(naxis / ur) * size_t(ur + 1);
 }
 
-int launch_grad_gather(int K, const GradGatherJob* jobs, int n, const LossArgs& la, const VArgs* va, hipStream_t st) {
+int launch_grad_gather(int K, const GradGatherJob* jobs, int n, const LossArgs& la, const VArgs* va, hipStream_t st, const RhoGroups* rho) {
   if (n < 1 || n > 2 || !la.hdrA || !la.losses || (la.kind == kLossLse && !la.lse_ms)) return CAFEQ_ERR_INVALID_ARG;
   // rows per workgroup: three workgroups per compute unit keep the memory busy
   int64_t blocks = 0;
@@ -467,7 +486,8 @@ int launch_grad_gather(int K, const GradGatherJob* jobs, int n, const LossArgs& 
     a.va = *va;
     a.ntail = unsigned(jobs[0].nb) * kMmidParts;
   }
-  nsort += a.ntail + 1;
+  if (rho) a.rho = *rho;
+  nsort += a.ntail + 1 + a.rho.ngroups;
   int64_t list = 0;
   for (int i = 0; i < n; ++i)
     if (jobs[i].nlines <= kGsList) list = std::max(list, jobs[i].nlines);
