@@ -6,6 +6,7 @@
 #include "xform_core.hpp"
 #include "loss_reduce.hpp"
 #include "mmid.hpp"
+#include "ns_inverse.hpp"
 
 namespace cafeq {
 
@@ -856,8 +857,11 @@ __global__ __launch_bounds__(256) void bgemm_chain32_kernel(const float* __restr
 // A gradient-descent step that divides by ||W||^2 sums it from the headers itself, in that workgroup's order.
 // Bound: the latencies of headers and partials, each with eight requests in flight: 5.5 us at
 // 8 blocks, 6.5 at 90, against 4.0 + 5.7 and 4.9 + 5.7 in two launches.
-__global__ __launch_bounds__(256) void tail_chain32_kernel(const ReduceArgs ra, const VArgs va, const LossArgs la, const float* __restrict__ P,
-                                                           const UpdateHook up) {
+// INV: a learning loop's step, with the inverse of the transform it leaves (warm-started from P, in P's place) by the first wave: what a
+// launch of its own took for itself and its loads (1147 x 2880, eight steps 201 -> 179 us).
+template <bool INV>
+__global__ __launch_bounds__(256) void tail_chain32_kernel(const ReduceArgs ra, const VArgs va, const LossArgs la, const float* P,
+                                                           const UpdateHook up, float* Tinv, int* status) {
   constexpr int K = 32;
   __shared__ __align__(16) Chain32Lds s;
   __shared__ __align__(16) float v[K];
@@ -950,6 +954,12 @@ __global__ __launch_bounds__(256) void tail_chain32_kernel(const ReduceArgs ra, 
   }
   if (up.T) update_store4(up, at, r, old, denom);
   else *reinterpret_cast<float4*>(ra.out + at) = r;
+  if constexpr (INV) {
+    static_assert(NsShape<K>::bytes <= sizeof(Chain32Lds) && NsShape<K>::NW == 1, "one wave, in the chain's room");
+    __syncthreads();                                  // (the block's new entries are written, the chain's LDS is free)
+    if (tid >= 64) return;
+    ns_inverse_body<K, 1>(up.T, Tinv, status, b, reinterpret_cast<unsigned char*>(&s));
+  }
 }
 
 // K == 32: one 32 x 32 product per workgroup, C = alpha A B + beta C
@@ -1077,15 +1087,18 @@ int launch_single_tail(const CoreParams& pgrad, const CoreParams& ploss, int K, 
 // the same with the gradient's way through the inverse and the update (blocks of 32; hook->denom, if any: losses[2])
 int launch_tail_chain32(const CoreParams& pgrad, const CoreParams& ploss, int G, bool fused, int nb, int transpose_out, float* gradT,
                         const float* P, int scale_rows, float beta, int nslot, float* losses, double* lse_ms, hipStream_t st,
-                        const UpdateHook* hook) {
+                        const UpdateHook* hook, float* Tinv, int* status) {
   constexpr int K = 32;
+  if (Tinv && !(hook && hook->T)) return CAFEQ_ERR_INVALID_ARG;
   if (hook && hook->denom && hook->denom != losses + 2) return CAFEQ_ERR_INVALID_ARG;
   const ReduceArgs ra = reduce_args(pgrad, K, G, fused, transpose_out, nullptr, nullptr, gradT);
   const VArgs va = mmid_args(ploss, K, K > G ? K : G, G, P, scale_rows, nullptr);
   LossArgs la{};
   la.hdrA = ploss.slot_hdr; la.nslotA = nslot; la.kind = kLossSur; la.beta = beta; la.losses = losses;
   la.lse_ms = lse_ms;
-  hipLaunchKernelGGL(tail_chain32_kernel, dim3(unsigned(nb + 1)), dim3(256), 0, st, ra, va, la, P, hook ? *hook : UpdateHook{});
+  const UpdateHook up = hook ? *hook : UpdateHook{};
+  if (Tinv) hipLaunchKernelGGL(tail_chain32_kernel<true>, dim3(unsigned(nb + 1)), dim3(256), 0, st, ra, va, la, P, up, Tinv, status);
+  else hipLaunchKernelGGL(tail_chain32_kernel<false>, dim3(unsigned(nb + 1)), dim3(256), 0, st, ra, va, la, P, up, Tinv, status);
   CAFEQ_CHECK_LAUNCH();
   return CAFEQ_OK;
 }

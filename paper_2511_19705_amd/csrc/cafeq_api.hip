@@ -753,8 +753,10 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
                      float lse_t, float* losses, float* gradT, int8_t* codesU, float* scalesU, int8_t* codesV,
                      float* scalesV, void* ws, void* stream, const UpdateHook* hook);
 
+// a loop's step may leave the inverse of the transform it leaves, where its last kernel has that in it (done)
+struct LoopInverse { float* Tinv; int* status; bool done; };
 static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_quant_cfg* cfg, float* losses, float* gradT,
-                       int8_t* codes, float* scales, void* ws, void* stream, const UpdateHook* hook, bool loop);
+                       int8_t* codes, float* scales, void* ws, void* stream, const UpdateHook* hook, bool loop, LoopInverse* inv = nullptr);
 
 int cafeq_optimize_single(const cafeq_mat* W, float* T, float* Tinv, int k, int nb, int rep,
                           const cafeq_quant_cfg* cfg, const cafeq_opt_cfg* opt, float* history, int* status,
@@ -770,13 +772,16 @@ int cafeq_optimize_single(const cafeq_mat* W, float* T, float* Tinv, int k, int 
   if ((rc = launch_fill(history, 0.f, int64_t(opt->steps) * 8, st))) return rc;
   // without a regulariser to add in between, the step rides in the epilogue of the gradient's last kernel
   const bool fuse = !(opt->lambda_orth > 0.f) && !small_m(k);
+  LoopInverse inv{Tinv, status, false};
   for (int s = 0; s < opt->steps; ++s) {
     float* h = history + size_t(s) * 8;
-    if ((rc = loop_inverse(s, T, k, nb, Tinv, status, w.sub, stream))) return rc;
+    if (!inv.done && (rc = loop_inverse(s, T, k, nb, Tinv, status, w.sub, stream))) return rc;
+    inv.done = false;
     if (fuse) {
       UpdateHook hook{};
       hook.T = T; hook.lr = opt->lr; hook.denom = opt->normalize ? h + 2 : nullptr;
-      if ((rc = single_impl(W, &x, cfg, h, w.grad, nullptr, nullptr, w.sub, stream, &hook, true))) return rc;
+      // (the last step's inverse is taken from scratch)
+      if ((rc = single_impl(W, &x, cfg, h, w.grad, nullptr, nullptr, w.sub, stream, &hook, true, s + 1 < opt->steps ? &inv : nullptr))) return rc;
       continue;
     }
     if ((rc = single_impl(W, &x, cfg, h, w.grad, nullptr, nullptr, w.sub, stream, nullptr, true))) return rc;
@@ -1120,7 +1125,7 @@ int cafeq_apply_transform(const cafeq_mat* W, const cafeq_xform* x, int axis, in
 // hook (learning loop only; blocks of 32 and more): the last kernel of the gradient applies the gradient-descent step
 // to T instead of storing the gradient (gradT is then scratch).  loop: called from a learning loop, with a hook or without.
 static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_quant_cfg* cfg, float* losses, float* gradT,
-                       int8_t* codes, float* scales, void* ws, void* stream, const UpdateHook* hook, bool loop) {
+                       int8_t* codes, float* scales, void* ws, void* stream, const UpdateHook* hook, bool loop, LoopInverse* inv) {
   int rc = check_mat(W);
   if (rc) return rc;
   rc = check_cfg(cfg, true, true);
@@ -1235,9 +1240,11 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
       if (pp.two &&
           (rc = run_grad_pass(K, cfg->axis, W, x->rep, pp, w.m, kLossSur, beta, 0.f, nullptr, 0, nullptr, &pg, st)))
         return rc;
-      if (K == 32)
+      if (K == 32) {
+        if (inv) inv->done = true;
         return launch_tail_chain32(pg, p, gp.Gk, pp.fused, nb, col ? 1 : 0, gradT, x->Tinv, col ? 1 : 0, beta, int(pl.nslot), losses, w.lse_ms,
-                                   st, hook);
+                                   st, hook, inv ? inv->Tinv : nullptr, inv ? inv->status : nullptr);
+      }
       // gradient reduction, the middle factor of the rho path and the loss reduction in one launch
       if ((rc = launch_single_tail(pg, p, K, gp.Gk, pp.fused, nb, col ? 1 : 0, gradT, x->Tinv, col ? 1 : 0, w.mmid, beta,
                                    int(pl.nslot), losses, w.lse_ms, st)))

@@ -157,7 +157,7 @@ struct UpdateHook { float *T, *m, *v; float lr, beta1, omb1, beta2, omb2, eps, c
 // blocks of 32: launch_single_tail with the gradient's way through the inverse, and the update, in the same launch
 int launch_tail_chain32(const CoreParams& pgrad, const CoreParams& ploss, int G, bool fused, int nb, int transpose_out, float* gradT,
                         const float* P, int scale_rows, float beta, int nslot, float* losses, double* lse_ms, hipStream_t st,
-                        const UpdateHook* hook);
+                        const UpdateHook* hook, float* Tinv = nullptr, int* status = nullptr);
 // C = alpha op(A) op(B) + beta C per block
 int launch_bgemm(bool ta, bool tb, const float* A, const float* B, float* C, int K, int nb, float alpha,
                  float beta, hipStream_t st, const UpdateHook* hook = nullptr);

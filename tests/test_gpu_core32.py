@@ -43,3 +43,24 @@ def test_not_finite(env, axis, value):
     if axis == O.ROW:
         bad = bad.transpose(0, 2, 1)
     assert bad[1, 13].all() and not bad[[0, 2, 3]].any()
+
+
+@pytest.mark.parametrize("lr", [0.5, 200.0])
+@pytest.mark.parametrize("axis", [O.COL, O.ROW])
+def test_loop_against_its_steps(env, axis, lr):
+    """The loop's last kernel of a step leaves the next inverse, from the one before (at the larger rate blocks leave Newton's reach and are
+    eliminated); each step's losses and transform against calls that take every inverse from scratch.  The two inverses differ by float32
+    rounding; a gradient by 1e-6 of itself."""
+    torch, cafeq = env
+    W, T, _ = _case(axis, 300, 256, 32, 1, 9600, eps=0.2)
+    W, T = _dev(torch, W), _dev(torch, T)
+    steps, mine = 4, T.clone()
+    P, history, status = cafeq.optimize_single(W, mine, 4, 32, axis, lr=lr, steps=steps)
+    for s in range(steps):
+        Q, st = cafeq.block_inverse(T)
+        losses, grad, _, _ = cafeq.proxy_loss_fwd_bwd(W, T, Q, 4, 32, axis)
+        np.testing.assert_allclose(history[s, :4].cpu().numpy(), losses.cpu().numpy(), rtol=1e-4)
+        cafeq.sgd_update(T, grad, lr, losses[2:3])
+    np.testing.assert_allclose(mine.cpu().numpy(), T.cpu().numpy(), rtol=0, atol=1e-4 * float(T.abs().max()))
+    Q, st = cafeq.block_inverse(mine)
+    assert torch.equal(P, Q) and torch.equal(status, st)
