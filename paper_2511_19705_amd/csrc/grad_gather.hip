@@ -333,13 +333,26 @@ __device__ __forceinline__ int gather_share(const uint2* __restrict__ sorted, co
   return first;
 }
 
+// Workgroup `id` of a member -> its block and which of the block's shares of rows.  Lines that several units read: the readers behind one L2
+// (9B-shaped (V, O) pair, blocks of 256 and groups of 64 57 -> 41 us); lines that are read once spread over the chip as they come (blocks of 32,
+// pair 2000 x 2048, the evaluation 55.7 us, behind one L2 57.2).
+template <bool ONCE>
+__device__ __forceinline__ void gather_place(unsigned id, unsigned per, unsigned total, int* b, int* share) {
+  if constexpr (ONCE) {
+    *b = int(id / per);
+    *share = int(id % per);
+  } else {
+    block_and_part(id, per, total, b, share);
+  }
+}
+
 // The products with S's zeros that the gather leaves out matter where a weight is infinite or not a number: there they are not
 // numbers, in all rows of the block.  Such a weight spoils the member's sum of squared rounding errors -- every transformed
 // value of its line and block is not a number -- which the launch before this one has reduced: a finite sum rules them out,
 // and only otherwise are the block's lines read once more, whole.
 // (The kernel's arguments are fetched anew, block and member worked out anew: kept until here -- the compiler would -- they take
 // blocks of 256 from 94 registers to 97, i.e. a wave per SIMD.)
-template <int K>
+template <int K, bool ONCE>
 __device__ __forceinline__ void spoiled_inputs(float* tile) {
   unsigned id = blockIdx.x;
   auto args = (const __attribute__((address_space(4))) GatherArgs*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -349,7 +362,7 @@ __device__ __forceinline__ void spoiled_inputs(float* tile) {
   if (fabsf(a.la.losses[a.loss_kind == kLossSur ? 1 : mi]) < INFINITY) return;   // (uniform)
   const auto& M = a.m[mi];
   int b, part;
-  block_and_part(mi ? id - a.m[0].nwg : id, unsigned(K / M.rows), M.nwg, &b, &part);
+  gather_place<ONCE>(mi ? id - a.m[0].nwg : id, unsigned(K / M.rows), M.nwg, &b, &part);
   const int m = int(threadIdx.x) % K;
   bool bad = false;
   for (int q = b * M.rep; q < (b + 1) * M.rep; ++q) {
@@ -379,7 +392,7 @@ __global__ __launch_bounds__(kGgThreads) void grad_gather_kernel(const GatherArg
   if (mi) id -= a.m[0].nwg;
   const int rows = M.rows, per = K / rows;
   int b, share;
-  block_and_part(id, unsigned(per), M.nwg, &b, &share);
+  gather_place<ONCE>(id, unsigned(per), M.nwg, &b, &share);
   const int j0 = share * rows;                                                   // block, first row
   const int upb = K / M.unit_rows, u0 = j0 / M.unit_rows, r0 = j0 % M.unit_rows; // units per block, the rows' unit, first row in it
   float* tile = gsm;                                  // [rows][LDT]
@@ -416,7 +429,7 @@ __global__ __launch_bounds__(kGgThreads) void grad_gather_kernel(const GatherArg
     }
   }
   __syncthreads();
-  spoiled_inputs<K>(tile);
+  spoiled_inputs<K, ONCE>(tile);
   float* dst = M.out + size_t(b) * K * K;
   if (M.transpose_out) {
     const int rq = rows / 4;
