@@ -247,14 +247,18 @@ bool gather_possible(int K, const GroupPlan& gp, bool lines) { return lines && (
 //   3584 x 4096 425 / 381, 4608 x 14336 1274 / 1486; 36864 x 4608 1384 / 1671, in bfloat16 1387 / 1280.
 //   k = 128, groups of 128: 14336 x 1024 .97, 36864 x 256 118 / 110, x 1024 164 / 171, x 4608 580 / 507, and with prepared weights, whose product
 //   reads tiles in its own order, 127 / 142 and 385 / 393.
+//   k = 32 with groups of 32, whose loss pass (core32.hip) forms the gradient on its way, as exact: by records / on the way 36864 x 2304 282 / 151,
+//   2304 x 9216 prepared 99 / 56, 4608 x 36864 447 / 291, in bfloat16 390 / 291, pairs 1000 x 4096 80 / 57, 3584 x 14336 270 / 208; not in
+//   bfloat16 along rows, of which a wave asks for 64 bytes at a time: pairs 4608 x 36864 648 / 809, 2304 x 9216 116 / 125.
 //   k = 32 and 64 in one matrix, where the loss pass forms the gradient on its way: 14336 x 1024 (k = 32) 68 / 85, 36864 x 2304
 //   308 / 259, 2304 x 4608 58 / 55, 1147 x 9216 63 / 61, 4.2 M weights 33 / 40; over prepared weights, whose loss pass only records, with groups of 128
 //   (bfloat16: of 64) 36864 x 1024 113 / 107, 9216 x 1024 57 / 50.  On the min/max grid, a pass of its own either way: groups of 32 1147 x 512
 //   31 / 25, 4608 x 256 33 / 37, 2304 x 9216 83 / 86, 36864 x 1024 120 / 184; 64 36864 x 1024 118 / 140, 14336 x 512 66 / 61.
 //   Pairs (prepared: two launches less): 4608 x 256 at k = 32, groups of 32 48 / 56, 2304 x 512 47 / 46; else by records throughout.
-bool gather_pays(const cafeq_mat* W, int K, const GroupPlan& gp, int64_t nlines, int64_t naxis, bool asym, bool pair, bool v2) {
+bool gather_pays(const cafeq_mat* W, int K, const GroupPlan& gp, int64_t nlines, int64_t naxis, bool asym, bool pair, bool v2, bool along_rows) {
   const int64_t weights = nlines * naxis;
   const bool bf16 = W->dtype == CAFEQ_BF16;
+  if (K == 32 && gp.G == 32 && !asym && !(bf16 && (pair || along_rows))) return false;
   const bool on_the_way = !pair && K <= 64 && gp.gspan == 1 && core_lds_bytes(K, gp.Gk, true) != 0 && !asym;
   if (on_the_way && weights < (int64_t(1) << 23)) return false;
   if (K == 256 && gp.G == 64) return bf16 || nlines <= 64 * naxis;
@@ -1167,7 +1171,7 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
   // their last place, although the gradient itself is ten times closer to float64's.  These loops, with or without a regulariser and
   // whatever the block, keep the product, and with it the transforms they have always ended at; evaluations do not depend on the bits.
   bool v2 = v2_eligible(W, K, gp, cfg, !col && (codes || scales)) && v2_pays(W, K, gp, nlines, naxis, codes || scales, !col);
-  const bool gather = gather_possible(K, gp, has_lines(W, cfg->axis)) && gather_pays(W, K, gp, nlines, naxis, asym, false, v2) &&
+  const bool gather = gather_possible(K, gp, has_lines(W, cfg->axis)) && gather_pays(W, K, gp, nlines, naxis, asym, false, v2, !col) &&
                       !(loop && cfg->bits == 2);
   if (K < 128 && grad && !gather) v2 = false;   // (the loss pass forms the gradient on its way)
   PassPlans pp;
@@ -1306,7 +1310,8 @@ static int dual_impl(const cafeq_mat* A, const cafeq_mat* B, const cafeq_xform* 
   const bool grad = gradT != nullptr;
   const bool asym = is_minmax(cfg);
   const bool gather = gather_possible(K, ga, has_lines(A, CAFEQ_AXIS_COL)) && gather_possible(K, gb, has_lines(B, CAFEQ_AXIS_ROW)) &&
-                      gather_pays(A, K, ga, A->rows, A->cols, asym, true, false) && gather_pays(B, K, gb, B->cols, B->rows, asym, true, false);
+                      gather_pays(A, K, ga, A->rows, A->cols, asym, true, false, false) &&
+                      gather_pays(B, K, gb, B->cols, B->rows, asym, true, false, true);
   bool v2A = v2_eligible(A, K, ga, cfg, false), v2B = v2_eligible(B, K, gb, cfg, codesV || scalesV);
   // both loss passes over prepared weights in one launch, each member on half of the chip: when neither writes
   // codes or scales and both use the same group length

@@ -10,6 +10,8 @@
 //   * the gradient's contraction runs over the strip's own 32 lines, staged through LDS by the wave that reads them (adding coefficient x
 //     line into 32 x 32 floats of LDS by atomics: 9.3 k cycles, nine a lane);
 //   * the half-waves exchange through v_permlane32_swap, the entry of the largest magnitude is found by comparing with the maximum.
+// The gradient's operands are split exactly into three bfloat16 parts like the forward transform's, six products: against float64 1.2e-7 to
+// 1.8e-7 off where the general kernel's two parts left 2.5e-6 to 6e-6 and sums by records in float32 1.3e-7 to 2.5e-7 (2 % of the launch).
 // Measured (MI355X): 256 x 256 8.2 us and 3.6 us for the planes' launch -> 6.1; 1147 x 2880 19.7 and 4.3 -> 11.9.  Three workgroups a
 // compute unit instead of two 11.5 (but the launch that adds the partials takes longer), four (128 registers, 16 spilled) 13.
 //
@@ -20,9 +22,9 @@ namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-// A wave's room in LDS for the gradient: the weights' high and middle parts transposed ([input][line], rows of 80 bytes: a 16-byte read
+// A wave's room in LDS for the gradient: the weights' three parts transposed ([input][line], rows of 80 bytes: a 16-byte read
 // of every lane meets no bank twice) and per line arg-max and coefficient; the wave's share of a partial when that leaves.
-constexpr int kC32Row = 80, kC32Plane = 32 * kC32Row, kC32Wave = 2 * kC32Plane + 32 * 2 + 32 * 4;
+constexpr int kC32Row = 80, kC32Plane = 32 * kC32Row, kC32Lines = 3 * kC32Plane, kC32Wave = kC32Lines + 32 * 4 + 32 * 4;
 static_assert(kC32Wave % 16 == 0 && kC32Wave >= 4096, "rows, and 32 x 32 floats");
 
 // where |z| == a: best = z, j = J + its place (called from the last values to the first: the lowest index stays).  Comparisons four
@@ -151,8 +153,8 @@ __global__ __launch_bounds__(kThreads, 3) void core32_kernel(const CoreParams p)
 #pragma unroll
   for (int v = 0; v < 16; ++v) gt[v] = 0.f;
   unsigned char* wst = room[GRAD ? wave : 0];
-  int16_t* jst = reinterpret_cast<int16_t*>(wst + (GRAD ? 2 * kC32Plane : 0));
-  uint32_t* cfp = reinterpret_cast<uint32_t*>(wst + (GRAD ? 2 * kC32Plane + 64 : 0));
+  uint32_t* jst = reinterpret_cast<uint32_t*>(wst + (GRAD ? kC32Lines : 0));         // arg-max | coefficient's third part << 16
+  uint32_t* cfp = reinterpret_cast<uint32_t*>(wst + (GRAD ? kC32Lines + 128 : 0));   // its first | its second << 16
 
   float x[16], xn[16] = {};
   load_w(seg, mis, x);
@@ -224,7 +226,7 @@ __global__ __launch_bounds__(kThreads, 3) void core32_kernel(const CoreParams p)
       const bf16x8 fh = as_bf16x8(*reinterpret_cast<const uintx4*>(ap)), fm = as_bf16x8(*reinterpret_cast<const uintx4*>(ap + 2048)),
                    fl = as_bf16x8(*reinterpret_cast<const uintx4*>(ap + 4096));
       if constexpr (GRAD) {
-        const uintx4 uh = __builtin_bit_cast(uintx4, bh), um = __builtin_bit_cast(uintx4, bm);
+        const uintx4 uh = __builtin_bit_cast(uintx4, bh), um = __builtin_bit_cast(uintx4, bm), ul = __builtin_bit_cast(uintx4, bl);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           unsigned char* at = wst + (16 * c + 8 * (i / 2) + 4 * h + 2 * (i % 2)) * kC32Row + 2 * ln;
@@ -232,6 +234,8 @@ __global__ __launch_bounds__(kThreads, 3) void core32_kernel(const CoreParams p)
           *reinterpret_cast<uint16_t*>(at + kC32Row) = uint16_t(uh[i] >> 16);
           *reinterpret_cast<uint16_t*>(at + kC32Plane) = uint16_t(um[i]);
           *reinterpret_cast<uint16_t*>(at + kC32Plane + kC32Row) = uint16_t(um[i] >> 16);
+          *reinterpret_cast<uint16_t*>(at + 2 * kC32Plane) = uint16_t(ul[i]);
+          *reinterpret_cast<uint16_t*>(at + 2 * kC32Plane + kC32Row) = uint16_t(ul[i] >> 16);
         }
       }
       z = CAFEQ_MFMA_BF16(fl, bh, z);
@@ -317,10 +321,12 @@ __global__ __launch_bounds__(kThreads, 3) void core32_kernel(const CoreParams p)
     // ---- the gradient: G[j][m] += sum over the strip's lines of S[line][j] W[line][m], S's parts built from (arg-max, coefficient)
     if constexpr (GRAD) {
       if (h == 0) {
-        // coefficient as a bfloat16 pair (high part in the low half)
-        const uint32_t ch = pack_bf16(coef, 0.f), cl = pack_bf16(coef - bf16_lo_f32(ch), 0.f);
-        jst[ln] = int16_t(j);
-        cfp[ln] = (ch & 0xFFFFu) | (cl << 16);
+        // coefficient in three bfloat16 parts
+        const uint32_t c0 = pack_bf16(coef, 0.f) & 0xFFFFu;
+        const float r0 = coef - bf16_lo_f32(c0);
+        const uint32_t c1 = pack_bf16(r0, 0.f) & 0xFFFFu, c2 = pack_bf16(r0 - bf16_lo_f32(c1), 0.f);
+        jst[ln] = uint32_t(j) | c2 << 16;
+        cfp[ln] = c0 | c1 << 16;
       }
       // (within the wave alone: its LDS instructions run in order)
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -328,20 +334,31 @@ __global__ __launch_bounds__(kThreads, 3) void core32_kernel(const CoreParams p)
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         const int l0 = 16 * c + 8 * h;
-        const uintx4 jv = *reinterpret_cast<const uintx4*>(jst + l0);
+        const uintx4 j0 = *reinterpret_cast<const uintx4*>(jst + l0), j1 = *reinterpret_cast<const uintx4*>(jst + l0 + 4);
         const uintx4 c0 = *reinterpret_cast<const uintx4*>(cfp + l0), c1 = *reinterpret_cast<const uintx4*>(cfp + l0 + 4);
-        const bf16x8 bh = as_bf16x8(*reinterpret_cast<const uintx4*>(wst + ln * kC32Row + 2 * l0));
-        const bf16x8 bm = as_bf16x8(*reinterpret_cast<const uintx4*>(wst + kC32Plane + ln * kC32Row + 2 * l0));
-        uint32_t sel[8];
+        const unsigned char* wrow = wst + ln * kC32Row + 2 * l0;
+        const bf16x8 bh = as_bf16x8(*reinterpret_cast<const uintx4*>(wrow)), bm = as_bf16x8(*reinterpret_cast<const uintx4*>(wrow + kC32Plane)),
+                     bl = as_bf16x8(*reinterpret_cast<const uintx4*>(wrow + 2 * kC32Plane));
+        uint32_t sel[8], third[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) sel[e] = int((jv[e / 2] >> (16 * (e % 2))) & 0xFFFFu) == ln ? (e < 4 ? c0[e] : c1[e - 4]) : 0u;
-        uintx4 sh, sl;
+        for (int e = 0; e < 8; ++e) {
+          const uint32_t jv = e < 4 ? j0[e] : j1[e - 4];
+          const bool mine = (jv & 0xFFFFu) == uint32_t(ln);
+          sel[e] = mine ? (e < 4 ? c0[e] : c1[e - 4]) : 0u;
+          third[e] = mine ? jv : 0u;
+        }
+        uintx4 sh, sm, sl;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           sh[e] = __builtin_amdgcn_perm(sel[2 * e + 1], sel[2 * e], 0x05040100u);
-          sl[e] = __builtin_amdgcn_perm(sel[2 * e + 1], sel[2 * e], 0x07060302u);
+          sm[e] = __builtin_amdgcn_perm(sel[2 * e + 1], sel[2 * e], 0x07060302u);
+          sl[e] = __builtin_amdgcn_perm(third[2 * e + 1], third[2 * e], 0x07060302u);
         }
+        // six products, smallest terms first
         gt = CAFEQ_MFMA_BF16(as_bf16x8(sl), bh, gt);
+        gt = CAFEQ_MFMA_BF16(as_bf16x8(sh), bl, gt);
+        gt = CAFEQ_MFMA_BF16(as_bf16x8(sm), bm, gt);
+        gt = CAFEQ_MFMA_BF16(as_bf16x8(sm), bh, gt);
         gt = CAFEQ_MFMA_BF16(as_bf16x8(sh), bm, gt);
         gt = CAFEQ_MFMA_BF16(as_bf16x8(sh), bh, gt);
       }
