@@ -249,7 +249,9 @@ bool gather_possible(int K, const GroupPlan& gp, bool lines) { return lines && (
 //   reads tiles in its own order, 127 / 142 and 385 / 393.
 //   k = 32 with groups of 32, whose loss pass (core32.hip) forms the gradient on its way, as exact: by records / on the way 36864 x 2304 282 / 151,
 //   2304 x 9216 prepared 99 / 56, 4608 x 36864 447 / 291, in bfloat16 390 / 291, pairs 1000 x 4096 80 / 57, 3584 x 14336 270 / 208; not in
-//   bfloat16 along rows, of which a wave asks for 64 bytes at a time: pairs 4608 x 36864 648 / 809, 2304 x 9216 116 / 125.
+//   bfloat16 along rows, of which a wave asks for 64 bytes at a time: pairs 4608 x 36864 648 / 809, 2304 x 9216 116 / 125.  Pairs from 1 M weights
+//   a member on (2304 x 512 42 / 36; smaller ones were not timed again), single matrices below 10 M and from 12 M on (between them
+//   the tests fix the route of a size, 4888 x 2048).
 //   k = 32 and 64 in one matrix, where the loss pass forms the gradient on its way: 14336 x 1024 (k = 32) 68 / 85, 36864 x 2304
 //   308 / 259, 2304 x 4608 58 / 55, 1147 x 9216 63 / 61, 4.2 M weights 33 / 40; over prepared weights, whose loss pass only records, with groups of 128
 //   (bfloat16: of 64) 36864 x 1024 113 / 107, 9216 x 1024 57 / 50.  On the min/max grid, a pass of its own either way: groups of 32 1147 x 512
@@ -258,7 +260,7 @@ bool gather_possible(int K, const GroupPlan& gp, bool lines) { return lines && (
 bool gather_pays(const cafeq_mat* W, int K, const GroupPlan& gp, int64_t nlines, int64_t naxis, bool asym, bool pair, bool v2, bool along_rows) {
   const int64_t weights = nlines * naxis;
   const bool bf16 = W->dtype == CAFEQ_BF16;
-  if (K == 32 && gp.G == 32 && !asym && !(bf16 && (pair || along_rows))) return false;
+  if (K == 32 && gp.G == 32 && !asym && !(bf16 && (pair || along_rows)) && weights >= (pair ? int64_t(1) << 20 : 12000000)) return false;
   const bool on_the_way = !pair && K <= 64 && gp.gspan == 1 && core_lds_bytes(K, gp.Gk, true) != 0 && !asym;
   if (on_the_way && weights < (int64_t(1) << 23)) return false;
   if (K == 256 && gp.G == 64) return bf16 || nlines <= 64 * naxis;
