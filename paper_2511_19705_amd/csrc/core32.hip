@@ -12,7 +12,8 @@
 //   * the half-waves exchange through v_permlane32_swap, the entry of the largest magnitude is found by comparing with the maximum.
 // The gradient's operands are split exactly into three bfloat16 parts like the forward transform's, six products: against float64 1.2e-7 to
 // 1.8e-7 off where the general kernel's two parts left 2.5e-6 to 6e-6 and sums by records in float32 1.3e-7 to 2.5e-7 (2 % of the launch).
-// Measured (MI355X): 256 x 256 8.2 us and 3.6 us for the planes' launch -> 6.1; 1147 x 2880 19.7 and 4.3 -> 11.9.  Three workgroups a
+// Measured (MI355X): 256 x 256 8.2 us and 3.6 us for the planes' launch -> 6.1; 1147 x 2880 19.7 and 4.3 -> 11.9 (both
+// with two parts; with three 6.4 and, in descent loops, 12.9).  Three workgroups a
 // compute unit instead of two 11.5 (but the launch that adds the partials takes longer), four (128 registers, 16 spilled) 13.
 //
 #include "xform_core.hpp"
