@@ -143,7 +143,8 @@ size_t cafeq_workspace_bytes(int call_id, const cafeq_mat* a, const cafeq_mat* b
  * a scaled rotation first tried with Newton-Schulz rounds from T^T ||T||_F^-2 k, kept only where ||I - T X||_F <= 1.5e-2
  * before the last; a Newton step on the float64 residual of either follows, and a second one where that is above 3e-4.  rho_row[nb*k] / rho_col[nb*k] (either may be NULL):
  * squared row / column norms of Tinv.  status[nb] (may be NULL): 0 ok, 1 singular to
- * working precision (Tinv, rho_row and rho_col of that block are then zero).
+ * working precision (Tinv, rho_row and rho_col of that block are then zero).  Tinv may be T itself for blocks of 32, 64 and
+ * 128; no other overlap is allowed.  A block's result does not depend on the others of the call.
  * k as in cafeq_xform (else CAFEQ_ERR_UNSUPPORTED). */
 int cafeq_block_inverse(const float* T, int k, int nb, float* Tinv, float* rho_row,
                         float* rho_col, int* status, void* ws, void* stream);

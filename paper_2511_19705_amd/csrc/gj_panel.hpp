@@ -21,7 +21,6 @@ struct GjArgs {
   const float* resid = nullptr;
   int nresid = 0;
   float resid_max = 0.f;
-  int col_slice = -1;    // 0, 1: of the result every other 32 columns, from these on (-1: all)
 };
 
 // Compile-time loop: f(integral_constant<int, I>) for I in [B, E).
@@ -315,10 +314,7 @@ __device__ void gj_panel_body(const GjArgs& a, const int b, GjShared<K, S>& sh) 
 #pragma unroll
     for (int i = 0; i < RT; ++i)
 #pragma unroll
-      for (int j = 0; j < CT; ++j) {
-        const int c = ct + j * NCT;
-        if (a.col_slice < 0 || (c >> 5 & 1) == a.col_slice) O[(rt + i * NRT) * K + c] = 0.f;
-      }
+      for (int j = 0; j < CT; ++j) O[(rt + i * NRT) * K + ct + j * NCT] = 0.f;
     return;
   }
   if (tid < K) kinv[pk[tid]] = tid;
@@ -331,8 +327,7 @@ __device__ void gj_panel_body(const GjArgs& a, const int b, GjShared<K, S>& sh) 
   for (int i = 0; i < RT; ++i) {
     const int orow = kinv[rt + i * NRT];
 #pragma unroll
-    for (int j = 0; j < CT; ++j)
-      if (a.col_slice < 0 || (ocol[j] >> 5 & 1) == a.col_slice) O[orow * K + ocol[j]] = float(reg[i][j] * scale);
+    for (int j = 0; j < CT; ++j) O[orow * K + ocol[j]] = float(reg[i][j] * scale);
   }
 }
 template <int K, int RT, int CT, typename S, bool PIV>

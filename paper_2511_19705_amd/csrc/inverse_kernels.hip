@@ -22,28 +22,26 @@
 namespace cafeq {
 namespace {
 
-template <int K, int WARM, bool SPLIT>
+template <int K, int WARM>
 __global__ __launch_bounds__(NsShape<K>::NW * 64) void ns_inverse_kernel(const float* __restrict__ T, float* __restrict__ Tinv,
                                                                          int* __restrict__ status) {
   extern __shared__ __align__(16) unsigned char ns_lds[];
-  int b = int(blockIdx.x), slice = 0;
-  if (SPLIT) block_and_part(blockIdx.x, 2, gridDim.x, &b, &slice);
-  ns_inverse_body<K, WARM, SPLIT>(T, Tinv, status, b, ns_lds, slice);
+  ns_inverse_body<K, WARM>(T, Tinv, status, int(blockIdx.x), ns_lds);
 }
 
-template <int K, int WARM, bool SPLIT = false>
+template <int K, int WARM>
 int launch_ns(const float* T, int nb, float* Tinv, int* status, hipStream_t st) {
   constexpr size_t lds = NsShape<K>::bytes;
   if (lds > 64 * 1024) {
     static std::atomic<bool> attr_set{false};
     if (!attr_set) {
-      if (hipFuncSetAttribute(reinterpret_cast<const void*>(ns_inverse_kernel<K, WARM, SPLIT>),
+      if (hipFuncSetAttribute(reinterpret_cast<const void*>(ns_inverse_kernel<K, WARM>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) != hipSuccess)
         return CAFEQ_ERR_LAUNCH;
       attr_set = true;
     }
   }
-  hipLaunchKernelGGL((ns_inverse_kernel<K, WARM, SPLIT>), dim3(unsigned(nb) * (SPLIT ? 2 : 1)), dim3(NsShape<K>::NW * 64), lds, st, T, Tinv, status);
+  hipLaunchKernelGGL((ns_inverse_kernel<K, WARM>), dim3(nb), dim3(NsShape<K>::NW * 64), lds, st, T, Tinv, status);
   CAFEQ_CHECK_LAUNCH();
   return CAFEQ_OK;
 }
@@ -55,10 +53,7 @@ int launch_block_inverse(const float* T, int K, int nb, double* work, float* Tin
   switch (K) {
     case 32: rc = launch_ns<32, 0>(T, nb, Tinv, status, st); break;
     case 64: rc = launch_ns<64, 0>(T, nb, Tinv, status, st); break;
-    // (two workgroups a block while each has a compute unit of its own)
-    case 128:
-      rc = 2 * int64_t(nb) <= device_cu_count() ? launch_ns<128, 0, true>(T, nb, Tinv, status, st) : launch_ns<128, 0>(T, nb, Tinv, status, st);
-      break;
+    case 128: rc = launch_ns<128, 0>(T, nb, Tinv, status, st); break;
     case 256: return launch_inverse256(T, nb, work, Tinv, rho_row, rho_col, status, false, st);
   }
   if (rc) return rc;

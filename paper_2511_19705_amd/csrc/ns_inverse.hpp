@@ -66,13 +66,11 @@ struct NsShape {
   static_assert(K * LDS * 4 <= 3 * K * LDH * 2, "and so does T");
 };
 // ns_lds: NsShape<K>::bytes; threads NsShape<K>::NW * 64 of the workgroup, the others of it, if any, have ended.
-// SPLIT (two tiles of columns a wave): one of two workgroups that take the rounds alike and the exact step, a third of the time, for one
-// column tile of each wave only; it writes those columns, eliminated or not.  36 blocks of 128 26.0 -> 23.5 us, 72 27.7 -> 25.5, 112 29.3 -> 27.4.
-template <int K, int WARM, bool SPLIT = false>
+template <int K, int WARM>
 __device__ __forceinline__ void ns_inverse_body(const float* __restrict__ T, float* __restrict__ Tinv, int* __restrict__ status, const int b,
-                                                unsigned char* ns_lds, const int slice = 0) {
+                                                unsigned char* ns_lds) {
   using S = NsShape<K>;
-  constexpr int TPW = S::TPW, TR = SPLIT ? 1 : TPW, NW = S::NW, LDH = S::LDH, NS = K / 16, kMaxRounds = 10;
+  constexpr int TPW = S::TPW, NW = S::NW, LDH = S::LDH, NS = K / 16, kMaxRounds = 10;
   uint16_t* xth = reinterpret_cast<uint16_t*>(ns_lds);   // X^T[j][i], high and low parts
   uint16_t* xtl = xth + K * LDH;
   uint16_t* rt = xtl + K * LDH;                           // R^T[j][i]
@@ -255,20 +253,13 @@ __device__ __forceinline__ void ns_inverse_body(const float* __restrict__ T, flo
     if (last) { result = kConverged; break; }
   }
 
-  float xm = 0.f;
-#pragma unroll
-  for (int t = 0; t < TPW; ++t)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) xm = fmaxf(xm, fabsf(x[t][v]));
-  // from here on the wave's tiles are x[t], t < TR, columns jr + 32 t
-  static_assert(!SPLIT || (TPW == 2 && !WARM), "a start that the other workgroup does not overwrite");
-  const int jr = SPLIT ? j0 + 32 * slice : j0;
-  if (SPLIT && slice) {
-#pragma unroll
-    for (int v = 0; v < 16; ++v) x[0][v] = x[TPW - 1][v];
-  }
   // the step with the exact residual; false: X is not the inverse it was taken for
   auto refine = [&]() __attribute__((always_inline)) {
+    float xm = 0.f;
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) xm = fmaxf(xm, fabsf(x[t][v]));
     xm = cluster_allmax<64>(xm);
     // T again, as digits of 2^-ex T: A operands, sixteen contraction indices per lane and step
     __syncthreads();                           // (slower waves are still reading red and the last round's operands)
@@ -300,7 +291,7 @@ __device__ __forceinline__ void ns_inverse_body(const float* __restrict__ T, flo
     unsigned char* dig = ns_lds;               // [digit][j][LDG]: X^T
     __syncthreads();                           // every wave has its rows of T
 #pragma unroll
-    for (int t = 0; t < TR; ++t)
+    for (int t = 0; t < TPW; ++t)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const float y[4] = {x[t][4 * g] * sd, x[t][4 * g + 1] * sd, x[t][4 * g + 2] * sd, x[t][4 * g + 3] * sd};
@@ -308,17 +299,17 @@ __device__ __forceinline__ void ns_inverse_body(const float* __restrict__ T, flo
         digit_words(y, d);
 #pragma unroll
         for (int p = 0; p < 4; ++p)
-          *reinterpret_cast<uint32_t*>(dig + (p * K + jr + 32 * t) * S::LDG + i0 + 8 * g) = d[p];
+          *reinterpret_cast<uint32_t*>(dig + (p * K + j0 + 32 * t) * S::LDG + i0 + 8 * g) = d[p];
       }
     __syncthreads();
     // one sum per weight 2^-12, 2^-20, .. 2^-44 (neighbouring matrix instructions then do not depend on each other), each
     // below 2^23 (the first digits are at most 64), taken from the identity largest first: what is left after each is small
     // enough to be exact in float32
-    uint2 rp[TR][4];                          // 2^20 R
+    uint2 rp[TPW][4];                          // 2^20 R
     const float rs = ldexpf(1.f, 20 + sh), back = 0x1p-20f;
     float f2 = 0.f;
 #pragma unroll
-    for (int t = 0; t < TR; ++t) {
+    for (int t = 0; t < TPW; ++t) {
       intx16 part[5];
 #pragma unroll
       for (int w = 0; w < 5; ++w)
@@ -329,14 +320,14 @@ __device__ __forceinline__ void ns_inverse_body(const float* __restrict__ T, flo
         intx4 xd[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          xd[q] = *reinterpret_cast<const intx4*>(dig + (q * K + jr + 32 * t) * S::LDG + 32 * s + 16 * h);
+          xd[q] = *reinterpret_cast<const intx4*>(dig + (q * K + j0 + 32 * t) * S::LDG + 32 * s + 16 * h);
 #pragma unroll
         for (int p = 0; p < 4; ++p)
 #pragma unroll
           for (int q = 0; q < 4; ++q)
             if (p + q < 5) part[p + q] = __builtin_amdgcn_mfma_i32_32x32x32_i8(td[p][s], xd[q], part[p + q], 0, 0, 0);
       }
-      const float one = jr + 32 * t - ln == i0 - 4 * h ? ldexpf(1.f, -sh) : 0.f;
+      const float one = j0 + 32 * t - ln == i0 - 4 * h ? ldexpf(1.f, -sh) : 0.f;
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         float u[4];
@@ -360,13 +351,13 @@ __device__ __forceinline__ void ns_inverse_body(const float* __restrict__ T, flo
     for (int w = 1; w < NW; ++w) f2 += red[NW + w];
     if (!(f2 * 0x1p-40f <= 4e-10f)) return false;
 #pragma unroll
-    for (int t = 0; t < TR; ++t)
+    for (int t = 0; t < TPW; ++t)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) *reinterpret_cast<uint2*>(rt + (jr + 32 * t) * LDH + i0 + 8 * g) = rp[t][g];
+      for (int g = 0; g < 4; ++g) *reinterpret_cast<uint2*>(rt + (j0 + 32 * t) * LDH + i0 + 8 * g) = rp[t][g];
     __syncthreads();
-    floatx16 acc[TR];
+    floatx16 acc[TPW];
 #pragma unroll
-    for (int t = 0; t < TR; ++t)
+    for (int t = 0; t < TPW; ++t)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
     // (xr: X before the last round's update; the difference is of third order)
@@ -374,13 +365,13 @@ __device__ __forceinline__ void ns_inverse_body(const float* __restrict__ T, flo
     for (int s = 0; s < NS; ++s) {
       const halfx8 av = as_halfx8(*reinterpret_cast<const uintx4*>(xr + (i0 - 4 * h + ln) * LDH + 16 * s + 8 * h));
 #pragma unroll
-      for (int t = 0; t < TR; ++t) {
-        const halfx8 bv = as_halfx8(*reinterpret_cast<const uintx4*>(rt + (jr + 32 * t) * LDH + 16 * s + 8 * h));
+      for (int t = 0; t < TPW; ++t) {
+        const halfx8 bv = as_halfx8(*reinterpret_cast<const uintx4*>(rt + (j0 + 32 * t) * LDH + 16 * s + 8 * h));
         acc[t] = CAFEQ_MFMA_F16(av, bv, acc[t]);
       }
     }
 #pragma unroll
-    for (int t = 0; t < TR; ++t)
+    for (int t = 0; t < TPW; ++t)
 #pragma unroll
       for (int v = 0; v < 16; ++v) x[t][v] = fmaf(acc[t][v], back, x[t][v]);
     return true;
@@ -391,15 +382,14 @@ __device__ __forceinline__ void ns_inverse_body(const float* __restrict__ T, flo
     GjArgs a;
     a.K = K; a.nz = 0; a.T = T; a.partial = nullptr; a.out = Tinv;
     a.status = status; a.status_stride = 1; a.status_offset = 0;
-    if (SPLIT) a.col_slice = slice;
     gj_panel_body<K, 4, 4 * TPW, double, true>(a, b, *reinterpret_cast<GjShared<K, double>*>(ns_lds));
     return;
   }
   // (an offset of its own: with the one of the warm start's loads their addresses stayed in registers all the way)
-  int at = i0 * K + jr;
+  int at = i0 * K + j0;
   asm volatile("" : "+v"(at));
 #pragma unroll
-  for (int t = 0; t < TR; ++t)
+  for (int t = 0; t < TPW; ++t)
 #pragma unroll
     for (int v = 0; v < 16; ++v) Ob[at + (8 * (v / 4) + (v % 4)) * K + 32 * t] = x[t][v] * inv_sX;
   if (status && tid == 0) status[b] = 0;
