@@ -958,7 +958,8 @@ __global__ __launch_bounds__(256) void tail_chain32_kernel(const ReduceArgs ra, 
     static_assert(NsShape<K>::bytes <= sizeof(Chain32Lds) && NsShape<K>::NW == 1, "one wave, in the chain's room");
     __syncthreads();                                  // (the block's new entries are written, the chain's LDS is free)
     if (tid >= 64) return;
-    ns_inverse_body<K, 1>(up.T, Tinv, status, b, reinterpret_cast<unsigned char*>(&s));
+    if (!ns_inverse_body<K, 1>(up.T, Tinv, status, b, reinterpret_cast<unsigned char*>(&s)))
+      gj_panel_body<K, 4, 4, double, true>(ns_eliminate_args(K, up.T, Tinv, status), b, *reinterpret_cast<GjShared<K, double>*>(&s));
   }
 }
 

@@ -26,7 +26,9 @@ template <int K, int WARM>
 __global__ __launch_bounds__(NsShape<K>::NW * 64) void ns_inverse_kernel(const float* __restrict__ T, float* __restrict__ Tinv,
                                                                          int* __restrict__ status) {
   extern __shared__ __align__(16) unsigned char ns_lds[];
-  ns_inverse_body<K, WARM>(T, Tinv, status, int(blockIdx.x), ns_lds);
+  const int b = int(blockIdx.x);
+  if (!ns_inverse_body<K, WARM>(T, Tinv, status, b, ns_lds))
+    gj_panel_body<K, 4, 4 * NsShape<K>::TPW, double, true>(ns_eliminate_args(K, T, Tinv, status), b, *reinterpret_cast<GjShared<K, double>*>(ns_lds));
 }
 
 template <int K, int WARM>

@@ -66,8 +66,10 @@ struct NsShape {
   static_assert(K * LDS * 4 <= 3 * K * LDH * 2, "and so does T");
 };
 // ns_lds: NsShape<K>::bytes; threads NsShape<K>::NW * 64 of the workgroup, the others of it, if any, have ended.
+// false: the block is to be eliminated, by the kernel itself, in the same LDS (ns_eliminate_args).  From in here gj_panel_body, a function of
+// its own at k = 128, would get a pointer of which the compiler has lost that it is LDS: 8 blocks of 128 far from rotations 99 -> 132 us.
 template <int K, int WARM>
-__device__ __forceinline__ void ns_inverse_body(const float* __restrict__ T, float* __restrict__ Tinv, int* __restrict__ status, const int b,
+__device__ __forceinline__ bool ns_inverse_body(const float* __restrict__ T, float* __restrict__ Tinv, int* __restrict__ status, const int b,
                                                 unsigned char* ns_lds) {
   using S = NsShape<K>;
   constexpr int TPW = S::TPW, NW = S::NW, LDH = S::LDH, NS = K / 16, kMaxRounds = 10;
@@ -379,11 +381,7 @@ __device__ __forceinline__ void ns_inverse_body(const float* __restrict__ T, flo
   if (result == kConverged && !refine()) result = kEliminate;
   if (result == kEliminate) {
     __syncthreads();                             // LDS changes hands
-    GjArgs a;
-    a.K = K; a.nz = 0; a.T = T; a.partial = nullptr; a.out = Tinv;
-    a.status = status; a.status_stride = 1; a.status_offset = 0;
-    gj_panel_body<K, 4, 4 * TPW, double, true>(a, b, *reinterpret_cast<GjShared<K, double>*>(ns_lds));
-    return;
+    return false;
   }
   // (an offset of its own: with the one of the warm start's loads their addresses stayed in registers all the way)
   int at = i0 * K + j0;
@@ -393,6 +391,13 @@ __device__ __forceinline__ void ns_inverse_body(const float* __restrict__ T, flo
 #pragma unroll
     for (int v = 0; v < 16; ++v) Ob[at + (8 * (v / 4) + (v % 4)) * K + 32 * t] = x[t][v] * inv_sX;
   if (status && tid == 0) status[b] = 0;
+  return true;
+}
+__device__ __forceinline__ GjArgs ns_eliminate_args(int K, const float* T, float* Tinv, int* status) {
+  GjArgs a;
+  a.K = K; a.nz = 0; a.T = T; a.partial = nullptr; a.out = Tinv;
+  a.status = status; a.status_stride = 1; a.status_offset = 0;
+  return a;
 }
 
 }  // namespace cafeq
