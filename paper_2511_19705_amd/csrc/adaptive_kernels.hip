@@ -394,8 +394,11 @@ __global__ __launch_bounds__(512) void gram_pair16_kernel(const GramArgs a) {
 //     S[i][j] = sum_t q[t][i] (s[t][i] Xq[t][j]),   R[i][j] = sum_t q[t][i] (s[t][i] E[t][j]),
 // a product needs three part products instead of six, and the row side no split at all.  The right operands then belong to the row's
 // group: V = 2 versions of them in a quadrant of 128 rows at groups of 64, one from 128 on.  Groups of 32 would need four versions, eight
-// splits where the kernel above has three, and stay there.  The scales of i are divided by a power of two near the head's first one
-// (and so are S and R, of which S^-1 R alone is used): the right operands keep the exponents of Xq and E.
+// splits where the kernel above has three, and stay there.  The scales of i are multiplied by a power of two (and so are S and R, of
+// which S^-1 R alone is used) that takes the square of the head's largest scale to about 1: the third parts of the right operands, products
+// of two scales, then stay numbers in weights down to 2^-60, as far down as squares of float32 reach.  The largest of 64 scales stands
+// for the head's: with 2^-64 to 2^64 as the factor's range no sum overflows that did not without it, unless all 64 are below a 2^-48th of it.
+// (The head's first scale alone, without that range, turned a first line of 1e-37 next to ordinary ones into infinities.)
 // A thread takes four contraction indices of one free index a step, for every version.  Along rows four lanes read a row's 64 bytes: 16
 // cache lines a request.  With eight indices a thread (32 lines a request) the line lookups, 1024 and with the row side's codes 1280
 // a step, were what the kernel took its time for: 104 us with six part products, 117 with three.
@@ -419,11 +422,14 @@ __global__ __launch_bounds__(512) void gram_pair_codes_kernel(const GramArgs a) 
   const int64_t t1 = t0 + a.chunk < a.tlen ? t0 + a.chunk : a.tlen;
   const int64_t f0 = COL ? int64_t(b) * K : (int64_t(b) * a.rep + qi) * K;
   const int64_t C = a.cols, cg = C / a.G;
-  float unit;                                    // 2^-e: s 2^-e in [1, 2) for the head's first scale
+  float unit;                                    // 2^-2e, e the exponent of the largest of 64 of the head's scales (the same for all its workgroups)
   {
-    const float s0 = a.scales[COL ? f0 / a.G : (int64_t(b) * a.rep * K / a.G) * C];
-    const int e = int(__float_as_uint(s0) >> 23) & 255;
-    unit = e > 0 && e < 254 ? __uint_as_float(uint32_t(254 - e) << 23) : 1.f;
+    const int64_t first = COL ? f0 : int64_t(b) * a.rep * K, g0 = first / a.G, g1 = (first + (COL ? K : a.rep * K) - 1) / a.G;
+    const int64_t t = int64_t(lane) * a.tlen / 64, g = g0 + lane % (g1 - g0 + 1);
+    const float m = cluster_allmax<64>(a.scales[COL ? t * cg + g : g * C + t]);
+    const int e = int(__float_as_uint(m) >> 23 & 255) - 127;
+    // (none of them but zeros: as if they were 2^-16, small enough for what cannot be seen and too large for nothing)
+    unit = ldexpf(1.f, m > 0.f ? min(max(-2 * e, -64), 64) : 32);
   }
 
   // loader role: free index, quarter of the step's 16 contraction indices
