@@ -656,7 +656,10 @@ __global__ __launch_bounds__(4 * K) void bgemm_chain_kernel(const float* __restr
 // Bound: the splits (880 vector instructions a wave) next to 96 matrix instructions, requests and stores of 4 bytes a lane at both ends
 // (72 blocks, 22 k cycles: requests 4, P^T 1.3, first product 4.4, exchange 2, second 8, stores 3; with Adam's state 29 k).
 // On v_mfma_f32_32x32x2_f32 / here: 72 blocks 15.7 / 13.2 us, with Adam 20.0 / 18.1, 112 17.4 / 15.2, 288 50 / 37.5.
+// Where the whole block of G is below kC16Small its third parts, or X's, would end below bfloat16's smallest number (the gradient of a
+// loss in weights of 1e-18 and less is 2^-120): it is taken times 2^60, and alpha divided by it.
 constexpr int kC16Part = 8 * 2 * 64 * 16;
+constexpr float kC16Small = 0x1p-60f;
 __device__ __forceinline__ void split3_pair(float x0, float x1, uint32_t& a, uint32_t& b, uint32_t& c) {
   a = pack_bf16(x0, x1);
   const float r0 = x0 - bf16_lo_f32(a), r1 = x1 - bf16_hi_f32(a);
@@ -669,6 +672,7 @@ __global__ __launch_bounds__(512, TWO ? 4 : 2) void bgemm_chain16_kernel(const f
                                                                float alpha, float beta, const UpdateHook up) {
   constexpr int K = 128;
   __shared__ __align__(16) unsigned char op[3 * kC16Part];
+  __shared__ float gmax[8];
   int b, slice;
   block_and_part(blockIdx.x, 2, gridDim.x, &b, &slice);
   const int i0 = slice * 64;
@@ -717,7 +721,19 @@ __global__ __launch_bounds__(512, TWO ? 4 : 2) void bgemm_chain16_kernel(const f
     *reinterpret_cast<uintx4*>(at + kC16Part) = __builtin_bit_cast(uintx4, t.mid);
     *reinterpret_cast<uintx4*>(at + 2 * kC16Part) = __builtin_bit_cast(uintx4, t.lo);
   }
+  float gm = 0.f;
+#pragma unroll
+  for (int e = 0; e < 64; ++e) gm = fmaxf(gm, fabsf(g[e]));
+  gm = cluster_allmax<64>(gm);
+  if (lane == 0) gmax[wave] = gm;
   __syncthreads();
+#pragma unroll
+  for (int w = 0; w < 8; ++w) gm = fmaxf(gm, gmax[w]);
+  if (gm < kC16Small) {                     // (uniform)
+    alpha *= kC16Small;
+#pragma unroll
+    for (int e = 0; e < 64; ++e) g[e] *= 1.f / kC16Small;
+  }
   floatx16 x;
 #pragma unroll
   for (int r = 0; r < 16; ++r) x[r] = 0.f;

@@ -1,6 +1,7 @@
-"""GPU parity of the gradient's way through the inverse for blocks of 128 on either side of the count from which X = P^T G passes
-through LDS in parts (two workgroups of 64 rows a block, 256 compute units): evaluations against the oracle (bounds of
-tests/parity.py: the arithmetic and its order are the same in both forms) and the update in the same kernel's epilogue."""
+"""GPU parity of the gradient's way through the inverse for blocks of 128 on either side of the count from which two workgroups share
+a compute unit (two workgroups of 64 rows a block, 256 compute units): evaluations against the oracle (bounds of tests/parity.py) and
+the update in the same kernel's epilogue; and gradients near the end of float32's range."""
+import numpy as np
 import pytest
 
 from oracle import cafeq_oracle as O
@@ -39,3 +40,18 @@ def test_adam_step(env, nb):
     cafeq.adam_update(ref, grad, m, v, 1, 1e-3, 0.1, 0.999, 1e-8)
     assert float((ref - T0).abs().max()) > 5e-4
     assert torch.equal(T, ref)
+
+
+# a power of two common to the weights: squared in the gradient, whose entries (2^-118 in the root mean square) still are numbers with 24
+# bits, and of which bfloat16 (down to 2^-133) would keep 15.  Sums and products keep their bits but for what ends below 2^-149: 2^-31
+# of an entry
+@pytest.mark.parametrize("nb", [4, 130])
+@pytest.mark.parametrize("axis,group", [(O.COL, 128), (O.ROW, 128), (O.COL, 0)])
+def test_small_weights(env, nb, axis, group):
+    torch, cafeq = env
+    W, T, P = _case(axis, 40, nb * 128, 128, 1, 3700 + nb)
+    grads = []
+    for e in (0, -55):
+        losses, grad, _, _ = cafeq.proxy_loss_fwd_bwd(_dev(torch, W * np.float32(2.0 ** e)), _dev(torch, T), _dev(torch, P), 4, group, axis)
+        grads.append(grad.double() * 2.0 ** (-2 * e))
+    assert float((grads[1] - grads[0]).norm() / grads[0].norm()) < 1e-7
