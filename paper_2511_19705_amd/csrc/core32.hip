@@ -253,7 +253,7 @@ __global__ __launch_bounds__(kThreads, 3) void core32_kernel(const CoreParams p)
 #pragma unroll
     for (int f = 0; f < 16; ++f) a = fmaxf(a, fabsf(z[f]));
     float zs = 0.f;
-    int j = 0;
+    int j = 4;                  // (of a group without a number the entry is 4, as in the general kernel)
     equal4<24>(zs, j, a, z[12], z[13], z[14], z[15]);
     equal4<16>(zs, j, a, z[8], z[9], z[10], z[11]);
     equal4<8>(zs, j, a, z[4], z[5], z[6], z[7]);

@@ -6,6 +6,7 @@ import pytest
 
 from oracle import cafeq_oracle as O
 from paper_2511_19705_amd import workloads as WL
+from tests import parity
 from tests.test_gpu_dual import _check_dual
 from tests.test_gpu_single import _case, _check_single, _dev
 
@@ -64,3 +65,26 @@ def test_loop_against_its_steps(env, axis, lr):
     np.testing.assert_allclose(mine.cpu().numpy(), T.cpu().numpy(), rtol=0, atol=1e-4 * float(T.abs().max()))
     Q, st = cafeq.block_inverse(mine)
     assert torch.equal(P, Q) and torch.equal(status, st)
+
+
+# a group without a number counts as a largest magnitude of zero at its entry 4 (as in the kernel for other blocks and groups): what its line's
+# other inputs add to the pair's gradient, by the loss pass itself and, over prepared weights, by records
+@pytest.mark.parametrize("prepared", [False, True])
+def test_group_without_a_number(env, prepared):
+    torch, cafeq = env
+    A, B, T = WL.small_pair(136, 128, 32, 1, 9450, eps=0.05)
+    P = O.block_inverse(T).astype(np.float32)
+    line, block, m0 = 70, 2, 13
+    Az = A.copy()
+    Az[line, 32 * block:32 * block + 32] = 0.0
+    ref = O.dual_lse(Az, B, T, P, 4, 32, 1, 5.0)
+    want = ref["gradT"].copy()
+    want[block, :, 4] += np.exp(-5.0 * ref["lse"]) * A[line, 32 * block:32 * block + 32].astype(np.float64)
+    A[line, 32 * block + m0] = np.nan
+    Ad, Bd = _dev(torch, A), _dev(torch, B)
+    prep = (cafeq.prepare_weights(Ad, O.COL), cafeq.prepare_weights(Bd, O.ROW)) if prepared else (None, None)
+    _, grad, _ = cafeq.dual_proxy_loss_fwd_bwd(Ad, Bd, _dev(torch, T), _dev(torch, P), 4, 32, 1, 5.0, prepared=prep)
+    got = grad.cpu().numpy()
+    assert np.isnan(got[block, m0]).all() and np.isnan(got).sum() == 32
+    got[block, m0] = want[block, m0]
+    parity.check_grad(got, want)
