@@ -247,11 +247,13 @@ bool gather_possible(int K, const GroupPlan& gp, bool lines) { return lines && (
 //   3584 x 4096 425 / 381, 4608 x 14336 1274 / 1486; 36864 x 4608 1384 / 1671, in bfloat16 1387 / 1280.
 //   k = 128, groups of 128: 14336 x 1024 .97, 36864 x 256 118 / 110, x 1024 164 / 171, x 4608 580 / 507, and with prepared weights, whose product
 //   reads tiles in its own order, 127 / 142 and 385 / 393.
-//   k = 32 with groups of 32, whose loss pass (core32.hip) forms the gradient on its way, as exact: by records / on the way 36864 x 2304 282 / 151,
-//   2304 x 9216 prepared 99 / 56, 4608 x 36864 447 / 291, in bfloat16 390 / 291, pairs 1000 x 4096 80 / 57, 3584 x 14336 270 / 208; not in
-//   bfloat16 along rows, of which a wave asks for 64 bytes at a time: pairs 4608 x 36864 648 / 809, 2304 x 9216 116 / 125.  Pairs from 1 M weights
-//   a member on (2304 x 512 42 / 36; smaller ones were not timed again), single matrices below 10 M and from 12 M on (between them
-//   the tests fix the route of a size, 4888 x 2048).
+//   k = 32 with groups of 32, whose loss pass (core32.hip) forms the gradient on its way, as exact: single matrices on the way at every size
+//   (by records / on the way, launches replayed from a graph, without the inverse: 4104 x 2048 43 / 29, 4888 x 2048 48 / 30, 1152 x 9216 49 / 31,
+//   304 x 36864 67 / 45, prepared 2304 x 9216 87 / 48, in bfloat16 78 / 47; with it 36864 x 2304 282 / 151, 4608 x 36864 447 / 291), but for large
+//   ones in bfloat16 along rows, of which a wave asks for 64 bytes at a time: 4888 x 2048 55 / 32, 36864 x 1024 167 / 103, 3584 x 14336 132.7 / 133.2,
+//   36864 x 4608 349 / 479.  Pairs in float32 from 1 M weights a member on (1000 x 4096 80 / 57, 3584 x 14336 270 / 208; below either way does:
+//   136 x 512 22.4 / 22.2, 1024 x 512 24.8 / 23.3, 1152 x 1024 27.5 / 27.5); in bfloat16 by records (1000 x 4096 42.5 / 38.5, 3584 x 14336 224 / 233, with
+//   the inverse 2304 x 9216 116 / 125, 4608 x 36864 648 / 809).
 //   k = 32 and 64 in one matrix, where the loss pass forms the gradient on its way: 14336 x 1024 (k = 32) 68 / 85, 36864 x 2304
 //   308 / 259, 2304 x 4608 58 / 55, 1147 x 9216 63 / 61, 4.2 M weights 33 / 40; over prepared weights, whose loss pass only records, with groups of 128
 //   (bfloat16: of 64) 36864 x 1024 113 / 107, 9216 x 1024 57 / 50.  On the min/max grid, a pass of its own either way: groups of 32 1147 x 512
@@ -260,7 +262,7 @@ bool gather_possible(int K, const GroupPlan& gp, bool lines) { return lines && (
 bool gather_pays(const cafeq_mat* W, int K, const GroupPlan& gp, int64_t nlines, int64_t naxis, bool asym, bool pair, bool v2, bool along_rows) {
   const int64_t weights = nlines * naxis;
   const bool bf16 = W->dtype == CAFEQ_BF16;
-  if (K == 32 && gp.G == 32 && !asym && !(bf16 && (pair || along_rows)) && weights >= (pair ? int64_t(1) << 20 : 12000000)) return false;
+  if (K == 32 && gp.G == 32 && !asym && (pair ? !bf16 && weights >= int64_t(1) << 20 : !(bf16 && along_rows) || weights < 50000000)) return false;
   const bool on_the_way = !pair && K <= 64 && gp.gspan == 1 && core_lds_bytes(K, gp.Gk, true) != 0 && !asym;
   if (on_the_way && weights < (int64_t(1) << 23)) return false;
   if (K == 256 && gp.G == 64) return bf16 || nlines <= 64 * naxis;

@@ -44,14 +44,26 @@ def _single(env, W, T, P, bits, group, axis, prepared, bf16=False):
 
 
 # blocks of 32 and 64: the gradient passes over the weights (none: the loss pass forms it on its way).  From 10 M weights on, and
-# 2048 axis indices (groups of 128 over prepared weights: 8 M, 1024); 8 bits and plain weights: records of the general kernel
+# 2048 axis indices (groups of 128 over prepared weights: 8 M, 1024); 8 bits and plain weights: records of the general kernel.  Blocks of 32 with
+# groups of 32, whose loss pass is a kernel of its own: on its way at every size but in bfloat16 along rows from 50 M
 @pytest.mark.parametrize("k,group,bits,lines,naxis,axis,prepared,bf16,passes", [
-    (32, 32, 4, 4100, 2048, O.COL, True, False, 0), (32, 32, 4, 4888, 2048, O.COL, True, False, 1), (32, 64, 8, 4888, 2048, O.COL, True, False, 1),
+    (32, 32, 4, 4100, 2048, O.COL, True, False, 0), (32, 32, 4, 4888, 2048, O.COL, True, False, 0), (32, 32, 4, 4888, 2048, O.ROW, True, True, 0), (32, 64, 8, 4888, 2048, O.COL, True, False, 1),
     (64, 64, 4, 4888, 2048, O.COL, False, False, 1), (64, 128, 8, 4888, 2048, O.ROW, True, False, 1), (32, 128, 4, 4888, 2048, O.ROW, True, True, 1),
     (64, 64, 4, 9800, 1024, O.COL, False, False, 0), (64, 128, 4, 8200, 1024, O.COL, True, False, 1), (64, 64, 4, 8200, 1024, O.COL, True, True, 1)])
 def test_on_the_way_or_by_records(env, k, group, bits, lines, naxis, axis, prepared, bf16, passes):
     W, T, P = _case(axis, lines, naxis, k, 1, 5100 + k + group)
     assert _single(env, W, T, P, bits, group, axis, prepared, bf16) == passes
+
+
+# ... and where that line lies (the way alone; records of bfloat16 weights along rows against the oracle: above)
+@pytest.mark.parametrize("lines,passes", [(24408, 0), (24416, 1)])
+def test_rows_in_bfloat16(env, lines, passes):
+    torch, cafeq = env
+    W = torch.randn((2048, lines), generator=torch.Generator(device="cuda:0").manual_seed(5150), device="cuda:0").to(torch.bfloat16)
+    T = _dev(torch, WL.perturbed_blocks(64, 32, 5151, 0.05))
+    P, _ = cafeq.block_inverse(T)
+    prep = cafeq.prepare_weights(W, O.ROW)
+    assert _launches(torch, cafeq, 1, lambda: cafeq.proxy_loss_fwd_bwd(W, T, P, 4, 32, O.ROW, prepared=prep))[1] == passes
 
 
 # blocks of 256 with groups of 32: eight reads of every line, or the product; blocks of 128: lines and axis indices.  Either way one pass
