@@ -275,7 +275,7 @@ int cafeq_infer_single(const float* X, int n, int64_t ldx, const cafeq_xform* xf
     // 9216 x 2304 11.5 / 9.0, 14336 x 1536 and two tokens 18.8 / 11.3, 2304 x 9216 10.0 / 9.2; of six waves 14336 x 10752 34 / 41, of eight
     // 4608 x 36864 51 / 54.
     const int waves = T / kWave;
-    const int64_t want = waves <= 5 ? 4096 / waves : 512;
+    const int64_t cus = device_cu_count(), want = waves <= 5 ? 16 * cus / waves : 2 * cus;
     const int64_t rpw = ((out + want - 1) / want + kRowsMax - 1) / kRowsMax * kRowsMax;
     a.rows_per_wg = int(rpw);
     const unsigned nwg = unsigned((out + rpw - 1) / rpw);
