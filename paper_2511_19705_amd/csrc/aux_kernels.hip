@@ -562,21 +562,16 @@ __global__ __launch_bounds__(256 * KS) void bgemm_mfma_kernel(const float* __res
 // registers of the wave that multiplies by it; X passes through LDS transposed.
 // Bound: latency of load, LDS and the chain of matrix instructions.
 constexpr int kChainLdX = 33;
-constexpr size_t chain_lds(int K) { return size_t(K * (K + 1) + 2 * K * kChainLdX) * sizeof(float); }
-template <int K>
-__global__ __launch_bounds__(4 * K) void bgemm_chain_kernel(const float* __restrict__ P, const float* __restrict__ G,
-                                                            float* __restrict__ C, float alpha, float beta,
-                                                            const UpdateHook up) {
-  static_assert(K == 64, "a block is one slice of 64 rows");
-  constexpr int kChainLdP = K + 1, NT = 4 * K, WJ = K / 32, SL = K / 64;   // threads, column tiles, slices per block
+constexpr size_t kChain64Lds = size_t(64 * 65 + 2 * 64 * kChainLdX) * sizeof(float);
+__global__ __launch_bounds__(256) void bgemm_chain64_kernel(const float* __restrict__ P, const float* __restrict__ G, float* __restrict__ C,
+                                                            float alpha, float beta, const UpdateHook up) {
+  constexpr int K = 64, kChainLdP = K + 1, NT = 256;
   extern __shared__ __align__(16) float csm[];
   float* sp = csm;                          // P[r][c]
-  float* sx = csm + K * kChainLdP;          // [2 row halves][l][32 rows]: X^T of the workgroup's slice
-  int b, slice;
-  block_and_part(blockIdx.x, SL, gridDim.x, &b, &slice);
-  const int i0 = slice * 64;
+  float* sx = csm + K * kChainLdP;          // [2 row halves][l][32 rows]: X^T
+  const int b = int(blockIdx.x);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ln = lane & 31, h = lane >> 5;
-  const int wi = wave / WJ, wj = wave % WJ;
+  const int wi = wave >> 1, wj = wave & 1;
   const float* Pb = P + size_t(b) * K * K;
   const float* Gb = G + size_t(b) * K * K;
   float* Cb = C + size_t(b) * K * K;
@@ -594,7 +589,7 @@ __global__ __launch_bounds__(4 * K) void bgemm_chain_kernel(const float* __restr
   for (int v = 0; v < 16; ++v) cold[v] = 0.f;
   if (beta != 0.f) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) cold[v] = Cb[(i0 + wi * 32 + 8 * (v / 4) + 4 * h + (v % 4)) * K + wj * 32 + ln];
+    for (int v = 0; v < 16; ++v) cold[v] = Cb[(wi * 32 + 8 * (v / 4) + 4 * h + (v % 4)) * K + wj * 32 + ln];
   }
 #pragma unroll
   for (int u = 0; u < NVP; ++u) {
@@ -608,7 +603,7 @@ __global__ __launch_bounds__(4 * K) void bgemm_chain_kernel(const float* __restr
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
   {
     // X[i][j] = sum_l P[l][i] G[l][j]
-    const float* pa = sp + h * kChainLdP + i0 + wi * 32 + ln;
+    const float* pa = sp + h * kChainLdP + wi * 32 + ln;
 #pragma unroll
     for (int t = 0; t < K / 2; ++t) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[2 * t * kChainLdP], g[t], acc, 0, 0, 0);
   }
@@ -622,7 +617,7 @@ __global__ __launch_bounds__(4 * K) void bgemm_chain_kernel(const float* __restr
   if (up.T) {
 #pragma unroll
     for (int v = 0; v < 16; ++v)
-      was[v] = update_load(up, size_t(b) * K * K + size_t(i0 + wi * 32 + 8 * (v / 4) + 4 * h + (v % 4)) * K + wj * 32 + ln);
+      was[v] = update_load(up, size_t(b) * K * K + size_t(wi * 32 + 8 * (v / 4) + 4 * h + (v % 4)) * K + wj * 32 + ln);
   }
   const float denom = up.T && up.denom ? *up.denom : 1.f;
   __syncthreads();
@@ -638,7 +633,7 @@ __global__ __launch_bounds__(4 * K) void bgemm_chain_kernel(const float* __restr
   }
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
-    const int i = i0 + wi * 32 + 8 * (v / 4) + 4 * h + (v % 4), j = wj * 32 + ln;
+    const int i = wi * 32 + 8 * (v / 4) + 4 * h + (v % 4), j = wj * 32 + ln;
     const float gr = alpha * acc[v] + (beta != 0.f ? beta * cold[v] : 0.f);
     if (up.T) {
       update_store(up, size_t(b) * K * K + size_t(i) * K + j, gr, was[v], denom);
@@ -1186,7 +1181,7 @@ int launch_bgemm_chain(const float* P, const float* G, float* x1, float* C, int 
   switch (K) {
     case 32: hipLaunchKernelGGL(bgemm_chain32_kernel, dim3(unsigned(nb)), dim3(256), 0, st, P, G, C, alpha, beta, up); break;
     case 64:
-      hipLaunchKernelGGL(bgemm_chain_kernel<64>, dim3(unsigned(nb)), dim3(256), chain_lds(64), st, P, G, C, alpha, beta, up);
+      hipLaunchKernelGGL(bgemm_chain64_kernel, dim3(unsigned(nb)), dim3(256), kChain64Lds, st, P, G, C, alpha, beta, up);
       break;
     case 128:
       // more workgroups than compute units: the form of which two fit one
