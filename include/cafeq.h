@@ -351,8 +351,9 @@ typedef struct {
  *   pair:   errU_sq, errV_sq, l2A_sq, l2B_sq, lse, n_groups, penalty, 0   (Adam)
  * moments (pair): 2*nb*k*k floats of optimiser state, zeroed by the call.
  * A step takes the gradient that an evaluation returns, bit for bit, but for a single matrix at two bits: there the loop's
- * gradient is always the product over the weights' 16-bit parts (about 1e-5 relative), where an evaluation may
- * sum the lines themselves (about 1e-7): steps at two bits amplify the difference into other transforms. */
+ * gradient is always the product over the weights' 16-bit parts (two of them, about 1e-5 relative; blocks of 32 and less with groups
+ * of 32 on the symmetric grid three, about 1e-7), where an evaluation may sum the lines themselves (about 1e-7): steps at two
+ * bits amplify the difference into other transforms. */
 int cafeq_optimize_single(const cafeq_mat* W, float* T, float* Tinv, int k, int nb, int rep,
                           const cafeq_quant_cfg* cfg, const cafeq_opt_cfg* opt, float* history,
                           int* status, void* ws, void* stream);

@@ -554,10 +554,8 @@ __global__ __launch_bounds__(256 * KS) void bgemm_mfma_kernel(const float* __res
 }
 
 // The gradient's way through the inverse in one launch for blocks of 64: C = beta C + alpha (P^T G) P^T per block
-// (Sec. 4.1 / 4.2: d/dT of a function of P = T^-1 is -P^T (d/dP) P^T).  Row i of the result needs row i of
-// X = P^T G only, so a workgroup of four waves of one 32 x 32 tile each computes X and then X P^T without any exchange between
-// workgroups, both products on v_mfma_f32_32x32x2_f32 in the arithmetic (and summation order) of bgemm_mfma_kernel.  P is staged once
-// in LDS, row-major with a row stride of 65 floats, which serves the first product's A operand (lanes along a row) and
+// (Sec. 4.1 / 4.2: d/dT of a function of P = T^-1 is -P^T (d/dP) P^T), a workgroup of four waves of one 32 x 32 tile each, both
+// products on v_mfma_f32_32x32x2_f32 in the arithmetic (and summation order) of bgemm_mfma_kernel.  P is staged once in LDS, row-major with a row stride of 65 floats, which serves the first product's A operand (lanes along a row) and
 // the second's B operand (lanes along a column) without bank conflicts; G goes from memory straight into the
 // registers of the wave that multiplies by it; X passes through LDS transposed.
 // Bound: latency of load, LDS and the chain of matrix instructions.
@@ -869,7 +867,7 @@ __global__ __launch_bounds__(256) void bgemm_chain32_kernel(const float* __restr
 // Bound: the latencies of headers and partials, each with eight requests in flight: 5.5 us at
 // 8 blocks, 6.5 at 90, against 4.0 + 5.7 and 4.9 + 5.7 in two launches.
 // INV: a learning loop's step, with the inverse of the transform it leaves (warm-started from P, in P's place) by the first wave: what a
-// launch of its own took for itself and its loads (1147 x 2880, eight steps 201 -> 179 us).
+// launch of its own took for itself and its loads (1147 x 2880, eight steps 208 -> 195 us).
 template <bool INV>
 __global__ __launch_bounds__(256) void tail_chain32_kernel(const ReduceArgs ra, const VArgs va, const LossArgs la, const float* P,
                                                            const UpdateHook up, float* Tinv, int* status) {

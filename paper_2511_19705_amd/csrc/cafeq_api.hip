@@ -168,7 +168,7 @@ float beta_for(const cafeq_quant_cfg* cfg, const QGrid& g) {
 // macro-tiles of 256 lines.
 // codes_along_rows: it writes codes or scales of a matrix transformed along its rows (byte stores).  Blocks of 32 and 64 with
 // float32 weights have no registers for that next to two parts of everything: 9216 x 2304, groups of 32 and 64 48 to 58 us
-// the general way, 58 to 69 this way; groups of 128 54 and 56 at k = 32, 58 and 50 at k = 64.
+// the general way (k = 32 with groups of 32 in its own kernel 39), 58 to 69 this way; groups of 128 54 and 56 at k = 32, 58 and 50 at k = 64.
 bool v2_eligible(const cafeq_mat* W, int K, const GroupPlan& gp, const cafeq_quant_cfg* cfg, bool codes_along_rows) {
   if (K < 128 && codes_along_rows && W->dtype == CAFEQ_F32 && !(K == 64 && gp.Gk == 128)) return false;
   return W->prepared != nullptr && K <= 128 && gp.Gk <= 128 && gp.gspan == 1 && cfg->bits <= 4 && !is_minmax(cfg);
@@ -183,7 +183,8 @@ void make_v2_plan(CorePlan* pl, int share = 1) {
   pl->nslot = pl->nwg + pl->nseg;
 }
 // rounds of workgroups that the loss pass takes over prepared weights and in the general kernel, in multiples of eight, as both ran when
-// the lines below were drawn.  Both now take a workgroup a tile while they fit (workgroups()): more than eight tiles that are no multiple of
+// the lines below were drawn (k = 32 with groups of 32 has had a kernel of its own since, core32.hip, in the general one's place: figures at the
+// lines).  Both now take a workgroup a tile while they fit (workgroups()): more than eight tiles that are no multiple of
 // eight count as two rounds here and run as one.  Timed again over 9600 shapes of 32 to 36864 lines, launches replayed from a graph, the
 // choices below lose against the faster pass of each shape, on average: without codes 0.2 to 4 % at k = 32 and 2 to 6 at 64 (most with groups
 // of 32 and 64: prepared / general .92 in bfloat16, 1.05 in float32 for 65 to 256 tiles of the general kernel, .77 and .90 up to 512); pairs 0 to 4, in float32 at k = 64
@@ -203,9 +204,8 @@ bool v2_rounds(int K, int G, int64_t nlines, int64_t naxis, int share, int64_t* 
 // Whether the loss pass over prepared weights is the faster one (blocks of 128: always; blocks of 32 and 64: not where there
 // are few of its tiles).  Both kernels take as long as their rounds of workgroups do: one a compute unit and tiles of 256 lines x
 // 128 indices here, two a unit and 128 lines x one segment of max(K, G) indices there.  Losses alone, the general kernel's
-// time / this one's in us: 1152 x 512 (two rounds here, one there) at k = 32, groups of 32 11 / 22 and at k = 64, groups of
-// 64 13 / 20; 2304 x 2304 (two and two) at k = 32, groups of 32 18 / 22, k = 64, groups of 64 21 / 21, of 128 31 / 20; 2304 x 9216
-// at k = 32, groups of 32 (three and eleven) 42 / 42; 36864 x 4608 (21 and 81) 270 / 177, at k = 64 (and 41) 293 / 178.
+// time / this one's in us, at k = 64: 1152 x 512 (two rounds here, one there), groups of 64 13 / 20; 2304 x 2304 (two and two),
+// groups of 64 21 / 21, of 128 31 / 20; 36864 x 4608 (21 and 41) 293 / 178.
 bool v2_pays(const cafeq_mat* W, int K, const GroupPlan& gp, int64_t nlines, int64_t naxis, bool out, bool along_rows) {
   if (K == 128) return true;
   int64_t here, there;
@@ -216,12 +216,17 @@ bool v2_pays(const cafeq_mat* W, int K, const GroupPlan& gp, int64_t nlines, int
   switch (std::max(K, gp.Gk)) {
     case 128: return there >= 1 + int(more || (out && along_rows && !bf16));
     case 64: return there >= 2 + int(more && (K == 32 || !bf16 || out || nlines < 512));
-    // (groups of 32: the vector phase's time is in the groups, of which neither kernel has fewer)
+    // (k = 32 with groups of 32, a line drawn against the general kernel and not redrawn against core32.hip, which takes the other side's place:
+    // it is the faster one further up, to about 50 M weights in float32 and 10 to 20 M in bfloat16, with codes further still.  core32 / this one, us, by
+    // replayed graphs, in bfloat16 behind the semicolon: losses 1152 x 512 7.8 / 19; 7.9 / 17, 2304 x 2304 15 / 22; 15 / 18.5, 2304 x 9216 36 / 45; 35.7 / 37.3,
+    // 9216 x 2304 33 / 42; 33 / 33.6, 3584 x 14336 69 / 67; 67 / 56, 36864 x 4608 214 / 180; 216 / 134; with codes along columns 2304 x 9216 42 / 59; 41 / 72,
+    // 3584 x 14336 109 / 108; 79 / 128, 36864 x 4608 411 / 279; 426 / 426, along rows in bfloat16 39 / 82, 79 / 144 and 251 / 399)
     default: return there >= (bf16 && !(out && along_rows) ? 3 + int(more) : 3 * here + 1);
   }
 }
-// The same for a pair whose members share a launch, half of the chip each, against two launches: 600 x 512 at k = 32, groups
-// of 32 18 / 24, 3584 x 512 21 / 20, 4608 x 1024 35 / 28; groups of 64 256 x 2304 22 / 28, else from 22 / 22 down.
+// The same for a pair whose members share a launch, half of the chip each, against two launches: at k = 32, groups of 32 (core32.hip the other
+// side) 600 x 512 13.5 / 20.2, 3584 x 512 17.2 / 20.7, 4608 x 1024 30.4 / 28.7, 3584 x 4096 50 / 43, 3584 x 14336 153 / 121, in bfloat16 13.8 / 18.5, 17.3 / 18.8,
+// 27.7 / 24.3, 49 / 36 and 139 / 90; groups of 64 256 x 2304 22 / 28, else from 22 / 22 down.
 bool v2_pair_pays(const cafeq_mat* A, const cafeq_mat* B, int K, const GroupPlan& gp) {
   if (std::max(K, gp.Gk) == 128) return true;
   int64_t ha, ta, hb, tb;
@@ -254,7 +259,7 @@ bool gather_possible(int K, const GroupPlan& gp, bool lines) { return lines && (
 //   36864 x 4608 349 / 479.  Pairs in float32 from 1 M weights a member on (1000 x 4096 80 / 57, 3584 x 14336 270 / 208; below either way does:
 //   136 x 512 22.4 / 22.2, 1024 x 512 24.8 / 23.3, 1152 x 1024 27.5 / 27.5); in bfloat16 by records (1000 x 4096 42.5 / 38.5, 3584 x 14336 224 / 233, with
 //   the inverse 2304 x 9216 116 / 125, 4608 x 36864 648 / 809).
-//   k = 32 and 64 in one matrix, where the loss pass forms the gradient on its way: 14336 x 1024 (k = 32) 68 / 85, 36864 x 2304
+//   Other groups at k = 32 and 64 in one matrix, where the general loss pass forms the gradient on its way: 14336 x 1024 (k = 32) 68 / 85, 36864 x 2304
 //   308 / 259, 2304 x 4608 58 / 55, 1147 x 9216 63 / 61, 4.2 M weights 33 / 40; over prepared weights, whose loss pass only records, with groups of 128
 //   (bfloat16: of 64) 36864 x 1024 113 / 107, 9216 x 1024 57 / 50.  On the min/max grid, a pass of its own either way: groups of 32 1147 x 512
 //   31 / 25, 4608 x 256 33 / 37, 2304 x 9216 83 / 86, 36864 x 1024 120 / 184; 64 36864 x 1024 118 / 140, 14336 x 512 66 / 61.
@@ -1173,7 +1178,9 @@ static int single_impl(const cafeq_mat* W, const cafeq_xform* x, const cafeq_qua
   // Gradient descent at two bits takes steps nine times those at three and amplifies what rounds: of 60 loops of eight steps 22
   // end more than 1e-5 (and up to 1) elsewhere by records than by the product, 10 where the weights move by half a unit in
   // their last place, although the gradient itself is ten times closer to float64's.  These loops, with or without a regulariser and
-  // whatever the block, keep the product, and with it the transforms they have always ended at; evaluations do not depend on the bits.
+  // whatever the block, take their sums over the lines from the product (blocks of 32 and 64 also on the loss pass' way), so that where one ends
+  // does not turn on the sizes from which records are the faster way.  It does turn on every other rounding of an iteration (the
+  // gradient's third part at k = 32 with groups of 32, the chain through the inverse at k = 128).  Evaluations do not depend on the bits.
   bool v2 = v2_eligible(W, K, gp, cfg, !col && (codes || scales)) && v2_pays(W, K, gp, nlines, naxis, codes || scales, !col);
   const bool gather = gather_possible(K, gp, has_lines(W, cfg->axis)) && gather_pays(W, K, gp, nlines, naxis, asym, false, v2, !col) &&
                       !(loop && cfg->bits == 2);
